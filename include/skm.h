@@ -335,6 +335,10 @@ int32_t skm_dprime_adjust(int32_t d, int32_t dprime, double prune_frac, float lo
  *   max_tiles  0 = default, > 0 = tiles per launch (a tall product is cut into bands of row tiles) */
 void skm_debug_gemm_config(int32_t tile256, int32_t panel_cols, int64_t max_tiles);
 
+/* Calls that were lent no workspace keep the device block they worked in for the next such call (at most 4 GiB over all
+ * devices and threads); this gives what is held back to the device.  Safe at any time, from any thread. */
+void skm_release_memory(void);
+
 const char *skm_strerror(int rc);
 const char *skm_last_error(void); /* text of the last failure on this thread */
 const char *skm_version(void);

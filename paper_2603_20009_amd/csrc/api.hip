@@ -39,6 +39,84 @@ int fail_hip(hipError_t e, const char *where) {
     if (e__ != hipSuccess) return fail_hip(e__, #expr);           \
   } while (0)
 
+// Device blocks that calls without a lent workspace have finished with, for the next such call: hipMalloc and hipFree of a
+// few buffers cost a step call 0.2 to 0.3 ms, several times its kernels, and hipFree of gigabytes 10 ms for each.  Every
+// call waits for its stream before it gives a block back, so the next one may use it on any stream; a call that fails
+// frees its block instead.  Bounded (kMost bytes over all devices), safe between threads, emptied by
+// skm_release_memory() and by a hipMalloc of the library that fails.
+struct BlockCache {
+  struct Block {
+    void *p;
+    size_t bytes;
+    int dev;
+  };
+  static constexpr size_t kMost = (size_t)4 << 30;
+  std::mutex mu;
+  std::vector<Block> idle;
+  size_t held = 0;
+  static int device() {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    return dev;
+  }
+  // the smallest idle block of the current device that holds `bytes`
+  void *take(size_t bytes, size_t *cap) {
+    const int dev = device();
+    std::lock_guard<std::mutex> lock(mu);
+    size_t best = idle.size();
+    for (size_t i = 0; i < idle.size(); ++i)
+      if (idle[i].dev == dev && idle[i].bytes >= bytes && (best == idle.size() || idle[i].bytes < idle[best].bytes)) best = i;
+    if (best == idle.size()) return nullptr;
+    void *p = idle[best].p;
+    *cap = idle[best].bytes;
+    held -= idle[best].bytes;
+    idle.erase(idle.begin() + (std::ptrdiff_t)best);
+    return p;
+  }
+  // keeps the block if the bound allows it, dropping older ones for it; frees it otherwise
+  void give(void *p, size_t bytes) {
+    std::vector<Block> drop;
+    {
+      const int dev = device();
+      std::lock_guard<std::mutex> lock(mu);
+      if (bytes <= kMost) {
+        while (held + bytes > kMost || idle.size() >= 16) {
+          drop.push_back(idle.front());
+          held -= idle.front().bytes;
+          idle.erase(idle.begin());
+        }
+        idle.push_back({p, bytes, dev});
+        held += bytes;
+        p = nullptr;
+      }
+    }
+    for (const Block &b : drop) (void)hipFree(b.p);
+    if (p) (void)hipFree(p);
+  }
+  void release() {
+    std::vector<Block> drop;
+    {
+      std::lock_guard<std::mutex> lock(mu);
+      drop.swap(idle);
+      held = 0;
+    }
+    for (const Block &b : drop) (void)hipFree(b.p);
+  }
+};
+BlockCache &block_cache() {
+  static BlockCache *c = new BlockCache;   // (never destroyed: the process's end takes the blocks)
+  return *c;
+}
+hipError_t device_malloc(void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    block_cache().release();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 // device allocations released when the call ends, whichever way it ends
 // A preallocated slab that Pools of nested calls carve their buffers from (the hierarchical fit runs hundreds of small
 // fits; a hipMalloc per buffer would dominate them).  A Pool constructed while an arena is current takes memory from it
@@ -48,12 +126,18 @@ struct Arena {
   size_t cap = 0, off = 0;
   bool owned = true;     // false: the caller's memory (params->workspace)
   bool strict = false;   // true: what does not fit is an error, never a hipMalloc
+  bool keep = false;     // the call has waited for its stream: an owned block goes to the cache
   ~Arena() {
-    if (base && owned) (void)hipFree(base);
+    if (!base || !owned) return;
+    if (keep) block_cache().give(base, cap);
+    else (void)hipFree(base);
   }
   hipError_t init(size_t bytes) {
+    bytes = (bytes + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
+    base = static_cast<char *>(block_cache().take(bytes, &cap));
+    if (base) return hipSuccess;
     cap = bytes;
-    return hipMalloc(reinterpret_cast<void **>(&base), bytes);
+    return device_malloc(reinterpret_cast<void **>(&base), bytes);
   }
   void lend(void *mem, size_t bytes) {
     base = static_cast<char *>(mem);
@@ -100,7 +184,7 @@ struct Pool {
         return hipErrorOutOfMemory;
       }
     }
-    hipError_t e = hipMalloc(&p, bytes);
+    hipError_t e = device_malloc(&p, bytes);
     if (e != hipSuccess) {
       *out = nullptr;
       return e;
@@ -142,6 +226,26 @@ struct PinnedCache {
 };
 thread_local PinnedCache tl_pinned;
 
+// one page-locked word that a kernel writes and the host reads once it has waited for the stream
+struct PinnedWord {
+  volatile unsigned int *host = nullptr;
+  unsigned int *dev = nullptr;
+  void *block = nullptr;
+  size_t cap = 0;
+  PinnedWord() {
+    block = tl_pinned.take(sizeof(unsigned int), &cap);
+    void *dv = nullptr;
+    if (!block || hipHostGetDevicePointer(&dv, block, 0) != hipSuccess) return;
+    host = static_cast<volatile unsigned int *>(block);
+    dev = static_cast<unsigned int *>(dv);
+  }
+  ~PinnedWord() {
+    if (block) tl_pinned.give(block, cap);
+  }
+  PinnedWord(const PinnedWord &) = delete;
+  PinnedWord &operator=(const PinnedWord &) = delete;
+};
+
 struct Events {
   std::vector<hipEvent_t> ev;
   ~Events() {
@@ -155,39 +259,43 @@ struct Events {
   }
 };
 
-// Records (stage, event) marks on the stream; after a synchronisation the time between two
-// consecutive marks is charged to the stage of the later mark.
+// Records (stage, event) marks on the stream; once the stream has been synchronised the time between two consecutive
+// marks of a step is charged to the stage of the later mark.  Nothing waits for a step's marks: a fit reads those of all
+// its steps at its end.
 enum Stage { ST_NONE = 0, ST_TAU, ST_GEMM, ST_PRUNE, ST_UPDATE, ST_ETR, ST_COUNT };
 struct StageTimer {
   Events pool;
   std::vector<std::pair<int, hipEvent_t>> marks;
-  size_t used = 0;
+  std::vector<size_t> first;   // first mark of every step
   hipStream_t st;
   bool on;
   StageTimer(hipStream_t s, bool enable) : st(s), on(enable) {}
+  void begin_step() { first.push_back(marks.size()); }
   void mark(int stage) {
     if (!on) return;
-    hipEvent_t e;
-    if (used < pool.ev.size()) e = pool.ev[used];
-    else e = pool.next();
+    const size_t used = marks.size();
+    hipEvent_t e = used < pool.ev.size() ? pool.ev[used] : pool.next();
     if (!e) return;
-    ++used;
     (void)hipEventRecord(e, st);
     marks.push_back({stage, e});
   }
-  // call after the stream is synchronised
-  void collect(float ms[ST_COUNT], float *total) {
+  // times of step q (call after the stream is synchronised)
+  void collect(size_t q, float ms[ST_COUNT], float *total) const {
     for (int s = 0; s < ST_COUNT; ++s) ms[s] = 0.f;
     *total = 0.f;
-    for (size_t i = 1; i < marks.size(); ++i) {
+    if (q >= first.size()) return;
+    const size_t end = q + 1 < first.size() ? first[q + 1] : marks.size();
+    for (size_t i = first[q] + 1; i < end; ++i) {
       float t = 0.f;
       if (hipEventElapsedTime(&t, marks[i - 1].second, marks[i].second) == hipSuccess) {
         ms[marks[i].first] += t;
         *total += t;
       }
     }
+  }
+  void reset() {   // the events are used again
     marks.clear();
-    used = 0;
+    first.clear();
   }
 };
 
@@ -372,12 +480,11 @@ struct Ctx {
   int64_t pair_cap = 0, sub_cap = 0, chunk_rows = 0;
   int32_t nchunks = 0;
   unsigned int emit_max = 0;         // a tile with at most this many alive pairs goes to the gather kernel
-  unsigned int *counters = nullptr;  // per chunk the fill counters of the sub-lists, then [1] error flag (overflow / unset point)
-  size_t ncounters = 0;              // words in `counters` before the flag
+  unsigned int *counters = nullptr;  // per chunk the fill counters of the sub-lists, then the tile counters
+  size_t ncounters = 0;              // words in `counters`
   float *ratio_dev = nullptr;        // [kMaxBlocks + 1]
-  float *ratio_host = nullptr;       // [kMaxBlocks + 1] page-locked staging for ratio_dev (behind the read-back block)
   unsigned long long *scal = nullptr;  // [SC_COUNT]
-  double *obj_partial = nullptr, *obj = nullptr;
+  double *obj_partial = nullptr;
   UpdateWs up{};
   IncUpdateWs inc{};                 // workspace of the incremental update
   double *S = nullptr;               // [k][ds] cluster sums of the last update (fp64), valid once S_valid
@@ -398,51 +505,72 @@ struct Ctx {
   unsigned int *amax = nullptr;      // [AM_COUNT] magnitude bounds of the GEMM operands
   enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8 };
 
-  // what a step reports (page-locked, see PinnedCache): the step scalars, the objective, the error flag, the
-  // cluster sizes
+  // What a step reports: the finalize kernel writes it straight into this page-locked block (see PinnedCache), so the
+  // host waits for the stream once per step and copies nothing.  Behind it lies room for the initial row numbers.
   void *rb_block = nullptr;
   size_t rb_cap = 0;
   Ctx() = default;
   Ctx(const Ctx &) = delete;
   Ctx &operator=(const Ctx &) = delete;
   ~Ctx() {
+    if (pending) (void)hipStreamSynchronize(st);      // (an error on the way: the block is not reused under a kernel)
     if (rb_block) tl_pinned.give(rb_block, rb_cap);   // a context lives and dies on one thread
   }
-  unsigned long long *rb_scal = nullptr;   // [SC_COUNT * kStatReplicas]
-  double *rb_obj = nullptr;
-  unsigned int *rb_flag = nullptr;
-  int32_t *rb_cnt = nullptr;               // [k]
-  bool rb_cnt_valid = false;               // rb_cnt holds the sizes of c.assign's clusters
-  char *zblock = nullptr;                  // device: counters | flag | scal | obj | up.cnt (see alloc_common)
-  size_t zbytes = 0, rb_off = 0;           // the part from rb_off on is what comes back to the host
-  // start of a step: everything it counts into is cleared
-  int clear_step_block() {
-    HIPCHK(hipMemsetAsync(zblock, 0, zbytes, st));
-    return SKM_OK;
-  }
-  // end of a step: flag, scalars, objective and cluster sizes in one copy; the caller waits on the stream
-  int fetch_step_block() {
-    HIPCHK(hipMemcpyAsync(rb_block, zblock + rb_off, zbytes - rb_off, hipMemcpyDeviceToHost, st));
-    return SKM_OK;
-  }
-  int alloc_readback(size_t o_scal, size_t o_obj, size_t o_cnt) {
-    const size_t o_ratio = (zbytes - rb_off + 15) & ~(size_t)15;
-    if (!rb_block) rb_block = tl_pinned.take(o_ratio + sizeof(float) * ((size_t)kMaxBlocks + 1), &rb_cap);
+  bool pending = false;                    // a kernel that writes the report has been launched and not been waited for
+  StepReport *report = nullptr;            // host address ...
+  StepReport *report_dev = nullptr;        // ... and the same block as kernels see it
+  int64_t *idx_host = nullptr;             // [k], page-locked, for at most kPinnedIdx clusters (NULL above)
+  const int64_t *idx_dev_view = nullptr;
+  bool sizes_known = false;                // report holds the empty clusters and the largest size of c.assign's clusters
+  const int32_t *prev_in = nullptr;        // the caller's labels, checked and copied to prev when the step starts
+  char *zblock = nullptr;                  // device: counters | flag | done | scal | cluster sizes (see alloc_common)
+  size_t zbytes = 0;
+  unsigned int *flag = nullptr, *done = nullptr;
+  int32_t *change_start = nullptr;         // [finalize_blocks(n)]
+  static constexpr int32_t kPinnedIdx = 65536;
+  int alloc_readback() {
+    const size_t off_idx = (sizeof(StepReport) + 63) & ~(size_t)63;
+    const size_t want = off_idx + (k <= kPinnedIdx ? (size_t)k * sizeof(int64_t) : 0);
+    rb_block = tl_pinned.take(want, &rb_cap);
     char *h = static_cast<char *>(rb_block);
-    if (!h) return fail(SKM_EHIP, "hipHostMalloc failed for the step read-back block");
-    rb_flag = reinterpret_cast<unsigned int *>(h);
-    rb_scal = reinterpret_cast<unsigned long long *>(h + o_scal);
-    rb_obj = reinterpret_cast<double *>(h + o_obj);
-    rb_cnt = reinterpret_cast<int32_t *>(h + o_cnt);
-    ratio_host = reinterpret_cast<float *>(h + o_ratio);
+    if (!h) return fail(SKM_EHIP, "hipHostMalloc failed for the step report");
+    void *dv = nullptr;
+    HIPCHK(hipHostGetDevicePointer(&dv, h, 0));
+    report = reinterpret_cast<StepReport *>(h);
+    report_dev = static_cast<StepReport *>(dv);
+    if (k <= kPinnedIdx) {
+      idx_host = reinterpret_cast<int64_t *>(h + off_idx);
+      idx_dev_view = reinterpret_cast<const int64_t *>(static_cast<char *>(dv) + off_idx);
+    }
     return SKM_OK;
   }
+  // the last kernel of a step, and the wait for it
+  int close_step() {
+    FinalizeArgs f{best, prev_counts ? prev : nullptr, n, assign, dist, up.cnt, k, flag};
+    f.done = done; f.obj_partial = obj_partial; f.change_start = change_start; f.scal = scal; f.report = report_dev;
+    HIPCHK(launch_finalize_assign(f, st));
+    pending = true;
+    return SKM_OK;
+  }
+  int wait_step() {
+    HIPCHK(hipStreamSynchronize(st));
+    pending = false;
+    sizes_known = true;
+    return SKM_OK;
+  }
+  bool prev_counts = true;                 // changed points are counted against prev (false in the exact step)
 
   int alloc_bounds() {
     HIPCHK(pool.get(&amax, (size_t)AM_COUNT));
+    if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT, 0u, st));
     return SKM_OK;
   }
   int measure_xr() { return measure_absmax(Xr, ldx, n, ds, amax + AM_XR, st); }
+  // the words that a step counts into, cleared by the pass over the centroids that starts it
+  void clear_with(CentroidPrep &a) const {
+    a.clear = reinterpret_cast<unsigned int *>(zblock);
+    a.clear_words = (int64_t)(zbytes / sizeof(unsigned int));
+  }
   bool y_amax_valid = false;   // amax[AM_Y] bounds the current Y (the update writes it; other changes of Y clear this)
   int measure_y() {
     if (y_amax_valid) return SKM_OK;
@@ -504,28 +632,27 @@ struct Ctx {
       HIPCHK(pool.get(&scr_cols, (size_t)tiles_chunk * 128));
       HIPCHK(pool.get(&scr_tile_rt, (size_t)tiles_chunk));
     }
-    // Everything a step clears at its start and reports at its end is one block: counters | flag | step scalars |
-    // objective | cluster sizes.  One memset, and one copy (from the flag on) into the page-locked mirror.
+    // everything a step clears at its start is one block: counters | flag | ticket | step scalars | cluster sizes
     {
       const size_t nscal = (size_t)SC_COUNT * kStatReplicas;
       const size_t off_flag = ncounters * sizeof(unsigned int);
-      const size_t off_scal = (off_flag + sizeof(unsigned int) + 7) & ~(size_t)7;
-      const size_t off_obj = off_scal + nscal * sizeof(unsigned long long);
-      const size_t off_cnt = off_obj + sizeof(double);
+      const size_t off_scal = (off_flag + 2 * sizeof(unsigned int) + 7) & ~(size_t)7;
+      const size_t off_cnt = off_scal + nscal * sizeof(unsigned long long);
       zbytes = off_cnt + sizeof(int32_t) * (size_t)k;
       HIPCHK(pool.get(&zblock, zbytes));
-      rb_off = off_flag;
       if (zblock) {
         counters = reinterpret_cast<unsigned int *>(zblock);
+        flag = reinterpret_cast<unsigned int *>(zblock + off_flag);
+        done = flag + 1;
         scal = reinterpret_cast<unsigned long long *>(zblock + off_scal);
-        obj = reinterpret_cast<double *>(zblock + off_obj);
         up.cnt = reinterpret_cast<int32_t *>(zblock + off_cnt);
       }
       if (!pool.count_only)   // (a size query touches no device and no page-locked memory)
-        if (int rc = alloc_readback(off_scal - off_flag, off_obj - off_flag, off_cnt - off_flag)) return rc;
+        if (int rc = alloc_readback()) return rc;
     }
     HIPCHK(pool.get(&ratio_dev, (size_t)kMaxBlocks + 1));
     HIPCHK(pool.get(&obj_partial, (size_t)(n + 1023) / 1024));   // at least finalize_blocks(m) for every m <= n
+    HIPCHK(pool.get(&change_start, (size_t)(n + 1023) / 1024));
     if (need_update) {
       HIPCHK(pool.get(&up.off, (size_t)k + 1));
       HIPCHK(pool.get(&up.cursor, (size_t)k));
@@ -545,7 +672,6 @@ struct Ctx {
       HIPCHK(pool.get(&inc.off, (size_t)k + 1));
       HIPCHK(pool.get(&inc.cursor, (size_t)k));
       HIPCHK(pool.get(&inc.segoff, (size_t)k + 1));
-      HIPCHK(pool.get(&inc.counter, 1));
       HIPCHK(pool.get(&inc.partial, (size_t)inc.max_segments * ds));
     }
     return SKM_OK;
@@ -597,6 +723,7 @@ struct CallArena {
   ~CallArena() {
     if (on) tl_arena = nullptr;
   }
+  void finished() { arena.keep = true; }   // the call has waited for its stream
   CallArena(const CallArena &) = delete;
   CallArena &operator=(const CallArena &) = delete;
 };
@@ -681,7 +808,8 @@ struct StepStats {
 // c.best[i] = packed (squared distance over dims [0, K), centroid) of the centroid nearest to point i on those dims,
 // exact (direct form, lowest index on ties): the one-product multiply over K dims lists the candidates, the gather
 // kernel takes their distances.  K = ds: the nearest centroid; K = d': the incumbent of a step that comes without one.
-// Clobbers ynorm, Ypdx, Ys / Yh, ratio_dev, tau; sets bit 0 of the step's flag word if the candidate list overflowed.
+// Clears the step's counters; clobbers ynorm, Ypdx, Ys / Yh, ratio_dev, tau; sets bit 0 of the step's flag word if the
+// candidate list overflowed.
 int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
   const int32_t nbK = (K + kBlockDims - 1) / kBlockDims;
   if (nbK > kMaxBlocks) return fail(SKM_EINTERNAL, "too many blocks");
@@ -695,15 +823,19 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
   }
   // ||y[0 : K)||^2 and the block-major copy of the first K dimensions, zero filled behind them (the gather kernel
   // starts every pair at dimension 0 and is told that rows end at K)
-  HIPCHK(launch_prep_centroids(c.Y, c.ds, c.k, K, K, c.ynorm, 0, nbK, c.Ypdx, c.st));
   if (int rc = c.measure_y()) return rc;
-  HIPCHK(launch_split_rows(c.Y, c.ds, c.k, c.ds, c.amax + Ctx::AM_Y, c.Ys, c.st, c.Yh));
+  float ratio[kMaxBlocks + 1];
+  for (int m = 0; m <= nbK; ++m) ratio[m] = 1.f;   // nothing is dropped on the way
+  CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
+  cp.ynorm = c.ynorm; cp.dn = K;
+  cp.dprime = 0; cp.nb = nbK; cp.Ypdx = c.Ypdx; cp.pdx_cols = K;
+  cp.Ys = c.Ys; cp.Yh = c.Yh; cp.y_absmax = c.amax + Ctx::AM_Y;
+  cp.ratio_out = c.ratio_dev;
+  c.clear_with(cp);
+  HIPCHK(launch_prep_centroids(cp, c.st, ratio, nbK + 1));
   HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   unsigned int *rowmin = reinterpret_cast<unsigned int *>(c.tau);   // (no thresholds while this runs)
   HIPCHK(launch_fill_u32(rowmin, c.n, 0xffffffffu, c.st));
-  float *ratio = c.ratio_host;
-  for (int m = 0; m <= nbK; ++m) ratio[m] = 1.f;   // nothing is dropped on the way
-  HIPCHK(hipMemcpyAsync(c.ratio_dev, ratio, sizeof(float) * ((size_t)nbK + 1), hipMemcpyHostToDevice, c.st));
   if (tm) tm->mark(ST_TAU);
   for (int32_t ch = 0; ch < c.nchunks; ++ch) {
     const int64_t r0 = (int64_t)ch * c.chunk_rows;
@@ -722,7 +854,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
     sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt;
     sl.scal = c.scal;
     sl.exact = 1; sl.rowmin = rowmin; sl.pairs = c.pairs; sl.pair_count = fill; sl.sub_capacity = (unsigned int)c.sub_cap;
-    sl.overflow = c.counters + c.ncounters;
+    sl.overflow = c.flag;
     HIPCHK(launch_screen(sl, c.st));
     PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, 0, K, nbK, c.ratio_dev,
                  c.best, c.scal, 0};
@@ -733,26 +865,20 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
 
 int step_exact_filtered(Ctx &c, StageTimer &tm, StepStats &ss) {
   tm.mark(ST_NONE);
-  if (int rc = c.clear_step_block()) return rc;
   if (int rc = filtered_nearest(c, c.ds, &tm)) return rc;
   tm.mark(ST_GEMM);
   // the packed minima already hold the direct distances
-  HIPCHK(launch_finalize_assign(c.best, nullptr, c.n, c.assign, c.dist, c.up.cnt, c.k, c.obj_partial, nullptr,
-                                c.counters + c.ncounters, c.st));
-  HIPCHK(launch_sum_partials(c.obj_partial, finalize_blocks(c.n), c.obj, c.st));
+  c.prev_counts = false;
+  int rc = c.close_step();
+  c.prev_counts = true;
+  if (rc) return rc;
   tm.mark(ST_TAU);
-  if (int rc = c.fetch_step_block()) return rc;
-  HIPCHK(hipStreamSynchronize(c.st));
-  c.rb_cnt_valid = true;
-  const size_t nscal = (size_t)SC_COUNT * kStatReplicas;
+  if ((rc = c.wait_step())) return rc;
   ss = StepStats();
-  for (int r = 0; r < kStatReplicas; ++r) {
-    ss.gather_pair_blocks += (int64_t)c.rb_scal[(size_t)r * SC_COUNT + SC_GATHER_PB];
-    ss.gather_pairs += (int64_t)c.rb_scal[(size_t)r * SC_COUNT + SC_GATHER_PAIRS];
-    ss.screen_dims += (int64_t)c.rb_scal[(size_t)r * SC_COUNT + SC_SCREEN_DIMS];
-  }
-  (void)nscal;
-  ss.objective = *c.rb_obj;
+  ss.gather_pair_blocks = (int64_t)c.report->scal[SC_GATHER_PB];
+  ss.gather_pairs = (int64_t)c.report->scal[SC_GATHER_PAIRS];
+  ss.screen_dims = (int64_t)c.report->scal[SC_SCREEN_DIMS];
+  ss.objective = c.report->objective;
   ss.dprime = c.d;
   ss.changed = c.n;
   return SKM_OK;
@@ -763,34 +889,37 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   // many centroids: the low-precision filter first, exact distances for the few candidates it leaves
   if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
     if (int rc = step_exact_filtered(c, tm, ss)) return rc;
-    if ((*c.rb_flag & 1u) == 0) {
-      if (*c.rb_flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
+    if ((c.report->flag & 1u) == 0) {
+      if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
       return SKM_OK;
     }
     c.exact_filter_off = true;   // the candidate list overflowed (never with the default capacities): the full GEMM instead
   }
   tm.mark(ST_NONE);
-  if (int rc = c.clear_step_block()) return rc;
-  HIPCHK(launch_prep_centroids(c.Y, c.ds, c.k, c.ds, c.ds, c.ynorm, 0, 0, nullptr, c.st));
-  HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   if (int rc = c.measure_y()) return rc;
+  CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
+  cp.ynorm = c.ynorm; cp.dn = c.ds;
+  cp.Ys = c.Ys; cp.y_absmax = c.amax + Ctx::AM_Y;
+  c.clear_with(cp);
+  HIPCHK(launch_prep_centroids(cp, c.st));
+  HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   GemmOperands g{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, c.ds};
   g.a_absmax = c.amax + Ctx::AM_XR; g.b_absmax = c.amax + Ctx::AM_Y;
-  g.b_split = c.Ys;   // every pruned step remakes it: free here
+  g.b_presplit = c.Ys; g.ldbs = c.ds + 32;
   HIPCHK(gemm_argmin(g, c.ynorm, c.best, c.st));
   tm.mark(ST_GEMM);
   // winners -> direct squared distances (also the objective of this step)
-  HIPCHK(launch_finalize_assign(c.best, nullptr, c.n, c.assign, nullptr, nullptr, c.k, nullptr, nullptr, c.counters + c.ncounters, c.st));
-  HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.assign, nullptr, c.best, c.st));
-  HIPCHK(launch_finalize_assign(c.best, nullptr, c.n, c.assign, c.dist, c.up.cnt, c.k, c.obj_partial, nullptr, nullptr, c.st));
-  HIPCHK(launch_sum_partials(c.obj_partial, finalize_blocks(c.n), c.obj, c.st));
+  HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, nullptr, nullptr, c.best, c.st, nullptr, nullptr, nullptr,
+                         nullptr, nullptr, nullptr, nullptr, c.flag));
+  c.prev_counts = false;
+  int rc = c.close_step();
+  c.prev_counts = true;
+  if (rc) return rc;
   tm.mark(ST_TAU);
-  if (int rc = c.fetch_step_block()) return rc;
-  HIPCHK(hipStreamSynchronize(c.st));
-  c.rb_cnt_valid = true;
-  if (*c.rb_flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
+  if ((rc = c.wait_step())) return rc;
+  if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
   ss = StepStats();
-  ss.objective = *c.rb_obj;
+  ss.objective = c.report->objective;
   ss.dprime = c.d;
   ss.changed = c.n;
   return SKM_OK;
@@ -807,31 +936,50 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   if (!have_prev && c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
     // many centroids: the nearest centroid on the first d' dimensions through the low-precision filter (a third of
     // the matrix work of the three-product GEMM below); if its candidate list overflows, that GEMM runs after all
-    if (int rc = c.clear_step_block()) return rc;
     if (int rc = filtered_nearest(c, dprime, &tm)) return rc;
-    HIPCHK(launch_finalize_assign(c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, nullptr, nullptr, c.counters + c.ncounters, c.st));
-    HIPCHK(hipMemcpyAsync(c.rb_flag, c.counters + c.ncounters, sizeof(unsigned int), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
-    if (*c.rb_flag == 0) found = true;
-    else if (*c.rb_flag & 1u) c.exact_filter_off = true;
+    c.pending = true;
+    HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, c.flag}, c.st));
+    HIPCHK(hipMemcpyAsync(&c.report->flag, c.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, c.st));
+    if (int rc = c.wait_step()) return rc;
+    c.sizes_known = false;
+    if (c.report->flag == 0) found = true;
+    else if (c.report->flag & 1u) c.exact_filter_off = true;
     else return fail(SKM_EINTERNAL, "a point was left without a centroid");
     tm.mark(ST_GEMM);
   }
-  HIPCHK(launch_prep_centroids(c.Y, c.ds, c.k, c.ds, dprime, c.ynorm, dprime, nb, c.Ypdx, c.st, c.ynp));
   if (int rc = c.measure_y()) return rc;
+  // Low-precision first filter: worth its pass over the front dimensions when most columns of a tile die at the
+  // first test.  The previous step's prune fraction predicts that from below (the centroids only get better): the
+  // step after one that cut half of the pairs cuts 85 to 99 % on the mixture workloads, and a wasted filter pass
+  // costs a tenth of the poorly pruned step it precedes.
+  const bool screen = c.colmask && nb > 0 &&
+                      (c.screen_mode > 0 || (c.screen_mode == 0 && c.last_prune_frac >= 0.50));
   // theta ratio at checkpoint m: t_m = min(d, d' + 64 m) dimensions seen
-  float *ratio = c.ratio_host;
+  float ratio[kMaxBlocks + 1];
   for (int m = 0; m <= nb; ++m) ratio[m] = (float)theta_ratio(c.d, std::min(c.d, dprime + kBlockDims * m), eps0);
-  HIPCHK(hipMemcpyAsync(c.ratio_dev, ratio, sizeof(float) * ((size_t)nb + 1), hipMemcpyHostToDevice, c.st));
-  if (int rc = c.clear_step_block()) return rc;
+  {
+    CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
+    cp.dprime = dprime; cp.nb = nb; cp.Ypdx = c.Ypdx; cp.ynp = c.ynp;
+    cp.Ys = c.Ys; cp.Yh = screen ? c.Yh : nullptr; cp.y_absmax = c.amax + Ctx::AM_Y;
+    cp.ratio_out = c.ratio_dev;
+    c.clear_with(cp);
+    HIPCHK(launch_prep_centroids(cp, c.st, ratio, nb + 1));
+  }
+  bool from_keys = false;   // the incumbents are the low halves of c.best
   if (!have_prev && !found) {
     HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
     g0.a_absmax = c.amax + Ctx::AM_XR; g0.b_absmax = c.amax + Ctx::AM_Y;
-    g0.b_split = c.Ys;   // rewritten for all dimensions below
-    HIPCHK(gemm_argmin(g0, c.ynorm, c.best, c.st));
-    HIPCHK(launch_finalize_assign(c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, nullptr, nullptr, c.counters + c.ncounters, c.st));
+    g0.b_presplit = c.Ys; g0.ldbs = c.ds + 32;
+    HIPCHK(gemm_argmin(g0, c.ynp, c.best, c.st));   // (row 0 of ynp: the norms over the first d' dimensions)
+    if (c.group_now) {
+      HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, c.flag}, c.st));
+    } else {
+      from_keys = true;   // the threshold pass unpacks them
+    }
     tm.mark(ST_GEMM);
+  } else if (have_prev && c.prev_in) {
+    HIPCHK(launch_copy_labels(c.prev_in, c.n, c.k, c.prev, c.flag, c.st));
   }
   // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
   // far less usefully than those of iteration 2)
@@ -841,10 +989,10 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     // (or were just given above), so that a row tile holds the points of one or two clusters and the first filter has
     // columns to drop.  One read-back of the group sizes decides whether the order is reproducible (see below).
     HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.st));
-    HIPCHK(hipMemcpyAsync(c.rb_cnt, c.grp_cnt, sizeof(int32_t) * (size_t)c.k, hipMemcpyDeviceToHost, c.st));
+    std::vector<int32_t> sizes((size_t)c.k);
+    HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * (size_t)c.k, hipMemcpyDeviceToHost, c.st));
     HIPCHK(hipStreamSynchronize(c.st));
-    c.max_cluster = *std::max_element(c.rb_cnt, c.rb_cnt + c.k);
-    c.rb_cnt_valid = false;
+    c.max_cluster = *std::max_element(sizes.begin(), sizes.end());
     regroup = true;
     c.group_now = false;
   }
@@ -875,19 +1023,12 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     c.permuted = true;
   } else {
     // the first pruned step of a context also writes the tables that depend on the points only
-    HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, c.best, c.st, c.xnp_valid ? nullptr : c.xnp,
-                           c.xnp_valid ? nullptr : c.Xs, c.amax + Ctx::AM_XR, nullptr, nullptr, nullptr,
-                           c.xnp_valid ? nullptr : c.Xh));
+    HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, from_keys ? nullptr : c.prev, c.tau, c.best, c.st,
+                           c.xnp_valid ? nullptr : c.xnp, c.xnp_valid ? nullptr : c.Xs, c.amax + Ctx::AM_XR, nullptr,
+                           nullptr, from_keys ? c.prev : nullptr, c.xnp_valid ? nullptr : c.Xh, c.flag));
   }
   c.order_fresh = false;
   c.xnp_valid = true;
-  // Low-precision first filter: worth its pass over the front dimensions when most columns of a tile die at the
-  // first test.  The previous step's prune fraction predicts that from below (the centroids only get better): the
-  // step after one that cut half of the pairs cuts 85 to 99 % on the mixture workloads, and a wasted filter pass
-  // costs a tenth of the poorly pruned step it precedes.
-  const bool screen = c.colmask && nb > 0 &&
-                      (c.screen_mode > 0 || (c.screen_mode == 0 && c.last_prune_frac >= 0.50));
-  HIPCHK(launch_split_rows(c.Y, c.ds, c.k, c.ds, c.amax + Ctx::AM_Y, c.Ys, c.st, screen ? c.Yh : nullptr));
   tm.mark(ST_TAU);
   for (int32_t ch = 0; ch < c.nchunks; ++ch) {
     const int64_t r0 = (int64_t)ch * c.chunk_rows;
@@ -902,7 +1043,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     unsigned int *fill = c.counters + (size_t)ch * kSubLists * kSubListStride;
     g.tile_counter = c.counters + ((size_t)c.nchunks * kSubLists + (size_t)ch * 8) * kSubListStride;
     g.pairs = c.pairs; g.pair_count = fill; g.sub_capacity = (unsigned int)c.sub_cap;
-    g.overflow = c.counters + c.ncounters; g.emit_max = c.emit_max;
+    g.overflow = c.flag; g.emit_max = c.emit_max;
     g.best = c.best; g.scal = c.scal; g.block_stats = c.block_stats ? 1 : 0;
     if (screen) {
       ScreenLaunch sl{};
@@ -930,20 +1071,14 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       tm.mark(ST_PRUNE);
     }
   }
-  HIPCHK(launch_finalize_assign(c.best, c.prev, c.n, c.assign, c.dist, c.up.cnt, c.k, c.obj_partial, c.scal + SC_CHANGED,
-                                nullptr, c.st));
-  HIPCHK(launch_sum_partials(c.obj_partial, finalize_blocks(c.n), c.obj, c.st));
+  if (int rc = c.close_step()) return rc;
   tm.mark(ST_TAU);
-  const size_t nscal = (size_t)SC_COUNT * kStatReplicas;
-  if (int rc = c.fetch_step_block()) return rc;
-  HIPCHK(hipStreamSynchronize(c.st));
-  c.rb_cnt_valid = true;
-  if (*c.rb_flag & 1u) return fail(SKM_EOVERFLOW, "the hand-over list of the dense tiles overflowed");
-  if (*c.rb_flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
-  std::vector<unsigned long long> scal_h(c.rb_scal, c.rb_scal + nscal);
-  const double obj = *c.rb_obj;
-  for (int r = 1; r < kStatReplicas; ++r)   // fold the replicas into the first
-    for (int q = 0; q < SC_COUNT; ++q) scal_h[(size_t)q] += scal_h[(size_t)r * SC_COUNT + q];
+  if (int rc = c.wait_step()) return rc;
+  const unsigned int step_flag = c.report->flag;
+  if (step_flag & 4u) return fail(SKM_EINVAL, "assignment label outside [0, k)");
+  if (step_flag & 1u) return fail(SKM_EOVERFLOW, "the hand-over list of the dense tiles overflowed");
+  if (step_flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
+  const unsigned long long *scal_h = c.report->scal;
   ss = StepStats();
   ss.survivors = (int64_t)scal_h[SC_SURVIVORS];
   ss.completed = (int64_t)scal_h[SC_COMPLETED];
@@ -957,7 +1092,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   c.last_prune_frac = c.k > 1 ? 1.0 - (double)ss.survivors / ((double)c.n * (double)(c.k - 1)) : -1.0;
   ++c.pruned_steps;
   for (int m = 0; m < std::min<int>(nb, SKM_MAX_BLOCKS); ++m) ss.enter[m] = (int64_t)scal_h[SC_ENTER + (size_t)m];
-  ss.objective = obj;
+  ss.objective = c.report->objective;
   ss.dprime = dprime;
   ss.nblocks = nb;
   ss.pruned = true;
@@ -982,10 +1117,11 @@ int step_update(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t
     }
   } else if (!full && c.S_valid && 2 * changed <= c.inc.capacity - 2) {
     ++c.inc_updates;
-    HIPCHK(launch_update_incremental(c.Xr, c.ldx, c.n, c.ds, c.assign, c.prev, changed, c.k, c.up, c.inc, c.S, c.Y, c.ds,
-                                     c.st, c.amax + Ctx::AM_Y));
+    HIPCHK(launch_update_incremental(c.Xr, c.ldx, c.n, c.ds, c.assign, c.prev, changed, c.change_start, c.k, c.up, c.inc,
+                                     c.S, c.Y, c.ds, c.st, c.amax + Ctx::AM_Y));
   } else {
-    HIPCHK(launch_update(c.Xr, c.ldx, c.n, c.ds, c.assign, c.k, c.up, c.Y, c.ds, c.st, c.S, c.amax + Ctx::AM_Y));
+    HIPCHK(launch_update(c.Xr, c.ldx, c.n, c.ds, c.assign, c.k, c.up, c.Y, c.ds, c.st, c.S, c.amax + Ctx::AM_Y, 0,
+                         c.sizes_known ? c.report->largest : -1));
     c.S_valid = true;
     fresh = true;
   }
@@ -994,25 +1130,25 @@ int step_update(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t
   return split_empty(c, tm, split_rng, split_eps, nempty_out);
 }
 
-// Empty clusters after an update (Section 3.2): c.rb_cnt (if rb_cnt_valid) or c.up.cnt holds the cluster sizes.
+// Empty clusters after an update (Section 3.2): c.up.cnt holds the cluster sizes, and the step's report (if sizes_known)
+// how many of them are zero and the largest.
 int split_empty(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t *nempty_out) {
-  // the cluster sizes came back with the step's scalars; neither update changes them
-  if (!c.rb_cnt_valid) {
-    HIPCHK(hipMemcpyAsync(c.rb_cnt, c.up.cnt, sizeof(int32_t) * (size_t)c.k, hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
-  }
-  c.rb_cnt_valid = false;
-  std::vector<int32_t> cnt(c.rb_cnt, c.rb_cnt + c.k);
-  int64_t nempty = 0;
-  int32_t largest = 0;
-  for (int32_t v : cnt) {
-    nempty += (v == 0);
-    largest = std::max(largest, v);
-  }
-  c.max_cluster = largest;   // of the labels the update just used (a split below moves a centroid, no label)
-  *nempty_out = nempty;
+  // the report of the step has said whether there are any (neither update changes the sizes); the sizes themselves are
+  // fetched only then
+  *nempty_out = 0;
   c.split_last = false;
-  if (nempty > 0) {
+  std::vector<int32_t> cnt;
+  if (!c.sizes_known || c.report->nempty > 0) {
+    cnt.resize((size_t)c.k);
+    HIPCHK(hipMemcpyAsync(cnt.data(), c.up.cnt, sizeof(int32_t) * (size_t)c.k, hipMemcpyDeviceToHost, c.st));
+    HIPCHK(hipStreamSynchronize(c.st));
+    for (int32_t v : cnt) *nempty_out += (v == 0);
+    c.max_cluster = *std::max_element(cnt.begin(), cnt.end());
+  } else {
+    c.max_cluster = c.report->largest;   // of the labels the update just used (a split below moves a centroid, no label)
+  }
+  c.sizes_known = false;
+  if (*nempty_out > 0) {
     // empty clusters in increasing index; donor drawn with probability proportional to its size
     // among clusters of at least two points; the donor's points are shared floor(n/2) / rest.
     // The draw "first cluster whose cumulative weight exceeds r" runs on a Fenwick tree over the weights
@@ -1105,8 +1241,7 @@ int split_empty(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t
   return SKM_OK;
 }
 
-void fill_row(skm_trace_row &r, const StepStats &ss, int64_t n, int32_t k, int64_t nempty, double recall,
-              const float ms[ST_COUNT], float total) {
+void fill_row(skm_trace_row &r, const StepStats &ss, int64_t n, int32_t k, int64_t nempty, double recall) {
   std::memset(&r, 0, sizeof(r));
   r.objective = ss.objective;
   r.prune_frac = (ss.pruned && k > 1) ? 1.0 - (double)ss.survivors / ((double)n * (double)(k - 1)) : 0.0;
@@ -1124,6 +1259,11 @@ void fill_row(skm_trace_row &r, const StepStats &ss, int64_t n, int32_t k, int64
   r.dprime = ss.dprime;
   r.nblocks = ss.nblocks;
   for (int m = 0; m < SKM_MAX_BLOCKS; ++m) r.enter[m] = ss.enter[m];
+}
+// stage times of step q into its row (after the stream has been waited for)
+void fill_times(skm_trace_row &r, const StageTimer &tm, size_t q) {
+  float ms[ST_COUNT], total;
+  tm.collect(q, ms, &total);
   r.ms_tau = ms[ST_TAU];
   r.ms_gemm = ms[ST_GEMM];
   r.ms_prune = ms[ST_PRUNE];
@@ -1135,10 +1275,28 @@ void fill_row(skm_trace_row &r, const StepStats &ss, int64_t n, int32_t k, int64
 // Rotation buffers: Rp = R padded to row stride ds, Rtp = R^T padded likewise (both d rows).
 struct Rot {
   float *Rp = nullptr, *Rtp = nullptr;
-  unsigned int *amax = nullptr;   // [0] max |R|, [1] max |input| of the last rotate_into
+  static constexpr int kSlots = 8;
+  unsigned int *amax = nullptr;   // [0] max |R|, the others magnitude bounds of the inputs of the products, one after the other
+  int used = 1;
   uint32_t *Rs = nullptr;         // workspace for the split-fp16 copy of R^T (tall rotations)
+  int alloc_bounds(Pool &pool, hipStream_t st) {
+    if (amax) return SKM_OK;
+    HIPCHK(pool.get(&amax, (size_t)kSlots));
+    HIPCHK(launch_fill_u32(amax, kSlots, 0u, st));
+    return SKM_OK;
+  }
+  // a zero word for the bound of the next product's input (stream order: the words are cleared again when all are used)
+  int next_slot(hipStream_t st, unsigned int **slot) {
+    if (used == kSlots) {
+      HIPCHK(launch_fill_u32(amax + 1, kSlots - 1, 0u, st));
+      used = 1;
+    }
+    *slot = amax + used++;
+    return SKM_OK;
+  }
 };
 int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const float *R_dev, uint64_t seed, Rot &rot) {
+  if (int rc = rot.alloc_bounds(pool, st)) return rc;
   float *Rown = nullptr;
   if (!R_dev) {
     HIPCHK(pool.get(&Rown, (size_t)d * d));
@@ -1148,32 +1306,38 @@ int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const floa
   }
   HIPCHK(pool.get(&rot.Rp, (size_t)d * ds));
   HIPCHK(pool.get(&rot.Rtp, (size_t)d * ds));
-  HIPCHK(launch_pad_copy(R_dev, d, d, d, rot.Rp, ds, ds, 0, st));
-  HIPCHK(launch_pad_copy(R_dev, d, d, d, rot.Rtp, ds, ds, 1, st));
-  if (!rot.amax) HIPCHK(pool.get(&rot.amax, 2));
   if (d % 32 == 0) HIPCHK(pool.get(&rot.Rs, (size_t)d * ((size_t)d + 32)));
-  return measure_absmax(R_dev, d, d, d, rot.amax, st);
+  HIPCHK(launch_rotation_operands(R_dev, d, rot.Rp, rot.Rtp, ds, rot.amax, st));
+  return SKM_OK;
 }
 // out (rows x ds, zero padded) = in (rows x d, stride ldin) * R
-// out_absmax (optional) receives the bit pattern of max |out|
-// (in_measured: rot.amax[1] already bounds |in|)
-int rotate_into(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t ds, const Rot &rot, float *out,
-                hipStream_t st, unsigned int *out_absmax = nullptr, bool in_measured = false) {
-  if (!in_measured)
-    if (int rc = measure_absmax(in, ldin, rows, d, rot.amax + 1, st)) return rc;
-  if (out_absmax) HIPCHK(launch_fill_u32(out_absmax, 1, 0u, st));
+// out_absmax (optional, zero before the call) receives the bit pattern of max |out|
+// (in_bound: a word that already bounds |in|)
+int rotate_into(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t ds, Rot &rot, float *out,
+                hipStream_t st, unsigned int *out_absmax = nullptr, const unsigned int *in_bound = nullptr) {
+  if (!in_bound) {
+    unsigned int *slot = nullptr;
+    if (int rc = rot.next_slot(st, &slot)) return rc;
+    HIPCHK(launch_absmax(in, ldin, rows, d, slot, st));
+    in_bound = slot;
+  }
   GemmOperands g{in, ldin, (int32_t)rows, rot.Rtp, ds, d, d};
-  g.a_absmax = rot.amax + 1; g.b_absmax = rot.amax;
+  g.a_absmax = in_bound; g.b_absmax = rot.amax;
   g.b_split = rot.Rs;
   HIPCHK(gemm_store(g, out, ds, ds, 1.f, 0.f, st, out_absmax));
   return SKM_OK;
 }
 // out (rows x d) = Yr (rows x d, stride ldy) * R^T
-int unrotate_into(const float *Yr, int64_t ldy, int32_t rows, int32_t d, int32_t ds, const Rot &rot, float *out,
-                  hipStream_t st) {
-  if (int rc = measure_absmax(Yr, ldy, rows, d, rot.amax + 1, st)) return rc;
+int unrotate_into(const float *Yr, int64_t ldy, int32_t rows, int32_t d, int32_t ds, Rot &rot, float *out,
+                  hipStream_t st, const unsigned int *in_bound = nullptr) {
+  if (!in_bound) {
+    unsigned int *slot = nullptr;
+    if (int rc = rot.next_slot(st, &slot)) return rc;
+    HIPCHK(launch_absmax(Yr, ldy, rows, d, slot, st));
+    in_bound = slot;
+  }
   GemmOperands g{Yr, ldy, rows, rot.Rp, ds, d, d};
-  g.a_absmax = rot.amax + 1; g.b_absmax = rot.amax;
+  g.a_absmax = in_bound; g.b_absmax = rot.amax;
   HIPCHK(gemm_store(g, out, d, d, 1.f, 0.f, st));
   return SKM_OK;
 }
@@ -1253,12 +1417,12 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   const bool timed = tr != nullptr;
   StageTimer tm(c.st, timed);
   Events evs;
-  hipEvent_t e_begin = nullptr, e_rot = nullptr, e_init = nullptr, e_end0 = nullptr, e_end = nullptr;
+  hipEvent_t e_begin = nullptr, e_rot = nullptr, e_init = nullptr, e_unrot0 = nullptr, e_unrot1 = nullptr, e_end = nullptr;
   hipEvent_t e_gt0 = nullptr, e_gt1 = nullptr, e_rot0 = nullptr;
   if (timed) {
-    e_begin = evs.next(); e_rot = evs.next(); e_init = evs.next(); e_end0 = evs.next(); e_end = evs.next();
+    e_begin = evs.next(); e_rot = evs.next(); e_init = evs.next(); e_unrot0 = evs.next(); e_unrot1 = evs.next(); e_end = evs.next();
     e_gt0 = evs.next(); e_gt1 = evs.next(); e_rot0 = evs.next();
-    if (!e_begin || !e_rot || !e_init || !e_end0 || !e_end || !e_gt0 || !e_gt1 || !e_rot0)
+    if (!e_begin || !e_rot || !e_init || !e_unrot0 || !e_unrot1 || !e_end || !e_gt0 || !e_gt1 || !e_rot0)
       return fail(SKM_EHIP, "hipEventCreate failed");
   }
   if (timed) HIPCHK(hipEventRecord(e_begin, c.st));
@@ -1279,16 +1443,17 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     } side;
     hipEvent_t e_fork = nullptr, e_join = nullptr;
     const bool beside = !p.R && (int64_t)n * d >= ((int64_t)1 << 26);
+    unsigned int *x_bound = nullptr;
     if (beside) {
       e_fork = evs.next();
       e_join = evs.next();
       if (!e_fork || !e_join) return fail(SKM_EHIP, "hipEventCreate failed");
       HIPCHK(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
-      HIPCHK(c.pool.get(&rot.amax, 2));
+      if ((rc = rot.alloc_bounds(c.pool, c.st))) return rc;
+      if ((rc = rot.next_slot(c.st, &x_bound))) return rc;
       HIPCHK(hipEventRecord(e_fork, c.st));   // X is ready where the caller's stream stands now
       HIPCHK(hipStreamWaitEvent(side.s, e_fork, 0));
-      rc = measure_absmax(X, d, n, d, rot.amax + 1, side.s, 1024);   // four workgroups per CU: the generator's kernels find room
-      if (rc) return rc;
+      HIPCHK(launch_absmax(X, d, n, d, x_bound, side.s, 1024));   // four workgroups per CU: the generator's kernels find room
       HIPCHK(hipEventRecord(e_join, side.s));
     }
     rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, seed, rot);
@@ -1296,7 +1461,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     if (beside) HIPCHK(hipStreamWaitEvent(c.st, e_join, 0));
     if (timed) HIPCHK(hipEventRecord(e_rot0, c.st));
-    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR, beside);
+    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR, x_bound);
     if (rc) return rc;
     if (beside) HIPCHK(hipStreamSynchronize(side.s));   // nothing is left on the side stream when it is destroyed
     if (timed) HIPCHK(hipEventRecord(e_rot, c.st));
@@ -1328,22 +1493,31 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     HIPCHK(c.pool.get(&c.subkey, (size_t)n));
   }
 
-  // ---- InitCentroids: k distinct rows of X~
+  // ---- InitCentroids: k distinct rows of X~.  The row numbers go through the page-locked block, so nothing waits here
+  // (the numbers are drawn while the rotation runs); a few are read from there by the gather itself.
   {
-    std::vector<int64_t> idx((size_t)k);
+    std::vector<int64_t> idx_big;
+    if (!c.idx_host) idx_big.resize((size_t)k);
+    int64_t *idx = c.idx_host ? c.idx_host : idx_big.data();
     if (p.init_idx) {
       for (int32_t i = 0; i < k; ++i) {
-        idx[(size_t)i] = p.init_idx[i];
-        if (idx[(size_t)i] < 0 || idx[(size_t)i] >= n) return fail(SKM_EINVAL, "init_idx out of range");
+        idx[i] = p.init_idx[i];
+        if (idx[i] < 0 || idx[i] >= n) return fail(SKM_EINVAL, "init_idx out of range");
       }
     } else {
-      sample_rows(seed, STREAM_INIT, n, k, idx.data());
+      sample_rows(seed, STREAM_INIT, n, k, idx);
     }
-    int64_t *idx_dev = nullptr;
-    HIPCHK(c.pool.get(&idx_dev, (size_t)k));
-    HIPCHK(hipMemcpyAsync(idx_dev, idx.data(), sizeof(int64_t) * idx.size(), hipMemcpyHostToDevice, c.st));
-    HIPCHK(launch_gather_rows(c.Xr, c.ldx, c.ds, idx_dev, k, c.Y, c.ds, c.ds, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
+    const int64_t *idx_view = c.idx_dev_view;
+    if (k > 1024) {
+      int64_t *idx_dev = nullptr;
+      HIPCHK(c.pool.get(&idx_dev, (size_t)k));
+      HIPCHK(hipMemcpyAsync(idx_dev, idx, sizeof(int64_t) * (size_t)k, hipMemcpyHostToDevice, c.st));
+      idx_view = idx_dev;
+    }
+    c.pending = true;   // (the block is in use until the first step has been waited for)
+    HIPCHK(launch_gather_rows(c.Xr, c.ldx, c.ds, idx_view, k, c.Y, c.ds, c.ds, c.st, c.amax + Ctx::AM_Y));
+    c.y_amax_valid = true;
+    if (!c.idx_host) HIPCHK(hipStreamSynchronize(c.st));
   }
 
   // ---- ETR set-up (Section 3.3): queries, ground truth, rotated queries
@@ -1400,12 +1574,14 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   double best_recall = -1.0;
   // recall of (current centroids, current assignment): Section 3.3
   auto measure_recall = [&](double *out) -> int {
-    HIPCHK(launch_prep_centroids(c.Y, c.ds, k, c.ds, c.ds, ynorm_full, 0, 0, nullptr, c.st));
+    CentroidPrep cp{c.Y, c.ds, k, c.ds};
+    cp.ynorm = ynorm_full; cp.dn = c.ds;
+    HIPCHK(launch_prep_centroids(cp, c.st));
     if (int mrc = c.measure_y()) return mrc;
     GemmOperands g{Qr, c.ds, p.nq, c.Y, c.ds, k, c.ds};
     g.a_absmax = c.amax + Ctx::AM_QR; g.b_absmax = c.amax + Ctx::AM_Y;
     HIPCHK(gemm_store(g, Sq, k, k, 1.f, 0.f, c.st));
-    HIPCHK(hipMemsetAsync(etr_scal, 0, 2 * sizeof(unsigned long long), c.st));
+    HIPCHK(launch_fill_u64(etr_scal, 2, 0ull, c.st));
     HIPCHK(launch_recall_scores(Sq, k, p.nq, k, ynorm_full, nprobe, gt_keys, p.topk, c.assign, etr_scal, etr_scal + 1,
                                 c.st));
     unsigned long long h[2] = {0, 0};
@@ -1417,6 +1593,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
 
   for (int32_t t = 1; t <= iters; ++t) {
     StepStats ss;
+    tm.begin_step();
     if (t == 1) {
       rc = step_exact(c, tm, ss);
     } else {
@@ -1439,11 +1616,9 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
       HIPCHK(launch_normalize_rows(c.Y, c.ds, k, c.ds, c.st));
       c.y_amax_valid = false;
     }
-    HIPCHK(hipStreamSynchronize(c.st));
-    float ms[ST_COUNT], total;
-    tm.collect(ms, &total);
+    // (no wait: the next step's launches follow while the update runs)
     run = t;
-    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, nempty, recall, ms, total);
+    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, nempty, recall);
     ++rows;
     if (t > 1 && p.adjust_dprime && k > 1) {
       const double f = 1.0 - (double)ss.survivors / ((double)n * (double)(k - 1));
@@ -1464,37 +1639,44 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (stop) break;
   }
 
-  // ---- final assignment with the two-phase approach (Section 3.3)
-  if (p.final_assign) {
-    StepStats ss;
-    std::swap(c.assign, c.prev);
-    c.regroup_ok = false;
-    rc = step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
-    if (rc) return rc;
-    float ms[ST_COUNT], total;
-    tm.collect(ms, &total);
-    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, 0, -1.0, ms, total);
-    ++rows;
-  }
-  if (c.permuted) {   // per-point results back in the caller's order
-    if (assign_out) HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
-    if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
-  } else {
-    if (assign_out) HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-    if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-  }
-
-  // ---- Algorithm 1, last line: Y = Y~ R^T
-  if (timed) HIPCHK(hipEventRecord(e_end0, c.st));
+  // ---- Algorithm 1, last line: Y = Y~ R^T (before the final assignment, which does not change the centroids: one wait
+  // then ends both)
+  if (timed) HIPCHK(hipEventRecord(e_unrot0, c.st));
   if (p.rotate) {
-    rc = unrotate_into(c.Y, c.ds, k, d, c.ds, rot, centroids_out, c.st);
+    rc = unrotate_into(c.Y, c.ds, k, d, c.ds, rot, centroids_out, c.st, c.y_amax_valid ? c.amax + Ctx::AM_Y : nullptr);
     if (rc) return rc;
   } else {
     HIPCHK(hipMemcpy2DAsync(centroids_out, sizeof(float) * (size_t)d, c.Y, sizeof(float) * (size_t)c.ds,
                             sizeof(float) * (size_t)d, (size_t)k, hipMemcpyDeviceToDevice, c.st));
   }
+  if (timed) HIPCHK(hipEventRecord(e_unrot1, c.st));
+
+  // ---- final assignment with the two-phase approach (Section 3.3)
+  bool waited = false;
+  if (p.final_assign) {
+    StepStats ss;
+    std::swap(c.assign, c.prev);
+    c.regroup_ok = false;
+    const bool direct = !c.permuted;   // points in the caller's order: the last kernel writes the caller's arrays
+    if (direct && assign_out) c.assign = assign_out;
+    if (direct && dist_out) c.dist = dist_out;
+    tm.begin_step();
+    rc = step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
+    if (rc) return rc;
+    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, 0, -1.0);
+    ++rows;
+    waited = direct;
+  }
+  if (c.permuted) {   // per-point results back in the caller's order
+    if (assign_out) HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
+    if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
+  } else if (!p.final_assign) {
+    if (assign_out) HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+    if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+  }
   if (timed) HIPCHK(hipEventRecord(e_end, c.st));
-  HIPCHK(hipStreamSynchronize(c.st));
+  if (timed || !waited) HIPCHK(hipStreamSynchronize(c.st));
+  c.pending = false;
   if (dprime_out) *dprime_out = dprime;
   if (tr) {
     tr->rows = std::min(rows, tr->capacity);
@@ -1503,9 +1685,11 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     (void)hipEventElapsedTime(&tr->ms_rotate, e_rot0, e_rot);
     (void)hipEventElapsedTime(&tr->ms_init, e_begin, e_init);
     (void)hipEventElapsedTime(&tr->ms_etr_gt, e_gt0, e_gt1);
-    (void)hipEventElapsedTime(&tr->ms_unrotate, e_end0, e_end);
+    (void)hipEventElapsedTime(&tr->ms_unrotate, e_unrot0, e_unrot1);
     (void)hipEventElapsedTime(&tr->ms_total, e_begin, e_end);
+    for (int32_t q = 0; q < tr->rows; ++q) fill_times(tr->row[q], tm, (size_t)q);
   }
+  ws.finished();
   host.body_done(tr);
   return SKM_OK;
 }
@@ -1586,7 +1770,8 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   HIPCHK(c.pool.get(&lab[1], (size_t)nbatch * W));
   if (dist_out_host) HIPCHK(c.pool.get(&dist_all, (size_t)nbatch * W));
   float *dist_batch = c.dist;
-  int32_t *cnt_dev = c.up.cnt;
+  int32_t *cnt_total = nullptr;   // [k] cluster sizes of the pass
+  HIPCHK(c.pool.get(&cnt_total, (size_t)k));
 
   // ---- InitCentroids: k distinct rows of X, rotated like the points
   {
@@ -1632,17 +1817,20 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   Rng split_rng = rng_stream(seed, STREAM_SPLIT);
   int32_t rows_out = 0;
   int cur = 0;   // lab[cur] receives the labels of the pass in work, lab[cur ^ 1] holds those of the pass before
-  std::vector<int64_t> cnt_total((size_t)k);
   for (int pass = 0; pass < npass; ++pass) {
     const bool final_pass = pass >= iters;
     StepStats tot;
     tot.pruned = pass > 0;
-    std::fill(cnt_total.begin(), cnt_total.end(), 0);
-    if (!final_pass) HIPCHK(hipMemsetAsync(c.S, 0, sizeof(double) * (size_t)k * c.ds, c.st));
+    tm.begin_step();
+    if (!final_pass) {
+      HIPCHK(launch_fill_u64(reinterpret_cast<unsigned long long *>(c.S), (int64_t)k * c.ds, 0ull, c.st));
+      HIPCHK(launch_fill_u32(reinterpret_cast<unsigned int *>(cnt_total), k, 0u, c.st));
+    }
     for (int64_t b = 0; b < nbatch; ++b) {
       const int64_t g = (int64_t)pass * nbatch + b, r0 = b * W, rows = std::min<int64_t>(W, n - r0);
       HIPCHK(hipStreamWaitEvent(c.st, ev_copied[g & 1], 0));
       if (p.rotate) {
+        HIPCHK(launch_fill_u32(c.amax + Ctx::AM_XR, 1, 0u, c.st));
         rc = rotate_into(raw[g & 1], d, rows, d, c.ds, rot, Xr_buf, c.st, c.amax + Ctx::AM_XR);
         if (rc) return rc;
       } else {
@@ -1664,7 +1852,6 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       StepStats ss;
       rc = pass == 0 ? step_exact(c, tm, ss) : step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
       if (rc) return rc;
-      for (int32_t j = 0; j < k; ++j) cnt_total[(size_t)j] += c.rb_cnt[j];
       tot.objective += ss.objective;
       tot.survivors += ss.survivors;
       tot.completed += ss.completed;
@@ -1679,25 +1866,29 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       tot.dprime = ss.dprime;
       tot.nblocks = ss.nblocks;
       if (!final_pass) {
-        HIPCHK(launch_update(c.Xr, c.ldx, rows, c.ds, c.assign, k, c.up, nullptr, c.ds, c.st, c.S, nullptr, 1));
+        HIPCHK(launch_add_counts(c.up.cnt, k, cnt_total, c.st));
+        HIPCHK(launch_update(c.Xr, c.ldx, rows, c.ds, c.assign, k, c.up, nullptr, c.ds, c.st, c.S, nullptr, 1, c.report->largest));
         tm.mark(ST_UPDATE);
       }
     }
     int64_t nempty = 0;
     if (!final_pass) {
       // means of the whole pass, then the split of empty clusters on the total sizes
-      for (int32_t j = 0; j < k; ++j) c.rb_cnt[j] = (int32_t)cnt_total[(size_t)j];
-      HIPCHK(hipMemcpyAsync(cnt_dev, c.rb_cnt, sizeof(int32_t) * (size_t)k, hipMemcpyHostToDevice, c.st));
-      HIPCHK(launch_means_from_sums(c.S, cnt_dev, k, c.ds, c.Y, c.ds, c.amax + Ctx::AM_Y, c.st));
+      HIPCHK(launch_means_from_sums(c.S, cnt_total, k, c.ds, c.Y, c.ds, c.amax + Ctx::AM_Y, c.st));
       c.y_amax_valid = true;
-      c.rb_cnt_valid = true;
+      c.sizes_known = false;   // (the report holds those of the last batch)
+      int32_t *batch_cnt = c.up.cnt;
+      c.up.cnt = cnt_total;
       rc = split_empty(c, tm, split_rng, p.split_eps, &nempty);
+      c.up.cnt = batch_cnt;
       if (rc) return rc;
     }
     HIPCHK(hipStreamSynchronize(c.st));
-    float ms[ST_COUNT], total;
-    tm.collect(ms, &total);
-    if (tr && rows_out < tr->capacity) fill_row(tr->row[rows_out], tot, n, k, nempty, -1.0, ms, total);
+    if (tr && rows_out < tr->capacity) {
+      fill_row(tr->row[rows_out], tot, n, k, nempty, -1.0);
+      fill_times(tr->row[rows_out], tm, 0);
+    }
+    tm.reset();
     ++rows_out;
     if (pass > 0 && !final_pass && p.adjust_dprime && k > 1) {
       const double f = 1.0 - (double)tot.survivors / ((double)n * (double)(k - 1));
@@ -1731,17 +1922,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
     (void)hipEventElapsedTime(&tr->ms_unrotate, e_end0, e_end);
     (void)hipEventElapsedTime(&tr->ms_total, e_begin, e_end);
   }
-  return SKM_OK;
-}
-
-// a label outside [0, k) would index past the centroid table: refuse it here
-int labels_in_range(const int32_t *a, int64_t n, int32_t k, unsigned int *flag_dev, hipStream_t st) {
-  unsigned int bad = 0;
-  HIPCHK(hipMemsetAsync(flag_dev, 0, sizeof(unsigned int), st));
-  HIPCHK(launch_check_labels(a, n, k, flag_dev, st));
-  HIPCHK(hipMemcpyAsync(&bad, flag_dev, sizeof(bad), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  if (bad) return fail(SKM_EINVAL, "assignment label outside [0, k)");
+  ws.finished();
   return SKM_OK;
 }
 
@@ -1766,7 +1947,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   c.ds = round_up(d, 16);
   c.block_stats = p.block_stats != 0;
   c.screen_mode = p.screen;
-  StageTimer tm(c.st, true);
+  StageTimer tm(c.st, tr != nullptr);
   Rot rot;
   float *Xr_own = nullptr;
   rc = c.alloc_bounds();
@@ -1779,8 +1960,9 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR);
     if (rc) return rc;
-    rc = rotate_into(centroids, d, k, d, c.ds, rot, c.Y, c.st);
+    rc = rotate_into(centroids, d, k, d, c.ds, rot, c.Y, c.st, c.amax + Ctx::AM_Y);
     if (rc) return rc;
+    c.y_amax_valid = true;
     c.Xr = Xr_own; c.ldx = c.ds;
   } else {
     if (d == c.ds && aligned16(X)) {
@@ -1794,11 +1976,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     rc = c.measure_xr();
     if (rc) return rc;
   }
-  if (prev_assign) {
-    rc = labels_in_range(prev_assign, n, k, c.counters, c.st);
-    if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(c.prev, prev_assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-  }
+  c.prev_in = prev_assign;   // checked and copied at the start of the step; a bad label leaves the outputs untouched
   // Many centroids: a step on its own pays for what a fit does once in its third step.  The points are rewritten
   // grouped by their incumbents and the first filter runs in front of the exact kernel (a million tiles of two slabs
   // each otherwise: the fixed costs of a tile, not the arithmetic, are then the whole run time).
@@ -1816,25 +1994,33 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   }
   const int32_t dprime = dprime_in > 0 ? snap16((double)dprime_in, d) : dprime_init(d, p.dprime_frac);
   StepStats ss;
+  const bool direct = !c.group_now;   // the last kernel writes the caller's arrays (not in a step that may regroup the points)
+  if (direct) {
+    c.assign = assign_out;
+    if (dist_out) c.dist = dist_out;
+  }
+  tm.begin_step();
   rc = step_pruned(c, tm, dprime, (double)p.eps0, prev_assign != nullptr, ss);
   if (rc) return rc;
-  if (c.permuted) {   // per-point results back in the caller's order
-    HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
-    if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
-  } else {
-    HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-    if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+  if (!direct) {
+    if (c.permuted) {   // per-point results back in the caller's order
+      HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
+      if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
+    } else {
+      HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+      if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+    }
+    HIPCHK(hipStreamSynchronize(c.st));
   }
-  HIPCHK(hipStreamSynchronize(c.st));
-  float ms[ST_COUNT], total;
-  tm.collect(ms, &total);
   if (tr && tr->row && tr->capacity >= 1) {
-    fill_row(tr->row[0], ss, n, k, 0, -1.0, ms, total);
+    fill_row(tr->row[0], ss, n, k, 0, -1.0);
+    fill_times(tr->row[0], tm, 0);
     tr->rows = 1;
     tr->iters_run = 0;
-    tr->ms_total = total;
+    tr->ms_total = tr->row[0].ms_step;
     host.body_done(tr);
   }
+  ws.finished();
   return SKM_OK;
 }
 
@@ -1947,6 +2133,7 @@ int fit_sampled(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, 
     (void)hipEventElapsedTime(&tr->ms_total, e0, e1);
     host.body_done(tr);
   }
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2205,6 +2392,7 @@ int fit_hierarchical(const float *X, int64_t n, int32_t d, int32_t k, int32_t me
     (void)hipEventElapsedTime(&tr->ms_total, e0, e1);
     host.body_done(tr);
   }
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2321,39 +2509,51 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
   if (rc) return rc;
   if (!centroids || !assign_out) return fail(SKM_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;
-  Pool pool;
   const int32_t ds = round_up(d, 16);
-  const float *Xp = X, *Yp = centroids;
-  int64_t ldx = d, ldy = d;
-  if (d != ds || !aligned16(X) || !aligned16(centroids)) {
-    float *Xo = nullptr, *Yo = nullptr;
-    HIPCHK(pool.get(&Xo, (size_t)n * ds));
-    HIPCHK(pool.get(&Yo, (size_t)k * ds));
-    HIPCHK(launch_pad_copy(X, d, n, d, Xo, ds, ds, 0, st));
-    HIPCHK(launch_pad_copy(centroids, d, k, d, Yo, ds, ds, 0, st));
-    Xp = Xo; Yp = Yo; ldx = ds; ldy = ds;
-  }
-  float *ynorm = nullptr;
+  // rows of an odd length or alignment go through a padded copy, 256 MB at a time
+  const bool pad_x = d != ds || !aligned16(X), pad_y = d != ds || !aligned16(centroids);
+  const int64_t chunk = pad_x ? std::min<int64_t>(n, std::max<int64_t>(((int64_t)64 << 20) / ds, 1024)) : n;
+  CallArena ws(((pad_x ? (size_t)chunk * ds : 0) + (pad_y ? (size_t)k * ds : 0) + (size_t)k * (ds + 33)) * 4 + (size_t)n * 8 + 8192);
+  Pool pool;
+  float *Xo = nullptr, *Yo = nullptr, *ynorm = nullptr;
   unsigned long long *best = nullptr;
+  unsigned int *amax = nullptr;
+  uint32_t *ysplit = nullptr;
+  if (pad_x) HIPCHK(pool.get(&Xo, (size_t)chunk * ds));
+  if (pad_y) HIPCHK(pool.get(&Yo, (size_t)k * ds));
   HIPCHK(pool.get(&ynorm, (size_t)k));
   HIPCHK(pool.get(&best, (size_t)n));
-  HIPCHK(launch_prep_centroids(Yp, ldy, k, ds, ds, ynorm, 0, 0, nullptr, st));
-  HIPCHK(launch_fill_u64(best, n, ~0ull, st));
-  unsigned int *amax = nullptr;
   HIPCHK(pool.get(&amax, 2));
-  rc = measure_absmax(Xp, ldx, n, ds, amax, st);
-  if (rc) return rc;
-  rc = measure_absmax(Yp, ldy, k, ds, amax + 1, st);
-  if (rc) return rc;
-  GemmOperands g{Xp, ldx, (int32_t)n, Yp, ldy, k, ds};
-  g.a_absmax = amax; g.b_absmax = amax + 1;
-  if (ds % 32 == 0) HIPCHK(pool.get(&g.b_split, (size_t)k * ((size_t)ds + 32)));
-  HIPCHK(gemm_argmin(g, ynorm, best, st));
-  HIPCHK(launch_finalize_assign(best, nullptr, n, assign_out, nullptr, nullptr, k, nullptr, nullptr, nullptr, st));
-  if (dist_out) {
-    HIPCHK(launch_tau_init(Xp, ldx, n, ds, Yp, ldy, assign_out, dist_out, nullptr, st));
+  HIPCHK(pool.get(&ysplit, (size_t)k * ((size_t)ds + 32)));
+  HIPCHK(launch_fill_u32(amax, 2, 0u, st));
+  HIPCHK(launch_absmax(X, d, n, d, amax, st));
+  HIPCHK(launch_absmax(centroids, d, k, d, amax + 1, st));
+  if (pad_y) HIPCHK(launch_pad_copy(centroids, d, k, d, Yo, ds, ds, 0, st));
+  const float *Yp = pad_y ? Yo : centroids;
+  CentroidPrep cp{Yp, ds, k, ds};
+  cp.ynorm = ynorm; cp.dn = ds;
+  cp.Ys = ysplit; cp.y_absmax = amax + 1;
+  HIPCHK(launch_prep_centroids(cp, st));
+  HIPCHK(launch_fill_u64(best, n, ~0ull, st));
+  for (int64_t r0 = 0; r0 < n; r0 += chunk) {
+    const int64_t rows = std::min<int64_t>(chunk, n - r0);
+    const float *Xp = X + r0 * d;
+    if (pad_x) {
+      HIPCHK(launch_pad_copy(Xp, d, rows, d, Xo, ds, ds, 0, st));
+      Xp = Xo;
+    }
+    GemmOperands g{Xp, ds, (int32_t)rows, Yp, ds, k, ds};
+    g.a_absmax = amax; g.b_absmax = amax + 1;
+    g.b_presplit = ysplit; g.ldbs = ds + 32;
+    HIPCHK(gemm_argmin(g, ynorm, best + r0, st));
+    if (dist_out)   // labels and direct distances in one pass over the rows
+      HIPCHK(launch_tau_init(Xp, ds, rows, ds, Yp, ds, nullptr, dist_out + r0, best + r0, st, nullptr, nullptr, nullptr,
+                             nullptr, nullptr, assign_out + r0));
   }
+  if (!dist_out)
+    HIPCHK(launch_finalize_assign(FinalizeArgs{best, nullptr, n, assign_out, nullptr, nullptr, k, nullptr}, st));
   HIPCHK(hipStreamSynchronize(st));
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2363,39 +2563,30 @@ int skm_update(const float *X, int64_t n, int32_t d, const int32_t *assign, int3
   if (rc) return rc;
   if (!assign || !centroids) return fail(SKM_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;
-  Pool pool;
+  // rows and centroids are read and written where they are, whatever their length and alignment; only the partial sums
+  // are padded
   const int32_t ds = round_up(d, 16);
-  const float *Xp = X;
-  int64_t ldx = d;
-  float *Yp = centroids;
-  int64_t ldy = d;
-  const bool padded = (d != ds) || !aligned16(X) || !aligned16(centroids);
-  if (padded) {
-    float *Xo = nullptr, *Yo = nullptr;
-    HIPCHK(pool.get(&Xo, (size_t)n * ds));
-    HIPCHK(pool.get(&Yo, (size_t)k * ds));
-    HIPCHK(launch_pad_copy(X, d, n, d, Xo, ds, ds, 0, st));
-    HIPCHK(launch_pad_copy(centroids, d, k, d, Yo, ds, ds, 0, st));
-    Xp = Xo; ldx = ds; Yp = Yo; ldy = ds;
-  }
   UpdateWs w{};
-  HIPCHK(pool.get(&w.cnt, (size_t)k));
+  w.max_segments = update_max_segments(n, k);
+  CallArena ws((size_t)w.max_segments * ds * sizeof(double) + (size_t)n * 4 + (size_t)k * 20 + 4096);
+  Pool pool;
+  unsigned int *flag = nullptr;   // [1 + k]: the flag, then the sizes
+  HIPCHK(pool.get(&flag, (size_t)k + 1));
+  w.cnt = reinterpret_cast<int32_t *>(flag + 1);
   HIPCHK(pool.get(&w.off, (size_t)k + 1));
   HIPCHK(pool.get(&w.cursor, (size_t)k));
   HIPCHK(pool.get(&w.segoff, (size_t)k + 1));
   HIPCHK(pool.get(&w.order, (size_t)n));
-  w.max_segments = update_max_segments(n, k);
   HIPCHK(pool.get(&w.partial, (size_t)w.max_segments * ds));
-  rc = labels_in_range(assign, n, k, reinterpret_cast<unsigned int *>(w.cursor), st);
-  if (rc) return rc;
-  HIPCHK(hipMemsetAsync(w.cnt, 0, sizeof(int32_t) * (size_t)k, st));
-  HIPCHK(launch_histogram(assign, n, w.cnt, st));
-  HIPCHK(launch_update(Xp, ldx, n, ds, assign, k, w, Yp, ldy, st));
-  if (padded)
-    HIPCHK(hipMemcpy2DAsync(centroids, sizeof(float) * (size_t)d, Yp, sizeof(float) * (size_t)ds,
-                            sizeof(float) * (size_t)d, (size_t)k, hipMemcpyDeviceToDevice, st));
+  PinnedWord bad;
+  if (!bad.host) return fail(SKM_EHIP, "hipHostMalloc failed");
+  HIPCHK(launch_fill_u32(flag, (int64_t)k + 1, 0u, st));
+  HIPCHK(launch_histogram(assign, n, k, w.cnt, flag, st));
+  HIPCHK(launch_update(X, d, n, d, assign, k, w, centroids, d, st, nullptr, nullptr, 0, -1, flag, bad.dev));
   if (counts_out) HIPCHK(hipMemcpyAsync(counts_out, w.cnt, sizeof(int32_t) * (size_t)k, hipMemcpyDeviceToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
+  ws.finished();
+  if (*bad.host) return fail(SKM_EINVAL, "assignment label outside [0, k)");
   return SKM_OK;
 }
 
@@ -2405,6 +2596,7 @@ int skm_etr_ground_truth(const float *X, int64_t n, int32_t d, const float *quer
   if (n < 1 || n >= (int64_t)1 << 31 || d < 1 || d > 16384) return fail(SKM_EINVAL, "shape out of range");
   if (nq < 1 || topk < 1 || topk > 256) return fail(SKM_EINVAL, "nq >= 1 and 1 <= topk <= 256 required");
   hipStream_t st = (hipStream_t)stream;
+  CallArena ws((size_t)n * 4 + (size_t)nq * (size_t)std::min<int64_t>(n, kGtChunk) * 4 + (size_t)nq * topk * 8 + 4096);
   Pool pool;
   unsigned int *amax = nullptr;
   unsigned long long *keys = nullptr;
@@ -2413,6 +2605,7 @@ int skm_etr_ground_truth(const float *X, int64_t n, int32_t d, const float *quer
   if (int rc = ground_truth_keys(pool, X, n, d, queries, nq, topk, amax, amax + 1, keys, st)) return rc;
   HIPCHK(launch_keys_to_index(keys, (int64_t)nq * topk, gt_out, st));
   HIPCHK(hipStreamSynchronize(st));
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2420,10 +2613,12 @@ int skm_make_rotation(int32_t d, uint64_t seed, void *stream, float *R_out) {
   if (!R_out) return fail(SKM_EINVAL, "null pointer");
   if (d < 1 || d > 16384) return fail(SKM_EINVAL, "d out of range");
   hipStream_t st = (hipStream_t)stream;
+  CallArena ws(((size_t)d * d + 20 * 64 * (size_t)d + (size_t)((d + 63) / 64) * 64 * (d + 64) + 8192) * sizeof(double));
   Pool pool;
   int rc = make_rotation_dev(pool, d, seed, st, R_out);
   if (rc) return rc;
   HIPCHK(hipStreamSynchronize(st));
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2431,22 +2626,22 @@ int skm_rotate(const float *X, int64_t n, int32_t d, const float *R, int32_t tra
   if (!X || !R || !out) return fail(SKM_EINVAL, "null pointer");
   if (n < 1 || n >= (int64_t)1 << 31 || d < 1 || d > 16384) return fail(SKM_EINVAL, "shape out of range");
   hipStream_t st = (hipStream_t)stream;
-  Pool pool;
   const int32_t ds = round_up(d, 16);
+  CallArena ws(((size_t)d * ds + (size_t)d * (d + 32)) * 4 + 4096);
+  Pool pool;
   float *B = nullptr;  // B[c][kk] = R[kk][c] for X R, R[c][kk] for X R^T
-  HIPCHK(pool.get(&B, (size_t)d * ds));
-  HIPCHK(launch_pad_copy(R, d, d, d, B, ds, ds, transpose ? 0 : 1, st));
   unsigned int *amax = nullptr;
+  HIPCHK(pool.get(&B, (size_t)d * ds));
   HIPCHK(pool.get(&amax, 2));
-  int rc = measure_absmax(X, d, n, d, amax, st);
-  if (rc) return rc;
-  rc = measure_absmax(R, d, d, d, amax + 1, st);
-  if (rc) return rc;
+  HIPCHK(launch_fill_u32(amax, 2, 0u, st));
+  HIPCHK(launch_rotation_operands(R, d, transpose ? B : nullptr, transpose ? nullptr : B, ds, amax + 1, st));
+  HIPCHK(launch_absmax(X, d, n, d, amax, st));
   GemmOperands g{X, d, (int32_t)n, B, ds, d, d};
   g.a_absmax = amax; g.b_absmax = amax + 1;
   if (d % 32 == 0) HIPCHK(pool.get(&g.b_split, (size_t)d * ((size_t)d + 32)));
   HIPCHK(gemm_store(g, out, d, d, 1.f, 0.f, st));
   HIPCHK(hipStreamSynchronize(st));
+  ws.finished();
   return SKM_OK;
 }
 
@@ -2465,6 +2660,8 @@ int32_t skm_dprime_adjust(int32_t d, int32_t dprime, double prune_frac, float lo
 void skm_debug_gemm_config(int32_t tile256, int32_t panel_cols, int64_t max_tiles) {
   gemm_debug_config(tile256, panel_cols, max_tiles);
 }
+
+void skm_release_memory(void) { block_cache().release(); }
 
 const char *skm_strerror(int rc) {
   switch (rc) {

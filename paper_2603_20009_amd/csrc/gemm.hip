@@ -683,8 +683,10 @@ void gemm_debug_config(int tile256, int panel_cols, int64_t max_tiles) {
 // The 256 x 256 form pays when the tall operand fills the device several times over and B can be split ahead.
 static bool wants_split256(const GemmOperands &g) {
   const int forced = g_tile256.load(std::memory_order_relaxed);   // -1: by shape, 0: never, 1: whenever the operands allow it
-  if (!g.b_split || !g.a_absmax || !g.b_absmax || g.K % 32 != 0 || g.K < 64 || forced == 0) return false;
-  if (!aligned16(g.A) || !aligned16(g.B) || !aligned16(g.b_split) || g.lda % 4 != 0 || g.ldb % 4 != 0) return false;
+  if ((!g.b_split && !g.b_presplit) || !g.a_absmax || !g.b_absmax || g.K % 32 != 0 || g.K < 64 || forced == 0) return false;
+  if (!aligned16(g.A) || !aligned16(g.B) || !aligned16(g.b_split) || !aligned16(g.b_presplit) || g.lda % 4 != 0 || g.ldb % 4 != 0 ||
+      g.ldbs % 4 != 0)
+    return false;
   const int64_t tiles = (int64_t)((g.M + T2 - 1) / T2) * ((g.N + T2 - 1) / T2);
   // narrow B: a last column tile that is mostly padding costs more than the larger tile gains
   const int64_t ncols = (int64_t)((g.N + T2 - 1) / T2) * T2;
@@ -701,7 +703,8 @@ static hipError_t launch_split256(const GemmOperands &g, const typename EpiArgs<
   const int64_t nwg = (int64_t)((g.M + T2 - 1) / T2) * ((g.N + T2 - 1) / T2);
   if (nwg <= 0) return hipSuccess;
   if (nwg > (1 << 22) - 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NT2), smem, st, g, (const uint32_t *)g.b_split, (int64_t)g.K + 32, e);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NT2), smem, st, g,
+                     g.b_presplit ? g.b_presplit : (const uint32_t *)g.b_split, g.b_presplit ? g.ldbs : (int64_t)g.K + 32, e);
   return hipGetLastError();
 }
 
@@ -731,7 +734,7 @@ static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>:
   const bool big = wants_split256(g);
   const int edge = big ? T2 : BM;
   const int64_t nct = (g.N + edge - 1) / edge;
-  if (big) {   // B, split into fp16 pairs, K + 32 words a row
+  if (big && !g.b_presplit) {   // B, split into fp16 pairs, K + 32 words a row
     hipError_t rc = launch_split_rows(g.B, g.ldb, g.N, g.K, g.b_absmax, g.b_split, st);
     if (rc != hipSuccess) return rc;
   }

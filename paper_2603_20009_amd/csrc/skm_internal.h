@@ -55,8 +55,11 @@ struct GemmOperands {
   const unsigned int *a_absmax = nullptr;
   const unsigned int *b_absmax = nullptr;
   // Optional workspace of N * (K + 32) words, 16-byte aligned: with it (and the bounds above, K a multiple of 32) a
-  // tall product splits B into fp16 pairs there first and runs on 256 x 256 tiles.
+  // tall product splits B into fp16 pairs there first and runs on 256 x 256 tiles.  b_presplit: such a copy (row stride
+  // ldbs words, rows of K columns or more, scaled by *b_absmax) that the caller has already, used instead.
   uint32_t *b_split = nullptr;
+  const uint32_t *b_presplit = nullptr;
+  int64_t ldbs = 0;
 };
 
 // Split-fp16 arithmetic.  A matrix whose largest magnitude is m is scaled by the power of two that brings m
@@ -214,11 +217,13 @@ hipError_t launch_prune(const PruneArgs &a, hipStream_t st);
 // permutation of 0 .. n - 1); the row of that point is copied to xr_out[p] (row stride ds) and its label to
 // label_out[p].  `assign` is still indexed by point.
 // xh (optional, with xs): also the plane of hi halves of launch_split_rows' out_hi.
+// assign = NULL: the labels are the low halves of best[] (packed keys of an argmin); a point whose key is ~0 takes label 0
+// and sets bit 1 of *unset (optional).  label_out without order receives the label of every point.
 hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
                            const int32_t *assign, float *tau, unsigned long long *best, hipStream_t st,
                            float *xnp = nullptr, uint32_t *xs = nullptr, const unsigned int *x_absmax = nullptr,
                            const int32_t *order = nullptr, float *xr_out = nullptr, int32_t *label_out = nullptr,
-                           uint32_t *xh = nullptr);
+                           uint32_t *xh = nullptr, unsigned int *unset = nullptr);
 // dst[idx[p]] = src[p] for 4-byte items
 hipError_t launch_scatter_by_index(const void *src, const int32_t *idx, int64_t n, void *dst, hipStream_t st);
 // order_out = order_in (points grouped by cluster, segment c = [off[c], off[c+1])) with every segment stably sorted by
@@ -230,10 +235,31 @@ hipError_t launch_suborder(const float *Xr, int64_t ldx, int64_t n, int32_t k, c
 hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32_t *perm, int64_t n, int32_t *inv_scratch,
                                 hipStream_t st);
 
-// ynorm[c] = ||Y[c][0:dn)||^2 and (if Ypdx) the block-major copy of the dims from dprime on.
-// ynp (optional, [nb + 1][k]): prefix norms of the centroids at the same checkpoints.
-hipError_t launch_prep_centroids(const float *Y, int64_t ldy, int32_t k, int32_t ds, int32_t dn, float *ynorm,
-                                 int32_t dprime, int32_t nb, float *Ypdx, hipStream_t st, float *ynp = nullptr);
+// What a step needs from the centroids (all outputs optional), and two jobs of the step's start that ride along: words to
+// clear and theta ratios (a host array, copied into the launch) to store on the device.  Y 16-byte aligned, ldy a
+// multiple of 4, ds, dn and dprime multiples of 16.
+struct CentroidPrep {
+  const float *Y;
+  int64_t ldy;
+  int32_t k, ds;
+  float *ynorm = nullptr;      // [k] ||Y[c][0 : dn)||^2
+  int32_t dn = 0;
+  int32_t dprime = 0, nb = 0;
+  float *Ypdx = nullptr;       // [nb][k][64] block-major copy of the dims from dprime on, zero filled past column pdx_cols
+  int32_t pdx_cols = 1 << 30;
+  float *ynp = nullptr;        // [nb + 1][k] prefix norms at the checkpoints min(ds, dprime + 64 m)
+  uint32_t *Ys = nullptr;      // split-fp16 copy (launch_split_rows), scaled by the bound *y_absmax
+  uint32_t *Yh = nullptr;      // its plane of hi halves
+  const unsigned int *y_absmax = nullptr;
+  unsigned int *clear = nullptr;
+  int64_t clear_words = 0;
+  float *ratio_out = nullptr;
+};
+struct ThetaRatios {
+  int n;
+  float v[kMaxBlocks + 1];
+};
+hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio = nullptr, int nratio = 0);
 
 // every non-zero row of A scaled to unit Euclidean length, in place (cols, lda multiples of 4; A 16-byte aligned)
 hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st);
@@ -241,15 +267,36 @@ hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t co
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
 hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st);
 
-// Unpack best -> assign/dist, count cluster sizes (cnt[k], optional), changed assignments, per-block objective partials.
-// *unset is set to 1 if some point still holds the "no centroid yet" key (an internal error).
-hipError_t launch_finalize_assign(const unsigned long long *best, const int32_t *prev, int64_t n, int32_t *assign,
-                                  float *dist, int32_t *cnt, int32_t k, double *obj_partial,
-                                  unsigned long long *changed, unsigned int *unset, hipStream_t st);
+// What the last kernel of a step writes into page-locked host memory.
+struct StepReport {
+  double objective;          // sum over the points of the squared distance found
+  unsigned int flag;         // bit 0: list overflow, bit 1: a point without a centroid, bit 2: a label of the caller's outside [0, k)
+  int32_t nempty, largest;   // of the cluster sizes
+  int32_t pad;
+  unsigned long long scal[SC_COUNT];   // the step scalars, replicas added up; SC_CHANGED = points with another label than prev
+};
+// Unpack best -> assign, dist; cluster sizes into cnt[k] (zero before).  With `done` (a zero word) the launch also closes
+// the step: see finalize_assign_kernel.
+struct FinalizeArgs {
+  const unsigned long long *best;
+  const int32_t *prev;        // [n] or NULL
+  int64_t n;
+  int32_t *assign;
+  float *dist;                // or NULL
+  int32_t *cnt;               // or NULL
+  int32_t k;
+  unsigned int *flag;         // or NULL
+  unsigned int *done = nullptr;
+  double *obj_partial = nullptr;      // [finalize_blocks(n)]
+  int32_t *change_start = nullptr;    // [finalize_blocks(n)] changed points before the points of each workgroup
+  const unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]
+  StepReport *report = nullptr;       // device-visible address of the page-locked block
+};
+hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st);
 int64_t finalize_blocks(int64_t n);
-hipError_t launch_sum_partials(const double *part, int64_t m, double *out, hipStream_t st);
-hipError_t launch_histogram(const int32_t *assign, int64_t n, int32_t *cnt, hipStream_t st);
-hipError_t launch_check_labels(const int32_t *a, int64_t n, int32_t k, unsigned int *bad, hipStream_t st);
+// cnt[l] += number of i with assign[i] = l; labels outside [0, k) are left out and set bit 2 of *flag (optional)
+hipError_t launch_histogram(const int32_t *assign, int64_t n, int32_t k, int32_t *cnt, unsigned int *flag, hipStream_t st);
+hipError_t launch_copy_labels(const int32_t *a, int64_t n, int32_t k, int32_t *out, unsigned int *flag, hipStream_t st);
 
 // Centroid update (Section 3.2) as a segmented reduction.
 struct UpdateWs {
@@ -271,9 +318,13 @@ int32_t update_sort_cap();
 // S (optional, [k][ds] fp64) receives the sum of every cluster; y_absmax (optional) the bit pattern of max |Y| of
 // the new centroids (the launcher clears it first).  With `accumulate` the sums of these n points are added to S
 // instead (one batch of a larger update); Y may then be NULL, and launch_means_from_sums finishes the update.
+// largest: the largest cluster size if known, else -1.  flag / flag_host: if *flag is not zero by then, Y is left as it
+// was; the word is copied to *flag_host (device-visible).  Labels outside [0, k) must have been left out of w.cnt.
 hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, int32_t k,
                          const UpdateWs &w, float *Y, int64_t ldy, hipStream_t st, double *S = nullptr,
-                         unsigned int *y_absmax = nullptr, int accumulate = 0);
+                         unsigned int *y_absmax = nullptr, int accumulate = 0, int32_t largest = -1,
+                         const unsigned int *flag = nullptr, unsigned int *flag_host = nullptr);
+hipError_t launch_add_counts(const int32_t *cnt, int32_t k, int32_t *total, hipStream_t st);
 hipError_t launch_means_from_sums(const double *S, const int32_t *cnt, int32_t k, int32_t ds, float *Y, int64_t ldy,
                                   unsigned int *y_absmax, hipStream_t st);
 
@@ -283,23 +334,26 @@ struct IncUpdateWs {
   int32_t *ent_lab;    // [capacity] cluster of the entry
   int32_t *order;      // [capacity]
   int32_t *cnt, *off, *cursor, *segoff;   // [k], [k+1], [k], [k+1]
-  unsigned int *counter;
   double *partial;     // [max_segments][ds]
   int64_t capacity, max_segments;
 };
 // Centroids from the cluster sums S of the previous update and the points whose label changed since
 // (Section 3.2, the same means computed from the difference).
 hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign,
-                                     const int32_t *prev, int64_t changed, int32_t k, const UpdateWs &w,
-                                     const IncUpdateWs &inc, double *S, float *Y, int64_t ldy, hipStream_t st,
-                                     unsigned int *y_absmax = nullptr);
+                                     const int32_t *prev, int64_t changed, const int32_t *change_start, int32_t k,
+                                     const UpdateWs &w, const IncUpdateWs &inc, double *S, float *Y, int64_t ldy,
+                                     hipStream_t st, unsigned int *y_absmax = nullptr);
 
 // Empty-cluster splits: pairs_dev = (empty, donor) pairs grouped into chains (splits that share a cluster, in the
 // host's order); chain_first_dev[c] .. chain_first_dev[c + 1] are the splits of chain c.  One workgroup per chain.
 hipError_t launch_split(float *Y, int64_t ldy, int32_t d, const int32_t *pairs_dev, const int32_t *chain_first_dev,
                         int32_t nchains, float eps, hipStream_t st);
-hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx_dev, int32_t k, float *dst,
-                              int64_t ldd, int32_t dpad, hipStream_t st);
+// dst[c] = src[idx[c]] (idx: device or page-locked host memory), zero padded to dpad; max |.| folded into *absmax (optional)
+hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx, int32_t k, float *dst,
+                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax = nullptr);
+// Rp (stride ld, zero padded to it) = R, Rtp likewise = R^T (either may be NULL), max |R| folded into *absmax
+hipError_t launch_rotation_operands(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld, unsigned int *absmax,
+                                    hipStream_t st);
 hipError_t launch_pad_copy(const float *src, int64_t lds, int64_t n, int32_t d, float *dst, int64_t ldd, int32_t dpad,
                            int32_t transpose, hipStream_t st);
 

@@ -74,7 +74,9 @@ int skm_assign_exact_static(const float *X, int64_t n, int32_t d, const float *c
   unsigned int *amax = reinterpret_cast<unsigned int *>(base + kOffAmax);
   uint32_t *split = reinterpret_cast<uint32_t *>(base + kOffSplit);
   // the array keeps what the last call left: everything read below is written first (fill kernels, no memset nodes)
-  HIPCHK(launch_prep_centroids(centroids, d, k, d, d, ynorm, 0, 0, nullptr, st));
+  CentroidPrep cp{centroids, d, k, d};
+  cp.ynorm = ynorm; cp.dn = d;
+  HIPCHK(launch_prep_centroids(cp, st));
   HIPCHK(launch_fill_u64(best, n, ~0ull, st));
   HIPCHK(launch_fill_u32(amax, 2, 0u, st));
   HIPCHK(launch_absmax(X, d, n, d, amax, st));
@@ -84,7 +86,7 @@ int skm_assign_exact_static(const float *X, int64_t n, int32_t d, const float *c
   g.b_absmax = amax + 1;
   if (d % 32 == 0 && (size_t)k * ((size_t)d + 32) <= kSplitWords) g.b_split = split;
   HIPCHK(gemm_argmin(g, ynorm, best, st));
-  HIPCHK(launch_finalize_assign(best, nullptr, n, assign_out, nullptr, nullptr, k, nullptr, nullptr, nullptr, st));
+  HIPCHK(launch_finalize_assign(FinalizeArgs{best, nullptr, n, assign_out, nullptr, nullptr, k, nullptr}, st));
   if (dist_out) HIPCHK(launch_tau_init(X, d, n, d, centroids, d, assign_out, dist_out, nullptr, st));
   HIPCHK(hipStreamSynchronize(st));
   return SKM_OK;

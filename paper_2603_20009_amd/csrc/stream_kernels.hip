@@ -53,6 +53,8 @@ struct PrefixOut {
   const int32_t *order;
   float *xr_out;
   int32_t *label_out;
+  unsigned int *unset = nullptr;   // labels taken from packed keys: bit 1 is set if a point has none
+  int span = 64;                   // BATCH: points a workgroup takes at a time (64, or 16 when there are few)
 };
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -118,7 +120,9 @@ __device__ inline float4 load_stream4(const float *p) {
 }
 
 // BATCH (with po.xnp, NV > 0): a workgroup takes 64 consecutive points at a time and writes their prefix norms through
-// LDS, 256 contiguous bytes per table row, instead of one 4-byte store per point and row.
+// LDS, 256 contiguous bytes per table row, instead of one 4-byte store per point and row.  Where 64 points a workgroup
+// would leave most of the chip without one (a wavefront then walks sixteen rows one after the other while other CUs
+// idle), it takes 16.
 constexpr int kPrefixStageRows = 128;   // ds <= 2048 in the batched form
 template <int NV, bool BATCH>
 __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t ldx, int64_t n, int32_t ds,
@@ -129,7 +133,17 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
   const int lane = threadIdx.x & 63;
   auto point = [&](int64_t p, int slot) {   // output slot p <- point i
     const int64_t i = po.order ? (int64_t)po.order[p] : p;
-    const int a = assign[i];
+    int a;
+    if (assign) {
+      a = assign[i];
+    } else {   // the labels are still packed keys (an argmin that has just run)
+      const unsigned long long key = best[i];
+      a = (int)(key & 0xffffffffull);
+      if (key == ~0ull) {   // no kernel offered this point a centroid: reported, kept in range
+        a = 0;
+        if (lane == 0 && po.unset) atomicOr(po.unset, 2u);
+      }
+    }
     const float *x = Xr + i * ldx;
     const float *y = Y + (int64_t)a * ldy;
     float s = 0.f;
@@ -208,14 +222,16 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
   };
   if (BATCH) {
     const int wave = threadIdx.x >> 6, rows = ds >> 4;
-    for (int64_t b0 = (int64_t)blockIdx.x * 64; b0 < n; b0 += (int64_t)gridDim.x * 64) {
-      for (int it = 0; it < 16; ++it) {
+    const int span = po.span, sh = span == 64 ? 6 : 4;
+    for (int64_t b0 = (int64_t)blockIdx.x * span; b0 < n; b0 += (int64_t)gridDim.x * span) {
+      for (int it = 0; it < span / 4; ++it) {
         const int slot = it * 4 + wave;
         if (b0 + slot < n) point(b0 + slot, slot);
       }
       __syncthreads();
-      if (b0 + lane < n)
-        for (int p = wave; p < rows; p += 4) po.xnp[(int64_t)p * po.n + b0 + lane] = s_np[p * 64 + lane];
+      const int col = threadIdx.x & (span - 1);
+      if (b0 + col < n)
+        for (int p = threadIdx.x >> sh; p < rows; p += 256 >> sh) po.xnp[(int64_t)p * po.n + b0 + col] = s_np[p * 64 + col];
       __syncthreads();
     }
   } else {
@@ -227,18 +243,20 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
 hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
                            const int32_t *assign, float *tau, unsigned long long *best, hipStream_t st, float *xnp,
                            uint32_t *xs, const unsigned int *x_absmax, const int32_t *order, float *xr_out,
-                           int32_t *label_out, uint32_t *xh) {
+                           int32_t *label_out, uint32_t *xh, unsigned int *unset) {
   if (n <= 0) return hipSuccess;
   const int nv = (ds + 255) / 256;
   const bool batch = xnp != nullptr && nv <= 8 && ds / 16 <= kPrefixStageRows;
-  int64_t blocks = batch ? (n + 63) / 64 : (n + 3) / 4;
+  // five workgroups of the batched form fit a CU (32 KB of LDS each): below one such round of 64 points, 16 at a time
+  const int span = n >= (int64_t)num_cus() * 5 * 64 ? 64 : 16;
+  int64_t blocks = batch ? (n + span - 1) / span : (n + 3) / 4;
   const int64_t cap = (int64_t)num_cus() * 32;
   if (blocks > cap) blocks = cap;
   if (xs && (ds % 16 != 0 || !x_absmax)) return hipErrorInvalidValue;
-  if ((order != nullptr) != (xr_out != nullptr) || (order != nullptr) != (label_out != nullptr)) return hipErrorInvalidValue;
+  if ((order != nullptr) != (xr_out != nullptr) || (order && (!label_out || !assign)) || (!assign && !best)) return hipErrorInvalidValue;
   if (xr_out && (reinterpret_cast<uintptr_t>(xr_out) & 15u)) return hipErrorInvalidValue;
   if (xh && (!xs || (reinterpret_cast<uintptr_t>(xh) & 15u))) return hipErrorInvalidValue;
-  const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out};
+  const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out, unset, span};
 #define SKM_TAU_LAUNCH(NV)                                                                                      \
   do {                                                                                                          \
     if (batch && NV > 0)                                                                                        \
@@ -352,50 +370,79 @@ hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32
 }
 
 // ------------------------------------------------------------------ centroid preparation
-// One workgroup per centroid: ynorm[c] over dims [0, dn), and the trailing dims from dprime on
-// copied to Ypdx[m][c][0..63] (block m = dims dprime+64m ..), zero filled past the row.
-__global__ void __launch_bounds__(256) prep_centroids_kernel(const float *Y, int64_t ldy, int32_t k, int32_t ds,
-                                                             int32_t dn, float *ynorm, int32_t dprime, int32_t nb,
-                                                             float *Ypdx, float *ynp) {
-  __shared__ float red[4];
-  __shared__ float piece[1024];   // ds <= 16384
-  const int c = blockIdx.x;
-  const float *y = Y + (int64_t)c * ldy;
-  float s = 0.f;
-  for (int j = threadIdx.x; j < dn; j += 256) s = fmaf(y[j], y[j], s);
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+// Everything a step needs from the centroids in one pass over them, one workgroup per centroid, a float4 per thread:
+// prefix norms at the checkpoints (ynp) or over dims [0, dn) (ynorm), the trailing dims from dprime on copied to
+// Ypdx[m][c][0..63] (block m = dims dprime + 64 m .., zero filled past the row), and the split-fp16 copy of the row with
+// its plane of hi halves (layouts of launch_split_rows).  The same launch carries the step's two small host-side jobs:
+// it clears the words that the step counts into and writes the theta ratios, which arrive as kernel arguments.  A small
+// step is a chain of launches of a few microseconds each, and a memset or a copy from the host costs three launches:
+// with all five in one, a pruned step of 20 000 x 128 points against 100 centroids issues four commands fewer.
+__global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, ThetaRatios ratios) {
+  __shared__ float s_pre[1025];   // ||y[0 : 16 p)||^2 at p (ds <= 16384)
+  const int c = blockIdx.x, tid = threadIdx.x;
+  for (int64_t w = (int64_t)c * 256 + tid; w < a.clear_words; w += (int64_t)gridDim.x * 256) a.clear[w] = 0u;
+  if (c == 0 && a.ratio_out)
+    for (int m = tid; m < ratios.n; m += 256) a.ratio_out[m] = ratios.v[m];
+  const float *y = a.Y + (int64_t)c * a.ldy;
+  PrefixOut po{nullptr, a.k, a.ds, a.Ys, a.Yh, nullptr, 0.f, nullptr, nullptr, nullptr};
+  if (a.Ys) {
+    po.scale = split_scale(*a.y_absmax);
+    if (tid < 64) emit_split_pads(po, c, tid);
+  }
+  const int pdx_end = a.Ypdx ? a.dprime + a.nb * kBlockDims : 0;   // columns up to here have a place in Ypdx
+  const int cend = a.ds > pdx_end ? a.ds : pdx_end;
+  for (int c0 = 0; c0 < cend; c0 += 1024) {
+    const int col = c0 + 4 * tid;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (col < a.ds) v = *reinterpret_cast<const float4 *>(y + col);
+    const float q = quad_sum(fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w))));
+    if (col < a.ds) {
+      if ((tid & 3) == 0) s_pre[(col >> 4) + 1] = q;
+      if (a.Ys) emit_split(po, c, col, v);
+    }
+    if (col >= a.dprime && col < pdx_end) {
+      const int t = col - a.dprime;
+      if (col >= a.pdx_cols) v = make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4 *>(a.Ypdx + ((int64_t)(t / kBlockDims) * a.k + c) * kBlockDims + t % kBlockDims) = v;
+    }
+  }
+  if (!a.ynorm && !a.ynp) return;
+  if (tid == 0) s_pre[0] = 0.f;
   __syncthreads();
-  if (threadIdx.x == 0 && ynorm) ynorm[c] = (red[0] + red[1]) + (red[2] + red[3]);
-  if (ynp) {
-    // ||y[0 : t_m)||^2 at the checkpoints t_m = min(ds, d' + 64 m): sums of squares of the 16-dim pieces of the row
-    // in LDS, then thread m adds up the pieces below its checkpoint (d' is a multiple of 16; rows are short)
-    const int np = (ds + 15) / 16;
-    for (int p = threadIdx.x; p < np; p += 256) {
-      float acc = 0.f;
-      for (int j = 16 * p; j < min(ds, 16 * p + 16); ++j) acc = fmaf(y[j], y[j], acc);
-      piece[p] = acc;
-    }
-    __syncthreads();
-    for (int m = threadIdx.x; m <= nb; m += 256) {
-      const int t = m == nb ? ds : min(ds, dprime + kBlockDims * m);
-      float acc = 0.f;
-      for (int p = 0; p < (t + 15) / 16; ++p) acc += piece[p];
-      ynp[(int64_t)m * k + c] = acc;
+  if (tid < 64) {   // inclusive scan of the pieces, 64 at a time
+    const int np = a.ds >> 4;
+    float carry = 0.f;
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      float v = p0 + tid < np ? s_pre[p0 + tid + 1] : 0.f;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const float u = __shfl_up(v, o, 64);
+        if (tid >= o) v += u;
+      }
+      v += carry;
+      if (p0 + tid < np) s_pre[p0 + tid + 1] = v;
+      carry = __shfl(v, 63, 64);
     }
   }
-  if (Ypdx) {
-    for (int t = threadIdx.x; t < nb * kBlockDims; t += 256) {
-      const int m = t / kBlockDims, qd = t % kBlockDims;
-      const int col = dprime + t;
-      Ypdx[((int64_t)m * k + c) * kBlockDims + qd] = col < ds ? y[col] : 0.f;
+  __syncthreads();
+  if (a.ynorm && tid == 0) a.ynorm[c] = s_pre[a.dn >> 4];
+  if (a.ynp)
+    for (int m = tid; m <= a.nb; m += 256) {
+      const int t = m == a.nb ? a.ds : min(a.ds, a.dprime + kBlockDims * m);
+      a.ynp[(int64_t)m * a.k + c] = s_pre[t >> 4];
     }
-  }
 }
 
-hipError_t launch_prep_centroids(const float *Y, int64_t ldy, int32_t k, int32_t ds, int32_t dn, float *ynorm,
-                                 int32_t dprime, int32_t nb, float *Ypdx, hipStream_t st, float *ynp) {
-  hipLaunchKernelGGL(prep_centroids_kernel, dim3(k), dim3(256), 0, st, Y, ldy, k, ds, dn, ynorm, dprime, nb, Ypdx, ynp);
+hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio, int nratio) {
+  if (a.k <= 0) return hipSuccess;
+  if (a.ds % 16 != 0 || a.ds > 16384 || a.ldy % 4 != 0 || (reinterpret_cast<uintptr_t>(a.Y) & 15u) || a.dn % 16 != 0 ||
+      a.dn > a.ds || a.dprime % 16 != 0 || (a.Ys && !a.y_absmax) || (a.Yh && !a.Ys) || nratio > kMaxBlocks + 1 ||
+      (a.ratio_out != nullptr) != (nratio > 0))
+    return hipErrorInvalidValue;
+  ThetaRatios r;
+  r.n = nratio;
+  for (int m = 0; m < nratio; ++m) r.v[m] = ratio[m];
+  hipLaunchKernelGGL(prep_centroids_kernel, dim3(a.k), dim3(256), 0, st, a, r);
   return hipGetLastError();
 }
 
@@ -511,180 +558,356 @@ hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t co
 // (k <= FIN_LDS_BINS) and flushed once per workgroup: a million atomic increments on the 64 cache lines that hold 1024
 // counters took 0.2 ms per step; larger k spreads them over more lines and goes to memory directly.
 // Small inputs (one small fit of many, as in the hierarchical fit) take 1024 points per workgroup instead: the
-// launch is then a few workgroups side by side rather than one long loop.
+// launch is then a few workgroups side by side rather than one long loop.  They count in LDS as well where a cluster
+// holds more than a handful of the points (direct increments of 20 000 points on 100 counters: 54 us, in LDS: 5 us).
+// The last workgroup to finish closes the step: it adds the objective's partials and the counter replicas in a fixed
+// order, takes the number of empty clusters and the largest size, turns the per-workgroup counts of changed points into
+// starts (for the incremental update), and writes the step's report straight into page-locked host memory.
 constexpr int FIN_THREADS = 256;
 constexpr int FIN_LDS_BINS = 8192;
 static int finalize_per_block(int64_t n) { return n >= (int64_t)1 << 18 ? 8192 : 1024; }
 int64_t finalize_blocks(int64_t n) { return (n + finalize_per_block(n) - 1) / finalize_per_block(n); }
 
-__global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(const unsigned long long *best,
-                                                                      const int32_t *prev, int64_t n, int32_t *assign,
-                                                                      float *dist, int32_t *cnt, int32_t k,
-                                                                      double *obj_partial, unsigned long long *changed,
-                                                                      unsigned int *unset, int per_block) {
-  __shared__ double red[4];
+template <typename T>
+__device__ inline T load_agent(const T *p) {   // a value that other workgroups of this launch have written
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeArgs a, int per_block, int in_lds) {
+  __shared__ double red[FIN_THREADS];
   __shared__ unsigned int redc[4];
   __shared__ int s_hist[FIN_LDS_BINS];
-  const bool in_lds = cnt && k <= FIN_LDS_BINS && per_block > 1024;
+  __shared__ int s_last;
+  const int tid = threadIdx.x;
   if (in_lds) {
-    for (int b = threadIdx.x; b < k; b += FIN_THREADS) s_hist[b] = 0;
+    for (int b = tid; b < a.k; b += FIN_THREADS) s_hist[b] = 0;
     __syncthreads();
   }
   double s = 0.0;
   unsigned int ch = 0;
   const int64_t base = (int64_t)blockIdx.x * per_block;
-  for (int t = threadIdx.x; t < per_block; t += FIN_THREADS) {
+  for (int t = tid; t < per_block; t += FIN_THREADS) {
     const int64_t i = base + t;
-    if (i < n) {
-      const unsigned long long key = best[i];
-      int32_t a = (int32_t)(key & 0xffffffffull);
+    if (i < a.n) {
+      const unsigned long long key = a.best[i];
+      int32_t l = (int32_t)(key & 0xffffffffull);
       float dv = ord2f((uint32_t)(key >> 32));
-      if (key == ~0ull) {   // a point no kernel offered a centroid for: reported through `unset`, kept in range
-        a = 0;
+      if (key == ~0ull) {   // a point no kernel offered a centroid for: reported through `flag`, kept in range
+        l = 0;
         dv = 0.f;
-        if (unset) atomicOr(unset, 2u);   // bit 1: unset point (bit 0 is the hand-over list's overflow)
+        if (a.flag) atomicOr(a.flag, 2u);   // bit 1: unset point (bit 0 is the hand-over list's overflow)
       }
-      assign[i] = a;
-      if (dist) dist[i] = dv;
-      if (in_lds) atomicAdd(&s_hist[a], 1);
-      else if (cnt) atomicAdd(cnt + a, 1);
-      if (prev) ch += (prev[i] != a);
+      a.assign[i] = l;
+      if (a.dist) a.dist[i] = dv;
+      if (in_lds) atomicAdd(&s_hist[l], 1);
+      else if (a.cnt) atomicAdd(a.cnt + l, 1);
+      if (a.prev) ch += (a.prev[i] != l);
       s += (double)dv;
     }
   }
   s = wave_sum(s);
   for (int m = 1; m < 64; m <<= 1) ch += __shfl_xor(ch, m, 64);
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6] = s;
-    redc[threadIdx.x >> 6] = ch;
+  if ((tid & 63) == 0) {
+    red[tid >> 6] = s;
+    redc[tid >> 6] = ch;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    if (obj_partial) obj_partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-    const unsigned int c4 = redc[0] + redc[1] + redc[2] + redc[3];
-    if (changed && c4) atomicAdd(changed, (unsigned long long)c4);
-  }
   if (in_lds) {   // (the barrier above has ordered the LDS increments before these reads)
-    for (int b = threadIdx.x; b < k; b += FIN_THREADS) {
+    for (int b = tid; b < a.k; b += FIN_THREADS) {
       const int v = s_hist[b];
-      if (v) atomicAdd(cnt + b, v);
+      if (v) atomicAdd(a.cnt + b, v);
     }
   }
+  if (!a.done) return;
+  if (tid == 0) {
+    __hip_atomic_store(a.obj_partial + blockIdx.x, (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.change_start + blockIdx.x, (int)(redc[0] + redc[1] + redc[2] + redc[3]), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // ---- the last workgroup closes the step
+  __threadfence();   // this thread's stores and increments before the ticket
+  __syncthreads();
+  if (tid == 0) s_last = atomicAdd(a.done, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  const int nblk = gridDim.x;
+  {
+    // objective: thread t adds the t-th contiguous part, the parts are added pairwise; changed points: the same parts
+    // scanned, every workgroup's count becomes the number of changed points before it
+    const int per = (nblk + FIN_THREADS - 1) / FIN_THREADS;
+    const int lo = min(tid * per, nblk), hi = min(lo + per, nblk);
+    double t = 0.0;
+    int mine = 0;
+    for (int i = lo; i < hi; ++i) {
+      t += load_agent(a.obj_partial + i);
+      mine += load_agent(a.change_start + i);
+    }
+    red[tid] = t;
+    s_hist[tid] = mine;
+    __syncthreads();
+    for (int w = FIN_THREADS / 2; w > 0; w >>= 1) {
+      if (tid < w) red[tid] += red[tid + w];
+      __syncthreads();
+    }
+    for (int o = 1; o < FIN_THREADS; o <<= 1) {
+      const int v = tid >= o ? s_hist[tid - o] : 0;
+      __syncthreads();
+      s_hist[tid] += v;
+      __syncthreads();
+    }
+    int run = s_hist[tid] - mine;
+    for (int i = lo; i < hi; ++i) {
+      const int v = load_agent(a.change_start + i);
+      a.change_start[i] = run;
+      run += v;
+    }
+  }
+  StepReport *r = a.report;
+  for (int q = tid; q < SC_COUNT; q += FIN_THREADS) {
+    unsigned long long v = 0;
+    for (int rep = 0; rep < kStatReplicas; ++rep) v += load_agent(a.scal + (size_t)rep * SC_COUNT + q);
+    if (q == SC_CHANGED) v = (unsigned long long)s_hist[FIN_THREADS - 1];
+    r->scal[q] = v;
+  }
+  int empty = 0, largest = 0;
+  if (a.cnt)
+    for (int b = tid; b < a.k; b += FIN_THREADS) {
+      const int v = load_agent(a.cnt + b);
+      empty += v == 0;
+      largest = max(largest, v);
+    }
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    empty += __shfl_xor(empty, m, 64);
+    largest = max(largest, __shfl_xor(largest, m, 64));
+  }
+  __syncthreads();
+  if ((tid & 63) == 0) {
+    s_hist[tid >> 6] = empty;
+    s_hist[4 + (tid >> 6)] = largest;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    r->objective = red[0];
+    r->flag = load_agent(a.flag);
+    r->nempty = (s_hist[0] + s_hist[1]) + (s_hist[2] + s_hist[3]);
+    r->largest = max(max(s_hist[4], s_hist[5]), max(s_hist[6], s_hist[7]));
+  }
 }
 
-hipError_t launch_finalize_assign(const unsigned long long *best, const int32_t *prev, int64_t n, int32_t *assign,
-                                  float *dist, int32_t *cnt, int32_t k, double *obj_partial,
-                                  unsigned long long *changed, unsigned int *unset, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(finalize_assign_kernel, dim3((unsigned)finalize_blocks(n)), dim3(FIN_THREADS), 0, st, best, prev, n,
-                     assign, dist, cnt, k, obj_partial, changed, unset, finalize_per_block(n));
+hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st) {
+  if (a.n <= 0) return hipSuccess;
+  if (a.done && (!a.obj_partial || !a.change_start || !a.scal || !a.report || !a.flag)) return hipErrorInvalidValue;
+  const int per_block = finalize_per_block(a.n);
+  const int in_lds = a.cnt && a.k <= FIN_LDS_BINS && (per_block > 1024 || a.n >= 8 * (int64_t)a.k);
+  hipLaunchKernelGGL(finalize_assign_kernel, dim3((unsigned)finalize_blocks(a.n)), dim3(FIN_THREADS), 0, st, a, per_block, in_lds);
   return hipGetLastError();
 }
 
-// fixed-order sum of the per-block partials (deterministic objective)
-__global__ void __launch_bounds__(256) sum_partials_kernel(const double *part, int64_t m, double *out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const int64_t per = (m + 255) / 256;
-  const int64_t lo = (int64_t)threadIdx.x * per;
-  for (int64_t i = lo; i < lo + per && i < m; ++i) s += part[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+// Counting by label.  Where a label holds several of the points, a workgroup counts its points in LDS first: a million
+// returning atomics on the few cache lines that hold 1024 counters took 0.2 ms, with one atomic per (workgroup, label)
+// 0.02 ms.  Labels outside [0, k) are left out and set bit 2 of *flag (if given).
+constexpr int CNT_THREADS = 512;
+constexpr int CNT_LDS_BINS = 8192;
+static int count_per_block(int64_t n) { return n >= (int64_t)1 << 18 ? 8192 : 1024; }
+static bool count_in_lds(int64_t n, int32_t k) { return k <= CNT_LDS_BINS && n >= 8 * (int64_t)k; }
+
+__global__ void __launch_bounds__(CNT_THREADS) histogram_kernel(const int32_t *assign, int64_t n, int32_t k, int32_t *cnt,
+                                                                unsigned int *flag, int per_block, int in_lds) {
+  extern __shared__ int s_bins[];
+  if (in_lds) {
+    for (int b = threadIdx.x; b < k; b += CNT_THREADS) s_bins[b] = 0;
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = red[0];
+  const int64_t base = (int64_t)blockIdx.x * per_block;
+  for (int t = threadIdx.x; t < per_block; t += CNT_THREADS) {
+    const int64_t i = base + t;
+    if (i >= n) break;
+    const int a = assign[i];
+    if ((unsigned int)a >= (unsigned int)k) {
+      if (flag) atomicOr(flag, 4u);
+    } else {
+      atomicAdd(in_lds ? s_bins + a : cnt + a, 1);
+    }
+  }
+  if (!in_lds) return;
+  __syncthreads();
+  for (int b = threadIdx.x; b < k; b += CNT_THREADS) {
+    const int v = s_bins[b];
+    if (v) atomicAdd(cnt + b, v);
+  }
 }
-hipError_t launch_sum_partials(const double *part, int64_t m, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, part, m, out);
+hipError_t launch_histogram(const int32_t *assign, int64_t n, int32_t k, int32_t *cnt, unsigned int *flag, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const int per = count_per_block(n);
+  const int in_lds = count_in_lds(n, k);
+  hipLaunchKernelGGL(histogram_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(CNT_THREADS),
+                     in_lds ? (size_t)k * sizeof(int) : 0, st, assign, n, k, cnt, flag, per, in_lds);
   return hipGetLastError();
 }
 
-__global__ void histogram_kernel(const int32_t *assign, int64_t n, int32_t *cnt) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    atomicAdd(cnt + assign[i], 1);
+// out[i] = a[i] where that is a label in [0, k); any other becomes 0 and sets bit 2 of *flag (the caller's labels are
+// checked and copied in one pass: nothing behind it indexes with an unchecked label)
+__global__ void copy_labels_kernel(const int32_t *a, int64_t n, int32_t k, int32_t *out, unsigned int *flag) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    int32_t v = a[i];
+    if (v < 0 || v >= k) {
+      v = 0;
+      atomicOr(flag, 4u);
+    }
+    out[i] = v;
+  }
 }
-hipError_t launch_histogram(const int32_t *assign, int64_t n, int32_t *cnt, hipStream_t st) {
+hipError_t launch_copy_labels(const int32_t *a, int64_t n, int32_t k, int32_t *out, unsigned int *flag, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = (n + 255) / 256;
   if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(histogram_kernel, dim3((unsigned)blocks), dim3(256), 0, st, assign, n, cnt);
-  return hipGetLastError();
-}
-
-// sets *bad to 1 if any label is outside [0, k)
-__global__ void check_labels_kernel(const int32_t *a, int64_t n, int32_t k, unsigned int *bad) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    if (a[i] < 0 || a[i] >= k) *bad = 1u;
-}
-hipError_t launch_check_labels(const int32_t *a, int64_t n, int32_t k, unsigned int *bad, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(check_labels_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, n, k, bad);
+  hipLaunchKernelGGL(copy_labels_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, n, k, out, flag);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ centroid update
 int64_t update_max_segments(int64_t n, int32_t k) { return (int64_t)k + n / kSegPoints + 1; }
 
-// single workgroup: exclusive scans of the cluster sizes and of the segment counts
+// single workgroup: exclusive scans of the cluster sizes and of the segment counts.  Thread t takes the t-th contiguous
+// part; one scan over the parts (k = 32 768: 122 us with a scan per 1024 sizes, 14 us).  Also clears the word that the
+// means' largest magnitude is folded into later (zero, optional).
 __global__ void __launch_bounds__(1024) scan_counts_kernel(const int32_t *cnt, int32_t k, int32_t *off, int32_t *cursor,
-                                                           int32_t *segoff) {
-  __shared__ int s_a[1024], s_b[1024];
-  __shared__ int carry_a, carry_b;
-  if (threadIdx.x == 0) { carry_a = 0; carry_b = 0; }
+                                                           int32_t *segoff, unsigned int *zero) {
+  __shared__ int s_a[16], s_b[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (zero && tid == 0) *zero = 0u;
+  const int per = (k + 1023) / 1024;
+  const int lo = min(tid * per, k), hi = min(lo + per, k);
+  int va = 0, vb = 0;
+  for (int c = lo; c < hi; ++c) {
+    const int v = cnt[c];
+    va += v;
+    vb += (v + kSegPoints - 1) / kSegPoints;
+  }
+  int ia = va, ib = vb;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int ta = __shfl_up(ia, o, 64), tb = __shfl_up(ib, o, 64);
+    if (lane >= o) { ia += ta; ib += tb; }
+  }
+  if (lane == 63) { s_a[wave] = ia; s_b[wave] = ib; }
   __syncthreads();
-  for (int base = 0; base < k; base += 1024) {
-    const int c = base + threadIdx.x;
-    const int va = c < k ? cnt[c] : 0;
-    const int vb = (va + kSegPoints - 1) / kSegPoints;
-    s_a[threadIdx.x] = va;
-    s_b[threadIdx.x] = vb;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-      int ta = 0, tb = 0;
-      if ((int)threadIdx.x >= o) { ta = s_a[threadIdx.x - o]; tb = s_b[threadIdx.x - o]; }
-      __syncthreads();
-      s_a[threadIdx.x] += ta;
-      s_b[threadIdx.x] += tb;
-      __syncthreads();
-    }
-    if (c < k) {
-      off[c] = carry_a + s_a[threadIdx.x] - va;
-      segoff[c] = carry_b + s_b[threadIdx.x] - vb;
-      cursor[c] = 0;
-    }
-    __syncthreads();
-    if (threadIdx.x == 1023) { carry_a += s_a[1023]; carry_b += s_b[1023]; }
-    __syncthreads();
+  int ra = ia - va, rb = ib - vb;
+  for (int w = 0; w < wave; ++w) { ra += s_a[w]; rb += s_b[w]; }
+  for (int c = lo; c < hi; ++c) {
+    const int v = cnt[c];
+    off[c] = ra;
+    segoff[c] = rb;
+    cursor[c] = 0;
+    ra += v;
+    rb += (v + kSegPoints - 1) / kSegPoints;
   }
-  if (threadIdx.x == 0) { off[k] = carry_a; segoff[k] = carry_b; }
+  if (tid == 1023) { off[k] = ra; segoff[k] = rb; }
 }
 
-// order[...] = i (or ids[i] when the labelled items are a list of ids), grouped by label
-__global__ void scatter_order_kernel(const int32_t *assign, int64_t n, const int32_t *off, int32_t *cursor,
-                                     int32_t *order, const int32_t *ids) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int a = assign[i];
-    const int pos = off[a] + atomicAdd(cursor + a, 1);
-    order[pos] = ids ? ids[i] : (int32_t)i;
+// order[...] = i (or ids[i] when the labelled items are a list of ids), grouped by label.  With the counters in LDS a
+// workgroup takes the rank of each of its items among its own, reserves one range per label it holds, and writes (80 to
+// 217 us for a million points with a returning atomic per point, 20 us).  Items with a label outside [0, k) are skipped.
+constexpr int CNT_ITEMS = 8192 / CNT_THREADS;
+__global__ void __launch_bounds__(CNT_THREADS) scatter_order_kernel(const int32_t *assign, int64_t n, int32_t k,
+                                                                    const int32_t *off, int32_t *cursor, int32_t *order,
+                                                                    const int32_t *ids, int per_block, int in_lds) {
+  extern __shared__ int s_bins[];
+  const int64_t base = (int64_t)blockIdx.x * per_block;
+  if (!in_lds) {
+    for (int t = threadIdx.x; t < per_block; t += CNT_THREADS) {
+      const int64_t i = base + t;
+      if (i >= n) break;
+      const int a = assign[i];
+      if ((unsigned int)a >= (unsigned int)k) continue;
+      order[off[a] + atomicAdd(cursor + a, 1)] = ids ? ids[i] : (int32_t)i;
+    }
+    return;
   }
+  for (int b = threadIdx.x; b < k; b += CNT_THREADS) s_bins[b] = 0;
+  __syncthreads();
+  int lab[CNT_ITEMS], rank[CNT_ITEMS];
+#pragma unroll
+  for (int j = 0; j < CNT_ITEMS; ++j) {
+    const int t = j * CNT_THREADS + threadIdx.x;
+    const int64_t i = base + t;
+    lab[j] = -1;
+    rank[j] = 0;
+    if (t < per_block && i < n) {
+      const int a = assign[i];
+      if ((unsigned int)a < (unsigned int)k) {
+        lab[j] = a;
+        rank[j] = atomicAdd(s_bins + a, 1);
+      }
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < k; b += CNT_THREADS) {
+    const int v = s_bins[b];
+    if (v) s_bins[b] = off[b] + atomicAdd(cursor + b, v);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < CNT_ITEMS; ++j)
+    if (lab[j] >= 0) {
+      const int64_t i = base + j * CNT_THREADS + threadIdx.x;
+      order[s_bins[lab[j]] + rank[j]] = ids ? ids[i] : (int32_t)i;
+    }
+}
+static void launch_scatter_order(const int32_t *assign, int64_t n, int32_t k, const int32_t *off, int32_t *cursor,
+                                 int32_t *order, const int32_t *ids, hipStream_t st) {
+  const int per = count_per_block(n);
+  const int in_lds = count_in_lds(n, k);
+  hipLaunchKernelGGL(scatter_order_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(CNT_THREADS),
+                     in_lds ? (size_t)k * sizeof(int) : 0, st, assign, n, k, off, cursor, order, ids, per, in_lds);
 }
 
-// The cursor order above depends on scheduling; sorting every segment of `order` makes the
-// summation order, and with it every bit of the result, independent of it.  One workgroup per
-// cluster, odd-even merge in LDS for clusters up to SORT_CAP points; larger clusters are summed in
-// fp64 in whatever order they were scattered (the fp64 sum of fp32 values then differs from the
-// sorted-order sum by at most a few ulps of fp64, far below the fp32 rounding of the mean).
-constexpr int SORT_CAP = 8192;
+// The cursor order above depends on scheduling; sorting every segment of `order` makes the summation order, and with it
+// every bit of the result, independent of it.  One workgroup per cluster.  Up to RANK_CAP ids every thread counts the
+// smaller ids of its own (they are distinct, so the count is the position; 244 ids: 0.3 us of compares and two barriers
+// where a bitonic network crosses 36: 82 -> 20 us for 4096 clusters of a million points); above, up to SORT_CAP,
+// odd-even merge in LDS; larger clusters are summed in fp64 in whatever order they were scattered (the fp64 sum of fp32
+// values then differs from the sorted-order sum by at most a few ulps of fp64, far below the fp32 rounding of the mean).
+constexpr int SORT_CAP = 8192, RANK_CAP = 2048;
 int32_t update_sort_cap() { return SORT_CAP; }
+__global__ void __launch_bounds__(256) rank_segments_kernel(const int32_t *off, int32_t *order) {
+  __shared__ __align__(16) int32_t s[RANK_CAP];
+  const int c = blockIdx.x;
+  const int lo = off[c], len = off[c + 1] - lo;
+  if (len < 2 || len > RANK_CAP) return;
+  const int len4 = (len + 3) & ~3;
+  for (int t = threadIdx.x; t < len4; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
+  __syncthreads();
+  for (int t0 = 0; t0 < len; t0 += 1024) {   // four ids of its own per thread and pass over the list
+    int mine[4], rank[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 256 * u + threadIdx.x;
+      mine[u] = t < len ? s[t] : -0x7fffffff - 1;
+      rank[u] = 0;
+    }
+    const bool one = t0 + 256 >= len;   // only the first of the four is in use
+    for (int q = 0; q < len4; q += 4) {
+      const int4 o = *reinterpret_cast<const int4 *>(s + q);
+      rank[0] += (o.x < mine[0]) + (o.y < mine[0]) + (o.z < mine[0]) + (o.w < mine[0]);
+      if (!one)
+#pragma unroll
+        for (int u = 1; u < 4; ++u) rank[u] += (o.x < mine[u]) + (o.y < mine[u]) + (o.z < mine[u]) + (o.w < mine[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 256 * u + threadIdx.x;
+      if (t < len) order[lo + rank[u]] = mine[u];
+    }
+  }
+}
 __global__ void __launch_bounds__(256) sort_segments_kernel(const int32_t *off, int32_t *order) {
   __shared__ int32_t s[SORT_CAP];
   const int c = blockIdx.x;
   const int lo = off[c], len = off[c + 1] - lo;
-  if (len < 2 || len > SORT_CAP) return;
+  if (len <= RANK_CAP || len > SORT_CAP) return;
   int np2 = 1;
   while (np2 < len) np2 <<= 1;
   for (int t = threadIdx.x; t < np2; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
@@ -703,13 +926,21 @@ __global__ void __launch_bounds__(256) sort_segments_kernel(const int32_t *off, 
     }
   for (int t = threadIdx.x; t < len; t += 256) order[lo + t] = s[t];
 }
+// largest: size of the largest segment where the host knows it, -1 where it does not
+static void launch_sort_segments(const int32_t *off, int32_t *order, int32_t k, int64_t n, int32_t largest, hipStream_t st) {
+  const int64_t most = largest >= 0 ? largest : n;
+  if (most < 2) return;
+  hipLaunchKernelGGL(rank_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+  if (most > RANK_CAP) hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+}
 
 // One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
 // `order` (each a contiguous row read).  Wavefront w takes the points p0 + w, p0 + w + 4, ... of the segment, four
 // rows in flight per thread, fp64 sums per thread; the four wavefronts' sums are added in a fixed order, so the
 // result depends on the segment only.
 // SIGNED: an entry i >= 0 adds row i, an entry ~i < 0 subtracts row i (a point that left the cluster).
-template <bool SIGNED>
+// ALIGNED: rows are 16-byte aligned and a multiple of 4 long; otherwise a lane reads its four values one by one.
+template <bool SIGNED, bool ALIGNED>
 __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64_t ldx, int32_t ds, int32_t k,
                                                           const int32_t *off, const int32_t *segoff,
                                                           const int32_t *order, double *partial) {
@@ -733,7 +964,15 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
   auto row = [&](int raw, float4 &v, double &sg) {
     const int i = SIGNED && raw < 0 ? ~raw : raw;
     sg = SIGNED && raw < 0 ? -1.0 : 1.0;
-    v = *reinterpret_cast<const float4 *>(Xr + (int64_t)i * ldx + col);
+    const float *x = Xr + (int64_t)i * ldx + col;
+    if (ALIGNED) {
+      v = *reinterpret_cast<const float4 *>(x);
+    } else {
+      v.x = x[0];
+      v.y = col + 1 < ds ? x[1] : 0.f;
+      v.z = col + 2 < ds ? x[2] : 0.f;
+      v.w = col + 3 < ds ? x[3] : 0.f;
+    }
   };
   auto add = [&](const float4 &v, double sg) {
     if (SIGNED) {
@@ -770,9 +1009,9 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
   if (w == 0 && live) {
     double *dst = partial + (int64_t)seg * ds + col;
     dst[0] = (a0 + red[0][lane][0]) + (red[1][lane][0] + red[2][lane][0]);
-    dst[1] = (a1 + red[0][lane][1]) + (red[1][lane][1] + red[2][lane][1]);
-    dst[2] = (a2 + red[0][lane][2]) + (red[1][lane][2] + red[2][lane][2]);
-    dst[3] = (a3 + red[0][lane][3]) + (red[1][lane][3] + red[2][lane][3]);
+    if (ALIGNED || col + 1 < ds) dst[1] = (a1 + red[0][lane][1]) + (red[1][lane][1] + red[2][lane][1]);
+    if (ALIGNED || col + 2 < ds) dst[2] = (a2 + red[0][lane][2]) + (red[1][lane][2] + red[2][lane][2]);
+    if (ALIGNED || col + 3 < ds) dst[3] = (a3 + red[0][lane][3]) + (red[1][lane][3] + red[2][lane][3]);
   }
 }
 
@@ -783,8 +1022,14 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
 // that the split-fp16 GEMMs of the next step scale the centroids by.
 __global__ void __launch_bounds__(256) centroid_mean_kernel(const double *partial, int32_t ds, const int32_t *cnt,
                                                             const int32_t *segoff, float *Y, int64_t ldy, double *S,
-                                                            int accumulate, unsigned int *y_absmax) {
+                                                            int accumulate, unsigned int *y_absmax,
+                                                            const unsigned int *flag, unsigned int *flag_host) {
   const int c = blockIdx.x;
+  if (flag) {   // labels that the counting pass found outside [0, k): reported, and Y stays what it was
+    const unsigned int f = *flag;
+    if (c == 0 && blockIdx.y == 0 && threadIdx.x == 0) *flag_host = f;
+    if (f) return;
+  }
   const int n_c = cnt[c];
   const int col = blockIdx.y * 256 + threadIdx.x;
   float y = 0.f;
@@ -826,24 +1071,54 @@ __global__ void __launch_bounds__(256) means_from_sums_kernel(const double *S, c
 }
 hipError_t launch_means_from_sums(const double *S, const int32_t *cnt, int32_t k, int32_t ds, float *Y, int64_t ldy,
                                   unsigned int *y_absmax, hipStream_t st) {
-  if (y_absmax) {
-    hipError_t rc = hipMemsetAsync(y_absmax, 0, sizeof(unsigned int), st);
-    if (rc != hipSuccess) return rc;
-  }
+  if (y_absmax)
+    if (hipError_t rc = launch_fill_u32(y_absmax, 1, 0u, st); rc != hipSuccess) return rc;
   hipLaunchKernelGGL(means_from_sums_kernel, dim3(k, (unsigned)((ds + 255) / 256)), dim3(256), 0, st, S, cnt, ds, Y, ldy,
                      y_absmax);
   return hipGetLastError();
 }
 
-// Points whose label changed: entry (i, new label) and entry (~i, old label), in any order (the segments are
-// sorted afterwards).  *counter must be 0; entries past `cap` are dropped and show in the final *counter.
+// total[c] += cnt[c] (sizes of the batches of a pass)
+__global__ void add_counts_kernel(const int32_t *cnt, int32_t k, int32_t *total) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < k) total[c] += cnt[c];
+}
+hipError_t launch_add_counts(const int32_t *cnt, int32_t k, int32_t *total, hipStream_t st) {
+  hipLaunchKernelGGL(add_counts_kernel, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, st, cnt, k, total);
+  return hipGetLastError();
+}
+
+// Points whose label changed: entry (i, new label) and entry (~i, old label), in ascending order of i.  start[b] is the
+// number of changed points before the points of workgroup b (the ranges of the finalize kernel, which took them).  A
+// wavefront owns a contiguous quarter of the workgroup's points: one pass counts, one writes, no atomics.  Also clears
+// what the kernels behind it add to: `zero` (one word) and zero_cnt[k].
 __global__ void __launch_bounds__(256) compact_changes_kernel(const int32_t *assign, const int32_t *prev, int64_t n,
-                                                              int32_t *ent_id, int32_t *ent_lab, unsigned int *counter,
-                                                              unsigned int cap) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int a = assign[i], b = prev[i];
+                                                              const int32_t *start, int per_block, int32_t *ent_id,
+                                                              int32_t *ent_lab, unsigned int cap, unsigned int *zero,
+                                                              int32_t *zero_cnt, int32_t k) {
+  __shared__ int s_cnt[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0 && tid == 0 && zero) *zero = 0u;
+  if (zero_cnt)
+    for (int64_t c = (int64_t)blockIdx.x * 256 + tid; c < k; c += (int64_t)gridDim.x * 256) zero_cnt[c] = 0;
+  const int quarter = per_block / 4;
+  const int64_t base = (int64_t)blockIdx.x * per_block + (int64_t)wave * quarter;
+  int mine = 0;
+  for (int t = 0; t < quarter; t += 64) {
+    const int64_t i = base + t + lane;
+    mine += __popcll(__ballot(i < n && assign[i] != prev[i]));
+  }
+  if (lane == 0) s_cnt[wave] = mine;
+  __syncthreads();
+  if (mine == 0) return;
+  unsigned int run = (unsigned int)start[blockIdx.x];
+  for (int w = 0; w < wave; ++w) run += (unsigned int)s_cnt[w];
+  for (int t = 0; t < quarter; t += 64) {
+    const int64_t i = base + t + lane;
+    const int a = i < n ? assign[i] : 0, b = i < n ? prev[i] : 0;
+    const unsigned long long bal = __ballot(a != b);
     if (a != b) {
-      const unsigned int e = atomicAdd(counter, 2u);
+      const unsigned int e = 2u * (run + (unsigned int)__popcll(bal & ((1ull << lane) - 1ull)));
       if (e + 2u <= cap) {
         ent_id[e] = (int32_t)i;
         ent_lab[e] = a;
@@ -851,29 +1126,100 @@ __global__ void __launch_bounds__(256) compact_changes_kernel(const int32_t *ass
         ent_lab[e + 1] = b;
       }
     }
+    run += (unsigned int)__popcll(bal);
   }
+}
+
+// The whole of a small incremental update behind the compaction: the workgroup of (cluster, slice of 256 dims) looks
+// through all m entries, keeps those of its cluster in their order, adds the rows that joined and subtracts those that
+// left, and writes the sum and the mean.  Every workgroup reads the m labels (from L2): worth it while
+// m * workgroups stays below kDirectUpdate labels; it replaces the counting, scan, scatter, sort, segment-sum and mean
+// kernels, whose launches are all the time of an update in which a few points moved (35 -> 12 us).
+constexpr int64_t kDirectUpdate = (int64_t)1 << 25;
+constexpr int DIRECT_CHUNK = 1024;
+__global__ void __launch_bounds__(256) direct_update_kernel(const float *Xr, int64_t ldx, int32_t ds, const int32_t *ent_id,
+                                                            const int32_t *ent_lab, int m, const int32_t *cnt, double *S,
+                                                            float *Y, int64_t ldy, unsigned int *y_absmax) {
+  __shared__ int s_ids[DIRECT_CHUNK];
+  __shared__ int s_w[4];
+  __shared__ double red[3][64][4];
+  const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int col = (blockIdx.y * 64 + lane) * 4;
+  const bool live = col < ds;
+  double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+  bool any = false;
+  for (int e0 = 0; e0 < m; e0 += DIRECT_CHUNK) {
+    // thread t holds entries e0 + 256 j + t: matches in order of (j, wavefront, lane)
+    int have = 0;
+    for (int j = 0; j < DIRECT_CHUNK / 256; ++j) {
+      const int e = e0 + 256 * j + tid;
+      const bool hit = e < m && ent_lab[e] == c;
+      const unsigned long long bal = __ballot(hit);
+      if (lane == 0) s_w[w] = __popcll(bal);
+      __syncthreads();
+      int at = have;
+      for (int u = 0; u < w; ++u) at += s_w[u];
+      if (hit) s_ids[at + __popcll(bal & ((1ull << lane) - 1ull))] = ent_id[e];
+      have += (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
+      __syncthreads();
+    }
+    any |= have > 0;
+    if (live)
+      for (int p = w; p < have; p += 4) {
+        const int raw = s_ids[p];
+        const int i = raw < 0 ? ~raw : raw;
+        const double sg = raw < 0 ? -1.0 : 1.0;
+        const float4 v = *reinterpret_cast<const float4 *>(Xr + (int64_t)i * ldx + col);
+        a0 += sg * (double)v.x; a1 += sg * (double)v.y; a2 += sg * (double)v.z; a3 += sg * (double)v.w;
+      }
+    if (have) __syncthreads();
+  }
+  if (any) {
+    if (w > 0) {
+      red[w - 1][lane][0] = a0; red[w - 1][lane][1] = a1; red[w - 1][lane][2] = a2; red[w - 1][lane][3] = a3;
+    }
+    __syncthreads();
+  }
+  float vmax = 0.f;
+  if (w == 0 && live) {
+    double d[4] = {a0, a1, a2, a3};
+    const int n_c = cnt[c];
+    double *sp = S + (int64_t)c * ds + col;
+    float *yp = Y + (int64_t)c * ldy + col;
+    float4 y = *reinterpret_cast<const float4 *>(yp);
+    float *ye = &y.x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      double s = sp[u];
+      if (any) {
+        s += (d[u] + red[0][lane][u]) + (red[1][lane][u] + red[2][lane][u]);
+        sp[u] = s;
+      }
+      if (n_c != 0) ye[u] = (float)(s / (double)n_c);   // an empty cluster keeps its centroid until the split
+      vmax = fmaxf(vmax, fabsf(ye[u]));
+    }
+    *reinterpret_cast<float4 *>(yp) = y;
+  }
+  if (y_absmax) block_absmax(vmax, y_absmax);
 }
 
 hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, int32_t k,
                          const UpdateWs &w, float *Y, int64_t ldy, hipStream_t st, double *S, unsigned int *y_absmax,
-                         int accumulate) {
-  if ((accumulate && !S) || (!Y && y_absmax)) return hipErrorInvalidValue;
-  if (y_absmax) {
-    hipError_t rc = hipMemsetAsync(y_absmax, 0, sizeof(unsigned int), st);
-    if (rc != hipSuccess) return rc;
-  }
-  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, w.cnt, k, w.off, w.cursor, w.segoff);
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(scatter_order_kernel, dim3((unsigned)blocks), dim3(256), 0, st, assign, n, w.off, w.cursor,
-                     w.order, (const int32_t *)nullptr);
-  hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, w.off, w.order);
-  const unsigned slices4 = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims per workgroup
-  hipLaunchKernelGGL(segment_sum_kernel<false>, dim3((unsigned)w.max_segments, slices4), dim3(256), 0, st, Xr, ldx, ds, k,
-                     w.off, w.segoff, w.order, w.partial);
-  const unsigned slices1 = (unsigned)((ds + 255) / 256);
-  hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices1), dim3(256), 0, st, w.partial, ds, w.cnt, w.segoff, Y, ldy, S,
-                     accumulate, y_absmax);
+                         int accumulate, int32_t largest, const unsigned int *flag, unsigned int *flag_host) {
+  if ((accumulate && !S) || (!Y && y_absmax) || (flag != nullptr) != (flag_host != nullptr)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, w.cnt, k, w.off, w.cursor, w.segoff, y_absmax);
+  launch_scatter_order(assign, n, k, w.off, w.cursor, w.order, nullptr, st);
+  launch_sort_segments(w.off, w.order, k, n, largest, st);
+  const unsigned slices = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims, or 256 dims, per workgroup
+  const bool aligned = (reinterpret_cast<uintptr_t>(Xr) & 15u) == 0 && ldx % 4 == 0 && ds % 4 == 0;
+  if (aligned)
+    hipLaunchKernelGGL((segment_sum_kernel<false, true>), dim3((unsigned)w.max_segments, slices), dim3(256), 0, st, Xr, ldx, ds,
+                       k, w.off, w.segoff, w.order, w.partial);
+  else
+    hipLaunchKernelGGL((segment_sum_kernel<false, false>), dim3((unsigned)w.max_segments, slices), dim3(256), 0, st, Xr, ldx,
+                       ds, k, w.off, w.segoff, w.order, w.partial);
+  hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, w.partial, ds, w.cnt, w.segoff, Y, ldy, S,
+                     accumulate, y_absmax, flag, flag_host);
   return hipGetLastError();
 }
 
@@ -883,56 +1229,45 @@ hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32
                               int32_t *segoff, int32_t *order, hipStream_t st) {
   hipError_t rc = launch_fill_u32(reinterpret_cast<unsigned int *>(cnt), k, 0u, st);
   if (rc != hipSuccess) return rc;
-  rc = launch_histogram(labels, n, cnt, st);
+  rc = launch_histogram(labels, n, k, cnt, nullptr, st);
   if (rc != hipSuccess) return rc;
-  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, cnt, k, off, cursor, segoff);
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(scatter_order_kernel, dim3((unsigned)blocks), dim3(256), 0, st, labels, n, off, cursor, order,
-                     (const int32_t *)nullptr);
-  hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, cnt, k, off, cursor, segoff, (unsigned int *)nullptr);
+  launch_scatter_order(labels, n, k, off, cursor, order, nullptr, st);
+  launch_sort_segments(off, order, k, n, -1, st);
   return hipGetLastError();
 }
 
 // The same update from the points that changed label only: S (the cluster sums of the previous update) takes the
 // rows of the points that joined minus those of the points that left, and every centroid is S / size again.
 // w.cnt holds the new cluster sizes; `changed` is the number of points with assign != prev (known to the host from
-// the assignment step), inc is a workspace for 2 * changed entries.
+// the assignment step) and change_start what the finalize kernel left; inc is a workspace for 2 * changed entries.
 hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign,
-                                     const int32_t *prev, int64_t changed, int32_t k, const UpdateWs &w,
-                                     const IncUpdateWs &inc, double *S, float *Y, int64_t ldy, hipStream_t st,
-                                     unsigned int *y_absmax) {
+                                     const int32_t *prev, int64_t changed, const int32_t *change_start, int32_t k,
+                                     const UpdateWs &w, const IncUpdateWs &inc, double *S, float *Y, int64_t ldy,
+                                     hipStream_t st, unsigned int *y_absmax) {
   const int64_t m2 = 2 * changed;
-  if (m2 > inc.capacity || !S) return hipErrorInvalidValue;
-  hipError_t rc = hipMemsetAsync(inc.counter, 0, sizeof(unsigned int), st);
+  if (m2 <= 0 || m2 > inc.capacity || !S) return hipErrorInvalidValue;
+  const unsigned slices = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims, or 256 dims, per workgroup
+  const bool direct = m2 * (int64_t)k * slices <= kDirectUpdate;
+  hipLaunchKernelGGL(compact_changes_kernel, dim3((unsigned)finalize_blocks(n)), dim3(256), 0, st, assign, prev, n,
+                     change_start, finalize_per_block(n), inc.ent_id, inc.ent_lab, (unsigned int)inc.capacity, y_absmax,
+                     direct ? (int32_t *)nullptr : inc.cnt, k);
+  if (direct) {
+    hipLaunchKernelGGL(direct_update_kernel, dim3(k, slices), dim3(256), 0, st, Xr, ldx, ds, (const int32_t *)inc.ent_id,
+                       (const int32_t *)inc.ent_lab, (int)m2, w.cnt, S, Y, ldy, y_absmax);
+    return hipGetLastError();
+  }
+  hipError_t rc = launch_histogram(inc.ent_lab, m2, k, inc.cnt, nullptr, st);
   if (rc != hipSuccess) return rc;
-  if (y_absmax) {
-    rc = hipMemsetAsync(y_absmax, 0, sizeof(unsigned int), st);
-    if (rc != hipSuccess) return rc;
-  }
-  rc = hipMemsetAsync(inc.cnt, 0, sizeof(int32_t) * (size_t)k, st);
-  if (rc != hipSuccess) return rc;
-  int64_t blocks = std::min<int64_t>((n + 255) / 256, 16384);
-  hipLaunchKernelGGL(compact_changes_kernel, dim3((unsigned)blocks), dim3(256), 0, st, assign, prev, n, inc.ent_id,
-                     inc.ent_lab, inc.counter, (unsigned int)inc.capacity);
-  if (m2 > 0) {
-    rc = launch_histogram(inc.ent_lab, m2, inc.cnt, st);
-    if (rc != hipSuccess) return rc;
-  }
-  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, inc.cnt, k, inc.off, inc.cursor, inc.segoff);
-  if (m2 > 0) {
-    blocks = std::min<int64_t>((m2 + 255) / 256, 16384);
-    hipLaunchKernelGGL(scatter_order_kernel, dim3((unsigned)blocks), dim3(256), 0, st, inc.ent_lab, m2, inc.off, inc.cursor,
-                       inc.order, (const int32_t *)inc.ent_id);
-    hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, inc.off, inc.order);
-    const unsigned slices4 = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims per workgroup
-    const int64_t segs = std::min<int64_t>(inc.max_segments, (int64_t)k + m2 / kSegPoints + 1);
-    hipLaunchKernelGGL(segment_sum_kernel<true>, dim3((unsigned)segs, slices4), dim3(256), 0, st, Xr, ldx, ds, k, inc.off,
-                       inc.segoff, inc.order, inc.partial);
-  }
-  const unsigned slices1 = (unsigned)((ds + 255) / 256);
-  hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices1), dim3(256), 0, st, inc.partial, ds, w.cnt, inc.segoff, Y, ldy,
-                     S, 1, y_absmax);
+  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, inc.cnt, k, inc.off, inc.cursor, inc.segoff,
+                     (unsigned int *)nullptr);
+  launch_scatter_order(inc.ent_lab, m2, k, inc.off, inc.cursor, inc.order, inc.ent_id, st);
+  launch_sort_segments(inc.off, inc.order, k, m2, -1, st);
+  const int64_t segs = std::min<int64_t>(inc.max_segments, (int64_t)k + m2 / kSegPoints + 1);
+  hipLaunchKernelGGL((segment_sum_kernel<true, true>), dim3((unsigned)segs, slices), dim3(256), 0, st, Xr, ldx, ds, k, inc.off,
+                     inc.segoff, inc.order, inc.partial);
+  hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, inc.partial, ds, w.cnt, inc.segoff, Y, ldy,
+                     S, 1, y_absmax, (const unsigned int *)nullptr, (unsigned int *)nullptr);
   return hipGetLastError();
 }
 
@@ -963,14 +1298,53 @@ hipError_t launch_split(float *Y, int64_t ldy, int32_t d, const int32_t *pairs_d
 
 // ------------------------------------------------------------------ small copies
 __global__ void __launch_bounds__(256) gather_rows_kernel(const float *src, int64_t lds, int32_t d,
-                                                          const int64_t *idx, float *dst, int64_t ldd, int32_t dpad) {
+                                                          const int64_t *idx, float *dst, int64_t ldd, int32_t dpad,
+                                                          unsigned int *absmax) {
   const int c = blockIdx.x;
   const float *s = src + idx[c] * lds;
-  for (int j = threadIdx.x; j < dpad; j += 256) dst[(int64_t)c * ldd + j] = j < d ? s[j] : 0.f;
+  float m = 0.f;
+  for (int j = threadIdx.x; j < dpad; j += 256) {
+    const float v = j < d ? s[j] : 0.f;
+    dst[(int64_t)c * ldd + j] = v;
+    m = fmaxf(m, fabsf(v));
+  }
+  if (absmax) block_absmax(m, absmax);
 }
-hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx_dev, int32_t k, float *dst,
-                              int64_t ldd, int32_t dpad, hipStream_t st) {
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(k), dim3(256), 0, st, src, lds, d, idx_dev, dst, ldd, dpad);
+hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx, int32_t k, float *dst,
+                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax) {
+  hipLaunchKernelGGL(gather_rows_kernel, dim3(k), dim3(256), 0, st, src, lds, d, idx, dst, ldd, dpad, absmax);
+  return hipGetLastError();
+}
+
+// Both padded copies of the rotation matrix, the transposed one through a 32 x 33 tile in LDS, and its largest magnitude
+// in one pass (a copy each and a pass for the bound before: with d = 128 three launches of 4 us for 64 KB).
+__global__ void __launch_bounds__(256) rotation_operands_kernel(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld,
+                                                                unsigned int *absmax) {
+  __shared__ float s_t[32][33];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+  float m = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = r0 + ty + 8 * u, c = c0 + tx;
+    const float v = r < d && c < d ? R[(int64_t)r * d + c] : 0.f;
+    s_t[ty + 8 * u][tx] = v;
+    m = fmaxf(m, fabsf(v));
+    if (Rp && r < d && c < ld) Rp[(int64_t)r * ld + c] = v;
+  }
+  __syncthreads();
+  if (Rtp)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {   // row c0 + .. of R^T
+      const int r = c0 + ty + 8 * u, c = r0 + tx;
+      if (r < d && c < ld) Rtp[(int64_t)r * ld + c] = s_t[tx][ty + 8 * u];
+    }
+  block_absmax(m, absmax);
+}
+hipError_t launch_rotation_operands(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld, unsigned int *absmax,
+                                    hipStream_t st) {
+  const unsigned t = (unsigned)((ld + 31) / 32);
+  hipLaunchKernelGGL(rotation_operands_kernel, dim3(t, t), dim3(256), 0, st, R, d, Rp, Rtp, ld, absmax);
   return hipGetLastError();
 }
 

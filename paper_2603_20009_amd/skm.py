@@ -62,7 +62,7 @@ EXPORTS = [
     "skm_make_rotation", "skm_rotate", "skm_sample_rows", "skm_theta_ratio", "skm_dprime_init", "skm_dprime_adjust",
     "skm_strerror", "skm_last_error", "skm_version", "skm_fit_hierarchical", "skm_hier_meso_count", "skm_hier_alloc",
     "skm_fit_host", "skm_workspace_bytes", "skm_hier_workspace_bytes", "skm_debug_gemm_config",
-    "skm_assign_exact_static", "skm_etr_ground_truth",
+    "skm_assign_exact_static", "skm_etr_ground_truth", "skm_release_memory",
 ]
 
 _lib = None
@@ -112,6 +112,8 @@ def lib():
         L.skm_dprime_init.restype = i32
         L.skm_dprime_adjust.argtypes = [i32, i32, C.c_double, f32, f32, f32]
         L.skm_dprime_adjust.restype = i32
+        L.skm_release_memory.argtypes = []
+        L.skm_release_memory.restype = None
         for f in ("skm_strerror", "skm_last_error", "skm_version"):
             getattr(L, f).restype = C.c_char_p
         L.skm_strerror.argtypes = [C.c_int]
@@ -193,7 +195,7 @@ def _row_dict(r: TraceRow) -> dict:
                 dense_dims=int(r.dense_dims), dense_pair_blocks=int(r.dense_pair_blocks),
                 gather_pair_blocks=int(r.gather_pair_blocks), gather_pairs=int(r.gather_pairs),
                 screen_dims=int(r.screen_dims), listed_tiles=int(r.listed_tiles), dprime=int(r.dprime),
-                nblocks=int(r.nblocks), enter=[int(v) for v in r.enter], ms_tau=r.ms_tau, ms_gemm=r.ms_gemm,
+                nblocks=int(r.nblocks), enter=r.enter[:], ms_tau=r.ms_tau, ms_gemm=r.ms_gemm,
                 ms_prune=r.ms_prune, ms_update=r.ms_update, ms_etr=r.ms_etr, ms_step=r.ms_step)
 
 
@@ -474,6 +476,11 @@ def dprime_adjust(d: int, dprime: int, f: float, lo=0.95, hi=0.97, step=0.20) ->
 def debug_gemm_config(tile256: int = -1, panel_cols: int = 0, max_tiles: int = 0):
     """skm_debug_gemm_config: force launch choices of the GEMM kernels (tests); no arguments = defaults."""
     lib().skm_debug_gemm_config(tile256, panel_cols, max_tiles)
+
+
+def release_memory() -> None:
+    """skm_release_memory: gives the device blocks that calls without a lent workspace keep back to the device."""
+    lib().skm_release_memory()
 
 
 def version() -> str:
