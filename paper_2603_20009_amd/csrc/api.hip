@@ -548,6 +548,7 @@ struct Ctx {
   int close_step() {
     FinalizeArgs f{best, prev_counts ? prev : nullptr, n, assign, dist, up.cnt, k, flag};
     f.done = done; f.obj_partial = obj_partial; f.change_start = change_start; f.scal = scal; f.report = report_dev;
+    f.nscal = block_stats ? SC_COUNT : SC_ENTER;   // (the counters per block are zero otherwise)
     HIPCHK(launch_finalize_assign(f, st));
     pending = true;
     return SKM_OK;
@@ -1091,7 +1092,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   ss.listed_tiles = (int64_t)scal_h[SC_LISTED_TILES];
   c.last_prune_frac = c.k > 1 ? 1.0 - (double)ss.survivors / ((double)c.n * (double)(c.k - 1)) : -1.0;
   ++c.pruned_steps;
-  for (int m = 0; m < std::min<int>(nb, SKM_MAX_BLOCKS); ++m) ss.enter[m] = (int64_t)scal_h[SC_ENTER + (size_t)m];
+  if (c.block_stats)
+    for (int m = 0; m < std::min<int>(nb, SKM_MAX_BLOCKS); ++m) ss.enter[m] = (int64_t)scal_h[SC_ENTER + (size_t)m];
   ss.objective = c.report->objective;
   ss.dprime = dprime;
   ss.nblocks = nb;
@@ -1295,7 +1297,9 @@ struct Rot {
     return SKM_OK;
   }
 };
-int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const float *R_dev, uint64_t seed, Rot &rot) {
+// (back = false: nothing will be rotated back, Rp is not made)
+int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const float *R_dev, uint64_t seed, Rot &rot,
+                   bool back = true) {
   if (int rc = rot.alloc_bounds(pool, st)) return rc;
   float *Rown = nullptr;
   if (!R_dev) {
@@ -1304,7 +1308,7 @@ int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const floa
     if (rc) return rc;
     R_dev = Rown;
   }
-  HIPCHK(pool.get(&rot.Rp, (size_t)d * ds));
+  if (back) HIPCHK(pool.get(&rot.Rp, (size_t)d * ds));
   HIPCHK(pool.get(&rot.Rtp, (size_t)d * ds));
   if (d % 32 == 0) HIPCHK(pool.get(&rot.Rs, (size_t)d * ((size_t)d + 32)));
   HIPCHK(launch_rotation_operands(R_dev, d, rot.Rp, rot.Rtp, ds, rot.amax, st));
@@ -1955,7 +1959,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   rc = c.alloc_common(p.pair_budget, p.dense_frac, false);
   if (rc) return rc;
   if (p.rotate) {
-    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, 0, rot);
+    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, 0, rot, false);
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR);

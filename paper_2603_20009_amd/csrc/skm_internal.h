@@ -290,6 +290,7 @@ struct FinalizeArgs {
   double *obj_partial = nullptr;      // [finalize_blocks(n)]
   int32_t *change_start = nullptr;    // [finalize_blocks(n)] changed points before the points of each workgroup
   const unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]
+  int nscal = SC_COUNT;               // scalars to report
   StepReport *report = nullptr;       // device-visible address of the page-locked block
 };
 hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st);

@@ -664,8 +664,9 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     }
   }
   StepReport *r = a.report;
-  for (int q = tid; q < SC_COUNT; q += FIN_THREADS) {
+  for (int q = tid; q < a.nscal; q += FIN_THREADS) {
     unsigned long long v = 0;
+#pragma unroll 8
     for (int rep = 0; rep < kStatReplicas; ++rep) v += load_agent(a.scal + (size_t)rep * SC_COUNT + q);
     if (q == SC_CHANGED) v = (unsigned long long)s_hist[FIN_THREADS - 1];
     r->scal[q] = v;
