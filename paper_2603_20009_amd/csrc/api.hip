@@ -259,43 +259,102 @@ struct Events {
   }
 };
 
-// Records (stage, event) marks on the stream; once the stream has been synchronised the time between two consecutive
-// marks of a step is charged to the stage of the later mark.  Nothing waits for a step's marks: a fit reads those of all
-// its steps at its end.
+// Stage times of a call: stamps that kernels at the stages' borders write into page-locked memory (put_stamp).  The time
+// between two consecutive marks of a step is charged to the stage of the later mark; all of them are read once the
+// stream has been waited for.
 enum Stage { ST_NONE = 0, ST_TAU, ST_GEMM, ST_PRUNE, ST_UPDATE, ST_ETR, ST_COUNT };
 struct StageTimer {
-  Events pool;
-  std::vector<std::pair<int, hipEvent_t>> marks;
-  std::vector<size_t> first;   // first mark of every step
-  hipStream_t st;
   bool on;
-  StageTimer(hipStream_t s, bool enable) : st(s), on(enable) {}
-  void begin_step() { first.push_back(marks.size()); }
-  void mark(int stage) {
-    if (!on) return;
-    const size_t used = marks.size();
-    hipEvent_t e = used < pool.ev.size() ? pool.ev[used] : pool.next();
-    if (!e) return;
-    (void)hipEventRecord(e, st);
-    marks.push_back({stage, e});
+  void *block = nullptr;
+  size_t block_bytes = 0, cap = 0, used = 0;
+  volatile stamp_t *host = nullptr;
+  stamp_t *dev = nullptr;
+  double ms_per_tick = 1e-5;
+  std::vector<std::pair<int, size_t>> marks;   // (stage, stamp)
+  std::vector<size_t> first;                   // first mark of every step
+  explicit StageTimer(bool enable) : on(enable) {}
+  StageTimer(const StageTimer &) = delete;
+  StageTimer &operator=(const StageTimer &) = delete;
+  ~StageTimer() {
+    if (block) tl_pinned.give(block, block_bytes);
   }
-  // times of step q (call after the stream is synchronised)
+  // room for so many stamps (further ones are not taken)
+  int init(size_t stamps) {
+    if (!on) return SKM_OK;
+    static const double tick = []() {
+      int dev_id = 0, khz = 0;
+      (void)hipGetDevice(&dev_id);
+      if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev_id) != hipSuccess || khz <= 0) khz = 100000;
+      return 1.0 / khz;
+    }();
+    ms_per_tick = tick;
+    cap = std::min<size_t>(stamps, (size_t)1 << 17);
+    block = tl_pinned.take(cap * sizeof(stamp_t), &block_bytes);
+    void *dv = nullptr;
+    if (!block || hipHostGetDevicePointer(&dv, block, 0) != hipSuccess) return fail(SKM_EHIP, "hipHostMalloc failed for the stage times");
+    host = static_cast<volatile stamp_t *>(block);
+    dev = static_cast<stamp_t *>(dv);
+    std::memset(block, 0, cap * sizeof(stamp_t));
+    return SKM_OK;
+  }
+  // a stamp on its own (*at = its number)
+  stamp_t *point(size_t *at) {
+    *at = next();
+    return on && *at < cap ? dev + *at : nullptr;
+  }
+  // The border lies where the next kernel that carries a stamp starts: that stamp serves for both.
+  static constexpr size_t kNone = ~(size_t)0;
+  size_t waiting = kNone;
+  size_t next() {
+    const size_t at = waiting != kNone ? waiting : used++;
+    waiting = kNone;
+    return at;
+  }
+  void mark_next(int stage) {
+    if (!on || used >= cap) return;
+    waiting = used++;
+    marks.push_back({stage, waiting});
+  }
+  void point_next(size_t *at) {
+    if (waiting == kNone) waiting = used++;
+    *at = waiting;
+  }
+  // ... and no such kernel follows
+  hipError_t flush(hipStream_t st) {
+    const size_t at = waiting;
+    waiting = kNone;
+    return on && at < cap ? launch_stamp(dev + at, st) : hipSuccess;
+  }
+  void begin_step() { first.push_back(marks.size()); }
+  // the border that ends a stretch of `stage` (and starts the next)
+  stamp_t *mark(int stage) {
+    const size_t at = next();
+    if (!on || at >= cap) return nullptr;
+    marks.push_back({stage, at});
+    return dev + at;
+  }
+  // (call these after the stream has been waited for)
+  float between(size_t a, size_t b) const {
+    if (!on || a >= cap || b >= cap || host[a] == 0 || host[b] <= host[a]) return 0.f;
+    return (float)((double)(host[b] - host[a]) * ms_per_tick);
+  }
   void collect(size_t q, float ms[ST_COUNT], float *total) const {
     for (int s = 0; s < ST_COUNT; ++s) ms[s] = 0.f;
     *total = 0.f;
     if (q >= first.size()) return;
     const size_t end = q + 1 < first.size() ? first[q + 1] : marks.size();
     for (size_t i = first[q] + 1; i < end; ++i) {
-      float t = 0.f;
-      if (hipEventElapsedTime(&t, marks[i - 1].second, marks[i].second) == hipSuccess) {
-        ms[marks[i].first] += t;
-        *total += t;
-      }
+      const float t = between(marks[i - 1].second, marks[i].second);
+      ms[marks[i].first] += t;
+      *total += t;
     }
   }
-  void reset() {   // the events are used again
+  void reset() {   // the stamps are used again
     marks.clear();
     first.clear();
+    if (block) std::memset(block, 0, std::min(used, cap) * sizeof(stamp_t));
+    used = 0;
+    waiting = kNone;
   }
 };
 
@@ -545,9 +604,10 @@ struct Ctx {
     return SKM_OK;
   }
   // the last kernel of a step, and the wait for it
-  int close_step() {
+  int close_step(stamp_t *start = nullptr, stamp_t *end = nullptr) {
     FinalizeArgs f{best, prev_counts ? prev : nullptr, n, assign, dist, up.cnt, k, flag};
     f.done = done; f.obj_partial = obj_partial; f.change_start = change_start; f.scal = scal; f.report = report_dev;
+    f.stamp = start; f.stamp_end = end;
     f.nscal = block_stats ? SC_COUNT : SC_ENTER;   // (the counters per block are zero otherwise)
     HIPCHK(launch_finalize_assign(f, st));
     pending = true;
@@ -561,9 +621,9 @@ struct Ctx {
   }
   bool prev_counts = true;                 // changed points are counted against prev (false in the exact step)
 
-  int alloc_bounds() {
+  int alloc_bounds(stamp_t *stamp = nullptr) {
     HIPCHK(pool.get(&amax, (size_t)AM_COUNT));
-    if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT, 0u, st));
+    if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT, 0u, st, stamp));
     return SKM_OK;
   }
   int measure_xr() { return measure_absmax(Xr, ldx, n, ds, amax + AM_XR, st); }
@@ -811,15 +871,17 @@ struct StepStats {
 // kernel takes their distances.  K = ds: the nearest centroid; K = d': the incumbent of a step that comes without one.
 // Clears the step's counters; clobbers ynorm, Ypdx, Ys / Yh, ratio_dev, tau; sets bit 0 of the step's flag word if the
 // candidate list overflowed.
-int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
+int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
   const int32_t nbK = (K + kBlockDims - 1) / kBlockDims;
   if (nbK > kMaxBlocks) return fail(SKM_EINTERNAL, "too many blocks");
+  stamp_t *start = tm.mark(ST_NONE);
   if (!c.xnp_valid) {
     // the points' split copy, its hi plane and their norms do not exist before the first pruned step: the pass that
     // writes them runs now (its thresholds, against centroid 0, are discarded)
     HIPCHK(launch_fill_u32(reinterpret_cast<unsigned int *>(c.prev), c.n, 0u, c.st));
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, nullptr, c.st, c.xnp, c.Xs,
-                           c.amax + Ctx::AM_XR, nullptr, nullptr, nullptr, c.Xh));
+                           c.amax + Ctx::AM_XR, nullptr, nullptr, nullptr, c.Xh, nullptr, start));
+    start = nullptr;
     c.xnp_valid = true;
   }
   // ||y[0 : K)||^2 and the block-major copy of the first K dimensions, zero filled behind them (the gather kernel
@@ -832,12 +894,12 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
   cp.dprime = 0; cp.nb = nbK; cp.Ypdx = c.Ypdx; cp.pdx_cols = K;
   cp.Ys = c.Ys; cp.Yh = c.Yh; cp.y_absmax = c.amax + Ctx::AM_Y;
   cp.ratio_out = c.ratio_dev;
+  cp.stamp = start;
   c.clear_with(cp);
   HIPCHK(launch_prep_centroids(cp, c.st, ratio, nbK + 1));
   HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   unsigned int *rowmin = reinterpret_cast<unsigned int *>(c.tau);   // (no thresholds while this runs)
   HIPCHK(launch_fill_u32(rowmin, c.n, 0xffffffffu, c.st));
-  if (tm) tm->mark(ST_TAU);
   for (int32_t ch = 0; ch < c.nchunks; ++ch) {
     const int64_t r0 = (int64_t)ch * c.chunk_rows;
     const int64_t rows = std::min<int64_t>(c.chunk_rows, c.n - r0);
@@ -856,6 +918,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
     sl.scal = c.scal;
     sl.exact = 1; sl.rowmin = rowmin; sl.pairs = c.pairs; sl.pair_count = fill; sl.sub_capacity = (unsigned int)c.sub_cap;
     sl.overflow = c.flag;
+    if (ch == 0) sl.stamp = tm.mark(ST_TAU);
     HIPCHK(launch_screen(sl, c.st));
     PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, 0, K, nbK, c.ratio_dev,
                  c.best, c.scal, 0};
@@ -865,15 +928,13 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer *tm = nullptr) {
 }
 
 int step_exact_filtered(Ctx &c, StageTimer &tm, StepStats &ss) {
-  tm.mark(ST_NONE);
-  if (int rc = filtered_nearest(c, c.ds, &tm)) return rc;
-  tm.mark(ST_GEMM);
+  if (int rc = filtered_nearest(c, c.ds, tm)) return rc;
   // the packed minima already hold the direct distances
   c.prev_counts = false;
-  int rc = c.close_step();
+  stamp_t *fin = tm.mark(ST_GEMM);
+  int rc = c.close_step(fin, tm.mark(ST_TAU));
   c.prev_counts = true;
   if (rc) return rc;
-  tm.mark(ST_TAU);
   if ((rc = c.wait_step())) return rc;
   ss = StepStats();
   ss.gather_pair_blocks = (int64_t)c.report->scal[SC_GATHER_PB];
@@ -896,9 +957,9 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
     }
     c.exact_filter_off = true;   // the candidate list overflowed (never with the default capacities): the full GEMM instead
   }
-  tm.mark(ST_NONE);
   if (int rc = c.measure_y()) return rc;
   CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
+  cp.stamp = tm.mark(ST_NONE);
   cp.ynorm = c.ynorm; cp.dn = c.ds;
   cp.Ys = c.Ys; cp.y_absmax = c.amax + Ctx::AM_Y;
   c.clear_with(cp);
@@ -908,15 +969,13 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   g.a_absmax = c.amax + Ctx::AM_XR; g.b_absmax = c.amax + Ctx::AM_Y;
   g.b_presplit = c.Ys; g.ldbs = c.ds + 32;
   HIPCHK(gemm_argmin(g, c.ynorm, c.best, c.st));
-  tm.mark(ST_GEMM);
   // winners -> direct squared distances (also the objective of this step)
   HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, nullptr, nullptr, c.best, c.st, nullptr, nullptr, nullptr,
-                         nullptr, nullptr, nullptr, nullptr, c.flag));
+                         nullptr, nullptr, nullptr, nullptr, c.flag, tm.mark(ST_GEMM)));
   c.prev_counts = false;
-  int rc = c.close_step();
+  int rc = c.close_step(nullptr, tm.mark(ST_TAU));
   c.prev_counts = true;
   if (rc) return rc;
-  tm.mark(ST_TAU);
   if ((rc = c.wait_step())) return rc;
   if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
   ss = StepStats();
@@ -932,12 +991,13 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
 int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_prev, StepStats &ss) {
   const int32_t nb = (c.d - dprime + kBlockDims - 1) / kBlockDims;
   if (nb > kMaxBlocks) return fail(SKM_EINTERNAL, "too many trailing blocks");
-  tm.mark(ST_NONE);
   bool found = false;   // the incumbents of a step that came without them are in c.prev
+  bool sought = false;  // ... and were looked for through the first filter
   if (!have_prev && c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
     // many centroids: the nearest centroid on the first d' dimensions through the low-precision filter (a third of
     // the matrix work of the three-product GEMM below); if its candidate list overflows, that GEMM runs after all
-    if (int rc = filtered_nearest(c, dprime, &tm)) return rc;
+    sought = true;
+    if (int rc = filtered_nearest(c, dprime, tm)) return rc;
     c.pending = true;
     HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, c.flag}, c.st));
     HIPCHK(hipMemcpyAsync(&c.report->flag, c.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, c.st));
@@ -946,8 +1006,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     if (c.report->flag == 0) found = true;
     else if (c.report->flag & 1u) c.exact_filter_off = true;
     else return fail(SKM_EINTERNAL, "a point was left without a centroid");
-    tm.mark(ST_GEMM);
   }
+
   if (int rc = c.measure_y()) return rc;
   // Low-precision first filter: worth its pass over the front dimensions when most columns of a tile die at the
   // first test.  The previous step's prune fraction predicts that from below (the centroids only get better): the
@@ -963,10 +1023,12 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     cp.dprime = dprime; cp.nb = nb; cp.Ypdx = c.Ypdx; cp.ynp = c.ynp;
     cp.Ys = c.Ys; cp.Yh = screen ? c.Yh : nullptr; cp.y_absmax = c.amax + Ctx::AM_Y;
     cp.ratio_out = c.ratio_dev;
+    cp.stamp = tm.mark(sought ? ST_GEMM : ST_NONE);   // (the search for the incumbents ends here)
     c.clear_with(cp);
     HIPCHK(launch_prep_centroids(cp, c.st, ratio, nb + 1));
   }
   bool from_keys = false;   // the incumbents are the low halves of c.best
+  stamp_t *tau_stamp = nullptr;
   if (!have_prev && !found) {
     HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
@@ -978,7 +1040,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     } else {
       from_keys = true;   // the threshold pass unpacks them
     }
-    tm.mark(ST_GEMM);
+    tau_stamp = tm.mark(ST_GEMM);
   } else if (have_prev && c.prev_in) {
     HIPCHK(launch_copy_labels(c.prev_in, c.n, c.k, c.prev, c.flag, c.st));
   }
@@ -1015,7 +1077,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     else
       HIPCHK(hipMemcpyAsync(c.pos_to_id, c.up.order, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, c.best, c.st, c.xnp, c.Xs,
-                           c.amax + Ctx::AM_XR, c.pos_to_id, c.Xr2, c.assign, c.Xh));
+                           c.amax + Ctx::AM_XR, c.pos_to_id, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
     std::swap(c.prev, c.assign);   // the incumbents in the new order; the other buffer receives this step's labels
     if (c.point_keys)   // (up.order is scratch until the next full update rebuilds it)
       HIPCHK(launch_remap_key_ids(c.point_keys, c.n_point_keys, c.pos_to_id, c.n, c.up.order, c.st));
@@ -1026,11 +1088,11 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     // the first pruned step of a context also writes the tables that depend on the points only
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, from_keys ? nullptr : c.prev, c.tau, c.best, c.st,
                            c.xnp_valid ? nullptr : c.xnp, c.xnp_valid ? nullptr : c.Xs, c.amax + Ctx::AM_XR, nullptr,
-                           nullptr, from_keys ? c.prev : nullptr, c.xnp_valid ? nullptr : c.Xh, c.flag));
+                           nullptr, from_keys ? c.prev : nullptr, c.xnp_valid ? nullptr : c.Xh, c.flag, tau_stamp));
   }
   c.order_fresh = false;
   c.xnp_valid = true;
-  tm.mark(ST_TAU);
+  stamp_t *border = tm.mark(ST_TAU);   // for the kernel that comes next
   for (int32_t ch = 0; ch < c.nchunks; ++ch) {
     const int64_t r0 = (int64_t)ch * c.chunk_rows;
     const int64_t rows = std::min<int64_t>(c.chunk_rows, c.n - r0);
@@ -1060,20 +1122,22 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt;
       sl.tile_counter = c.counters + ((size_t)c.nchunks * (kSubLists + 8) + (size_t)ch * 8) * kSubListStride;
       sl.scal = c.scal;
+      sl.stamp = border;
       HIPCHK(launch_screen(sl, c.st));
       g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles;
     }
+    if (!screen) g.stamp = border;
     HIPCHK(launch_progressive(g, c.st));
-    tm.mark(ST_GEMM);
+    border = tm.mark(ST_GEMM);
     if (c.emit_max > 0) {
       PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, dprime, c.ds, nb, c.ratio_dev,
                    c.best, c.scal, c.block_stats ? 1 : 0};
+      pa.stamp = border;
       HIPCHK(launch_prune(pa, c.st));
-      tm.mark(ST_PRUNE);
+      border = tm.mark(ST_PRUNE);
     }
   }
-  if (int rc = c.close_step()) return rc;
-  tm.mark(ST_TAU);
+  if (int rc = c.close_step(border, tm.mark(ST_TAU))) return rc;
   if (int rc = c.wait_step()) return rc;
   const unsigned int step_flag = c.report->flag;
   if (step_flag & 4u) return fail(SKM_EINVAL, "assignment label outside [0, k)");
@@ -1105,9 +1169,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
 // `changed` = points whose label differs from c.prev (c.n after the exact step).  While few points move, the cluster
 // sums of the previous update are corrected by the rows that joined and left instead of being recomputed from all
 // points (full = true forces the recomputation).
-int split_empty(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t *nempty_out);
-int step_update(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t *nempty_out, int64_t changed,
-                bool full) {
+int split_empty(Ctx &c, Rng &split_rng, float split_eps, int64_t *nempty_out);
+int step_update(Ctx &c, Rng &split_rng, float split_eps, int64_t *nempty_out, int64_t changed, bool full) {
   bool fresh = false;   // up.order rebuilt from the labels of this step
   if (!full && c.S_valid && changed == 0) {
     // no point changed its cluster: sums, sizes and therefore the means are those of the previous update.  If that
@@ -1129,12 +1192,12 @@ int step_update(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t
   }
   c.order_fresh = fresh;
   c.y_amax_valid = true;
-  return split_empty(c, tm, split_rng, split_eps, nempty_out);
+  return split_empty(c, split_rng, split_eps, nempty_out);
 }
 
 // Empty clusters after an update (Section 3.2): c.up.cnt holds the cluster sizes, and the step's report (if sizes_known)
 // how many of them are zero and the largest.
-int split_empty(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t *nempty_out) {
+int split_empty(Ctx &c, Rng &split_rng, float split_eps, int64_t *nempty_out) {
   // the report of the step has said whether there are any (neither update changes the sizes); the sizes themselves are
   // fetched only then
   *nempty_out = 0;
@@ -1239,7 +1302,6 @@ int split_empty(Ctx &c, StageTimer &tm, Rng &split_rng, float split_eps, int64_t
       HIPCHK(hipStreamSynchronize(c.st));  // `up` must outlive the copy
     }
   }
-  tm.mark(ST_UPDATE);
   return SKM_OK;
 }
 
@@ -1318,7 +1380,8 @@ int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const floa
 // out_absmax (optional, zero before the call) receives the bit pattern of max |out|
 // (in_bound: a word that already bounds |in|)
 int rotate_into(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t ds, Rot &rot, float *out,
-                hipStream_t st, unsigned int *out_absmax = nullptr, const unsigned int *in_bound = nullptr) {
+                hipStream_t st, unsigned int *out_absmax = nullptr, const unsigned int *in_bound = nullptr,
+                stamp_t *stamp = nullptr) {
   if (!in_bound) {
     unsigned int *slot = nullptr;
     if (int rc = rot.next_slot(st, &slot)) return rc;
@@ -1328,12 +1391,13 @@ int rotate_into(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t 
   GemmOperands g{in, ldin, (int32_t)rows, rot.Rtp, ds, d, d};
   g.a_absmax = in_bound; g.b_absmax = rot.amax;
   g.b_split = rot.Rs;
+  g.stamp = stamp;
   HIPCHK(gemm_store(g, out, ds, ds, 1.f, 0.f, st, out_absmax));
   return SKM_OK;
 }
 // out (rows x d) = Yr (rows x d, stride ldy) * R^T
 int unrotate_into(const float *Yr, int64_t ldy, int32_t rows, int32_t d, int32_t ds, Rot &rot, float *out,
-                  hipStream_t st, const unsigned int *in_bound = nullptr) {
+                  hipStream_t st, const unsigned int *in_bound = nullptr, stamp_t *stamp = nullptr) {
   if (!in_bound) {
     unsigned int *slot = nullptr;
     if (int rc = rot.next_slot(st, &slot)) return rc;
@@ -1342,6 +1406,7 @@ int unrotate_into(const float *Yr, int64_t ldy, int32_t rows, int32_t d, int32_t
   }
   GemmOperands g{Yr, ldy, rows, rot.Rp, ds, d, d};
   g.a_absmax = in_bound; g.b_absmax = rot.amax;
+  g.stamp = stamp;
   HIPCHK(gemm_store(g, out, d, d, 1.f, 0.f, st));
   return SKM_OK;
 }
@@ -1419,18 +1484,11 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   // stage times are taken only for a caller that asked for the trace (a small fit inside the hierarchical fit spends
   // a third of its host time creating and reading events otherwise)
   const bool timed = tr != nullptr;
-  StageTimer tm(c.st, timed);
-  Events evs;
-  hipEvent_t e_begin = nullptr, e_rot = nullptr, e_init = nullptr, e_unrot0 = nullptr, e_unrot1 = nullptr, e_end = nullptr;
-  hipEvent_t e_gt0 = nullptr, e_gt1 = nullptr, e_rot0 = nullptr;
-  if (timed) {
-    e_begin = evs.next(); e_rot = evs.next(); e_init = evs.next(); e_unrot0 = evs.next(); e_unrot1 = evs.next(); e_end = evs.next();
-    e_gt0 = evs.next(); e_gt1 = evs.next(); e_rot0 = evs.next();
-    if (!e_begin || !e_rot || !e_init || !e_unrot0 || !e_unrot1 || !e_end || !e_gt0 || !e_gt1 || !e_rot0)
-      return fail(SKM_EHIP, "hipEventCreate failed");
-  }
-  if (timed) HIPCHK(hipEventRecord(e_begin, c.st));
-  rc = c.alloc_bounds();
+  StageTimer tm(timed);
+  if ((rc = tm.init(64 + (size_t)(std::min(iters, 4096) + 2) * 64))) return rc;
+  Events evs;   // of the second stream below
+  size_t t_begin = 0, t_rot0 = 0, t_rot = 0, t_unrot0 = 0, t_unrot1 = 0, t_end = 0, t_gt0 = 0, t_gt1 = 0;
+  rc = c.alloc_bounds(tm.point(&t_begin));
   if (rc) return rc;
 
   // ---- Algorithm 1: R, X~ = X R
@@ -1464,11 +1522,9 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     if (beside) HIPCHK(hipStreamWaitEvent(c.st, e_join, 0));
-    if (timed) HIPCHK(hipEventRecord(e_rot0, c.st));
-    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR, x_bound);
+    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR, x_bound, tm.point(&t_rot0));
     if (rc) return rc;
     if (beside) HIPCHK(hipStreamSynchronize(side.s));   // nothing is left on the side stream when it is destroyed
-    if (timed) HIPCHK(hipEventRecord(e_rot, c.st));
     c.Xr = Xr_own; c.ldx = c.ds;
   } else if (d == c.ds && aligned16(X) && !p.angular) {
     c.Xr = X; c.ldx = d;
@@ -1479,10 +1535,6 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   }
   if (p.angular) HIPCHK(launch_normalize_rows(Xr_own, c.ds, n, c.ds, c.st));   // the library's own copy, in place
   if (!p.rotate || p.angular) {
-    if (!p.rotate) {
-      if (timed) HIPCHK(hipEventRecord(e_rot0, c.st));
-      if (timed) HIPCHK(hipEventRecord(e_rot, c.st));
-    }
     rc = c.measure_xr();
     if (rc) return rc;
   }
@@ -1519,7 +1571,8 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
       idx_view = idx_dev;
     }
     c.pending = true;   // (the block is in use until the first step has been waited for)
-    HIPCHK(launch_gather_rows(c.Xr, c.ldx, c.ds, idx_view, k, c.Y, c.ds, c.ds, c.st, c.amax + Ctx::AM_Y));
+    HIPCHK(launch_gather_rows(c.Xr, c.ldx, c.ds, idx_view, k, c.Y, c.ds, c.ds, c.st, c.amax + Ctx::AM_Y,
+                              tm.point(&t_rot)));   // (the rotation has ended where this starts)
     c.y_amax_valid = true;
     if (!c.idx_host) HIPCHK(hipStreamSynchronize(c.st));
   }
@@ -1528,7 +1581,6 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   float *Qr = nullptr, *Sq = nullptr, *ynorm_full = nullptr;
   unsigned long long *gt_keys = nullptr, *etr_scal = nullptr;
   int32_t nprobe = 0;
-  if (timed) HIPCHK(hipEventRecord(e_gt0, c.st));
   if (p.etr) {
     if (p.nq < 1 || p.topk < 1 || p.topk > 256) return fail(SKM_EINVAL, "ETR: nq >= 1 and 1 <= topk <= 256 required");
     nprobe = nprobe_of(k, p.probe_frac);
@@ -1551,8 +1603,10 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (p.gt) {
       HIPCHK(launch_index_to_keys(p.gt, (int64_t)p.nq * p.topk, gt_keys, c.st));
     } else {
+      HIPCHK(launch_stamp(tm.point(&t_gt0), c.st));
       rc = ground_truth_keys(c.pool, X, n, d, Q, p.nq, p.topk, c.amax + Ctx::AM_X, c.amax + Ctx::AM_Q, gt_keys, c.st);
       if (rc) return rc;
+      HIPCHK(launch_stamp(tm.point(&t_gt1), c.st));
     }
     HIPCHK(c.pool.get(&Qr, (size_t)p.nq * c.ds));
     if (p.rotate) {
@@ -1569,8 +1623,6 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     c.point_keys = gt_keys;   // the ground truth names points: it follows them if they are regrouped
     c.n_point_keys = (int64_t)p.nq * p.topk;
   }
-  if (timed) HIPCHK(hipEventRecord(e_gt1, c.st));
-  if (timed) HIPCHK(hipEventRecord(e_init, c.st));
 
   int32_t dprime = dprime_init(d, p.dprime_frac);
   Rng split_rng = rng_stream(seed, STREAM_SPLIT);
@@ -1611,16 +1663,16 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (p.etr) {
       rc = measure_recall(&recall);
       if (rc) return rc;
-      tm.mark(ST_ETR);
+      HIPCHK(launch_stamp(tm.mark(ST_ETR), c.st));
     }
     int64_t nempty = 0;
-    rc = step_update(c, tm, split_rng, p.split_eps, &nempty, ss.changed, p.full_update != 0);
+    rc = step_update(c, split_rng, p.split_eps, &nempty, ss.changed, p.full_update != 0);
     if (rc) return rc;
     if (p.angular) {
       HIPCHK(launch_normalize_rows(c.Y, c.ds, k, c.ds, c.st));
       c.y_amax_valid = false;
     }
-    // (no wait: the next step's launches follow while the update runs)
+    tm.mark_next(ST_UPDATE);   // (no wait: the next step's launches follow while the update runs)
     run = t;
     if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, nempty, recall);
     ++rows;
@@ -1645,15 +1697,16 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
 
   // ---- Algorithm 1, last line: Y = Y~ R^T (before the final assignment, which does not change the centroids: one wait
   // then ends both)
-  if (timed) HIPCHK(hipEventRecord(e_unrot0, c.st));
   if (p.rotate) {
-    rc = unrotate_into(c.Y, c.ds, k, d, c.ds, rot, centroids_out, c.st, c.y_amax_valid ? c.amax + Ctx::AM_Y : nullptr);
+    rc = unrotate_into(c.Y, c.ds, k, d, c.ds, rot, centroids_out, c.st, c.y_amax_valid ? c.amax + Ctx::AM_Y : nullptr,
+                       tm.point(&t_unrot0));
     if (rc) return rc;
   } else {
     HIPCHK(hipMemcpy2DAsync(centroids_out, sizeof(float) * (size_t)d, c.Y, sizeof(float) * (size_t)c.ds,
                             sizeof(float) * (size_t)d, (size_t)k, hipMemcpyDeviceToDevice, c.st));
   }
-  if (timed) HIPCHK(hipEventRecord(e_unrot1, c.st));
+  tm.point_next(&t_unrot1);
+  if (!p.final_assign) HIPCHK(tm.flush(c.st));
 
   // ---- final assignment with the two-phase approach (Section 3.3)
   bool waited = false;
@@ -1678,19 +1731,23 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (assign_out) HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
     if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
   }
-  if (timed) HIPCHK(hipEventRecord(e_end, c.st));
-  if (timed || !waited) HIPCHK(hipStreamSynchronize(c.st));
+  if (!waited) {
+    HIPCHK(launch_stamp(tm.point(&t_end), c.st));
+    HIPCHK(hipStreamSynchronize(c.st));
+  } else if (!tm.marks.empty()) {
+    t_end = tm.marks.back().second;   // the last kernel's end
+  }
   c.pending = false;
   if (dprime_out) *dprime_out = dprime;
   if (tr) {
     tr->rows = std::min(rows, tr->capacity);
     tr->iters_run = run;
     tr->inc_updates = c.inc_updates;
-    (void)hipEventElapsedTime(&tr->ms_rotate, e_rot0, e_rot);
-    (void)hipEventElapsedTime(&tr->ms_init, e_begin, e_init);
-    (void)hipEventElapsedTime(&tr->ms_etr_gt, e_gt0, e_gt1);
-    (void)hipEventElapsedTime(&tr->ms_unrotate, e_unrot0, e_unrot1);
-    (void)hipEventElapsedTime(&tr->ms_total, e_begin, e_end);
+    tr->ms_rotate = p.rotate ? tm.between(t_rot0, t_rot) : 0.f;
+    tr->ms_init = tm.marks.empty() ? 0.f : tm.between(t_begin, tm.marks.front().second);
+    tr->ms_etr_gt = t_gt1 > t_gt0 ? tm.between(t_gt0, t_gt1) : 0.f;
+    tr->ms_unrotate = p.rotate ? tm.between(t_unrot0, t_unrot1) : 0.f;
+    tr->ms_total = tm.between(t_begin, t_end);
     for (int32_t q = 0; q < tr->rows; ++q) fill_times(tr->row[q], tm, (size_t)q);
   }
   ws.finished();
@@ -1740,7 +1797,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   c.ds = round_up(d, 16);
   c.block_stats = p.block_stats != 0;
   c.screen_mode = p.screen;
-  StageTimer tm(c.st, true);
+  StageTimer tm(tr != nullptr);
   Events evs;
   hipEvent_t e_begin = evs.next(), e_init = evs.next(), e_end0 = evs.next(), e_end = evs.next();
   hipEvent_t ev_copied[2] = {evs.next(), evs.next()}, ev_free[2] = {evs.next(), evs.next()};
@@ -1759,6 +1816,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   rc = c.alloc_common(p.pair_budget, p.dense_frac, true);
   if (rc) return rc;
   const int64_t tile_rows = c.chunk_rows;   // rows per launch of the tile kernel inside a batch
+  if ((rc = tm.init(16 + (size_t)nbatch * (8 + 2 * ((size_t)(W + tile_rows - 1) / tile_rows))))) return rc;
 
   Rot rot;
   if (p.rotate) {
@@ -1872,7 +1930,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       if (!final_pass) {
         HIPCHK(launch_add_counts(c.up.cnt, k, cnt_total, c.st));
         HIPCHK(launch_update(c.Xr, c.ldx, rows, c.ds, c.assign, k, c.up, nullptr, c.ds, c.st, c.S, nullptr, 1, c.report->largest));
-        tm.mark(ST_UPDATE);
+        HIPCHK(launch_stamp(tm.mark(ST_UPDATE), c.st));
       }
     }
     int64_t nempty = 0;
@@ -1883,9 +1941,10 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       c.sizes_known = false;   // (the report holds those of the last batch)
       int32_t *batch_cnt = c.up.cnt;
       c.up.cnt = cnt_total;
-      rc = split_empty(c, tm, split_rng, p.split_eps, &nempty);
+      rc = split_empty(c, split_rng, p.split_eps, &nempty);
       c.up.cnt = batch_cnt;
       if (rc) return rc;
+      HIPCHK(launch_stamp(tm.mark(ST_UPDATE), c.st));
     }
     HIPCHK(hipStreamSynchronize(c.st));
     if (tr && rows_out < tr->capacity) {
@@ -1951,7 +2010,8 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   c.ds = round_up(d, 16);
   c.block_stats = p.block_stats != 0;
   c.screen_mode = p.screen;
-  StageTimer tm(c.st, tr != nullptr);
+  StageTimer tm(tr != nullptr && tr->row && tr->capacity >= 1);
+  if ((rc = tm.init(256))) return rc;
   Rot rot;
   float *Xr_own = nullptr;
   rc = c.alloc_bounds();

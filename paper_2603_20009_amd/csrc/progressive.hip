@@ -120,6 +120,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __shared__ unsigned int s_base;         // first list slot of a tile that hands its pairs over
   __shared__ int s_q[4];   // ring of tile numbers drawn from the XCD's counter, two tiles ahead of the one in work
   __shared__ int s_cid[BN];   // listed columns: the centroid ids of the tile being committed (INT_MAX = none)
+  put_stamp(g.stamp);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;

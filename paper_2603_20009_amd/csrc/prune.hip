@@ -32,6 +32,7 @@ __global__ void __launch_bounds__(PRUNE_THREADS) prune_kernel(PruneArgs a) {
   __shared__ float s_ratio[kMaxBlocks + 1];
   __shared__ unsigned int s_enter[kMaxBlocks + 1];
   __shared__ unsigned int s_completed, s_steps, s_pairs;
+  put_stamp(a.stamp);
   const int tid = threadIdx.x;
   for (int m = tid; m <= a.nb; m += PRUNE_THREADS) {
     s_ratio[m] = a.ratio[m];

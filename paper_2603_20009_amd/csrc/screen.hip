@@ -464,7 +464,8 @@ __global__ void __launch_bounds__(256) screen_terms_kernel(const float *tau, con
 }
 
 // *out = max of v[0 .. n) (non-negative values: their bit patterns order like the numbers)
-__global__ void __launch_bounds__(1024) max_value_kernel(const float *v, int32_t n, float *out) {
+__global__ void __launch_bounds__(1024) max_value_kernel(const float *v, int32_t n, float *out, stamp_t *stamp) {
+  put_stamp(stamp);
   __shared__ float red[16];
   float m = 0.f;
   for (int i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, v[i]);
@@ -510,7 +511,7 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   g.a_absmax = a.a_absmax; g.b_absmax = a.b_absmax;
   g.dprime = a.dprime;
   float *ynmax = reinterpret_cast<float *>(a.ntiles + 1);   // (the word after the tile count)
-  hipLaunchKernelGGL(max_value_kernel, dim3(1), dim3(1024), 0, st, a.yn, a.N, ynmax);
+  hipLaunchKernelGGL(max_value_kernel, dim3(1), dim3(1024), 0, st, a.yn, a.N, ynmax, a.stamp);
   hipLaunchKernelGGL(screen_terms_kernel, dim3((unsigned)((std::max<int64_t>(a.M, a.N) + 255) / 256)), dim3(256), 0, st,
                      a.tau, a.xn, a.row_base, a.M, a.yn, a.N, (const float *)ynmax, a.ratio0, a.dprime, a.a_absmax,
                      a.b_absmax, a.arow, a.ycol, a.exact ? 1 : 0);

@@ -38,6 +38,14 @@ __host__ __device__ inline uint64_t pack_key(float v, int32_t idx) {
   return ((uint64_t)f2ord(v) << 32) | (uint32_t)idx;
 }
 
+// Times of a call's stages without commands of their own: a kernel at a stage's border stores the device's constant
+// clock (100 MHz) as its first workgroup starts.  (An event record cost 5 us of host and stream time each, a quarter of
+// a small fit.)  NULL: no stamp.
+typedef unsigned long long stamp_t;
+__device__ inline void put_stamp(stamp_t *stamp) {
+  if (stamp && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *stamp = wall_clock64();
+}
+
 // ---------------------------------------------------------------- GEMM family
 // C-shaped work: scores s(i, j) = sum_k A[i][k] * B[j][k] for an M x K row-major A and an
 // N x K row-major B (both K-contiguous), on fp32 MFMA, with one of three fused epilogues.
@@ -60,6 +68,7 @@ struct GemmOperands {
   uint32_t *b_split = nullptr;
   const uint32_t *b_presplit = nullptr;
   int64_t ldbs = 0;
+  stamp_t *stamp = nullptr;
 };
 
 // Split-fp16 arithmetic.  A matrix whose largest magnitude is m is scaled by the power of two that brings m
@@ -148,6 +157,7 @@ struct ProgArgs {
   // Listed columns (after launch_screen; all NULL otherwise): tile t is row tile tile_rt[t] against the 128 centroids
   // col_list[128 t ..] (ascending ids, -1 = none); *ntiles tiles in all.
   const int32_t *tile_rt = nullptr, *col_list = nullptr, *ntiles = nullptr;
+  stamp_t *stamp = nullptr;
 };
 hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
 
@@ -181,6 +191,7 @@ struct ScreenLaunch {
   unsigned int *pair_count = nullptr;
   unsigned int sub_capacity = 0;
   unsigned int *overflow = nullptr;
+  stamp_t *stamp = nullptr;
 };
 hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st);
 int64_t progressive_tiles(int64_t rows, int32_t k);
@@ -204,6 +215,7 @@ struct PruneArgs {
   unsigned long long *best;        // [n] packed (distance, centroid)
   unsigned long long *scal;        // [kStatReplicas][SC_COUNT]: SC_COMPLETED, SC_GATHER_*, and SC_ENTER + m when block_stats
   int32_t block_stats;
+  stamp_t *stamp = nullptr;
 };
 hipError_t launch_prune(const PruneArgs &a, hipStream_t st);
 
@@ -223,7 +235,7 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
                            const int32_t *assign, float *tau, unsigned long long *best, hipStream_t st,
                            float *xnp = nullptr, uint32_t *xs = nullptr, const unsigned int *x_absmax = nullptr,
                            const int32_t *order = nullptr, float *xr_out = nullptr, int32_t *label_out = nullptr,
-                           uint32_t *xh = nullptr, unsigned int *unset = nullptr);
+                           uint32_t *xh = nullptr, unsigned int *unset = nullptr, stamp_t *stamp = nullptr);
 // dst[idx[p]] = src[p] for 4-byte items
 hipError_t launch_scatter_by_index(const void *src, const int32_t *idx, int64_t n, void *dst, hipStream_t st);
 // order_out = order_in (points grouped by cluster, segment c = [off[c], off[c+1])) with every segment stably sorted by
@@ -254,6 +266,7 @@ struct CentroidPrep {
   unsigned int *clear = nullptr;
   int64_t clear_words = 0;
   float *ratio_out = nullptr;
+  stamp_t *stamp = nullptr;
 };
 struct ThetaRatios {
   int n;
@@ -265,7 +278,8 @@ hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const fl
 hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st);
 
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
-hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st);
+hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st, stamp_t *stamp = nullptr);
+hipError_t launch_stamp(stamp_t *stamp, hipStream_t st);   // a stamp with no kernel to carry it
 
 // What the last kernel of a step writes into page-locked host memory.
 struct StepReport {
@@ -292,6 +306,7 @@ struct FinalizeArgs {
   const unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]
   int nscal = SC_COUNT;               // scalars to report
   StepReport *report = nullptr;       // device-visible address of the page-locked block
+  stamp_t *stamp = nullptr, *stamp_end = nullptr;   // start and (of the closing workgroup) end
 };
 hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st);
 int64_t finalize_blocks(int64_t n);
@@ -351,7 +366,8 @@ hipError_t launch_split(float *Y, int64_t ldy, int32_t d, const int32_t *pairs_d
                         int32_t nchains, float eps, hipStream_t st);
 // dst[c] = src[idx[c]] (idx: device or page-locked host memory), zero padded to dpad; max |.| folded into *absmax (optional)
 hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx, int32_t k, float *dst,
-                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax = nullptr);
+                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax = nullptr,
+                              stamp_t *stamp = nullptr);
 // Rp (stride ld, zero padded to it) = R, Rtp likewise = R^T (either may be NULL), max |R| folded into *absmax
 hipError_t launch_rotation_operands(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld, unsigned int *absmax,
                                     hipStream_t st);

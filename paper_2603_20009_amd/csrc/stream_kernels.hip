@@ -55,6 +55,7 @@ struct PrefixOut {
   int32_t *label_out;
   unsigned int *unset = nullptr;   // labels taken from packed keys: bit 1 is set if a point has none
   int span = 64;                   // BATCH: points a workgroup takes at a time (64, or 16 when there are few)
+  stamp_t *stamp = nullptr;
 };
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -129,6 +130,7 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
                                                        const float *Y, int64_t ldy, const int32_t *assign, float *tau,
                                                        unsigned long long *best, PrefixOut po) {
   __shared__ float s_np[BATCH ? kPrefixStageRows * 64 : 1];
+  put_stamp(po.stamp);
   if (po.xs) po.scale = split_scale(*po.absmax);
   const int lane = threadIdx.x & 63;
   auto point = [&](int64_t p, int slot) {   // output slot p <- point i
@@ -243,7 +245,7 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
 hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
                            const int32_t *assign, float *tau, unsigned long long *best, hipStream_t st, float *xnp,
                            uint32_t *xs, const unsigned int *x_absmax, const int32_t *order, float *xr_out,
-                           int32_t *label_out, uint32_t *xh, unsigned int *unset) {
+                           int32_t *label_out, uint32_t *xh, unsigned int *unset, stamp_t *stamp) {
   if (n <= 0) return hipSuccess;
   const int nv = (ds + 255) / 256;
   const bool batch = xnp != nullptr && nv <= 8 && ds / 16 <= kPrefixStageRows;
@@ -256,7 +258,7 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
   if ((order != nullptr) != (xr_out != nullptr) || (order && (!label_out || !assign)) || (!assign && !best)) return hipErrorInvalidValue;
   if (xr_out && (reinterpret_cast<uintptr_t>(xr_out) & 15u)) return hipErrorInvalidValue;
   if (xh && (!xs || (reinterpret_cast<uintptr_t>(xh) & 15u))) return hipErrorInvalidValue;
-  const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out, unset, span};
+  const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out, unset, span, stamp};
 #define SKM_TAU_LAUNCH(NV)                                                                                      \
   do {                                                                                                          \
     if (batch && NV > 0)                                                                                        \
@@ -380,6 +382,7 @@ hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32
 __global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, ThetaRatios ratios) {
   __shared__ float s_pre[1025];   // ||y[0 : 16 p)||^2 at p (ds <= 16384)
   const int c = blockIdx.x, tid = threadIdx.x;
+  put_stamp(a.stamp);
   for (int64_t w = (int64_t)c * 256 + tid; w < a.clear_words; w += (int64_t)gridDim.x * 256) a.clear[w] = 0u;
   if (c == 0 && a.ratio_out)
     for (int m = tid; m < ratios.n; m += 256) a.ratio_out[m] = ratios.v[m];
@@ -448,22 +451,29 @@ hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const fl
 
 // ------------------------------------------------------------------ fills
 template <typename T>
-__global__ void fill_kernel(T *p, int64_t n, T v) {
+__global__ void fill_kernel(T *p, int64_t n, T v, stamp_t *stamp) {
+  put_stamp(stamp);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 template <typename T>
-static hipError_t launch_fill(T *p, int64_t n, T v, hipStream_t st) {
+static hipError_t launch_fill(T *p, int64_t n, T v, hipStream_t st, stamp_t *stamp = nullptr) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = (n + 255) / 256;
   if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(fill_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, p, n, v);
+  hipLaunchKernelGGL(fill_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, p, n, v, stamp);
   return hipGetLastError();
 }
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st) {
   return launch_fill<unsigned long long>(p, n, v, st);
 }
-hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st) {
-  return launch_fill<unsigned int>(p, n, v, st);
+hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st, stamp_t *stamp) {
+  return launch_fill<unsigned int>(p, n, v, st, stamp);
+}
+__global__ void stamp_kernel(stamp_t *stamp) { put_stamp(stamp); }
+hipError_t launch_stamp(stamp_t *stamp, hipStream_t st) {
+  if (!stamp) return hipSuccess;
+  hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(64), 0, st, stamp);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ largest magnitude of a matrix
@@ -579,6 +589,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
   __shared__ int s_hist[FIN_LDS_BINS];
   __shared__ int s_last;
   const int tid = threadIdx.x;
+  put_stamp(a.stamp);
   if (in_lds) {
     for (int b = tid; b < a.k; b += FIN_THREADS) s_hist[b] = 0;
     __syncthreads();
@@ -694,6 +705,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     r->flag = load_agent(a.flag);
     r->nempty = (s_hist[0] + s_hist[1]) + (s_hist[2] + s_hist[3]);
     r->largest = max(max(s_hist[4], s_hist[5]), max(s_hist[6], s_hist[7]));
+    if (a.stamp_end) *a.stamp_end = wall_clock64();
   }
 }
 
@@ -1300,8 +1312,9 @@ hipError_t launch_split(float *Y, int64_t ldy, int32_t d, const int32_t *pairs_d
 // ------------------------------------------------------------------ small copies
 __global__ void __launch_bounds__(256) gather_rows_kernel(const float *src, int64_t lds, int32_t d,
                                                           const int64_t *idx, float *dst, int64_t ldd, int32_t dpad,
-                                                          unsigned int *absmax) {
+                                                          unsigned int *absmax, stamp_t *stamp) {
   const int c = blockIdx.x;
+  put_stamp(stamp);
   const float *s = src + idx[c] * lds;
   float m = 0.f;
   for (int j = threadIdx.x; j < dpad; j += 256) {
@@ -1312,8 +1325,8 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const float *src, int6
   if (absmax) block_absmax(m, absmax);
 }
 hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx, int32_t k, float *dst,
-                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax) {
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(k), dim3(256), 0, st, src, lds, d, idx, dst, ldd, dpad, absmax);
+                              int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax, stamp_t *stamp) {
+  hipLaunchKernelGGL(gather_rows_kernel, dim3(k), dim3(256), 0, st, src, lds, d, idx, dst, ldd, dpad, absmax, stamp);
   return hipGetLastError();
 }
 
