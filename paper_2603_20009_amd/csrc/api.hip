@@ -514,6 +514,7 @@ struct Ctx {
   uint32_t *Ys = nullptr;     // [k][ds + 32] the same of Y, remade in every pruned step
   float *xnp = nullptr;       // [ds / 16][n] prefix norms of the points at every multiple of 16 dims, written by the
   bool xnp_valid = false;     // first pruned step (the points of a context never change)
+  bool xh_valid = false;      // Xh likewise: left out of a pass that a regrouping pass will repeat
   // Regrouping (a fit with several steps left): once the tables exist and a full update has just grouped the points
   // by their cluster, the next threshold pass rewrites the points, their split copy, their tables and every per-point
   // array in that order.  Row tiles then hold points of one or two clusters, whose challengers are the same few
@@ -719,6 +720,8 @@ struct Ctx {
       HIPCHK(pool.get(&up.cursor, (size_t)k));
       HIPCHK(pool.get(&up.segoff, (size_t)k + 1));
       HIPCHK(pool.get(&up.order, (size_t)n));
+      // (a batch of a host-resident fit may be shorter than n: the rule is asked again there)
+      if (stable_order_applies(n, k)) HIPCHK(pool.get(&up.base, (size_t)stable_order_words(n, k)));
       up.max_segments = update_max_segments(n, k);
       HIPCHK(pool.get(&up.partial, (size_t)up.max_segments * ds));
       HIPCHK(pool.get(&split_dev, (size_t)3 * k + 2));   // (empty, donor) pairs | first split of every chain
@@ -733,6 +736,7 @@ struct Ctx {
       HIPCHK(pool.get(&inc.off, (size_t)k + 1));
       HIPCHK(pool.get(&inc.cursor, (size_t)k));
       HIPCHK(pool.get(&inc.segoff, (size_t)k + 1));
+      if (stable_order_applies(inc.capacity, k)) HIPCHK(pool.get(&inc.base, (size_t)stable_order_words(inc.capacity, k)));
       HIPCHK(pool.get(&inc.partial, (size_t)inc.max_segments * ds));
     }
     return SKM_OK;
@@ -875,14 +879,14 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
   const int32_t nbK = (K + kBlockDims - 1) / kBlockDims;
   if (nbK > kMaxBlocks) return fail(SKM_EINTERNAL, "too many blocks");
   stamp_t *start = tm.mark(ST_NONE);
-  if (!c.xnp_valid) {
+  if (!c.xnp_valid || !c.xh_valid) {
     // the points' split copy, its hi plane and their norms do not exist before the first pruned step: the pass that
     // writes them runs now (its thresholds, against centroid 0, are discarded)
     HIPCHK(launch_fill_u32(reinterpret_cast<unsigned int *>(c.prev), c.n, 0u, c.st));
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, nullptr, c.st, c.xnp, c.Xs,
                            c.amax + Ctx::AM_XR, nullptr, nullptr, nullptr, c.Xh, nullptr, start));
     start = nullptr;
-    c.xnp_valid = true;
+    c.xnp_valid = c.xh_valid = true;
   }
   // ||y[0 : K)||^2 and the block-major copy of the first K dimensions, zero filled behind them (the gather kernel
   // starts every pair at dimension 0 and is told that rows end at K)
@@ -1084,11 +1088,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     c.Xr = c.Xr2;
     c.ldx = c.ds;
     c.permuted = true;
+    c.xh_valid = c.Xh != nullptr;
   } else {
-    // the first pruned step of a context also writes the tables that depend on the points only
+    // The first pruned step of a context also writes the tables that depend on the points only.  The plane of hi halves
+    // is left out where this step does not read it and a regrouping pass, which writes all of them again, is likely to
+    // come before a step that does (3 of 16 GB of that pass at 1M x 1536); if it does not come, the first step that
+    // needs the plane writes the tables once more.
+    const bool tables = !c.xnp_valid || (screen && !c.xh_valid);
+    uint32_t *xh = tables && (screen || !c.Xr2) ? c.Xh : nullptr;
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, from_keys ? nullptr : c.prev, c.tau, c.best, c.st,
-                           c.xnp_valid ? nullptr : c.xnp, c.xnp_valid ? nullptr : c.Xs, c.amax + Ctx::AM_XR, nullptr,
-                           nullptr, from_keys ? c.prev : nullptr, c.xnp_valid ? nullptr : c.Xh, c.flag, tau_stamp));
+                           tables ? c.xnp : nullptr, tables ? c.Xs : nullptr, c.amax + Ctx::AM_XR, nullptr,
+                           nullptr, from_keys ? c.prev : nullptr, xh, c.flag, tau_stamp));
+    if (tables) c.xh_valid = xh != nullptr;
   }
   c.order_fresh = false;
   c.xnp_valid = true;
@@ -1533,8 +1544,10 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     HIPCHK(launch_pad_copy(X, d, n, d, Xr_own, c.ds, c.ds, 0, c.st));
     c.Xr = Xr_own; c.ldx = c.ds;
   }
-  if (p.angular) HIPCHK(launch_normalize_rows(Xr_own, c.ds, n, c.ds, c.st));   // the library's own copy, in place
-  if (!p.rotate || p.angular) {
+  if (p.angular) {   // the library's own copy, in place; its bound is that of the scaled rows
+    if (p.rotate) HIPCHK(launch_fill_u32(c.amax + Ctx::AM_XR, 1, 0u, c.st));
+    HIPCHK(launch_normalize_rows(Xr_own, c.ds, n, c.ds, c.st, c.amax + Ctx::AM_XR));
+  } else if (!p.rotate) {
     rc = c.measure_xr();
     if (rc) return rc;
   }
@@ -1669,8 +1682,9 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     rc = step_update(c, split_rng, p.split_eps, &nempty, ss.changed, p.full_update != 0);
     if (rc) return rc;
     if (p.angular) {
-      HIPCHK(launch_normalize_rows(c.Y, c.ds, k, c.ds, c.st));
-      c.y_amax_valid = false;
+      HIPCHK(launch_fill_u32(c.amax + Ctx::AM_Y, 1, 0u, c.st));
+      HIPCHK(launch_normalize_rows(c.Y, c.ds, k, c.ds, c.st, c.amax + Ctx::AM_Y));
+      c.y_amax_valid = true;
     }
     tm.mark_next(ST_UPDATE);   // (no wait: the next step's launches follow while the update runs)
     run = t;
@@ -1903,7 +1917,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       c.n = rows;
       c.nchunks = (int32_t)((rows + tile_rows - 1) / tile_rows);
       c.Xr = Xr_buf; c.ldx = c.ds;
-      c.xnp_valid = false;
+      c.xnp_valid = c.xh_valid = false;
       c.assign = lab[cur] + r0;
       c.prev = lab[cur ^ 1] + r0;
       c.dist = dist_all ? dist_all + r0 : dist_batch;
@@ -1929,7 +1943,9 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       tot.nblocks = ss.nblocks;
       if (!final_pass) {
         HIPCHK(launch_add_counts(c.up.cnt, k, cnt_total, c.st));
-        HIPCHK(launch_update(c.Xr, c.ldx, rows, c.ds, c.assign, k, c.up, nullptr, c.ds, c.st, c.S, nullptr, 1, c.report->largest));
+        UpdateWs uw = c.up;
+        if (!stable_order_applies(rows, k)) uw.base = nullptr;
+        HIPCHK(launch_update(c.Xr, c.ldx, rows, c.ds, c.assign, k, uw, nullptr, c.ds, c.st, c.S, nullptr, 1, c.report->largest));
         HIPCHK(launch_stamp(tm.mark(ST_UPDATE), c.st));
       }
     }
@@ -2632,22 +2648,24 @@ int skm_update(const float *X, int64_t n, int32_t d, const int32_t *assign, int3
   const int32_t ds = round_up(d, 16);
   UpdateWs w{};
   w.max_segments = update_max_segments(n, k);
-  CallArena ws((size_t)w.max_segments * ds * sizeof(double) + (size_t)n * 4 + (size_t)k * 20 + 4096);
+  const bool stable = stable_order_applies(n, k);
+  CallArena ws((size_t)w.max_segments * ds * sizeof(double) + (size_t)n * 4 + (size_t)k * 20 +
+               (stable ? (size_t)stable_order_words(n, k) * 4 : 0) + 4096);
   Pool pool;
-  unsigned int *flag = nullptr;   // [1 + k]: the flag, then the sizes
-  HIPCHK(pool.get(&flag, (size_t)k + 1));
-  w.cnt = reinterpret_cast<int32_t *>(flag + 1);
+  unsigned int *flag = nullptr;
+  HIPCHK(pool.get(&flag, 1));
+  HIPCHK(pool.get(&w.cnt, (size_t)k));
   HIPCHK(pool.get(&w.off, (size_t)k + 1));
   HIPCHK(pool.get(&w.cursor, (size_t)k));
   HIPCHK(pool.get(&w.segoff, (size_t)k + 1));
   HIPCHK(pool.get(&w.order, (size_t)n));
+  if (stable) HIPCHK(pool.get(&w.base, (size_t)stable_order_words(n, k)));
   HIPCHK(pool.get(&w.partial, (size_t)w.max_segments * ds));
   PinnedWord bad;
   if (!bad.host) return fail(SKM_EHIP, "hipHostMalloc failed");
-  HIPCHK(launch_fill_u32(flag, (int64_t)k + 1, 0u, st));
-  HIPCHK(launch_histogram(assign, n, k, w.cnt, flag, st));
-  HIPCHK(launch_update(X, d, n, d, assign, k, w, centroids, d, st, nullptr, nullptr, 0, -1, flag, bad.dev));
-  if (counts_out) HIPCHK(hipMemcpyAsync(counts_out, w.cnt, sizeof(int32_t) * (size_t)k, hipMemcpyDeviceToDevice, st));
+  const UnsafeLabels unsafe{flag, bad.dev, counts_out};
+  HIPCHK(launch_fill_u32(flag, 1, 0u, st));
+  HIPCHK(launch_update(X, d, n, d, assign, k, w, centroids, d, st, nullptr, nullptr, 0, -1, &unsafe));
   HIPCHK(hipStreamSynchronize(st));
   ws.finished();
   if (*bad.host) return fail(SKM_EINVAL, "assignment label outside [0, k)");

@@ -275,7 +275,9 @@ struct ThetaRatios {
 hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio = nullptr, int nratio = 0);
 
 // every non-zero row of A scaled to unit Euclidean length, in place (cols, lda multiples of 4; A 16-byte aligned)
-hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st);
+// (absmax, optional: max |A| of the scaled rows is folded into it)
+hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st,
+                                 unsigned int *absmax = nullptr);
 
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
 hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t st, stamp_t *stamp = nullptr);
@@ -321,10 +323,13 @@ struct UpdateWs {
   int32_t *cursor;     // [k]
   int32_t *segoff;     // [k+1] exclusive scan of ceil(cnt / kSegPoints)
   int32_t *order;      // [n]   point ids grouped by cluster
+  int32_t *base = nullptr;   // [stable_order_words(n, k)] where stable_order_applies(n, k); NULL otherwise
   double *partial;     // [max_segments][ds]
   int64_t max_segments;
 };
 int64_t update_max_segments(int64_t n, int32_t k);
+bool stable_order_applies(int64_t n, int32_t k);
+int64_t stable_order_words(int64_t n, int32_t k);   // of `base` below, for n points or fewer
 // The grouping half of launch_update alone: cnt[k] sizes, off[k+1] starts, order[n] point ids grouped by label (cursor[k]
 // and segoff[k+1] are scratch).
 hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32_t *cnt, int32_t *off, int32_t *cursor,
@@ -334,12 +339,17 @@ int32_t update_sort_cap();
 // S (optional, [k][ds] fp64) receives the sum of every cluster; y_absmax (optional) the bit pattern of max |Y| of
 // the new centroids (the launcher clears it first).  With `accumulate` the sums of these n points are added to S
 // instead (one batch of a larger update); Y may then be NULL, and launch_means_from_sums finishes the update.
-// largest: the largest cluster size if known, else -1.  flag / flag_host: if *flag is not zero by then, Y is left as it
-// was; the word is copied to *flag_host (device-visible).  Labels outside [0, k) must have been left out of w.cnt.
+// largest: the largest cluster size if known, else -1.  unsafe: the labels are a caller's, unchecked, and w.cnt is not
+// known yet: they are counted first, and if one lies outside [0, k) nothing but *flag_host is written.
+struct UnsafeLabels {
+  unsigned int *flag;        // a zero word
+  unsigned int *flag_host;   // receives it (device-visible)
+  int32_t *counts_out;       // [k] or NULL: the sizes
+};
 hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, int32_t k,
                          const UpdateWs &w, float *Y, int64_t ldy, hipStream_t st, double *S = nullptr,
                          unsigned int *y_absmax = nullptr, int accumulate = 0, int32_t largest = -1,
-                         const unsigned int *flag = nullptr, unsigned int *flag_host = nullptr);
+                         const UnsafeLabels *unsafe = nullptr);
 hipError_t launch_add_counts(const int32_t *cnt, int32_t k, int32_t *total, hipStream_t st);
 hipError_t launch_means_from_sums(const double *S, const int32_t *cnt, int32_t k, int32_t ds, float *Y, int64_t ldy,
                                   unsigned int *y_absmax, hipStream_t st);
@@ -350,6 +360,7 @@ struct IncUpdateWs {
   int32_t *ent_lab;    // [capacity] cluster of the entry
   int32_t *order;      // [capacity]
   int32_t *cnt, *off, *cursor, *segoff;   // [k], [k+1], [k], [k+1]
+  int32_t *base = nullptr;                // [stable_order_words(capacity, k)], or NULL
   double *partial;     // [max_segments][ds]
   int64_t capacity, max_segments;
 };

@@ -531,35 +531,38 @@ hipError_t launch_absmax(const float *A, int64_t lda, int64_t rows, int32_t cols
 
 // ------------------------------------------------------------------ unit-length rows (angular metric)
 // One wavefront per row: sum of squares in fp32 over float4 loads, then the row is scaled in place.
-// Rows of zeros are left alone.
-__global__ void __launch_bounds__(256) normalize_rows_kernel(float *A, int64_t lda, int64_t rows, int32_t cols) {
+// Rows of zeros are left alone.  absmax (optional): the largest magnitude of the scaled rows.
+__global__ void __launch_bounds__(256) normalize_rows_kernel(float *A, int64_t lda, int64_t rows, int32_t cols,
+                                                             unsigned int *absmax) {
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  float *row = A + r * lda;
-  float s = 0.f;
-  for (int c = 4 * lane; c < cols; c += 256) {
-    const float4 v = *reinterpret_cast<const float4 *>(row + c);
-    s = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s))));
-  }
+  float m = 0.f;
+  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += (int64_t)gridDim.x * 4) {
+    float *row = A + r * lda;
+    float s = 0.f;
+    for (int c = 4 * lane; c < cols; c += 256) {
+      const float4 v = *reinterpret_cast<const float4 *>(row + c);
+      s = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s))));
+    }
 #pragma unroll
-  for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w, 64);
-  if (!(s > 0.f)) return;
-  const float inv = 1.0f / sqrtf(s);
-  for (int c = 4 * lane; c < cols; c += 256) {
-    float4 v = *reinterpret_cast<const float4 *>(row + c);
-    v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
-    *reinterpret_cast<float4 *>(row + c) = v;
+    for (int w = 1; w < 64; w <<= 1) s += __shfl_xor(s, w, 64);
+    if (!(s > 0.f)) continue;
+    const float inv = 1.0f / sqrtf(s);
+    for (int c = 4 * lane; c < cols; c += 256) {
+      float4 v = *reinterpret_cast<const float4 *>(row + c);
+      v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+      *reinterpret_cast<float4 *>(row + c) = v;
+    }
   }
+  if (absmax) block_absmax(m, absmax);
 }
 
 // cols and lda multiples of 4, A 16-byte aligned (the padded buffers of the library)
-hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st) {
+hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t cols, hipStream_t st, unsigned int *absmax) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   if ((reinterpret_cast<uintptr_t>(A) & 15u) || lda % 4 || cols % 4) return hipErrorInvalidValue;
-  const int64_t blocks = (rows + 3) / 4;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(normalize_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, lda, rows, cols);
+  const int64_t blocks = std::min<int64_t>((rows + 3) / 4, (int64_t)num_cus() * 32);
+  hipLaunchKernelGGL(normalize_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, lda, rows, cols, absmax);
   return hipGetLastError();
 }
 
@@ -567,13 +570,13 @@ hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t co
 // A workgroup takes 8192 consecutive points.  The cluster sizes are counted in LDS first when the k counters fit
 // (k <= FIN_LDS_BINS) and flushed once per workgroup: a million atomic increments on the 64 cache lines that hold 1024
 // counters took 0.2 ms per step; larger k spreads them over more lines and goes to memory directly.
+// (1024 threads share them: with 256 the loads of a workgroup were one long chain, 46 us a million points, 24 us.)
 // Small inputs (one small fit of many, as in the hierarchical fit) take 1024 points per workgroup instead: the
 // launch is then a few workgroups side by side rather than one long loop.  They count in LDS as well where a cluster
 // holds more than a handful of the points (direct increments of 20 000 points on 100 counters: 54 us, in LDS: 5 us).
 // The last workgroup to finish closes the step: it adds the objective's partials and the counter replicas in a fixed
 // order, takes the number of empty clusters and the largest size, turns the per-workgroup counts of changed points into
 // starts (for the incremental update), and writes the step's report straight into page-locked host memory.
-constexpr int FIN_THREADS = 256;
 constexpr int FIN_LDS_BINS = 8192;
 static int finalize_per_block(int64_t n) { return n >= (int64_t)1 << 18 ? 8192 : 1024; }
 int64_t finalize_blocks(int64_t n) { return (n + finalize_per_block(n) - 1) / finalize_per_block(n); }
@@ -583,9 +586,11 @@ __device__ inline T load_agent(const T *p) {   // a value that other workgroups 
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+template <int FIN_THREADS>
 __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeArgs a, int per_block, int in_lds) {
   __shared__ double red[FIN_THREADS];
-  __shared__ unsigned int redc[4];
+  constexpr int NW = FIN_THREADS / 64;
+  __shared__ unsigned int redc[NW];
   __shared__ int s_hist[FIN_LDS_BINS];
   __shared__ int s_last;
   const int tid = threadIdx.x;
@@ -631,17 +636,24 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
   }
   if (!a.done) return;
   if (tid == 0) {
-    __hip_atomic_store(a.obj_partial + blockIdx.x, (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.change_start + blockIdx.x, (int)(redc[0] + redc[1] + redc[2] + redc[3]), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    double t = 0.0;
+    unsigned int c = 0;
+    for (int u = 0; u < NW; u += 4) {
+      t += (red[u] + red[u + 1]) + (red[u + 2] + red[u + 3]);
+      c += (redc[u] + redc[u + 1]) + (redc[u + 2] + redc[u + 3]);
+    }
+    __hip_atomic_store(a.obj_partial + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.change_start + blockIdx.x, (int)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  // ---- the last workgroup closes the step
-  __threadfence();   // this thread's stores and increments before the ticket
+  // ---- the last workgroup closes the step.  What it reads of the others are agent-scope atomics (sizes, flag, partials,
+  // counters): they have been performed once they are no longer outstanding, so a wait orders them before the ticket.  (A
+  // release fence would write the caches' dirty lines back first, the eight megabytes of labels and distances among
+  // them: 50 us a million points, 28 us.)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) s_last = atomicAdd(a.done, 1u) == gridDim.x - 1;
+  if (tid == 0) s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   const int nblk = gridDim.x;
   {
     // objective: thread t adds the t-th contiguous part, the parts are added pairwise; changed points: the same parts
@@ -697,14 +709,19 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
   __syncthreads();
   if ((tid & 63) == 0) {
     s_hist[tid >> 6] = empty;
-    s_hist[4 + (tid >> 6)] = largest;
+    s_hist[NW + (tid >> 6)] = largest;
   }
   __syncthreads();
   if (tid == 0) {
     r->objective = red[0];
     r->flag = load_agent(a.flag);
-    r->nempty = (s_hist[0] + s_hist[1]) + (s_hist[2] + s_hist[3]);
-    r->largest = max(max(s_hist[4], s_hist[5]), max(s_hist[6], s_hist[7]));
+    int e = 0, l = 0;
+    for (int u = 0; u < NW; ++u) {
+      e += s_hist[u];
+      l = max(l, s_hist[NW + u]);
+    }
+    r->nempty = e;
+    r->largest = l;
     if (a.stamp_end) *a.stamp_end = wall_clock64();
   }
 }
@@ -714,7 +731,10 @@ hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st) {
   if (a.done && (!a.obj_partial || !a.change_start || !a.scal || !a.report || !a.flag)) return hipErrorInvalidValue;
   const int per_block = finalize_per_block(a.n);
   const int in_lds = a.cnt && a.k <= FIN_LDS_BINS && (per_block > 1024 || a.n >= 8 * (int64_t)a.k);
-  hipLaunchKernelGGL(finalize_assign_kernel, dim3((unsigned)finalize_blocks(a.n)), dim3(FIN_THREADS), 0, st, a, per_block, in_lds);
+  if (per_block > 1024)
+    hipLaunchKernelGGL(finalize_assign_kernel<1024>, dim3((unsigned)finalize_blocks(a.n)), dim3(1024), 0, st, a, per_block, in_lds);
+  else
+    hipLaunchKernelGGL(finalize_assign_kernel<256>, dim3((unsigned)finalize_blocks(a.n)), dim3(256), 0, st, a, per_block, in_lds);
   return hipGetLastError();
 }
 
@@ -877,74 +897,138 @@ static void launch_scatter_order(const int32_t *assign, int64_t n, int32_t k, co
                      in_lds ? (size_t)k * sizeof(int) : 0, st, assign, n, k, off, cursor, order, ids, per, in_lds);
 }
 
-// The cursor order above depends on scheduling; sorting every segment of `order` makes the summation order, and with it
-// every bit of the result, independent of it.  One workgroup per cluster.  Up to RANK_CAP ids every thread counts the
-// smaller ids of its own (they are distinct, so the count is the position; 244 ids: 0.3 us of compares and two barriers
-// where a bitonic network crosses 36: 82 -> 20 us for 4096 clusters of a million points); above, up to SORT_CAP,
-// odd-even merge in LDS; larger clusters are summed in fp64 in whatever order they were scattered (the fp64 sum of fp32
-// values then differs from the sorted-order sum by at most a few ulps of fp64, far below the fp32 rounding of the mean).
-constexpr int SORT_CAP = 8192, RANK_CAP = 2048;
-int32_t update_sort_cap() { return SORT_CAP; }
-__global__ void __launch_bounds__(256) rank_segments_kernel(const int32_t *off, int32_t *order) {
-  __shared__ __align__(16) int32_t s[RANK_CAP];
-  const int c = blockIdx.x;
-  const int lo = off[c], len = off[c + 1] - lo;
-  if (len < 2 || len > RANK_CAP) return;
-  const int len4 = (len + 3) & ~3;
-  for (int t = threadIdx.x; t < len4; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
+// The same grouping with the members of every label in ascending order, without atomics and without a sort: the
+// workgroups' label counts become starts (rank_base_kernel: for every label, over the workgroups in order), and a
+// workgroup places its points stably.  Its wavefronts own contiguous eighths of its range and count them first, so each
+// knows where its own members of a label start; it then walks its points 64 at a time, the lanes of one label finding
+// each other by one ballot per label bit.  Grouping a million points by 4096 labels: 17 (scatter) + 84 (ordering the
+// groups) us before, 40 us in all; by 1024 labels 11 + 200 us, 38 us.  For up to kStableLabels labels (the wavefronts'
+// counters fill the LDS) and not for a label range larger than the point set, where the count matrix would be the work.
+constexpr int STB_THREADS = 512, STB_WAVES = STB_THREADS / 64;
+constexpr int32_t kStableLabels = 8192;
+static int stable_per_block(int64_t n) { return n >= (int64_t)1 << 18 ? 8192 : 1024; }
+bool stable_order_applies(int64_t n, int32_t k) { return k <= kStableLabels && n >= 8 * (int64_t)k; }
+static int64_t stable_order_blocks(int64_t n) { return (n + stable_per_block(n) - 1) / stable_per_block(n); }
+int64_t stable_order_words(int64_t n, int32_t k) {   // for this many points or fewer
+  return std::max<int64_t>(stable_order_blocks(n), std::min<int64_t>((n + 1023) / 1024, 256)) * k;
+}
+
+// base[blk][c] = number of points of workgroup blk with label c; labels outside [0, k) set bit 2 of *flag (optional)
+__global__ void __launch_bounds__(STB_THREADS) block_counts_kernel(const int32_t *lab, int64_t n, int32_t k, int32_t *base,
+                                                                   int per_block, unsigned int *flag) {
+  extern __shared__ int s_bins[];
+  for (int b = threadIdx.x; b < k; b += STB_THREADS) s_bins[b] = 0;
   __syncthreads();
-  for (int t0 = 0; t0 < len; t0 += 1024) {   // four ids of its own per thread and pass over the list
-    int mine[4], rank[4];
+  const int64_t i0 = (int64_t)blockIdx.x * per_block;
+  for (int t = threadIdx.x; t < per_block; t += STB_THREADS) {
+    if (i0 + t >= n) break;
+    const int a = lab[i0 + t];
+    if ((unsigned int)a < (unsigned int)k) atomicAdd(s_bins + a, 1);
+    else if (flag) atomicOr(flag, 4u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < k; b += STB_THREADS) base[(int64_t)blockIdx.x * k + b] = s_bins[b];
+}
+// counts -> starts inside the label: base[blk][c] = points of label c in the workgroups before blk; their total to
+// cnt[c] (optional)
+__global__ void __launch_bounds__(64) rank_base_kernel(int32_t *base, int32_t nblk, int32_t k, int32_t *cnt) {
+  const int c = blockIdx.x * 64 + threadIdx.x;
+  if (c >= k) return;
+  int run = 0;
+  int b = 0;
+  for (; b + 16 <= nblk; b += 16) {
+    int v[16];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int t = t0 + 256 * u + threadIdx.x;
-      mine[u] = t < len ? s[t] : -0x7fffffff - 1;
-      rank[u] = 0;
-    }
-    const bool one = t0 + 256 >= len;   // only the first of the four is in use
-    for (int q = 0; q < len4; q += 4) {
-      const int4 o = *reinterpret_cast<const int4 *>(s + q);
-      rank[0] += (o.x < mine[0]) + (o.y < mine[0]) + (o.z < mine[0]) + (o.w < mine[0]);
-      if (!one)
+    for (int u = 0; u < 16; ++u) v[u] = base[(int64_t)(b + u) * k + c];
 #pragma unroll
-        for (int u = 1; u < 4; ++u) rank[u] += (o.x < mine[u]) + (o.y < mine[u]) + (o.z < mine[u]) + (o.w < mine[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int t = t0 + 256 * u + threadIdx.x;
-      if (t < len) order[lo + rank[u]] = mine[u];
+    for (int u = 0; u < 16; ++u) {
+      base[(int64_t)(b + u) * k + c] = run;
+      run += v[u];
     }
   }
+  for (; b < nblk; ++b) {
+    const int v = base[(int64_t)b * k + c];
+    base[(int64_t)b * k + c] = run;
+    run += v;
+  }
+  if (cnt) cnt[c] = run;
 }
-__global__ void __launch_bounds__(256) sort_segments_kernel(const int32_t *off, int32_t *order) {
-  __shared__ int32_t s[SORT_CAP];
-  const int c = blockIdx.x;
-  const int lo = off[c], len = off[c + 1] - lo;
-  if (len <= RANK_CAP || len > SORT_CAP) return;
-  int np2 = 1;
-  while (np2 < len) np2 <<= 1;
-  for (int t = threadIdx.x; t < np2; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
+__global__ void __launch_bounds__(STB_THREADS) stable_scatter_kernel(const int32_t *lab, int64_t n, int32_t k, int bits,
+                                                                     const int32_t *off, const int32_t *base,
+                                                                     const int32_t *ids, int32_t *order, int per_block) {
+  extern __shared__ unsigned short s_cnt[];   // [STB_WAVES][k]: members before this wavefront's next one, in the workgroup
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int per_wave = per_block / STB_WAVES;   // a multiple of 64
+  const int64_t i0 = (int64_t)blockIdx.x * per_block + (int64_t)w * per_wave;
+  unsigned short *mine = s_cnt + (size_t)w * k;
+  for (int b = threadIdx.x; b < STB_WAVES * k / 2; b += STB_THREADS) reinterpret_cast<unsigned int *>(s_cnt)[b] = 0u;
+  if ((STB_WAVES * k) & 1) s_cnt[STB_WAVES * k - 1] = 0;
   __syncthreads();
-  for (int kk = 2; kk <= np2; kk <<= 1)
-    for (int jj = kk >> 1; jj > 0; jj >>= 1) {
-      for (int t = threadIdx.x; t < np2; t += 256) {
-        const int p = t ^ jj;
-        if (p > t) {
-          const int32_t a = s[t], b = s[p];
-          const bool up = (t & kk) == 0;
-          if ((a > b) == up) { s[t] = b; s[p] = a; }
-        }
-      }
-      __syncthreads();
+  // lanes of this round with the same label as this lane (all lanes take part; a lane without a point has label k)
+  auto peers = [&](int a) {
+    unsigned long long m = ~0ull;
+    for (int b = 0; b < bits; ++b) {
+      const unsigned long long on = __ballot((a >> b) & 1);
+      m &= ((a >> b) & 1) ? on : ~on;
     }
-  for (int t = threadIdx.x; t < len; t += 256) order[lo + t] = s[t];
+    return m;
+  };
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (int t = 0; t < per_wave; t += 64) {
+    const int64_t i = i0 + t + lane;
+    int a = i < n ? lab[i] : k;
+    if ((unsigned int)a > (unsigned int)k) a = k;
+    const unsigned long long m = peers(a);
+    if (a < k && (m & below) == 0) mine[a] = (unsigned short)(mine[a] + __popcll(m));
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < k; c += STB_THREADS) {   // counts of the wavefronts -> members before each of them
+    unsigned short run = 0;
+#pragma unroll
+    for (int u = 0; u < STB_WAVES; ++u) {
+      const unsigned short v = s_cnt[(size_t)u * k + c];
+      s_cnt[(size_t)u * k + c] = run;
+      run = (unsigned short)(run + v);
+    }
+  }
+  __syncthreads();
+  for (int t = 0; t < per_wave; t += 64) {
+    const int64_t i = i0 + t + lane;
+    int a = i < n ? lab[i] : k;
+    if ((unsigned int)a > (unsigned int)k) a = k;
+    const unsigned long long m = peers(a);
+    int rank = 0;
+    if (a < k) rank = mine[a] + __popcll(m & below);
+    __builtin_amdgcn_wave_barrier();   // every lane has read the counter
+    if (a < k) {
+      if ((m & below) == 0) mine[a] = (unsigned short)(mine[a] + __popcll(m));
+      order[off[a] + base[(int64_t)blockIdx.x * k + a] + rank] = ids ? ids[i] : (int32_t)i;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
 }
-// largest: size of the largest segment where the host knows it, -1 where it does not
-static void launch_sort_segments(const int32_t *off, int32_t *order, int32_t k, int64_t n, int32_t largest, hipStream_t st) {
-  const int64_t most = largest >= 0 ? largest : n;
-  if (most < 2) return;
-  hipLaunchKernelGGL(rank_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
-  if (most > RANK_CAP) hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+// the counting half (cnt, if given, receives the label counts, flag as in block_counts_kernel) ...
+static void launch_stable_counts(const int32_t *lab, int64_t n, int32_t k, int32_t *base, int32_t *cnt, unsigned int *flag,
+                                 hipStream_t st) {
+  const unsigned nblk = (unsigned)stable_order_blocks(n);
+  hipLaunchKernelGGL(block_counts_kernel, dim3(nblk), dim3(STB_THREADS), (size_t)k * sizeof(int), st, lab, n, k, base,
+                     stable_per_block(n), flag);
+  hipLaunchKernelGGL(rank_base_kernel, dim3((unsigned)((k + 63) / 64)), dim3(64), 0, st, base, (int32_t)nblk, k, cnt);
+}
+// ... and the placing half, with the labels' starts known
+static hipError_t launch_stable_scatter(const int32_t *lab, int64_t n, int32_t k, const int32_t *off, const int32_t *base,
+                                        int32_t *order, const int32_t *ids, hipStream_t st) {
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(stable_scatter_kernel),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                        STB_WAVES * kStableLabels * (int)sizeof(unsigned short) + 4);
+  if (attr_rc != hipSuccess) return attr_rc;
+  int bits = 1;
+  while ((1 << bits) <= k) ++bits;   // labels 0 .. k
+  hipLaunchKernelGGL(stable_scatter_kernel, dim3((unsigned)stable_order_blocks(n)), dim3(STB_THREADS),
+                     (size_t)STB_WAVES * k * sizeof(unsigned short) + 4, st, lab, n, k, bits, off, base, ids, order,
+                     stable_per_block(n));
+  return hipGetLastError();
 }
 
 // One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
@@ -1036,7 +1120,8 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
 __global__ void __launch_bounds__(256) centroid_mean_kernel(const double *partial, int32_t ds, const int32_t *cnt,
                                                             const int32_t *segoff, float *Y, int64_t ldy, double *S,
                                                             int accumulate, unsigned int *y_absmax,
-                                                            const unsigned int *flag, unsigned int *flag_host) {
+                                                            const unsigned int *flag, unsigned int *flag_host,
+                                                            int32_t *counts_out) {
   const int c = blockIdx.x;
   if (flag) {   // labels that the counting pass found outside [0, k): reported, and Y stays what it was
     const unsigned int f = *flag;
@@ -1044,6 +1129,7 @@ __global__ void __launch_bounds__(256) centroid_mean_kernel(const double *partia
     if (f) return;
   }
   const int n_c = cnt[c];
+  if (counts_out && blockIdx.y == 0 && threadIdx.x == 0) counts_out[c] = n_c;
   const int col = blockIdx.y * 256 + threadIdx.x;
   float y = 0.f;
   if (col < ds) {
@@ -1216,13 +1302,38 @@ __global__ void __launch_bounds__(256) direct_update_kernel(const float *Xr, int
   if (y_absmax) block_absmax(vmax, y_absmax);
 }
 
+// order[] = the items grouped by label (off: the groups' starts), ascending in a group: stably where `base` is given, else
+// scattered and then ordered
+static hipError_t group_by_label(const int32_t *lab, int64_t n, int32_t k, const int32_t *off, int32_t *cursor, int32_t *base,
+                                 int32_t *order, const int32_t *ids, int32_t largest, hipStream_t st) {
+  if (base) {
+    launch_stable_counts(lab, n, k, base, nullptr, nullptr, st);
+    return launch_stable_scatter(lab, n, k, off, base, order, ids, st);
+  }
+  launch_scatter_order(lab, n, k, off, cursor, order, ids, st);
+  launch_sort_segments(off, order, k, n, largest, st);
+  return hipSuccess;
+}
+
 hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, int32_t k,
                          const UpdateWs &w, float *Y, int64_t ldy, hipStream_t st, double *S, unsigned int *y_absmax,
-                         int accumulate, int32_t largest, const unsigned int *flag, unsigned int *flag_host) {
-  if ((accumulate && !S) || (!Y && y_absmax) || (flag != nullptr) != (flag_host != nullptr)) return hipErrorInvalidValue;
+                         int accumulate, int32_t largest, const UnsafeLabels *unsafe) {
+  if ((w.base && !stable_order_applies(n, k)) || (accumulate && !S) || (!Y && y_absmax)) return hipErrorInvalidValue;
+  if (unsafe) {   // labels nobody has counted or checked
+    if (w.base) {
+      launch_stable_counts(assign, n, k, w.base, w.cnt, unsafe->flag, st);
+    } else {
+      hipError_t rc = launch_fill_u32(reinterpret_cast<unsigned int *>(w.cnt), k, 0u, st);
+      if (rc == hipSuccess) rc = launch_histogram(assign, n, k, w.cnt, unsafe->flag, st);
+      if (rc != hipSuccess) return rc;
+    }
+  }
   hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, w.cnt, k, w.off, w.cursor, w.segoff, y_absmax);
-  launch_scatter_order(assign, n, k, w.off, w.cursor, w.order, nullptr, st);
-  launch_sort_segments(w.off, w.order, k, n, largest, st);
+  {
+    hipError_t rc = unsafe && w.base ? launch_stable_scatter(assign, n, k, w.off, w.base, w.order, nullptr, st)
+                                     : group_by_label(assign, n, k, w.off, w.cursor, w.base, w.order, nullptr, largest, st);
+    if (rc != hipSuccess) return rc;
+  }
   const unsigned slices = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims, or 256 dims, per workgroup
   const bool aligned = (reinterpret_cast<uintptr_t>(Xr) & 15u) == 0 && ldx % 4 == 0 && ds % 4 == 0;
   if (aligned)
@@ -1232,7 +1343,8 @@ hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, co
     hipLaunchKernelGGL((segment_sum_kernel<false, false>), dim3((unsigned)w.max_segments, slices), dim3(256), 0, st, Xr, ldx,
                        ds, k, w.off, w.segoff, w.order, w.partial);
   hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, w.partial, ds, w.cnt, w.segoff, Y, ldy, S,
-                     accumulate, y_absmax, flag, flag_host);
+                     accumulate, y_absmax, unsafe ? (const unsigned int *)unsafe->flag : nullptr,
+                     unsafe ? unsafe->flag_host : nullptr, unsafe ? unsafe->counts_out : nullptr);
   return hipGetLastError();
 }
 
@@ -1274,13 +1386,15 @@ hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, in
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, inc.cnt, k, inc.off, inc.cursor, inc.segoff,
                      (unsigned int *)nullptr);
-  launch_scatter_order(inc.ent_lab, m2, k, inc.off, inc.cursor, inc.order, inc.ent_id, st);
-  launch_sort_segments(inc.off, inc.order, k, m2, -1, st);
+  // (the entries are in ascending order of their points, joined before left: stable grouping keeps that)
+  rc = group_by_label(inc.ent_lab, m2, k, inc.off, inc.cursor, stable_order_applies(m2, k) ? inc.base : nullptr, inc.order,
+                      inc.ent_id, -1, st);
+  if (rc != hipSuccess) return rc;
   const int64_t segs = std::min<int64_t>(inc.max_segments, (int64_t)k + m2 / kSegPoints + 1);
   hipLaunchKernelGGL((segment_sum_kernel<true, true>), dim3((unsigned)segs, slices), dim3(256), 0, st, Xr, ldx, ds, k, inc.off,
                      inc.segoff, inc.order, inc.partial);
   hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, inc.partial, ds, w.cnt, inc.segoff, Y, ldy,
-                     S, 1, y_absmax, (const unsigned int *)nullptr, (unsigned int *)nullptr);
+                     S, 1, y_absmax, (const unsigned int *)nullptr, (unsigned int *)nullptr, (int32_t *)nullptr);
   return hipGetLastError();
 }
 
