@@ -1031,6 +1031,76 @@ static hipError_t launch_stable_scatter(const int32_t *lab, int64_t n, int32_t k
   return hipGetLastError();
 }
 
+// The cursor order above depends on scheduling; sorting every segment of `order` makes the summation order, and with it
+// every bit of the result, independent of it.  One workgroup per cluster.  Up to RANK_CAP ids every thread counts the
+// smaller ids of its own (they are distinct, so the count is the position; 244 ids: 0.3 us of compares and two barriers
+// where a bitonic network crosses 36: 82 -> 20 us for 4096 clusters of a million points); above, up to SORT_CAP,
+// odd-even merge in LDS; larger clusters are summed in fp64 in whatever order they were scattered (the fp64 sum of fp32
+// values then differs from the sorted-order sum by at most a few ulps of fp64, far below the fp32 rounding of the mean).
+constexpr int SORT_CAP = 8192, RANK_CAP = 2048;
+int32_t update_sort_cap() { return SORT_CAP; }
+__global__ void __launch_bounds__(256) rank_segments_kernel(const int32_t *off, int32_t *order) {
+  __shared__ __align__(16) int32_t s[RANK_CAP];
+  const int c = blockIdx.x;
+  const int lo = off[c], len = off[c + 1] - lo;
+  if (len < 2 || len > RANK_CAP) return;
+  const int len4 = (len + 3) & ~3;
+  for (int t = threadIdx.x; t < len4; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
+  __syncthreads();
+  for (int t0 = 0; t0 < len; t0 += 1024) {   // four ids of its own per thread and pass over the list
+    int mine[4], rank[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 256 * u + threadIdx.x;
+      mine[u] = t < len ? s[t] : -0x7fffffff - 1;
+      rank[u] = 0;
+    }
+    const bool one = t0 + 256 >= len;   // only the first of the four is in use
+    for (int q = 0; q < len4; q += 4) {
+      const int4 o = *reinterpret_cast<const int4 *>(s + q);
+      rank[0] += (o.x < mine[0]) + (o.y < mine[0]) + (o.z < mine[0]) + (o.w < mine[0]);
+      if (!one)
+#pragma unroll
+        for (int u = 1; u < 4; ++u) rank[u] += (o.x < mine[u]) + (o.y < mine[u]) + (o.z < mine[u]) + (o.w < mine[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 256 * u + threadIdx.x;
+      if (t < len) order[lo + rank[u]] = mine[u];
+    }
+  }
+}
+__global__ void __launch_bounds__(256) sort_segments_kernel(const int32_t *off, int32_t *order) {
+  __shared__ int32_t s[SORT_CAP];
+  const int c = blockIdx.x;
+  const int lo = off[c], len = off[c + 1] - lo;
+  if (len <= RANK_CAP || len > SORT_CAP) return;
+  int np2 = 1;
+  while (np2 < len) np2 <<= 1;
+  for (int t = threadIdx.x; t < np2; t += 256) s[t] = t < len ? order[lo + t] : 0x7fffffff;
+  __syncthreads();
+  for (int kk = 2; kk <= np2; kk <<= 1)
+    for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+      for (int t = threadIdx.x; t < np2; t += 256) {
+        const int p = t ^ jj;
+        if (p > t) {
+          const int32_t a = s[t], b = s[p];
+          const bool up = (t & kk) == 0;
+          if ((a > b) == up) { s[t] = b; s[p] = a; }
+        }
+      }
+      __syncthreads();
+    }
+  for (int t = threadIdx.x; t < len; t += 256) order[lo + t] = s[t];
+}
+// largest: size of the largest segment where the host knows it, -1 where it does not
+static void launch_sort_segments(const int32_t *off, int32_t *order, int32_t k, int64_t n, int32_t largest, hipStream_t st) {
+  const int64_t most = largest >= 0 ? largest : n;
+  if (most < 2) return;
+  hipLaunchKernelGGL(rank_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+  if (most > RANK_CAP) hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
+}
+
 // One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
 // `order` (each a contiguous row read).  Wavefront w takes the points p0 + w, p0 + w + 4, ... of the segment, four
 // rows in flight per thread, fp64 sums per thread; the four wavefronts' sums are added in a fixed order, so the
