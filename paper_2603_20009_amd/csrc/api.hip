@@ -832,6 +832,16 @@ int64_t sample_size(int64_t n, int32_t k, float frac) {
   const int64_t s = (int64_t)std::llround((double)frac * (double)n);
   return std::min<int64_t>(std::max<int64_t>(s, k), n);
 }
+// Sizes of the form through the one-product multiply (etr.hip).
+struct GtPlan {
+  bool on = false;
+  int32_t ds = 0, ngroups = 0;
+  int64_t nsel = 0, chunk = 0;
+  unsigned int cap = 0;
+  size_t bytes = 0;   // of the call's buffers
+};
+GtPlan gt_plan(int64_t n, int32_t d, int32_t nq, int32_t K);
+size_t gt_full_bytes(int64_t n, int32_t nq);
 size_t fit_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &p) {
   const size_t ds0 = (size_t)((d + 15) / 16 * 16);
   if (p.sample_frac > 0.f && p.sample_frac < 1.f) {
@@ -851,7 +861,8 @@ size_t fit_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &p) 
                 (size_t)k * 16 + ((size_t)32 << 20);
   if (p.etr && p.nq > 0 && p.topk > 0) {
     const size_t nq = (size_t)p.nq;
-    need += (size_t)n * 4 + nq * (size_t)std::min<int64_t>(n, 1 << 16) * 4 + nq * (size_t)p.topk * 8 + nq * (ds0 + d) * 4 +
+    const GtPlan plan = gt_plan(n, d, p.nq, p.topk);   // (and, should a candidate list run over, the full form behind it)
+    need += (plan.on ? plan.bytes : 0) + gt_full_bytes(n, p.nq) + nq * (size_t)p.topk * 8 + nq * (ds0 + d) * 4 +
             nq * 8 + nq * (size_t)k * 4 + (size_t)k * 4 + ((size_t)1 << 16);
   }
   return need;
@@ -1423,10 +1434,80 @@ int unrotate_into(const float *Yr, int64_t ldy, int32_t rows, int32_t d, int32_t
 }
 
 // Ground truth of ETR (Section 3.3): the K nearest points of every query by L2 over X (original space, lowest index
-// on ties) as packed (distance, index) keys, ascending.  The scores q . x come from the GEMM in chunks of 65 536
-// points; each chunk is merged into the running lists.  amax_x / amax_q: one word each for the operand bounds.
+// on ties) as packed (distance, index) keys, ascending.
 constexpr int64_t kGtChunk = 1 << 16;
-int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const float *Q, int32_t nq, int32_t K,
+
+GtPlan gt_plan(int64_t n, int32_t d, int32_t nq, int32_t K) {
+  GtPlan p;
+  p.ds = round_up(d, 32);
+  // the sample: large enough that about 512 points of a query lie below its threshold, 65 536 at least (one pass of the
+  // multiply over it costs little beside the one over all points)
+  p.nsel = std::min<int64_t>(n, std::max<int64_t>(1 << 16, (int64_t)K * (n / 512)));
+  const int64_t groups = (p.nsel + 63) / 64;
+  // too few points for a useful threshold, or too many for its sort: the score matrix in full
+  if (groups < 2 * (int64_t)K || groups > kGtMaxGroups || n >= ((int64_t)1 << 31)) return p;
+  p.ngroups = (int32_t)groups;
+  // chunks whose fp16 copy (128 MB) is still in the Infinity Cache when the multiply reads it, whole tiles
+  p.chunk = std::max<int64_t>(16384, ((int64_t)64 << 20) / p.ds / 256 * 256);
+  p.chunk = std::min<int64_t>(p.chunk, (n + 255) / 256 * 256);
+  const double expect = (double)K * (double)n / (double)p.nsel;
+  p.cap = 1024;
+  while ((double)p.cap < 4.0 * expect + 512.0 && p.cap < kGtMaxCand) p.cap <<= 1;
+  p.on = (double)p.cap >= 2.0 * expect;
+  p.bytes = (size_t)(p.chunk + nq) * p.ds * 2 + (size_t)p.chunk * 8 + (size_t)nq * (16 + 4 + (size_t)p.ngroups * 4 + (size_t)p.cap * 8) + 8192;
+  return p;
+}
+size_t gt_full_bytes(int64_t n, int32_t nq) { return (size_t)n * 4 + (size_t)nq * (size_t)std::min<int64_t>(n, kGtChunk) * 4 + 4096; }
+
+// *overflow_host (page-locked, valid once the stream has been waited for) != 0: a candidate list ran over, gt_keys is void
+int ground_truth_screened(Pool &pool, const GtPlan &p, const float *X, int64_t n, int32_t d, const float *Q, int32_t nq,
+                          int32_t K, unsigned long long *gt_keys, unsigned int *overflow_dev, hipStream_t st) {
+  uint32_t *plane = nullptr, *qplane = nullptr;
+  float *scale = nullptr, *term = nullptr, *qscale = nullptr, *qterm = nullptr, *tq = nullptr, *rterm = nullptr, *gmin = nullptr;
+  unsigned long long *cand = nullptr;
+  unsigned int *words = nullptr;   // max norm of the points so far | of the sample | of the queries | [nq] list lengths
+  HIPCHK(pool.get(&plane, (size_t)p.chunk * (p.ds / 2)));
+  HIPCHK(pool.get(&qplane, (size_t)nq * (p.ds / 2)));
+  HIPCHK(pool.get(&scale, (size_t)p.chunk));
+  HIPCHK(pool.get(&term, (size_t)p.chunk));
+  HIPCHK(pool.get(&qscale, (size_t)nq));
+  HIPCHK(pool.get(&qterm, (size_t)nq));
+  HIPCHK(pool.get(&tq, (size_t)nq));
+  HIPCHK(pool.get(&rterm, (size_t)nq));
+  HIPCHK(pool.get(&gmin, (size_t)nq * p.ngroups));
+  HIPCHK(pool.get(&cand, (size_t)nq * p.cap));
+  HIPCHK(pool.get(&words, (size_t)nq + 4));
+  HIPCHK(launch_fill_u32(words, (int64_t)nq + 4, 0u, st));
+  unsigned int *mx = words, *mx_sample = words + 1, *mx_q = words + 2, *count = words + 4;
+  HIPCHK(launch_gt_convert(Q, d, nq, nq, 0, nq, d, p.ds, qplane, qscale, qterm, mx_q, st));
+  NeighbourLaunch a{};
+  a.A = qplane; a.B = plane; a.M = nq; a.ds = p.ds;
+  a.row_term = rterm; a.row_scale = qscale; a.col_term = term; a.col_scale = scale;
+  a.group_min = gmin; a.ngroups = p.ngroups;
+  a.cand = cand; a.cand_count = count; a.cand_cap = p.cap;
+  for (int64_t r0 = 0; r0 < p.nsel; r0 += p.chunk) {
+    const int64_t m = std::min<int64_t>(p.chunk, p.nsel - r0);
+    HIPCHK(launch_gt_convert(X, d, n, p.nsel, r0, m, d, p.ds, plane, scale, term, mx_sample, st));
+    a.N = (int32_t)m;
+    a.group0 = (int32_t)(r0 / 64);
+    HIPCHK(launch_neighbour_screen(a, true, st));
+  }
+  HIPCHK(launch_gt_threshold(gmin, p.ngroups, nq, K, qscale, qterm, mx_sample, d, tq, st));
+  for (int64_t r0 = 0; r0 < n; r0 += p.chunk) {
+    const int64_t m = std::min<int64_t>(p.chunk, n - r0);
+    HIPCHK(launch_gt_convert(X, d, n, n, r0, m, d, p.ds, plane, scale, term, mx, st));
+    HIPCHK(launch_gt_terms(tq, qscale, qterm, nq, mx, d, rterm, st));
+    a.N = (int32_t)m;
+    a.point0 = r0;
+    HIPCHK(launch_neighbour_screen(a, false, st));
+  }
+  HIPCHK(launch_gt_select(cand, count, p.cap, nq, K, X, d, Q, d, qscale, qterm, mx, gt_keys, overflow_dev, st));
+  return SKM_OK;
+}
+
+// The scores q . x from the GEMM in chunks of 65 536 points; each chunk is merged into the running lists.  amax_x /
+// amax_q: one word each for the operand bounds.
+int ground_truth_full(Pool &pool, const float *X, int64_t n, int32_t d, const float *Q, int32_t nq, int32_t K,
                       unsigned int *amax_x, unsigned int *amax_q, unsigned long long *gt_keys, hipStream_t st) {
   float *xnorm = nullptr, *S = nullptr;
   const int64_t colchunk = std::min<int64_t>(n, kGtChunk);
@@ -1444,6 +1525,24 @@ int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const fl
     HIPCHK(launch_topk_merge(S, colchunk, nq, (int32_t)m, c0, xnorm, K, gt_keys, st));
   }
   return SKM_OK;
+}
+
+// Waits for the stream (in the screened form: for the word that says whether a list ran over).
+int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const float *Q, int32_t nq, int32_t K,
+                      unsigned int *amax_x, unsigned int *amax_q, unsigned long long *gt_keys, hipStream_t st) {
+  const GtPlan plan = gt_plan(n, d, nq, K);
+  if (plan.on) {
+    PinnedWord over;
+    if (!over.host) return fail(SKM_EHIP, "hipHostMalloc failed");
+    *over.host = 0u;
+    if (int rc = ground_truth_screened(pool, plan, X, n, d, Q, nq, K, gt_keys, over.dev, st)) {
+      (void)hipStreamSynchronize(st);
+      return rc;
+    }
+    HIPCHK(hipStreamSynchronize(st));
+    if (!*over.host) return SKM_OK;
+  }
+  return ground_truth_full(pool, X, n, d, Q, nq, K, amax_x, amax_q, gt_keys, st);
 }
 
 // A single assignment step regroups the points itself (see assign_impl) when there are thousands of centroids, several
@@ -2678,7 +2777,8 @@ int skm_etr_ground_truth(const float *X, int64_t n, int32_t d, const float *quer
   if (n < 1 || n >= (int64_t)1 << 31 || d < 1 || d > 16384) return fail(SKM_EINVAL, "shape out of range");
   if (nq < 1 || topk < 1 || topk > 256) return fail(SKM_EINVAL, "nq >= 1 and 1 <= topk <= 256 required");
   hipStream_t st = (hipStream_t)stream;
-  CallArena ws((size_t)n * 4 + (size_t)nq * (size_t)std::min<int64_t>(n, kGtChunk) * 4 + (size_t)nq * topk * 8 + 4096);
+  const GtPlan plan = gt_plan(n, d, nq, topk);
+  CallArena ws((plan.on ? plan.bytes : gt_full_bytes(n, nq)) + (size_t)nq * topk * 8 + 4096);
   Pool pool;
   unsigned int *amax = nullptr;
   unsigned long long *keys = nullptr;

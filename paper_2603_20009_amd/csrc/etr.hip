@@ -3,6 +3,8 @@
 // The score matrices come from the MFMA GEMM; these kernels only select.
 #include "skm_internal.h"
 
+#include <algorithm>
+
 namespace skm {
 
 __device__ inline unsigned long long block_min_u64(unsigned long long v, unsigned long long *red) {
@@ -136,6 +138,237 @@ hipError_t launch_recall_scores(const float *S, int64_t lds, int32_t nq, int32_t
   if (nprobe > MAX_PROBE || nprobe < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(recall_kernel, dim3(nq), dim3(256), 0, st, S, lds, k, ynorm, nprobe, gt_keys, K, assign, hits,
                      total);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- ground truth through a one-product multiply
+// The K nearest points of a query need exact scores only near the K-th smallest: the score matrix of all pairs, in full
+// arithmetic and through memory, was nine tenths of the time (1000 queries over 1M x 768: 10.1 ms, of it 5.7 ms of
+// three-product multiply, 4.2 GB of scores written and read again, 1.4 ms for two passes that bound and norm the rows).
+// Here
+//   1. a sample of the points, spread evenly, is multiplied in one fp16 product; the K-th smallest of the minima over groups
+//      of 64 points is an upper bound of the K-th smallest score (K different points have scores at or below it), up to
+//      the error of a one-product score;
+//   2. all points are multiplied the same way, in chunks whose fp16 copy stays in the Infinity Cache; a pair whose score
+//      is within twice the error bound of that threshold becomes a candidate (K n / sample and a few per query);
+//   3. of a query's candidates, those within twice the bound of their own K-th smallest score get their exact distance
+//      (direct form, fp32), and the K smallest (distance, index) are the result.
+// Error bound: a row is scaled by the power of two that brings its largest value into [2^14, 2^15) and rounded to fp16, a
+// relative error of 2^-11 per value (absolute 2^-25 below 2^-14), so q.x is off by at most (2^-10 + 2^-22) ||q|| ||x|| plus
+// d 2^-38 max|q| max|x| (Cauchy-Schwarz), taken 10 % larger for the fp32 accumulation; the score by twice that.  The
+// largest norm stands for ||x||.  A list that runs over its capacity makes the caller take the full path instead.
+__device__ inline float gt_band(float qnorm2, float maxnorm2, int d) {
+  const float q = sqrtf(fmaxf(qnorm2, 0.f)), x = sqrtf(fmaxf(maxnorm2, 0.f));
+  return (2.f * 1.1f / 1024.f + (float)d * (1.f / 68719476736.f)) * q * x + (1e-6f + 1e-9f * (float)d) * (maxnorm2 + 2.f * q * x);
+}
+
+// one wavefront per row; NV > 0: the row in registers (ds <= 256 NV), 0: two passes over it
+template <int NV, bool ALIGNED>
+__global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t ldx, int64_t n, int64_t nsel, int64_t row0,
+                                                         int64_t rows, int32_t d, int32_t ds, uint32_t *plane, float *scale,
+                                                         float *term, unsigned int *maxnorm) {
+  __shared__ float s_m[4];
+  const int lane = threadIdx.x & 63;
+  float most = 0.f;
+  auto load = [&](const float *x, int c) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ALIGNED) {
+      if (c < d) v = *reinterpret_cast<const float4 *>(x + c);
+    } else {
+      if (c + 0 < d) v.x = x[c];
+      if (c + 1 < d) v.y = x[c + 1];
+      if (c + 2 < d) v.z = x[c + 2];
+      if (c + 3 < d) v.w = x[c + 3];
+    }
+    return v;
+  };
+  auto emit = [&](uint32_t *dst, int c, const float4 &v, float sc) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+    const f32x2_t p0 = {v.x * sc, v.y * sc}, p1 = {v.z * sc, v.w * sc};
+    *reinterpret_cast<uint2 *>(dst + c / 2) =
+        make_uint2(__builtin_bit_cast(unsigned int, __builtin_convertvector(p0, f16x2_t)),
+                   __builtin_bit_cast(unsigned int, __builtin_convertvector(p1, f16x2_t)));
+  };
+  for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < rows; i += (int64_t)gridDim.x * 4) {
+    const int64_t src = nsel == n ? row0 + i : (int64_t)(((double)(row0 + i) + 0.5) * ((double)n / (double)nsel));
+    const float *x = X + (src < n ? src : n - 1) * ldx;
+    float4 v[NV > 0 ? NV : 1];
+    float s = 0.f, m = 0.f;
+    auto take = [&](const float4 &w) {
+      s = fmaf(w.x, w.x, fmaf(w.y, w.y, fmaf(w.z, w.z, fmaf(w.w, w.w, s))));
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))));
+    };
+    if (NV > 0) {
+#pragma unroll
+      for (int u = 0; u < NV; ++u) v[u] = load(x, 256 * u + 4 * lane);
+#pragma unroll
+      for (int u = 0; u < NV; ++u) take(v[u]);
+    } else {
+      for (int c = 4 * lane; c < ds; c += 256) take(load(x, c));
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      s += __shfl_xor(s, o, 64);
+      m = fmaxf(m, __shfl_xor(m, o, 64));
+    }
+    const float sc = m > 0.f ? split_scale(__builtin_bit_cast(unsigned int, m)) : 1.f;
+    uint32_t *dst = plane + i * (int64_t)(ds / 2);
+    if (NV > 0) {
+#pragma unroll
+      for (int u = 0; u < NV; ++u)
+        if (256 * u + 4 * lane < ds) emit(dst, 256 * u + 4 * lane, v[u], sc);
+    } else {
+      for (int c = 4 * lane; c < ds; c += 256) emit(dst, c, load(x, c), sc);
+    }
+    if (lane == 0) {
+      scale[i] = sc;
+      term[i] = 0.5f * s * sc;
+    }
+    most = fmaxf(most, s);
+  }
+  if (lane == 0) s_m[threadIdx.x >> 6] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned int b = __builtin_bit_cast(unsigned int, fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3])));
+    if (b > __atomic_load_n(maxnorm, __ATOMIC_RELAXED)) atomicMax(maxnorm, b);
+  }
+}
+
+hipError_t launch_gt_convert(const float *X, int64_t ldx, int64_t n, int64_t nsel, int64_t row0, int64_t rows, int32_t d,
+                             int32_t ds, uint32_t *plane, float *scale, float *term, unsigned int *maxnorm, hipStream_t st) {
+  if (rows <= 0) return hipSuccess;
+  if (ds % 32 != 0 || ds < d) return hipErrorInvalidValue;
+  const bool al = (reinterpret_cast<uintptr_t>(X) & 15u) == 0 && ldx % 4 == 0 && d % 4 == 0;
+  const int64_t blocks = std::min<int64_t>((rows + 3) / 4, 256 * 32);
+#define SKM_GT_CONVERT(NV)                                                                                                 \
+  do {                                                                                                                     \
+    if (al) hipLaunchKernelGGL((gt_convert_kernel<NV, true>), dim3((unsigned)blocks), dim3(256), 0, st, X, ldx, n, nsel,    \
+                               row0, rows, d, ds, plane, scale, term, maxnorm);                                            \
+    else hipLaunchKernelGGL((gt_convert_kernel<NV, false>), dim3((unsigned)blocks), dim3(256), 0, st, X, ldx, n, nsel, row0, \
+                            rows, d, ds, plane, scale, term, maxnorm);                                                     \
+  } while (0)
+  if (ds <= 256) SKM_GT_CONVERT(1);
+  else if (ds <= 512) SKM_GT_CONVERT(2);
+  else if (ds <= 768) SKM_GT_CONVERT(3);
+  else if (ds <= 1024) SKM_GT_CONVERT(4);
+  else if (ds <= 1536) SKM_GT_CONVERT(6);
+  else if (ds <= 2048) SKM_GT_CONVERT(8);
+  else SKM_GT_CONVERT(0);
+#undef SKM_GT_CONVERT
+  return hipGetLastError();
+}
+
+// ascending bitonic sort of N (a power of two) items in LDS by all threads of the workgroup
+template <typename T>
+__device__ inline void lds_sort(T *s, int n) {
+  for (int k = 2; k <= n; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      __syncthreads();
+      for (int t = threadIdx.x; t < n / 2; t += blockDim.x) {
+        const int i = 2 * t - (t & (j - 1)), p = i + j;   // the t-th pair at distance j
+        const T a = s[i], b = s[p];
+        if ((a > b) == ((i & k) == 0)) {
+          s[i] = b;
+          s[p] = a;
+        }
+      }
+    }
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(256) gt_threshold_kernel(const float *group_min, int32_t ngroups, int32_t np2, int32_t K,
+                                                           const float *q_scale, const float *q_term,
+                                                           const unsigned int *maxnorm, int32_t d, float *tq) {
+  extern __shared__ float s_g[];
+  const int q = blockIdx.x;
+  for (int t = threadIdx.x; t < np2; t += 256) s_g[t] = t < ngroups ? group_min[(int64_t)q * ngroups + t] : 3.4e38f;
+  lds_sort(s_g, np2);
+  if (threadIdx.x == 0)
+    tq[q] = s_g[K - 1] + gt_band(2.f * q_term[q] / q_scale[q], __builtin_bit_cast(float, *maxnorm), d);
+}
+hipError_t launch_gt_threshold(const float *group_min, int32_t ngroups, int32_t nq, int32_t K, const float *q_scale,
+                               const float *q_term, const unsigned int *maxnorm, int32_t d, float *tq, hipStream_t st) {
+  if (K < 1 || K > ngroups || ngroups > kGtMaxGroups) return hipErrorInvalidValue;
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(gt_threshold_kernel),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kGtMaxGroups * 4);
+  if (attr_rc != hipSuccess) return attr_rc;
+  int np2 = 2;
+  while (np2 < ngroups) np2 <<= 1;
+  hipLaunchKernelGGL(gt_threshold_kernel, dim3((unsigned)nq), dim3(256), (size_t)np2 * sizeof(float), st, group_min, ngroups, np2,
+                     K, q_scale, q_term, maxnorm, d, tq);
+  return hipGetLastError();
+}
+
+__global__ void gt_terms_kernel(const float *tq, const float *q_scale, const float *q_term, int32_t nq,
+                                const unsigned int *maxnorm, int32_t d, float *row_term) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= nq) return;
+  const float band = gt_band(2.f * q_term[q] / q_scale[q], __builtin_bit_cast(float, *maxnorm), d);
+  row_term[q] = -0.5f * (tq[q] + band) * q_scale[q];
+}
+hipError_t launch_gt_terms(const float *tq, const float *q_scale, const float *q_term, int32_t nq, const unsigned int *maxnorm,
+                           int32_t d, float *row_term, hipStream_t st) {
+  hipLaunchKernelGGL(gt_terms_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, st, tq, q_scale, q_term, nq, maxnorm, d,
+                     row_term);
+  return hipGetLastError();
+}
+
+// One workgroup per query.  The candidates are ordered by their one-product score; those within twice the bound of the
+// K-th get their exact distance, a wavefront each, and are ordered by (distance, index).
+__global__ void __launch_bounds__(256) gt_select_kernel(const unsigned long long *cand, const unsigned int *count, unsigned int cap,
+                                                        int32_t K, const float *X, int64_t ldx, const float *Q, int32_t d,
+                                                        const float *q_scale, const float *q_term, const unsigned int *maxnorm,
+                                                        unsigned long long *keys, volatile unsigned int *overflow) {
+  extern __shared__ unsigned long long s_k[];
+  __shared__ int s_m;
+  const int q = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned int total = count[q];
+  if (total > cap || (int)total < K) {   // (fewer than K: only where a score is not finite)
+    if (threadIdx.x == 0) *overflow = 1u;
+    return;
+  }
+  int np2 = 2;
+  while (np2 < (int)total) np2 <<= 1;
+  for (int t = threadIdx.x; t < np2; t += 256) s_k[t] = t < (int)total ? cand[(int64_t)q * cap + t] : ~0ull;
+  if (threadIdx.x == 0) s_m = 0;
+  lds_sort(s_k, np2);
+  const float band = gt_band(2.f * q_term[q] / q_scale[q], __builtin_bit_cast(float, *maxnorm), d);
+  const unsigned long long lim =
+      ((unsigned long long)f2ord(ord2f((unsigned int)(s_k[K - 1] >> 32)) + 2.f * band) << 32) | 0xffffffffull;
+  for (int t = threadIdx.x; t < (int)total; t += 256)
+    if (s_k[t] <= lim && (t + 1 == (int)total || s_k[t + 1] > lim)) s_m = t + 1;   // (sorted: one thread finds the end)
+  __syncthreads();
+  const int m = s_m;
+  const float *qr = Q + (int64_t)q * d;
+  for (int t = wave; t < m; t += 4) {
+    const unsigned int id = (unsigned int)(s_k[t] & 0xffffffffull);
+    const float *x = X + (int64_t)id * ldx;
+    float s = 0.f;
+    for (int c = lane; c < d; c += 64) {
+      const float df = x[c] - qr[c];
+      s = fmaf(df, df, s);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) s_k[t] = ((unsigned long long)f2ord(s) << 32) | id;
+  }
+  __syncthreads();
+  int mp2 = 2;
+  while (mp2 < m) mp2 <<= 1;
+  for (int t = m + threadIdx.x; t < mp2; t += 256) s_k[t] = ~0ull;
+  lds_sort(s_k, mp2);
+  for (int t = threadIdx.x; t < K; t += 256) keys[(int64_t)q * K + t] = t < m ? s_k[t] : ~0ull;
+}
+hipError_t launch_gt_select(const unsigned long long *cand, const unsigned int *count, unsigned int cap, int32_t nq, int32_t K,
+                            const float *X, int64_t ldx, const float *Q, int32_t d, const float *q_scale, const float *q_term,
+                            const unsigned int *maxnorm, unsigned long long *keys, unsigned int *overflow, hipStream_t st) {
+  if (cap > kGtMaxCand || (cap & (cap - 1)) != 0 || cap < 2) return hipErrorInvalidValue;
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(gt_select_kernel),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGtMaxCand * 8);
+  if (attr_rc != hipSuccess) return attr_rc;
+  hipLaunchKernelGGL(gt_select_kernel, dim3((unsigned)nq), dim3(256), (size_t)cap * 8, st, cand, count, cap, K, X, ldx, Q, d,
+                     q_scale, q_term, maxnorm, keys, overflow);
   return hipGetLastError();
 }
 

@@ -69,7 +69,17 @@ struct ScreenArgs {
   unsigned int *pair_count;     // [kSubLists * kSubListStride]
   unsigned int sub_capacity;
   unsigned int *overflow;
+  // neighbour modes: rows are queries, columns points, every row of either operand scaled by a power of two of its own
+  const float *row_scale, *col_scale;   // [M] (with arow = the row's threshold term), [N] (with ycol = ||x||^2 times scale / 2)
+  float *group_min;                     // SCREEN_GROUPS: [M][ngroups] smallest score of every 64 columns
+  int32_t ngroups, group0;
+  unsigned long long *cand;             // SCREEN_CANDIDATES: [M][cand_cap] (score, point) entries
+  unsigned int *cand_count;             // [M]
+  unsigned int cand_cap;
+  int64_t point0;                       // point of column 0
 };
+
+enum { SCREEN_FIRST_TEST = 0, SCREEN_EXACT = 1, SCREEN_GROUPS = 2, SCREEN_CANDIDATES = 3 };
 
 // A workgroup of 8 wavefronts owns 256 points x 256 centroids; a wavefront owns 128 x 64 (4 x 2 accumulators of
 // 32 x 32: per matrix instruction three quarters of the fragment bytes of a 64 x 64 arrangement), so the rows of a
@@ -90,11 +100,17 @@ struct ScreenArgs {
 // stale value is only larger), and emits the pairs within 2 b_i of the smaller of the two: j* is among them whenever
 // its tile runs.  In random order a row emits in about ln(column tiles) tiles.  The gather kernel then takes the exact
 // distance of every emitted pair, and the packed minimum over those is the exact nearest centroid.
-template <bool EXACT>
+//
+// SCREEN_GROUPS, SCREEN_CANDIDATES (Section 3.3, ground truth of the recall measurement; see etr.hip): rows are queries,
+// columns are points, and the score is ||x_j||^2 - 2 (q_i.x_j)~.  The first mode writes the smallest score of every 64
+// columns, the second appends the points whose score does not exceed the row's threshold to the row's list.
+template <int MODE>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) screen_kernel(ScreenArgs g) {
   extern __shared__ __align__(16) uint32_t smem[];   // [NSTAGE stages][A: BM rows | B: BN rows][ROW_WORDS]
   __shared__ __align__(16) float s_a[NSTAGE][BM];    // per row of a tile in flight: the widened threshold in accumulator units
   __shared__ __align__(16) float s_y[NSTAGE][BN];    // per column of a tile in flight: its prefix norm in the same units
+  constexpr bool EXACT = MODE == SCREEN_EXACT, NEIGH = MODE >= SCREEN_GROUPS;
+  __shared__ __align__(16) float s_a2[NEIGH ? NSTAGE : 1][BM], s_y2[NEIGH ? NSTAGE : 1][BN];   // scales of rows and columns
   __shared__ unsigned int s_rmin[EXACT ? BM : 1];    // EXACT: minimum of every row of the tile (ordered float bits)
   __shared__ float s_thr[EXACT ? BM : 1];            // EXACT: emission threshold of every row
 
@@ -125,9 +141,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int ld_row = 16 * wave + lrow;                        // + 128 j
   const int ld_c = lpos ^ ((ld_row >> 2) & 3);                // piece that belongs at this lane's position
   const int ld_words = 4 * ld_c;                              // its word offset inside the slab's 16 hi words
-  const int koff = -((BK - g.dprime % BK) % BK);
+  const int koff = NEIGH ? 0 : -((BK - g.dprime % BK) % BK);
   const int nslab = (g.dprime - koff) / BK;                   // slabs [koff, d')
-  const int kw0 = 8 + koff / 2;                               // word of the hi plane where slab 0 starts
+  const int kw0 = NEIGH ? 0 : 8 + koff / 2;                   // word of the hi plane where slab 0 starts
 
   // ---- the loading side runs DEPTH slabs ahead of the multiplying side, across tile boundaries (a tile of a
   // well-pruned step is two or three slabs: one tile's worth of loads in flight would leave the matrix cores waiting
@@ -157,6 +173,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         float *dst = (wave < 4 ? s_a[ltile & (NSTAGE - 1)] : s_y[ltile & (NSTAGE - 1)]) + 64 * (wave & 3);
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
                                          (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
+        if constexpr (NEIGH) {
+          const float *src2 = wave < 4 ? g.row_scale + row0 + min(e, limA) : g.col_scale + col0 + min(e, limB);
+          float *dst2 = (wave < 4 ? s_a2[ltile & (NSTAGE - 1)] : s_y2[ltile & (NSTAGE - 1)]) + 64 * (wave & 3);
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src2,
+                                           (__attribute__((address_space(3))) void *)dst2, 4, 0, 0);
+        }
       }
       ++ltile;
     }
@@ -202,16 +224,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // the matrix instructions before this point have consumed.)
       __builtin_amdgcn_s_barrier();
       request();         // slab cjob + DEPTH -> the stage slab cjob - 1 was in (NSTAGE = DEPTH + 1)
-      if (s == 0 && EXACT) {
+      if (s == 0 && (EXACT || NEIGH)) {
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
           for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-        if (tid < BM) s_rmin[tid] = 0xffffffffu;   // (read after this tile's slab barriers)
+        if constexpr (EXACT)
+          if (tid < BM) s_rmin[tid] = 0xffffffffu;   // (read after this tile's slab barriers)
       }
-      if (s == 0 && !EXACT) {      // every accumulator element starts from its row's term
+      if (s == 0 && MODE == SCREEN_FIRST_TEST) {      // every accumulator element starts from its row's term
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -246,7 +269,66 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
     dims_done += (unsigned long long)(BK * nslab);
 
-    if (EXACT) {
+    if constexpr (NEIGH) {
+      // score of (row, column) = (rq ct - acc) 2 / (rq sj), rq and sj the two scales, ct = ||x||^2 sj / 2
+      const int slot_t = ctile & (NSTAGE - 1);
+      const float c0 = s_y[slot_t][wn * 64 + r32], c1 = s_y[slot_t][wn * 64 + 32 + r32];
+      const float j0 = s_y2[slot_t][wn * 64 + r32], j1 = s_y2[slot_t][wn * 64 + 32 + r32];
+      int zero = 0;   // (renewed every four rows so that their terms are fetched four at a time: see the EXACT form)
+      if constexpr (MODE == SCREEN_GROUPS) {
+        const float i0 = colok[0] ? 1.f / j0 : 0.f, i1 = colok[1] ? 1.f / j1 : 0.f;   // (powers of two: exact)
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            if ((v & 3) == 0) asm volatile("" : "+v"(zero) : : "memory");
+            const int rl = wm * 128 + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3) + zero;
+            const float rq = s_a2[slot_t][rl];
+            float m = 3.0e38f;
+            if (colok[0]) m = fmaf(rq, c0, -acc[a][0][v]) * i0;
+            if (colok[1]) m = fminf(m, fmaf(rq, c1, -acc[a][1][v]) * i1);
+            m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, false)));
+            m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x4E, 0xF, 0xF, false)));
+            m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x141, 0xF, 0xF, false)));
+            m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x140, 0xF, 0xF, false)));
+            m = fminf(m, __shfl_xor(m, 16, 64));
+            const int row = rt * BM + rl, grp = g.group0 + ct * (BN / 64) + wn;
+            if (r32 == 0 && row < g.M && col0 + wn * 64 < g.N) g.group_min[(int64_t)row * g.ngroups + grp] = m * (2.f / rq);
+          }
+      } else {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            if ((v & 3) == 0) asm volatile("" : "+v"(zero) : : "memory");
+            const int rl = wm * 128 + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3) + zero;
+            const float rq = s_a2[slot_t][rl], rterm = s_a[slot_t][rl];
+            const bool e0 = colok[0] && acc[a][0][v] >= fmaf(rq, c0, rterm * j0);
+            const bool e1 = colok[1] && acc[a][1][v] >= fmaf(rq, c1, rterm * j1);
+            if (__ballot(e0 || e1)) {
+              const int row = rt * BM + rl;
+              if (row < g.M) {
+                if (e0) {
+                  const unsigned int p = atomicAdd(g.cand_count + row, 1u);
+                  const float sc = fmaf(rq, c0, -acc[a][0][v]) * (2.f / rq) * (1.f / j0);
+                  if (p < g.cand_cap)
+                    g.cand[(int64_t)row * g.cand_cap + p] =
+                        ((unsigned long long)f2ord(sc) << 32) | (unsigned int)(g.point0 + col0 + wn * 64 + r32);
+                }
+                if (e1) {
+                  const unsigned int p = atomicAdd(g.cand_count + row, 1u);
+                  const float sc = fmaf(rq, c1, -acc[a][1][v]) * (2.f / rq) * (1.f / j1);
+                  if (p < g.cand_cap)
+                    g.cand[(int64_t)row * g.cand_cap + p] =
+                        ((unsigned long long)f2ord(sc) << 32) | (unsigned int)(g.point0 + col0 + wn * 64 + 32 + r32);
+                }
+              }
+            }
+          }
+      }
+      continue;
+    }
+    if constexpr (EXACT) {
       // ---- minimum of every row over the tile's columns
       const float *yc = s_y[ctile & (NSTAGE - 1)] + wn * 64 + r32;
       const float y0 = colok[0] ? yc[0] : 3.0e38f, y1 = colok[1] ? yc[32] : 3.0e38f;
@@ -342,7 +424,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
   }
-  if (tid == 0 && dims_done)   // (in units of the exact kernel's 128 x 128 tiles: four per tile of this kernel)
+  if (!NEIGH && tid == 0 && dims_done)   // (in units of the exact kernel's 128 x 128 tiles: four per tile of this kernel)
     atomicAdd(g.scal + (size_t)(blockIdx.x & (kStatReplicas - 1)) * SC_COUNT + SC_SCREEN_DIMS, 4ull * dims_done);
 }
 
@@ -479,6 +561,53 @@ __global__ void __launch_bounds__(1024) max_value_kernel(const float *v, int32_t
   }
 }
 
+namespace {
+// LDS size and grid, once per process (the initialisation of a function-local static is synchronised between threads)
+struct ScreenSetup {
+  hipError_t rc;
+  int wgs = 0;
+  ScreenSetup() {
+    constexpr int smem = NSTAGE * STAGE_WORDS * (int)sizeof(uint32_t);
+    const void *forms[4] = {reinterpret_cast<const void *>(screen_kernel<SCREEN_FIRST_TEST>),
+                            reinterpret_cast<const void *>(screen_kernel<SCREEN_EXACT>),
+                            reinterpret_cast<const void *>(screen_kernel<SCREEN_GROUPS>),
+                            reinterpret_cast<const void *>(screen_kernel<SCREEN_CANDIDATES>)};
+    rc = hipSuccess;
+    for (const void *f : forms)
+      if (rc == hipSuccess) rc = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    int dev = 0, cus = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    wgs = cus;   // one workgroup of eight wavefronts per CU
+  }
+};
+const ScreenSetup &screen_setup() {
+  static const ScreenSetup setup;
+  return setup;
+}
+}  // namespace
+
+hipError_t launch_neighbour_screen(const NeighbourLaunch &a, bool groups, hipStream_t st) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  if (a.ds % 32 != 0 || (reinterpret_cast<uintptr_t>(a.A) & 15u) || (reinterpret_cast<uintptr_t>(a.B) & 15u)) return hipErrorInvalidValue;
+  constexpr size_t smem = (size_t)NSTAGE * STAGE_WORDS * sizeof(uint32_t);
+  const ScreenSetup &setup = screen_setup();
+  if (setup.rc != hipSuccess) return setup.rc;
+  const int64_t ntiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  if (ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  ScreenArgs g{};
+  g.A = a.A; g.lda = a.ds / 2; g.M = a.M;
+  g.B = a.B; g.ldb = a.ds / 2; g.N = a.N;
+  g.dprime = a.ds;
+  g.arow = a.row_term; g.ycol = a.col_term; g.row_scale = a.row_scale; g.col_scale = a.col_scale;
+  g.group_min = a.group_min; g.ngroups = a.ngroups; g.group0 = a.group0;
+  g.cand = a.cand; g.cand_count = a.cand_count; g.cand_cap = a.cand_cap; g.point0 = a.point0;
+  const int64_t grid = std::max<int64_t>(8, std::min<int64_t>(setup.wgs, (ntiles + 7) / 8 * 8));
+  if (groups) hipLaunchKernelGGL(screen_kernel<SCREEN_GROUPS>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+  else hipLaunchKernelGGL(screen_kernel<SCREEN_CANDIDATES>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+  return hipGetLastError();
+}
+
 hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.dprime % 16 != 0 || a.dprime < 16 || a.dprime > a.ds || a.lda != a.ds / 2 + 16 || a.ldb != a.ds / 2 + 16 ||
@@ -486,22 +615,7 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
     return hipErrorInvalidValue;
   if (a.exact && (!a.rowmin || !a.pairs || !a.pair_count || !a.overflow)) return hipErrorInvalidValue;
   constexpr size_t smem = (size_t)NSTAGE * STAGE_WORDS * sizeof(uint32_t);
-  struct Setup {
-    hipError_t rc;
-    int wgs = 0;
-    Setup() {
-      rc = hipFuncSetAttribute(reinterpret_cast<const void *>(screen_kernel<false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      if (rc == hipSuccess)
-        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(screen_kernel<true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      int dev = 0, cus = 256;
-      (void)hipGetDevice(&dev);
-      (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-      wgs = cus;   // one workgroup of eight wavefronts per CU
-    }
-  };
-  static const Setup setup;
+  const ScreenSetup &setup = screen_setup();
   if (setup.rc != hipSuccess) return setup.rc;
   const int nrt = (a.M + RT - 1) / RT, nct = (a.N + 127) / 128;   // row tiles and column tiles of the exact kernel
   const int64_t ntiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
@@ -521,10 +635,10 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   g.sub_capacity = a.sub_capacity; g.overflow = a.overflow;
   const int64_t grid = std::max<int64_t>(8, std::min<int64_t>(setup.wgs, (ntiles + 7) / 8 * 8));
   if (a.exact) {
-    hipLaunchKernelGGL(screen_kernel<true>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+    hipLaunchKernelGGL(screen_kernel<SCREEN_EXACT>, dim3((unsigned)grid), dim3(NT), smem, st, g);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(screen_kernel<false>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+  hipLaunchKernelGGL(screen_kernel<SCREEN_FIRST_TEST>, dim3((unsigned)grid), dim3(NT), smem, st, g);
   hipError_t rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)((nrt + 3) / 4)), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt);

@@ -194,6 +194,23 @@ struct ScreenLaunch {
   stamp_t *stamp = nullptr;
 };
 hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st);
+
+// The same one-product multiply for the ground truth (etr.hip): rows are queries, columns points.  A, B: planes of fp16
+// values, ds a multiple of 32, row stride ds / 2 words, every row scaled by row_scale[i] / col_scale[j];
+// col_term[j] = ||x_j||^2 col_scale[j] / 2.  groups: group_min[i][group0 + j / 64] = smallest score ||x||^2 - 2 q.x of the
+// 64 columns.  Otherwise every column with a score <= t_i, row_term[i] = -t_i row_scale[i] / 2, is appended to cand[i].
+struct NeighbourLaunch {
+  const uint32_t *A, *B;
+  int32_t M, N, ds;
+  const float *row_term, *row_scale, *col_term, *col_scale;
+  float *group_min;
+  int32_t ngroups, group0;
+  unsigned long long *cand;    // [M][cand_cap]: (order-preserving bits of the score << 32) | point
+  unsigned int *cand_count;    // [M]; may exceed cand_cap
+  unsigned int cand_cap;
+  int64_t point0;
+};
+hipError_t launch_neighbour_screen(const NeighbourLaunch &a, bool groups, hipStream_t st);
 int64_t progressive_tiles(int64_t rows, int32_t k);
 int32_t progressive_tile_pairs();
 int32_t progressive_tile_cols();
@@ -402,6 +419,24 @@ hipError_t launch_topk_merge(const float *S, int64_t lds, int32_t nq, int32_t m,
 hipError_t launch_recall_scores(const float *S, int64_t lds, int32_t nq, int32_t k, const float *ynorm, int32_t nprobe,
                                 const unsigned long long *gt_keys, int32_t K, const int32_t *assign,
                                 unsigned long long *hits, unsigned long long *total, hipStream_t st);
+// Ground truth through the one-product multiply.  launch_gt_convert: rows [row0, row0 + rows) of the nsel rows spread
+// evenly over the n rows of X (nsel = n: the rows themselves) as fp16 rows of ds values in units of a power of two of
+// their own: plane, scale, term = ||x||^2 scale / 2, and max ||x||^2 folded into *maxnorm (bit pattern).
+hipError_t launch_gt_convert(const float *X, int64_t ldx, int64_t n, int64_t nsel, int64_t row0, int64_t rows, int32_t d,
+                             int32_t ds, uint32_t *plane, float *scale, float *term, unsigned int *maxnorm, hipStream_t st);
+// tq[i] = K-th smallest of group_min[i][0 .. ngroups) + the error bound of a score of query i
+hipError_t launch_gt_threshold(const float *group_min, int32_t ngroups, int32_t nq, int32_t K, const float *q_scale,
+                               const float *q_term, const unsigned int *maxnorm, int32_t d, float *tq, hipStream_t st);
+// row_term[i] = -(tq[i] + the error bound) q_scale[i] / 2
+hipError_t launch_gt_terms(const float *tq, const float *q_scale, const float *q_term, int32_t nq, const unsigned int *maxnorm,
+                           int32_t d, float *row_term, hipStream_t st);
+// keys[i][0 .. K) = the K nearest of the candidates of query i by their exact distance (direct form); *overflow is set (a
+// plain store: page-locked memory will do) if a list is longer than its capacity (a power of two) or shorter than K
+hipError_t launch_gt_select(const unsigned long long *cand, const unsigned int *count, unsigned int cap, int32_t nq, int32_t K,
+                            const float *X, int64_t ldx, const float *Q, int32_t d, const float *q_scale, const float *q_term,
+                            const unsigned int *maxnorm, unsigned long long *keys, unsigned int *overflow, hipStream_t st);
+constexpr unsigned int kGtMaxCand = 8192;
+constexpr int32_t kGtMaxGroups = 16384;
 hipError_t launch_row_norms(const float *X, int64_t ldx, int64_t n, int32_t d, float *out, hipStream_t st);
 hipError_t launch_keys_to_index(const unsigned long long *keys, int64_t n, int64_t *idx, hipStream_t st);
 hipError_t launch_index_to_keys(const int64_t *idx, int64_t n, unsigned long long *keys, hipStream_t st);
