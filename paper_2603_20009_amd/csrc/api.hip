@@ -561,6 +561,7 @@ struct Ctx {
   uint32_t *Xh = nullptr, *Yh = nullptr;   // [n][ds / 2 + 16], [k][ds / 2 + 16]: the hi halves of Xs, Ys as planes of their own
   int32_t pruned_steps = 0;                // pruned steps this context has completed
   bool exact_filter_off = false;           // iteration 1 takes the full GEMM (set after a candidate-list overflow)
+  float2 *scr_widen = nullptr;
   int32_t *scr_cnt = nullptr, *scr_first = nullptr, *scr_ntiles = nullptr, *scr_cols = nullptr, *scr_tile_rt = nullptr;
   unsigned int *amax = nullptr;      // [AM_COUNT] magnitude bounds of the GEMM operands
   enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8 };
@@ -673,17 +674,17 @@ struct Ctx {
     // redone with the full GEMM): room for 16 per point of a chunk in each of the eight parts
     // (the kernels behind the filter address a listed centroid's row with 32-bit offsets: not for a centroid table of
     // 2^31 words or more, where the steps simply run unfiltered)
-    const bool may_screen = (screen_mode > 0 || (screen_mode == 0 && k >= 2 * progressive_tile_cols())) &&
+    const bool may_screen = (screen_mode > 0 || (screen_mode == 0 && k >= 256)) &&
                             (int64_t)k * (ds + 32) < ((int64_t)1 << 31);
     if (may_screen) sub_cap = std::max<int64_t>(sub_cap, 16 * std::min<int64_t>(chunk_rows, n));
     pair_cap = sub_cap * kSubLists;
     if (pair_cap >= ((int64_t)1 << 32)) return fail(SKM_EINVAL, "pair_budget too large (must stay below 2^32 pairs)");
     HIPCHK(pool.get(&pairs, (size_t)pair_cap));
     ncounters = (size_t)nchunks * (kSubLists + 16) * kSubListStride;   // list fill counters, tile counters of the two tile kernels
-    if (may_screen) {   // (unless forced: of no use below two column tiles)
+    if (may_screen) {   // (unless forced: of no use with few centroids)
       // one bit per (row tile, centroid); at most one tile of listed columns per (row tile, column tile) of the chunk
       const int64_t nrt_chunk = (std::min<int64_t>(chunk_rows, n) + 127) / 128;
-      HIPCHK(pool.get(&colmask, (size_t)nrt_chunk * 4 * (size_t)col_tiles));
+      HIPCHK(pool.get(&colmask, (size_t)nrt_chunk * 4 * (size_t)((k + 127) / 128)));
       HIPCHK(pool.get(&scr_cnt, (size_t)nrt_chunk));
       HIPCHK(pool.get(&scr_first, (size_t)nrt_chunk));
       HIPCHK(pool.get(&scr_ntiles, 2));   // the tile count, then a float scalar of the filter
@@ -691,7 +692,8 @@ struct Ctx {
       HIPCHK(pool.get(&scr_ycol, (size_t)k));
       HIPCHK(pool.get(&Xh, (size_t)n * (ds / 2 + 16)));
       HIPCHK(pool.get(&Yh, (size_t)k * (ds / 2 + 16)));
-      HIPCHK(pool.get(&scr_cols, (size_t)tiles_chunk * 128));
+      HIPCHK(pool.get(&scr_cols, (size_t)tiles_chunk * kListCols));
+      HIPCHK(pool.get(&scr_widen, (size_t)kMaxBlocks + 1));
       HIPCHK(pool.get(&scr_tile_rt, (size_t)tiles_chunk));
     }
     // everything a step clears at its start is one block: counters | flag | ticket | step scalars | cluster sizes
@@ -935,7 +937,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
     sl.overflow = c.flag;
     if (ch == 0) sl.stamp = tm.mark(ST_TAU);
     HIPCHK(launch_screen(sl, c.st));
-    PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, 0, K, nbK, c.ratio_dev,
+    PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, 0, K, nbK, c.Y, c.ratio_dev,
                  c.best, c.scal, 0};
     HIPCHK(launch_prune(pa, c.st));
   }
@@ -1139,6 +1141,10 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.tau = c.tau; sl.row_base = r0;
       sl.xn = c.xnp + (int64_t)(dprime / 16 - 1) * c.n;
       sl.yn = c.ynp;
+      // Behind the first test of a listed tile one product and widened tests will do where the gather kernel finishes
+      // what is left (not where every test's count is asked for, nor with a hand-over share beyond an eighth).
+      const bool deep = !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
+      if (deep) { sl.ynp = c.ynp; sl.nb = nb; sl.widen = c.scr_widen; }
       sl.arow = c.scr_arow; sl.ycol = c.scr_ycol;
       sl.colmask = c.colmask; sl.cnt = c.scr_cnt; sl.first = c.scr_first; sl.ntiles = c.scr_ntiles;
       sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt;
@@ -1147,12 +1153,19 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.stamp = border;
       HIPCHK(launch_screen(sl, c.st));
       g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles;
+      if (deep) {
+        g.deep = 1;
+        g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
+        g.emit_first = c.emit_max * 5 / 8;
+        g.emit_deep = c.emit_max / 8;
+        g.deep_max = (unsigned int)progressive_tile_pairs() / 4;
+      }
     }
     if (!screen) g.stamp = border;
     HIPCHK(launch_progressive(g, c.st));
     border = tm.mark(ST_GEMM);
     if (c.emit_max > 0) {
-      PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, dprime, c.ds, nb, c.ratio_dev,
+      PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, dprime, c.ds, nb, c.Y, c.ratio_dev,
                    c.best, c.scal, c.block_stats ? 1 : 0};
       pa.stamp = border;
       HIPCHK(launch_prune(pa, c.st));

@@ -77,18 +77,6 @@ __device__ inline void tile_of_block(int nrt, int nct, int PC, int &rt, int &ct)
   ct = p * PC + (r - rt * pc);
 }
 
-// One step of a reduce-scatter of keys over the lanes of a wavefront half: of the two keys, lanes with BIT clear go on
-// with the first and lanes with it set with the second, each merged (minimum) with the partner's.
-template <int DPP, int BIT>
-__device__ inline unsigned long long halve_min(unsigned long long p, unsigned long long q, int lane) {
-  const bool up = lane & BIT;
-  const unsigned long long keep = up ? q : p, give = up ? p : q;
-  const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)give, DPP, 0xF, 0xF, false);
-  const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)(give >> 32), DPP, 0xF, 0xF, false);
-  const unsigned long long got = ((unsigned long long)hi << 32) | lo;
-  return got < keep ? got : keep;
-}
-
 // Epilogues of a finished TB x TB tile (TB / 64 wavefronts each way).  `unscale` turns an accumulator into the
 // score s(i, j).  Accumulator layout of the 32 x 32 MFMA results: register v of lane (r32, kh) holds
 // row 8*(v/4) + 4*kh + (v%4), column r32 of the 32 x 32 tile.
@@ -141,11 +129,8 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[TM][TN], const GemmOperands &
       gc[b] = col0 + wn * WTN + b * 32 + r32;
       yn[b] = gc[b] < g.N ? e.ynorm[gc[b]] : 0.f;
     }
-    // A lane holds 2 keys for each of 32 rows, 32 lanes share the rows.  Reducing row by row takes five exchanges of a
-    // 64-bit key per row, 160 in all, each through LDS.  Here the rows are shared out on the way (reduce-scatter): a step
-    // halves the rows a lane is responsible for, so 16 + 8 + 4 + 2 + 1 exchanges do, on the row swap and the lane moves
-    // of the vector unit; lane (r32, kh) ends with the row (a, v) = (r32 >> 4, r32 & 15) of its half.  (100 003 x 112
-    // against 1000 centroids: 216 -> 137 us; 1M x 1536 against 1024: 9.5 -> 9.2 ms.)
+    // A lane holds 2 keys for each of 32 rows, 32 lanes share the rows (see reduce_rows32; row by row through LDS before:
+    // 100 003 x 112 against 1000 centroids 216 -> 137 us, 1M x 1536 against 1024 9.5 -> 9.2 ms).
     auto key_of = [&](int a, int v) {
       unsigned long long key = ~0ull;
 #pragma unroll
@@ -158,27 +143,7 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[TM][TN], const GemmOperands &
       return key;
     };
     static_assert(TM == 2, "one row swap step");
-    unsigned long long k8[8];
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {   // rows v = h and h + 8: lane bit 4 takes a, lane bit 3 takes bit 3 of v
-      unsigned long long k16[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const unsigned long long p = key_of(0, h + 8 * u), q = key_of(1, h + 8 * u);
-        // rows of 16 lanes: (p0 p1), (q0 q1) -> (p0 q0), (p1 q1)
-        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned int)p, (unsigned int)q, false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned int)(p >> 32), (unsigned int)(q >> 32), false, false);
-        const unsigned long long x = ((unsigned long long)hi[0] << 32) | lo[0], y = ((unsigned long long)hi[1] << 32) | lo[1];
-        k16[u] = x < y ? x : y;
-      }
-      k8[h] = halve_min<0x128, 8>(k16[0], k16[1], lane);   // row_ror:8
-    }
-    unsigned long long k4[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) k4[h] = halve_min<0x141, 4>(k8[h], k8[h + 4], lane);   // row_half_mirror
-    const unsigned long long k2a = halve_min<0x4E, 2>(k4[0], k4[2], lane);             // quad_perm [2,3,0,1]
-    const unsigned long long k2b = halve_min<0x4E, 2>(k4[1], k4[3], lane);
-    red[wn * TB + row_of(r32 >> 4, r32 & 15)] = halve_min<0xB1, 1>(k2a, k2b, lane);    // quad_perm [1,0,3,2]
+    red[wn * TB + row_of(r32 >> 4, r32 & 15)] = reduce_rows32(key_of, lane);
     __syncthreads();
     if (tid < TB) {
       unsigned long long key = red[tid];

@@ -23,7 +23,7 @@
 #include "skm_internal.h"
 
 #include <algorithm>
-#include <cstdlib>
+#include <type_traits>
 
 namespace skm {
 
@@ -77,17 +77,25 @@ hipError_t launch_split_rows(const float *A, int64_t lda, int64_t rows, int32_t 
 }
 
 namespace {
-constexpr int BM = 128, BN = 128, BK = 32;
-constexpr int WTM = 64, WTN = 64, TM = 2, TN = 2;
+constexpr int BM = 128;                             // rows of a workgroup's tile; its columns: 128 NB, NB = 1 or 2
+constexpr int TM = 4;                               // 4 wavefronts side by side, each 128 rows x NB blocks of 32 columns
 constexpr int NT = 256;
-constexpr int ROW_WORDS = BK;                       // a tile row of a slab: 32 hi + 32 lo halves = 128 bytes
-constexpr int STAGE_WORDS = (BM + BN) * ROW_WORDS;  // one slab of both operands: 32 KB
-constexpr int ROWS_PASS = NT / 8;                   // 8 lanes move one tile row: 32 rows per load instruction
-constexpr int A_LD = BM / ROWS_PASS;                // 4 load instructions per thread, slab and operand
-constexpr int B_LD = BN / ROWS_PASS;
+constexpr int ROW_WORDS = 16;                       // a tile row of a unit: 64 bytes (16 hi + 16 lo halves, or 32 hi halves)
+template <int NB> constexpr int kStageWords = (BM + 128 * NB) * ROW_WORDS;   // one unit of both operands: 16 or 24 KB
+constexpr int NSTAGE = 3;                           // the unit being multiplied and two in flight
+constexpr int ROWS_PASS = NT / 4;                   // 4 lanes move one tile row: 64 rows per load instruction
+constexpr int A_LD = BM / ROWS_PASS;                // 2 load instructions per thread, unit and operand
 
 // wait until at most n of this wavefront's vector memory operations are outstanding (LDS and export counters untouched)
 #define SKM_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
+// barrier behind this wavefront's LDS traffic only: loads in flight stay in flight
+#define SKM_BARRIER()                                             \
+  do {                                                            \
+    asm volatile("" : : : "memory");                              \
+    __builtin_amdgcn_s_waitcnt(0xC07F); /* lgkmcnt(0) */          \
+    __builtin_amdgcn_s_barrier();                                 \
+    asm volatile("" : : : "memory");                              \
+  } while (0)
 
 // Sum over the 64 lanes of a wavefront through the data-parallel lane moves: within quads, mirrored
 // within half rows and rows, then the row totals handed on to the following rows; lane 63 ends with the result.
@@ -105,36 +113,109 @@ __device__ inline int wave_sum_i32(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+template <int NB> using acc_t = f32x16[TM][NB];
+
+// One unit of 16 dimensions, hi and lo halves: x.y ~ hi.hi' + lo.hi' + hi.lo'.  p0 / p1: word offsets of this lane's
+// first and second 16-byte piece inside a tile row.
+template <int NB>
+__device__ inline void unit_three(acc_t<NB> &acc, const uint32_t *Ab, const uint32_t *Bb, int p0, int p1) {
+  f16x8 ah[TM], al[TM], bh[NB], bl[NB];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) bh[b] = *reinterpret_cast<const f16x8 *>(Bb + b * 128 * ROW_WORDS + p0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) ah[a] = *reinterpret_cast<const f16x8 *>(Ab + a * 32 * ROW_WORDS + p0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) al[a] = *reinterpret_cast<const f16x8 *>(Ab + a * 32 * ROW_WORDS + p1);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) bl[b] = *reinterpret_cast<const f16x8 *>(Bb + b * 128 * ROW_WORDS + p1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[a], bh[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[a], bl[b], acc[a][b], 0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// One unit of 32 dimensions, hi halves only.
+template <int NB>
+__device__ inline void unit_one(acc_t<NB> &acc, const uint32_t *Ab, const uint32_t *Bb, int p0, int p1) {
+  f16x8 x[TM], y[NB], x1[TM], y1[NB];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) y[b] = *reinterpret_cast<const f16x8 *>(Bb + b * 128 * ROW_WORDS + p0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) x[a] = *reinterpret_cast<const f16x8 *>(Ab + a * 32 * ROW_WORDS + p0);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) y1[b] = *reinterpret_cast<const f16x8 *>(Bb + b * 128 * ROW_WORDS + p1);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) x1[a] = *reinterpret_cast<const f16x8 *>(Ab + a * 32 * ROW_WORDS + p1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[a], y[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1[a], y1[b], acc[a][b], 0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 }  // namespace
 
-// Slabs of BK dimensions start at koff = -((BK - d' % BK) % BK), so that slab ends fall on every
-// checkpoint d' + 64 m; the zero granules around every row of the split operands cover dimensions below 0
-// or past ds.
-template <bool LISTED>
+// A workgroup of 4 wavefronts owns 128 points x 128 NB centroids, two workgroups share a CU: while one tests, the other
+// multiplies.  A wavefront w owns all 128 rows of the column blocks w and w + 4 (blocks of 32).
+//
+// The tile advances in units of 64 bytes per tile row: 16 dimensions of both halves, multiplied three ways, or - behind
+// the first test of a listed tile, see below - 32 dimensions of the hi halves, multiplied once.  Units are requested two
+// ahead, global memory -> LDS directly, 16 bytes per lane, four lanes per row; piece c of row r is kept at position
+// c ^ ((r >> 2) & 3), so that the 16-byte fragment reads of 16 consecutive rows fall into 16 different bank groups.
+// One barrier per unit.
+//
+// Listed tiles (g.deep): the first test is exact (three products over d' dimensions: the survivors of the first test are
+// counted there).  What follows only has to find the few pairs that can reach the end: one product per dimension
+// (a third of the matrix work), and the tests widened by its error bound (screen.hip) over the dimensions behind d'.  A
+// pair that passes the exact tests passes the widened ones.  Once few pairs are left, or at the end, they go to the
+// gather kernel, which starts them from dimension 0 again and applies the exact tests (p < 0 marks them): labels,
+// distances and counts are those of the exact tests.  A tile most of whose pairs survive the first test, or that ends
+// with more pairs than it may hand over, is done in three products throughout.
+template <bool LISTED, int NB>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) progressive_kernel(ProgArgs g) {
-  extern __shared__ __align__(16) uint32_t smem[];   // [2 stages][A: BM rows | B: BN rows][ROW_WORDS]
-  __shared__ __align__(16) float s_tau[2][BM], s_thr[BM], s_xn[BM], s_yn[BN];   // s_tau: by tile parity
-  __shared__ float s_ratio[kMaxBlocks + 1];
-  __shared__ unsigned long long s_dead[NT];   // per thread: accumulator elements that start dead (the incumbent)
+  constexpr int BN = 128 * NB, TN = NB, STAGE_WORDS = kStageWords<NB>;
+  constexpr int B_LD = BN / ROWS_PASS;               // load instructions per thread and unit of the columns' rows
+  static_assert(!LISTED || BN == kListCols, "a tile of listed columns");
+  extern __shared__ __align__(16) uint32_t smem[];   // [NSTAGE][A: BM rows | B: BN rows][ROW_WORDS]
+  // (two copies of the thresholds by tile parity: the previous tile may still be handing pairs over while the next is
+  // committed; a listed tile's commit has a barrier that settles this)
+  __shared__ __align__(16) float s_tau[LISTED ? 1 : 2][BM], s_thr[BM], s_xn[BM], s_yn[BN];
+  __shared__ int s_cid[LISTED ? BN : 1];             // listed columns: the centroid ids of the tile (INT_MAX = none)
+  __shared__ unsigned int s_dead[NT * 4];            // per thread: accumulator elements that start dead (the incumbent)
   __shared__ __align__(16) unsigned int s_wcnt[2][4];   // alive pairs of every wavefront at the last checkpoint (by checkpoint parity)
   __shared__ unsigned int s_base;         // first list slot of a tile that hands its pairs over
   __shared__ int s_q[4];   // ring of tile numbers drawn from the XCD's counter, two tiles ahead of the one in work
-  __shared__ int s_cid[BN];   // listed columns: the centroid ids of the tile being committed (INT_MAX = none)
   put_stamp(g.stamp);
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, kh = lane >> 5;
-  const int swz = (r32 >> 1) & 7;   // position swizzle of the tile rows this lane reads fragments from
+  const int swz = (r32 >> 2) & 3;
+  const int p0 = (kh ^ swz) << 2, p1 = ((2 + kh) ^ swz) << 2;   // this lane's two pieces of a tile row
   const int nrt = (g.M + BM - 1) / BM, nct = (g.N + BN - 1) / BN;
-  // Listed columns (after the low-precision first filter): tile t is row tile tile_rt[t] against the 128 centroids
-  // col_list[128 t ..]; the "column tile" of such a tile is its own number.
-  constexpr bool listed = LISTED;
-  const int ntiles = listed ? *g.ntiles : nrt * nct;
+  // Listed columns (after the low-precision first filter): tile t is row tile tile_rt[t] against the 256 centroids
+  // col_list[256 t ..]; the "column tile" of such a tile is its own number.
+  const int ntiles = LISTED ? *g.ntiles : nrt * nct;
   // column tiles per panel of the tile walk: in the steady state only d' + a few blocks of every centroid are read,
-  // so a panel of 16 column tiles fits one XCD's L2 and every point tile is read once per 16 column tiles
-  constexpr int PC = 16;
+  // so a panel of 2048 centroids fits one XCD's L2 and every point tile is read once per panel
+  constexpr int PC = 2048 / BN;
 
   // This workgroup's share: the contiguous range of logical tile ids of its XCD (workgroups are dealt
   // round-robin to the 8 XCDs), walked through a per-XCD counter.
@@ -144,127 +225,95 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int xcount = tbase + (xcd < trem ? 1 : 0);
   unsigned int *ctr = g.tile_counter + xcd * kSubListStride;
   const int panel_sz = PC * nrt;
-  const float inv_panel = 1.0f / (float)panel_sz;
   auto tile_rc = [&](int q, int &rt, int &ct) {   // q-th tile of this XCD -> (row tile, column tile)
     const int logical = xstart + q;
-    if (listed) {
+    if (LISTED) {
       rt = g.tile_rt[logical];
       ct = logical;
       return;
     }
-    // panel = logical / panel_sz without an integer division: the float estimate is within one of the quotient
-    // (fewer than 2^20 panels), and the remainder says which way
-    int p = (int)((float)logical * inv_panel);
-    int r = logical - p * panel_sz;
-    if (r < 0) {
-      --p;
-      r += panel_sz;
-    } else if (r >= panel_sz) {
-      ++p;
-      r -= panel_sz;
-    }
+    const int p = logical / panel_sz, r = logical - p * panel_sz;   // (uniform)
     const int pc = (nct - p * PC) < PC ? (nct - p * PC) : PC;
-    rt = pc == PC ? r >> 4 : r / pc;   // only the last panel can be narrower
+    rt = r / pc;
     ct = p * PC + (r - rt * pc);
   };
-  static_assert(PC == 16, "the shift above");
 
   unsigned long long *sc = g.scal + (size_t)(blockIdx.x & (kStatReplicas - 1)) * SC_COUNT;
-  for (int m = tid; m <= g.nb; m += NT) s_ratio[m] = g.ratio[m];
-  s_dead[tid] = 0ull;
+#pragma unroll
+  for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
 
-  // Staging: load instruction j of wavefront w moves tile rows 32 j + 8 w .. + 7 of a slab, 8 lanes per row and 16
-  // bytes per lane, from global memory straight into LDS, where the lanes' pieces land one after the other: LDS rows
-  // are 128 bytes without padding.  Piece c of a row (c = 4 h + 2 lo + kh: half-slab, hi or lo halves, dims 8 kh ..
-  // + 7 of the half-slab) is kept at position c ^ swz(row), swz = (row >> 1) & 7, so that the 16-byte fragment reads
-  // of 16 consecutive rows fall into 16 different bank groups; a lane therefore fetches the piece that belongs at
-  // its own position.
-  const int lrow = lane >> 3, lpos = lane & 7;
-  const int ld_row = 8 * wave + lrow;                        // + 32 j
-  const int ld_piece = lpos ^ ((ld_row >> 1) & 7);
-  const int koff = -((BK - g.dprime % BK) % BK);
-  const int nslab = (g.ds - koff + BK - 1) / BK;
-  const int kw0 = 16 + koff;                                 // word of a split row where slab 0 starts (one zero granule leads)
+  // Staging: load instruction j of wavefront w moves tile rows 64 j + 16 w .. + 15 of a unit.
+  const int ld_row = 16 * wave + (lane >> 2);                       // + 64 j
+  const int ld_piece = 4 * ((lane & 3) ^ ((ld_row >> 2) & 3));      // word offset of the piece that belongs at this lane's position
+  const int ldh = g.ds / 2 + 16;
 
-  // Rows past the end are clamped to the last row (their accumulator elements start dead).
-  unsigned int offA[A_LD], offB[B_LD];      // word offset of this lane's piece from the tile's first row / column
+  // ---- the tile being loaded.  Rows past the end repeat the last one (their accumulator elements start dead).
+  int arow[A_LD], brow[B_LD];               // tile rows (relative to its first) and centroid rows of this lane's pieces
   float tau_reg = 0.f;
   int prev_reg = -1;
-  const uint32_t *baseA = g.A, *baseB = g.B;   // first row / column of the tile being loaded (uniform)
-  int limA = 0, limB = 0;                      // last valid row / column of that tile, relative to its first (uniform)
-  // prefix norms: threads 0..127 fetch those of the tile's rows, threads 128..255 those of its columns
-  const float *npre = g.xnp;                // &norm[0][this thread's row or column]
-  const int64_t npre_stride = tid < BM ? g.xn_stride : (int64_t)g.N;
-  float nreg = 0.f;
-  int cid_reg = 0;   // listed columns, threads BM..: the centroid id of column tid - BM of the tile being loaded
-  auto aim = [&](int row0, int col0) {
-    baseA = g.A + (int64_t)row0 * g.lda;
-    limA = g.M - 1 - row0;
+  const uint32_t *baseA = g.A, *baseAh = g.Ah;   // first row of the tile (uniform)
+  const float *nx = g.xnp, *ny = g.ynp;     // prefix norms of row tid & 127 and of column tid
+  float nxreg = 0.f, nyreg = 0.f, rreg = 0.f;
+  float2 wreg = make_float2(0.f, 0.f);
+  int ids[LISTED ? B_LD : 1], cid_reg = 0;
+  // the listed ids of a tile (a missing one loads centroid 0 and starts dead)
+  auto fetch_ids = [&](int ct) {
+    const int32_t *list = g.col_list + (int64_t)ct * BN;
+    if constexpr (LISTED) {
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j)
-      offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda + 4 * ld_piece);
-    if (listed) {
-      // col0 is the tile's number: its columns are listed ids (a missing one loads centroid 0 and starts dead)
-      const int32_t *ids = g.col_list + (int64_t)col0 * BN;
-      baseB = g.B;
-      limB = BN - 1;
-#pragma unroll
-      for (int j = 0; j < B_LD; ++j) {
-        const int id = ids[ld_row + ROWS_PASS * j];
-        offB[j] = (unsigned int)(max(id, 0) * (int)g.ldb + 4 * ld_piece);
-      }
-      cid_reg = tid >= BM ? ids[tid - BM] : 0;
-      npre = tid < BM ? g.xnp + g.row_base + row0 + min(tid, limA) : g.ynp + max(cid_reg, 0);
-      return;
+      for (int j = 0; j < B_LD; ++j) ids[j] = list[ld_row + ROWS_PASS * j];
+      cid_reg = list[tid];
     }
-    baseB = g.B + (int64_t)col0 * g.ldb;
-    limB = g.N - 1 - col0;
-#pragma unroll
-    for (int j = 0; j < B_LD; ++j)
-      offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb + 4 * ld_piece);
-    npre = tid < BM ? g.xnp + g.row_base + row0 + min(tid, limA) : g.ynp + col0 + min(tid - BM, limB);
   };
-  // slab s of the aimed tile -> LDS stage `stage` (asynchronous: SKM_VMCNT(0) and a barrier before it is read)
-  auto issue = [&](int stage, int s) {
-    uint32_t *sb = smem + stage * STAGE_WORDS + 8 * wave * ROW_WORDS;
-    const int kw = kw0 + BK * s;
+  auto aim = [&](int rt, int ct) {
+    const int row0 = rt * BM;
+    baseA = g.A + (int64_t)row0 * g.lda;
+    if (LISTED && g.deep) baseAh = g.Ah + (int64_t)row0 * ldh;
+    const int limA = g.M - 1 - row0;
+#pragma unroll
+    for (int j = 0; j < A_LD; ++j) arow[j] = min(ld_row + ROWS_PASS * j, limA);
+    nx = g.xnp + g.row_base + row0 + min(tid & (BM - 1), limA);
+    if constexpr (LISTED) {
+#pragma unroll
+      for (int j = 0; j < B_LD; ++j) brow[j] = max(ids[j], 0);
+      ny = g.ynp + max(cid_reg, 0);
+    } else {
+      const int col0 = ct * BN, limB = g.N - 1;
+#pragma unroll
+      for (int j = 0; j < B_LD; ++j) brow[j] = min(col0 + ld_row + ROWS_PASS * j, limB);
+      ny = g.ynp + min(col0 + tid, limB);
+    }
+    const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
+    tau_reg = g.tau[g.row_base + gr];
+    prev_reg = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM)
+  };
+  // unit starting at dimension t of the aimed tile -> LDS stage (asynchronous)
+  auto request = [&](int t, bool one, int stage) {
+    uint32_t *sb = smem + stage * STAGE_WORDS + 16 * wave * ROW_WORDS;
+    const uint32_t *pa = LISTED && one ? baseAh : baseA, *pb = LISTED && one ? g.Bh : g.B;
+    const int ld = LISTED && one ? ldh : (int)g.lda, at = (LISTED && one ? 8 + t / 2 : 16 + t) + ld_piece;
 #pragma unroll
     for (int j = 0; j < A_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(baseA + offA[j] + kw),
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + (unsigned int)(arow[j] * ld + at)),
                                        (__attribute__((address_space(3))) void *)(sb + ROWS_PASS * j * ROW_WORDS), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < B_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(baseB + offB[j] + kw),
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + ((uint64_t)(uint32_t)brow[j] * (uint32_t)ld + (uint32_t)at)),
                                        (__attribute__((address_space(3))) void *)(sb + (BM + ROWS_PASS * j) * ROW_WORDS), 16, 0, 0);
   };
-  // Row of the norm tables that multiply step s needs if it ends on a checkpoint (any valid row otherwise): the
-  // points' table has a row per 16 dimensions, the centroids' a row per checkpoint of this step.
-  auto load_norm = [&](int s) {
-    const int td = koff + BK * (s + 1);
-    const bool end = s + 1 >= nslab;
-    const int px = ((end ? g.ds : min(max(td, 16), g.ds)) >> 4) - 1;
-    const int py = end ? g.nb : min(max((td - g.dprime) / kBlockDims, 0), g.nb);
-    nreg = npre[(int64_t)(tid < BM ? px : py) * npre_stride];
-  };
-  auto load_rows = [&](int row0) {   // per-row data of a tile, one row per thread of the first two wavefronts
-    if (tid < BM) {
-      const int gr = min(row0 + tid, g.M - 1);
-      tau_reg = g.tau[g.row_base + gr];
-      prev_reg = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;
-    }
+  // Checkpoint m's prefix norms (the points' table has a row per 16 dimensions, the centroids' a row per checkpoint of
+  // this step), theta ratio and, for the widened tests, the largest centroid norms.
+  auto load_norm = [&](int m) {
+    m = min(m, g.nb);
+    const int px = (min(g.dprime + kBlockDims * m, g.ds) >> 4) - 1;
+    nxreg = nx[(int64_t)px * g.xn_stride];
+    nyreg = ny[(int64_t)m * g.N];
+    rreg = g.ratio[m];
+    if (LISTED && g.deep) wreg = g.widen[m];
   };
   const unsigned int amax = *g.a_absmax, bmax = *g.b_absmax;
   const float m2 = -2.f * split_unscale(amax) * split_unscale(bmax);   // accumulator -> -2 x.y
-  // the prefix norms fetched during the previous step -> LDS, with the row's threshold theta(t_m, tau) - ||x_t||^2
-  auto publish_norms = [&](float ratio) {
-    if (tid < BM) {
-      s_xn[tid] = nreg;
-      s_thr[tid] = ratio * tau_reg - nreg;
-    } else {
-      s_yn[tid - BM] = nreg;
-    }
-  };
-  auto row_of = [&](int a, int v) { return wm * WTM + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3); };
+  auto row_of = [&](int a, int v) { return a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3); };
 
   // first tile of this workgroup
   __syncthreads();
@@ -279,245 +328,287 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   tile_rc(q, rt, ct);
   rt = __builtin_amdgcn_readfirstlane(rt);
   ct = __builtin_amdgcn_readfirstlane(ct);
-  // (listed columns: a tile's "first column" is its number, see aim and commit)
-  auto col_arg = [&](int c) { return listed ? c : c * BN; };
-  aim(rt * BM, col_arg(ct));
-  int stg = 0;   // LDS stage that holds (or is receiving) the slab of the multiply step in work
-  load_norm(0);
-  issue(stg, 0);
-  load_rows(rt * BM);
-  // A tile is committed once its first slab and its per-row data have arrived: the thresholds go to LDS (two copies by
-  // tile parity: the previous tile may still be handing pairs over), the incumbents are marked, and the number of the
-  // tile after next is drawn (the counter's answer is stored at the end of the tile, so its round trip never stalls
-  // the workgroup).  One barrier separates two tiles.
+  int cur = 0;   // LDS stage of the unit being multiplied
+  int treq = 0;  // dimensions requested so far of the tile
+  bool redone = false;   // (listed) the tile is being done again, in three products
+  auto start_tile = [&]() {   // first two units of the aimed tile -> stages cur and cur + 1
+    load_norm(0);
+    request(0, false, cur);
+    treq = 16;
+    if (treq < g.ds) {
+      const bool one = LISTED && g.deep && !redone && treq >= g.dprime;
+      request(treq, one, cur == NSTAGE - 1 ? 0 : cur + 1);
+      treq += one ? 32 : 16;
+    }
+  };
+  if (LISTED) fetch_ids(ct);
+  aim(rt, ct);
+  start_tile();
+  // A tile is committed once its per-row data have arrived: the thresholds go to LDS, the incumbents are marked, and the
+  // number of the tile after next is drawn (the counter's answer is stored at the end of the tile, so its round trip
+  // never stalls the workgroup).
   unsigned int drawn = 0;
   auto commit = [&](int col0, int par) {
-    SKM_VMCNT(0);
-    if (listed) {   // the tile's centroid ids, ascending, for the search below
-      if (tid >= BM) s_cid[tid - BM] = cid_reg < 0 ? 0x7fffffff : cid_reg;
+    if constexpr (LISTED) {   // the tile's centroid ids, ascending, for the search below
+      s_cid[tid] = cid_reg < 0 ? 0x7fffffff : cid_reg;
       __syncthreads();
     }
     if (tid < BM) {
       s_tau[par][tid] = tau_reg;
       // the incumbent of this row, if it is a column of this tile, starts dead: find the thread and the
-      // accumulator element that hold (row tid, column prev - col0).  (Every thread emptied its own marks right
-      // after the previous commit's barrier, and has crossed a multiply step's barrier since.)
+      // accumulator element that hold (row tid, column prev - col0)
       int cl = prev_reg - col0;
-      if (listed) {   // position of the incumbent among the listed ids, if it is one of them
+      if constexpr (LISTED) {   // position of the incumbent among the listed ids, if it is one of them
         int lo = 0;
 #pragma unroll
         for (int step = BN / 2; step > 0; step >>= 1)
           if (s_cid[lo + step] <= prev_reg) lo += step;
         cl = (prev_reg >= 0 && s_cid[lo] == prev_reg) ? lo : -1;
       }
-      if (cl >= 0 && cl < BN) {
-        const int rr = tid & 31;
-        const int lane_t = ((rr >> 2) & 1) * 32 + (cl & 31);
-        const int wave_t = (tid >> 6) * 2 + (cl >> 6);
-        const int v_t = 4 * (rr >> 3) + (rr & 3);
-        const int bit = ((((tid & 63) >> 5) * TN) + ((cl & 63) >> 5)) * 16 + v_t;
-        atomicOr(&s_dead[wave_t * 64 + lane_t], 1ull << bit);
+      if (prev_reg >= 0 && cl >= 0 && cl < BN) {
+        const int rr = tid & 31, blk = cl >> 5;   // column block blk belongs to wavefront blk & 3, its block blk >> 2
+        const int thread = (blk & 3) * 64 + ((rr >> 2) & 1) * 32 + (cl & 31);
+        atomicOr(&s_dead[thread * 4 + (tid >> 5)], 1u << ((blk >> 2) * 16 + 4 * (rr >> 3) + (rr & 3)));
       }
     }
     if (tid == 0) drawn = atomicAdd(ctr, 1u);
     __syncthreads();
   };
-  commit(col_arg(ct), 0);
+  commit(ct * BN, 0);
 
   for (int tile_no = 0;; ++tile_no) {
-    const int row0 = rt * BM, col0 = col_arg(ct);
-    const int par = tile_no & 1;
-
-    f32x16 acc[TM][TN];
+    const int row0 = rt * BM, col0 = ct * BN;
+    const int par = LISTED ? 0 : tile_no & 1;
+    // the tile after this one: its number is known already, its list of columns is fetched while this one is multiplied
+    q = __builtin_amdgcn_readfirstlane(s_q[(tile_no + 1) & 3]);
+    const bool more = q < xcount;
+    int rt_next = 0, ct_next = 0;
+    if (more) {
+      tile_rc(q, rt_next, ct_next);
+      rt_next = __builtin_amdgcn_readfirstlane(rt_next);
+      ct_next = __builtin_amdgcn_readfirstlane(ct_next);
+      if (LISTED) fetch_ids(ct_next);
+    }
+    acc_t<NB> acc;
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
       for (int b = 0; b < TN; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    int gc[TN];   // centroid of this lane's accumulator columns (listed columns: from the committed ids, INT_MAX = none)
+    int gc[TN];   // centroid of this lane's accumulator columns (INT_MAX = none)
 #pragma unroll
-    for (int b = 0; b < TN; ++b) gc[b] = listed ? s_cid[wn * WTN + b * 32 + r32] : col0 + wn * WTN + b * 32 + r32;
-
-    // one alive-bit per accumulator element
-    unsigned long long bits = ~s_dead[tid];
-    s_dead[tid] = 0ull;
-    if (row0 + BM > g.M || (listed ? (gc[0] >= g.N || gc[1] >= g.N) : col0 + BN > g.N)) {
-      // ragged edge tile: rows / columns past the end (or not listed) start dead
+    for (int b = 0; b < TN; ++b) {
+      const int cl = (b * 4 + wave) * 32 + r32;
+      if constexpr (LISTED) gc[b] = s_cid[cl];
+      else gc[b] = col0 + cl < g.N ? col0 + cl : 0x7fffffff;
+    }
+    // one alive-bit per accumulator element: word a, bit 16 b + v
+    unsigned int bits[TM];
+    auto first_bits = [&]() {
+      const uint4 dead = *reinterpret_cast<const uint4 *>(&s_dead[tid * 4]);
+      bits[0] = ~dead.x; bits[1] = ~dead.y; bits[2] = ~dead.z; bits[3] = ~dead.w;
+      const unsigned int cols = (gc[0] < g.N ? 0xffffu : 0u) | (NB > 1 && gc[NB - 1] < g.N ? 0xffff0000u : 0u);
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+      for (int a = 0; a < TM; ++a) bits[a] &= cols;
+      if (row0 + BM > g.M) {   // rows past the end start dead
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const bool ok = (row0 + row_of(a, v) < g.M) && (gc[b] < g.N);
-            bits &= ~((unsigned long long)(!ok) << ((a * TN + b) * 16 + v));
-          }
+          for (int v = 0; v < 16; ++v)
+            if (row0 + row_of(a, v) >= g.M) bits[a] &= ~(0x10001u << v);
+      }
+    };
+    const bool wide = NB > 1 && (LISTED ? s_cid[128 * (NB - 1)] < g.N : g.N - col0 > 128);   // more than 128 columns
+    first_bits();
+    if (!LISTED) {
+#pragma unroll
+      for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
     }
 
     int fin_mode = 0, fin_m = 0;   // how the tile ends: 0 = nothing alive, 1 = reached t = d, 2 = handed over at fin_m
     int wave_alive = 0;            // alive pairs of this wavefront at the last checkpoint
     unsigned int slot0 = 0;        // thread 0: reply of the list reservation
-    float yn[TN] = {0.f, 0.f};
-    // Fragments of half a slab (16 dims): lane half kh supplies the 8 consecutive dims 16 h + 8 kh .. + 7 of both
-    // operands.  x.y ~ hi.hi' + lo.hi' + hi.lo' on the fp16 matrix cores, fp32 accumulation, in groups of four
-    // matrix instructions; the fragments of the second half-slab are fetched as the first half releases registers.
-    f16x8 ah[TM], al[TM], bh[TN], bl[TN];
-    auto frag = [&](const uint32_t *base, int h, int lo, int t) {
-      return *reinterpret_cast<const f16x8 *>(base + t * 32 * ROW_WORDS + (((4 * h + 2 * lo + kh) ^ swz) << 2));
-    };
-    auto mma4 = [&](const f16x8 (&x)[TM], const f16x8 (&y)[TN]) {
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[a], y[b], acc[a][b], 0, 0, 0);
-    };
-    for (int s = 0; s < nslab; ++s) {
-      const int tdone = koff + BK * (s + 1);   // dimensions multiplied after this step
-      const bool last = (s + 1 == nslab);
-      const bool check = !last && tdone >= g.dprime && tdone < g.d && ((tdone - g.dprime) & (kBlockDims - 1)) == 0;
-      const bool cp = check || last;
-      const int m = last ? g.nb : (tdone - g.dprime) / kBlockDims;   // checkpoint index, t_m = min(d, d' + 64 m)
-      // the norms of checkpoint m were requested one step ago (or with the tile's first slab); every step requests
-      // those of the step after it, needed or not, so that the request is never behind a branch
-      if (cp) publish_norms(s_ratio[m]);
-      load_norm(s + 1);
-      // the next slab goes straight into the other stage, which every wavefront has finished reading (the barrier
-      // that ended the previous step); it is complete, and visible, after the wait and the barrier below
-      if (!last) issue(stg ^ 1, s + 1);
-      const uint32_t *Ab = smem + stg * STAGE_WORDS + (wm * WTM + r32) * ROW_WORDS;
-      const uint32_t *Bb = smem + stg * STAGE_WORDS + (BM + wn * WTN + r32) * ROW_WORDS;
-      {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          ah[t] = frag(Ab, 0, 0, t); bh[t] = frag(Bb, 0, 0, t);
-          al[t] = frag(Ab, 0, 1, t); bl[t] = frag(Bb, 0, 1, t);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        mma4(ah, bh);
-        mma4(al, bh);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) { al[t] = frag(Ab, 1, 1, t); bh[t] = frag(Bb, 1, 0, t); }
-        mma4(ah, bl);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) { ah[t] = frag(Ab, 1, 0, t); bl[t] = frag(Bb, 1, 1, t); }
-        mma4(al, bh);
-        __builtin_amdgcn_sched_barrier(0);
-        mma4(ah, bl);
-        mma4(ah, bh);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      stg ^= 1;
-      SKM_VMCNT(0);
-      __syncthreads();
+    float yn[TN] = {};
+    float xn0 = 0.f;               // this thread's row: its norm over the first d' dimensions
+    const bool deep = LISTED && __builtin_amdgcn_readfirstlane(g.deep && !redone);
+    int t = 0;                     // dimensions multiplied
+    int m = 0;                     // next checkpoint, at dimension tcp
+    int tcp = g.dprime;
+    int ncp = 0;                   // checkpoints seen (row of s_wcnt)
+    unsigned int dims3 = 0, dims1 = 0;
+    // Units until the tile ends (0), goes on in one product (1) or has to be done again in three (2); kind: one product
+    // or three, a constant.  (Two loops rather than one with both kinds of unit: the accumulators of a loop with two
+    // multiply blocks do not stay in place.)
+    auto advance = [&](auto kind) -> int {
+    constexpr bool one = decltype(kind)::value;
+    constexpr int step = one ? 32 : 16;
+    while (true) {
+      cur = __builtin_amdgcn_readfirstlane(cur);   // (uniform: kept in scalar registers)
+      treq = __builtin_amdgcn_readfirstlane(treq);
+      t = __builtin_amdgcn_readfirstlane(t);
+      m = __builtin_amdgcn_readfirstlane(m);
+      tcp = __builtin_amdgcn_readfirstlane(tcp);
+      // the unit has arrived once at most the unit requested after it is outstanding (loads are counted in order)
+      if (treq > t + step) SKM_VMCNT(A_LD + B_LD);
+      else SKM_VMCNT(0);
+      const bool cp = t + step >= tcp, last = t + step >= g.ds;
       if (cp) {
+        // the prefix norms fetched one checkpoint ago -> LDS, with the row's threshold theta(t_m, tau) - ||x_t||^2
+        if (tid < BM) {
+          float thr = rreg * tau_reg - nxreg;
+          if (one)   // + the error bound of the one product over the dimensions behind d', and guards
+            thr += fmaf(wreg.x, sqrtf(fmaxf(nxreg - xn0, 0.f) + 1e-6f * nxreg), fmaf(1e-6f, rreg * tau_reg + nxreg, wreg.y));
+          s_xn[tid] = nxreg;
+          s_thr[tid] = thr;
+          if (LISTED && m == 0) xn0 = nxreg;
+        }
+        if (NB > 1 || tid < BN) s_yn[tid] = nyreg;
+      }
+      SKM_BARRIER();   // everyone's share of the unit is there, and the stage before it is free
+      if (cp) load_norm(m + 1);
+      if (treq < g.ds) {
+        const bool o = LISTED && deep && treq >= g.dprime;
+        request(treq, o, cur == 0 ? NSTAGE - 1 : cur - 1);
+        treq += o ? 32 : 16;
+      }
+      {
+        const uint32_t *Ab = smem + cur * STAGE_WORDS + r32 * ROW_WORDS;
+        const uint32_t *Bb = smem + cur * STAGE_WORDS + (BM + wave * 32 + r32) * ROW_WORDS;
+        if constexpr (one) unit_one<NB>(acc, Ab, Bb, p0, p1);
+        else unit_three<NB>(acc, Ab, Bb, p0, p1);
+      }
+      cur = cur == NSTAGE - 1 ? 0 : cur + 1;
+      t += step;
+      if (one) dims1 += step;
+      else dims3 += step;
+      if (!cp) continue;
+
 #pragma unroll
-        for (int b = 0; b < TN; ++b) yn[b] = s_yn[wn * WTN + b * 32 + r32];
-        if (!last || g.nb == 0) {
-          // test theta(t_m, tau_i): drop the pair when its partial distance exceeds it.  The sign of threshold minus
-          // distance is the verdict (a difference of two floats is negative exactly when the second is larger); the
-          // signs of the 32 elements of an accumulator row block are shifted into one word, last element first, one
-          // funnel shift each.
+      for (int b = 0; b < TN; ++b) yn[b] = s_yn[(b * 4 + wave) * 32 + r32];
+      if (!last || g.nb == 0) {
+        // test theta(t_m, tau_i): drop the pair when its partial distance exceeds it.  The sign of threshold minus
+        // distance is the verdict (a difference of two floats is negative exactly when the second is larger); the
+        // signs of the 32 elements of an accumulator row block are shifted into one word, last element first, one
+        // funnel shift each.
 #pragma unroll
-          for (int a = 0; a < TM; ++a) {
-            unsigned int dropped = 0u;
+        for (int a = 0; a < TM; ++a) {
+          unsigned int dropped = 0u;
+          float thr[16];
 #pragma unroll
-            for (int b = TN - 1; b >= 0; --b)
-#pragma unroll
-              for (int v = 15; v >= 0; --v) {
-                const float margin = s_thr[row_of(a, v)] - fmaf(m2, acc[a][b][v], yn[b]);
-                dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
-              }
-            bits &= ~((unsigned long long)dropped << (32 * a));
+          for (int v4 = 0; v4 < 4; ++v4) {
+            const float4 f = *reinterpret_cast<const float4 *>(&s_thr[a * 32 + 8 * v4 + 4 * kh]);
+            thr[4 * v4] = f.x; thr[4 * v4 + 1] = f.y; thr[4 * v4 + 2] = f.z; thr[4 * v4 + 3] = f.w;
           }
-          static_assert(TN * 16 == 32, "one word per accumulator row block");
+#pragma unroll
+          for (int b = TN - 1; b >= 0; --b)
+#pragma unroll
+            for (int v = 15; v >= 0; --v) {
+              const float margin = thr[v] - fmaf(m2, acc[a][b][v], yn[b]);
+              dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
+            }
+          bits[a] &= ~dropped;
         }
-        // alive pairs of this wavefront and of the whole tile
-        wave_alive = wave_sum_i32(__popcll(bits));
-        if (lane == 0) s_wcnt[m & 1][wave] = (unsigned int)wave_alive;
-        __syncthreads();
-        // (the counts of checkpoint m + 1 go to the other row: a wavefront that is already there cannot disturb this read)
-        const uint4 wc = *reinterpret_cast<const uint4 *>(s_wcnt[m & 1]);
-        const unsigned int total = wc.x + wc.y + wc.z + wc.w;
-        if (tid == 0) {
-          // a tile that hands its pairs over reserves their slots now (one reservation per tile in the sub-list of
-          // this workgroup's XCD): the answer is not needed before the next tile's loads have been requested
-          if (!last && total != 0u && total <= g.emit_max) slot0 = atomicAdd(g.pair_count + xcd * kSubListStride, total);
-          if (total) {
-            if (m == 0) atomicAdd(sc + SC_SURVIVORS, (unsigned long long)total);
-            if (!last && g.block_stats) atomicAdd(sc + SC_ENTER + m, (unsigned long long)total);
-            if (last) atomicAdd(sc + SC_COMPLETED, (unsigned long long)total);
-          }
-          if (total == 0u || last || total <= g.emit_max)   // the tile ends here
-            atomicAdd(sc + SC_DENSE_DIMS, (unsigned long long)(BK * (s + 1)));
-          else                                               // the next block of these pairs is done densely
-            atomicAdd(sc + SC_DENSE_PB, (unsigned long long)total);
-        }
-        if (total == 0u) break;
-        if (last) {
-          fin_mode = 1;
-          fin_m = m;
-          break;
-        }
-        if (total <= g.emit_max) {
-          fin_mode = 2;
-          fin_m = m;
-          break;
+        static_assert(TN * 16 <= 32, "one word per accumulator row block");
+      }
+      // alive pairs of this wavefront and of the whole tile
+      wave_alive = wave_sum_i32(__popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]));
+      if (lane == 0) s_wcnt[ncp & 1][wave] = (unsigned int)wave_alive;
+      SKM_BARRIER();
+      // (the next checkpoint's counts go to the other row: a wavefront that is already there cannot disturb this read)
+      const uint4 wc = *reinterpret_cast<const uint4 *>(s_wcnt[ncp & 1]);
+      ++ncp;
+      const unsigned int total = __builtin_amdgcn_readfirstlane(wc.x + wc.y + wc.z + wc.w);
+      // behind the first test a widened tile hands over once few pairs are left (their way starts again at dimension 0),
+      // and at the end; otherwise a tile that is sparse does
+      const unsigned int limit = LISTED && deep ? (m == 0 ? g.emit_first : (last ? g.emit_max : g.emit_deep)) : g.emit_max;
+      const bool redo = LISTED && deep && (m == 0 ? total > g.deep_max : last && total > g.emit_max);
+      const bool hand = total != 0u && total <= limit && (!last || one) && !redo;
+      if (tid == 0) {
+        // a tile that hands its pairs over reserves their slots now (one reservation per tile in the sub-list of
+        // this workgroup's XCD): the answer is not needed before the next tile's loads have been requested
+        if (hand) slot0 = atomicAdd(g.pair_count + xcd * kSubListStride, total);
+        if (total) {
+          if (m == 0 && !redone) atomicAdd(sc + SC_SURVIVORS, (unsigned long long)total);
+          if (!last && g.block_stats) atomicAdd(sc + SC_ENTER + m, (unsigned long long)total);
+          if (last && !hand && !redo) atomicAdd(sc + SC_COMPLETED, (unsigned long long)total);
+          if (!last && !hand && !redo) atomicAdd(sc + SC_DENSE_PB, (unsigned long long)total);   // the next block of these pairs is done densely
         }
       }
+      if (total == 0u) return 0;
+      if (hand) {
+        fin_mode = 2;
+        fin_m = m;
+        return 0;
+      }
+      if (redo) return 2;
+      if (last) {
+        fin_mode = 1;
+        fin_m = m;
+        return 0;
+      }
+      ++m;
+      tcp = min(g.dprime + kBlockDims * m, g.ds);
+      if (LISTED && !one && deep) return 1;   // behind the first test
+    }
+    };
+    int act = advance(std::false_type());
+    if constexpr (LISTED) {
+      if (act == 1) act = advance(std::true_type());
+    }
+    if (tid == 0) {   // (in tiles of 128 x 128)
+      atomicAdd(sc + SC_DENSE_DIMS, (unsigned long long)dims3 << (wide ? 1 : 0));
+      if (LISTED && dims1) atomicAdd(sc + SC_SCREEN_DIMS, (unsigned long long)dims1 << (wide ? 1 : 0));
     }
 
-    // ---- start fetching the next tile before this one is written out
-    q = __builtin_amdgcn_readfirstlane(s_q[(tile_no + 1) & 3]);
-    const bool more = q < xcount;
-    int nrt_ = 0, nct_ = 0;
+    // ---- start fetching the next tile before this one is written out (what was requested ahead of this tile's end has
+    // to land first: the stages are reused; stage cur - 1, the last one read, stays free for the hand-over below)
+    SKM_VMCNT(0);
+    if (LISTED && act == 2) {
+      // the tile once more, in three products throughout
+      redone = true;
+      start_tile();
+      --tile_no;
+      continue;
+    }
     if (more) {
-      tile_rc(q, nrt_, nct_);
-      nrt_ = __builtin_amdgcn_readfirstlane(nrt_);
-      nct_ = __builtin_amdgcn_readfirstlane(nct_);
-      aim(nrt_ * BM, col_arg(nct_));
-      load_norm(0);
-      issue(stg, 0);   // both stages are free: every wavefront has passed the barrier of the last multiply step
-      load_rows(nrt_ * BM);
+      aim(rt_next, ct_next);
+      start_tile();
     }
 
-    if (fin_mode == 1) {
+    if (!LISTED && fin_mode == 1) {
       // finished distances: offer those below tau_i to the point's packed minimum
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+      for (int h = 0; h < TM; h += 2) {
+        const unsigned long long key = reduce_rows32(
+            [&](int a, int v) {
+              unsigned long long k = ~0ull;
+              const int rl = row_of(h + a, v);
+              const float xr = s_xn[rl], tr = s_tau[par][rl];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int rl = row_of(a, v);
-          unsigned long long key = ~0ull;
-#pragma unroll
-          for (int b = 0; b < TN; ++b) {
-            if ((bits >> ((a * TN + b) * 16 + v)) & 1ull) {
-              float dist = s_xn[rl] + fmaf(m2, acc[a][b][v], yn[b]);
-              dist = dist > 0.f ? dist : 0.f;
-              if (dist < s_tau[par][rl]) {
-                const unsigned long long kb = pack_key(dist, gc[b]);
-                key = kb < key ? kb : key;
-              }
-            }
-          }
-          if (__ballot(key != ~0ull)) {
-#pragma unroll
-            for (int sh = 1; sh < 32; sh <<= 1) {
-              const unsigned long long o = __shfl_xor(key, sh, 64);
-              key = o < key ? o : key;
-            }
-            if (r32 == 0 && key != ~0ull) atomicMin(g.best + g.row_base + row0 + rl, key);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-    } else if (fin_mode == 2) {
-      // sparse enough: hand the alive pairs to the gather kernel, which resumes at block fin_m
-      if (tid == 0) {
-        const unsigned int tot = s_wcnt[fin_m & 1][0] + s_wcnt[fin_m & 1][1] + s_wcnt[fin_m & 1][2] + s_wcnt[fin_m & 1][3];
+              for (int b = 0; b < TN; ++b)
+                if ((bits[h + a] >> (b * 16 + v)) & 1u) {
+                  float dist = xr + fmaf(m2, acc[h + a][b][v], yn[b]);
+                  dist = dist > 0.f ? dist : 0.f;
+                  if (dist < tr) {
+                    const unsigned long long kb = pack_key(dist, gc[b]);
+                    k = kb < k ? kb : k;
+                  }
+                }
+              return k;
+            },
+            lane);
+        const int rl = row_of(h + (r32 >> 4), r32 & 15);
+        if (key != ~0ull) atomicMin(g.best + g.row_base + row0 + rl, key);   // (rows past the end are dead: ~0)
+      }
+    } else if (fin_mode != 0) {
+      // sparse enough: hand the alive pairs to the gather kernel, which resumes at block fin_m (or starts over).
+      // (A listed tile that is finished here offers its few distances one by one on the same way.)
+      const bool offer = LISTED && fin_mode == 1;
+      if (!offer && tid == 0) {
         unsigned int base = slot0;
+        const unsigned int *w = s_wcnt[(ncp - 1) & 1];
+        const unsigned int tot = w[0] + w[1] + w[2] + w[3];
         if ((unsigned long long)base + tot > (unsigned long long)g.sub_capacity) {
           atomicOr(g.overflow, 1u);
           base = 0xffffffffu;
@@ -526,15 +617,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
         s_base = base;
       }
-      __syncthreads();
-      unsigned int run = s_base;
+      SKM_BARRIER();
+      unsigned int run = offer ? 0u : s_base;
       if (run != 0xffffffffu && wave_alive > 0) {
-        for (int w = 0; w < wave; ++w) run += s_wcnt[fin_m & 1][w];
+        for (int w = 0; w < wave; ++w) run += s_wcnt[(ncp - 1) & 1][w];
         // A sparse tile holds one or two alive pairs per lane.  Every lane walks its own alive bits; the accumulator
-        // element behind a bit is found through LDS, where the lane parks its 32 values of a row block (a register
-        // cannot be chosen per lane): the stage the last multiply step read is free, 8 KB per wavefront as [32][64].
+        // element behind a bit is found through LDS, where the lane parks its 16 values of a block (a register
+        // cannot be chosen per lane): the stage the last unit was read from is free, 4 KB per wavefront as [16][64].
         // List slots: the wavefront's range, then lane by lane (prefix sum of the lanes' counts), then bit by bit.
-        int upto = __popcll(bits);
+        int upto = __popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]);
         const int mine = upto;
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, false);   // row_shr:1
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xF, 0xF, false);   // row_shr:2
@@ -543,58 +634,78 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xA, 0xF, false);   // row_bcast:15
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xC, 0xF, false);   // row_bcast:31
         unsigned int pos = run + (unsigned int)(upto - mine);
-        float *park = reinterpret_cast<float *>(smem + (stg ^ 1) * STAGE_WORDS + wave * (32 * 64)) + lane;
-        const int irow = wm * WTM + 4 * kh;   // + a * 32 + 8 * (v >> 2) + (v & 3)
+        const bool over = LISTED && fin_m > 0 && deep;   // the partial sum holds one-product parts: the pair starts over
+        float *park = reinterpret_cast<float *>(smem + (cur == 0 ? NSTAGE - 1 : cur - 1) * STAGE_WORDS + wave * (16 * 64)) + lane;
+        const unsigned int mtag = over ? 0u : (unsigned int)fin_m << 24;
 #pragma unroll
-        for (int a = 0; a < TM; ++a) {
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-          for (int b = 0; b < TN; ++b)
+          for (int b = 0; b < TN; ++b) {
+            unsigned int left = (bits[a] >> (16 * b)) & 0xffffu;
+            if (!__ballot(left)) continue;
+            if (!over) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) park[(b * 16 + v) * 64] = acc[a][b][v];
-          unsigned int left = (unsigned int)(bits >> (32 * a));
-          while (left) {
-            const int e = __builtin_ctz(left);   // b * 16 + v
-            left &= left - 1u;
-            const int v = e & 15, b = e >> 4;
-            const int rl = irow + a * 32 + 8 * (v >> 2) + (v & 3);
-            Pair pr;
-            pr.i = (int32_t)g.row_base + row0 + rl;
-            pr.j = (int32_t)((uint32_t)gc[b ? 1 : 0] | ((uint32_t)fin_m << 24));
-            const float p = s_xn[rl] + fmaf(m2, park[e * 64], b ? yn[1] : yn[0]);
-            pr.p = p > 0.f ? p : 0.f;
-            pr.tau = s_tau[par][rl];
-            g.pairs[pos++] = pr;
+              for (int v = 0; v < 16; ++v) park[v * 64] = acc[a][b][v];
+            }
+            while (left) {
+              const int v = __builtin_ctz(left);
+              left &= left - 1u;
+              const int rl = a * 32 + 4 * kh + 8 * (v >> 2) + (v & 3);
+              float p = -1.f;
+              if (!over) {
+                p = s_xn[rl] + fmaf(m2, park[v * 64], yn[b]);
+                p = p > 0.f ? p : 0.f;
+              }
+              if (LISTED && offer) {
+                if (p < s_tau[par][rl]) atomicMin(g.best + g.row_base + row0 + rl, pack_key(p, gc[b]));
+                continue;
+              }
+              Pair pr;
+              pr.i = (int32_t)g.row_base + row0 + rl;
+              pr.j = (int32_t)((uint32_t)gc[b] | mtag);
+              pr.p = p;
+              pr.tau = s_tau[par][rl];
+              g.pairs[pos++] = pr;
+            }
           }
-        }
       }
     }
 
+    redone = false;
     if (!more) break;
-    rt = nrt_;
-    ct = nct_;
+    rt = rt_next;
+    ct = ct_next;
+    if (LISTED) {
+#pragma unroll
+      for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
+    }
     if (tid == 0) s_q[(tile_no + 2) & 3] = (int)drawn;
-    commit(col_arg(ct), par ^ 1);   // its barrier also ends this tile: everyone is done with the tile's LDS
+    commit(ct * BN, LISTED ? 0 : par ^ 1);   // its barrier also ends this tile: everyone is done with the tile's LDS
   }
 }
 
-hipError_t launch_progressive(const ProgArgs &g, hipStream_t st) {
+hipError_t launch_progressive(const ProgArgs &args, hipStream_t st) {
+  ProgArgs g = args;
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.ds % 16 != 0 || g.dprime % 16 != 0 || g.dprime < 16 || g.dprime > g.ds || g.lda != g.ds + 32 || g.ldb != g.ds + 32 ||
       g.nb > kMaxBlocks || (reinterpret_cast<uintptr_t>(g.A) & 15u) || (reinterpret_cast<uintptr_t>(g.B) & 15u) ||
       g.N > (1 << 24))
     return hipErrorInvalidValue;
-  constexpr size_t smem = (size_t)2 * STAGE_WORDS * sizeof(uint32_t);
   // once per process (the initialisation of a function-local static is synchronised between threads): the kernel's LDS
   // size, and two workgroups per CU (LDS and registers allow no more)
+  constexpr size_t smem1 = (size_t)NSTAGE * kStageWords<1> * sizeof(uint32_t), smem2 = (size_t)NSTAGE * kStageWords<2> * sizeof(uint32_t);
   struct Setup {
     hipError_t rc;
     int wgs = 0;
     Setup() {
-      rc = hipFuncSetAttribute(reinterpret_cast<const void *>(progressive_kernel<false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      rc = hipFuncSetAttribute(reinterpret_cast<const void *>(progressive_kernel<false, 1>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem1);
       if (rc == hipSuccess)
-        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(progressive_kernel<true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(progressive_kernel<false, 2>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem2);
+      if (rc == hipSuccess)
+        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(progressive_kernel<true, 2>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem2);
       int dev = 0, cus = 256;
       (void)hipGetDevice(&dev);
       (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -606,18 +717,27 @@ hipError_t launch_progressive(const ProgArgs &g, hipStream_t st) {
   const int wgs = setup.wgs;
   if ((g.col_list != nullptr) != (g.tile_rt != nullptr) || (g.col_list != nullptr) != (g.ntiles != nullptr))
     return hipErrorInvalidValue;
-  const int64_t ntiles = (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  if (g.deep && (!g.col_list || !g.Ah || !g.Bh || !g.widen || (reinterpret_cast<uintptr_t>(g.Ah) & 15u) ||
+                 (reinterpret_cast<uintptr_t>(g.Bh) & 15u)))
+    return hipErrorInvalidValue;
+  // Tiles of 128 columns where tiles of 256 would give a CU fewer than eight: what the last round leaves idle then costs
+  // more than the narrower tile's extra fragment reads.
+  const int64_t nrt = (g.M + BM - 1) / BM;
+  const bool narrow = !g.col_list && nrt * ((g.N + 255) / 256) < (int64_t)4 * wgs;
+  if (narrow) g.emit_max /= 2;
+  const int64_t ntiles = nrt * (narrow ? (g.N + 127) / 128 : (g.N + 255) / 256);
   if (ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
   const int64_t grid = std::max<int64_t>(8, std::min<int64_t>(wgs, (ntiles + 7) / 8 * 8));
   if (g.col_list)
-    hipLaunchKernelGGL(progressive_kernel<true>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+    hipLaunchKernelGGL((progressive_kernel<true, 2>), dim3((unsigned)grid), dim3(NT), smem2, st, g);
+  else if (narrow)
+    hipLaunchKernelGGL((progressive_kernel<false, 1>), dim3((unsigned)grid), dim3(NT), smem1, st, g);
   else
-    hipLaunchKernelGGL(progressive_kernel<false>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+    hipLaunchKernelGGL((progressive_kernel<false, 2>), dim3((unsigned)grid), dim3(NT), smem2, st, g);
   return hipGetLastError();
 }
 
-int64_t progressive_tiles(int64_t rows, int32_t k) { return ((rows + BM - 1) / BM) * (int64_t)((k + BN - 1) / BN); }
-int32_t progressive_tile_pairs() { return BM * BN; }
-int32_t progressive_tile_cols() { return BN; }
+int64_t progressive_tiles(int64_t rows, int32_t k) { return ((rows + BM - 1) / BM) * (int64_t)((k + 255) / 256); }
+int32_t progressive_tile_pairs() { return BM * 256; }
 
 }  // namespace skm

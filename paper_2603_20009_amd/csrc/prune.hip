@@ -58,15 +58,16 @@ __global__ void __launch_bounds__(PRUNE_THREADS) prune_kernel(PruneArgs a) {
   const int q = tid & (PAIR_LANES - 1);
   unsigned int p = (blockIdx.x >> 3) * (PRUNE_THREADS / PAIR_LANES) + (tid / PAIR_LANES);
   bool active = p < total;
-  int i = 0, j = 0, m = 0;
+  int i = 0, j = 0, m = 0, front = 0;
   float acc = 0.f, tau = 0.f;
   auto unpack = [&](const Pair &pr) {
     const unsigned int jm = (unsigned int)pr.j;
     i = pr.i;
     j = (int)(jm & 0xffffffu);
     m = (int)(jm >> 24);   // first block still to be added
-    acc = pr.p;
+    acc = fmaxf(pr.p, 0.f);
     tau = pr.tau;
+    front = pr.p < 0.f ? 0 : a.dprime;   // p < 0: the pair starts over, its first d' dimensions come first
     // An entry that names no point or centroid is skipped (finished at once, offering nothing).  Every producer
     // writes valid entries only; but after a producer's overflow, which the host answers by redoing the step another
     // way, slots inside the counted range may never have been written.
@@ -76,6 +77,7 @@ __global__ void __launch_bounds__(PRUNE_THREADS) prune_kernel(PruneArgs a) {
       m = a.nb;
       acc = 1.f;
       tau = 0.f;
+      front = a.dprime;
     }
   };
   if (active) {
@@ -87,16 +89,22 @@ __global__ void __launch_bounds__(PRUNE_THREADS) prune_kernel(PruneArgs a) {
   if (pn < total) nx = list[pn];
   while (__any(active)) {
     if (active) {
-      if (m < a.nb) {
+      const bool ahead = front < a.dprime;
+      if (ahead || m < a.nb) {
         // lane q holds float4 q and float4 q + 8 of the 16 in a block
-        const int col = a.dprime + kBlockDims * m + 4 * q;
+        const int col = (ahead ? front : a.dprime + kBlockDims * m) + 4 * q;
+        const int end = ahead ? a.dprime : a.ds;
         const float *xp = a.Xr + (int64_t)i * a.ldx + col;
-        const float *yp = a.Ypdx + ((int64_t)m * a.k + j) * kBlockDims + 4 * q;
-        float4 x0 = make_float4(0.f, 0.f, 0.f, 0.f), x1 = x0;
-        if (col < a.ds) x0 = *reinterpret_cast<const float4 *>(xp);
-        if (col + 32 < a.ds) x1 = *reinterpret_cast<const float4 *>(xp + 32);
-        const float4 y0 = *reinterpret_cast<const float4 *>(yp);
-        const float4 y1 = *reinterpret_cast<const float4 *>(yp + 32);
+        const float *yp = ahead ? a.Y + (int64_t)j * a.ds + col : a.Ypdx + ((int64_t)m * a.k + j) * kBlockDims + 4 * q;
+        float4 x0 = make_float4(0.f, 0.f, 0.f, 0.f), x1 = x0, y0 = x0, y1 = x0;
+        if (col < end) {
+          x0 = *reinterpret_cast<const float4 *>(xp);
+          y0 = *reinterpret_cast<const float4 *>(yp);
+        }
+        if (col + 32 < end) {
+          x1 = *reinterpret_cast<const float4 *>(xp + 32);
+          y1 = *reinterpret_cast<const float4 *>(yp + 32);
+        }
         float dx = x0.x - y0.x, dy = x0.y - y0.y, dz = x0.z - y0.z, dw = x0.w - y0.w;
         float s = dx * dx;
         s = fmaf(dy, dy, s);
@@ -108,12 +116,15 @@ __global__ void __launch_bounds__(PRUNE_THREADS) prune_kernel(PruneArgs a) {
         s = fmaf(dz, dz, s);
         s = fmaf(dw, dw, s);
         acc += row8_sum(s);
-        ++m;
+        front += kBlockDims;
+        m += ahead ? 0 : 1;
         ++my_steps;
       }
-      const bool done = m >= a.nb;
+      // (behind the first d' dimensions of a pair that starts over there is no test: it has passed it)
+      const bool done = !ahead && m >= a.nb;
       bool drop = false;
-      if (done) {
+      if (ahead) {
+      } else if (done) {
         if (q == 0) {
           atomicAdd(&s_completed, 1u);
           if (acc < tau) atomicMin(a.best + i, pack_key(acc, j));

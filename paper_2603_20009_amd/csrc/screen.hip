@@ -7,7 +7,7 @@
 // half the bytes through L2 and LDS, a third of the matrix instructions), and the first test with its threshold
 // widened by a bound of the error that the dropped lo halves can cause.  A pair that passes the exact test passes the
 // widened one, so a column that no point of a row tile passes here is dead for that whole tile.  The output is one bit
-// per (row tile, centroid); compaction turns the bits into a list of centroid ids per row tile, cut into tiles of 128
+// per (row tile, centroid); compaction turns the bits into a list of centroid ids per row tile, cut into tiles of 256
 // listed columns, and the progressive kernel then runs on those tiles only, with the full arithmetic, the exact tests
 // and the exact counters.  What is pruned here is pruned by Algorithm 1's first test as well: the result of the step
 // does not depend on whether this pass ran.
@@ -441,15 +441,18 @@ __global__ void __launch_bounds__(256) mask_count_kernel(const uint32_t *mask, i
   if (lane == 0) cnt[rt] = c;
 }
 
-// first[rt] = first tile of row tile rt (tiles of 128 listed columns, row tiles in order), *ntiles = their number
+// first[rt] = first tile of row tile rt (tiles of kListCols listed columns, row tiles in order), *ntiles = their number
 __global__ void __launch_bounds__(1024) mask_scan_kernel(const int32_t *cnt, int32_t nrt, int32_t *first, int32_t *ntiles,
                                                          unsigned long long *scal) {
   __shared__ int s_part[1024];
   const int tid = threadIdx.x;
   const int per = (nrt + 1023) / 1024;
   const int lo = min(tid * per, nrt), hi = min(lo + per, nrt);
-  int sum = 0;
-  for (int r = lo; r < hi; ++r) sum += (cnt[r] + 127) >> 7;
+  int sum = 0, listed = 0;
+  for (int r = lo; r < hi; ++r) {
+    sum += (cnt[r] + kListCols - 1) / kListCols;
+    listed += (cnt[r] + 127) >> 7;
+  }
   s_part[tid] = sum;
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {   // inclusive scan of the per-thread sums
@@ -461,16 +464,16 @@ __global__ void __launch_bounds__(1024) mask_scan_kernel(const int32_t *cnt, int
   int run = s_part[tid] - sum;
   for (int r = lo; r < hi; ++r) {
     first[r] = run;
-    run += (cnt[r] + 127) >> 7;
+    run += (cnt[r] + kListCols - 1) / kListCols;
   }
-  if (tid == 1023) {
-    *ntiles = s_part[1023];
-    atomicAdd(scal + SC_LISTED_TILES, (unsigned long long)s_part[1023]);
-  }
+  if (tid == 1023) *ntiles = s_part[1023];
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) listed += __shfl_xor(listed, m, 64);
+  if ((tid & 63) == 0 && listed) atomicAdd(scal + SC_LISTED_TILES, (unsigned long long)listed);   // (in tiles of 128)
 }
 
-// One workgroup per row tile: the ids of its set bits in ascending order, padded with -1 to a multiple of 128, into
-// col_list[128 * first[rt] ...]; tile_rt[t] = rt for each of its tiles.
+// One workgroup per row tile: the ids of its set bits in ascending order, padded with -1 to a multiple of kListCols,
+// into col_list[kListCols * first[rt] ...]; tile_rt[t] = rt for each of its tiles.
 __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, int32_t maskw, const int32_t *cnt,
                                                         const int32_t *first, int32_t *col_list, int32_t *tile_rt) {
   __shared__ int s_wave[4];
@@ -478,8 +481,8 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
   const int rt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int total = cnt[rt];
-  const int t0 = first[rt], nt = (total + 127) >> 7;
-  int32_t *out = col_list + (int64_t)t0 * 128;
+  const int t0 = first[rt], nt = (total + kListCols - 1) / kListCols;
+  int32_t *out = col_list + (int64_t)t0 * kListCols;
   if (tid == 0) s_base = 0;
   __syncthreads();
   for (int w0 = 0; w0 < maskw; w0 += 256) {
@@ -505,7 +508,7 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     if (tid == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
     __syncthreads();
   }
-  for (int p = total + tid; p < nt * 128; p += 256) out[p] = -1;
+  for (int p = total + tid; p < nt * kListCols; p += 256) out[p] = -1;
   for (int t = tid; t < nt; t += 256) tile_rt[t0 + t] = rt;
 }
 
@@ -545,19 +548,42 @@ __global__ void __launch_bounds__(256) screen_terms_kernel(const float *tau, con
   if (i < N) ycol[i] = yn[i] * (1.f - kGuard) * inv_k;
 }
 
-// *out = max of v[0 .. n) (non-negative values: their bit patterns order like the numbers)
-__global__ void __launch_bounds__(1024) max_value_kernel(const float *v, int32_t n, float *out, stamp_t *stamp) {
+// Workgroup 0: *out = max of yn[0 .. n) (non-negative values: their bit patterns order like the numbers).
+// Workgroup 1 + m (with ynp): the terms of the widened test at checkpoint m, widen[m] = (widening 1.1 2^-9 times the
+// largest centroid norm over the dimensions d' .. t_m, slack for halves below the smallest normal fp16 + guard for the
+// rounding of values of the centroids' size).
+__global__ void __launch_bounds__(1024) max_value_kernel(const float *yn, const float *ynp, int32_t n, float *out,
+                                                         float2 *widen, int32_t ds, const unsigned int *a_absmax,
+                                                         const unsigned int *b_absmax, stamp_t *stamp) {
   put_stamp(stamp);
-  __shared__ float red[16];
-  float m = 0.f;
-  for (int i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, v[i]);
+  __shared__ float red[16], red2[16];
+  const float *v = blockIdx.x == 0 ? yn : ynp + (int64_t)(blockIdx.x - 1) * n;
+  float m = 0.f, p = 0.f;
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    m = fmaxf(m, v[i]);
+    p = fmaxf(p, v[i] - yn[i]);
+  }
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  for (int off = 1; off < 64; off <<= 1) {
+    m = fmaxf(m, __shfl_xor(m, off, 64));
+    p = fmaxf(p, __shfl_xor(p, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = m;
+    red2[threadIdx.x >> 6] = p;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w]);
-    *out = m;
+    for (int w = 1; w < 16; ++w) {
+      m = fmaxf(m, red[w]);
+      p = fmaxf(p, red2[w]);
+    }
+    if (blockIdx.x == 0) {
+      *out = m;
+    } else {
+      const float slack = (float)ds * __builtin_bit_cast(float, *a_absmax) * __builtin_bit_cast(float, *b_absmax) * (1.f / 8589934592.f);
+      widen[blockIdx.x - 1] = make_float2(kWiden * sqrtf(p + kGuard * m), slack + 2.f * kGuard * m);
+    }
   }
 }
 
@@ -625,7 +651,8 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   g.a_absmax = a.a_absmax; g.b_absmax = a.b_absmax;
   g.dprime = a.dprime;
   float *ynmax = reinterpret_cast<float *>(a.ntiles + 1);   // (the word after the tile count)
-  hipLaunchKernelGGL(max_value_kernel, dim3(1), dim3(1024), 0, st, a.yn, a.N, ynmax, a.stamp);
+  hipLaunchKernelGGL(max_value_kernel, dim3(a.widen ? (unsigned)a.nb + 2 : 1), dim3(1024), 0, st, a.yn, a.ynp, a.N, ynmax,
+                     a.widen, a.ds, a.a_absmax, a.b_absmax, a.stamp);
   hipLaunchKernelGGL(screen_terms_kernel, dim3((unsigned)((std::max<int64_t>(a.M, a.N) + 255) / 256)), dim3(256), 0, st,
                      a.tau, a.xn, a.row_base, a.M, a.yn, a.N, (const float *)ynmax, a.ratio0, a.dprime, a.a_absmax,
                      a.b_absmax, a.arow, a.ycol, a.exact ? 1 : 0);

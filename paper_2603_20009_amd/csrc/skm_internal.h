@@ -20,6 +20,49 @@ struct __attribute__((aligned(16))) Pair {
   float tau;   // the point's pruning threshold for this step
 };
 
+#if defined(__HIPCC__)
+// One step of a reduce-scatter of keys over the lanes of a wavefront half: of the two keys, lanes with BIT clear go on
+// with the first and lanes with it set with the second, each merged (minimum) with the partner's.
+template <int DPP, int BIT>
+__device__ inline unsigned long long halve_min(unsigned long long p, unsigned long long q, int lane) {
+  const bool up = lane & BIT;
+  const unsigned long long keep = up ? q : p, give = up ? p : q;
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)give, DPP, 0xF, 0xF, false);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)(give >> 32), DPP, 0xF, 0xF, false);
+  const unsigned long long got = ((unsigned long long)hi << 32) | lo;
+  return got < keep ? got : keep;
+}
+// A lane holds a key for each of 32 rows (a, v), a < 2, v < 16, and the 32 lanes of its half share the rows.  Reducing row
+// by row takes five exchanges of a 64-bit key per row, 160 in all, each through LDS.  Here the rows are shared out on
+// the way (reduce-scatter): a step halves the rows a lane is responsible for, so 16 + 8 + 4 + 2 + 1 exchanges do, on
+// the row swap and the lane moves of the vector unit; lane (r32, kh) ends with the smallest key of the row
+// (a, v) = (r32 >> 4, r32 & 15) of its half.
+template <class F>
+__device__ inline unsigned long long reduce_rows32(F key_of, int lane) {
+  unsigned long long k8[8];
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {   // rows v = h and h + 8: lane bit 4 takes a, lane bit 3 takes bit 3 of v
+    unsigned long long k16[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const unsigned long long p = key_of(0, h + 8 * u), q = key_of(1, h + 8 * u);
+      // rows of 16 lanes: (p0 p1), (q0 q1) -> (p0 q0), (p1 q1)
+      const auto lo = __builtin_amdgcn_permlane16_swap((unsigned int)p, (unsigned int)q, false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap((unsigned int)(p >> 32), (unsigned int)(q >> 32), false, false);
+      const unsigned long long x = ((unsigned long long)hi[0] << 32) | lo[0], y = ((unsigned long long)hi[1] << 32) | lo[1];
+      k16[u] = x < y ? x : y;
+    }
+    k8[h] = halve_min<0x128, 8>(k16[0], k16[1], lane);   // row_ror:8
+  }
+  unsigned long long k4[4];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) k4[h] = halve_min<0x141, 4>(k8[h], k8[h + 4], lane);   // row_half_mirror
+  const unsigned long long k2a = halve_min<0x4E, 2>(k4[0], k4[2], lane);             // quad_perm [2,3,0,1]
+  const unsigned long long k2b = halve_min<0x4E, 2>(k4[1], k4[3], lane);
+  return halve_min<0xB1, 1>(k2a, k2b, lane);                                         // quad_perm [1,0,3,2]
+}
+#endif
+
 // Error reporting shared by the translation units that hold entry points: records the text skm_last_error() returns
 // on this thread and gives back the code (SKM_ENOMEM for an out-of-memory HIP error, SKM_EHIP for any other).
 int report_error(int rc, const char *what);
@@ -115,8 +158,9 @@ constexpr int kStatReplicas = 32;
 // fill counter (counters are kSubListStride words apart).
 constexpr int kSubLists = 8;
 constexpr int kSubListStride = 16;
+constexpr int kListCols = 256;   // columns of a tile of listed centroids
 
-// Progressive-pruning GEMM (Algorithm 1, iterations >= 2): a 128 x 128 tile is multiplied densely over
+// Progressive-pruning GEMM (Algorithm 1, iterations >= 2): a 128 x 256 tile is multiplied densely over
 // d', d'+64, d'+128, ... dimensions; after each step the pairs whose partial distance exceeds
 // theta(t, tau_i) die; the tile stops when nothing is alive, hands its pairs to the gather kernel when
 // at most emit_max are alive, and offers finished distances below tau_i to best[] at t = d.
@@ -154,18 +198,26 @@ struct ProgArgs {
   unsigned long long *best;       // [n] packed (distance, centroid)
   unsigned long long *scal;       // [kStatReplicas][SC_COUNT] step scalars (SC_SURVIVORS, SC_COMPLETED, SC_DENSE_*, SC_ENTER..)
   int32_t block_stats;            // also count pairs entering every trailing block (SC_ENTER + m)
-  // Listed columns (after launch_screen; all NULL otherwise): tile t is row tile tile_rt[t] against the 128 centroids
-  // col_list[128 t ..] (ascending ids, -1 = none); *ntiles tiles in all.
+  // Listed columns (after launch_screen; all NULL otherwise): tile t is row tile tile_rt[t] against the 256 centroids
+  // col_list[256 t ..] (ascending ids, -1 = none); *ntiles tiles in all.
   const int32_t *tile_rt = nullptr, *col_list = nullptr, *ntiles = nullptr;
+  // Listed columns only: one product and widened tests behind the first test (deep = 1).  Ah / Bh: the planes of hi
+  // halves; widen[m] = (widening per unit of the row's norm behind d', guard) of checkpoint m.  A tile hands over at
+  // the first test with at most emit_first pairs alive, later with at most emit_deep; one with more than deep_max alive
+  // at the first test takes three products throughout.
+  int32_t deep = 0;
+  const uint32_t *Ah = nullptr, *Bh = nullptr;
+  const float2 *widen = nullptr;
+  unsigned int emit_first = 0, emit_deep = 0, deep_max = 0;
   stamp_t *stamp = nullptr;
 };
 hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
 
 // Low-precision first filter (screen.hip): one fp16 product on the first d' dimensions and the first test
 // theta(d', tau) widened by the error bound of the dropped halves; then, per row tile of 128 points, the centroids
-// that some point of the tile may still pass, as an ascending id list padded with -1 to a multiple of 128.
-// Outputs: cnt[row tiles], first[row tiles] (first tile of 128 listed columns of every row tile), *ntiles,
-// col_list[128 * ntiles], tile_rt[ntiles]; capacity needed: one tile per (row tile, column tile) of the full problem.
+// that some point of the tile may still pass, as an ascending id list padded with -1 to a multiple of 256.
+// Outputs: cnt[row tiles], first[row tiles] (first tile of 256 listed columns of every row tile), *ntiles,
+// col_list[256 * ntiles], tile_rt[ntiles]; capacity needed: one tile per (row tile, column tile) of the full problem.
 struct ScreenLaunch {
   const uint32_t *A; int64_t lda; int32_t M;
   const uint32_t *B; int64_t ldb; int32_t N;
@@ -177,6 +229,9 @@ struct ScreenLaunch {
   const float *xn;           // [n] ||x_i[0 : d')||^2, indexed like tau
   const float *yn;           // [N] ||y_j[0 : d')||^2
   float *arow, *ycol;        // scratch: [M] and [N] (the test's per-point and per-centroid terms)
+  const float *ynp = nullptr;   // (first test) [nb + 1][N] prefix norms of the centroids, row 0 = yn; with it widen[0 .. nb]
+  int32_t nb = 0;               // receives the terms of the later, widened tests (ProgArgs)
+  float2 *widen = nullptr;
   uint32_t *colmask;         // scratch: [row tiles][4 * column tiles]
   int32_t *cnt, *first, *ntiles, *col_list, *tile_rt;   // (ntiles: two words, the second is scratch)
   unsigned int *tile_counter;   // (unused)
@@ -213,7 +268,6 @@ struct NeighbourLaunch {
 hipError_t launch_neighbour_screen(const NeighbourLaunch &a, bool groups, hipStream_t st);
 int64_t progressive_tiles(int64_t rows, int32_t k);
 int32_t progressive_tile_pairs();
-int32_t progressive_tile_cols();
 
 // ---------------------------------------------------------------- pruning
 struct PruneArgs {
@@ -228,6 +282,7 @@ struct PruneArgs {
   int32_t dprime;
   int32_t ds;            // padded row length (multiple of 16)
   int32_t nb;            // trailing blocks
+  const float *Y;        // rotated centroids, row stride ds: the first d' dimensions of a pair that starts over (p < 0)
   const float *ratio;    // [nb + 1] theta ratio at checkpoint m, t_m = min(d, d' + 64 m) (device array)
   unsigned long long *best;        // [n] packed (distance, centroid)
   unsigned long long *scal;        // [kStatReplicas][SC_COUNT]: SC_COMPLETED, SC_GATHER_*, and SC_ENTER + m when block_stats
