@@ -672,10 +672,10 @@ struct Ctx {
     sub_cap = ((tiles_chunk + kSubLists - 1) / kSubLists) * per_tile;
     // the filtered iteration 1 lists a few candidates per point in the same list (if it ever overflows, the step is
     // redone with the full GEMM): room for 16 per point of a chunk in each of the eight parts
-    // (the kernels behind the filter address a listed centroid's row with 32-bit offsets: not for a centroid table of
-    // 2^31 words or more, where the steps simply run unfiltered)
+    // (the kernels behind the filter address a listed centroid's row with 32-bit byte offsets: not for a centroid table
+    // of 2^30 words or more, where the steps simply run unfiltered)
     const bool may_screen = (screen_mode > 0 || (screen_mode == 0 && k >= 256)) &&
-                            (int64_t)k * (ds + 32) < ((int64_t)1 << 31);
+                            (int64_t)k * (ds + 32) < ((int64_t)1 << 30);
     if (may_screen) sub_cap = std::max<int64_t>(sub_cap, 16 * std::min<int64_t>(chunk_rows, n));
     pair_cap = sub_cap * kSubLists;
     if (pair_cap >= ((int64_t)1 << 32)) return fail(SKM_EINVAL, "pair_budget too large (must stay below 2^32 pairs)");
@@ -1143,7 +1143,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.yn = c.ynp;
       // Behind the first test of a listed tile one product and widened tests will do where the gather kernel finishes
       // what is left (not where every test's count is asked for, nor with a hand-over share beyond an eighth).
-      const bool deep = !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
+      const bool deep = nb >= 3 && !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
       if (deep) { sl.ynp = c.ynp; sl.nb = nb; sl.widen = c.scr_widen; }
       sl.arow = c.scr_arow; sl.ycol = c.scr_ycol;
       sl.colmask = c.colmask; sl.cnt = c.scr_cnt; sl.first = c.scr_first; sl.ntiles = c.scr_ntiles;
@@ -1157,7 +1157,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
         g.deep = 1;
         g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
         g.emit_first = c.emit_max * 5 / 8;
-        g.emit_deep = c.emit_max / 8;
+        g.emit_deep = 48;
+        g.deep_stride = 2;
         g.deep_max = (unsigned int)progressive_tile_pairs() / 4;
       }
     }

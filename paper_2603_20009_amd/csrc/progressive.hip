@@ -97,6 +97,13 @@ constexpr int A_LD = BM / ROWS_PASS;                // 2 load instructions per t
     asm volatile("" : : : "memory");                              \
   } while (0)
 
+// the same pointer in scalar registers (it is uniform, which the compiler cannot always tell)
+__device__ inline const char *uniform_ptr(const void *p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return reinterpret_cast<const char *>((hi << 32) | lo);
+}
+
 // Sum over the 64 lanes of a wavefront through the data-parallel lane moves: within quads, mirrored
 // within half rows and rows, then the row totals handed on to the following rows; lane 63 ends with the result.
 #define SKM_WAVE_REDUCE(v, OP)                                                                \
@@ -184,8 +191,8 @@ __device__ inline void unit_one(acc_t<NB> &acc, const uint32_t *Ab, const uint32
 // Listed tiles (g.deep): the first test is exact (three products over d' dimensions: the survivors of the first test are
 // counted there).  What follows only has to find the few pairs that can reach the end: one product per dimension
 // (a third of the matrix work), and the tests widened by its error bound (screen.hip) over the dimensions behind d'.  A
-// pair that passes the exact tests passes the widened ones.  Once few pairs are left, or at the end, they go to the
-// gather kernel, which starts them from dimension 0 again and applies the exact tests (p < 0 marks them): labels,
+// pair that passes the exact tests passes the widened ones.  Once few pairs are left, or at the last test, they go to
+// the gather kernel, which starts them from dimension 0 again and applies the exact tests (p < 0 marks them): labels,
 // distances and counts are those of the exact tests.  A tile most of whose pairs survive the first test, or that ends
 // with more pairs than it may hand over, is done in three products throughout.
 template <bool LISTED, int NB>
@@ -244,14 +251,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
   // Staging: load instruction j of wavefront w moves tile rows 64 j + 16 w .. + 15 of a unit.
   const int ld_row = 16 * wave + (lane >> 2);                       // + 64 j
-  const int ld_piece = 4 * ((lane & 3) ^ ((ld_row >> 2) & 3));      // word offset of the piece that belongs at this lane's position
+  const unsigned int ld_piece = 16u * ((lane & 3) ^ ((ld_row >> 2) & 3));   // byte offset of the piece that belongs at this lane's position
   const int ldh = g.ds / 2 + 16;
 
   // ---- the tile being loaded.  Rows past the end repeat the last one (their accumulator elements start dead).
-  int arow[A_LD], brow[B_LD];               // tile rows (relative to its first) and centroid rows of this lane's pieces
+  // byte offsets of this lane's rows from the tile's first row / the first row of the tile's columns (three-product copy)
+  unsigned int offA[A_LD], offB[B_LD];
   float tau_reg = 0.f;
   int prev_reg = -1;
-  const uint32_t *baseA = g.A, *baseAh = g.Ah;   // first row of the tile (uniform)
+  const uint32_t *baseA = g.A, *baseAh = g.Ah, *baseB = g.B;   // first rows (uniform)
   const float *nx = g.xnp, *ny = g.ynp;     // prefix norms of row tid & 127 and of column tid
   float nxreg = 0.f, nyreg = 0.f, rreg = 0.f;
   float2 wreg = make_float2(0.f, 0.f);
@@ -271,17 +279,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (LISTED && g.deep) baseAh = g.Ah + (int64_t)row0 * ldh;
     const int limA = g.M - 1 - row0;
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j) arow[j] = min(ld_row + ROWS_PASS * j, limA);
+    for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda) * 4u;
     nx = g.xnp + g.row_base + row0 + min(tid & (BM - 1), limA);
     if constexpr (LISTED) {
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) brow[j] = max(ids[j], 0);
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(ids[j], 0) * (unsigned int)g.ldb * 4u;   // (the launcher checks the range)
       ny = g.ynp + max(cid_reg, 0);
     } else {
-      const int col0 = ct * BN, limB = g.N - 1;
+      const int col0 = ct * BN, limB = g.N - 1 - col0;
+      baseB = g.B + (int64_t)col0 * g.ldb;
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) brow[j] = min(col0 + ld_row + ROWS_PASS * j, limB);
-      ny = g.ynp + min(col0 + tid, limB);
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u;
+      ny = g.ynp + col0 + min(tid, limB);
     }
     const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
     tau_reg = g.tau[g.row_base + gr];
@@ -290,16 +299,26 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // unit starting at dimension t of the aimed tile -> LDS stage (asynchronous)
   auto request = [&](int t, bool one, int stage) {
     uint32_t *sb = smem + stage * STAGE_WORDS + 16 * wave * ROW_WORDS;
-    const uint32_t *pa = LISTED && one ? baseAh : baseA, *pb = LISTED && one ? g.Bh : g.B;
-    const int ld = LISTED && one ? ldh : (int)g.lda, at = (LISTED && one ? 8 + t / 2 : 16 + t) + ld_piece;
+    // (uniform bases and 32-bit byte offsets: the address of a load is its offset register.  A row of the one-product copy
+    // is half as long as one of the three-product copy)
+    const bool o = LISTED && one;
+    const char *pa = uniform_ptr((o ? baseAh : baseA) + (o ? 8 + t / 2 : 16 + t));
+    const char *pb = uniform_ptr((o ? g.Bh : baseB) + (o ? 8 + t / 2 : 16 + t));
+    const int sh = o ? 1 : 0;
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + (unsigned int)(arow[j] * ld + at)),
+    for (int j = 0; j < A_LD; ++j) {
+      unsigned int off = (offA[j] >> sh) + ld_piece;
+      asm("" : "+v"(off));   // (kept apart from the base)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + off),
                                        (__attribute__((address_space(3))) void *)(sb + ROWS_PASS * j * ROW_WORDS), 16, 0, 0);
+    }
 #pragma unroll
-    for (int j = 0; j < B_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + ((uint64_t)(uint32_t)brow[j] * (uint32_t)ld + (uint32_t)at)),
+    for (int j = 0; j < B_LD; ++j) {
+      unsigned int off = (offB[j] >> sh) + ld_piece;
+      asm("" : "+v"(off));
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + off),
                                        (__attribute__((address_space(3))) void *)(sb + (BM + ROWS_PASS * j) * ROW_WORDS), 16, 0, 0);
+    }
   };
   // Checkpoint m's prefix norms (the points' table has a row per 16 dimensions, the centroids' a row per checkpoint of
   // this step), theta ratio and, for the widened tests, the largest centroid norms.
@@ -403,8 +422,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       if constexpr (LISTED) gc[b] = s_cid[cl];
       else gc[b] = col0 + cl < g.N ? col0 + cl : 0x7fffffff;
     }
-    // one alive-bit per accumulator element: word a, bit 16 b + v
+    // one alive-bit per accumulator element: word a, bit 16 b + v.  (Listed tiles instead set a dead element to kDead,
+    // which no test passes and no product changes, and make the bits when they hand over.)
     unsigned int bits[TM];
+    constexpr float kDead = -3.0e38f;
     auto first_bits = [&]() {
       const uint4 dead = *reinterpret_cast<const uint4 *>(&s_dead[tid * 4]);
       bits[0] = ~dead.x; bits[1] = ~dead.y; bits[2] = ~dead.z; bits[3] = ~dead.w;
@@ -421,7 +442,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     };
     const bool wide = NB > 1 && (LISTED ? s_cid[128 * (NB - 1)] < g.N : g.N - col0 > 128);   // more than 128 columns
     first_bits();
-    if (!LISTED) {
+    if constexpr (LISTED) {
+      if (__ballot((bits[0] & bits[1] & bits[2] & bits[3]) != 0xffffffffu)) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              if (!((bits[a] >> (16 * b + v)) & 1u)) acc[a][b][v] = kDead;
+      }
+    } else {
 #pragma unroll
       for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
     }
@@ -435,7 +466,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int t = 0;                     // dimensions multiplied
     int m = 0;                     // next checkpoint, at dimension tcp
     int tcp = g.dprime;
-    int ncp = 0;                   // checkpoints seen (row of s_wcnt)
+    int ncp = 0;                   // exchanges so far (row of s_wcnt)
+    // in one product a test every deep_stride blocks will do, the last one is the last test there is
+    auto after = [&](int mm) { return LISTED && deep ? min(mm + g.deep_stride, g.nb - 1) : mm + 1; };
+    const int tend = LISTED && deep ? g.dprime + kBlockDims * (g.nb - 1) : g.ds;   // dimensions that may be needed
     unsigned int dims3 = 0, dims1 = 0;
     // Units until the tile ends (0), goes on in one product (1) or has to be done again in three (2); kind: one product
     // or three, a constant.  (Two loops rather than one with both kinds of unit: the accumulators of a loop with two
@@ -452,7 +486,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // the unit has arrived once at most the unit requested after it is outstanding (loads are counted in order)
       if (treq > t + step) SKM_VMCNT(A_LD + B_LD);
       else SKM_VMCNT(0);
-      const bool cp = t + step >= tcp, last = t + step >= g.ds;
+      const bool cp = t + step >= tcp, last = !one && t + step >= g.ds;
       if (cp) {
         // the prefix norms fetched one checkpoint ago -> LDS, with the row's threshold theta(t_m, tau) - ||x_t||^2
         if (tid < BM) {
@@ -466,8 +500,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         if (NB > 1 || tid < BN) s_yn[tid] = nyreg;
       }
       SKM_BARRIER();   // everyone's share of the unit is there, and the stage before it is free
-      if (cp) load_norm(m + 1);
-      if (treq < g.ds) {
+      if (cp) load_norm(after(m));
+      if (treq < tend) {
         const bool o = LISTED && deep && treq >= g.dprime;
         request(treq, o, cur == 0 ? NSTAGE - 1 : cur - 1);
         treq += o ? 32 : 16;
@@ -486,44 +520,97 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 #pragma unroll
       for (int b = 0; b < TN; ++b) yn[b] = s_yn[(b * 4 + wave) * 32 + r32];
-      if (!last || g.nb == 0) {
-        // test theta(t_m, tau_i): drop the pair when its partial distance exceeds it.  The sign of threshold minus
-        // distance is the verdict (a difference of two floats is negative exactly when the second is larger); the
-        // signs of the 32 elements of an accumulator row block are shifted into one word, last element first, one
-        // funnel shift each.
+      auto row_thresholds = [&](int a, float (&thr)[16]) {
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+          const float4 f = *reinterpret_cast<const float4 *>(&s_thr[a * 32 + 8 * v4 + 4 * kh]);
+          thr[4 * v4] = f.x; thr[4 * v4 + 1] = f.y; thr[4 * v4 + 2] = f.z; thr[4 * v4 + 3] = f.w;
+        }
+      };
+      // the four wavefronts' numbers added up (the next exchange goes through the other row: a wavefront that is already
+      // there cannot disturb this read)
+      auto tile_sum = [&](int mine) {
+        if (lane == 0) s_wcnt[ncp & 1][wave] = (unsigned int)mine;
+        SKM_BARRIER();
+        const uint4 wc = *reinterpret_cast<const uint4 *>(s_wcnt[ncp & 1]);
+        ++ncp;
+        return (unsigned int)__builtin_amdgcn_readfirstlane(wc.x + wc.y + wc.z + wc.w);
+      };
+      // Test theta(t_m, tau_i): drop the pair when its partial distance exceeds it.
+      if constexpr (one) {
+        // Is anything left?  Per lane and column the smallest distance minus threshold over its 64 rows, a fused
+        // multiply and half a minimum per element; the pairs themselves are told apart only once few columns are left.
+        int cols = 0;
+        float least[TN];
+#pragma unroll
+        for (int b = 0; b < TN; ++b) least[b] = 3.0e38f;
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
-          unsigned int dropped = 0u;
           float thr[16];
+          row_thresholds(a, thr);
 #pragma unroll
-          for (int v4 = 0; v4 < 4; ++v4) {
-            const float4 f = *reinterpret_cast<const float4 *>(&s_thr[a * 32 + 8 * v4 + 4 * kh]);
-            thr[4 * v4] = f.x; thr[4 * v4 + 1] = f.y; thr[4 * v4 + 2] = f.z; thr[4 * v4 + 3] = f.w;
-          }
+          for (int b = 0; b < TN; ++b)
 #pragma unroll
-          for (int b = TN - 1; b >= 0; --b)
-#pragma unroll
-            for (int v = 15; v >= 0; --v) {
-              const float margin = thr[v] - fmaf(m2, acc[a][b][v], yn[b]);
-              dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
-            }
-          bits[a] &= ~dropped;
+            for (int v = 0; v < 16; v += 2)
+              least[b] = fminf(fminf(least[b], fmaf(m2, acc[a][b][v], -thr[v])), fmaf(m2, acc[a][b][v + 1], -thr[v + 1]));
         }
-        static_assert(TN * 16 <= 32, "one word per accumulator row block");
+#pragma unroll
+        for (int b = 0; b < TN; ++b) cols += __popcll(__ballot(least[b] <= -yn[b]));
+        const unsigned int left = tile_sum(cols);
+        if (left == 0u) return 0;
+        const bool stop = m >= g.nb - 1;   // (the last test there is)
+        if (!stop && left > g.emit_deep) {
+          m = after(m);
+          tcp = min(g.dprime + kBlockDims * m, g.ds);
+          continue;
+        }
       }
-      // alive pairs of this wavefront and of the whole tile
-      wave_alive = wave_sum_i32(__popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]));
-      if (lane == 0) s_wcnt[ncp & 1][wave] = (unsigned int)wave_alive;
-      SKM_BARRIER();
-      // (the next checkpoint's counts go to the other row: a wavefront that is already there cannot disturb this read)
-      const uint4 wc = *reinterpret_cast<const uint4 *>(s_wcnt[ncp & 1]);
-      ++ncp;
-      const unsigned int total = __builtin_amdgcn_readfirstlane(wc.x + wc.y + wc.z + wc.w);
-      // behind the first test a widened tile hands over once few pairs are left (their way starts again at dimension 0),
-      // and at the end; otherwise a tile that is sparse does
-      const unsigned int limit = LISTED && deep ? (m == 0 ? g.emit_first : (last ? g.emit_max : g.emit_deep)) : g.emit_max;
-      const bool redo = LISTED && deep && (m == 0 ? total > g.deep_max : last && total > g.emit_max);
-      const bool hand = total != 0u && total <= limit && (!last || one) && !redo;
+      if constexpr (LISTED && !one) {
+        // (a count per wavefront on the scalar unit, the verdict as the element's value)
+        if (!last) {
+          wave_alive = 0;
+#pragma unroll
+          for (int a = 0; a < TM; ++a) {
+            float thr[16];
+            row_thresholds(a, thr);
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const bool alive = fmaf(m2, acc[a][b][v], yn[b]) <= thr[v];
+                acc[a][b][v] = alive ? acc[a][b][v] : kDead;
+                wave_alive += __popcll(__ballot(alive));
+              }
+          }
+        }
+      } else {
+        // The sign of threshold minus distance is the verdict (a difference of two floats is negative exactly when the
+        // second is larger); the signs of the 32 elements of an accumulator row block are shifted into one word, last
+        // element first, one funnel shift each.
+        if (!last || g.nb == 0) {
+#pragma unroll
+          for (int a = 0; a < TM; ++a) {
+            unsigned int dropped = 0u;
+            float thr[16];
+            row_thresholds(a, thr);
+#pragma unroll
+            for (int b = TN - 1; b >= 0; --b)
+#pragma unroll
+              for (int v = 15; v >= 0; --v) {
+                const float margin = thr[v] - fmaf(m2, acc[a][b][v], yn[b]);
+                dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
+              }
+            if (LISTED) bits[a] = ~dropped;
+            else bits[a] &= ~dropped;
+          }
+          static_assert(TN * 16 <= 32, "one word per accumulator row block");
+        }
+        wave_alive = wave_sum_i32(__popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]));
+      }
+      const unsigned int total = tile_sum(wave_alive);
+      // a tile that is sparse hands over; in one product, whose pairs start again at dimension 0, once few columns are left
+      const bool redo = LISTED && deep && (one ? m >= g.nb - 1 && total > g.emit_max : m == 0 && total > g.deep_max);
+      const bool hand = total != 0u && !last && !redo && total <= (LISTED && !one && deep ? g.emit_first : g.emit_max);
       if (tid == 0) {
         // a tile that hands its pairs over reserves their slots now (one reservation per tile in the sub-list of
         // this workgroup's XCD): the answer is not needed before the next tile's loads have been requested
@@ -531,7 +618,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         if (total) {
           if (m == 0 && !redone) atomicAdd(sc + SC_SURVIVORS, (unsigned long long)total);
           if (!last && g.block_stats) atomicAdd(sc + SC_ENTER + m, (unsigned long long)total);
-          if (last && !hand && !redo) atomicAdd(sc + SC_COMPLETED, (unsigned long long)total);
+          if (last) atomicAdd(sc + SC_COMPLETED, (unsigned long long)total);
           if (!last && !hand && !redo) atomicAdd(sc + SC_DENSE_PB, (unsigned long long)total);   // the next block of these pairs is done densely
         }
       }
@@ -547,7 +634,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         fin_m = m;
         return 0;
       }
-      ++m;
+      m = after(m);
       tcp = min(g.dprime + kBlockDims * m, g.ds);
       if (LISTED && !one && deep) return 1;   // behind the first test
     }
@@ -625,6 +712,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         // element behind a bit is found through LDS, where the lane parks its 16 values of a block (a register
         // cannot be chosen per lane): the stage the last unit was read from is free, 4 KB per wavefront as [16][64].
         // List slots: the wavefront's range, then lane by lane (prefix sum of the lanes' counts), then bit by bit.
+        if (LISTED && !(deep && fin_m > 0)) {   // (in one product the last test has made the bits)
+#pragma unroll
+          for (int a = 0; a < TM; ++a) {
+            unsigned int dead = 0u;
+#pragma unroll
+            for (int b = TN - 1; b >= 0; --b)
+#pragma unroll
+              for (int v = 15; v >= 0; --v)
+                dead = __builtin_amdgcn_alignbit(dead, __builtin_bit_cast(unsigned int, acc[a][b][v] - 0.5f * kDead), 31);
+            bits[a] = ~dead;
+          }
+        }
         int upto = __popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]);
         const int mine = upto;
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, false);   // row_shr:1
@@ -715,9 +814,10 @@ hipError_t launch_progressive(const ProgArgs &args, hipStream_t st) {
   static const Setup setup;
   if (setup.rc != hipSuccess) return setup.rc;
   const int wgs = setup.wgs;
+  if (g.col_list && (int64_t)g.N * g.ldb >= ((int64_t)1 << 30)) return hipErrorInvalidValue;   // (32-bit byte offsets)
   if ((g.col_list != nullptr) != (g.tile_rt != nullptr) || (g.col_list != nullptr) != (g.ntiles != nullptr))
     return hipErrorInvalidValue;
-  if (g.deep && (!g.col_list || !g.Ah || !g.Bh || !g.widen || (reinterpret_cast<uintptr_t>(g.Ah) & 15u) ||
+  if (g.deep && (g.nb < 3 || g.deep_stride < 1 || !g.col_list || !g.Ah || !g.Bh || !g.widen || (reinterpret_cast<uintptr_t>(g.Ah) & 15u) ||
                  (reinterpret_cast<uintptr_t>(g.Bh) & 15u)))
     return hipErrorInvalidValue;
   // Tiles of 128 columns where tiles of 256 would give a CU fewer than eight: what the last round leaves idle then costs

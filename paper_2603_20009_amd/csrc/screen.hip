@@ -472,17 +472,30 @@ __global__ void __launch_bounds__(1024) mask_scan_kernel(const int32_t *cnt, int
   if ((tid & 63) == 0 && listed) atomicAdd(scal + SC_LISTED_TILES, (unsigned long long)listed);   // (in tiles of 128)
 }
 
-// One workgroup per row tile: the ids of its set bits in ascending order, padded with -1 to a multiple of kListCols,
-// into col_list[kListCols * first[rt] ...]; tile_rt[t] = rt for each of its tiles.
-__global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, int32_t maskw, const int32_t *cnt,
+// One workgroup per row tile: the ids of its set bits in ascending order, padded with -1 to a multiple of kListCols, one
+// tile of kListCols after the other.  Tiles are placed so that the tiles in work at a time share rows and centroids:
+// kListGroup row tiles together, tile 0 of each, then tile 1 of each, ... (all lists ascend, so the c-th tiles of two row
+// tiles name mostly the same centroids).  Row tile after row tile every centroid came from outside the XCD's L2 once per
+// row tile: 5.4 TB/s of misses in an assignment of 2.5M x 384 to 32768 centroids.
+__global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, int32_t nrt, int32_t maskw, const int32_t *cnt,
                                                         const int32_t *first, int32_t *col_list, int32_t *tile_rt) {
   __shared__ int s_wave[4];
   __shared__ int s_base;
   const int rt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int total = cnt[rt];
-  const int t0 = first[rt], nt = (total + kListCols - 1) / kListCols;
-  int32_t *out = col_list + (int64_t)t0 * kListCols;
+  const int nt = (total + kListCols - 1) / kListCols;
+  const int g0 = rt / kListGroup * kListGroup;
+  int others[kListGroup];   // tiles of the group's row tiles
+#pragma unroll
+  for (int r = 0; r < kListGroup; ++r) others[r] = g0 + r < nrt ? (cnt[g0 + r] + kListCols - 1) / kListCols : 0;
+  const int start = first[g0];
+  auto place = [&](int c) {   // of tile c of this row tile
+    int p = start;
+#pragma unroll
+    for (int r = 0; r < kListGroup; ++r) p += min(others[r], c) + (g0 + r < rt && others[r] > c ? 1 : 0);
+    return p;
+  };
   if (tid == 0) s_base = 0;
   __syncthreads();
   for (int w0 = 0; w0 < maskw; w0 += 256) {
@@ -499,17 +512,27 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     __syncthreads();
     int pos = s_base + incl - mine;
     for (int ww = 0; ww < wave; ++ww) pos += s_wave[ww];
+    int at = -1;
+    int32_t *out = nullptr;
     while (bits) {
       const int b = __builtin_ctz(bits);
       bits &= bits - 1u;
-      out[pos++] = w * 32 + b;
+      if (pos / kListCols != at) {
+        at = pos / kListCols;
+        out = col_list + (int64_t)place(at) * kListCols;
+      }
+      out[pos % kListCols] = w * 32 + b;
+      ++pos;
     }
     __syncthreads();
     if (tid == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
     __syncthreads();
   }
-  for (int p = total + tid; p < nt * kListCols; p += 256) out[p] = -1;
-  for (int t = tid; t < nt; t += 256) tile_rt[t0 + t] = rt;
+  if (nt > 0) {
+    int32_t *out = col_list + (int64_t)place(nt - 1) * kListCols;
+    for (int p = total - (nt - 1) * kListCols + tid; p < kListCols; p += 256) out[p] = -1;
+  }
+  for (int t = tid; t < nt; t += 256) tile_rt[place(t)] = rt;
 }
 
 // The test of a pair, theta + widening - ||x'||^2 >= ||y'||^2 - 2 x'.y', in accumulator units (the accumulator holds
@@ -670,7 +693,7 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)((nrt + 3) / 4)), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt);
   hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(1024), 0, st, a.cnt, nrt, a.first, a.ntiles, a.scal);
-  hipLaunchKernelGGL(mask_fill_kernel, dim3((unsigned)nrt), dim3(256), 0, st, a.colmask, 4 * nct, a.cnt, a.first,
+  hipLaunchKernelGGL(mask_fill_kernel, dim3((unsigned)nrt), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt, a.first,
                      a.col_list, a.tile_rt);
   return hipGetLastError();
 }

@@ -159,6 +159,7 @@ constexpr int kStatReplicas = 32;
 constexpr int kSubLists = 8;
 constexpr int kSubListStride = 16;
 constexpr int kListCols = 256;   // columns of a tile of listed centroids
+constexpr int kListGroup = 8;    // row tiles whose listed tiles are placed in turn
 
 // Progressive-pruning GEMM (Algorithm 1, iterations >= 2): a 128 x 256 tile is multiplied densely over
 // d', d'+64, d'+128, ... dimensions; after each step the pairs whose partial distance exceeds
@@ -203,12 +204,14 @@ struct ProgArgs {
   const int32_t *tile_rt = nullptr, *col_list = nullptr, *ntiles = nullptr;
   // Listed columns only: one product and widened tests behind the first test (deep = 1).  Ah / Bh: the planes of hi
   // halves; widen[m] = (widening per unit of the row's norm behind d', guard) of checkpoint m.  A tile hands over at
-  // the first test with at most emit_first pairs alive, later with at most emit_deep; one with more than deep_max alive
-  // at the first test takes three products throughout.
+  // the first test with at most emit_first pairs alive, later with at most emit_deep columns (of half a tile's rows) that
+  // hold any; one with more than deep_max pairs alive at the first test takes three products throughout.  A test every
+  // deep_stride blocks.
   int32_t deep = 0;
   const uint32_t *Ah = nullptr, *Bh = nullptr;
   const float2 *widen = nullptr;
   unsigned int emit_first = 0, emit_deep = 0, deep_max = 0;
+  int32_t deep_stride = 1;
   stamp_t *stamp = nullptr;
 };
 hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
@@ -216,7 +219,7 @@ hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
 // Low-precision first filter (screen.hip): one fp16 product on the first d' dimensions and the first test
 // theta(d', tau) widened by the error bound of the dropped halves; then, per row tile of 128 points, the centroids
 // that some point of the tile may still pass, as an ascending id list padded with -1 to a multiple of 256.
-// Outputs: cnt[row tiles], first[row tiles] (first tile of 256 listed columns of every row tile), *ntiles,
+// Outputs: cnt[row tiles], first[row tiles] (tiles of 256 listed columns before every row tile), *ntiles,
 // col_list[256 * ntiles], tile_rt[ntiles]; capacity needed: one tile per (row tile, column tile) of the full problem.
 struct ScreenLaunch {
   const uint32_t *A; int64_t lda; int32_t M;
