@@ -562,7 +562,8 @@ struct Ctx {
   int32_t pruned_steps = 0;                // pruned steps this context has completed
   bool exact_filter_off = false;           // iteration 1 takes the full GEMM (set after a candidate-list overflow)
   float2 *scr_widen = nullptr;
-  int32_t *scr_cnt = nullptr, *scr_first = nullptr, *scr_ntiles = nullptr, *scr_cols = nullptr, *scr_tile_rt = nullptr;
+  int32_t *scr_cnt = nullptr, *scr_first = nullptr, *scr_ntiles = nullptr, *scr_cols = nullptr, *scr_pos = nullptr;
+  int2 *scr_tile_rt = nullptr;
   unsigned int *amax = nullptr;      // [AM_COUNT] magnitude bounds of the GEMM operands
   enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8 };
 
@@ -695,6 +696,7 @@ struct Ctx {
       HIPCHK(pool.get(&scr_cols, (size_t)tiles_chunk * kListCols));
       HIPCHK(pool.get(&scr_widen, (size_t)kMaxBlocks + 1));
       HIPCHK(pool.get(&scr_tile_rt, (size_t)tiles_chunk));
+      HIPCHK(pool.get(&scr_pos, (size_t)n));
     }
     // everything a step clears at its start is one block: counters | flag | ticket | step scalars | cluster sizes
     {
@@ -1147,18 +1149,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       if (deep) { sl.ynp = c.ynp; sl.nb = nb; sl.widen = c.scr_widen; }
       sl.arow = c.scr_arow; sl.ycol = c.scr_ycol;
       sl.colmask = c.colmask; sl.cnt = c.scr_cnt; sl.first = c.scr_first; sl.ntiles = c.scr_ntiles;
-      sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt;
+      sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt; sl.prev = c.prev; sl.list_pos = c.scr_pos;
       sl.tile_counter = c.counters + ((size_t)c.nchunks * (kSubLists + 8) + (size_t)ch * 8) * kSubListStride;
       sl.scal = c.scal;
       sl.stamp = border;
       HIPCHK(launch_screen(sl, c.st));
-      g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles;
+      g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles; g.prev = c.scr_pos;
       if (deep) {
         g.deep = 1;
         g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
-        g.emit_first = c.emit_max * 5 / 8;
-        g.emit_deep = 48;
-        g.deep_stride = 2;
+        g.emit_first = c.emit_max * 5 / 16;
+        g.emit_deep = 24;
+        g.deep_stride = 3;
         g.deep_max = (unsigned int)progressive_tile_pairs() / 4;
       }
     }

@@ -202,9 +202,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   static_assert(!LISTED || BN == kListCols, "a tile of listed columns");
   extern __shared__ __align__(16) uint32_t smem[];   // [NSTAGE][A: BM rows | B: BN rows][ROW_WORDS]
   // (two copies of the thresholds by tile parity: the previous tile may still be handing pairs over while the next is
-  // committed; a listed tile's commit has a barrier that settles this)
-  __shared__ __align__(16) float s_tau[LISTED ? 1 : 2][BM], s_thr[BM], s_xn[BM], s_yn[BN];
-  __shared__ int s_cid[LISTED ? BN : 1];             // listed columns: the centroid ids of the tile (INT_MAX = none)
+  // committed)
+  __shared__ __align__(16) float s_tau[2][BM], s_thr[BM], s_xn[BM], s_yn[BN];
   __shared__ unsigned int s_dead[NT * 4];            // per thread: accumulator elements that start dead (the incumbent)
   __shared__ __align__(16) unsigned int s_wcnt[2][4];   // alive pairs of every wavefront at the last checkpoint (by checkpoint parity)
   __shared__ unsigned int s_base;         // first list slot of a tile that hands its pairs over
@@ -234,8 +233,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int panel_sz = PC * nrt;
   auto tile_rc = [&](int q, int &rt, int &ct) {   // q-th tile of this XCD -> (row tile, column tile)
     const int logical = xstart + q;
-    if (LISTED) {
-      rt = g.tile_rt[logical];
+    if (LISTED) {   // (the list tells the row tile; ct is the tile's place in the list)
       ct = logical;
       return;
     }
@@ -255,7 +253,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int ldh = g.ds / 2 + 16;
 
   // ---- the tile being loaded.  Rows past the end repeat the last one (their accumulator elements start dead).
-  // byte offsets of this lane's rows from the tile's first row / the first row of the tile's columns (three-product copy)
+  // byte offsets of this lane's pieces from the tile's first row / the first row of the tile's columns
   unsigned int offA[A_LD], offB[B_LD];
   float tau_reg = 0.f;
   int prev_reg = -1;
@@ -264,61 +262,84 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   float nxreg = 0.f, nyreg = 0.f, rreg = 0.f;
   float2 wreg = make_float2(0.f, 0.f);
   int ids[LISTED ? B_LD : 1], cid_reg = 0;
+  int2 where = make_int2(0, 0);   // row tile of a listed tile, and the number of its list's columns before it
   // the listed ids of a tile (a missing one loads centroid 0 and starts dead)
   auto fetch_ids = [&](int ct) {
     const int32_t *list = g.col_list + (int64_t)ct * BN;
     if constexpr (LISTED) {
+      where = g.tile_rt[ct];
 #pragma unroll
       for (int j = 0; j < B_LD; ++j) ids[j] = list[ld_row + ROWS_PASS * j];
       cid_reg = list[tid];
     }
   };
-  auto aim = [&](int rt, int ct) {
+  int first_col = 0;   // of the aimed tile: its first column, or for a listed tile its first position in the row tile's list
+  auto aim = [&](int &rt, int ct) {
+    first_col = ct * BN;
+    if (LISTED) {
+      rt = __builtin_amdgcn_readfirstlane(where.x);
+      first_col = __builtin_amdgcn_readfirstlane(where.y);
+    }
     const int row0 = rt * BM;
     baseA = g.A + (int64_t)row0 * g.lda;
     if (LISTED && g.deep) baseAh = g.Ah + (int64_t)row0 * ldh;
     const int limA = g.M - 1 - row0;
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda) * 4u;
+    for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda) * 4u + ld_piece;
     nx = g.xnp + g.row_base + row0 + min(tid & (BM - 1), limA);
     if constexpr (LISTED) {
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(ids[j], 0) * (unsigned int)g.ldb * 4u;   // (the launcher checks the range)
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(ids[j], 0) * (unsigned int)g.ldb * 4u + ld_piece;   // (the launcher checks the range)
       ny = g.ynp + max(cid_reg, 0);
     } else {
       const int col0 = ct * BN, limB = g.N - 1 - col0;
       baseB = g.B + (int64_t)col0 * g.ldb;
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u;
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u + ld_piece;
       ny = g.ynp + col0 + min(tid, limB);
     }
     const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
     tau_reg = g.tau[g.row_base + gr];
-    prev_reg = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM)
+    prev_reg = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM; listed tiles: position in the list)
   };
-  // unit starting at dimension t of the aimed tile -> LDS stage (asynchronous)
-  auto request = [&](int t, bool one, int stage) {
-    uint32_t *sb = smem + stage * STAGE_WORDS + 16 * wave * ROW_WORDS;
-    // (uniform bases and 32-bit byte offsets: the address of a load is its offset register.  A row of the one-product copy
-    // is half as long as one of the three-product copy)
-    const bool o = LISTED && one;
-    const char *pa = uniform_ptr((o ? baseAh : baseA) + (o ? 8 + t / 2 : 16 + t));
-    const char *pb = uniform_ptr((o ? g.Bh : baseB) + (o ? 8 + t / 2 : 16 + t));
-    const int sh = o ? 1 : 0;
+  // ---- requests: the next unit of the aimed tile -> LDS (asynchronous).  The addresses of a load are a uniform base, which
+  // moves on by 64 bytes a unit, and an offset register; rows of the one-product copy are half as long as those of the
+  // three-product copy, so the offsets are halved once where a tile changes over.
+  int cur = 0;            // word offset of the LDS stage of the unit being multiplied
+  int rstage = 0;         // ... of the next request
+  int treq = 0, rstep = 16;   // dimensions requested so far of the tile, and those of the next request
+  const char *nextA = nullptr, *nextB = nullptr;
+  auto ring = [&](int stage) { return stage == (NSTAGE - 1) * STAGE_WORDS ? 0 : stage + STAGE_WORDS; };
+  auto request = [&]() {
+    uint32_t *sb = smem + rstage + 16 * wave * ROW_WORDS;
+    const char *pa = uniform_ptr(nextA), *pb = uniform_ptr(nextB);
 #pragma unroll
     for (int j = 0; j < A_LD; ++j) {
-      unsigned int off = (offA[j] >> sh) + ld_piece;
+      unsigned int off = offA[j];
       asm("" : "+v"(off));   // (kept apart from the base)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + off),
                                        (__attribute__((address_space(3))) void *)(sb + ROWS_PASS * j * ROW_WORDS), 16, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < B_LD; ++j) {
-      unsigned int off = (offB[j] >> sh) + ld_piece;
+      unsigned int off = offB[j];
       asm("" : "+v"(off));
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + off),
                                        (__attribute__((address_space(3))) void *)(sb + (BM + ROWS_PASS * j) * ROW_WORDS), 16, 0, 0);
     }
+    nextA = pa + 64;
+    nextB = pb + 64;
+    treq += rstep;
+    rstage = ring(rstage);
+  };
+  auto change_over = [&]() {   // to one product, at dimension d'
+    nextA = reinterpret_cast<const char *>(baseAh + 8 + g.dprime / 2);
+    nextB = reinterpret_cast<const char *>(g.Bh + 8 + g.dprime / 2);
+#pragma unroll
+    for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) >> 1) + ld_piece;
+#pragma unroll
+    for (int j = 0; j < B_LD; ++j) offB[j] = ((offB[j] - ld_piece) >> 1) + ld_piece;
+    rstep = 32;
   };
   // Checkpoint m's prefix norms (the points' table has a row per 16 dimensions, the centroids' a row per checkpoint of
   // this step), theta ratio and, for the widened tests, the largest centroid norms.
@@ -343,61 +364,54 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __syncthreads();
   int q = __builtin_amdgcn_readfirstlane(s_q[0]);
   if (q >= xcount) return;
-  int rt, ct;
+  int rt = 0, ct = 0;
   tile_rc(q, rt, ct);
   rt = __builtin_amdgcn_readfirstlane(rt);
   ct = __builtin_amdgcn_readfirstlane(ct);
-  int cur = 0;   // LDS stage of the unit being multiplied
-  int treq = 0;  // dimensions requested so far of the tile
   bool redone = false;   // (listed) the tile is being done again, in three products
-  auto start_tile = [&]() {   // first two units of the aimed tile -> stages cur and cur + 1
+  auto start_tile = [&]() {   // first two units of the aimed tile
     load_norm(0);
-    request(0, false, cur);
-    treq = 16;
+    nextA = reinterpret_cast<const char *>(baseA + 16);   // (a granule of zeros leads every row)
+    nextB = reinterpret_cast<const char *>(baseB + 16);
+    treq = 0;
+    rstep = 16;
+    rstage = cur;
+    request();
     if (treq < g.ds) {
-      const bool one = LISTED && g.deep && !redone && treq >= g.dprime;
-      request(treq, one, cur == NSTAGE - 1 ? 0 : cur + 1);
-      treq += one ? 32 : 16;
+      if (LISTED && g.deep && !redone && treq == g.dprime) change_over();
+      request();
     }
   };
   if (LISTED) fetch_ids(ct);
-  aim(rt, ct);
+  aim(rt, ct);   // (sets rt of a listed tile)
   start_tile();
   // A tile is committed once its per-row data have arrived: the thresholds go to LDS, the incumbents are marked, and the
   // number of the tile after next is drawn (the counter's answer is stored at the end of the tile, so its round trip
   // never stalls the workgroup).
   unsigned int drawn = 0;
-  auto commit = [&](int col0, int par) {
-    if constexpr (LISTED) {   // the tile's centroid ids, ascending, for the search below
-      s_cid[tid] = cid_reg < 0 ? 0x7fffffff : cid_reg;
-      __syncthreads();
-    }
+  auto mark_incumbents = [&]() {
     if (tid < BM) {
-      s_tau[par][tid] = tau_reg;
-      // the incumbent of this row, if it is a column of this tile, starts dead: find the thread and the
-      // accumulator element that hold (row tid, column prev - col0)
-      int cl = prev_reg - col0;
-      if constexpr (LISTED) {   // position of the incumbent among the listed ids, if it is one of them
-        int lo = 0;
-#pragma unroll
-        for (int step = BN / 2; step > 0; step >>= 1)
-          if (s_cid[lo + step] <= prev_reg) lo += step;
-        cl = (prev_reg >= 0 && s_cid[lo] == prev_reg) ? lo : -1;
-      }
+      // the incumbent of this row, if it is a column of this tile, starts dead: the thread and the accumulator element
+      // that hold (row tid, column prev - first_col).  (Every thread emptied its own marks when it read them.)
+      const int cl = prev_reg - first_col;
       if (prev_reg >= 0 && cl >= 0 && cl < BN) {
         const int rr = tid & 31, blk = cl >> 5;   // column block blk belongs to wavefront blk & 3, its block blk >> 2
         const int thread = (blk & 3) * 64 + ((rr >> 2) & 1) * 32 + (cl & 31);
         atomicOr(&s_dead[thread * 4 + (tid >> 5)], 1u << ((blk >> 2) * 16 + 4 * (rr >> 3) + (rr & 3)));
       }
     }
-    if (tid == 0) drawn = atomicAdd(ctr, 1u);
-    __syncthreads();
   };
-  commit(ct * BN, 0);
+  auto commit = [&](int par) {
+    if (tid < BM) s_tau[par][tid] = tau_reg;
+    mark_incumbents();
+    if (tid == 0) drawn = atomicAdd(ctr, 1u);
+    SKM_BARRIER();
+  };
+  commit(0);
 
   for (int tile_no = 0;; ++tile_no) {
     const int row0 = rt * BM, col0 = ct * BN;
-    const int par = LISTED ? 0 : tile_no & 1;
+    const int par = tile_no & 1;
     // the tile after this one: its number is known already, its list of columns is fetched while this one is multiplied
     q = __builtin_amdgcn_readfirstlane(s_q[(tile_no + 1) & 3]);
     const bool more = q < xcount;
@@ -406,7 +420,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       tile_rc(q, rt_next, ct_next);
       rt_next = __builtin_amdgcn_readfirstlane(rt_next);
       ct_next = __builtin_amdgcn_readfirstlane(ct_next);
-      if (LISTED) fetch_ids(ct_next);
     }
     acc_t<NB> acc;
 #pragma unroll
@@ -419,19 +432,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int b = 0; b < TN; ++b) {
       const int cl = (b * 4 + wave) * 32 + r32;
-      if constexpr (LISTED) gc[b] = s_cid[cl];
-      else gc[b] = col0 + cl < g.N ? col0 + cl : 0x7fffffff;
+      if constexpr (LISTED) {
+        const int id = g.col_list[(int64_t)ct * BN + cl];
+        gc[b] = id < 0 ? 0x7fffffff : id;
+      } else {
+        gc[b] = col0 + cl < g.N ? col0 + cl : 0x7fffffff;
+      }
     }
-    // one alive-bit per accumulator element: word a, bit 16 b + v.  (Listed tiles instead set a dead element to kDead,
-    // which no test passes and no product changes, and make the bits when they hand over.)
+    if (LISTED && more) fetch_ids(ct_next);
+    // one alive-bit per accumulator element: word a, bit 16 b + v
     unsigned int bits[TM];
-    constexpr float kDead = -3.0e38f;
-    auto first_bits = [&]() {
+    {
       const uint4 dead = *reinterpret_cast<const uint4 *>(&s_dead[tid * 4]);
       bits[0] = ~dead.x; bits[1] = ~dead.y; bits[2] = ~dead.z; bits[3] = ~dead.w;
-      const unsigned int cols = (gc[0] < g.N ? 0xffffu : 0u) | (NB > 1 && gc[NB - 1] < g.N ? 0xffff0000u : 0u);
-#pragma unroll
-      for (int a = 0; a < TM; ++a) bits[a] &= cols;
       if (row0 + BM > g.M) {   // rows past the end start dead
 #pragma unroll
         for (int a = 0; a < TM; ++a)
@@ -439,23 +452,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           for (int v = 0; v < 16; ++v)
             if (row0 + row_of(a, v) >= g.M) bits[a] &= ~(0x10001u << v);
       }
-    };
-    const bool wide = NB > 1 && (LISTED ? s_cid[128 * (NB - 1)] < g.N : g.N - col0 > 128);   // more than 128 columns
-    first_bits();
-    if constexpr (LISTED) {
-      if (__ballot((bits[0] & bits[1] & bits[2] & bits[3]) != 0xffffffffu)) {
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if (!((bits[a] >> (16 * b + v)) & 1u)) acc[a][b][v] = kDead;
-      }
-    } else {
-#pragma unroll
-      for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
     }
+#pragma unroll
+    for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
 
     int fin_mode = 0, fin_m = 0;   // how the tile ends: 0 = nothing alive, 1 = reached t = d, 2 = handed over at fin_m
     int wave_alive = 0;            // alive pairs of this wavefront at the last checkpoint
@@ -480,6 +479,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     while (true) {
       cur = __builtin_amdgcn_readfirstlane(cur);   // (uniform: kept in scalar registers)
       treq = __builtin_amdgcn_readfirstlane(treq);
+      rstage = __builtin_amdgcn_readfirstlane(rstage);
+      rstep = __builtin_amdgcn_readfirstlane(rstep);
       t = __builtin_amdgcn_readfirstlane(t);
       m = __builtin_amdgcn_readfirstlane(m);
       tcp = __builtin_amdgcn_readfirstlane(tcp);
@@ -502,17 +503,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       SKM_BARRIER();   // everyone's share of the unit is there, and the stage before it is free
       if (cp) load_norm(after(m));
       if (treq < tend) {
-        const bool o = LISTED && deep && treq >= g.dprime;
-        request(treq, o, cur == 0 ? NSTAGE - 1 : cur - 1);
-        treq += o ? 32 : 16;
+        if (LISTED && !one && deep && treq == g.dprime) change_over();
+        request();
       }
       {
-        const uint32_t *Ab = smem + cur * STAGE_WORDS + r32 * ROW_WORDS;
-        const uint32_t *Bb = smem + cur * STAGE_WORDS + (BM + wave * 32 + r32) * ROW_WORDS;
+        const uint32_t *Ab = smem + cur + r32 * ROW_WORDS;
+        const uint32_t *Bb = smem + cur + (BM + wave * 32 + r32) * ROW_WORDS;
         if constexpr (one) unit_one<NB>(acc, Ab, Bb, p0, p1);
         else unit_three<NB>(acc, Ab, Bb, p0, p1);
       }
-      cur = cur == NSTAGE - 1 ? 0 : cur + 1;
+      cur = ring(cur);
       t += step;
       if (one) dims1 += step;
       else dims3 += step;
@@ -539,23 +539,25 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // Test theta(t_m, tau_i): drop the pair when its partial distance exceeds it.
       if constexpr (one) {
         // Is anything left?  Per lane and column the smallest distance minus threshold over its 64 rows, a fused
-        // multiply and half a minimum per element; the pairs themselves are told apart only once few columns are left.
+        // multiply and half a minimum per element; the pairs themselves are told apart only once few columns are left
+        // (pairs that died at the first test may count here: a column too many then)
         int cols = 0;
-        float least[TN];
-#pragma unroll
-        for (int b = 0; b < TN; ++b) least[b] = 3.0e38f;
+        float least[TM][TN];
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
           float thr[16];
           row_thresholds(a, thr);
 #pragma unroll
-          for (int b = 0; b < TN; ++b)
+          for (int b = 0; b < TN; ++b) {
+            least[a][b] = fminf(fmaf(m2, acc[a][b][0], -thr[0]), fmaf(m2, acc[a][b][1], -thr[1]));
 #pragma unroll
-            for (int v = 0; v < 16; v += 2)
-              least[b] = fminf(fminf(least[b], fmaf(m2, acc[a][b][v], -thr[v])), fmaf(m2, acc[a][b][v + 1], -thr[v + 1]));
+            for (int v = 2; v < 16; v += 2)
+              least[a][b] = fminf(fminf(least[a][b], fmaf(m2, acc[a][b][v], -thr[v])), fmaf(m2, acc[a][b][v + 1], -thr[v + 1]));
+          }
         }
 #pragma unroll
-        for (int b = 0; b < TN; ++b) cols += __popcll(__ballot(least[b] <= -yn[b]));
+        for (int b = 0; b < TN; ++b)
+          cols += __popcll(__ballot(fminf(fminf(least[0][b], least[1][b]), fminf(least[2][b], least[3][b])) <= -yn[b] && gc[b] < g.N));
         const unsigned int left = tile_sum(cols);
         if (left == 0u) return 0;
         const bool stop = m >= g.nb - 1;   // (the last test there is)
@@ -564,29 +566,36 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           tcp = min(g.dprime + kBlockDims * m, g.ds);
           continue;
         }
-      }
-      if constexpr (LISTED && !one) {
-        // (a count per wavefront on the scalar unit, the verdict as the element's value)
-        if (!last) {
-          wave_alive = 0;
 #pragma unroll
-          for (int a = 0; a < TM; ++a) {
-            float thr[16];
-            row_thresholds(a, thr);
+        for (int a = 0; a < TM; ++a) {
+          float thr[16];
+          row_thresholds(a, thr);
+          unsigned int kept = 0u;
 #pragma unroll
-            for (int b = 0; b < TN; ++b)
+          for (int b = TN - 1; b >= 0; --b) {
+            kept <<= 16;
+            if (__ballot(least[a][b] <= -yn[b])) {   // (few blocks of 32 x 32 have any)
+              unsigned int dropped = 0u;
 #pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const bool alive = fmaf(m2, acc[a][b][v], yn[b]) <= thr[v];
-                acc[a][b][v] = alive ? acc[a][b][v] : kDead;
-                wave_alive += __popcll(__ballot(alive));
+              for (int v = 15; v >= 0; --v) {
+                const float margin = thr[v] - fmaf(m2, acc[a][b][v], yn[b]);
+                dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
               }
+              kept |= ~dropped & 0xffffu;
+            }
           }
+          bits[a] &= kept;
         }
+        wave_alive = wave_sum_i32(__popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]));
       } else {
         // The sign of threshold minus distance is the verdict (a difference of two floats is negative exactly when the
         // second is larger); the signs of the 32 elements of an accumulator row block are shifted into one word, last
         // element first, one funnel shift each.
+        if (m == 0) {   // columns past the end
+          const unsigned int cols = (gc[0] < g.N ? 0xffffu : 0u) | (NB > 1 && gc[NB - 1] < g.N ? 0xffff0000u : 0u);
+#pragma unroll
+          for (int a = 0; a < TM; ++a) bits[a] &= cols;
+        }
         if (!last || g.nb == 0) {
 #pragma unroll
           for (int a = 0; a < TM; ++a) {
@@ -600,8 +609,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 const float margin = thr[v] - fmaf(m2, acc[a][b][v], yn[b]);
                 dropped = __builtin_amdgcn_alignbit(dropped, __builtin_bit_cast(unsigned int, margin), 31);
               }
-            if (LISTED) bits[a] = ~dropped;
-            else bits[a] &= ~dropped;
+            bits[a] &= ~dropped;
           }
           static_assert(TN * 16 <= 32, "one word per accumulator row block");
         }
@@ -643,6 +651,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (LISTED) {
       if (act == 1) act = advance(std::true_type());
     }
+    const bool wide = NB > 1 && __ballot(gc[NB - 1] < g.N) != 0;   // (wavefront 0: more than 128 columns)
     if (tid == 0) {   // (in tiles of 128 x 128)
       atomicAdd(sc + SC_DENSE_DIMS, (unsigned long long)dims3 << (wide ? 1 : 0));
       if (LISTED && dims1) atomicAdd(sc + SC_SCREEN_DIMS, (unsigned long long)dims1 << (wide ? 1 : 0));
@@ -654,6 +663,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (LISTED && act == 2) {
       // the tile once more, in three products throughout
       redone = true;
+      if (rstep == 32) {
+#pragma unroll
+        for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) << 1) + ld_piece;
+#pragma unroll
+        for (int j = 0; j < B_LD; ++j) offB[j] = ((offB[j] - ld_piece) << 1) + ld_piece;
+      }
+      mark_incumbents();
+      SKM_BARRIER();
       start_tile();
       --tile_no;
       continue;
@@ -712,18 +729,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         // element behind a bit is found through LDS, where the lane parks its 16 values of a block (a register
         // cannot be chosen per lane): the stage the last unit was read from is free, 4 KB per wavefront as [16][64].
         // List slots: the wavefront's range, then lane by lane (prefix sum of the lanes' counts), then bit by bit.
-        if (LISTED && !(deep && fin_m > 0)) {   // (in one product the last test has made the bits)
-#pragma unroll
-          for (int a = 0; a < TM; ++a) {
-            unsigned int dead = 0u;
-#pragma unroll
-            for (int b = TN - 1; b >= 0; --b)
-#pragma unroll
-              for (int v = 15; v >= 0; --v)
-                dead = __builtin_amdgcn_alignbit(dead, __builtin_bit_cast(unsigned int, acc[a][b][v] - 0.5f * kDead), 31);
-            bits[a] = ~dead;
-          }
-        }
         int upto = __popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]);
         const int mine = upto;
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, false);   // row_shr:1
@@ -734,7 +739,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xC, 0xF, false);   // row_bcast:31
         unsigned int pos = run + (unsigned int)(upto - mine);
         const bool over = LISTED && fin_m > 0 && deep;   // the partial sum holds one-product parts: the pair starts over
-        float *park = reinterpret_cast<float *>(smem + (cur == 0 ? NSTAGE - 1 : cur - 1) * STAGE_WORDS + wave * (16 * 64)) + lane;
+        float *park = reinterpret_cast<float *>(smem + (cur == 0 ? (NSTAGE - 1) * STAGE_WORDS : cur - STAGE_WORDS) + wave * (16 * 64)) + lane;
         const unsigned int mtag = over ? 0u : (unsigned int)fin_m << 24;
 #pragma unroll
         for (int a = 0; a < TM; ++a)
@@ -774,12 +779,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (!more) break;
     rt = rt_next;
     ct = ct_next;
-    if (LISTED) {
-#pragma unroll
-      for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
-    }
     if (tid == 0) s_q[(tile_no + 2) & 3] = (int)drawn;
-    commit(ct * BN, LISTED ? 0 : par ^ 1);   // its barrier also ends this tile: everyone is done with the tile's LDS
+    commit(par ^ 1);   // its barrier also ends this tile: everyone is done with the tile's LDS
   }
 }
 

@@ -478,8 +478,11 @@ __global__ void __launch_bounds__(1024) mask_scan_kernel(const int32_t *cnt, int
 // tiles name mostly the same centroids).  Row tile after row tile every centroid came from outside the XCD's L2 once per
 // row tile: 5.4 TB/s of misses in an assignment of 2.5M x 384 to 32768 centroids.
 __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, int32_t nrt, int32_t maskw, const int32_t *cnt,
-                                                        const int32_t *first, int32_t *col_list, int32_t *tile_rt) {
+                                                        const int32_t *first, int32_t *col_list, int2 *tile_rt,
+                                                        const int32_t *prev, int32_t *list_pos, int64_t row_base, int32_t M) {
   __shared__ int s_wave[4];
+  __shared__ int s_pos[256];   // positions of the chunk's words
+  __shared__ unsigned int s_bits[256];
   __shared__ int s_base;
   const int rt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -496,6 +499,8 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     for (int r = 0; r < kListGroup; ++r) p += min(others[r], c) + (g0 + r < rt && others[r] > c ? 1 : 0);
     return p;
   };
+  const int inc = tid < RT && rt * RT + tid < M ? prev[row_base + rt * RT + tid] : -1;   // incumbent of row tid of the row tile
+  int at_pos = -1;
   if (tid == 0) s_base = 0;
   __syncthreads();
   for (int w0 = 0; w0 < maskw; w0 += 256) {
@@ -512,6 +517,8 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     __syncthreads();
     int pos = s_base + incl - mine;
     for (int ww = 0; ww < wave; ++ww) pos += s_wave[ww];
+    s_pos[tid] = pos;
+    s_bits[tid] = bits;
     int at = -1;
     int32_t *out = nullptr;
     while (bits) {
@@ -525,6 +532,10 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
       ++pos;
     }
     __syncthreads();
+    if (inc >= 32 * w0 && inc < 32 * (w0 + 256)) {   // the row's incumbent is in this chunk of words
+      const unsigned int b = s_bits[(inc >> 5) - w0], bit = 1u << (inc & 31);
+      if (b & bit) at_pos = s_pos[(inc >> 5) - w0] + __popc(b & (bit - 1u));
+    }
     if (tid == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
     __syncthreads();
   }
@@ -532,7 +543,8 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     int32_t *out = col_list + (int64_t)place(nt - 1) * kListCols;
     for (int p = total - (nt - 1) * kListCols + tid; p < kListCols; p += 256) out[p] = -1;
   }
-  for (int t = tid; t < nt; t += 256) tile_rt[place(t)] = rt;
+  for (int t = tid; t < nt; t += 256) tile_rt[place(t)] = make_int2(rt, t * kListCols);
+  if (inc >= 0) list_pos[row_base + rt * RT + tid] = at_pos;
 }
 
 // The test of a pair, theta + widening - ||x'||^2 >= ||y'||^2 - 2 x'.y', in accumulator units (the accumulator holds
@@ -694,7 +706,7 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)((nrt + 3) / 4)), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt);
   hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(1024), 0, st, a.cnt, nrt, a.first, a.ntiles, a.scal);
   hipLaunchKernelGGL(mask_fill_kernel, dim3((unsigned)nrt), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt, a.first,
-                     a.col_list, a.tile_rt);
+                     a.col_list, a.tile_rt, a.prev, a.list_pos, a.row_base, a.M);
   return hipGetLastError();
 }
 

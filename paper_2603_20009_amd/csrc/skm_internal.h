@@ -199,9 +199,12 @@ struct ProgArgs {
   unsigned long long *best;       // [n] packed (distance, centroid)
   unsigned long long *scal;       // [kStatReplicas][SC_COUNT] step scalars (SC_SURVIVORS, SC_COMPLETED, SC_DENSE_*, SC_ENTER..)
   int32_t block_stats;            // also count pairs entering every trailing block (SC_ENTER + m)
-  // Listed columns (after launch_screen; all NULL otherwise): tile t is row tile tile_rt[t] against the 256 centroids
+  // Listed columns (after launch_screen; all NULL otherwise): tile t is row tile tile_rt[t].x against the 256 centroids
   // col_list[256 t ..] (ascending ids, -1 = none); *ntiles tiles in all.
-  const int32_t *tile_rt = nullptr, *col_list = nullptr, *ntiles = nullptr;
+  // prev then holds the position of the incumbent in the row tile's list (-1 = not listed), and tile_rt[t] also how many of
+  // the list's columns come before the tile.
+  const int2 *tile_rt = nullptr;
+  const int32_t *col_list = nullptr, *ntiles = nullptr;
   // Listed columns only: one product and widened tests behind the first test (deep = 1).  Ah / Bh: the planes of hi
   // halves; widen[m] = (widening per unit of the row's norm behind d', guard) of checkpoint m.  A tile hands over at
   // the first test with at most emit_first pairs alive, later with at most emit_deep columns (of half a tile's rows) that
@@ -220,7 +223,7 @@ hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
 // theta(d', tau) widened by the error bound of the dropped halves; then, per row tile of 128 points, the centroids
 // that some point of the tile may still pass, as an ascending id list padded with -1 to a multiple of 256.
 // Outputs: cnt[row tiles], first[row tiles] (tiles of 256 listed columns before every row tile), *ntiles,
-// col_list[256 * ntiles], tile_rt[ntiles]; capacity needed: one tile per (row tile, column tile) of the full problem.
+// col_list[256 * ntiles], tile_rt[ntiles] (see ProgArgs); capacity needed: one tile per (row tile, column tile) of the full problem.
 struct ScreenLaunch {
   const uint32_t *A; int64_t lda; int32_t M;
   const uint32_t *B; int64_t ldb; int32_t N;
@@ -236,7 +239,10 @@ struct ScreenLaunch {
   int32_t nb = 0;               // receives the terms of the later, widened tests (ProgArgs)
   float2 *widen = nullptr;
   uint32_t *colmask;         // scratch: [row tiles][4 * column tiles]
-  int32_t *cnt, *first, *ntiles, *col_list, *tile_rt;   // (ntiles: two words, the second is scratch)
+  int32_t *cnt, *first, *ntiles, *col_list;   // (ntiles: two words, the second is scratch)
+  int2 *tile_rt;
+  const int32_t *prev;       // (first test) [n] incumbents, indexed like tau; list_pos[row_base + row] receives the position
+  int32_t *list_pos;         // of a row's incumbent in its row tile's list, -1 if it is not listed
   unsigned int *tile_counter;   // (unused)
   unsigned long long *scal;     // step scalars (SC_SCREEN_DIMS)
   // Exact mode (iteration 1: dprime = ds, xn / yn the full norms, tau and ratio0 unused, no column lists): for every
