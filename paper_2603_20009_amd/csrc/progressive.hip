@@ -97,11 +97,12 @@ constexpr int A_LD = BM / ROWS_PASS;                // 2 load instructions per t
     asm volatile("" : : : "memory");                              \
   } while (0)
 
-// the same pointer in scalar registers (it is uniform, which the compiler cannot always tell)
-__device__ inline const char *uniform_ptr(const void *p) {
+typedef __attribute__((address_space(3))) uint32_t *lds_words_t;
+// a raw buffer at p, which is uniform (the compiler cannot always tell)
+__device__ inline __amdgpu_buffer_rsrc_t uniform_buffer(const void *p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
-  return reinterpret_cast<const char *>((hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((hi << 32) | lo), 0, (int)0xffffffffu, 0x00027000);
 }
 
 // Sum over the 64 lanes of a wavefront through the data-parallel lane moves: within quads, mirrored
@@ -261,7 +262,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const float *nx = g.xnp, *ny = g.ynp;     // prefix norms of row tid & 127 and of column tid
   float nxreg = 0.f, nyreg = 0.f, rreg = 0.f;
   float2 wreg = make_float2(0.f, 0.f);
-  int ids[LISTED ? B_LD : 1], cid_reg = 0;
+  int ids[LISTED ? B_LD : 1], cid_reg = 0, gc_next[LISTED ? TN : 1];
   int2 where = make_int2(0, 0);   // row tile of a listed tile, and the number of its list's columns before it
   // the listed ids of a tile (a missing one loads centroid 0 and starts dead)
   auto fetch_ids = [&](int ct) {
@@ -271,7 +272,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int j = 0; j < B_LD; ++j) ids[j] = list[ld_row + ROWS_PASS * j];
       cid_reg = list[tid];
+#pragma unroll
+      for (int b = 0; b < TN; ++b) gc_next[b] = list[(b * 4 + wave) * 32 + r32];
     }
+  };
+  float tau_next = 0.f;
+  int prev_next = -1;
+  auto fetch_rows = [&](int rt) {   // thresholds and incumbents of the next tile (listed: after fetch_ids)
+    const int row0 = (LISTED ? __builtin_amdgcn_readfirstlane(where.x) : rt) * BM;
+    const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
+    tau_next = g.tau[g.row_base + gr];
+    prev_next = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM; listed tiles: position in the list)
   };
   int first_col = 0;   // of the aimed tile: its first column, or for a listed tile its first position in the row tile's list
   auto aim = [&](int &rt, int ct) {
@@ -298,43 +309,37 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u + ld_piece;
       ny = g.ynp + col0 + min(tid, limB);
     }
-    const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
-    tau_reg = g.tau[g.row_base + gr];
-    prev_reg = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM; listed tiles: position in the list)
+    tau_reg = tau_next;
+    prev_reg = prev_next;
   };
-  // ---- requests: the next unit of the aimed tile -> LDS (asynchronous).  The addresses of a load are a uniform base, which
-  // moves on by 64 bytes a unit, and an offset register; rows of the one-product copy are half as long as those of the
-  // three-product copy, so the offsets are halved once where a tile changes over.
+  // ---- requests: the next unit of the aimed tile -> LDS (asynchronous).  Buffer loads: a uniform base, a uniform offset
+  // that moves on by 64 bytes a unit, and an offset register per load.  (They are known to be no LDS reads: behind
+  // global_load_lds the compiler lets the first matrix instruction of a unit wait for all of its fragments.)  Rows of the
+  // one-product copy are half as long as those of the three-product copy: the offsets are halved once where a tile
+  // changes over.
   int cur = 0;            // word offset of the LDS stage of the unit being multiplied
   int rstage = 0;         // ... of the next request
   int treq = 0, rstep = 16;   // dimensions requested so far of the tile, and those of the next request
-  const char *nextA = nullptr, *nextB = nullptr;
+  int soff = 0;           // byte offset of the next unit in a row
+  const uint32_t *fromA = g.A, *fromB = g.B;
   auto ring = [&](int stage) { return stage == (NSTAGE - 1) * STAGE_WORDS ? 0 : stage + STAGE_WORDS; };
   auto request = [&]() {
-    uint32_t *sb = smem + rstage + 16 * wave * ROW_WORDS;
-    const char *pa = uniform_ptr(nextA), *pb = uniform_ptr(nextB);
+    lds_words_t sb = (lds_words_t)smem + rstage + 16 * wave * ROW_WORDS;
+    const __amdgpu_buffer_rsrc_t ra = uniform_buffer(fromA), rb = uniform_buffer(fromB);
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j) {
-      unsigned int off = offA[j];
-      asm("" : "+v"(off));   // (kept apart from the base)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + off),
-                                       (__attribute__((address_space(3))) void *)(sb + ROWS_PASS * j * ROW_WORDS), 16, 0, 0);
-    }
+    for (int j = 0; j < A_LD; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, sb + ROWS_PASS * j * ROW_WORDS, 16, (int)offA[j], soff, 0, 0);
 #pragma unroll
-    for (int j = 0; j < B_LD; ++j) {
-      unsigned int off = offB[j];
-      asm("" : "+v"(off));
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + off),
-                                       (__attribute__((address_space(3))) void *)(sb + (BM + ROWS_PASS * j) * ROW_WORDS), 16, 0, 0);
-    }
-    nextA = pa + 64;
-    nextB = pb + 64;
+    for (int j = 0; j < B_LD; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, sb + (BM + ROWS_PASS * j) * ROW_WORDS, 16, (int)offB[j], soff, 0, 0);
+    soff += 64;
     treq += rstep;
     rstage = ring(rstage);
   };
   auto change_over = [&]() {   // to one product, at dimension d'
-    nextA = reinterpret_cast<const char *>(baseAh + 8 + g.dprime / 2);
-    nextB = reinterpret_cast<const char *>(g.Bh + 8 + g.dprime / 2);
+    fromA = baseAh;
+    fromB = g.Bh;
+    soff = 4 * (8 + g.dprime / 2);
 #pragma unroll
     for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) >> 1) + ld_piece;
 #pragma unroll
@@ -371,8 +376,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   bool redone = false;   // (listed) the tile is being done again, in three products
   auto start_tile = [&]() {   // first two units of the aimed tile
     load_norm(0);
-    nextA = reinterpret_cast<const char *>(baseA + 16);   // (a granule of zeros leads every row)
-    nextB = reinterpret_cast<const char *>(baseB + 16);
+    fromA = baseA;
+    fromB = baseB;
+    soff = 64;   // (a granule of zeros leads every row)
     treq = 0;
     rstep = 16;
     rstage = cur;
@@ -383,9 +389,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
   };
   if (LISTED) fetch_ids(ct);
+  fetch_rows(rt);
   aim(rt, ct);   // (sets rt of a listed tile)
   start_tile();
-  // A tile is committed once its per-row data have arrived: the thresholds go to LDS, the incumbents are marked, and the
+  // A tile is committed: the thresholds go to LDS, the incumbents are marked, and the
   // number of the tile after next is drawn (the counter's answer is stored at the end of the tile, so its round trip
   // never stalls the workgroup).
   unsigned int drawn = 0;
@@ -428,18 +435,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       for (int b = 0; b < TN; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    int gc[TN];   // centroid of this lane's accumulator columns (INT_MAX = none)
+    int gc[TN];   // centroid of this lane's accumulator columns (listed tiles: -1 = none)
 #pragma unroll
     for (int b = 0; b < TN; ++b) {
-      const int cl = (b * 4 + wave) * 32 + r32;
-      if constexpr (LISTED) {
-        const int id = g.col_list[(int64_t)ct * BN + cl];
-        gc[b] = id < 0 ? 0x7fffffff : id;
-      } else {
-        gc[b] = col0 + cl < g.N ? col0 + cl : 0x7fffffff;
-      }
+      if constexpr (LISTED) gc[b] = gc_next[b];
+      else gc[b] = col0 + (b * 4 + wave) * 32 + r32;
     }
+    auto is_col = [&](int b) { return (unsigned int)gc[b] < (unsigned int)g.N; };
     if (LISTED && more) fetch_ids(ct_next);
+    if (!LISTED && more) fetch_rows(rt_next);
     // one alive-bit per accumulator element: word a, bit 16 b + v
     unsigned int bits[TM];
     {
@@ -481,6 +485,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       treq = __builtin_amdgcn_readfirstlane(treq);
       rstage = __builtin_amdgcn_readfirstlane(rstage);
       rstep = __builtin_amdgcn_readfirstlane(rstep);
+      soff = __builtin_amdgcn_readfirstlane(soff);
       t = __builtin_amdgcn_readfirstlane(t);
       m = __builtin_amdgcn_readfirstlane(m);
       tcp = __builtin_amdgcn_readfirstlane(tcp);
@@ -520,6 +525,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 #pragma unroll
       for (int b = 0; b < TN; ++b) yn[b] = s_yn[(b * 4 + wave) * 32 + r32];
+      if (LISTED && !one && m == 0 && more) fetch_rows(0);   // (the list's row tile has long arrived)
       auto row_thresholds = [&](int a, float (&thr)[16]) {
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4) {
@@ -557,7 +563,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
 #pragma unroll
         for (int b = 0; b < TN; ++b)
-          cols += __popcll(__ballot(fminf(fminf(least[0][b], least[1][b]), fminf(least[2][b], least[3][b])) <= -yn[b] && gc[b] < g.N));
+          cols += __popcll(__ballot(fminf(fminf(least[0][b], least[1][b]), fminf(least[2][b], least[3][b])) <= -yn[b] && is_col(b)));
         const unsigned int left = tile_sum(cols);
         if (left == 0u) return 0;
         const bool stop = m >= g.nb - 1;   // (the last test there is)
@@ -592,7 +598,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         // second is larger); the signs of the 32 elements of an accumulator row block are shifted into one word, last
         // element first, one funnel shift each.
         if (m == 0) {   // columns past the end
-          const unsigned int cols = (gc[0] < g.N ? 0xffffu : 0u) | (NB > 1 && gc[NB - 1] < g.N ? 0xffff0000u : 0u);
+          const unsigned int cols = (is_col(0) ? 0xffffu : 0u) | (NB > 1 && is_col(NB - 1) ? 0xffff0000u : 0u);
 #pragma unroll
           for (int a = 0; a < TM; ++a) bits[a] &= cols;
         }
@@ -651,7 +657,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (LISTED) {
       if (act == 1) act = advance(std::true_type());
     }
-    const bool wide = NB > 1 && __ballot(gc[NB - 1] < g.N) != 0;   // (wavefront 0: more than 128 columns)
+    const bool wide = NB > 1 && __ballot(is_col(NB - 1)) != 0;   // (wavefront 0: more than 128 columns)
     if (tid == 0) {   // (in tiles of 128 x 128)
       atomicAdd(sc + SC_DENSE_DIMS, (unsigned long long)dims3 << (wide ? 1 : 0));
       if (LISTED && dims1) atomicAdd(sc + SC_SCREEN_DIMS, (unsigned long long)dims1 << (wide ? 1 : 0));
@@ -663,6 +669,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (LISTED && act == 2) {
       // the tile once more, in three products throughout
       redone = true;
+      if constexpr (LISTED) {
+#pragma unroll
+        for (int b = 0; b < TN; ++b) gc_next[b] = gc[b];   // (fetched for the next tile already)
+      }
       if (rstep == 32) {
 #pragma unroll
         for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) << 1) + ld_piece;
