@@ -205,7 +205,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // (two copies of the thresholds by tile parity: the previous tile may still be handing pairs over while the next is
   // committed)
   __shared__ __align__(16) float s_tau[2][BM], s_thr[BM], s_xn[BM], s_yn[BN];
-  __shared__ unsigned int s_dead[NT * 4];            // per thread: accumulator elements that start dead (the incumbent)
+  __shared__ int s_ids[LISTED ? 2 : 1][LISTED ? BN : 1];   // by tile parity: the listed centroid ids (-1 = none)
+  __shared__ int s_prev[BM];                         // incumbents of the tile being loaded (listed tiles: position in the list)
+  __shared__ __align__(16) int s_inc[BM];            // column of every row's incumbent in the tile in work (-1 = another tile's)
+  __shared__ int s_any[2];                           // whether there are any, rows 0 .. 63 and 64 .. 127
   __shared__ __align__(16) unsigned int s_wcnt[2][4];   // alive pairs of every wavefront at the last checkpoint (by checkpoint parity)
   __shared__ unsigned int s_base;         // first list slot of a tile that hands its pairs over
   __shared__ int s_q[4];   // ring of tile numbers drawn from the XCD's counter, two tiles ahead of the one in work
@@ -245,8 +248,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   };
 
   unsigned long long *sc = g.scal + (size_t)(blockIdx.x & (kStatReplicas - 1)) * SC_COUNT;
-#pragma unroll
-  for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
 
   // Staging: load instruction j of wavefront w moves tile rows 64 j + 16 w .. + 15 of a unit.
   const int ld_row = 16 * wave + (lane >> 2);                       // + 64 j
@@ -256,40 +257,36 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- the tile being loaded.  Rows past the end repeat the last one (their accumulator elements start dead).
   // byte offsets of this lane's pieces from the tile's first row / the first row of the tile's columns
   unsigned int offA[A_LD], offB[B_LD];
-  float tau_reg = 0.f;
-  int prev_reg = -1;
   const uint32_t *baseA = g.A, *baseAh = g.Ah, *baseB = g.B;   // first rows (uniform)
-  const float *nx = g.xnp, *ny = g.ynp;     // prefix norms of row tid & 127 and of column tid
+  int nrow = 0, ncol = 0;                   // row tid & 127 and column tid, for their prefix norms
   float nxreg = 0.f, nyreg = 0.f, rreg = 0.f;
   float2 wreg = make_float2(0.f, 0.f);
-  int ids[LISTED ? B_LD : 1], cid_reg = 0, gc_next[LISTED ? TN : 1];
-  int2 where = make_int2(0, 0);   // row tile of a listed tile, and the number of its list's columns before it
-  // the listed ids of a tile (a missing one loads centroid 0 and starts dead)
-  auto fetch_ids = [&](int ct) {
-    const int32_t *list = g.col_list + (int64_t)ct * BN;
+  int2 where = make_int2(0, 0);   // row tile of the next listed tile, and the number of its list's columns before it
+  // What the next tile needs is brought to LDS a tile ahead: the list's ids (a missing one loads centroid 0 and starts
+  // dead), the rows' thresholds and incumbents.
+  auto fetch_ids = [&](int ct, int par) {
     if constexpr (LISTED) {
-      where = g.tile_rt[ct];
-#pragma unroll
-      for (int j = 0; j < B_LD; ++j) ids[j] = list[ld_row + ROWS_PASS * j];
-      cid_reg = list[tid];
-#pragma unroll
-      for (int b = 0; b < TN; ++b) gc_next[b] = list[(b * 4 + wave) * 32 + r32];
+      const auto *w = reinterpret_cast<const __attribute__((address_space(4))) int *>(reinterpret_cast<uint64_t>(g.tile_rt + ct));
+      where = make_int2(w[0], w[1]);   // (scalar loads: written by an earlier kernel)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(g.col_list + (int64_t)ct * BN), (lds_words_t)s_ids[par] + 64 * wave, 4,
+                                               tid * 4, 0, 0, 0);
     }
   };
-  float tau_next = 0.f;
-  int prev_next = -1;
-  auto fetch_rows = [&](int rt) {   // thresholds and incumbents of the next tile (listed: after fetch_ids)
-    const int row0 = (LISTED ? __builtin_amdgcn_readfirstlane(where.x) : rt) * BM;
-    const int gr = min(row0 + (tid & (BM - 1)), g.M - 1);
-    tau_next = g.tau[g.row_base + gr];
-    prev_next = row0 + tid < g.M ? g.prev[g.row_base + gr] : -1;   // (used by threads < BM; listed tiles: position in the list)
+  auto fetch_rows = [&](int rt, int par) {
+    if (LISTED) rt = where.x;
+    const int64_t at = g.row_base + (int64_t)rt * BM;
+    if (wave < BM / 64) {
+      const int off = 4 * min(tid, g.M - 1 - rt * BM);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(g.tau + at), (lds_words_t)s_tau[par] + 64 * wave, 4, off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(g.prev + at), (lds_words_t)s_prev + 64 * wave, 4, off, 0, 0, 0);
+    }
   };
   int first_col = 0;   // of the aimed tile: its first column, or for a listed tile its first position in the row tile's list
-  auto aim = [&](int &rt, int ct) {
+  auto aim = [&](int &rt, int ct, int par) {
     first_col = ct * BN;
     if (LISTED) {
-      rt = __builtin_amdgcn_readfirstlane(where.x);
-      first_col = __builtin_amdgcn_readfirstlane(where.y);
+      rt = where.x;
+      first_col = where.y;
     }
     const int row0 = rt * BM;
     baseA = g.A + (int64_t)row0 * g.lda;
@@ -297,20 +294,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int limA = g.M - 1 - row0;
 #pragma unroll
     for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda) * 4u + ld_piece;
-    nx = g.xnp + g.row_base + row0 + min(tid & (BM - 1), limA);
+    nrow = row0 + min(tid & (BM - 1), limA);
     if constexpr (LISTED) {
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(ids[j], 0) * (unsigned int)g.ldb * 4u + ld_piece;   // (the launcher checks the range)
-      ny = g.ynp + max(cid_reg, 0);
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(s_ids[par][ld_row + ROWS_PASS * j], 0) * (unsigned int)g.ldb * 4u + ld_piece;   // (the launcher checks the range)
+      ncol = max(s_ids[par][tid], 0);
     } else {
       const int col0 = ct * BN, limB = g.N - 1 - col0;
       baseB = g.B + (int64_t)col0 * g.ldb;
 #pragma unroll
       for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u + ld_piece;
-      ny = g.ynp + col0 + min(tid, limB);
+      ncol = col0 + min(tid, limB);
     }
-    tau_reg = tau_next;
-    prev_reg = prev_next;
   };
   // ---- requests: the next unit of the aimed tile -> LDS (asynchronous).  Buffer loads: a uniform base, a uniform offset
   // that moves on by 64 bytes a unit, and an offset register per load.  (They are known to be no LDS reads: behind
@@ -351,8 +346,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   auto load_norm = [&](int m) {
     m = min(m, g.nb);
     const int px = (min(g.dprime + kBlockDims * m, g.ds) >> 4) - 1;
-    nxreg = nx[(int64_t)px * g.xn_stride];
-    nyreg = ny[(int64_t)m * g.N];
+    nxreg = (g.xnp + ((int64_t)px * g.xn_stride + g.row_base))[nrow];
+    nyreg = (g.ynp + (int64_t)m * g.N)[ncol];
     rreg = g.ratio[m];
     if (LISTED && g.deep) wreg = g.widen[m];
   };
@@ -388,33 +383,27 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       request();
     }
   };
-  if (LISTED) fetch_ids(ct);
-  fetch_rows(rt);
-  aim(rt, ct);   // (sets rt of a listed tile)
+  if (LISTED) fetch_ids(ct, 0);
+  fetch_rows(rt, 0);
+  SKM_VMCNT(0);
+  SKM_BARRIER();
+  aim(rt, ct, 0);   // (sets rt of a listed tile)
   start_tile();
-  // A tile is committed: the thresholds go to LDS, the incumbents are marked, and the
-  // number of the tile after next is drawn (the counter's answer is stored at the end of the tile, so its round trip
-  // never stalls the workgroup).
+  // A tile is committed: the incumbents' columns are noted, and the number of the tile after next is drawn (the counter's
+  // answer is stored at the end of the tile, so its round trip never stalls the workgroup).
   unsigned int drawn = 0;
-  auto mark_incumbents = [&]() {
-    if (tid < BM) {
-      // the incumbent of this row, if it is a column of this tile, starts dead: the thread and the accumulator element
-      // that hold (row tid, column prev - first_col).  (Every thread emptied its own marks when it read them.)
-      const int cl = prev_reg - first_col;
-      if (prev_reg >= 0 && cl >= 0 && cl < BN) {
-        const int rr = tid & 31, blk = cl >> 5;   // column block blk belongs to wavefront blk & 3, its block blk >> 2
-        const int thread = (blk & 3) * 64 + ((rr >> 2) & 1) * 32 + (cl & 31);
-        atomicOr(&s_dead[thread * 4 + (tid >> 5)], 1u << ((blk >> 2) * 16 + 4 * (rr >> 3) + (rr & 3)));
-      }
+  auto commit = [&]() {
+    if (wave < BM / 64) {
+      const int prev = s_prev[tid], cl = prev - first_col;
+      const bool here = prev >= 0 && cl >= 0 && cl < BN;
+      s_inc[tid] = here ? cl : -1;
+      const bool any = __ballot(here) != 0;
+      if (lane == 0) s_any[wave] = any;
     }
-  };
-  auto commit = [&](int par) {
-    if (tid < BM) s_tau[par][tid] = tau_reg;
-    mark_incumbents();
     if (tid == 0) drawn = atomicAdd(ctr, 1u);
     SKM_BARRIER();
   };
-  commit(0);
+  commit();
 
   for (int tile_no = 0;; ++tile_no) {
     const int row0 = rt * BM, col0 = ct * BN;
@@ -438,17 +427,31 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int gc[TN];   // centroid of this lane's accumulator columns (listed tiles: -1 = none)
 #pragma unroll
     for (int b = 0; b < TN; ++b) {
-      if constexpr (LISTED) gc[b] = gc_next[b];
+      if constexpr (LISTED) gc[b] = s_ids[par][(b * 4 + wave) * 32 + r32];
       else gc[b] = col0 + (b * 4 + wave) * 32 + r32;
     }
     auto is_col = [&](int b) { return (unsigned int)gc[b] < (unsigned int)g.N; };
-    if (LISTED && more) fetch_ids(ct_next);
-    if (!LISTED && more) fetch_rows(rt_next);
+    if (LISTED && more) fetch_ids(ct_next, par ^ 1);
+    if (!LISTED && more) fetch_rows(rt_next, par ^ 1);
     // one alive-bit per accumulator element: word a, bit 16 b + v
     unsigned int bits[TM];
     {
-      const uint4 dead = *reinterpret_cast<const uint4 *>(&s_dead[tid * 4]);
-      bits[0] = ~dead.x; bits[1] = ~dead.y; bits[2] = ~dead.z; bits[3] = ~dead.w;
+#pragma unroll
+      for (int a = 0; a < TM; ++a) bits[a] = NB > 1 ? 0xffffffffu : 0xffffu;
+      if (s_any[0] | s_any[1]) {   // incumbents start dead
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int v4 = 0; v4 < 4; ++v4) {
+            const int4 c = *reinterpret_cast<const int4 *>(&s_inc[a * 32 + 8 * v4 + 4 * kh]);
+            const int cl[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int b = 0; b < TN; ++b)
+                if (cl[u] == (b * 4 + wave) * 32 + r32) bits[a] &= ~(1u << (16 * b + 4 * v4 + u));
+          }
+      }
       if (row0 + BM > g.M) {   // rows past the end start dead
 #pragma unroll
         for (int a = 0; a < TM; ++a)
@@ -457,8 +460,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             if (row0 + row_of(a, v) >= g.M) bits[a] &= ~(0x10001u << v);
       }
     }
-#pragma unroll
-    for (int a = 0; a < TM; ++a) s_dead[tid * 4 + a] = 0u;
 
     int fin_mode = 0, fin_m = 0;   // how the tile ends: 0 = nothing alive, 1 = reached t = d, 2 = handed over at fin_m
     int wave_alive = 0;            // alive pairs of this wavefront at the last checkpoint
@@ -496,9 +497,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       if (cp) {
         // the prefix norms fetched one checkpoint ago -> LDS, with the row's threshold theta(t_m, tau) - ||x_t||^2
         if (tid < BM) {
-          float thr = rreg * tau_reg - nxreg;
+          const float tau = s_tau[par][tid];
+          float thr = rreg * tau - nxreg;
           if (one)   // + the error bound of the one product over the dimensions behind d', and guards
-            thr += fmaf(wreg.x, sqrtf(fmaxf(nxreg - xn0, 0.f) + 1e-6f * nxreg), fmaf(1e-6f, rreg * tau_reg + nxreg, wreg.y));
+            thr += fmaf(wreg.x, sqrtf(fmaxf(nxreg - xn0, 0.f) + 1e-6f * nxreg), fmaf(1e-6f, rreg * tau + nxreg, wreg.y));
           s_xn[tid] = nxreg;
           s_thr[tid] = thr;
           if (LISTED && m == 0) xn0 = nxreg;
@@ -525,7 +527,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 #pragma unroll
       for (int b = 0; b < TN; ++b) yn[b] = s_yn[(b * 4 + wave) * 32 + r32];
-      if (LISTED && !one && m == 0 && more) fetch_rows(0);   // (the list's row tile has long arrived)
+      if (LISTED && !one && m == 0 && more) fetch_rows(0, par ^ 1);
       auto row_thresholds = [&](int a, float (&thr)[16]) {
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4) {
@@ -669,24 +671,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (LISTED && act == 2) {
       // the tile once more, in three products throughout
       redone = true;
-      if constexpr (LISTED) {
-#pragma unroll
-        for (int b = 0; b < TN; ++b) gc_next[b] = gc[b];   // (fetched for the next tile already)
-      }
       if (rstep == 32) {
 #pragma unroll
         for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) << 1) + ld_piece;
 #pragma unroll
         for (int j = 0; j < B_LD; ++j) offB[j] = ((offB[j] - ld_piece) << 1) + ld_piece;
       }
-      mark_incumbents();
-      SKM_BARRIER();
       start_tile();
       --tile_no;
       continue;
     }
     if (more) {
-      aim(rt_next, ct_next);
+      if (LISTED) SKM_BARRIER();   // (the ids were brought by all wavefronts)
+      aim(rt_next, ct_next, par ^ 1);
       start_tile();
     }
 
@@ -790,7 +787,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     rt = rt_next;
     ct = ct_next;
     if (tid == 0) s_q[(tile_no + 2) & 3] = (int)drawn;
-    commit(par ^ 1);   // its barrier also ends this tile: everyone is done with the tile's LDS
+    commit();   // its barrier also ends this tile: everyone is done with the tile's LDS
   }
 }
 
