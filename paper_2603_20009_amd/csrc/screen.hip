@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr bool EXACT = MODE == SCREEN_EXACT, NEIGH = MODE >= SCREEN_GROUPS;
   __shared__ __align__(16) float s_a2[NEIGH ? NSTAGE : 1][BM], s_y2[NEIGH ? NSTAGE : 1][BN];   // scales of rows and columns
   __shared__ unsigned int s_rmin[EXACT ? BM : 1];    // EXACT: minimum of every row of the tile (ordered float bits)
-  __shared__ float s_thr[EXACT ? BM : 1];            // EXACT: emission threshold of every row
+  __shared__ __align__(16) float s_thr[EXACT ? BM : 1];   // EXACT: emission threshold of every row
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -200,6 +200,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   };
 
   if (slot >= xcount) return;
+  if constexpr (EXACT) {
+    if (tid < BM) s_rmin[tid] = 0xffffffffu;
+    __syncthreads();
+  }
 #pragma unroll
   for (int i = 0; i < DEPTH; ++i) request();
 
@@ -231,8 +235,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-        if constexpr (EXACT)
-          if (tid < BM) s_rmin[tid] = 0xffffffffu;   // (read after this tile's slab barriers)
       }
       if (s == 0 && MODE == SCREEN_FIRST_TEST) {      // every accumulator element starts from its row's term
 #pragma unroll
@@ -329,76 +331,86 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       continue;
     }
     if constexpr (EXACT) {
+      // The rows are shared out among the lanes on the way to their minima, and the candidates are counted before room
+      // for all of a wavefront's is taken at once: five lane moves and an LDS exchange per row, and a trip to the list's
+      // counter for every row with a candidate, were 27 of the 54 us of a tile of 768 dimensions.
+      const int slot_t = ctile & (NSTAGE - 1);
       // ---- minimum of every row over the tile's columns
-      const float *yc = s_y[ctile & (NSTAGE - 1)] + wn * 64 + r32;
+      const float *yc = s_y[slot_t] + wn * 64 + r32;
       const float y0 = colok[0] ? yc[0] : 3.0e38f, y1 = colok[1] ? yc[32] : 3.0e38f;
+      const int my_row = rt * BM + tid;   // (wavefronts 0 to 3)
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if ((v & 3) == 0) asm volatile("" : : : "memory");   // (four rows at a time: see the registers note below)
-          float m = fminf(y0 - acc[a][0][v], y1 - acc[a][1][v]);
-          // over the 32 lanes that hold this row (same lane half): quads, half rows, rows, then the two rows of the half
-          m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, false)));
-          m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x4E, 0xF, 0xF, false)));
-          m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x141, 0xF, 0xF, false)));
-          m = fminf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), 0x140, 0xF, 0xF, false)));
-          m = fminf(m, __shfl_xor(m, 16, 64));
-          if (r32 == 0) atomicMin(&s_rmin[wm * 128 + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3)], f2ord(m));
-        }
+      for (int h = 0; h < TM; h += 2) {
+        const float m = reduce_rows32_f32([&](int a, int v) { return fminf(y0 - acc[h + a][0][v], y1 - acc[h + a][1][v]); }, lane);
+        const int v = r32 & 15;
+        atomicMin(&s_rmin[wm * 128 + (h + (r32 >> 4)) * 32 + 8 * (v >> 2) + 4 * kh + (v & 3)], f2ord(m));
+      }
       __syncthreads();
       // ---- the point's running minimum takes it; the threshold is the smaller of the two plus the band
       if (tid < BM) {
-        const int row = rt * BM + tid;
         float thr = -3.0e38f;
-        if (row < g.M) {
+        if (my_row < g.M) {
           const unsigned int local = s_rmin[tid];
-          const unsigned int old = atomicMin(g.rowmin + g.row_base + row, local);
-          thr = ord2f(old < local ? old : local) + s_a[ctile & (NSTAGE - 1)][tid];
+          // (not a read ahead of the minimum: the tiles of a row that end together would not see each other's)
+          const unsigned int old = atomicMin(g.rowmin + g.row_base + my_row, local);
+          thr = ord2f(old < local ? old : local) + s_a[slot_t][tid];
         }
         s_thr[tid] = thr;
+        s_rmin[tid] = 0xffffffffu;   // for the next tile
       }
       __syncthreads();
-      // ---- emit the pairs at or below the threshold of their row
-      const int xsub = blockIdx.x & 7;
-      int zero = 0;
+      // ---- emit the pairs at or below the threshold of their row: bit 2 v + b of word a
+      unsigned int bits[TM];
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+      for (int a = 0; a < TM; ++a) {
+        asm volatile("" : : : "memory");   // (one block's thresholds at a time: all 64 would not fit the registers)
+        bits[a] = 0u;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          // (a value the compiler cannot see through, renewed every four rows: the thresholds are then fetched four
-          // at a time instead of all 64 ahead, which would not fit the registers next to the accumulators)
-          if ((v & 3) == 0) asm volatile("" : "+v"(zero) : : "memory");
-          const int rl = wm * 128 + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3) + zero;
-          const float thr = s_thr[rl];
-          // (v~ <= thr written from the accumulator's side: the differences of the first pass are not kept alive)
-          const bool e0 = acc[a][0][v] >= y0 - thr, e1 = acc[a][1][v] >= y1 - thr;
-          const unsigned long long b0 = __ballot(e0), b1 = __ballot(e1);
-          if (b0 | b1) {
-            const int n0 = __popcll(b0), tot = n0 + __popcll(b1);
-            unsigned int base = 0;
-            if (lane == 0) base = atomicAdd(g.pair_count + xsub * kSubListStride, (unsigned int)tot);
-            base = __builtin_amdgcn_readfirstlane(base);
-            if ((unsigned long long)base + tot > (unsigned long long)g.sub_capacity) {
-              if (lane == 0) atomicOr(g.overflow, 1u);
-            } else {
-              const unsigned long long below = (1ull << lane) - 1ull;
-              Pair pr;
-              pr.i = (int32_t)(g.row_base + rt * BM + rl);
-              pr.p = 0.f;
-              pr.tau = 3.0e38f;
-              Pair *dst = g.pairs + (size_t)xsub * g.sub_capacity + base;
-              if (e0) {
-                pr.j = col0 + wn * 64 + r32;
-                dst[__popcll(b0 & below)] = pr;
-              }
-              if (e1) {
-                pr.j = col0 + wn * 64 + 32 + r32;
-                dst[n0 + __popcll(b1 & below)] = pr;
-              }
-            }
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const float4 t4 = *reinterpret_cast<const float4 *>(&s_thr[wm * 128 + a * 32 + 8 * q4 + 4 * kh]);
+          const float thr[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {   // (v~ <= thr written from the accumulator's side)
+            const int v = 4 * q4 + u;
+            bits[a] |= acc[a][0][v] >= y0 - thr[u] ? 1u << (2 * v) : 0u;
+            bits[a] |= acc[a][1][v] >= y1 - thr[u] ? 2u << (2 * v) : 0u;
           }
         }
+      }
+      int mine = 0;
+#pragma unroll
+      for (int a = 0; a < TM; ++a) mine += __popc(bits[a]);
+      if (__ballot(mine != 0)) {
+        int upto = mine;   // list slots: lane by lane (prefix sum of the lanes' counts), then bit by bit
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xF, 0xF, false);   // row_shr:1
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xF, 0xF, false);   // row_shr:2
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xF, 0xF, false);   // row_shr:4
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xF, 0xF, false);   // row_shr:8
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xA, 0xF, false);   // row_bcast:15
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xC, 0xF, false);   // row_bcast:31
+        const unsigned int tot = (unsigned int)__builtin_amdgcn_readlane(upto, 63);
+        const int xsub = blockIdx.x & 7;
+        unsigned int base = 0;
+        if (lane == 0) base = atomicAdd(g.pair_count + xsub * kSubListStride, tot);
+        base = __builtin_amdgcn_readfirstlane(base);
+        if ((unsigned long long)base + tot > (unsigned long long)g.sub_capacity) {
+          if (lane == 0) atomicOr(g.overflow, 1u);
+        } else {
+          Pair *dst = g.pairs + (size_t)xsub * g.sub_capacity + base + (unsigned int)(upto - mine);
+          Pair pr;
+          pr.p = 0.f;
+          pr.tau = 3.0e38f;
+#pragma unroll
+          for (int a = 0; a < TM; ++a)
+            while (bits[a]) {
+              const int e = __builtin_ctz(bits[a]), v = e >> 1;
+              bits[a] &= bits[a] - 1u;
+              pr.i = (int32_t)(g.row_base + rt * BM + wm * 128 + a * 32 + 8 * (v >> 2) + 4 * kh + (v & 3));
+              pr.j = col0 + wn * 64 + 32 * (e & 1) + r32;
+              *dst++ = pr;
+            }
+        }
+      }
       continue;
     }
 

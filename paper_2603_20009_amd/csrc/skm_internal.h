@@ -61,6 +61,33 @@ __device__ inline unsigned long long reduce_rows32(F key_of, int lane) {
   const unsigned long long k2b = halve_min<0x4E, 2>(k4[1], k4[3], lane);
   return halve_min<0xB1, 1>(k2a, k2b, lane);                                         // quad_perm [1,0,3,2]
 }
+// The same of a float per row (fminf: a NaN counts only where there is nothing else).
+template <int DPP, int BIT>
+__device__ inline float halve_min_f32(float p, float q, int lane) {
+  const bool up = lane & BIT;
+  const float keep = up ? q : p, give = up ? p : q;
+  return fminf(keep, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), DPP, 0xF, 0xF, false)));
+}
+template <class F>
+__device__ inline float reduce_rows32_f32(F value_of, int lane) {
+  float k8[8];
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {
+    float k16[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned int, value_of(0, h + 8 * u)),
+                                                      __builtin_bit_cast(unsigned int, value_of(1, h + 8 * u)), false, false);
+      k16[u] = fminf(__builtin_bit_cast(float, (unsigned int)r[0]), __builtin_bit_cast(float, (unsigned int)r[1]));
+    }
+    k8[h] = halve_min_f32<0x128, 8>(k16[0], k16[1], lane);
+  }
+  float k4[4];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) k4[h] = halve_min_f32<0x141, 4>(k8[h], k8[h + 4], lane);
+  const float k2a = halve_min_f32<0x4E, 2>(k4[0], k4[2], lane), k2b = halve_min_f32<0x4E, 2>(k4[1], k4[3], lane);
+  return halve_min_f32<0xB1, 1>(k2a, k2b, lane);
+}
 #endif
 
 // Error reporting shared by the translation units that hold entry points: records the text skm_last_error() returns
