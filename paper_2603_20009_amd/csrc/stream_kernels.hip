@@ -501,6 +501,19 @@ __global__ void __launch_bounds__(256) absmax_kernel(const float *A, int64_t lda
   const int64_t total = rows * per_row;
   const bool flat = lda == cols;
   float m = 0.f;
+  if (VEC4 && flat) {   // four loads in flight
+    const float4 *v4 = reinterpret_cast<const float4 *>(A);
+    const int64_t stride = (int64_t)gridDim.x * 1024;
+    for (int64_t e = (int64_t)blockIdx.x * 1024 + threadIdx.x; e < total; e += stride) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = v4[min(e + 256 * u, total - 1)];   // (past the end: the last one again)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+    }
+    block_absmax(m, out);
+    return;
+  }
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     int64_t at = e * (VEC4 ? 4 : 1);
     if (!flat) {
@@ -522,8 +535,9 @@ hipError_t launch_absmax(const float *A, int64_t lda, int64_t rows, int32_t cols
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const bool vec = (reinterpret_cast<uintptr_t>(A) & 15u) == 0 && lda % 4 == 0 && cols % 4 == 0;
   const int64_t work = rows * (int64_t)(vec ? cols / 4 : cols);
-  // at least four elements per thread where there are that many: fewer workgroups meet at the one result word
-  const unsigned blocks = (unsigned)std::min<int64_t>((work + 1023) / 1024, max_blocks > 0 ? max_blocks : 256 * 16);
+  // At least four elements per thread where there are that many, and two workgroups per CU at most: that keeps enough
+  // loads in flight, and the atomics at the one result word, 10 ns each, stay few (4096 workgroups: 40 us for 20 000 x 1536).
+  const unsigned blocks = (unsigned)std::min<int64_t>((work + 1023) / 1024, max_blocks > 0 ? max_blocks : 2 * num_cus());
   if (vec) hipLaunchKernelGGL(absmax_kernel<true>, dim3(blocks), dim3(256), 0, st, A, lda, rows, cols, out);
   else hipLaunchKernelGGL(absmax_kernel<false>, dim3(blocks), dim3(256), 0, st, A, lda, rows, cols, out);
   return hipGetLastError();
@@ -1516,33 +1530,43 @@ hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const in
 
 // Both padded copies of the rotation matrix, the transposed one through a 32 x 33 tile in LDS, and its largest magnitude
 // in one pass (a copy each and a pass for the bound before: with d = 128 three launches of 4 us for 64 KB).
+// (four tiles a workgroup: every workgroup may raise the one word of the bound, 10 ns each)
+constexpr int kOperandTiles = 4;
 __global__ void __launch_bounds__(256) rotation_operands_kernel(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld,
                                                                 unsigned int *absmax) {
-  __shared__ float s_t[32][33];
+  __shared__ float s_t[kOperandTiles][32][33];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+  const int c0 = blockIdx.x * 32;
   float m = 0.f;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int r = r0 + ty + 8 * u, c = c0 + tx;
-    const float v = r < d && c < d ? R[(int64_t)r * d + c] : 0.f;
-    s_t[ty + 8 * u][tx] = v;
-    m = fmaxf(m, fabsf(v));
-    if (Rp && r < d && c < ld) Rp[(int64_t)r * ld + c] = v;
+  for (int q = 0; q < kOperandTiles; ++q) {
+    const int r0 = (blockIdx.y * kOperandTiles + q) * 32;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = r0 + ty + 8 * u, c = c0 + tx;
+      const float v = r < d && c < d ? R[(int64_t)r * d + c] : 0.f;
+      s_t[q][ty + 8 * u][tx] = v;
+      m = fmaxf(m, fabsf(v));
+      if (Rp && r < d && c < ld) Rp[(int64_t)r * ld + c] = v;
+    }
   }
   __syncthreads();
   if (Rtp)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {   // row c0 + .. of R^T
-      const int r = c0 + ty + 8 * u, c = r0 + tx;
-      if (r < d && c < ld) Rtp[(int64_t)r * ld + c] = s_t[tx][ty + 8 * u];
+    for (int q = 0; q < kOperandTiles; ++q) {
+      const int r0 = (blockIdx.y * kOperandTiles + q) * 32;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {   // row c0 + .. of R^T
+        const int r = c0 + ty + 8 * u, c = r0 + tx;
+        if (r < d && c < ld) Rtp[(int64_t)r * ld + c] = s_t[q][tx][ty + 8 * u];
+      }
     }
   block_absmax(m, absmax);
 }
 hipError_t launch_rotation_operands(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld, unsigned int *absmax,
                                     hipStream_t st) {
   const unsigned t = (unsigned)((ld + 31) / 32);
-  hipLaunchKernelGGL(rotation_operands_kernel, dim3(t, t), dim3(256), 0, st, R, d, Rp, Rtp, ld, absmax);
+  hipLaunchKernelGGL(rotation_operands_kernel, dim3(t, (t + kOperandTiles - 1) / kOperandTiles), dim3(256), 0, st, R, d, Rp, Rtp, ld, absmax);
   return hipGetLastError();
 }
 
