@@ -97,14 +97,6 @@ constexpr int A_LD = BM / ROWS_PASS;                // 2 load instructions per t
     asm volatile("" : : : "memory");                              \
   } while (0)
 
-typedef __attribute__((address_space(3))) uint32_t *lds_words_t;
-// a raw buffer at p, which is uniform (the compiler cannot always tell)
-__device__ inline __amdgpu_buffer_rsrc_t uniform_buffer(const void *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((hi << 32) | lo), 0, (int)0xffffffffu, 0x00027000);
-}
-
 // Sum over the 64 lanes of a wavefront through the data-parallel lane moves: within quads, mirrored
 // within half rows and rows, then the row totals handed on to the following rows; lane 63 ends with the result.
 #define SKM_WAVE_REDUCE(v, OP)                                                                \

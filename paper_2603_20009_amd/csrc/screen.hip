@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __shared__ __align__(16) float s_thr[EXACT ? BM : 1];   // EXACT: emission threshold of every row
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int r32 = lane & 31, kh = lane >> 5;
   const int swz = (r32 >> 2) & 3;
@@ -152,9 +152,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   int ltile = 0;                    // tiles requested so far (ring slot of the row terms)
   int ljob = 0;                     // slabs requested so far (ring slot of the stage)
   const uint32_t *baseA = g.A, *baseB = g.B;
-  unsigned int offA[A_LD], offB[B_LD];
-  auto request = [&]() {            // one slab; at a tile's first slab also its row terms
-    if (lq >= xcount) return;
+  unsigned int offA[A_LD], offB[B_LD];   // bytes
+  auto aim = [&]() {                // at a tile's first slab: its addresses and its row terms
     if (ls == 0) {
       int rt, ct;
       tile_rc(lq, rt, ct);
@@ -163,9 +162,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       baseB = g.B + (int64_t)col0 * g.ldb;
       const int limA = g.M - 1 - row0, limB = g.N - 1 - col0;   // rows / columns past the end repeat the last one
 #pragma unroll
-      for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda + ld_words);
+      for (int j = 0; j < A_LD; ++j) offA[j] = 4u * (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda + ld_words);
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb + ld_words);
+      for (int j = 0; j < B_LD; ++j) offB[j] = 4u * (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb + ld_words);
       // the tile's row terms (wavefronts 0-3) and column terms (4-7): one more 4-byte load each, straight into LDS
       {
         const int e = tid & (BM - 1);
@@ -182,16 +181,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
       ++ltile;
     }
-    uint32_t *sb = smem + (ljob & (NSTAGE - 1)) * STAGE_WORDS + 16 * wave * ROW_WORDS;
-    const int kw = kw0 + (BK / 2) * ls;
-#pragma unroll
-    for (int j = 0; j < A_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(baseA + offA[j] + kw),
-                                       (__attribute__((address_space(3))) void *)(sb + ROWS_PASS * j * ROW_WORDS), 16, 0, 0);
-#pragma unroll
-    for (int j = 0; j < B_LD; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(baseB + offB[j] + kw),
-                                       (__attribute__((address_space(3))) void *)(sb + (BM + ROWS_PASS * j) * ROW_WORDS), 16, 0, 0);
+  };
+  static_assert(A_LD + B_LD == TM, "one load behind every row block's matrix instructions");
+  // one of a slab's loads: a uniform base and a uniform offset, an offset register per load
+  auto load = [&](int j) {
+    lds_words_t sb = (lds_words_t)smem + (ljob & (NSTAGE - 1)) * STAGE_WORDS + 16 * wave * ROW_WORDS;
+    const int at = 4 * (kw0 + (BK / 2) * ls);
+    if (j < A_LD)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(baseA), sb + ROWS_PASS * j * ROW_WORDS, 16, (int)offA[j < A_LD ? j : 0], at, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(baseB), sb + ROWS_PASS * j * ROW_WORDS, 16, (int)offB[j < A_LD ? 0 : j - A_LD], at, 0, 0);
+  };
+  auto requested = [&]() {
     ++ljob;
     if (++ls == nslab) {
       ls = 0;
@@ -205,7 +206,45 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < DEPTH; ++i) request();
+  for (int i = 0; i < DEPTH; ++i)
+    if (lq < xcount) {
+      aim();
+#pragma unroll
+      for (int j = 0; j < TM; ++j) load(j);
+      requested();
+    }
+
+  // Fragments of a slab's two halves of 16 dimensions, read half a slab ahead: those of the second half are requested
+  // before the first half is multiplied, those of the next slab's first half behind the barrier in the middle of this
+  // slab, before its second half is multiplied.  The matrix cores have work on both sides of the barrier.
+  f16x8 a0[TM], b0[TN], a1[TM], b1[TN];
+  auto fragments = [&](int job, int h, f16x8 (&x)[TM], f16x8 (&y)[TN]) {
+    const uint32_t *st = smem + (job & (NSTAGE - 1)) * STAGE_WORDS;
+    const uint32_t *Ab = st + (wm * 128 + r32) * ROW_WORDS + (((2 * h + kh) ^ swz) << 2);
+    const uint32_t *Bb = st + (BM + wn * 64 + r32) * ROW_WORDS + (((2 * h + kh) ^ swz) << 2);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) y[t] = *reinterpret_cast<const f16x8 *>(Bb + t * 32 * ROW_WORDS);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) x[t] = *reinterpret_cast<const f16x8 *>(Ab + t * 32 * ROW_WORDS);
+  };
+  // Slab `job` has arrived, for every wavefront's share of it, and the stage of slab job - 2 is free.  Only the requests
+  // made after it may be outstanding: one slab of loads (counted in order; the tile terms in between only make the wait
+  // stricter); near the end fewer requests follow, so everything is awaited.  (A bare barrier: a fenced one would first
+  // wait for every load in flight.  The reads of slab job - 2 have been consumed by matrix instructions before this
+  // point, those of slab job - 1 concern a stage that stays as it is.)
+  auto arrived = [&](int later) {
+    if (lq < xcount) {
+      if (later == 2) SKM_SCREEN_VMCNT(2 * (A_LD + B_LD));
+      else SKM_SCREEN_VMCNT(A_LD + B_LD);
+    } else {
+      SKM_SCREEN_VMCNT(0);
+    }
+    asm volatile("" : : : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : : : "memory");
+  };
+  arrived(2);
+  fragments(0, 0, a0, b0);
 
   unsigned long long dims_done = 0ull;
   int cjob = 0, ctile = 0;
@@ -218,16 +257,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int b = 0; b < TN; ++b) colok[b] = col0 + wn * 64 + b * 32 + r32 < g.N;
     f32x16 acc[TM][TN];
     for (int s = 0; s < nslab; ++s, ++cjob) {
-      // slab cjob has arrived once at most the requests made after it are outstanding (DEPTH - 1 slabs of four loads
-      // each; loads are counted in order, the tile terms in between only make the wait stricter); near the end fewer
-      // requests follow, so everything is awaited
-      if (lq < xcount) SKM_SCREEN_VMCNT((DEPTH - 1) * (A_LD + B_LD));
-      else SKM_SCREEN_VMCNT(0);
-      // ... for every wavefront's share of it; and the stage of slab cjob - 1 is free.  (A bare barrier: a fenced one
-      // would first wait for every load in flight.  The only LDS traffic besides those loads are reads whose results
-      // the matrix instructions before this point have consumed.)
-      __builtin_amdgcn_s_barrier();
-      request();         // slab cjob + DEPTH -> the stage slab cjob - 1 was in (NSTAGE = DEPTH + 1)
       if (s == 0 && (EXACT || NEIGH)) {
 #pragma unroll
         for (int a = 0; a < TM; ++a)
@@ -251,23 +280,32 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             }
           }
       }
-      const uint32_t *st = smem + (cjob & (NSTAGE - 1)) * STAGE_WORDS;
-      const uint32_t *Ab = st + (wm * 128 + r32) * ROW_WORDS;
-      const uint32_t *Bb = st + (BM + wn * 64 + r32) * ROW_WORDS;
+      fragments(cjob, 1, a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        f16x8 ah[TM], bh[TN];
+      for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int t = 0; t < TM; ++t)
-          ah[t] = *reinterpret_cast<const f16x8 *>(Ab + t * 32 * ROW_WORDS + (((2 * h + kh) ^ swz) << 2));
+        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[a], b0[b], acc[a][b], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const bool next = s + 1 < nslab || q + nslots < xcount;
+      arrived(1);
+      // Slab cjob + DEPTH -> the stage slab cjob - 1 was in (NSTAGE = DEPTH + 1).  Its loads go between the matrix
+      // instructions: a wavefront whose load has to queue for the address unit issues nothing else meanwhile.  (All four
+      // ahead of them, 1000 queries against 1M x 768: 3.02 instead of 2.93 ms; 128 x 64 a wavefront in 16 dimensions is
+      // 256 cycles of matrix work, so there is room for a load behind every two instructions.)
+      const bool more = lq < xcount;
+      if (more) aim();
+      if (next) fragments(cjob + 1, 0, a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < TN; ++t)
-          bh[t] = *reinterpret_cast<const f16x8 *>(Bb + t * 32 * ROW_WORDS + (((2 * h + kh) ^ swz) << 2));
+      for (int a = 0; a < TM; ++a) {
 #pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[a], bh[b], acc[a][b], 0, 0, 0);
+        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[a], b1[b], acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) load(a);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      if (more) requested();
     }
     dims_done += (unsigned long long)(BK * nslab);
 

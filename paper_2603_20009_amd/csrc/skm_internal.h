@@ -21,6 +21,14 @@ struct __attribute__((aligned(16))) Pair {
 };
 
 #if defined(__HIPCC__)
+typedef __attribute__((address_space(3))) uint32_t *lds_words_t;
+// a raw buffer at p, which is uniform (the compiler cannot always tell)
+__device__ inline __amdgpu_buffer_rsrc_t uniform_buffer(const void *p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((hi << 32) | lo), 0, (int)0xffffffffu, 0x00027000);
+}
+
 // One step of a reduce-scatter of keys over the lanes of a wavefront half: of the two keys, lanes with BIT clear go on
 // with the first and lanes with it set with the second, each merged (minimum) with the partner's.
 template <int DPP, int BIT>
