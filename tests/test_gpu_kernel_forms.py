@@ -1,0 +1,139 @@
+"""The forms that a kernel takes by size, type or alignment, at the sizes where one hands over to another: each against the
+CPU oracle (fp64) or against the form next to it."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+from parity import EPS0, check_assignment
+from test_gpu_parity import check_ground_truth, cuda, dg, say, skm  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+# The exact assignment reads rows whose length is a multiple of four as they are from 32 dimensions on, unless the padded
+# length is a multiple of 32; other rows, and rows that are not 16-byte aligned, go through a padded copy.
+@pytest.mark.parametrize("n,d,k", [(1000, 36, 70), (257, 44, 129), (700, 100, 130), (300, 124, 40), (200, 20, 30),
+                                   (150, 1004, 60), (129, 52, 1), (128, 34, 128)])
+def test_exact_assignment_of_rows_that_are_no_multiple_of_16(skm, orc, dg, n, d, k):  # noqa: F811
+    say("exact rows", n, d, k)
+    rng = np.random.default_rng(n + d + k)
+    X = dg.mixture(n, d, 20, 2, "linear").numpy()
+    Y = X[rng.choice(n, k, replace=k > n)] + (0.01 * rng.standard_normal((k, d))).astype(np.float32)
+    ao, do = orc.assign_full(X.astype(np.float64), Y.astype(np.float64))
+    a, dist = skm.assign_exact(cuda(X), cuda(Y))
+    check_assignment(a.cpu().numpy(), ao, X, Y, min_agree=0.999)
+    same = a.cpu().numpy() == ao
+    assert np.abs(dist.cpu().numpy()[same] - do[same]).max() < 1e-6 * max(1.0, do.max())
+    # the same rows behind a start that is not 16-byte aligned: the padded copy, the same sums with zeros behind them
+    shifted = torch.empty(n * d + 1, device="cuda")
+    shifted[1:] = cuda(X).reshape(-1)
+    b, dist_b = skm.assign_exact(shifted[1:].view(n, d), cuda(Y))
+    assert torch.equal(a, b) and torch.equal(dist, dist_b)
+
+
+# Behind the first test of a listed tile: one product and widened tests (no counts per block asked for, three blocks or more,
+# pairs handed over), or three products throughout.  Poor incumbents leave tiles that are done again in three products,
+# good ones tiles that hand over at the first test.
+@pytest.mark.parametrize("poor", [0, 4, 1])          # no incumbent, every fourth, or all of them drawn at random
+@pytest.mark.parametrize("n,d,k,dp", [(1500, 304, 257, 48), (700, 208, 256, 16), (513, 1536, 600, 192),
+                                      (129, 272, 513, 80), (2000, 240, 64, 48)])
+def test_listed_tiles_in_one_product(skm, orc, dg, n, d, k, dp, poor):  # noqa: F811
+    say("listed", n, d, k, dp, poor)
+    rng = np.random.default_rng(7 * n + k)
+    X = dg.mixture(n, d, 30, n + k, "linear" if d < 512 else "embed").numpy()
+    R = orc.random_rotation(d, 5)
+    Y = X[rng.integers(0, n, k)] + (0.01 * rng.standard_normal((k, d))).astype(np.float32)   # (more than points, some)
+    Xr, Yr = orc.rotate(X, R), orc.rotate(Y, R)
+    prev = orc.assign_full(Xr, Yr)[0].astype(np.int32)
+    if poor:
+        prev[::poor] = rng.integers(0, k, len(prev[::poor]))
+    ref = orc.assign_pruned(Xr, Yr, prev, dp, EPS0, 0)
+    a, dist, row = skm.assign(cuda(X), cuda(Y), cuda(prev), dp, skm.FitOptions(R=cuda(R), screen=1))
+    assert row["screen_dims"] > 0
+    check_assignment(a.cpu().numpy(), ref.assign, Xr, Yr)
+    same = a.cpu().numpy() == ref.assign
+    assert np.abs(dist.cpu().numpy()[same] - ref.dist[same]).max() < 2e-5 * max(1.0, ref.dist.max())
+    surv_ref = n * (k - 1) - ref.pruned_first
+    assert abs(row["survivors"] - surv_ref) <= max(2, 1e-3 * surv_ref)
+    assert abs(row["completed"] - ref.enter[-1]) <= max(2, 1e-3 * ref.enter[-1])
+    assert row["changed"] == int((a.cpu().numpy() != prev).sum())
+
+
+# Grouping by label: a stable counting order for k <= 8192 and n >= 8 k, a scatter with ordered segments otherwise (segments
+# up to 2048 by rank, longer ones sorted).  The means are fp64 sums rounded to fp32: any order gives them to 1 ulp.
+@pytest.mark.parametrize("n,d,k,skew", [(800, 16, 100, 0), (799, 16, 100, 0), (65_536, 16, 8192, 0), (65_535, 16, 8192, 0),
+                                        (66_000, 20, 8193, 0), (30_000, 64, 9000, 25_000), (20_001, 48, 3000, 2049),
+                                        (4096, 32, 1, 0), (33, 100, 33, 0)])
+def test_update_at_the_borders_of_its_orders(skm, orc, dg, n, d, k, skew):  # noqa: F811
+    say("update", n, d, k, skew)
+    rng = np.random.default_rng(n + k)
+    X = dg.mixture(n, d, 30, 4, "linear").numpy()
+    a = rng.integers(0, k, n).astype(np.int32)
+    a[:skew] = k // 2
+    Y0 = rng.standard_normal((k, d)).astype(np.float32)
+    Yo, co = orc.update(X.astype(np.float64), a, Y0.astype(np.float64))
+    out = []
+    for _ in range(2):
+        Yg = cuda(Y0)
+        assert (skm.update(cuda(X), cuda(a), Yg).cpu().numpy() == co).all()
+        out.append(Yg.cpu().numpy())
+    assert np.abs(out[0] - Yo).max() < 1e-6
+    assert np.array_equal(out[0][co == 0], Y0[co == 0])
+    if n >= 8 * k and k <= 8192:
+        assert np.array_equal(out[0], out[1])        # the stable order: the same bits every time
+
+
+# Panels of 64 rows, the last square or narrower, factored twice where it is: d at the panels' edges.
+@pytest.mark.parametrize("d", [17, 63, 64, 65, 127, 128, 129, 191, 200])
+def test_rotation_at_the_edges_of_its_panels(skm, d):  # noqa: F811
+    R = skm.make_rotation(d, 11).cpu().numpy().astype(np.float64)
+    # d entries, each off by half an ulp of fp32 at most, meet in an element of R R^T: 2^-24 sqrt(d) at most by Cauchy-Schwarz
+    assert np.abs(R @ R.T - np.eye(d)).max() < 2 * 2.0 ** -24 * np.sqrt(d)
+
+
+# The ground truth goes through the points in chunks of whole rounds of tiles (256 points x 256 queries): one tile row and
+# several, a ragged last chunk, and too few points for the one-product form.
+@pytest.mark.parametrize("n,d,nq,K", [(40_000, 1536, 300, 10), (70_001, 1000, 257, 1), (20_000, 96, 64, 10),
+                                      (140_000, 64, 5, 100)])
+def test_ground_truth_in_chunks(skm, orc, dg, n, d, nq, K):  # noqa: F811
+    say("ground truth", n, d, nq, K)
+    X = dg.mixture(n, d, 200, 3, "embed").numpy()
+    Q = dg.mixture(nq, d, 200, 3, "embed", sample_seed=99).numpy()
+    gt = skm.etr_ground_truth(cuda(X), cuda(Q), K).cpu().numpy()
+    check_ground_truth(gt, orc.ground_truth(X, Q, K), X, Q)
+
+
+def test_calls_of_several_threads_share_the_kept_blocks(skm, dg):  # noqa: F811
+    """Calls without a lent workspace keep their device blocks for the next such call: calls of several threads on streams of
+    their own, between calls that give everything back, return what a call alone returns."""
+    n, d, k = 6000, 96, 130
+    X = dg.mixture(n, d, 40, 5, "linear").cuda()
+    Y = X[:k].contiguous() + 0.01
+    want = skm.assign(X, Y, None)[0]
+    wrong, errors = [], []
+
+    def work(i):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                for r in range(6):
+                    if r % 3 == i % 3:
+                        skm.release_memory()
+                    got = skm.assign(X, Y, None)[0]
+                    s.synchronize()
+                    if not torch.equal(got, want):
+                        wrong.append((i, r))
+        except Exception as e:   # noqa: BLE001
+            errors.append(repr(e))
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors and not wrong
+    skm.release_memory()
+    assert torch.equal(skm.assign(X, Y, None)[0], want)
