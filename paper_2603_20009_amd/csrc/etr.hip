@@ -94,6 +94,9 @@ hipError_t launch_topk_merge(const float *S, int64_t lds, int32_t nq, int32_t m,
 // ynorm[c] - 2 S[q][c].  The nprobe nearest centroids are drawn one at a time into LDS, then every
 // ground-truth neighbour is looked up: it is retrieved iff its cluster is probed.
 constexpr int MAX_PROBE = kMaxProbe;
+// NK > 0: at most 256 NK centroids, whose keys every thread keeps in registers over the rounds of the selection (read again in
+// every round, 1000 queries against 4096 centroids took 173 us, forty rounds of dependent loads).
+template <int NK>
 __global__ void __launch_bounds__(256) recall_kernel(const float *S, int64_t lds, int32_t k, const float *ynorm,
                                                      int32_t nprobe, const unsigned long long *gt_keys, int32_t K,
                                                      const int32_t *assign, unsigned long long *hits,
@@ -105,11 +108,23 @@ __global__ void __launch_bounds__(256) recall_kernel(const float *S, int64_t lds
   const float *row = S + (int64_t)q * lds;
   if (threadIdx.x == 0) { s_hits = 0; s_total = 0; }
   unsigned long long last = 0ull;
+  auto key_of = [&](int c) {
+    return ((unsigned long long)f2ord(ynorm[c] - 2.f * row[c]) << 32) | (unsigned long long)(uint32_t)c;
+  };
+  unsigned long long keys[NK > 0 ? NK : 1];
+#pragma unroll
+  for (int u = 0; u < NK; ++u) keys[u] = (int)threadIdx.x + 256 * u < k ? key_of((int)threadIdx.x + 256 * u) : ~0ull;
   for (int r = 0; r < nprobe; ++r) {
     unsigned long long best = ~0ull;
-    for (int c = threadIdx.x; c < k; c += 256) {
-      const unsigned long long key = ((unsigned long long)f2ord(ynorm[c] - 2.f * row[c]) << 32) | (unsigned long long)(uint32_t)c;
-      if ((r == 0 || key > last) && key < best) best = key;
+    if constexpr (NK > 0) {
+#pragma unroll
+      for (int u = 0; u < NK; ++u)
+        if ((r == 0 || keys[u] > last) && keys[u] < best) best = keys[u];
+    } else {
+      for (int c = threadIdx.x; c < k; c += 256) {
+        const unsigned long long key = key_of(c);
+        if ((r == 0 || key > last) && key < best) best = key;
+      }
     }
     best = block_min_u64(best, red);
     if (threadIdx.x == 0) s_probe[r] = (int32_t)(best & 0xffffffffull);
@@ -136,7 +151,8 @@ hipError_t launch_recall_scores(const float *S, int64_t lds, int32_t nq, int32_t
                                 const unsigned long long *gt_keys, int32_t K, const int32_t *assign,
                                 unsigned long long *hits, unsigned long long *total, hipStream_t st) {
   if (nprobe > MAX_PROBE || nprobe < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(recall_kernel, dim3(nq), dim3(256), 0, st, S, lds, k, ynorm, nprobe, gt_keys, K, assign, hits,
+  hipLaunchKernelGGL(k <= 256 ? recall_kernel<1> : k <= 1024 ? recall_kernel<4> : k <= 4096 ? recall_kernel<16> : recall_kernel<0>,
+                     dim3(nq), dim3(256), 0, st, S, lds, k, ynorm, nprobe, gt_keys, K, assign, hits,
                      total);
   return hipGetLastError();
 }

@@ -137,3 +137,18 @@ def test_calls_of_several_threads_share_the_kept_blocks(skm, dg):  # noqa: F811
     assert not errors and not wrong
     skm.release_memory()
     assert torch.equal(skm.assign(X, Y, None)[0], want)
+
+
+# The probes of a query are drawn from keys in registers (1, 4 or 16 a thread of 256) or, beyond 4096 centroids, read again.
+@pytest.mark.parametrize("k", [256, 1025, 4096, 4097])
+def test_recall_at_the_borders_of_its_forms(skm, orc, dg, k):  # noqa: F811
+    say("recall", k)
+    n, d, nq, K = 2 * k + 11, 32, 30, 10
+    X = dg.mixture(n, d, 30, 3, "linear").numpy()
+    Q = dg.mixture(nq, d, 30, 4, "linear").numpy()
+    R = orc.random_rotation(d, 6)
+    kw = dict(etr=True, topk=K, probe_frac=0.01, adjust_dprime=False, etr_tol=-1.0)
+    ref = orc.fit(X, k, 2, 2, orc.FitParams(eps0=EPS0, **kw), R=R, init_idx=orc.sample_rows(2, n, k), queries=Q)
+    got = skm.fit(cuda(X), k, 2, 2, skm.FitOptions(R=cuda(R), queries=cuda(Q), **kw))
+    for g, r in zip(got.trace[:2], ref.trace):
+        assert g["recall"] == pytest.approx(r["recall"], abs=2.0 / (nq * K))   # (a near-tie may move one neighbour or one probe)
