@@ -11,7 +11,7 @@ allocates nothing; ``--own-workspace`` lets the library allocate and free it ins
 
 Prints ONE JSON line: metric, value (point*centroid*dim per second over whole fits), ms_per_step, the workload in
 config, per-iteration seconds, host-clock figures (wall time of a call, wall minus device time), `roofline` for the
-dominant kernel (algorithmic flop per launch over its HIP-event time, against the dense fp16 matrix peak divided by
+dominant kernel (algorithmic flop per launch over its device time, against the dense fp16 matrix peak divided by
 the three products of the split arithmetic), `stages` with the same figures for every kernel family,
 `other_workloads` (the rest of the metric's range, k = 4096 ... 32 768: C4, C3, C5, a few timed fits each, same
 figures), `hierarchical` (the hierarchical fit of C4 beside the flat one) and `cpu_baseline` (the CPU oracle timed on a bounded sample of the headline workload).
@@ -87,7 +87,7 @@ def run_workload(name, steps, warmup, own_workspace, traffic_json, n_override=0)
     iters_run = results[-1].iters_run
     value = n * k * d * iters_run / (ms_per_step * 1e-3)
 
-    # ---- per-stage device times (HIP events recorded by the library on its stream), averaged over the steps
+    # ---- per-stage device times (clock stamps written by the library on its stream), averaged over the steps
     def avg(f):
         return float(np.mean([f(r) for r in results]))
 
@@ -209,7 +209,7 @@ def run_workload(name, steps, warmup, own_workspace, traffic_json, n_override=0)
                                    "progressive_gemm": flop_alg}[dom],
                     mfma_dtype="f16", mfma_flop_per_algorithmic_flop=SPLIT_PRODUCTS,
                     note="achieved = algorithmic flop (first-test GEMM 2nkd' + 128 per alive pair-block done densely) per "
-                         "pruned step / device time of the kernel's launches in that step (HIP events); peak = dense "
+                         "pruned step / device time of the kernel's launches in that step (clock stamps); peak = dense "
                          "fp16 MFMA peak (2500 TFLOP/s) / 3, because every fp32-class product costs three fp16 matrix "
                          "instructions; 'executed' in stages counts every dimension the tiles multiplied")
     if dom == "progressive_gemm":

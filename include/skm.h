@@ -69,7 +69,7 @@ typedef struct skm_trace_row {
   int32_t nblocks;     /* trailing 64-dim blocks (the last may be shorter) */
   int64_t enter[SKM_MAX_BLOCKS]; /* pairs that entered trailing block m (only when
                                     params.block_stats != 0, else zeros) */
-  float ms_tau;        /* stage times from HIP events on the call's stream */
+  float ms_tau;        /* stage times on the call's stream, from clock stamps that kernels at the borders write */
   float ms_gemm;
   float ms_prune;
   float ms_update;
@@ -82,11 +82,11 @@ typedef struct skm_trace {
   int32_t rows;        /* out: rows written */
   int32_t iters_run;   /* out: update steps performed */
   int32_t inc_updates; /* out: update steps done incrementally (from the points that changed cluster only) */
-  float ms_rotate;     /* out: the X~ = X R GEMM alone (events around its launch) */
+  float ms_rotate;     /* out: the X~ = X R GEMM alone (stamps around its launch) */
   float ms_init;       /* out: everything before iteration 1: workspace, R, rotation, initial centroids, ETR set-up */
   float ms_etr_gt;     /* out: ETR ground truth (0 when supplied or ETR off) */
   float ms_unrotate;   /* out: Y = Y~ R^T */
-  float ms_total;      /* out: whole call, device time (HIP events on the call's stream) */
+  float ms_total;      /* out: whole call, device time on the call's stream */
   float ms_host_total; /* out: whole call on the host clock, entry to return (skm_fit_ex, skm_assign_ex) */
   float ms_host_alloc; /* out: of that, getting the workspace (0 with params->workspace) */
   float ms_host_free;  /* out: of that, releasing it */
@@ -123,7 +123,7 @@ typedef struct skm_params {
   int64_t pair_budget;   /* 0 = default (2^29): capacity, in (point, centroid) pairs, of the list that carries pairs
                             from the dense tiles to the gather kernel; points are processed in chunks of rows
                             sized so that the list cannot overflow */
-  float dense_frac;      /* 0.0125 : a 128 x 128 tile keeps multiplying densely, 64 dimensions at a time, while more
+  float dense_frac;      /* 0.0125 : a 128 x 256 tile keeps multiplying densely, 64 dimensions at a time, while more
                             than this share of its pairs is alive; below it the alive pairs are finished one by
                             one by the gather kernel.  1 = hand over right after the first test (the paper's
                             split), 0 = dense tiles only.  Execution strategy only: the tests applied to a
