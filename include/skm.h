@@ -127,7 +127,9 @@ typedef struct skm_params {
                             than this share of its pairs is alive; below it the alive pairs are finished one by
                             one by the gather kernel.  1 = hand over right after the first test (the paper's
                             split), 0 = dense tiles only.  Execution strategy only: the tests applied to a
-                            pair, and so the result, do not depend on it */
+                            pair do not depend on it.  Where a pair changes over decides how its distance is rounded
+                            (the product form up to there, the direct form behind; 1e-7 of the squared norms): a
+                            point whose two nearest centroids are equally near to that rounding may get either */
   float sample_frac;     /* 0    : in (0, 1): run Algorithm 1 on a uniform sample of round(frac * n) rows (at least k),
                             then assign every point to the final centroids with the two-phase step (Section 4.4) */
   int32_t angular;       /* 0    : 1 = angular metric (Section 2, "Determining Assignments"): the rotated points are scaled
@@ -158,7 +160,8 @@ typedef struct skm_params {
                             rounding bound of the row's smallest approximate distance), and only those get their exact
                             distance.  0 = in pruned steps that follow a step which cut at least half of the pairs at the
                             first test, and in iteration 1 from 2048 centroids on; 1 = in every step; -1 = never.
-                            Execution strategy only: a pair the filter drops is dropped by the exact arithmetic too */
+                            Execution strategy only: a pair the filter drops is dropped by the exact arithmetic too
+                            (the distances of those it leaves are rounded as dense_frac says) */
   int32_t tau_group;     /* 0    : centroids after which a point's threshold tau is refreshed inside a step.  0 (= k):
                             tau keeps its initial value for the whole step, the only form this library runs (the
                             result is then independent of the order in which tiles are processed); any other value

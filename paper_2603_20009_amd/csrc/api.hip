@@ -1040,6 +1040,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   {
     CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
     cp.dprime = dprime; cp.nb = nb; cp.Ypdx = c.Ypdx; cp.ynp = c.ynp;
+    if (!have_prev && !found) { cp.ynorm = c.ynorm; cp.dn = dprime; }   // (for the product below)
     cp.Ys = c.Ys; cp.Yh = screen ? c.Yh : nullptr; cp.y_absmax = c.amax + Ctx::AM_Y;
     cp.ratio_out = c.ratio_dev;
     cp.stamp = tm.mark(sought ? ST_GEMM : ST_NONE);   // (the search for the incumbents ends here)
@@ -1053,7 +1054,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
     g0.a_absmax = c.amax + Ctx::AM_XR; g0.b_absmax = c.amax + Ctx::AM_Y;
     g0.b_presplit = c.Ys; g0.ldbs = c.ds + 32;
-    HIPCHK(gemm_argmin(g0, c.ynp, c.best, c.st));   // (row 0 of ynp: the norms over the first d' dimensions)
+    HIPCHK(gemm_argmin(g0, c.ynorm, c.best, c.st));
     if (c.group_now) {
       HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, c.flag}, c.st));
     } else {

@@ -457,8 +457,12 @@ hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32
 // it clears the words that the step counts into and writes the theta ratios, which arrive as kernel arguments.  A small
 // step is a chain of launches of a few microseconds each, and a memset or a copy from the host costs three launches:
 // with all five in one, a pruned step of 20 000 x 128 points against 100 centroids issues four commands fewer.
+// The order in which a norm's squares are added is part of the results (see unit_three in progressive.hip): for ynp the
+// dimensions of a piece of 16 and then the pieces, one after the other; for ynorm thread t adds the dimensions t, t + 256, ..
+// and the threads' sums are added pairwise.
 __global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, ThetaRatios ratios) {
-  __shared__ float s_pre[1025];   // ||y[0 : 16 p)||^2 at p (ds <= 16384)
+  __shared__ float s_piece[1024];   // ||y[16 p : 16 p + 16)||^2 at p (ds <= 16384)
+  __shared__ float s_red[4];
   const int c = blockIdx.x, tid = threadIdx.x;
   put_stamp(a.stamp);
   for (int64_t w = (int64_t)c * 256 + tid; w < a.clear_words; w += (int64_t)gridDim.x * 256) a.clear[w] = 0u;
@@ -476,41 +480,38 @@ __global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, The
     const int col = c0 + 4 * tid;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col < a.ds) v = *reinterpret_cast<const float4 *>(y + col);
-    const float q = quad_sum(fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w))));
-    if (col < a.ds) {
-      if ((tid & 3) == 0) s_pre[(col >> 4) + 1] = q;
-      if (a.Ys) emit_split(po, c, col, v);
+    if (a.ynp) {
+      // the 16 squares of a piece one after the other, handed from lane to lane of its quad: lane 3 ends with all of them
+      float q = 0.f;
+#pragma unroll
+      for (int l = 0; l < 4; ++l) {
+        if (l > 0) q = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, q), 0x90, 0xF, 0xF, true));   // quad_perm [0,0,1,2]
+        q = fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, fmaf(v.x, v.x, q))));
+      }
+      if ((tid & 3) == 3 && col < a.ds) s_piece[col >> 4] = q;
     }
+    if (col < a.ds && a.Ys) emit_split(po, c, col, v);
     if (col >= a.dprime && col < pdx_end) {
       const int t = col - a.dprime;
       if (col >= a.pdx_cols) v = make_float4(0.f, 0.f, 0.f, 0.f);
       *reinterpret_cast<float4 *>(a.Ypdx + ((int64_t)(t / kBlockDims) * a.k + c) * kBlockDims + t % kBlockDims) = v;
     }
   }
-  if (!a.ynorm && !a.ynp) return;
-  if (tid == 0) s_pre[0] = 0.f;
-  __syncthreads();
-  if (tid < 64) {   // inclusive scan of the pieces, 64 at a time
-    const int np = a.ds >> 4;
-    float carry = 0.f;
-    for (int p0 = 0; p0 < np; p0 += 64) {
-      float v = p0 + tid < np ? s_pre[p0 + tid + 1] : 0.f;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float u = __shfl_up(v, o, 64);
-        if (tid >= o) v += u;
-      }
-      v += carry;
-      if (p0 + tid < np) s_pre[p0 + tid + 1] = v;
-      carry = __shfl(v, 63, 64);
-    }
+  if (a.ynorm) {
+    float s = 0.f;
+    for (int j = tid; j < a.dn; j += 256) s = fmaf(y[j], y[j], s);
+    s = wave_sum(s);
+    if ((tid & 63) == 0) s_red[tid >> 6] = s;
   }
   __syncthreads();
-  if (a.ynorm && tid == 0) a.ynorm[c] = s_pre[a.dn >> 4];
+  if (a.ynorm && tid == 0) a.ynorm[c] = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
   if (a.ynp)
     for (int m = tid; m <= a.nb; m += 256) {
-      const int t = m == a.nb ? a.ds : min(a.ds, a.dprime + kBlockDims * m);
-      a.ynp[(int64_t)m * a.k + c] = s_pre[t >> 4];
+      const int np = (m == a.nb ? a.ds : min(a.ds, a.dprime + kBlockDims * m)) >> 4;
+      float acc = 0.f;
+#pragma unroll 8
+      for (int p = 0; p < np; ++p) acc += s_piece[p];   // (in order, whatever d' is)
+      a.ynp[(int64_t)m * a.k + c] = acc;
     }
 }
 

@@ -1,6 +1,8 @@
 """The forms that a kernel takes by size, type or alignment, at the sizes where one hands over to another: each against the
 CPU oracle (fp64) or against the form next to it."""
+import os
 import threading
+import zlib
 
 import numpy as np
 import pytest
@@ -152,3 +154,24 @@ def test_recall_at_the_borders_of_its_forms(skm, orc, dg, k):  # noqa: F811
     got = skm.fit(cuda(X), k, 2, 2, skm.FitOptions(R=cuda(R), queries=cuda(Q), **kw))
     for g, r in zip(got.trace[:2], ref.trace):
         assert g["recall"] == pytest.approx(r["recall"], abs=2.0 / (nq * K))   # (a near-tie may move one neighbour or one probe)
+
+
+# A split leaves two centroids at y (1 +- 1/1024); the points between them are decided by the last bits of their distances,
+# and one that falls the other way moves every later centroid of the two.  The order in which products and norms are added
+# therefore stays what it is: the labels of these fits (all split an empty cluster) are pinned bit by bit.
+def test_labels_of_fits_that_split_a_cluster_are_pinned(skm):  # noqa: F811
+    n, d, k = 20_000, 128, 100
+    scale = (1.0 - 0.9 * np.arange(d) / (d - 1)).astype(np.float32)
+    with open(os.path.join(os.path.dirname(__file__), "golden", "split_fit_labels.txt")) as f:
+        pins = [line.split() for line in f if not line.startswith("#")]
+    other = []
+    for seed, crc in pins:
+        say("pinned fit", seed)
+        rng = np.random.default_rng(int(seed))
+        means = rng.standard_normal((k, d), dtype=np.float32)
+        X = rng.standard_normal((n, d), dtype=np.float32) * scale + means[rng.integers(0, k, n)]
+        r = skm.fit(cuda(X), k, 10, int(seed))
+        assert sum(t["nempty"] for t in r.trace) > 0
+        if zlib.crc32(r.assign.cpu().numpy().tobytes()) != int(crc, 16):
+            other.append(seed)
+    assert not other
