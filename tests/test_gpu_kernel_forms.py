@@ -175,3 +175,16 @@ def test_labels_of_fits_that_split_a_cluster_are_pinned(skm):  # noqa: F811
         if zlib.crc32(r.assign.cpu().numpy().tobytes()) != int(crc, 16):
             other.append(seed)
     assert not other
+
+
+# The last 256 rows are projected and factorised twice: the matrix before rounding is orthogonal to some 1e-14, and with one
+# pass less an entry of each of these rounds to the other side.
+def test_rotation_matrices_are_pinned(skm):  # noqa: F811
+    with open(os.path.join(os.path.dirname(__file__), "golden", "rotations.txt")) as f:
+        pins = [line.split() for line in f if not line.startswith("#")]
+    other = []
+    for d, seed, crc in pins:
+        say("pinned rotation", d, seed)
+        if zlib.crc32(skm.make_rotation(int(d), int(seed)).cpu().numpy().tobytes()) != int(crc, 16):
+            other.append((d, seed))
+    assert not other
