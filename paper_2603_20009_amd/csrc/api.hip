@@ -199,6 +199,8 @@ struct Pool {
 // so one wait per step covers all of them (a copy into pageable memory waits for its own staging).  Blocks are kept
 // in a per-thread cache and reused by later calls on that thread (the hierarchical fit runs hundreds of small fits);
 // worker threads release their cache before they end, that of a caller's thread stays until the process ends.
+// Whoever gives a block back has waited for every kernel that may write into it: the next call on the thread, on whatever
+// stream, takes it at once.
 struct PinnedCache {
   std::vector<std::pair<void *, size_t>> idle;
   void *take(size_t bytes, size_t *cap) {
@@ -226,13 +228,15 @@ struct PinnedCache {
 };
 thread_local PinnedCache tl_pinned;
 
-// one page-locked word that a kernel writes and the host reads once it has waited for the stream
+// one page-locked word that a kernel on the stream writes and the host reads once it has waited for the stream
 struct PinnedWord {
   volatile unsigned int *host = nullptr;
   unsigned int *dev = nullptr;
   void *block = nullptr;
   size_t cap = 0;
-  PinnedWord() {
+  hipStream_t st;
+  bool waited = false;   // (left false by a call that returns on the way: the destructor waits)
+  explicit PinnedWord(hipStream_t stream) : st(stream) {
     block = tl_pinned.take(sizeof(unsigned int), &cap);
     void *dv = nullptr;
     if (!block || hipHostGetDevicePointer(&dv, block, 0) != hipSuccess) return;
@@ -240,7 +244,14 @@ struct PinnedWord {
     dev = static_cast<unsigned int *>(dv);
   }
   ~PinnedWord() {
-    if (block) tl_pinned.give(block, cap);
+    if (!block) return;
+    if (!waited) (void)hipStreamSynchronize(st);
+    tl_pinned.give(block, cap);
+  }
+  int wait() {
+    HIPCHK(hipStreamSynchronize(st));
+    waited = true;
+    return SKM_OK;
   }
   PinnedWord(const PinnedWord &) = delete;
   PinnedWord &operator=(const PinnedWord &) = delete;
@@ -272,11 +283,15 @@ struct StageTimer {
   double ms_per_tick = 1e-5;
   std::vector<std::pair<int, size_t>> marks;   // (stage, stamp)
   std::vector<size_t> first;                   // first mark of every step
-  explicit StageTimer(bool enable) : on(enable) {}
+  hipStream_t st;
+  bool waited = false;   // the call has waited for its stream behind the last stamp (left false by one that returns on the way)
+  StageTimer(bool enable, hipStream_t stream) : on(enable), st(stream) {}
   StageTimer(const StageTimer &) = delete;
   StageTimer &operator=(const StageTimer &) = delete;
   ~StageTimer() {
-    if (block) tl_pinned.give(block, block_bytes);
+    if (!block) return;
+    if (!waited) (void)hipStreamSynchronize(st);
+    tl_pinned.give(block, block_bytes);
   }
   // room for so many stamps (further ones are not taken)
   int init(size_t stamps) {
@@ -497,6 +512,13 @@ int check_shape(const void *X, int64_t n, int32_t d, int32_t k, bool fit = true)
   if (n < 1 || n >= (int64_t)1 << 31) return fail(SKM_EINVAL, "n out of range [1, 2^31)");
   if (d < 16 || d > 16384) return fail(SKM_EINVAL, "d out of range [16, 16384]");
   if (k < 1 || (fit && k > n) || k > (1 << 24)) return fail(SKM_EINVAL, "k out of range [1, min(n, 2^24)]");
+  return SKM_OK;
+}
+
+// the caller's initial rows, if there are any (checked before anything is enqueued)
+int check_init_idx(const skm_params &p, int64_t n, int32_t k) {
+  for (int32_t i = 0; p.init_idx && i < k; ++i)
+    if (p.init_idx[i] < 0 || p.init_idx[i] >= n) return fail(SKM_EINVAL, "init_idx out of range");
   return SKM_OK;
 }
 
@@ -1553,14 +1575,11 @@ int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const fl
                       unsigned int *amax_x, unsigned int *amax_q, unsigned long long *gt_keys, hipStream_t st) {
   const GtPlan plan = gt_plan(n, d, nq, K);
   if (plan.on) {
-    PinnedWord over;
+    PinnedWord over(st);
     if (!over.host) return fail(SKM_EHIP, "hipHostMalloc failed");
     *over.host = 0u;
-    if (int rc = ground_truth_screened(pool, plan, X, n, d, Q, nq, K, gt_keys, over.dev, st)) {
-      (void)hipStreamSynchronize(st);
-      return rc;
-    }
-    HIPCHK(hipStreamSynchronize(st));
+    if (int rc = ground_truth_screened(pool, plan, X, n, d, Q, nq, K, gt_keys, over.dev, st)) return rc;
+    if (int rc = over.wait()) return rc;
     if (!*over.host) return SKM_OK;
   }
   return ground_truth_full(pool, X, n, d, Q, nq, K, amax_x, amax_q, gt_keys, st);
@@ -1600,6 +1619,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (p.angular) return fail(SKM_EINVAL, "the angular metric is not combined with sample_frac");
     return fit_sampled(X, n, d, k, iters, seed, p, centroids_out, assign_out, dist_out);
   }
+  if ((rc = check_init_idx(p, n, k))) return rc;
 
   // the workspace in one piece (the caller's, if it lends one): the context's buffers, the rotated points, the rotation
   // matrices and their generator, the ETR buffers
@@ -1615,7 +1635,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   // stage times are taken only for a caller that asked for the trace (a small fit inside the hierarchical fit spends
   // a third of its host time creating and reading events otherwise)
   const bool timed = tr != nullptr;
-  StageTimer tm(timed);
+  StageTimer tm(timed, c.st);
   if ((rc = tm.init(64 + (size_t)(std::min(iters, 4096) + 2) * 64))) return rc;
   Events evs;   // of the second stream below
   size_t t_begin = 0, t_rot0 = 0, t_rot = 0, t_unrot0 = 0, t_unrot1 = 0, t_end = 0, t_gt0 = 0, t_gt1 = 0;
@@ -1689,21 +1709,18 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (!c.idx_host) idx_big.resize((size_t)k);
     int64_t *idx = c.idx_host ? c.idx_host : idx_big.data();
     if (p.init_idx) {
-      for (int32_t i = 0; i < k; ++i) {
-        idx[i] = p.init_idx[i];
-        if (idx[i] < 0 || idx[i] >= n) return fail(SKM_EINVAL, "init_idx out of range");
-      }
+      std::copy(p.init_idx, p.init_idx + k, idx);
     } else {
       sample_rows(seed, STREAM_INIT, n, k, idx);
     }
     const int64_t *idx_view = c.idx_dev_view;
+    c.pending = true;   // (the block is in use until the first step has been waited for)
     if (k > 1024) {
       int64_t *idx_dev = nullptr;
       HIPCHK(c.pool.get(&idx_dev, (size_t)k));
       HIPCHK(hipMemcpyAsync(idx_dev, idx, sizeof(int64_t) * (size_t)k, hipMemcpyHostToDevice, c.st));
       idx_view = idx_dev;
     }
-    c.pending = true;   // (the block is in use until the first step has been waited for)
     HIPCHK(launch_gather_rows(c.Xr, c.ldx, c.ds, idx_view, k, c.Y, c.ds, c.ds, c.st, c.amax + Ctx::AM_Y,
                               tm.point(&t_rot)));   // (the rotation has ended where this starts)
     c.y_amax_valid = true;
@@ -1872,6 +1889,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     t_end = tm.marks.back().second;   // the last kernel's end
   }
   c.pending = false;
+  tm.waited = true;
   if (dprime_out) *dprime_out = dprime;
   if (tr) {
     tr->rows = std::min(rows, tr->capacity);
@@ -1911,6 +1929,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
     return fail(SKM_EINVAL, "the host-resident fit is not combined with ETR, the angular metric or sample_frac");
   skm_trace *tr = p.trace;
   if (tr && (!tr->row || tr->capacity < 1)) return fail(SKM_EINVAL, "trace without rows");
+  if ((rc = check_init_idx(p, n, k))) return rc;
 
   // rows per batch: a multiple of 128 (whole tiles; the per-point arrays of a batch then start 512-byte aligned)
   int64_t W = batch_rows > 0 ? batch_rows : (int64_t)131072;
@@ -1931,7 +1950,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   c.ds = round_up(d, 16);
   c.block_stats = p.block_stats != 0;
   c.screen_mode = p.screen;
-  StageTimer tm(tr != nullptr);
+  StageTimer tm(tr != nullptr, c.st);
   Events evs;
   hipEvent_t e_begin = evs.next(), e_init = evs.next(), e_end0 = evs.next(), e_end = evs.next();
   hipEvent_t ev_copied[2] = {evs.next(), evs.next()}, ev_free[2] = {evs.next(), evs.next()};
@@ -1973,10 +1992,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   {
     std::vector<int64_t> idx((size_t)k);
     if (p.init_idx) {
-      for (int32_t i = 0; i < k; ++i) {
-        idx[(size_t)i] = p.init_idx[i];
-        if (idx[(size_t)i] < 0 || idx[(size_t)i] >= n) return fail(SKM_EINVAL, "init_idx out of range");
-      }
+      std::copy(p.init_idx, p.init_idx + k, idx.begin());
     } else {
       sample_rows(seed, STREAM_INIT, n, k, idx.data());
     }
@@ -2110,6 +2126,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   }
   HIPCHK(hipEventRecord(e_end, c.st));
   HIPCHK(hipStreamSynchronize(c.st));
+  tm.waited = true;
   HIPCHK(hipStreamSynchronize(cs.s));
   if (tr) {
     tr->rows = std::min(rows_out, tr->capacity);
@@ -2146,7 +2163,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   c.ds = round_up(d, 16);
   c.block_stats = p.block_stats != 0;
   c.screen_mode = p.screen;
-  StageTimer tm(tr != nullptr && tr->row && tr->capacity >= 1);
+  StageTimer tm(tr != nullptr && tr->row && tr->capacity >= 1, c.st);
   if ((rc = tm.init(256))) return rc;
   Rot rot;
   float *Xr_own = nullptr;
@@ -2212,6 +2229,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     }
     HIPCHK(hipStreamSynchronize(c.st));
   }
+  tm.waited = true;   // (the step itself ends with a wait)
   if (tr && tr->row && tr->capacity >= 1) {
     fill_row(tr->row[0], ss, n, k, 0, -1.0);
     fill_times(tr->row[0], tm, 0);
@@ -2786,12 +2804,12 @@ int skm_update(const float *X, int64_t n, int32_t d, const int32_t *assign, int3
   HIPCHK(pool.get(&w.order, (size_t)n));
   if (stable) HIPCHK(pool.get(&w.base, (size_t)stable_order_words(n, k)));
   HIPCHK(pool.get(&w.partial, (size_t)w.max_segments * ds));
-  PinnedWord bad;
+  PinnedWord bad(st);
   if (!bad.host) return fail(SKM_EHIP, "hipHostMalloc failed");
   const UnsafeLabels unsafe{flag, bad.dev, counts_out};
   HIPCHK(launch_fill_u32(flag, 1, 0u, st));
   HIPCHK(launch_update(X, d, n, d, assign, k, w, centroids, d, st, nullptr, nullptr, 0, -1, &unsafe));
-  HIPCHK(hipStreamSynchronize(st));
+  if (int wrc = bad.wait()) return wrc;
   ws.finished();
   if (*bad.host) return fail(SKM_EINVAL, "assignment label outside [0, k)");
   return SKM_OK;

@@ -188,3 +188,34 @@ def test_rotation_matrices_are_pinned(skm):  # noqa: F811
         if zlib.crc32(skm.make_rotation(int(d), int(seed)).cpu().numpy().tobytes()) != int(crc, 16):
             other.append((d, seed))
     assert not other
+
+
+# A call that ends with an error leaves no kernel behind that could still write into its page-locked blocks (the next call of
+# the thread, on whatever stream, takes them): initial rows out of range are refused before anything is enqueued, and what
+# is only seen later is returned once the stream has been waited for.
+def test_calls_that_end_with_an_error_leave_nothing_running(skm, dg):  # noqa: F811
+    n, d, k = 60_000, 512, 16
+    X = dg.mixture(n, d, 40, 3, "linear", "cuda")
+    ws = torch.full((skm.workspace_bytes(n, d, k),), 0xA5, dtype=torch.uint8, device="cuda")
+    rows = list(range(k - 1))
+    torch.cuda.synchronize()
+    for bad in (n, -1):
+        with pytest.raises(skm.SkmError, match="init_idx"):
+            skm.fit(X, k, 3, 1, skm.FitOptions(init_idx=rows + [bad], workspace=ws))
+        assert torch.cuda.current_stream().query()
+        assert bool((ws == 0xA5).all())
+        with pytest.raises(skm.SkmError, match="init_idx"):
+            skm.fit_host(X[:1000].cpu(), k, 2, 1, opts=skm.FitOptions(init_idx=rows + [bad]))
+    with pytest.raises(skm.SkmError, match="nq > n"):
+        skm.fit(X, k, 3, 1, skm.FitOptions(etr=True, nq=n + 1))
+    assert torch.cuda.current_stream().query()
+    # the thread's next calls, on another stream
+    labels = torch.arange(n, device="cuda", dtype=torch.int32) % k
+    Y = torch.zeros(k, d, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        counts = skm.update(X, labels, Y)
+        a, _, row = skm.assign(X, Y, labels)
+    torch.cuda.synchronize()
+    assert torch.equal(counts.cpu(), torch.bincount(labels.cpu(), minlength=k).int())
+    assert row["ms_step"] > 0 and int(a.min()) >= 0 and int(a.max()) < k
