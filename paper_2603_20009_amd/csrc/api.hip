@@ -330,16 +330,6 @@ struct StageTimer {
     waiting = used++;
     marks.push_back({stage, waiting});
   }
-  void point_next(size_t *at) {
-    if (waiting == kNone) waiting = used++;
-    *at = waiting;
-  }
-  // ... and no such kernel follows
-  hipError_t flush(hipStream_t st) {
-    const size_t at = waiting;
-    waiting = kNone;
-    return on && at < cap ? launch_stamp(dev + at, st) : hipSuccess;
-  }
   void begin_step() { first.push_back(marks.size()); }
   // the border that ends a stretch of `stage` (and starts the next)
   stamp_t *mark(int stage) {
@@ -628,7 +618,8 @@ struct Ctx {
     }
     return SKM_OK;
   }
-  // the last kernel of a step, and the wait for it
+  // the last kernel of a step, and the wait for it (a step whose flag is set by then leaves labels and distances, which may
+  // be the caller's arrays, as they are)
   int close_step(stamp_t *start = nullptr, stamp_t *end = nullptr) {
     FinalizeArgs f{best, prev_counts ? prev : nullptr, n, assign, dist, up.cnt, k, flag};
     f.done = done; f.obj_partial = obj_partial; f.change_start = change_start; f.scal = scal; f.report = report_dev;
@@ -1638,7 +1629,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   StageTimer tm(timed, c.st);
   if ((rc = tm.init(64 + (size_t)(std::min(iters, 4096) + 2) * 64))) return rc;
   Events evs;   // of the second stream below
-  size_t t_begin = 0, t_rot0 = 0, t_rot = 0, t_unrot0 = 0, t_unrot1 = 0, t_end = 0, t_gt0 = 0, t_gt1 = 0;
+  size_t t_begin = 0, t_rot0 = 0, t_rot = 0, t_unrot0 = 0, t_end = 0, t_gt0 = 0, t_gt1 = 0;
   rc = c.alloc_bounds(tm.point(&t_begin));
   if (rc) return rc;
 
@@ -1846,8 +1837,31 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (stop) break;
   }
 
-  // ---- Algorithm 1, last line: Y = Y~ R^T (before the final assignment, which does not change the centroids: one wait
-  // then ends both)
+  // ---- final assignment with the two-phase approach (Section 3.3)
+  bool written = false;   // the outputs per point are in the caller's arrays
+  if (p.final_assign) {
+    StepStats ss;
+    std::swap(c.assign, c.prev);
+    c.regroup_ok = false;
+    written = !c.permuted;   // points in the caller's order: the last kernel writes the caller's arrays
+    if (written && assign_out) c.assign = assign_out;
+    if (written && dist_out) c.dist = dist_out;
+    tm.begin_step();
+    rc = step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
+    if (rc) return rc;
+    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, 0, -1.0);
+    ++rows;
+  }
+  if (c.permuted) {   // per-point results back in the caller's order
+    if (assign_out) HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
+    if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
+  } else if (!written) {
+    if (assign_out) HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+    if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
+  }
+
+  // ---- Algorithm 1, last line: Y = Y~ R^T (behind the final assignment, which does not change the centroids: a call that
+  // fails there has written none of its outputs)
   if (p.rotate) {
     rc = unrotate_into(c.Y, c.ds, k, d, c.ds, rot, centroids_out, c.st, c.y_amax_valid ? c.amax + Ctx::AM_Y : nullptr,
                        tm.point(&t_unrot0));
@@ -1856,38 +1870,8 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     HIPCHK(hipMemcpy2DAsync(centroids_out, sizeof(float) * (size_t)d, c.Y, sizeof(float) * (size_t)c.ds,
                             sizeof(float) * (size_t)d, (size_t)k, hipMemcpyDeviceToDevice, c.st));
   }
-  tm.point_next(&t_unrot1);
-  if (!p.final_assign) HIPCHK(tm.flush(c.st));
-
-  // ---- final assignment with the two-phase approach (Section 3.3)
-  bool waited = false;
-  if (p.final_assign) {
-    StepStats ss;
-    std::swap(c.assign, c.prev);
-    c.regroup_ok = false;
-    const bool direct = !c.permuted;   // points in the caller's order: the last kernel writes the caller's arrays
-    if (direct && assign_out) c.assign = assign_out;
-    if (direct && dist_out) c.dist = dist_out;
-    tm.begin_step();
-    rc = step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
-    if (rc) return rc;
-    if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, 0, -1.0);
-    ++rows;
-    waited = direct;
-  }
-  if (c.permuted) {   // per-point results back in the caller's order
-    if (assign_out) HIPCHK(launch_scatter_by_index(c.assign, c.pos_to_id, n, assign_out, c.st));
-    if (dist_out) HIPCHK(launch_scatter_by_index(c.dist, c.pos_to_id, n, dist_out, c.st));
-  } else if (!p.final_assign) {
-    if (assign_out) HIPCHK(hipMemcpyAsync(assign_out, c.assign, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-    if (dist_out) HIPCHK(hipMemcpyAsync(dist_out, c.dist, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, c.st));
-  }
-  if (!waited) {
-    HIPCHK(launch_stamp(tm.point(&t_end), c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
-  } else if (!tm.marks.empty()) {
-    t_end = tm.marks.back().second;   // the last kernel's end
-  }
+  HIPCHK(launch_stamp(tm.point(&t_end), c.st));
+  HIPCHK(hipStreamSynchronize(c.st));
   c.pending = false;
   tm.waited = true;
   if (dprime_out) *dprime_out = dprime;
@@ -1898,7 +1882,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     tr->ms_rotate = p.rotate ? tm.between(t_rot0, t_rot) : 0.f;
     tr->ms_init = tm.marks.empty() ? 0.f : tm.between(t_begin, tm.marks.front().second);
     tr->ms_etr_gt = t_gt1 > t_gt0 ? tm.between(t_gt0, t_gt1) : 0.f;
-    tr->ms_unrotate = p.rotate ? tm.between(t_unrot0, t_unrot1) : 0.f;
+    tr->ms_unrotate = p.rotate ? tm.between(t_unrot0, t_end) : 0.f;
     tr->ms_total = tm.between(t_begin, t_end);
     for (int32_t q = 0; q < tr->rows; ++q) fill_times(tr->row[q], tm, (size_t)q);
   }
@@ -2193,7 +2177,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     rc = c.measure_xr();
     if (rc) return rc;
   }
-  c.prev_in = prev_assign;   // checked and copied at the start of the step; a bad label leaves the outputs untouched
+  c.prev_in = prev_assign;   // checked and copied at the start of the step; a bad label leaves the outputs untouched (close_step)
   // Many centroids: a step on its own pays for what a fit does once in its third step.  The points are rewritten
   // grouped by their incumbents and the first filter runs in front of the exact kernel (a million tiles of two slabs
   // each otherwise: the fixed costs of a tile, not the arithmetic, are then the whole run time).

@@ -407,7 +407,7 @@ struct StepReport {
   int32_t pad;
   unsigned long long scal[SC_COUNT];   // the step scalars, replicas added up; SC_CHANGED = points with another label than prev
 };
-// Unpack best -> assign, dist; cluster sizes into cnt[k] (zero before).  With `done` (a zero word) the launch also closes
+// Unpack best -> assign, dist (not if *flag is set already); cluster sizes into cnt[k] (zero before).  With `done` (a zero word) the launch also closes
 // the step: see finalize_assign_kernel.
 struct FinalizeArgs {
   const unsigned long long *best;

@@ -667,6 +667,7 @@ hipError_t launch_normalize_rows(float *A, int64_t lda, int64_t rows, int32_t co
 // Small inputs (one small fit of many, as in the hierarchical fit) take 1024 points per workgroup instead: the
 // launch is then a few workgroups side by side rather than one long loop.  They count in LDS as well where a cluster
 // holds more than a handful of the points (direct increments of 20 000 points on 100 counters: 54 us, in LDS: 5 us).
+// Where *flag is set before the launch, labels and distances are left as they are (the caller's arrays of a refused call).
 // The last workgroup to finish closes the step: it adds the objective's partials and the counter replicas in a fixed
 // order, takes the number of empty clusters and the largest size, turns the per-workgroup counts of changed points into
 // starts (for the incremental update), and writes the step's report straight into page-locked host memory.
@@ -692,6 +693,8 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     for (int b = tid; b < a.k; b += FIN_THREADS) s_hist[b] = 0;
     __syncthreads();
   }
+  // (flags of the kernels before this one: a label out of range, a list that ran over)
+  const bool refused = a.flag && load_agent(a.flag) != 0u;
   double s = 0.0;
   unsigned int ch = 0;
   const int64_t base = (int64_t)blockIdx.x * per_block;
@@ -706,8 +709,10 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
         dv = 0.f;
         if (a.flag) atomicOr(a.flag, 2u);   // bit 1: unset point (bit 0 is the hand-over list's overflow)
       }
-      a.assign[i] = l;
-      if (a.dist) a.dist[i] = dv;
+      if (!refused) {
+        a.assign[i] = l;
+        if (a.dist) a.dist[i] = dv;
+      }
       if (in_lds) atomicAdd(&s_hist[l], 1);
       else if (a.cnt) atomicAdd(a.cnt + l, 1);
       if (a.prev) ch += (a.prev[i] != l);

@@ -219,3 +219,33 @@ def test_calls_that_end_with_an_error_leave_nothing_running(skm, dg):  # noqa: F
     torch.cuda.synchronize()
     assert torch.equal(counts.cpu(), torch.bincount(labels.cpu(), minlength=k).int())
     assert row["ms_step"] > 0 and int(a.min()) >= 0 and int(a.max()) < k
+
+
+# An assignment with a label outside [0, k) is refused and leaves the outputs as they are, also where they are the labels
+# that came in: in a step that writes the caller's arrays itself, and in one that groups the points first (k >= 4096).
+@pytest.mark.parametrize("n,d,k", [(500, 64, 10), (3000, 100, 37), (40_000, 32, 4100)])
+def test_refused_labels_leave_the_outputs_as_they_are(skm, dg, n, d, k):  # noqa: F811
+    import ctypes as C
+    say("refused labels", n, d, k)
+    L = skm.lib()
+    vp = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    X = dg.mixture(n, d, 20, 5, "linear", "cuda")
+    Y = X[:k].contiguous()
+    for bad in (k, -1):
+        prev = torch.zeros(n, dtype=torch.int32, device="cuda")
+        prev[n // 2] = bad
+        kept = prev.clone()
+        a = torch.full((n,), -9, dtype=torch.int32, device="cuda")
+        dist = torch.full((n,), -3.0, device="cuda")
+        torch.cuda.synchronize()
+        assert L.skm_assign_ex(vp(X), n, d, vp(Y), k, vp(prev), 0, None, vp(a), vp(dist)) == -1
+        assert L.skm_assign_ex(vp(X), n, d, vp(Y), k, vp(prev), 0, None, vp(prev), vp(dist)) == -1
+        torch.cuda.synchronize()
+        assert bool((a == -9).all()) and bool((dist == -3.0).all()) and torch.equal(prev, kept)
+    # in place, with labels that are good
+    prev = torch.zeros(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    assert L.skm_assign_ex(vp(X), n, d, vp(Y), k, vp(prev), 0, None, vp(prev), vp(dist)) == 0
+    b, dist_b, _ = skm.assign(X, Y, torch.zeros(n, dtype=torch.int32, device="cuda"), opts=skm.FitOptions(R=skm.make_rotation(d, 0)))
+    torch.cuda.synchronize()
+    assert torch.equal(prev, b) and torch.equal(dist, dist_b)
