@@ -339,7 +339,9 @@ int32_t skm_dprime_adjust(int32_t d, int32_t dprime, double prune_frac, float lo
 void skm_debug_gemm_config(int32_t tile256, int32_t panel_cols, int64_t max_tiles);
 
 /* Calls that were lent no workspace keep the device block they worked in for the next such call (at most 4 GiB over all
- * devices and threads); this gives what is held back to the device.  Safe at any time, from any thread. */
+ * devices and threads); this gives what is held back to the device.  Safe at any time, from any thread.  Other allocators
+ * of the process cannot see these blocks: call it where one of them runs out (the Python binding does so for the tensors
+ * that it allocates itself). */
 void skm_release_memory(void);
 
 const char *skm_strerror(int rc);

@@ -141,6 +141,16 @@ def _dev(t: torch.Tensor, dtype, name: str):
     return C.c_void_p(t.data_ptr())
 
 
+def _empty(*args, **kwargs) -> torch.Tensor:
+    """torch.empty; if the device has no room, once more without the blocks that the library keeps between calls (which
+    torch's allocator cannot see)."""
+    try:
+        return torch.empty(*args, **kwargs)
+    except torch.OutOfMemoryError:
+        release_memory()
+        return torch.empty(*args, **kwargs)
+
+
 def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
@@ -261,7 +271,7 @@ def _lend_workspace(p: Params, o: FitOptions, n: int, d: int, k: int, device, ke
         p.workspace_bytes = o.workspace.numel()
         return
     nbytes = hier_workspace_bytes(n, d, k, p) if hierarchical else workspace_bytes(n, d, k, p)
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    ws = _empty(nbytes, dtype=torch.uint8, device=device)
     keep.append(ws)
     p.workspace = ws.data_ptr()
     p.workspace_bytes = nbytes
@@ -284,9 +294,9 @@ def fit(X: torch.Tensor, k: int, iters: int, seed: int, opts: FitOptions | None 
     tr = _new_trace(iters + 1, keep)
     p = _params(o, keep, tr)
     _lend_workspace(p, o, n, d, k, X.device, keep)
-    cent = torch.empty((k, d), device=X.device, dtype=torch.float32)
-    assign = torch.empty(n, device=X.device, dtype=torch.int32)
-    dist = torch.empty(n, device=X.device, dtype=torch.float32)
+    cent = _empty((k, d), device=X.device, dtype=torch.float32)
+    assign = _empty(n, device=X.device, dtype=torch.int32)
+    dist = _empty(n, device=X.device, dtype=torch.float32)
     rc = lib().skm_fit_ex(_dev(X, torch.float32, "X"), n, d, k, iters, C.c_uint64(seed), C.byref(p),
                           C.c_void_p(cent.data_ptr()), C.c_void_p(assign.data_ptr()), C.c_void_p(dist.data_ptr()))
     _check(rc)
@@ -308,9 +318,9 @@ def fit_hierarchical(X: torch.Tensor, k: int, seed: int, meso_iters: int = 3, fi
     tr = _new_trace(meso_iters + 2, keep)
     p = _params(o, keep, tr)
     _lend_workspace(p, o, n, d, k, X.device, keep, hierarchical=True)
-    cent = torch.empty((k, d), device=X.device, dtype=torch.float32)
-    assign = torch.empty(n, device=X.device, dtype=torch.int32)
-    dist = torch.empty(n, device=X.device, dtype=torch.float32)
+    cent = _empty((k, d), device=X.device, dtype=torch.float32)
+    assign = _empty(n, device=X.device, dtype=torch.int32)
+    dist = _empty(n, device=X.device, dtype=torch.float32)
     sizes = (C.c_int64 * km)()
     counts = (C.c_int32 * km)()
     rc = lib().skm_fit_hierarchical(_dev(X, torch.float32, "X"), n, d, k, meso_iters, fine_iters, C.c_uint64(seed),
@@ -334,7 +344,7 @@ def fit_host(X_host: torch.Tensor, k: int, iters: int, seed: int, batch_rows: in
     keep: list = []
     tr = _new_trace(iters + 1, keep)
     p = _params(o, keep, tr)
-    cent = torch.empty((k, d), device=device, dtype=torch.float32)
+    cent = _empty((k, d), device=device, dtype=torch.float32)
     assign = torch.empty(n, dtype=torch.int32, pin_memory=True)
     dist = torch.empty(n, dtype=torch.float32, pin_memory=True)
     rc = lib().skm_fit_host(C.c_void_p(X_host.data_ptr()), n, d, k, iters, C.c_uint64(seed), C.byref(p), batch_rows,
@@ -348,8 +358,8 @@ def fit_host(X_host: torch.Tensor, k: int, iters: int, seed: int, batch_rows: in
 def fit_default(X: torch.Tensor, k: int, iters: int, seed: int):
     """skm_fit: default parameters, default stream."""
     n, d = X.shape
-    cent = torch.empty((k, d), device=X.device, dtype=torch.float32)
-    assign = torch.empty(n, device=X.device, dtype=torch.int32)
+    cent = _empty((k, d), device=X.device, dtype=torch.float32)
+    assign = _empty(n, device=X.device, dtype=torch.int32)
     torch.cuda.synchronize()
     _check(lib().skm_fit(_dev(X, torch.float32, "X"), n, d, k, iters, C.c_uint64(seed), C.c_void_p(cent.data_ptr()),
                          C.c_void_p(assign.data_ptr())))
@@ -366,8 +376,8 @@ def assign(X: torch.Tensor, centroids: torch.Tensor, prev: torch.Tensor | None =
     tr = _new_trace(1, keep)
     p = _params(o, keep, tr)
     _lend_workspace(p, o, n, d, k, X.device, keep)
-    a = torch.empty(n, device=X.device, dtype=torch.int32)
-    dist = torch.empty(n, device=X.device, dtype=torch.float32)
+    a = _empty(n, device=X.device, dtype=torch.int32)
+    dist = _empty(n, device=X.device, dtype=torch.float32)
     pv = None if prev is None else _dev(prev, torch.int32, "prev")
     rc = lib().skm_assign_ex(_dev(X, torch.float32, "X"), n, d, _dev(centroids, torch.float32, "centroids"), k, pv,
                              dprime, C.byref(p), C.c_void_p(a.data_ptr()), C.c_void_p(dist.data_ptr()))
@@ -379,8 +389,8 @@ def assign_default(X: torch.Tensor, centroids: torch.Tensor, prev: torch.Tensor 
     """skm_assign: default parameters, default stream, rotation from seed 0."""
     n, d = X.shape
     k = centroids.shape[0]
-    a = torch.empty(n, device=X.device, dtype=torch.int32)
-    dist = torch.empty(n, device=X.device, dtype=torch.float32)
+    a = _empty(n, device=X.device, dtype=torch.int32)
+    dist = _empty(n, device=X.device, dtype=torch.float32)
     pv = None if prev is None else _dev(prev, torch.int32, "prev")
     torch.cuda.synchronize()
     _check(lib().skm_assign(_dev(X, torch.float32, "X"), n, d, _dev(centroids, torch.float32, "centroids"), k, pv,
@@ -391,8 +401,8 @@ def assign_default(X: torch.Tensor, centroids: torch.Tensor, prev: torch.Tensor 
 def assign_exact(X: torch.Tensor, centroids: torch.Tensor):
     n, d = X.shape
     k = centroids.shape[0]
-    a = torch.empty(n, device=X.device, dtype=torch.int32)
-    dist = torch.empty(n, device=X.device, dtype=torch.float32)
+    a = _empty(n, device=X.device, dtype=torch.int32)
+    dist = _empty(n, device=X.device, dtype=torch.float32)
     _check(lib().skm_assign_exact(_dev(X, torch.float32, "X"), n, d, _dev(centroids, torch.float32, "centroids"), k,
                                   _stream(), C.c_void_p(a.data_ptr()), C.c_void_p(dist.data_ptr())))
     return a, dist
@@ -402,8 +412,8 @@ def assign_exact_static(X: torch.Tensor, centroids: torch.Tensor, out=None):
     """skm_assign_exact_static: the exact step with no device allocation inside the call (outputs are the caller's)."""
     n, d = X.shape
     k = centroids.shape[0]
-    a, dist = out if out is not None else (torch.empty(n, device=X.device, dtype=torch.int32),
-                                           torch.empty(n, device=X.device, dtype=torch.float32))
+    a, dist = out if out is not None else (_empty(n, device=X.device, dtype=torch.int32),
+                                           _empty(n, device=X.device, dtype=torch.float32))
     _check(lib().skm_assign_exact_static(_dev(X, torch.float32, "X"), n, d, _dev(centroids, torch.float32, "centroids"),
                                          k, _stream(), C.c_void_p(a.data_ptr()), C.c_void_p(dist.data_ptr())))
     return a, dist
@@ -413,7 +423,7 @@ def update(X: torch.Tensor, assign_: torch.Tensor, centroids: torch.Tensor):
     """skm_update: in-place mean update of `centroids`; returns the cluster sizes."""
     n, d = X.shape
     k = centroids.shape[0]
-    counts = torch.empty(k, device=X.device, dtype=torch.int32)
+    counts = _empty(k, device=X.device, dtype=torch.int32)
     _check(lib().skm_update(_dev(X, torch.float32, "X"), n, d, _dev(assign_, torch.int32, "assign"), k, _stream(),
                             _dev(centroids, torch.float32, "centroids"), C.c_void_p(counts.data_ptr())))
     return counts
@@ -423,21 +433,21 @@ def etr_ground_truth(X: torch.Tensor, queries: torch.Tensor, topk: int) -> torch
     """skm_etr_ground_truth: nq x topk int64 indices of the nearest points of every query."""
     n, d = X.shape
     nq = queries.shape[0]
-    gt = torch.empty((nq, topk), device=X.device, dtype=torch.int64)
+    gt = _empty((nq, topk), device=X.device, dtype=torch.int64)
     _check(lib().skm_etr_ground_truth(_dev(X, torch.float32, "X"), n, d, _dev(queries, torch.float32, "queries"), nq,
                                       topk, _stream(), C.c_void_p(gt.data_ptr())))
     return gt
 
 
 def make_rotation(d: int, seed: int, device="cuda") -> torch.Tensor:
-    R = torch.empty((d, d), device=device, dtype=torch.float32)
+    R = _empty((d, d), device=device, dtype=torch.float32)
     _check(lib().skm_make_rotation(d, C.c_uint64(seed), _stream(), C.c_void_p(R.data_ptr())))
     return R
 
 
 def rotate(X: torch.Tensor, R: torch.Tensor, transpose: bool = False) -> torch.Tensor:
     n, d = X.shape
-    out = torch.empty((n, d), device=X.device, dtype=torch.float32)
+    out = _empty((n, d), device=X.device, dtype=torch.float32)
     _check(lib().skm_rotate(_dev(X, torch.float32, "X"), n, d, _dev(R, torch.float32, "R"), int(transpose), _stream(),
                             C.c_void_p(out.data_ptr())))
     return out

@@ -96,3 +96,19 @@ def test_workspace_size_query(skm):
     L.skm_params_default(C.byref(p))
     p.etr, p.nq, p.topk = 1, 1000, 10
     assert skm.workspace_bytes(1_000_000, 1536, 1024, p) > big
+
+
+def test_output_tensors_get_the_blocks_that_the_library_keeps(skm, monkeypatch):
+    calls = []
+    real = skm.torch.empty
+
+    def empty(*args, **kwargs):
+        calls.append("empty")
+        if calls.count("empty") == 1:
+            raise skm.torch.OutOfMemoryError("no room")
+        return real(*args, **kwargs)
+
+    monkeypatch.setattr(skm.torch, "empty", empty)
+    monkeypatch.setattr(skm, "release_memory", lambda: calls.append("release"))
+    assert skm._empty((3, 2), dtype=skm.torch.int32).shape == (3, 2)
+    assert calls == ["empty", "release", "empty"]
