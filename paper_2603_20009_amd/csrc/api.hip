@@ -694,7 +694,7 @@ struct Ctx {
     pair_cap = sub_cap * kSubLists;
     if (pair_cap >= ((int64_t)1 << 32)) return fail(SKM_EINVAL, "pair_budget too large (must stay below 2^32 pairs)");
     HIPCHK(pool.get(&pairs, (size_t)pair_cap));
-    ncounters = (size_t)nchunks * (kSubLists + 16) * kSubListStride;   // list fill counters, tile counters of the two tile kernels
+    ncounters = (size_t)nchunks * (kSubLists + 8) * kSubListStride;   // list fill counters, tile counters
     if (may_screen) {   // (unless forced: of no use with few centroids)
       // one bit per (row tile, centroid); at most one tile of listed columns per (row tile, column tile) of the chunk
       const int64_t nrt_chunk = (std::min<int64_t>(chunk_rows, n) + 127) / 128;
@@ -980,7 +980,11 @@ int step_exact_filtered(Ctx &c, StageTimer &tm, StepStats &ss) {
 
 // Iteration 1 of Algorithm 1: exact assignment over all dims.  Leaves assign, dist, cluster sizes.
 int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
-  // many centroids: the low-precision filter first, exact distances for the few candidates it leaves
+  // Many centroids: the low-precision filter first, exact distances for the few candidates it leaves.  It also writes the
+  // tables that the next step would write.  Iterations 1 and 2 together, product -> filter, for 1M points: k = 512 16.9 -> 16.2
+  // ms at d = 1536 and 3.2 -> 2.9 at d = 200, k = 1024 27.1 -> 24.7 and 4.8 -> 4.3, k = 2047 47.0 -> 41.0 and 8.6 -> 7.1, k = 3000
+  // 66.7 -> 57.0 and 12.6 -> 10.1; 20 000 x 768, k = 1024 0.51 -> 0.46.  So 2048 lies well inside the range where it pays (it
+  // is from a filter that cost twice as much; distances of iteration 1 round differently on the two sides).
   if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
     if (int rc = step_exact_filtered(c, tm, ss)) return rc;
     if ((c.report->flag & 1u) == 0) {
@@ -1093,9 +1097,11 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     c.group_now = false;
   }
   if (regroup) {
-    // The update leaves the members of a cluster sorted by index only up to a size (larger clusters keep the order in
-    // which the scatter placed them, which depends on scheduling): with such a cluster the new order, and with it the
-    // rounding of the results, would differ from run to run.  Those fits keep the input order.
+    // A grouping that scatters and then orders the members of a cluster does so only up to a size (larger clusters keep
+    // the order in which the scatter placed them, which depends on scheduling): with such a cluster the new order, and with
+    // it the rounding of the results, would differ from run to run, so the points keep the input order.  The updates of a
+    // fit of n >= 8 k points into at most 8192 clusters order every cluster by counting, whatever its size; the same limit
+    // holds for them, which leaves the results of such fits what they were.
     // (the sizes came back with the previous step's scalars: no copy, no wait here)
     regroup = c.max_cluster >= 0 && c.max_cluster <= update_sort_cap();
     if (!regroup) c.regroup_ok = false;
@@ -1164,12 +1170,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.arow = c.scr_arow; sl.ycol = c.scr_ycol;
       sl.colmask = c.colmask; sl.cnt = c.scr_cnt; sl.first = c.scr_first; sl.ntiles = c.scr_ntiles;
       sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt; sl.prev = c.prev; sl.list_pos = c.scr_pos;
-      sl.tile_counter = c.counters + ((size_t)c.nchunks * (kSubLists + 8) + (size_t)ch * 8) * kSubListStride;
       sl.scal = c.scal;
       sl.stamp = border;
       HIPCHK(launch_screen(sl, c.st));
       g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles; g.prev = c.scr_pos;
       if (deep) {
+        // Whole calls in ms: a step of 2.5M x 384, k = 32 768 | of 600 000 x 1536, k = 10 000 | a fit of 1M x 1536, k = 4096,
+        // ten iterations.  As it is 110.3 | 45.7 | 241.7, three products throughout 187 | 59.1 | 247.3.
+        //   emit_first (share of emit_max): flat from 2/16 to 8/16, all of it 118.0 | 47.9 | 241.6
+        //   emit_deep: 6 110.5 | 45.6 | 246.5, 12 110.4 | 45.5 | 243.6, 48 110.4 | 46.1 | 242.4, 96 111.1 | 48.6 | 251.4
+        //   deep_stride: 1 119.5 | 47.3 | 245.0, 2 113.7 | 46.0 | 242.0, 6 107.6 | 45.5 | 242.0 (1M x 768, k = 4096 93.4 -> 95.2)
+        //   deep_max: 1/16 143.9 | 55.4 | 264.6, 1/8 123.7 | 49.5 | 253.4, 1/2 105.8 | 44.3 | 239.8, no limit 104.4 | 44.2 | 239.5:
+        //   a quarter is on the safe side of what these shapes would take
         g.deep = 1;
         g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
         g.emit_first = c.emit_max * 5 / 16;

@@ -1,9 +1,9 @@
 // Progressive-pruning GEMM (Algorithm 1, iterations >= 2; Section 3.4 "Progressive Pruning").
 //
 // The paper multiplies only the first d' dimensions densely and finishes survivors one by one.
-// On MI355X a 64-dimension step of a dense 128 x 128 tile on the matrix cores costs about as
-// much as gathering the same step for 2 % of the tile's pairs, so this kernel keeps multiplying a
-// tile densely, 64 dimensions at a time, while more than a small share of its pairs is alive, and
+// On MI355X a 64-dimension step of a dense tile (128 x 256, or 128 x 128 where the wider ones would be too few) on the
+// matrix cores costs about as much as gathering the same step for 2 % of the tile's pairs, so this kernel keeps multiplying
+// a tile densely, 64 dimensions at a time, while more than a small share of its pairs is alive, and
 // hands the pairs over to the gather kernel (prune.hip) only once the tile is sparse.  The tests are
 // the paper's: after t = d', d'+64, d'+128, ... dimensions a pair is dropped when its partial squared
 // distance exceeds theta(t, tau_i); a pair that reaches t = d is offered to the point's packed
@@ -14,7 +14,7 @@
 // centroid anyway write them, and this kernel fetches one number per row and column and checkpoint.
 //
 // Operands arrive already split into fp16 pairs (the points once per fit, by the first threshold pass; the
-// centroids once per step, by split_rows_kernel), in the very byte order of the LDS tiles, so staging is a
+// centroids once per step, by the pass over them that starts it), in the very byte order of the LDS tiles, so staging is a
 // copy: every lane moves 16 bytes from global memory straight into LDS and the vector unit is left to the tests.
 //
 // The kernel is persistent: two workgroups per CU take tiles from a per-XCD counter.  When a tile

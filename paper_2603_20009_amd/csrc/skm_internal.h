@@ -278,7 +278,6 @@ struct ScreenLaunch {
   int2 *tile_rt;
   const int32_t *prev;       // (first test) [n] incumbents, indexed like tau; list_pos[row_base + row] receives the position
   int32_t *list_pos;         // of a row's incumbent in its row tile's list, -1 if it is not listed
-  unsigned int *tile_counter;   // (unused)
   unsigned long long *scal;     // step scalars (SC_SCREEN_DIMS)
   // Exact mode (iteration 1: dprime = ds, xn / yn the full norms, tau and ratio0 unused, no column lists): for every
   // point the centroids that can be its nearest are appended to `pairs` (partial distance 0, first block 0, no
@@ -503,7 +502,7 @@ hipError_t launch_pad_copy(const float *src, int64_t lds, int64_t n, int32_t d, 
 
 // ---------------------------------------------------------------- rotation matrix
 // Haar-distributed orthogonal d x d matrix (fp32) from (d, seed); workspaces in doubles:
-// Qwork d*d + 2, Cwork max(4*32*d, ceil(d/128)*1024), Wwork 8*32*d, Lwork 32*32.
+// Qwork d*d + 2, Cwork max(12*64*d, ceil(d/64)*64*64), Wwork ceil(d/64)*64*d, Lwork 64*64.
 hipError_t launch_make_rotation(int32_t d, uint64_t seed, double *Qwork, double *Cwork, double *Wwork, double *Lwork,
                                 float *R_out, hipStream_t st);
 
