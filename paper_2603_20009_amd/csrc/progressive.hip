@@ -676,6 +676,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       --tile_no;
       continue;
     }
+    redone = false;   // (of the finished tile: the next one's first requests already ask for it)
     if (more) {
       if (LISTED) SKM_BARRIER();   // (the ids were brought by all wavefronts)
       aim(rt_next, ct_next, par ^ 1);
@@ -777,7 +778,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
 
-    redone = false;
     if (!more) break;
     rt = rt_next;
     ct = ct_next;

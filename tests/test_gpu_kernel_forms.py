@@ -249,3 +249,28 @@ def test_refused_labels_leave_the_outputs_as_they_are(skm, dg, n, d, k):  # noqa
     b, dist_b, _ = skm.assign(X, Y, torch.zeros(n, dtype=torch.int32, device="cuda"), opts=skm.FitOptions(R=skm.make_rotation(d, 0)))
     torch.cuda.synchronize()
     assert torch.equal(prev, b) and torch.equal(dist, dist_b)
+
+
+# Several tiles to a workgroup, some of them done again in three products (poor incumbents in every third row tile): the tile
+# after such a one starts in one product behind the first test like any other.  d' = 16: its second unit is already the
+# first of one product.
+@pytest.mark.parametrize("n,d,k,dp", [(30_000, 153, 1100, 16), (30_000, 208, 1100, 16), (30_000, 200, 1100, 32)])
+def test_listed_tiles_behind_one_that_was_done_again(skm, orc, dg, n, d, k, dp):  # noqa: F811
+    say("listed, done again", n, d, k, dp)
+    rng = np.random.default_rng(n + d)
+    X = dg.mixture(n, d, k // 3, 17, "embed").numpy()
+    R = orc.random_rotation(d, 6)
+    Y = X[rng.choice(n, k, replace=False)] + (0.01 * rng.standard_normal((k, d))).astype(np.float32)
+    Xr, Yr = orc.rotate(X, R), orc.rotate(Y, R)
+    prev = orc.assign_full(Xr, Yr)[0].astype(np.int32)
+    poor = (np.arange(n) // 128) % 3 == 0
+    prev[poor] = rng.integers(0, k, int(poor.sum()))
+    near = rng.random(n) < 0.5                     # and half of the others an incumbent that is beaten
+    prev[near & ~poor] = orc.assign_full(Xr[near & ~poor], Yr[: k // 2])[0]
+    ref = orc.assign_pruned(Xr, Yr, prev, dp, EPS0, 0)
+    for screen in (1, -1):
+        a, dist, row = skm.assign(cuda(X), cuda(Y), cuda(prev), dp, skm.FitOptions(R=cuda(R), screen=screen))
+        check_assignment(a.cpu().numpy(), ref.assign, Xr, Yr)
+        same = a.cpu().numpy() == ref.assign
+        assert np.abs(dist.cpu().numpy()[same] - ref.dist[same]).max() < 2e-5 * max(1.0, ref.dist.max())
+        assert abs(row["completed"] - ref.enter[-1]) <= max(2, 1e-3 * ref.enter[-1])
