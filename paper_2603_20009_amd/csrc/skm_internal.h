@@ -7,6 +7,10 @@
 
 namespace skm {
 
+// four floats at any 4-byte boundary: one 16-byte load from global memory (the vector memory path takes unaligned addresses)
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+
 constexpr int kBlockDims = 64;  // Section 3.2: trailing dimensions are explored 64 at a time
 constexpr int kMaxBlocks = 256; // (16384 - 16) / 64 rounded up
 constexpr int kSegPoints = 512; // points per partial-sum segment of the centroid update

@@ -274,3 +274,27 @@ def test_listed_tiles_behind_one_that_was_done_again(skm, orc, dg, n, d, k, dp):
         same = a.cpu().numpy() == ref.assign
         assert np.abs(dist.cpu().numpy()[same] - ref.dist[same]).max() < 2e-5 * max(1.0, ref.dist.max())
         assert abs(row["completed"] - ref.enter[-1]) <= max(2, 1e-3 * ref.enter[-1])
+
+
+# Rows of any length and alignment: four values a load from any 4-byte boundary, the last ones of a row again where the length is
+# no multiple of four (from 64 on; shorter rows in fp32 products).  n, d around the tiles of 128 and the slabs of 32.
+@pytest.mark.parametrize("n,d", [(127, 61), (129, 63), (1, 65), (128, 66), (300, 67), (257, 95), (130, 97), (65, 127), (200, 129), (140, 495)])
+def test_products_of_rows_of_any_length(skm, dg, n, d):  # noqa: F811
+    say("rows of any length", n, d)
+    X = dg.mixture(n, d, 5, 2, "embed").cuda()
+    R = skm.make_rotation(d, 3)
+    shifted = torch.empty(n * d + 3, device="cuda")
+    shifted[3:] = X.reshape(-1)
+    rows = shifted[3:].view(n, d)                      # (not 16-byte aligned)
+    # halves of 22 bits a value and fp32 sums: 2^-21 of every product and 2^-24 of the partial sums at each of d / 16 steps of
+    # 16, all bounded by the norms (Cauchy-Schwarz; rows and columns have norm 1)
+    bound = 2.0 ** -21 + (d / 16 + 16) * 2.0 ** -24
+    for x in (X, rows):
+        for transpose in (False, True):
+            ref = X.double() @ (R.double().T.contiguous() if transpose else R.double())
+            assert (skm.rotate(x, R, transpose).double() - ref).abs().max().item() < bound
+    if n > 1:                                          # a row that is not a number stays by itself
+        X[n // 2] = float("nan")
+        out = skm.rotate(X, R)
+        bad = torch.isnan(out).any(1)
+        assert bool(bad[n // 2]) and int(bad.sum()) == 1
