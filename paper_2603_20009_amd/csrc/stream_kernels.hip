@@ -1200,17 +1200,67 @@ static void launch_sort_segments(const int32_t *off, int32_t *order, int32_t k, 
   if (most > RANK_CAP) hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
 }
 
-// One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
-// `order` (each a contiguous row read).  Wavefront w takes the points p0 + w, p0 + w + 4, ... of the segment, four
-// rows in flight per thread, fp64 sums per thread; the four wavefronts' sums are added in a fixed order, so the
-// result depends on the segment only.
-// SIGNED: an entry i >= 0 adds row i, an entry ~i < 0 subtracts row i (a point that left the cluster).
+// Sum of rows in a fixed order, for a lane's four dimensions: entries first, first + STEP, ... of s_ids[0 .. count),
+// ROWS of them requested while the ROWS before are added (a row is a round trip to memory: 30 us for a segment of 512 rows
+// with four in flight behind the loads of their numbers, 23 with twice eight; the whole update of 1M x 768 680 -> 669).
+// SIGNED: an entry i >= 0 adds row i, an entry ~i < 0 subtracts row i.
 // ALIGNED: rows are 16-byte aligned and a multiple of 4 long; otherwise a lane reads its four values one by one.
+template <bool SIGNED, bool ALIGNED, int STEP>
+__device__ inline void add_rows(const float *Xr, int64_t ldx, int32_t ds, int col, const int *s_ids, int count, int first,
+                                double &a0, double &a1, double &a2, double &a3) {
+  constexpr int ROWS = 8;
+  float4 v[2][ROWS];
+  int id[2][ROWS];
+  auto fetch = [&](int p, float4 (&to)[ROWS], int (&ids)[ROWS]) {
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+      const int raw = __builtin_amdgcn_readfirstlane(s_ids[min(p + STEP * u, count - 1)]);   // (past the end: the last one again)
+      ids[u] = raw;
+      const float *x = Xr + (int64_t)(SIGNED && raw < 0 ? ~raw : raw) * ldx + col;
+      if (ALIGNED) {
+        to[u] = *reinterpret_cast<const float4 *>(x);
+      } else {
+        to[u].x = x[0];
+        to[u].y = col + 1 < ds ? x[1] : 0.f;
+        to[u].z = col + 2 < ds ? x[2] : 0.f;
+        to[u].w = col + 3 < ds ? x[3] : 0.f;
+      }
+    }
+  };
+  auto add = [&](int p, const float4 (&from)[ROWS], const int (&ids)[ROWS]) {
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u)
+      if (p + STEP * u < count) {
+        const float4 f = from[u];
+        if (SIGNED) {
+          const double sg = ids[u] < 0 ? -1.0 : 1.0;
+          a0 += sg * (double)f.x; a1 += sg * (double)f.y; a2 += sg * (double)f.z; a3 += sg * (double)f.w;
+        } else {
+          a0 += (double)f.x; a1 += (double)f.y; a2 += (double)f.z; a3 += (double)f.w;
+        }
+      }
+  };
+  constexpr int BATCH = STEP * ROWS;
+  if (first >= count) return;
+  fetch(first, v[0], id[0]);
+  for (int p = first; p < count; p += 2 * BATCH) {
+    if (p + BATCH < count) fetch(p + BATCH, v[1], id[1]);
+    add(p, v[0], id[0]);
+    if (p + 2 * BATCH < count) fetch(p + 2 * BATCH, v[0], id[0]);
+    add(p + BATCH, v[1], id[1]);
+  }
+}
+
+// One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
+// `order` (each a contiguous row read), fp64 sums per thread; the four wavefronts' sums are added in a fixed order, so the
+// result depends on the segment only.
+// SIGNED, ALIGNED: see add_rows (an entry ~i: a point that left the cluster).
 template <bool SIGNED, bool ALIGNED>
 __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64_t ldx, int32_t ds, int32_t k,
                                                           const int32_t *off, const int32_t *segoff,
                                                           const int32_t *order, double *partial) {
   __shared__ double red[3][64][4];
+  __shared__ int s_ids[kSegPoints];
   const int seg = blockIdx.x;
   if (seg >= segoff[k]) return;
   // cluster of this segment: last c with segoff[c] <= seg
@@ -1227,47 +1277,9 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
   const int col = (blockIdx.y * 64 + lane) * 4;
   const bool live = col < ds;
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-  auto row = [&](int raw, float4 &v, double &sg) {
-    const int i = SIGNED && raw < 0 ? ~raw : raw;
-    sg = SIGNED && raw < 0 ? -1.0 : 1.0;
-    const float *x = Xr + (int64_t)i * ldx + col;
-    if (ALIGNED) {
-      v = *reinterpret_cast<const float4 *>(x);
-    } else {
-      v.x = x[0];
-      v.y = col + 1 < ds ? x[1] : 0.f;
-      v.z = col + 2 < ds ? x[2] : 0.f;
-      v.w = col + 3 < ds ? x[3] : 0.f;
-    }
-  };
-  auto add = [&](const float4 &v, double sg) {
-    if (SIGNED) {
-      a0 += sg * (double)v.x; a1 += sg * (double)v.y; a2 += sg * (double)v.z; a3 += sg * (double)v.w;
-    } else {
-      a0 += (double)v.x; a1 += (double)v.y; a2 += (double)v.z; a3 += (double)v.w;
-    }
-  };
-  if (live) {
-    int p = p0 + w;
-    for (; p + 12 < p1; p += 16) {
-      float4 v0, v1, v2, v3;
-      double s0, s1, s2, s3;
-      row(order[p], v0, s0);
-      row(order[p + 4], v1, s1);
-      row(order[p + 8], v2, s2);
-      row(order[p + 12], v3, s3);
-      add(v0, s0);
-      add(v1, s1);
-      add(v2, s2);
-      add(v3, s3);
-    }
-    for (; p < p1; p += 4) {
-      float4 v;
-      double sg;
-      row(order[p], v, sg);
-      add(v, sg);
-    }
-  }
+  for (int t = threadIdx.x; t < p1 - p0; t += 256) s_ids[t] = order[p0 + t];
+  __syncthreads();
+  if (live) add_rows<SIGNED, ALIGNED, 4>(Xr, ldx, ds, col, s_ids, p1 - p0, w, a0, a1, a2, a3);
   if (w > 0) {
     red[w - 1][lane][0] = a0; red[w - 1][lane][1] = a1; red[w - 1][lane][2] = a2; red[w - 1][lane][3] = a3;
   }
@@ -1402,46 +1414,79 @@ __global__ void __launch_bounds__(256) compact_changes_kernel(const int32_t *ass
 // through all m entries, keeps those of its cluster in their order, adds the rows that joined and subtracts those that
 // left, and writes the sum and the mean.  Every workgroup reads the m labels (from L2): worth it while
 // m * workgroups stays below kDirectUpdate labels; it replaces the counting, scan, scatter, sort, segment-sum and mean
-// kernels, whose launches are all the time of an update in which a few points moved (35 -> 12 us).
+// kernels, whose launches are all the time of an update in which a few points moved (35 -> 12 us).  (47 000 entries on 70
+// clusters: a row at a time behind every chunk of 1024 labels 201 us, eight and more in flight over the chunks 100.)
 constexpr int64_t kDirectUpdate = (int64_t)1 << 25;
 constexpr int DIRECT_CHUNK = 1024;
 __global__ void __launch_bounds__(256) direct_update_kernel(const float *Xr, int64_t ldx, int32_t ds, const int32_t *ent_id,
                                                             const int32_t *ent_lab, int m, const int32_t *cnt, double *S,
                                                             float *Y, int64_t ldy, unsigned int *y_absmax) {
-  __shared__ int s_ids[DIRECT_CHUNK];
-  __shared__ int s_w[4];
+  // The rows of a cluster in a chunk of entries go to the four wavefronts in turn (the order of the sums does not depend on
+  // how many chunks are taken together); their lists are worked off when one is nearly full, and at the end.
+  constexpr int LIST = 1024;
+  __shared__ int s_ids[4][LIST];
+  __shared__ int s_n[2][DIRECT_CHUNK / 64];   // (by chunk parity: the chunk before may still be read)
   __shared__ double red[3][64][4];
   const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int col = (blockIdx.y * 64 + lane) * 4;
   const bool live = col < ds;
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
   bool any = false;
-  for (int e0 = 0; e0 < m; e0 += DIRECT_CHUNK) {
-    // thread t holds entries e0 + 256 j + t: matches in order of (j, wavefront, lane)
-    int have = 0;
-    for (int j = 0; j < DIRECT_CHUNK / 256; ++j) {
-      const int e = e0 + 256 * j + tid;
-      const bool hit = e < m && ent_lab[e] == c;
-      const unsigned long long bal = __ballot(hit);
-      if (lane == 0) s_w[w] = __popcll(bal);
-      __syncthreads();
-      int at = have;
-      for (int u = 0; u < w; ++u) at += s_w[u];
-      if (hit) s_ids[at + __popcll(bal & ((1ull << lane) - 1ull))] = ent_id[e];
-      have += (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
-      __syncthreads();
+  // thread t holds entries e0 + 256 j + t of a chunk: matches in order of (j, wavefront, lane).  The next chunk's labels are
+  // requested behind this one's, the numbers of the rows reach their lists a chunk later.
+  constexpr int PER = DIRECT_CHUNK / 256;
+  int lab[PER], id[PER], at[PER], len[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < PER; ++j) at[j] = -1;
+  auto fetch = [&](int e0) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) lab[j] = e0 + 256 * j + tid < m ? ent_lab[e0 + 256 * j + tid] : -1;
+  };
+  auto write = [&]() {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (at[j] >= 0) (&s_ids[0][0])[at[j]] = id[j];
+      at[j] = -1;
     }
-    any |= have > 0;
-    if (live)
-      for (int p = w; p < have; p += 4) {
-        const int raw = s_ids[p];
-        const int i = raw < 0 ? ~raw : raw;
-        const double sg = raw < 0 ? -1.0 : 1.0;
-        const float4 v = *reinterpret_cast<const float4 *>(Xr + (int64_t)i * ldx + col);
-        a0 += sg * (double)v.x; a1 += sg * (double)v.y; a2 += sg * (double)v.z; a3 += sg * (double)v.w;
+  };
+  auto work_off = [&]() {
+    write();
+    __syncthreads();
+    const int mine = w == 0 ? len[0] : w == 1 ? len[1] : w == 2 ? len[2] : len[3];
+    if (live && mine > 0) add_rows<true, true, 1>(Xr, ldx, ds, col, s_ids[w], mine, 0, a0, a1, a2, a3);
+    __syncthreads();
+    len[0] = len[1] = len[2] = len[3] = 0;
+  };
+  fetch(0);
+  for (int e0 = 0; e0 < m; e0 += DIRECT_CHUNK) {
+    const int par = (e0 / DIRECT_CHUNK) & 1;
+    unsigned long long bal[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      bal[j] = __ballot(lab[j] == c);
+      if (lane == 0) s_n[par][4 * j + w] = __popcll(bal[j]);
+    }
+    if (e0 + DIRECT_CHUNK < m) fetch(e0 + DIRECT_CHUNK);
+    write();
+    __syncthreads();
+    int have = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (u == w && ((bal[j] >> lane) & 1ull)) {
+          const int p = have + __popcll(bal[j] & ((1ull << lane) - 1ull)), q = p & 3;
+          at[j] = q * LIST + (q == 0 ? len[0] : q == 1 ? len[1] : q == 2 ? len[2] : len[3]) + (p >> 2);
+          id[j] = ent_id[e0 + 256 * j + tid];
+        }
+        have += s_n[par][4 * j + u];
       }
-    if (have) __syncthreads();
+    any |= have > 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) len[u] += (have + 3 - u) >> 2;
+    if (len[0] > LIST - DIRECT_CHUNK / 4) work_off();   // (the longest list; the same for all threads)
   }
+  if (len[0] > 0) work_off();
   if (any) {
     if (w > 0) {
       red[w - 1][lane][0] = a0; red[w - 1][lane][1] = a1; red[w - 1][lane][2] = a2; red[w - 1][lane][3] = a3;
