@@ -203,18 +203,23 @@ int skm_fit_ex(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, u
 /*
  * skm_fit_host -- Algorithm 1 on points that stay in HOST memory (Section 7.1:
  *   the points pass through the device in batches; copies and kernels overlap).
- *   For data larger than the device memory.  Every pass over the data (an
- *   iteration, or the final assignment) copies the rows to the device in batches
- *   of batch_rows rows through two buffers, rotates the batch there, assigns it,
- *   and adds its cluster sums (fp64) to those of the pass; the means are taken
- *   when the pass is complete.  The result is that of skm_fit_ex with
- *   params->full_update = 1, up to the rounding of sums taken in another order.
+ *   For data larger than the device memory.  The first pass over the data copies
+ *   the rows to the device in batches of batch_rows rows through two buffers,
+ *   rotates the batch there, assigns it, and adds its cluster sums (fp64) to those
+ *   of the pass; the means are taken when the pass is complete.  With batch_rows
+ *   0 the rotated rows of as many batches as fit into half of the free device
+ *   memory stay there for the passes that follow (the other iterations, the final
+ *   assignment), which send only the rest.  The result is the same either way,
+ *   and that of skm_fit_ex with params->full_update = 1, up to the rounding of
+ *   sums taken in another order.
  *   X_host          HOST n x d fp32.  Page-locked memory (hipHostMalloc) lets the
  *                   copies run beside the kernels; pageable memory works, each
  *                   copy then holds the calling thread until it is done.
- *   batch_rows      rows per batch, rounded up to a multiple of 128; 0 = 131072.
+ *   batch_rows      rows per batch, rounded up to a multiple of 128; 0 = 131072,
+ *                   and rows that fit stay on the device.
  *                   Device memory in use: about 3 * batch_rows * d * 4 bytes for the
- *                   batches plus 8 (12 with dist_out_host) bytes per point.
+ *                   batches plus 8 (12 with dist_out_host) bytes per point; with 0
+ *                   and the rows that stay, up to 11 bytes per value more.
  *   centroids_out   DEVICE k x d fp32, original space
  *   assign_out_host HOST n int32 or NULL; dist_out_host HOST n fp32 or NULL
  *   params->R, if set, is a DEVICE pointer as elsewhere; params->init_idx a host

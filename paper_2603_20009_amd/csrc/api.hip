@@ -93,6 +93,14 @@ struct BlockCache {
     for (const Block &b : drop) (void)hipFree(b.p);
     if (p) (void)hipFree(p);
   }
+  size_t idle_bytes() {   // of the current device
+    const int dev = device();
+    std::lock_guard<std::mutex> lock(mu);
+    size_t sum = 0;
+    for (const Block &b : idle)
+      if (b.dev == dev) sum += b.bytes;
+    return sum;
+  }
   void release() {
     std::vector<Block> drop;
     {
@@ -577,6 +585,7 @@ struct Ctx {
   int2 *scr_tile_rt = nullptr;
   unsigned int *amax = nullptr;      // [AM_COUNT] magnitude bounds of the GEMM operands
   enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8 };
+  unsigned int *xr_bound = nullptr;  // that of Xr: amax[AM_XR], or a word that is kept with the rows (fit_host_impl)
 
   // What a step reports: the finalize kernel writes it straight into this page-locked block (see PinnedCache), so the
   // host waits for the stream once per step and copies nothing.  Behind it lies room for the initial row numbers.
@@ -639,9 +648,10 @@ struct Ctx {
   int alloc_bounds(stamp_t *stamp = nullptr) {
     HIPCHK(pool.get(&amax, (size_t)AM_COUNT));
     if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT, 0u, st, stamp));
+    xr_bound = amax + AM_XR;
     return SKM_OK;
   }
-  int measure_xr() { return measure_absmax(Xr, ldx, n, ds, amax + AM_XR, st); }
+  int measure_xr() { return measure_absmax(Xr, ldx, n, ds, xr_bound, st); }
   // the words that a step counts into, cleared by the pass over the centroids that starts it
   void clear_with(CentroidPrep &a) const {
     a.clear = reinterpret_cast<unsigned int *>(zblock);
@@ -911,7 +921,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
     // writes them runs now (its thresholds, against centroid 0, are discarded)
     HIPCHK(launch_fill_u32(reinterpret_cast<unsigned int *>(c.prev), c.n, 0u, c.st));
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, nullptr, c.st, c.xnp, c.Xs,
-                           c.amax + Ctx::AM_XR, nullptr, nullptr, nullptr, c.Xh, nullptr, start));
+                           c.xr_bound, nullptr, nullptr, nullptr, c.Xh, nullptr, start));
     start = nullptr;
     c.xnp_valid = c.xh_valid = true;
   }
@@ -938,7 +948,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
     ScreenLaunch sl{};
     sl.A = c.Xh + r0 * (c.ds / 2 + 16); sl.lda = c.ds / 2 + 16; sl.M = (int32_t)rows;
     sl.B = c.Yh; sl.ldb = c.ds / 2 + 16; sl.N = c.k;
-    sl.a_absmax = c.amax + Ctx::AM_XR; sl.b_absmax = c.amax + Ctx::AM_Y;
+    sl.a_absmax = c.xr_bound; sl.b_absmax = c.amax + Ctx::AM_Y;
     sl.ds = c.ds; sl.dprime = K; sl.ratio0 = 1.f;
     sl.tau = c.tau; sl.row_base = r0;
     sl.xn = c.xnp + (int64_t)(K / 16 - 1) * c.n;   // ||x[0 : K)||^2: row K / 16 - 1 of the prefix table
@@ -1001,7 +1011,7 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   HIPCHK(launch_prep_centroids(cp, c.st));
   HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   GemmOperands g{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, c.ds};
-  g.a_absmax = c.amax + Ctx::AM_XR; g.b_absmax = c.amax + Ctx::AM_Y;
+  g.a_absmax = c.xr_bound; g.b_absmax = c.amax + Ctx::AM_Y;
   g.b_presplit = c.Ys; g.ldbs = c.ds + 32;
   HIPCHK(gemm_argmin(g, c.ynorm, c.best, c.st));
   // winners -> direct squared distances (also the objective of this step)
@@ -1068,7 +1078,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   if (!have_prev && !found) {
     HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
-    g0.a_absmax = c.amax + Ctx::AM_XR; g0.b_absmax = c.amax + Ctx::AM_Y;
+    g0.a_absmax = c.xr_bound; g0.b_absmax = c.amax + Ctx::AM_Y;
     g0.b_presplit = c.Ys; g0.ldbs = c.ds + 32;
     HIPCHK(gemm_argmin(g0, c.ynorm, c.best, c.st));
     if (c.group_now) {
@@ -1115,7 +1125,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     else
       HIPCHK(hipMemcpyAsync(c.pos_to_id, c.up.order, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, c.best, c.st, c.xnp, c.Xs,
-                           c.amax + Ctx::AM_XR, c.pos_to_id, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
+                           c.xr_bound, c.pos_to_id, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
     std::swap(c.prev, c.assign);   // the incumbents in the new order; the other buffer receives this step's labels
     if (c.point_keys)   // (up.order is scratch until the next full update rebuilds it)
       HIPCHK(launch_remap_key_ids(c.point_keys, c.n_point_keys, c.pos_to_id, c.n, c.up.order, c.st));
@@ -1131,7 +1141,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     const bool tables = !c.xnp_valid || (screen && !c.xh_valid);
     uint32_t *xh = tables && (screen || !c.Xr2) ? c.Xh : nullptr;
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, from_keys ? nullptr : c.prev, c.tau, c.best, c.st,
-                           tables ? c.xnp : nullptr, tables ? c.Xs : nullptr, c.amax + Ctx::AM_XR, nullptr,
+                           tables ? c.xnp : nullptr, tables ? c.Xs : nullptr, c.xr_bound, nullptr,
                            nullptr, from_keys ? c.prev : nullptr, xh, c.flag, tau_stamp));
     if (tables) c.xh_valid = xh != nullptr;
   }
@@ -1144,7 +1154,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     ProgArgs g{};
     g.A = c.Xs + r0 * (c.ds + 32); g.lda = c.ds + 32; g.M = (int32_t)rows;
     g.B = c.Ys; g.ldb = c.ds + 32; g.N = c.k;
-    g.a_absmax = c.amax + Ctx::AM_XR; g.b_absmax = c.amax + Ctx::AM_Y;
+    g.a_absmax = c.xr_bound; g.b_absmax = c.amax + Ctx::AM_Y;
     g.ds = c.ds; g.d = c.d; g.dprime = dprime; g.nb = nb;
     g.ratio = c.ratio_dev; g.tau = c.tau; g.prev = c.prev; g.row_base = r0;
     g.xnp = c.xnp; g.xn_stride = c.n; g.ynp = c.ynp;
@@ -1675,7 +1685,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     if (beside) HIPCHK(hipStreamWaitEvent(c.st, e_join, 0));
-    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR, x_bound, tm.point(&t_rot0));
+    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.xr_bound, x_bound, tm.point(&t_rot0));
     if (rc) return rc;
     if (beside) HIPCHK(hipStreamSynchronize(side.s));   // nothing is left on the side stream when it is destroyed
     c.Xr = Xr_own; c.ldx = c.ds;
@@ -1687,8 +1697,8 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     c.Xr = Xr_own; c.ldx = c.ds;
   }
   if (p.angular) {   // the library's own copy, in place; its bound is that of the scaled rows
-    if (p.rotate) HIPCHK(launch_fill_u32(c.amax + Ctx::AM_XR, 1, 0u, c.st));
-    HIPCHK(launch_normalize_rows(Xr_own, c.ds, n, c.ds, c.st, c.amax + Ctx::AM_XR));
+    if (p.rotate) HIPCHK(launch_fill_u32(c.xr_bound, 1, 0u, c.st));
+    HIPCHK(launch_normalize_rows(Xr_own, c.ds, n, c.ds, c.st, c.xr_bound));
   } else if (!p.rotate) {
     rc = c.measure_xr();
     if (rc) return rc;
@@ -1903,11 +1913,85 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
 }
 
 
+// Rotated rows of a host-resident fit that stay on the device between its passes (the first `batches` batches): a block of
+// its own beside the workspace.  A pass over kept rows costs its kernels, one over streamed rows the transfer (17 ms per GB,
+// ten times as much): 200 000 x 768 with k = 1024, four passes, 45.6 ms when all of them were sent every time, now 17.0.
+// At most half of what is free is taken, and only where the caller left the batch size, and with it the memory in use, to
+// the library; a block that cannot be had means that everything is streamed.
+struct KeptRows {
+  int64_t batches = 0, rows = 0;
+  bool tables = false;              // the split copies and prefix norms stay, too
+  float *X = nullptr, *xnp = nullptr;
+  uint32_t *Xs = nullptr, *Xh = nullptr;
+  unsigned int *bound = nullptr;    // [batches] max |X~| of a batch
+  std::vector<char> xnp_valid, xh_valid;   // of a batch's tables
+  bool finished = false;            // the call has waited for its stream: the block goes to the cache
+  ~KeptRows() {
+    if (!block) return;
+    if (finished) block_cache().give(block, cap);
+    else (void)hipFree(block);
+  }
+  KeptRows() = default;
+  KeptRows(const KeptRows &) = delete;
+  KeptRows &operator=(const KeptRows &) = delete;
+  // hi: the plane of hi halves is among the tables
+  void plan(int64_t n, int64_t W, int32_t ds, bool hi) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    const size_t budget = (free_b + block_cache().idle_bytes()) / 2;
+    const int64_t nbatch = (n + W - 1) / W;
+    const size_t row = (size_t)ds * 4, more = (size_t)(ds + 32) * 4 + (size_t)ds / 4 + (hi ? (size_t)(ds / 2 + 16) * 4 : 0);
+    const size_t fixed = (size_t)nbatch * 4 + 5 * 256;
+    if (budget <= fixed) return;
+    // the tables of all rows, or the rows alone, as many whole batches as there is room for
+    const bool with = (size_t)n * (row + more) + fixed <= budget;
+    const int64_t kept = with ? nbatch : std::min<int64_t>(nbatch, (int64_t)((budget - fixed) / ((size_t)W * row)));
+    if (kept < 1) return;
+    const int64_t r = std::min<int64_t>(n, kept * W);
+    const size_t bytes = ((size_t)r * (row + (with ? more : 0)) + fixed + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
+    block = static_cast<char *>(block_cache().take(bytes, &cap));
+    if (!block) {
+      void *p = nullptr;
+      if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+      }
+      block = static_cast<char *>(p);
+      cap = bytes;
+    }
+    size_t at = 0;
+    auto carve = [&](size_t want) {
+      char *p = block + at;
+      at = (at + want + 255) & ~(size_t)255;
+      return p;
+    };
+    X = reinterpret_cast<float *>(carve((size_t)r * row));
+    bound = reinterpret_cast<unsigned int *>(carve((size_t)nbatch * 4));
+    if (with) {
+      Xs = reinterpret_cast<uint32_t *>(carve((size_t)r * (size_t)(ds + 32) * 4));
+      xnp = reinterpret_cast<float *>(carve((size_t)r * ((size_t)ds / 4)));
+      if (hi) Xh = reinterpret_cast<uint32_t *>(carve((size_t)r * (size_t)(ds / 2 + 16) * 4));
+    }
+    batches = kept;
+    rows = r;
+    tables = with;
+    xnp_valid.assign((size_t)kept, 0);
+    xh_valid.assign((size_t)kept, 0);
+  }
+
+ private:
+  char *block = nullptr;
+  size_t cap = 0;
+};
+
 // Algorithm 1 on points that stay in host memory (Section 7.1: batches of X pass through the device, copies and kernels
-// overlap).  Every pass over the data (an iteration, or the final assignment) sends the rows through two device buffers
-// of `W` rows: while batch g is rotated and assigned, batch g + 1 is already there and batch g + 2 follows as soon as the
-// rotation has released its buffer.  A batch is rotated again in every pass (a d x d product per row, small next to the
-// transfer), so nothing of size n x d is kept on the device: per point only its label, and its distance if asked for.
+// overlap).  In the first pass over the data all rows are sent, through two device buffers of `W` rows: while batch g is
+// rotated and assigned, batch g + 1 is already there and batch g + 2 follows as soon as the rotation has released its
+// buffer.  The rotated rows of as many batches as there is room for stay on the device (KeptRows); later passes (the other
+// iterations, the final assignment) send and rotate only the others.
 // An update adds the batch's cluster sums (fp64) to S; the means are taken once the pass is complete.
 int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iters, uint64_t seed, const skm_params *pp,
                   int64_t batch_rows, float *centroids_out, int32_t *assign_out_host, float *dist_out_host) {
@@ -1954,7 +2038,9 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   struct CopyStream {
     hipStream_t s = nullptr;
     ~CopyStream() {
-      if (s) (void)hipStreamDestroy(s);
+      if (!s) return;
+      (void)hipStreamSynchronize(s);   // (a call that fails: the caller's rows are not read any more once it returns)
+      (void)hipStreamDestroy(s);
     }
   } cs;
   HIPCHK(hipStreamCreateWithFlags(&cs.s, hipStreamNonBlocking));
@@ -1979,6 +2065,25 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   HIPCHK(c.pool.get(&lab[0], (size_t)nbatch * W));
   HIPCHK(c.pool.get(&lab[1], (size_t)nbatch * W));
   if (dist_out_host) HIPCHK(c.pool.get(&dist_all, (size_t)nbatch * W));
+  KeptRows kept;
+  if (batch_rows == 0 && npass > 1) kept.plan(n, W, c.ds, c.Xh != nullptr);
+
+  // ---- the stream of batches: what is sent is every batch once, then in every later pass those that are not kept; send
+  // number g goes through device buffer g & 1
+  const int64_t per_pass = nbatch - kept.batches, gtotal = nbatch + (int64_t)(npass - 1) * per_pass;
+  auto send = [&](int64_t g) -> int {   // enqueue the copy on the copy stream
+    if (g >= gtotal) return SKM_OK;
+    const int64_t b = g < nbatch ? g : kept.batches + (g - nbatch) % per_pass;
+    const int64_t r0 = b * W, rows = std::min<int64_t>(W, n - r0);
+    if (g >= 2) HIPCHK(hipStreamWaitEvent(cs.s, ev_free[g & 1], 0));
+    HIPCHK(hipMemcpyAsync(raw[g & 1], Xh + (size_t)r0 * d, sizeof(float) * (size_t)rows * d, hipMemcpyHostToDevice, cs.s));
+    HIPCHK(hipEventRecord(ev_copied[g & 1], cs.s));
+    return SKM_OK;
+  };
+  // (the generator's kernels are enqueued: the first copies run beside them and the initial centroids)
+  HIPCHK(hipStreamWaitEvent(cs.s, e_begin, 0));   // (the block may still be in use by what the caller's stream did before)
+  if ((rc = send(0))) return rc;
+  if ((rc = send(1))) return rc;
   float *dist_batch = c.dist;
   int32_t *cnt_total = nullptr;   // [k] cluster sizes of the pass
   HIPCHK(c.pool.get(&cnt_total, (size_t)k));
@@ -2007,23 +2112,13 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
   }
   HIPCHK(hipEventRecord(e_init, c.st));
 
-  // ---- the stream of batches: batch number g = pass * nbatch + b uses device buffer g & 1
-  const int64_t gtotal = (int64_t)npass * nbatch;
-  auto send = [&](int64_t g) -> int {   // enqueue the copy of batch g on the copy stream
-    if (g >= gtotal) return SKM_OK;
-    const int64_t b = g % nbatch, r0 = b * W, rows = std::min<int64_t>(W, n - r0);
-    if (g >= 2) HIPCHK(hipStreamWaitEvent(cs.s, ev_free[g & 1], 0));
-    HIPCHK(hipMemcpyAsync(raw[g & 1], Xh + (size_t)r0 * d, sizeof(float) * (size_t)rows * d, hipMemcpyHostToDevice, cs.s));
-    HIPCHK(hipEventRecord(ev_copied[g & 1], cs.s));
-    return SKM_OK;
-  };
-  if ((rc = send(0))) return rc;
-  if ((rc = send(1))) return rc;
-
   int32_t dprime = dprime_init(d, p.dprime_frac);
   Rng split_rng = rng_stream(seed, STREAM_SPLIT);
   int32_t rows_out = 0;
   int cur = 0;   // lab[cur] receives the labels of the pass in work, lab[cur ^ 1] holds those of the pass before
+  int64_t sent = 0;   // batches taken from the device buffers so far
+  uint32_t *const own_Xs = c.Xs, *const own_Xh = c.Xh;
+  float *const own_xnp = c.xnp;
   for (int pass = 0; pass < npass; ++pass) {
     const bool final_pass = pass >= iters;
     StepStats tot;
@@ -2034,31 +2129,45 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       HIPCHK(launch_fill_u32(reinterpret_cast<unsigned int *>(cnt_total), k, 0u, c.st));
     }
     for (int64_t b = 0; b < nbatch; ++b) {
-      const int64_t g = (int64_t)pass * nbatch + b, r0 = b * W, rows = std::min<int64_t>(W, n - r0);
-      HIPCHK(hipStreamWaitEvent(c.st, ev_copied[g & 1], 0));
-      if (p.rotate) {
-        HIPCHK(launch_fill_u32(c.amax + Ctx::AM_XR, 1, 0u, c.st));
-        rc = rotate_into(raw[g & 1], d, rows, d, c.ds, rot, Xr_buf, c.st, c.amax + Ctx::AM_XR);
-        if (rc) return rc;
-      } else {
-        HIPCHK(launch_pad_copy(raw[g & 1], d, rows, d, Xr_buf, c.ds, c.ds, 0, c.st));
-      }
-      HIPCHK(hipEventRecord(ev_free[g & 1], c.st));
-      if ((rc = send(g + 2))) return rc;
+      const int64_t r0 = b * W, rows = std::min<int64_t>(W, n - r0);
+      const bool keep = b < kept.batches;
+      float *Xb = keep ? kept.X + (size_t)r0 * c.ds : Xr_buf;
       c.n = rows;
       c.nchunks = (int32_t)((rows + tile_rows - 1) / tile_rows);
-      c.Xr = Xr_buf; c.ldx = c.ds;
-      c.xnp_valid = c.xh_valid = false;
+      c.Xr = Xb; c.ldx = c.ds;
+      c.xr_bound = keep ? kept.bound + b : c.amax + Ctx::AM_XR;
+      c.Xs = keep && kept.tables ? kept.Xs + (size_t)r0 * (c.ds + 32) : own_Xs;
+      c.xnp = keep && kept.tables ? kept.xnp + (size_t)r0 * (c.ds / 16) : own_xnp;
+      c.Xh = keep && kept.tables ? (kept.Xh ? kept.Xh + (size_t)r0 * (c.ds / 2 + 16) : nullptr) : own_Xh;
+      c.xnp_valid = keep && kept.tables && kept.xnp_valid[(size_t)b];
+      c.xh_valid = keep && kept.tables && kept.xh_valid[(size_t)b];
+      if (pass == 0 || !keep) {   // the rows arrive
+        const int64_t g = sent++;
+        HIPCHK(hipStreamWaitEvent(c.st, ev_copied[g & 1], 0));
+        HIPCHK(launch_fill_u32(c.xr_bound, 1, 0u, c.st));
+        if (p.rotate) {
+          rc = rotate_into(raw[g & 1], d, rows, d, c.ds, rot, Xb, c.st, c.xr_bound);
+          if (rc) return rc;
+        } else {
+          HIPCHK(launch_pad_copy(raw[g & 1], d, rows, d, Xb, c.ds, c.ds, 0, c.st));
+        }
+        HIPCHK(hipEventRecord(ev_free[g & 1], c.st));
+        if ((rc = send(g + 2))) return rc;
+        if (!p.rotate) {
+          rc = c.measure_xr();
+          if (rc) return rc;
+        }
+      }
       c.assign = lab[cur] + r0;
       c.prev = lab[cur ^ 1] + r0;
       c.dist = dist_all ? dist_all + r0 : dist_batch;
-      if (!p.rotate) {
-        rc = c.measure_xr();
-        if (rc) return rc;
-      }
       StepStats ss;
       rc = pass == 0 ? step_exact(c, tm, ss) : step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
       if (rc) return rc;
+      if (keep && kept.tables) {
+        kept.xnp_valid[(size_t)b] = c.xnp_valid;
+        kept.xh_valid[(size_t)b] = c.xh_valid;
+      }
       tot.objective += ss.objective;
       tot.survivors += ss.survivors;
       tot.completed += ss.completed;
@@ -2134,6 +2243,7 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
     (void)hipEventElapsedTime(&tr->ms_total, e_begin, e_end);
   }
   ws.finished();
+  kept.finished = true;
   return SKM_OK;
 }
 
@@ -2170,7 +2280,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, 0, rot, false);
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
-    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.amax + Ctx::AM_XR);
+    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.xr_bound);
     if (rc) return rc;
     rc = rotate_into(centroids, d, k, d, c.ds, rot, c.Y, c.st, c.amax + Ctx::AM_Y);
     if (rc) return rc;

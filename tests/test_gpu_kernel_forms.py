@@ -315,3 +315,28 @@ def test_incremental_update_with_many_changes_in_few_clusters(skm, dg, n, d, k):
     moved = int((inc.assign != full.assign).sum())
     assert moved <= 4
     assert (inc.centroids - full.centroids).abs().max().item() < 1e-6 + 8.0 * (moved + 1) * k / n * float(moved > 0)
+
+
+# Rows of a host-resident fit that stay on the device between its passes: all of them with their tables, or as many whole
+# batches as half of the free memory holds; the results are those of a fit that sends every row in every pass, bit by bit.
+@pytest.mark.parametrize("n,d,k,room", [(140_000, 100, 40, "all"), (300_000, 64, 300, "all"), (280_000, 256, 30, "some")])
+def test_host_resident_fit_keeps_what_fits(skm, dg, n, d, k, room):  # noqa: F811
+    say("kept rows", n, d, k, room)
+    X = dg.mixture(n, d, 60, 3, "embed")
+    skm.release_memory()
+    before = torch.cuda.mem_get_info()[0]
+    sent = skm.fit_host(X, k, 3, 5, batch_rows=131_072)
+    used = before - torch.cuda.mem_get_info()[0]       # the workspace, which the library keeps for the next call
+    filler = None
+    if room == "some":
+        # free, without the kept workspace: one and a half batches of rotated rows, twice (half of it is taken)
+        torch.cuda.empty_cache()
+        leave = used + 3 * 131_072 * d * 4
+        skm.release_memory()
+        filler = torch.empty(torch.cuda.mem_get_info()[0] - leave, dtype=torch.uint8, device="cuda")
+    kept = skm.fit_host(X, k, 3, 5)
+    del filler
+    torch.cuda.empty_cache()
+    assert torch.equal(sent.assign, kept.assign) and torch.equal(sent.dist, kept.dist)
+    assert torch.equal(sent.centroids, kept.centroids)
+    assert [r["survivors"] for r in sent.trace] == [r["survivors"] for r in kept.trace]
