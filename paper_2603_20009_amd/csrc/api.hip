@@ -991,10 +991,11 @@ int step_exact_filtered(Ctx &c, StageTimer &tm, StepStats &ss) {
 int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   // Many centroids: the low-precision filter first, exact distances for the few candidates it leaves.  It also writes the
   // tables that the next step would write.  Iterations 1 and 2 together, product -> filter, for 1M points: k = 512 16.9 -> 16.2
-  // ms at d = 1536 and 3.2 -> 2.9 at d = 200, k = 1024 27.1 -> 24.7 and 4.8 -> 4.3, k = 2047 47.0 -> 41.0 and 8.6 -> 7.1, k = 3000
-  // 66.7 -> 57.0 and 12.6 -> 10.1; 20 000 x 768, k = 1024 0.51 -> 0.46.  So 2048 lies well inside the range where it pays (it
-  // is from a filter that cost twice as much; distances of iteration 1 round differently on the two sides).
-  if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
+  // ms at d = 1536 and 2.67 -> 2.53 at d = 100, k = 1024 27.1 -> 24.7, k = 2047 47.0 -> 41.0; 300 000 x 1024, k = 800 7.81 -> 7.25,
+  // 200 000 x 79, k = 700 900 -> 770 us, 20 000 x 128, k = 600 342 -> 332, 20 000 x 1536, k = 512 1152 -> 1125; but 5000 x 768, k =
+  // 600 438 -> 458: with few rows the launches in front of the multiply are what counts.
+  const int32_t filter_from = c.n >= 16384 ? 512 : 2048;
+  if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= filter_from)) {
     if (int rc = step_exact_filtered(c, tm, ss)) return rc;
     if ((c.report->flag & 1u) == 0) {
       if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
@@ -1185,18 +1186,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles; g.prev = c.scr_pos;
       if (deep) {
         // Whole calls in ms: a step of 2.5M x 384, k = 32 768 | of 600 000 x 1536, k = 10 000 | a fit of 1M x 1536, k = 4096,
-        // ten iterations.  As it is 110.3 | 45.7 | 241.7, three products throughout 187 | 59.1 | 247.3.
+        // ten iterations.  With deep_max at a quarter 110.3 | 45.7 | 241.7, three products throughout 187 | 59.1 | 247.3.
         //   emit_first (share of emit_max): flat from 2/16 to 8/16, all of it 118.0 | 47.9 | 241.6
         //   emit_deep: 6 110.5 | 45.6 | 246.5, 12 110.4 | 45.5 | 243.6, 48 110.4 | 46.1 | 242.4, 96 111.1 | 48.6 | 251.4
         //   deep_stride: 1 119.5 | 47.3 | 245.0, 2 113.7 | 46.0 | 242.0, 6 107.6 | 45.5 | 242.0 (1M x 768, k = 4096 93.4 -> 95.2)
-        //   deep_max: 1/16 143.9 | 55.4 | 264.6, 1/8 123.7 | 49.5 | 253.4, 1/2 105.8 | 44.3 | 239.8, no limit 104.4 | 44.2 | 239.5:
-        //   a quarter is on the safe side of what these shapes would take
+        //   deep_max: 1/16 143.9 | 55.4 | 264.6, 1/8 123.7 | 49.5 | 253.4, 1/4 as it was, 1/2 105.8 | 44.3 | 239.8, no limit 104.4 | 44.2 |
+        //   239.5: half, so that a tile of poor incumbents is not done twice
         g.deep = 1;
         g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
         g.emit_first = c.emit_max * 5 / 16;
         g.emit_deep = 24;
         g.deep_stride = 3;
-        g.deep_max = (unsigned int)progressive_tile_pairs() / 4;
+        g.deep_max = (unsigned int)progressive_tile_pairs() / 2;
       }
     }
     if (!screen) g.stamp = border;

@@ -340,3 +340,19 @@ def test_host_resident_fit_keeps_what_fits(skm, dg, n, d, k, room):  # noqa: F81
     assert torch.equal(sent.assign, kept.assign) and torch.equal(sent.dist, kept.dist)
     assert torch.equal(sent.centroids, kept.centroids)
     assert [r["survivors"] for r in sent.trace] == [r["survivors"] for r in kept.trace]
+
+
+# Iteration 1 goes through the one-product filter from 512 clusters on (2048 below 16 384 points), through the product of all
+# pairs otherwise: the labels of a fit of one iteration on both sides of the lines.
+@pytest.mark.parametrize("n,k", [(16_383, 512), (16_384, 511), (16_384, 512), (16_500, 513), (4096, 2047), (4096, 2048)])
+def test_iteration_one_on_both_sides_of_the_filter(skm, orc, dg, n, k):  # noqa: F811
+    say("iteration 1", n, k)
+    d = 48
+    X = dg.mixture(n, d, 300, 8, "embed").numpy()
+    R = orc.random_rotation(d, 2)
+    fit = skm.fit(cuda(X), k, 1, 6, skm.FitOptions(R=cuda(R), final_assign=False))
+    assert (fit.trace[0]["screen_dims"] > 0) == (k >= (512 if n >= 16_384 else 2048))
+    Xr = orc.rotate(X, R)
+    Y0 = Xr[orc.sample_rows(6, n, k)]
+    ref, _ = orc.assign_full(Xr, Y0)
+    check_assignment(fit.assign.cpu().numpy(), ref, Xr, Y0, min_agree=0.999)
