@@ -656,6 +656,143 @@ __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, cons
   tile_epilogue<EPI, T2>(acc, g, e, row0, col0, unscale, smem);
 }
 
+// ---------------------------------------------------------------- row argmin with the rows in registers
+// For short rows (K <= 16 NS).  A tile of the product kernels above multiplies four slabs or so and then spends as long on
+// its start and on the row minima.  Here a wavefront holds its 32 rows as fp16 pairs in registers, the workgroup of 8
+// wavefronts walks the columns 64 at a time (already split into fp16 pairs, global -> LDS directly, the next 64 requested
+// while these are multiplied), every lane keeps the smallest value and its column per row, and the reduction over the lanes
+// and the one atomic per row come at the end of a row tile.  100 003 x 100 against 1000 centroids: 129 -> 78 us.
+// The tiles of 256 rows x 64 columns, a row tile's one after the other, are cut into equal ranges, one a workgroup.
+// The products of a pair are added in the order of the tile kernels (PLAIN: that of the 128 x 128 tiles, whose last slab
+// of 32 takes both halves alike), so the values are the same.
+// LDS: row r of a stage is KS = NS (rounded up to even) granules of 64 bytes (two pieces of hi halves, two of lo halves); the
+// 16-byte piece p sits at position p ^ (r & 7), which spreads the fragment reads of 8 consecutive rows over all banks.
+// Up to four granules two workgroups share a CU; beyond, the registers allow one.  (Looking at a tile's values while the next
+// one is multiplied, with a second set of accumulators, gained nothing: 80 us.)
+constexpr int AR_NT = 512, AR_ROWS = 256, AR_COLS = 64;
+template <int NS> constexpr int kArStage = AR_COLS * ((NS + 1) / 2 * 2) * 16;   // words of a stage
+template <int NS> constexpr size_t kArSmem = sizeof(uint32_t) * 2 * (kArStage<NS> + AR_COLS);
+template <int NS> constexpr int kArPerCu = NS <= 4 ? 2 : 1;
+
+template <int NS, bool PLAIN>
+__global__ void __launch_bounds__(AR_NT) __attribute__((amdgpu_waves_per_eu(2 * kArPerCu<NS>, 2 * kArPerCu<NS>)))
+argmin_rows_kernel(GemmOperands g, const uint32_t *Bs, int64_t ldbs, ArgminArgs e) {
+  constexpr int KS = (NS + 1) / 2 * 2, LAST_SLAB = (NS - 1) / 2;
+  put_stamp(g.stamp);
+  extern __shared__ __align__(16) float smem[];
+  uint32_t *lds = reinterpret_cast<uint32_t *>(smem);   // [2][AR_COLS][KS * 16], then [2][AR_COLS] column norms
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, kh = lane >> 5;
+  const int nct = (g.N + AR_COLS - 1) / AR_COLS;
+  const int tiles = (g.M + AR_ROWS - 1) / AR_ROWS * nct;   // (the launcher has checked the range)
+  const int u1 = (int)((int64_t)tiles * (blockIdx.x + 1) / gridDim.x);
+
+  // request a stage: thread tid of instruction j fills position (j NT + tid) of the stage, four positions a granule
+  auto stage = [&](int ct, int buf) {
+    lds_words_t to = (lds_words_t)lds + buf * kArStage<NS> + 256 * wave;
+    const __amdgpu_buffer_rsrc_t from = uniform_buffer(Bs);
+#pragma unroll
+    for (int j = 0; j < KS / 2; ++j) {
+      const int at = j * AR_NT + tid, row = at / (4 * KS), piece = (at % (4 * KS)) ^ (row & 7);
+      // (granules past the K dimensions are not multiplied; one zero granule leads a row and one ends it)
+      const int word = 16 * (min(piece >> 2, NS) + 1) + 4 * (piece & 3);
+      const unsigned int off = 4u * ((unsigned int)min(ct * AR_COLS + row, g.N - 1) * (unsigned int)ldbs + (unsigned int)word);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(from, to + j * AR_NT * 4, 16, (int)off, 0, 0, 0);
+    }
+    if (wave == 0)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(e.ynorm), (lds_words_t)lds + 2 * kArStage<NS> + buf * AR_COLS, 4,
+                                               4 * min(ct * AR_COLS + lane, g.N - 1), 0, 0, 0);
+  };
+  const unsigned int ma = *g.a_absmax, mb = *g.b_absmax;
+  const float scale = split_scale(ma), m2 = -2.f * (split_unscale(ma) * split_unscale(mb));
+
+#pragma unroll 1
+  for (int u = (int)((int64_t)tiles * blockIdx.x / gridDim.x); u < u1;) {   // a row tile's part of the range
+    const int rt = u / nct, c0 = u - rt * nct, c1 = min(nct, c0 + (u1 - u));
+    u += c1 - c0;
+    __syncthreads();   // (the row tile before this one: everyone is done with the stages)
+    stage(c0, 0);
+    const int row0 = rt * AR_ROWS + wave * 32;
+    f16x8 ah[NS], al[NS];   // lane (r32, kh): dims 16 s + 8 kh .. + 7 of row r32
+    {
+      const float *src = g.A + (int64_t)min(row0 + r32, g.M - 1) * g.lda;
+      float4 v[NS][2];
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v[s][q] = *reinterpret_cast<const float4 *>(src + min(16 * s + 8 * kh + 4 * q, g.K - 4));
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float f = 16 * s + 8 * kh + 4 * q < g.K ? scale : 0.f;
+          const f32x2 p0 = {v[s][q].x * f, v[s][q].y * f}, p1 = {v[s][q].z * f, v[s][q].w * f};
+          const f16x2 h0 = __builtin_convertvector(p0, f16x2), h1 = __builtin_convertvector(p1, f16x2);
+          const f16x2 l0 = __builtin_convertvector(p0 - __builtin_convertvector(h0, f32x2), f16x2);
+          const f16x2 l1 = __builtin_convertvector(p1 - __builtin_convertvector(h1, f32x2), f16x2);
+          ah[s][4 * q] = h0.x; ah[s][4 * q + 1] = h0.y; ah[s][4 * q + 2] = h1.x; ah[s][4 * q + 3] = h1.y;
+          al[s][4 * q] = l0.x; al[s][4 * q + 1] = l0.y; al[s][4 * q + 2] = l1.x; al[s][4 * q + 3] = l1.y;
+        }
+      }
+    }
+    float best[16];
+    int col[16];   // block of 32 columns
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      best[v] = __builtin_inff();
+      col[v] = 2 * c0;
+    }
+    for (int ct = c0; ct < c1; ++ct) {
+      const int buf = (ct - c0) & 1;
+      SKM_GEMM_VMCNT0();   // this wavefront's share of the stage; everyone's behind the barrier, where the other stage is free
+      __syncthreads();
+      if (ct + 1 < c1) stage(ct + 1, buf ^ 1);
+      const uint32_t *sb = lds + buf * kArStage<NS> + r32 * (KS * 16);
+      f32x16 acc[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        f16x8 bh[2], bl[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          bh[b] = *reinterpret_cast<const f16x8 *>(sb + b * 32 * (KS * 16) + (((4 * s + kh) ^ (r32 & 7)) << 2));
+          bl[b] = *reinterpret_cast<const f16x8 *>(sb + b * 32 * (KS * 16) + (((4 * s + 2 + kh) ^ (r32 & 7)) << 2));
+        }
+        auto product = [&](const f16x8 &x, const f16x8 (&y)[2]) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x, y[b], acc[b], 0, 0, 0);
+        };
+        const bool second = (s & 1) && !(PLAIN && (s >> 1) == LAST_SLAB);
+        if (!second) product(ah[s], bh);
+        product(al[s], bh);
+        product(ah[s], bl);
+        if (second) product(ah[s], bh);
+      }
+      const float *yn = reinterpret_cast<const float *>(lds + 2 * kArStage<NS> + buf * AR_COLS);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const float y = ct * AR_COLS + 32 * b + r32 < g.N ? yn[32 * b + r32] : __builtin_inff();   // (no column: never smaller)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float val = fmaf(m2, acc[b][v], y);
+          const bool less = val < best[v];
+          best[v] = less ? val : best[v];
+          col[v] = less ? 2 * ct + b : col[v];
+        }
+      }
+    }
+    // rows (a, v) of reduce_rows32 with a = 0 only
+    const unsigned long long key = reduce_rows32(
+        [&](int a, int v) { return a ? ~0ull : pack_key(best[v], 32 * col[v] + r32); }, lane);
+    const int gr = row0 + 8 * ((r32 & 15) >> 2) + 4 * kh + (r32 & 3);
+    if (r32 < 16 && gr < g.M && key < __atomic_load_n(e.best + gr, __ATOMIC_RELAXED)) atomicMin(e.best + gr, key);
+  }
+}
+
 constexpr int64_t kMaxTilesPerLaunchFwd = (1 << 24) - 1;
 template <int BK>
 constexpr size_t smem_bytes() {
@@ -751,6 +888,31 @@ static int panel_cols_for(int64_t nct) {
 inline void shift_rows(StoreArgs &e, int64_t r0) { e.C += r0 * e.ldc; }
 inline void shift_rows(ArgminArgs &e, int64_t r0) { e.best += r0; }
 
+// Rows in registers: a split copy of B at hand (32-bit byte offsets into it), aligned rows of 32 to 128 dimensions, several
+// column tiles for the rows' conversion to pay, and several tiles to a CU.  Whole calls of an exact assignment in us, tiles ->
+// rows: 100 003 x 100, k = 1000 187 -> 138; 50 000 x 64, k = 4000 213 -> 146; 600 000 x 64, k = 300 296 -> 215; 200 000 x 128,
+// k = 1024 295 -> 229; 500 000 x 32, k = 200 177 -> 133; on the other side of the line 1M x 128, k = 64 382 -> 432, 20 000 x 128,
+// k = 100 49 -> 60, 1000 x 128, k = 1000 43 -> 49, 300 x 36, k = 5000 72 -> 77.  (With registers for 256 dimensions 30 000 x 256,
+// k = 999 112 -> 103, but 70 001 x 176, k = 333 97 -> 115 and 20 000 x 192, k = 1024 78 -> 81.)
+static int64_t rows_tiles(const GemmOperands &g) {
+  return ((g.M + AR_ROWS - 1) / AR_ROWS) * (int64_t)((g.N + AR_COLS - 1) / AR_COLS);
+}
+static bool wants_rows(const GemmOperands &g) {
+  return g.b_presplit && g.a_absmax && g.b_absmax && g.K >= SBK && g.K <= 128 && g.K % 4 == 0 && g.lda % 4 == 0 && aligned16(g.A) &&
+         aligned16(g.b_presplit) && g.ldbs % 4 == 0 && (int64_t)g.N * g.ldbs < ((int64_t)1 << 29) &&
+         g.N > AR_COLS * (g.K <= 64 ? 3 : 7) && rows_tiles(g) >= 4 * num_cus() && rows_tiles(g) < ((int64_t)1 << 31);
+}
+template <int NS, bool PLAIN>
+static hipError_t launch_rows(const GemmOperands &g, const ArgminArgs &e, hipStream_t st) {
+  auto kern = argmin_rows_kernel<NS, PLAIN>;
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kArSmem<NS>);
+  if (attr_rc != hipSuccess) return attr_rc;
+  const int64_t nwg = std::min<int64_t>(rows_tiles(g), (int64_t)kArPerCu<NS> * num_cus());
+  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(AR_NT), kArSmem<NS>, st, g, g.b_presplit, g.ldbs, e);
+  return hipGetLastError();
+}
+
 template <int EPI>
 static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>::type &e, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
@@ -758,6 +920,19 @@ static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>:
   // slabs of 32 for long K; slabs of 16 when K is short or not a multiple of 32 (d' is a multiple of 16)
   const bool bk32 = (g.K % 32 == 0) && g.K >= 256;
   const bool big = wants_split256(g);
+  if constexpr (EPI == EPI_ARGMIN) {
+    if (wants_rows(g)) {
+      switch ((g.K + 15) / 16) {
+        case 2: return big ? launch_rows<2, false>(g, e, st) : launch_rows<2, true>(g, e, st);
+        case 3: return launch_rows<3, true>(g, e, st);   // (an odd number of granules: the same order either way)
+        case 4: return big ? launch_rows<4, false>(g, e, st) : launch_rows<4, true>(g, e, st);
+        case 5: return launch_rows<5, true>(g, e, st);
+        case 6: return big ? launch_rows<6, false>(g, e, st) : launch_rows<6, true>(g, e, st);
+        case 7: return launch_rows<7, true>(g, e, st);
+        default: return big ? launch_rows<8, false>(g, e, st) : launch_rows<8, true>(g, e, st);
+      }
+    }
+  }
   const int edge = big ? T2 : BM;
   const int64_t nct = (g.N + edge - 1) / edge;
   if (big && !g.b_presplit) {   // B, split into fp16 pairs, K + 32 words a row

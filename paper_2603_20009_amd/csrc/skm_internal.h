@@ -102,6 +102,8 @@ __device__ inline float reduce_rows32_f32(F value_of, int lane) {
 }
 #endif
 
+int num_cus();   // compute units of the current device
+
 // Error reporting shared by the translation units that hold entry points: records the text skm_last_error() returns
 // on this thread and gives back the code (SKM_ENOMEM for an out-of-memory HIP error, SKM_EHIP for any other).
 int report_error(int rc, const char *what);

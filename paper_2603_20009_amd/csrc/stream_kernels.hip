@@ -26,7 +26,7 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-static int num_cus() {
+int num_cus() {
   static const int cus = []() {   // (initialised once, synchronised between threads)
     int dev = 0, v = 0;
     (void)hipGetDevice(&dev);

@@ -356,3 +356,36 @@ def test_iteration_one_on_both_sides_of_the_filter(skm, orc, dg, n, k):  # noqa:
     Y0 = Xr[orc.sample_rows(6, n, k)]
     ref, _ = orc.assign_full(Xr, Y0)
     check_assignment(fit.assign.cpu().numpy(), ref, Xr, Y0, min_agree=0.999)
+
+
+# Nearest centroids with the rows in registers (aligned rows of 32 to 128 dimensions, more than 192 columns or 448 beyond 64
+# dimensions, four tiles of 256 x 64 to a CU): every number of 16-dimension steps, rows and columns that end inside a tile,
+# ranges that begin and end inside a row tile; against the oracle and, where the old form stands beside it, bit by bit.
+@pytest.mark.parametrize("n,d,k", [(66_000, 32, 257), (40_001, 48, 449), (33_000, 64, 513), (25_700, 80, 700), (36_000, 96, 511),
+                                   (20_003, 112, 900), (18_000, 128, 1000), (16_384, 100, 1024), (90_000, 36, 193)])
+def test_exact_assignment_with_rows_in_registers(skm, orc, dg, n, d, k):  # noqa: F811
+    say("rows in registers", n, d, k)
+    X = dg.mixture(n, d, 300, 5, "embed")
+    Y = dg.mixture(k, d, 300, 5, "embed", sample_seed=3)
+    a, dist = skm.assign_exact(X.cuda(), Y.cuda())
+    few = torch.randperm(n, generator=torch.Generator().manual_seed(1))[:3000].sort().values
+    few[-1] = n - 1
+    ao, do = orc.assign_full(X[few].numpy().astype(np.float64), Y.numpy().astype(np.float64))
+    check_assignment(a[few.cuda()].cpu().numpy(), ao, X[few].numpy(), Y.numpy(), min_agree=0.999)
+    # a call with few rows takes the tiles of 128 x 128, which add the products in the same order
+    part = slice(n // 3, n // 3 + 1500)
+    scale = X.abs().max()
+    rows = torch.cat([X[part], torch.full((1, d), float(scale))])    # (the same magnitude bound: the same halves)
+    b, dist_b = skm.assign_exact(rows.cuda(), Y.cuda())
+    assert torch.equal(a[part], b[:-1]) and torch.equal(dist[part], dist_b[:-1])
+
+
+def test_rows_in_registers_that_are_no_numbers(skm, dg):  # noqa: F811
+    say("rows in registers, nan and inf")
+    n, d, k = 70_000, 64, 300
+    X, Y = dg.mixture(n, d, 100, 5, "embed").cuda(), dg.mixture(k, d, 100, 5, "embed", sample_seed=3).cuda()
+    want = skm.assign_exact(X, Y)[0]
+    X[5000] = float("nan")
+    got = skm.assign_exact(X, Y)[0]
+    keep = torch.arange(n, device="cuda") != 5000
+    assert torch.equal(got[keep], want[keep]) and int(got[5000]) == 0
