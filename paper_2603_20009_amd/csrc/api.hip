@@ -569,6 +569,10 @@ struct Ctx {
   double *S = nullptr;               // [k][ds] cluster sums of the last update (fp64), valid once S_valid
   bool S_valid = false;
   bool split_last = false;           // the last update re-seeded empty clusters (their donors' rows are perturbed)
+  // thresholds that the last step left in tau and that still hold: of no point, of those in untouched clusters, of all
+  enum { KEPT_NONE = 0, KEPT_UNTOUCHED = 1, KEPT_ALL = 2 };
+  int tau_kept = KEPT_NONE;
+  uint32_t *touched = nullptr;       // [k] clusters that the last (incremental) update changed
   int32_t inc_updates = 0;           // update steps that took the incremental path
   int32_t *split_dev = nullptr;
   bool block_stats = false;
@@ -751,6 +755,7 @@ struct Ctx {
       up.max_segments = update_max_segments(n, k);
       HIPCHK(pool.get(&up.partial, (size_t)up.max_segments * ds));
       HIPCHK(pool.get(&split_dev, (size_t)3 * k + 2));   // (empty, donor) pairs | first split of every chain
+      HIPCHK(pool.get(&touched, (size_t)k));
       // the incremental update is used while at most one point in eight changes its label
       HIPCHK(pool.get(&S, (size_t)k * ds));
       inc.capacity = 2 * (n / 8) + 2;
@@ -1134,6 +1139,9 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     c.ldx = c.ds;
     c.permuted = true;
     c.xh_valid = c.Xh != nullptr;
+  } else if (have_prev && c.tau_kept != Ctx::KEPT_NONE && c.xnp_valid && !(screen && !c.xh_valid)) {
+    HIPCHK(launch_tau_kept(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau_kept == Ctx::KEPT_ALL ? nullptr : c.touched, c.tau, c.best,
+                           c.st, tau_stamp));
   } else {
     // The first pruned step of a context also writes the tables that depend on the points only.  The plane of hi halves
     // is left out where this step does not read it and a regrouping pass, which writes all of them again, is likely to
@@ -1146,6 +1154,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
                            nullptr, from_keys ? c.prev : nullptr, xh, c.flag, tau_stamp));
     if (tables) c.xh_valid = xh != nullptr;
   }
+  c.tau_kept = Ctx::KEPT_NONE;
   c.order_fresh = false;
   c.xnp_valid = true;
   stamp_t *border = tm.mark(ST_TAU);   // for the kernel that comes next
@@ -1266,7 +1275,21 @@ int step_update(Ctx &c, Rng &split_rng, float split_eps, int64_t *nempty_out, in
   }
   c.order_fresh = fresh;
   c.y_amax_valid = true;
-  return split_empty(c, split_rng, split_eps, nempty_out);
+  const bool split_before = c.split_last;
+  if (int rc = split_empty(c, split_rng, split_eps, nempty_out)) return rc;
+  // A cluster that no point joined or left has the centroid it had, bit by bit (unless one of the last two splits moved it).
+  // Marking the others is a launch more: where the thresholds are a pass of some length, and at most a quarter to a half of the
+  // clusters can be touched.
+  c.tau_kept = Ctx::KEPT_NONE;
+  if (!full && !fresh && !split_before && !c.split_last && c.ds <= kTauKeptMaxDims) {
+    if (changed == 0) {
+      c.tau_kept = Ctx::KEPT_ALL;
+    } else if (4 * changed <= c.k && c.n * c.ds >= ((int64_t)1 << 24)) {
+      HIPCHK(launch_mark_touched(c.inc.ent_lab, (int32_t)(2 * changed), c.k, c.touched, c.st));
+      c.tau_kept = Ctx::KEPT_UNTOUCHED;
+    }
+  }
+  return SKM_OK;
 }
 
 // Empty clusters after an update (Section 3.2): c.up.cnt holds the cluster sizes, and the step's report (if sizes_known)
@@ -1835,6 +1858,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
       HIPCHK(launch_fill_u32(c.amax + Ctx::AM_Y, 1, 0u, c.st));
       HIPCHK(launch_normalize_rows(c.Y, c.ds, k, c.ds, c.st, c.amax + Ctx::AM_Y));
       c.y_amax_valid = true;
+      c.tau_kept = Ctx::KEPT_NONE;   // (scaling a row that has been scaled before may change its last bits)
     }
     tm.mark_next(ST_UPDATE);   // (no wait: the next step's launches follow while the update runs)
     run = t;

@@ -352,6 +352,12 @@ hipError_t launch_prune(const PruneArgs &a, hipStream_t st);
 // xh (optional, with xs): also the plane of hi halves of launch_split_rows' out_hi.
 // assign = NULL: the labels are the low halves of best[] (packed keys of an argmin); a point whose key is ~0 takes label 0
 // and sets bit 1 of *unset (optional).  label_out without order receives the label of every point.
+// The thresholds of the last step, kept where a point's cluster was not touched since (touched[c], NULL: none was): tau[] in
+// and out, best[] out.
+constexpr int32_t kTauKeptMaxDims = 2048;
+hipError_t launch_tau_kept(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy, const int32_t *assign,
+                           const uint32_t *touched, float *tau, unsigned long long *best, hipStream_t st, stamp_t *stamp);
+hipError_t launch_mark_touched(const int32_t *labels, int32_t m, int32_t k, uint32_t *touched, hipStream_t st);
 hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
                            const int32_t *assign, float *tau, unsigned long long *best, hipStream_t st,
                            float *xnp = nullptr, uint32_t *xs = nullptr, const unsigned int *x_absmax = nullptr,

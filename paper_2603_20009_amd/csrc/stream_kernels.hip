@@ -357,6 +357,92 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
   return hipGetLastError();
 }
 
+// Thresholds of a step before which few clusters were touched: a point whose cluster neither gained nor lost a point has the
+// centroid, the label and with them the threshold of the step before, which is still in tau[]; only the others are taken again
+// (a wavefront's points one after the other, two rows in flight).  touched: a word per cluster, or NULL where none was.  The
+// sums are those of tau_init_kernel.  1M x 1536 1112 us -> 8 with no cluster touched, 103 with a tenth of them.
+template <int NV>
+__global__ void __launch_bounds__(256) tau_kept_kernel(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y,
+                                                       int64_t ldy, const int32_t *assign, const uint32_t *touched, float *tau,
+                                                       unsigned long long *best, stamp_t *stamp) {
+  put_stamp(stamp);
+  const int lane = threadIdx.x & 63;
+  for (int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64; base < n; base += (int64_t)gridDim.x * 256) {
+    const int64_t p = min(base + lane, n - 1);
+    const bool in = base + lane < n;
+    const int a = assign[p];
+    const bool again = in && touched && touched[a] != 0u;
+    if (in && !again) best[p] = pack_key(tau[p], a);
+    unsigned long long left = __ballot(again);
+    while (left) {
+      int64_t i[2];
+      int c[2];
+      float4 x[2][NV], y[2][NV];
+      const int first = __builtin_ctzll(left);
+      left &= left - 1ull;
+      const bool two = left != 0ull;
+      const int second = two ? __builtin_ctzll(left) : first;
+      left &= left - (two ? 1ull : 0ull);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int b = r ? second : first;
+        i[r] = base + b;
+        c[r] = __builtin_amdgcn_readlane(a, b);
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+          const int col = lane * 4 + 256 * u;
+          x[r][u] = col < ds ? load_stream4(Xr + i[r] * ldx + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+          y[r][u] = col < ds ? *reinterpret_cast<const float4 *>(Y + (int64_t)c[r] * ldy + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+          const float dx = x[r][u].x - y[r][u].x, dy = x[r][u].y - y[r][u].y, dz = x[r][u].z - y[r][u].z, dw = x[r][u].w - y[r][u].w;
+          s = fmaf(dx, dx, s);
+          s = fmaf(dy, dy, s);
+          s = fmaf(dz, dz, s);
+          s = fmaf(dw, dw, s);
+        }
+        s = wave_sum(s);
+        if (lane == 0) {
+          tau[i[r]] = s;
+          best[i[r]] = pack_key(s, c[r]);
+        }
+      }
+    }
+  }
+}
+hipError_t launch_tau_kept(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy, const int32_t *assign,
+                           const uint32_t *touched, float *tau, unsigned long long *best, hipStream_t st, stamp_t *stamp) {
+  if (n <= 0) return hipSuccess;
+  if (ds > kTauKeptMaxDims) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, (int64_t)num_cus() * 32);
+  const int nv = (ds + 255) / 256;
+#define SKM_TAU_KEPT(NV) hipLaunchKernelGGL(tau_kept_kernel<NV>, dim3(blocks), dim3(256), 0, st, Xr, ldx, n, ds, Y, ldy, assign, touched, tau, best, stamp)
+  if (nv <= 1) SKM_TAU_KEPT(1);
+  else if (nv <= 2) SKM_TAU_KEPT(2);
+  else if (nv <= 3) SKM_TAU_KEPT(3);
+  else if (nv <= 4) SKM_TAU_KEPT(4);
+  else if (nv <= 6) SKM_TAU_KEPT(6);
+  else SKM_TAU_KEPT(8);
+#undef SKM_TAU_KEPT
+  return hipGetLastError();
+}
+
+// touched[c] = 1 for the clusters that the m labels name, 0 for the others (one workgroup: the two passes are ordered)
+__global__ void __launch_bounds__(1024) mark_touched_kernel(const int32_t *labels, int m, int32_t k, uint32_t *touched) {
+  for (int c = threadIdx.x; c < k; c += 1024) touched[c] = 0u;
+  __syncthreads();
+  for (int e = threadIdx.x; e < m; e += 1024) touched[labels[e]] = 1u;
+}
+hipError_t launch_mark_touched(const int32_t *labels, int32_t m, int32_t k, uint32_t *touched, hipStream_t st) {
+  hipLaunchKernelGGL(mark_touched_kernel, dim3(1), dim3(1024), 0, st, labels, m, k, touched);
+  return hipGetLastError();
+}
+
 // dst[idx[p]] = src[p] (4-byte items): per-point results back from a regrouped order to the caller's
 __global__ void scatter_by_index_kernel(const uint32_t *src, const int32_t *idx, int64_t n, uint32_t *dst) {
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) dst[idx[p]] = src[p];

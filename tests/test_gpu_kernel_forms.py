@@ -389,3 +389,23 @@ def test_rows_in_registers_that_are_no_numbers(skm, dg):  # noqa: F811
     got = skm.assign_exact(X, Y)[0]
     keep = torch.arange(n, device="cuda") != 5000
     assert torch.equal(got[keep], want[keep]) and int(got[5000]) == 0
+
+
+# Thresholds kept from the step before: of all points once no label changes any more, of those in untouched clusters while few
+# do (rows of some length, at most a quarter as many changes as clusters).  Every row length that the pass is made for.
+@pytest.mark.parametrize("n,d,k", [(66_000, 256, 300), (33_500, 500, 400), (24_000, 700, 500), (17_000, 1000, 400), (12_000, 1500, 300),
+                                   (9000, 2000, 220), (20_000, 64, 100)])
+def test_thresholds_kept_from_the_step_before(skm, dg, n, d, k):  # noqa: F811
+    say("kept thresholds", n, d, k)
+    X = dg.mixture(n, d, 2 * k, 4, "embed").cuda()
+    R = skm.make_rotation(d, 2)
+    fit = skm.fit(X, k, 14, 3, skm.FitOptions(R=R))
+    changed = [row["changed"] for row in fit.trace[:-1]]
+    assert 0 in changed and (n * d < 1 << 24 or any(0 < c <= k // 4 for c in changed))
+    full = skm.fit(X, k, 14, 3, skm.FitOptions(R=R, full_update=True))        # (takes every threshold again)
+    assert torch.equal(fit.assign, full.assign) and [r["survivors"] for r in fit.trace] == [r["survivors"] for r in full.trace]
+    # fp32 sums of d squares in either form: d 2^-24 of the sum at most
+    assert ((fit.dist - full.dist).abs() <= 2 * d * 2.0 ** -24 * full.dist + 1e-12).all()
+    direct = ((X.double() - fit.centroids.double()[fit.assign.long()]) ** 2).sum(1)
+    # ... and the rotated copies of rows and centroids are rounded to fp32: 2^-23 (||x|| + ||y||) per row (norms of 1 at most)
+    assert ((fit.dist.double() - direct).abs() <= (2 * d * 2.0 ** -24) * direct + 8 * 2.0 ** -21 * direct.sqrt() + 1e-9).all()
