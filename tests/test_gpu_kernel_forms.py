@@ -409,3 +409,20 @@ def test_thresholds_kept_from_the_step_before(skm, dg, n, d, k):  # noqa: F811
     direct = ((X.double() - fit.centroids.double()[fit.assign.long()]) ** 2).sum(1)
     # ... and the rotated copies of rows and centroids are rounded to fp32: 2^-23 (||x|| + ||y||) per row (norms of 1 at most)
     assert ((fit.dist.double() - direct).abs() <= (2 * d * 2.0 ** -24) * direct + 8 * 2.0 ** -21 * direct.sqrt() + 1e-9).all()
+
+
+# The pass that closes a step: 1024 points a workgroup, 8192 from 2^18 on; more workgroups than its 1024 threads from 8 388 609
+# points on; sizes read ahead up to 1024 clusters (4096 from 2^18 points), the rest in a loop.
+@pytest.mark.parametrize("n,d,k", [(1, 16, 1), (255, 20, 3), (1023, 16, 7), (1025, 16, 1024), (4097, 32, 1025), (20_000, 64, 2500),
+                                   (262_143, 16, 10), (262_145, 16, 5000), (8_388_609, 16, 5)])
+def test_what_the_closing_pass_reports(skm, n, d, k):  # noqa: F811
+    say("closing pass", n, d, k)
+    g = torch.Generator("cuda").manual_seed(n + k)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    Y = X[torch.randperm(n, generator=g, device="cuda")[:k]].clone()
+    prev = torch.randint(0, k, (n,), generator=g, device="cuda", dtype=torch.int32)
+    a, dist, row = skm.assign(X, Y, prev, 16, skm.FitOptions(R=torch.eye(d, device="cuda")))
+    assert row["changed"] == int((a != prev).sum()) and int(a.min()) >= 0 and int(a.max()) < k
+    assert row["nempty"] == int((torch.bincount(a.long(), minlength=k) == 0).sum())
+    # fp64 sums of the same fp32 values in another order: n 2^-53 of the sum at most
+    assert row["objective"] == pytest.approx(float(dist.double().sum()), rel=n * 2.0 ** -53, abs=1e-300)
