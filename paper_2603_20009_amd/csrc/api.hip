@@ -529,8 +529,8 @@ struct Ctx {
   int64_t ldx = 0;
   float *Y = nullptr;         // centroids k x ds (rotated space)
   float *Ypdx = nullptr;
-  uint32_t *Xs = nullptr;     // [n][ds + 32] split-fp16 copy of Xr for the progressive kernel, made with xnp
-  uint32_t *Ys = nullptr;     // [k][ds + 32] the same of Y, remade in every pruned step
+  uint32_t *Xs = nullptr;     // split-fp16 copy of Xr for the progressive kernel, made with xnp
+  uint32_t *Ys = nullptr;     // the same of Y, remade in every pruned step
   float *xnp = nullptr;       // [ds / 16][n] prefix norms of the points at every multiple of 16 dims, written by the
   bool xnp_valid = false;     // first pruned step (the points of a context never change)
   bool xh_valid = false;      // Xh likewise: left out of a pass that a regrouping pass will repeat
@@ -581,7 +581,8 @@ struct Ctx {
   double last_prune_frac = -1.0;     // of the previous pruned step of this context (-1: none yet)
   uint32_t *colmask = nullptr;
   float *scr_arow = nullptr, *scr_ycol = nullptr;
-  uint32_t *Xh = nullptr, *Yh = nullptr;   // [n][ds / 2 + 16], [k][ds / 2 + 16]: the hi halves of Xs, Ys as planes of their own
+  uint32_t *Xh = nullptr, *Yh = nullptr;   // the hi halves of Xs, Ys as planes of their own
+  uint32_t *Yd = nullptr;                  // ... of Ys from d' on, for the listed tiles
   int32_t pruned_steps = 0;                // pruned steps this context has completed
   bool exact_filter_off = false;           // iteration 1 takes the full GEMM (set after a candidate-list overflow)
   float2 *scr_widen = nullptr;
@@ -673,8 +674,8 @@ struct Ctx {
     const int32_t nbmax = (ds - 16 + kBlockDims - 1) / kBlockDims + 1;
     HIPCHK(pool.get(&Ypdx, (size_t)nbmax * k * kBlockDims));
     HIPCHK(pool.get(&xnp, (size_t)(ds / 16) * n));
-    HIPCHK(pool.get(&Xs, (size_t)n * (ds + 32)));
-    HIPCHK(pool.get(&Ys, (size_t)k * (ds + 32)));
+    HIPCHK(pool.get(&Xs, split_words(n, ds)));
+    HIPCHK(pool.get(&Ys, split_words(k, ds)));
     HIPCHK(pool.get(&ynp, (size_t)nbmax * k));
     HIPCHK(pool.get(&ynorm, (size_t)k));
     HIPCHK(pool.get(&tau, (size_t)n));
@@ -702,7 +703,7 @@ struct Ctx {
     // (the kernels behind the filter address a listed centroid's row with 32-bit byte offsets: not for a centroid table
     // of 2^30 words or more, where the steps simply run unfiltered)
     const bool may_screen = (screen_mode > 0 || (screen_mode == 0 && k >= 256)) &&
-                            (int64_t)k * (ds + 32) < ((int64_t)1 << 30);
+                            ((int64_t)k + 1) * split_ld(ds) < ((int64_t)1 << 30);
     if (may_screen) sub_cap = std::max<int64_t>(sub_cap, 16 * std::min<int64_t>(chunk_rows, n));
     pair_cap = sub_cap * kSubLists;
     if (pair_cap >= ((int64_t)1 << 32)) return fail(SKM_EINVAL, "pair_budget too large (must stay below 2^32 pairs)");
@@ -717,8 +718,9 @@ struct Ctx {
       HIPCHK(pool.get(&scr_ntiles, 2));   // the tile count, then a float scalar of the filter
       HIPCHK(pool.get(&scr_arow, (size_t)std::min<int64_t>(chunk_rows, n)));
       HIPCHK(pool.get(&scr_ycol, (size_t)k));
-      HIPCHK(pool.get(&Xh, (size_t)n * (ds / 2 + 16)));
-      HIPCHK(pool.get(&Yh, (size_t)k * (ds / 2 + 16)));
+      HIPCHK(pool.get(&Xh, split_words(n, ds) / 2));
+      HIPCHK(pool.get(&Yh, split_words(k, ds) / 2));
+      HIPCHK(pool.get(&Yd, split_words(k, ds)));
       HIPCHK(pool.get(&scr_cols, (size_t)tiles_chunk * kListCols));
       HIPCHK(pool.get(&scr_widen, (size_t)kMaxBlocks + 1));
       HIPCHK(pool.get(&scr_tile_rt, (size_t)tiles_chunk));
@@ -938,7 +940,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
   CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
   cp.ynorm = c.ynorm; cp.dn = K;
   cp.dprime = 0; cp.nb = nbK; cp.Ypdx = c.Ypdx; cp.pdx_cols = K;
-  cp.Ys = c.Ys; cp.Yh = c.Yh; cp.y_absmax = c.amax + Ctx::AM_Y;
+  cp.Ys = c.Ys; cp.Yh = c.Yh; cp.hi_dims = K; cp.y_absmax = c.amax + Ctx::AM_Y;
   cp.ratio_out = c.ratio_dev;
   cp.stamp = start;
   c.clear_with(cp);
@@ -951,8 +953,8 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
     const int64_t rows = std::min<int64_t>(c.chunk_rows, c.n - r0);
     unsigned int *fill = c.counters + (size_t)ch * kSubLists * kSubListStride;
     ScreenLaunch sl{};
-    sl.A = c.Xh + r0 * (c.ds / 2 + 16); sl.lda = c.ds / 2 + 16; sl.M = (int32_t)rows;
-    sl.B = c.Yh; sl.ldb = c.ds / 2 + 16; sl.N = c.k;
+    sl.A = c.Xh + r0 * (split_ld(c.ds) / 2); sl.lda = split_ld(c.ds) / 2; sl.M = (int32_t)rows;
+    sl.B = c.Yh; sl.ldb = split_ld(c.ds) / 2; sl.N = c.k;
     sl.a_absmax = c.xr_bound; sl.b_absmax = c.amax + Ctx::AM_Y;
     sl.ds = c.ds; sl.dprime = K; sl.ratio0 = 1.f;
     sl.tau = c.tau; sl.row_base = r0;
@@ -1018,7 +1020,7 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
   GemmOperands g{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, c.ds};
   g.a_absmax = c.xr_bound; g.b_absmax = c.amax + Ctx::AM_Y;
-  g.b_presplit = c.Ys; g.ldbs = c.ds + 32;
+  g.b_presplit = c.Ys; g.ldbs = split_ld(c.ds);
   HIPCHK(gemm_argmin(g, c.ynorm, c.best, c.st));
   // winners -> direct squared distances (also the objective of this step)
   HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, nullptr, nullptr, c.best, c.st, nullptr, nullptr, nullptr,
@@ -1073,7 +1075,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     CentroidPrep cp{c.Y, c.ds, c.k, c.ds};
     cp.dprime = dprime; cp.nb = nb; cp.Ypdx = c.Ypdx; cp.ynp = c.ynp;
     if (!have_prev && !found) { cp.ynorm = c.ynorm; cp.dn = dprime; }   // (for the product below)
-    cp.Ys = c.Ys; cp.Yh = screen ? c.Yh : nullptr; cp.y_absmax = c.amax + Ctx::AM_Y;
+    cp.Ys = c.Ys; cp.Yh = screen ? c.Yh : nullptr; cp.hi_dims = dprime; cp.Yd = screen ? c.Yd : nullptr; cp.y_absmax = c.amax + Ctx::AM_Y;
     cp.ratio_out = c.ratio_dev;
     cp.stamp = tm.mark(sought ? ST_GEMM : ST_NONE);   // (the search for the incumbents ends here)
     c.clear_with(cp);
@@ -1085,7 +1087,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
     g0.a_absmax = c.xr_bound; g0.b_absmax = c.amax + Ctx::AM_Y;
-    g0.b_presplit = c.Ys; g0.ldbs = c.ds + 32;
+    g0.b_presplit = c.Ys; g0.ldbs = split_ld(c.ds);
     HIPCHK(gemm_argmin(g0, c.ynorm, c.best, c.st));
     if (c.group_now) {
       HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, c.n, c.prev, nullptr, nullptr, c.k, c.flag}, c.st));
@@ -1162,8 +1164,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     const int64_t r0 = (int64_t)ch * c.chunk_rows;
     const int64_t rows = std::min<int64_t>(c.chunk_rows, c.n - r0);
     ProgArgs g{};
-    g.A = c.Xs + r0 * (c.ds + 32); g.lda = c.ds + 32; g.M = (int32_t)rows;
-    g.B = c.Ys; g.ldb = c.ds + 32; g.N = c.k;
+    g.A = c.Xs + r0 * split_ld(c.ds); g.lda = split_ld(c.ds); g.M = (int32_t)rows;
+    g.B = c.Ys; g.ldb = split_ld(c.ds); g.N = c.k;
     g.a_absmax = c.xr_bound; g.b_absmax = c.amax + Ctx::AM_Y;
     g.ds = c.ds; g.d = c.d; g.dprime = dprime; g.nb = nb;
     g.ratio = c.ratio_dev; g.tau = c.tau; g.prev = c.prev; g.row_base = r0;
@@ -1175,8 +1177,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     g.best = c.best; g.scal = c.scal; g.block_stats = c.block_stats ? 1 : 0;
     if (screen) {
       ScreenLaunch sl{};
-      sl.A = c.Xh + r0 * (c.ds / 2 + 16); sl.lda = c.ds / 2 + 16; sl.M = g.M;
-      sl.B = c.Yh; sl.ldb = c.ds / 2 + 16; sl.N = g.N;
+      sl.A = c.Xh + r0 * (split_ld(c.ds) / 2); sl.lda = split_ld(c.ds) / 2; sl.M = g.M;
+      sl.B = c.Yh; sl.ldb = split_ld(c.ds) / 2; sl.N = g.N;
       sl.a_absmax = g.a_absmax; sl.b_absmax = g.b_absmax;
       sl.ds = c.ds; sl.dprime = dprime; sl.ratio0 = ratio[0];
       sl.tau = c.tau; sl.row_base = r0;
@@ -1202,7 +1204,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
         //   deep_max: 1/16 143.9 | 55.4 | 264.6, 1/8 123.7 | 49.5 | 253.4, 1/4 as it was, 1/2 105.8 | 44.3 | 239.8, no limit 104.4 | 44.2 |
         //   239.5: half, so that a tile of poor incumbents is not done twice
         g.deep = 1;
-        g.Ah = sl.A; g.Bh = sl.B; g.widen = c.scr_widen;
+        g.Ah = sl.A; g.Bh = c.Yd; g.widen = c.scr_widen;
         g.emit_first = c.emit_max * 5 / 16;
         g.emit_deep = 24;
         g.deep_stride = 3;
@@ -1469,7 +1471,7 @@ int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const floa
   }
   if (back) HIPCHK(pool.get(&rot.Rp, (size_t)d * ds));
   HIPCHK(pool.get(&rot.Rtp, (size_t)d * ds));
-  if (d % 32 == 0) HIPCHK(pool.get(&rot.Rs, (size_t)d * ((size_t)d + 32)));
+  if (d % 32 == 0) HIPCHK(pool.get(&rot.Rs, split_words(d, d)));
   HIPCHK(launch_rotation_operands(R_dev, d, rot.Rp, rot.Rtp, ds, rot.amax, st));
   return SKM_OK;
 }
@@ -1533,7 +1535,7 @@ GtPlan gt_plan(int64_t n, int32_t d, int32_t nq, int32_t K) {
   p.cap = 1024;
   while ((double)p.cap < 4.0 * expect + 512.0 && p.cap < kGtMaxCand) p.cap <<= 1;
   p.on = (double)p.cap >= 2.0 * expect;
-  p.bytes = (size_t)(p.chunk + nq) * p.ds * 2 + (size_t)p.chunk * 8 + (size_t)nq * (16 + 4 + (size_t)p.ngroups * 4 + (size_t)p.cap * 8) + 8192;
+  p.bytes = (size_t)(p.chunk + nq + 2) * p.ds * 2 + (size_t)p.chunk * 8 + (size_t)nq * (16 + 4 + (size_t)p.ngroups * 4 + (size_t)p.cap * 8) + 8192;
   return p;
 }
 size_t gt_full_bytes(int64_t n, int32_t nq) { return (size_t)n * 4 + (size_t)nq * (size_t)std::min<int64_t>(n, kGtChunk) * 4 + 4096; }
@@ -1545,8 +1547,8 @@ int ground_truth_screened(Pool &pool, const GtPlan &p, const float *X, int64_t n
   float *scale = nullptr, *term = nullptr, *qscale = nullptr, *qterm = nullptr, *tq = nullptr, *rterm = nullptr, *gmin = nullptr;
   unsigned long long *cand = nullptr;
   unsigned int *words = nullptr;   // max norm of the points so far | of the sample | of the queries | [nq] list lengths
-  HIPCHK(pool.get(&plane, (size_t)p.chunk * (p.ds / 2)));
-  HIPCHK(pool.get(&qplane, (size_t)nq * (p.ds / 2)));
+  HIPCHK(pool.get(&plane, (size_t)((p.chunk + 1) / 2 * 2) * (p.ds / 2)));
+  HIPCHK(pool.get(&qplane, (size_t)round_up(nq, 2) * (p.ds / 2)));
   HIPCHK(pool.get(&scale, (size_t)p.chunk));
   HIPCHK(pool.get(&term, (size_t)p.chunk));
   HIPCHK(pool.get(&qscale, (size_t)nq));
@@ -1968,8 +1970,8 @@ struct KeptRows {
     }
     const size_t budget = (free_b + block_cache().idle_bytes()) / 2;
     const int64_t nbatch = (n + W - 1) / W;
-    const size_t row = (size_t)ds * 4, more = (size_t)(ds + 32) * 4 + (size_t)ds / 4 + (hi ? (size_t)(ds / 2 + 16) * 4 : 0);
-    const size_t fixed = (size_t)nbatch * 4 + 5 * 256;
+    const size_t row = (size_t)ds * 4, more = (size_t)split_ld(ds) * 4 + (size_t)ds / 4 + (hi ? (size_t)split_ld(ds) * 2 : 0);
+    const size_t fixed = (size_t)nbatch * 4 + 5 * 256 + (size_t)split_ld(ds) * 6;   // (an odd row more in the copies)
     if (budget <= fixed) return;
     // the tables of all rows, or the rows alone, as many whole batches as there is room for
     const bool with = (size_t)n * (row + more) + fixed <= budget;
@@ -1996,9 +1998,9 @@ struct KeptRows {
     X = reinterpret_cast<float *>(carve((size_t)r * row));
     bound = reinterpret_cast<unsigned int *>(carve((size_t)nbatch * 4));
     if (with) {
-      Xs = reinterpret_cast<uint32_t *>(carve((size_t)r * (size_t)(ds + 32) * 4));
+      Xs = reinterpret_cast<uint32_t *>(carve(split_words(r, ds) * 4));
       xnp = reinterpret_cast<float *>(carve((size_t)r * ((size_t)ds / 4)));
-      if (hi) Xh = reinterpret_cast<uint32_t *>(carve((size_t)r * (size_t)(ds / 2 + 16) * 4));
+      if (hi) Xh = reinterpret_cast<uint32_t *>(carve(split_words(r, ds) * 2));
     }
     batches = kept;
     rows = r;
@@ -2161,9 +2163,9 @@ int fit_host_impl(const float *Xh, int64_t n, int32_t d, int32_t k, int32_t iter
       c.nchunks = (int32_t)((rows + tile_rows - 1) / tile_rows);
       c.Xr = Xb; c.ldx = c.ds;
       c.xr_bound = keep ? kept.bound + b : c.amax + Ctx::AM_XR;
-      c.Xs = keep && kept.tables ? kept.Xs + (size_t)r0 * (c.ds + 32) : own_Xs;
+      c.Xs = keep && kept.tables ? kept.Xs + (size_t)r0 * split_ld(c.ds) : own_Xs;
       c.xnp = keep && kept.tables ? kept.xnp + (size_t)r0 * (c.ds / 16) : own_xnp;
-      c.Xh = keep && kept.tables ? (kept.Xh ? kept.Xh + (size_t)r0 * (c.ds / 2 + 16) : nullptr) : own_Xh;
+      c.Xh = keep && kept.tables ? (kept.Xh ? kept.Xh + (size_t)r0 * (split_ld(c.ds) / 2) : nullptr) : own_Xh;
       c.xnp_valid = keep && kept.tables && kept.xnp_valid[(size_t)b];
       c.xh_valid = keep && kept.tables && kept.xh_valid[(size_t)b];
       if (pass == 0 || !keep) {   // the rows arrive
@@ -2877,7 +2879,7 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
   HIPCHK(pool.get(&ynorm, (size_t)k));
   HIPCHK(pool.get(&best, (size_t)n));
   HIPCHK(pool.get(&amax, 2));
-  HIPCHK(pool.get(&ysplit, (size_t)k * ((size_t)ds + 32)));
+  HIPCHK(pool.get(&ysplit, split_words(k, ds)));
   HIPCHK(launch_fill_u32(amax, 2, 0u, st));
   HIPCHK(launch_absmax(X, d, n, d, amax, st));
   HIPCHK(launch_absmax(centroids, d, k, d, amax + 1, st));
@@ -2897,7 +2899,7 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
     }
     GemmOperands g{Xp, dx, (int32_t)rows, Yp, ds, k, dx};
     g.a_absmax = amax; g.b_absmax = amax + 1;
-    g.b_presplit = ysplit; g.ldbs = ds + 32;
+    g.b_presplit = ysplit; g.ldbs = split_ld(ds);
     HIPCHK(gemm_argmin(g, ynorm, best + r0, st));
     if (dist_out)   // labels and direct distances in one pass over the rows
       HIPCHK(launch_tau_init(Xp, dx, rows, dx, Yp, ds, nullptr, dist_out + r0, best + r0, st, nullptr, nullptr, nullptr,
@@ -2983,7 +2985,7 @@ int skm_rotate(const float *X, int64_t n, int32_t d, const float *R, int32_t tra
   if (n < 1 || n >= (int64_t)1 << 31 || d < 1 || d > 16384) return fail(SKM_EINVAL, "shape out of range");
   hipStream_t st = (hipStream_t)stream;
   const int32_t ds = round_up(d, 16);
-  CallArena ws(((size_t)d * ds + (size_t)d * (d + 32)) * 4 + 4096);
+  CallArena ws(((size_t)d * ds + split_words(d, d)) * 4 + 4096);
   Pool pool;
   float *B = nullptr;  // B[c][kk] = R[kk][c] for X R, R[c][kk] for X R^T
   unsigned int *amax = nullptr;
@@ -2994,7 +2996,7 @@ int skm_rotate(const float *X, int64_t n, int32_t d, const float *R, int32_t tra
   HIPCHK(launch_absmax(X, d, n, d, amax, st));
   GemmOperands g{X, d, (int32_t)n, B, ds, d, d};
   g.a_absmax = amax; g.b_absmax = amax + 1;
-  if (d % 32 == 0) HIPCHK(pool.get(&g.b_split, (size_t)d * ((size_t)d + 32)));
+  if (d % 32 == 0) HIPCHK(pool.get(&g.b_split, split_words(d, d)));
   HIPCHK(gemm_store(g, out, d, d, 1.f, 0.f, st));
   HIPCHK(hipStreamSynchronize(st));
   ws.finished();

@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
     const f32x2_t p0 = {v.x * sc, v.y * sc}, p1 = {v.z * sc, v.w * sc};
-    *reinterpret_cast<uint2 *>(dst + c / 2) =
+    *reinterpret_cast<uint2 *>(dst + 32 * (c / 32) + (c % 32) / 2) =
         make_uint2(__builtin_bit_cast(unsigned int, __builtin_convertvector(p0, f16x2_t)),
                    __builtin_bit_cast(unsigned int, __builtin_convertvector(p1, f16x2_t)));
   };
@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t
       m = fmaxf(m, __shfl_xor(m, o, 64));
     }
     const float sc = m > 0.f ? split_scale(__builtin_bit_cast(unsigned int, m)) : 1.f;
-    uint32_t *dst = plane + i * (int64_t)(ds / 2);
+    uint32_t *dst = plane + split_row(i, ds / 2);
     if (NV > 0) {
 #pragma unroll
       for (int u = 0; u < NV; ++u)

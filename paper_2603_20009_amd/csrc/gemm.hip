@@ -558,7 +558,8 @@ __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, cons
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int rb = 8 * wave + 128 * j + lrow;
-    gb[j] = Bsplit + (int64_t)min(col0 + rb, g.N - 1) * ldbs + 16 + 4 * (lpos ^ ((rb >> 1) & 7));   // one zero granule leads a row
+    const int piece = lpos ^ ((rb >> 1) & 7);   // of the slab's two granules (one zero granule leads a row)
+    gb[j] = Bsplit + split_row(min(col0 + rb, g.N - 1), ldbs) + 32 * (1 + (piece >> 2)) + 4 * (piece & 3);
     const int ra_ = arow + 128 * j, sw = (ra_ >> 1) & 7;
     ga[j] = g.A + (int64_t)min(row0 + ra_, g.M - 1) * g.lda + 4 * kq;
     wa[j] = lds + ra_ * 32 + ((c_hi ^ sw) << 2) + 2 * (kq & 1);
@@ -568,7 +569,7 @@ __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, cons
     uint32_t *sb = lds + stage * T2_STAGE + T2 * 32 + 8 * wave * 32;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gb[j] + k0),
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gb[j] + 2 * k0),
                                        (__attribute__((address_space(3))) void *)(sb + 128 * j * 32), 16, 0, 0);
   };
   float4 ra[2];
@@ -696,8 +697,8 @@ argmin_rows_kernel(GemmOperands g, const uint32_t *Bs, int64_t ldbs, ArgminArgs 
     for (int j = 0; j < KS / 2; ++j) {
       const int at = j * AR_NT + tid, row = at / (4 * KS), piece = (at % (4 * KS)) ^ (row & 7);
       // (granules past the K dimensions are not multiplied; one zero granule leads a row and one ends it)
-      const int word = 16 * (min(piece >> 2, NS) + 1) + 4 * (piece & 3);
-      const unsigned int off = 4u * ((unsigned int)min(ct * AR_COLS + row, g.N - 1) * (unsigned int)ldbs + (unsigned int)word);
+      const int word = 32 * (min(piece >> 2, NS) + 1) + 4 * (piece & 3);
+      const unsigned int off = 4u * ((unsigned int)split_row(min(ct * AR_COLS + row, g.N - 1), ldbs) + (unsigned int)word);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(from, to + j * AR_NT * 4, 16, (int)off, 0, 0, 0);
     }
     if (wave == 0)
@@ -867,7 +868,7 @@ static hipError_t launch_split256(const GemmOperands &g, const typename EpiArgs<
   if (nwg <= 0) return hipSuccess;
   if (nwg > (1 << 22) - 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NT2), smem, st, g,
-                     g.b_presplit ? g.b_presplit : (const uint32_t *)g.b_split, g.b_presplit ? g.ldbs : (int64_t)g.K + 32, e);
+                     g.b_presplit ? g.b_presplit : (const uint32_t *)g.b_split, g.b_presplit ? g.ldbs : (int64_t)split_ld(g.K), e);
   return hipGetLastError();
 }
 
@@ -899,7 +900,7 @@ static int64_t rows_tiles(const GemmOperands &g) {
 }
 static bool wants_rows(const GemmOperands &g) {
   return g.b_presplit && g.a_absmax && g.b_absmax && g.K >= SBK && g.K <= 128 && g.K % 4 == 0 && g.lda % 4 == 0 && aligned16(g.A) &&
-         aligned16(g.b_presplit) && g.ldbs % 4 == 0 && (int64_t)g.N * g.ldbs < ((int64_t)1 << 29) &&
+         aligned16(g.b_presplit) && g.ldbs % 4 == 0 && ((int64_t)g.N + 1) * g.ldbs < ((int64_t)1 << 29) &&
          g.N > AR_COLS * (g.K <= 64 ? 3 : 7) && rows_tiles(g) >= 4 * num_cus() && rows_tiles(g) < ((int64_t)1 << 31);
 }
 template <int NS, bool PLAIN>
@@ -935,7 +936,7 @@ static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>:
   }
   const int edge = big ? T2 : BM;
   const int64_t nct = (g.N + edge - 1) / edge;
-  if (big && !g.b_presplit) {   // B, split into fp16 pairs, K + 32 words a row
+  if (big && !g.b_presplit) {   // B, split into fp16 pairs
     hipError_t rc = launch_split_rows(g.B, g.ldb, g.N, g.K, g.b_absmax, g.b_split, st);
     if (rc != hipSuccess) return rc;
   }

@@ -33,14 +33,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- split-fp16 copies of the operands
-// Row r of a matrix scaled by split_scale(*absmax): granule g (dims 16 g .. 16 g + 15) is 16 words at word
-// 16 (g + 1) of the row: 8 words of hi halves (fp16 of the scaled value, two per word), then 8 words of lo
-// halves (fp16 of the remainder).  Granule positions 0 and ds / 16 + 1 are zero, so that a 32-dimension slab
-// starting 16 dimensions before the row or ending 16 after it reads zeros.  Row stride ds + 32 words.
-// out_hi (optional): the hi halves once more as a plane of their own, ds / 2 + 16 words a row (8 zero words, the row two
-// dimensions a word, 8 zero words): what the low-precision first filter reads, 64 contiguous bytes per row and slab.
+// Row r of a matrix scaled by split_scale(*absmax): granule g (dims 16 g .. 16 g + 15) is 16 words: 8 words of hi halves
+// (fp16 of the scaled value, two per word), then 8 words of lo halves (fp16 of the remainder).  Granule positions 0 and
+// ds / 16 + 1 are zero.  Where a granule lies: see skm_internal.h.
 __global__ void __launch_bounds__(256) split_rows_kernel(const float *A, int64_t lda, int64_t rows, int32_t ds,
-                                                         const unsigned int *absmax, uint32_t *out, uint32_t *out_hi) {
+                                                         const unsigned int *absmax, uint32_t *out) {
   const float scale = split_scale(*absmax);
   const int per_row = ds / 4 + 8;   // float4 pieces per output row, pads included
   const int64_t total = rows * per_row;
@@ -58,21 +55,19 @@ __global__ void __launch_bounds__(256) split_rows_kernel(const float *A, int64_t
       hi.x = __builtin_bit_cast(unsigned int, h0); hi.y = __builtin_bit_cast(unsigned int, h1);
       lo.x = __builtin_bit_cast(unsigned int, l0); lo.y = __builtin_bit_cast(unsigned int, l1);
     }
-    uint32_t *dst = out + r * (int64_t)(ds + 32) + 16 * gpos;
+    uint32_t *dst = out + split_row(r, split_ld(ds)) + 32 * gpos;
     *reinterpret_cast<uint2 *>(dst + 2 * q) = hi;
     *reinterpret_cast<uint2 *>(dst + 8 + 2 * q) = lo;
-    if (out_hi) *reinterpret_cast<uint2 *>(out_hi + r * (int64_t)(ds / 2 + 16) + 2 * piece) = hi;
   }
 }
 hipError_t launch_split_rows(const float *A, int64_t lda, int64_t rows, int32_t ds, const unsigned int *absmax,
-                             uint32_t *out, hipStream_t st, uint32_t *out_hi) {
+                             uint32_t *out, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   if (ds % 16 != 0 || lda % 4 != 0 || (reinterpret_cast<uintptr_t>(A) & 15u) || (reinterpret_cast<uintptr_t>(out) & 15u))
     return hipErrorInvalidValue;
   const int64_t total = rows * (ds / 4 + 8);
   const int64_t blocks = std::min<int64_t>((total + 255) / 256, 1 << 16);
-  if (reinterpret_cast<uintptr_t>(out_hi) & 15u) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, lda, rows, ds, absmax, out, out_hi);
+  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, lda, rows, ds, absmax, out);
   return hipGetLastError();
 }
 
@@ -247,7 +242,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // Staging: load instruction j of wavefront w moves tile rows 64 j + 16 w .. + 15 of a unit.
   const int ld_row = 16 * wave + (lane >> 2);                       // + 64 j
   const unsigned int ld_piece = 16u * ((lane & 3) ^ ((ld_row >> 2) & 3));   // byte offset of the piece that belongs at this lane's position
-  const int ldh = g.ds / 2 + 16;
+  const int ldh = (int)(g.lda >> 1);
 
   // ---- the tile being loaded.  Rows past the end repeat the last one (their accumulator elements start dead).
   // byte offsets of this lane's pieces from the tile's first row / the first row of the tile's columns
@@ -288,25 +283,26 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (LISTED && g.deep) baseAh = g.Ah + (int64_t)row0 * ldh;
     const int limA = g.M - 1 - row0;
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda) * 4u + ld_piece;
+    for (int j = 0; j < A_LD; ++j) offA[j] = (unsigned int)split_row(min(ld_row + ROWS_PASS * j, limA), (int)g.lda) * 4u + ld_piece;
     nrow = row0 + min(tid & (BM - 1), limA);
     if constexpr (LISTED) {
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)max(s_ids[par][ld_row + ROWS_PASS * j], 0) * (unsigned int)g.ldb * 4u + ld_piece;   // (the launcher checks the range)
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)split_row(max(s_ids[par][ld_row + ROWS_PASS * j], 0), (int)g.ldb) * 4u + ld_piece;   // (the launcher checks the range)
       ncol = max(s_ids[par][tid], 0);
     } else {
       const int col0 = ct * BN, limB = g.N - 1 - col0;
       baseB = g.B + (int64_t)col0 * g.ldb;
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb) * 4u + ld_piece;
+      for (int j = 0; j < B_LD; ++j) offB[j] = (unsigned int)split_row(min(ld_row + ROWS_PASS * j, limB), (int)g.ldb) * 4u + ld_piece;
       ncol = col0 + min(tid, limB);
     }
   };
   // ---- requests: the next unit of the aimed tile -> LDS (asynchronous).  Buffer loads: a uniform base, a uniform offset
-  // that moves on by 64 bytes a unit, and an offset register per load.  (They are known to be no LDS reads: behind
-  // global_load_lds the compiler lets the first matrix instruction of a unit wait for all of its fragments.)  Rows of the
-  // one-product copy are half as long as those of the three-product copy: the offsets are halved once where a tile
-  // changes over.
+  // that moves on by 128 bytes a unit (a unit of two rows), and an offset register per load.  (They are known to be no LDS reads: behind
+  // global_load_lds the compiler lets the first matrix instruction of a unit wait for all of its fragments.)  Row pairs of
+  // the points' hi plane are half as long as those of the three-product copy: the offsets (128 bytes a granule of two rows,
+  // 64 bytes a row) are halved once where a tile changes over.  Where d' is an odd multiple of 16 the plane's units and those
+  // of this tile are half a unit apart: a piece comes from the second half of one or the first half of the next.
   int cur = 0;            // word offset of the LDS stage of the unit being multiplied
   int rstage = 0;         // ... of the next request
   int treq = 0, rstep = 16;   // dimensions requested so far of the tile, and those of the next request
@@ -322,18 +318,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int j = 0; j < B_LD; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, sb + (BM + ROWS_PASS * j) * ROW_WORDS, 16, (int)offB[j], soff, 0, 0);
-    soff += 64;
+    soff += 128;
     treq += rstep;
     rstage = ring(rstage);
   };
+  const unsigned int ld_odd = !LISTED || (g.dprime & 16) == 0 ? 0u : ld_piece < 32u ? 32u : 96u;
   auto change_over = [&]() {   // to one product, at dimension d'
     fromA = baseAh;
     fromB = g.Bh;
-    soff = 4 * (8 + g.dprime / 2);
+    soff = 128 * (g.dprime / 32);
 #pragma unroll
-    for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) >> 1) + ld_piece;
-#pragma unroll
-    for (int j = 0; j < B_LD; ++j) offB[j] = ((offB[j] - ld_piece) >> 1) + ld_piece;
+    for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] & ~127u) >> 1) + (offA[j] & 127u) + ld_odd;
     rstep = 32;
   };
   // Checkpoint m's prefix norms (the points' table has a row per 16 dimensions, the centroids' a row per checkpoint of
@@ -368,7 +363,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     load_norm(0);
     fromA = baseA;
     fromB = baseB;
-    soff = 64;   // (a granule of zeros leads every row)
+    soff = 128;   // (a granule of zeros leads every row)
     treq = 0;
     rstep = 16;
     rstage = cur;
@@ -668,9 +663,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       redone = true;
       if (rstep == 32) {
 #pragma unroll
-        for (int j = 0; j < A_LD; ++j) offA[j] = ((offA[j] - ld_piece) << 1) + ld_piece;
-#pragma unroll
-        for (int j = 0; j < B_LD; ++j) offB[j] = ((offB[j] - ld_piece) << 1) + ld_piece;
+        for (int j = 0; j < A_LD; ++j) offA[j] = (((offA[j] - ld_odd) & ~127u) << 1) + ((offA[j] - ld_odd) & 127u);
       }
       start_tile();
       --tile_no;
@@ -789,7 +782,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 hipError_t launch_progressive(const ProgArgs &args, hipStream_t st) {
   ProgArgs g = args;
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.ds % 16 != 0 || g.dprime % 16 != 0 || g.dprime < 16 || g.dprime > g.ds || g.lda != g.ds + 32 || g.ldb != g.ds + 32 ||
+  if (g.ds % 16 != 0 || g.dprime % 16 != 0 || g.dprime < 16 || g.dprime > g.ds || g.lda != split_ld(g.ds) || g.ldb != split_ld(g.ds) ||
       g.nb > kMaxBlocks || (reinterpret_cast<uintptr_t>(g.A) & 15u) || (reinterpret_cast<uintptr_t>(g.B) & 15u) ||
       g.N > (1 << 24))
     return hipErrorInvalidValue;
@@ -817,7 +810,7 @@ hipError_t launch_progressive(const ProgArgs &args, hipStream_t st) {
   static const Setup setup;
   if (setup.rc != hipSuccess) return setup.rc;
   const int wgs = setup.wgs;
-  if (g.col_list && (int64_t)g.N * g.ldb >= ((int64_t)1 << 30)) return hipErrorInvalidValue;   // (32-bit byte offsets)
+  if (g.col_list && ((int64_t)g.N + 1) * g.ldb >= ((int64_t)1 << 30)) return hipErrorInvalidValue;   // (32-bit byte offsets)
   if ((g.col_list != nullptr) != (g.tile_rt != nullptr) || (g.col_list != nullptr) != (g.ntiles != nullptr))
     return hipErrorInvalidValue;
   if (g.deep && (g.nb < 3 || g.deep_stride < 1 || !g.col_list || !g.Ah || !g.Bh || !g.widen || (reinterpret_cast<uintptr_t>(g.Ah) & 15u) ||

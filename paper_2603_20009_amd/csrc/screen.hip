@@ -49,7 +49,7 @@ constexpr int DEPTH = 3, NSTAGE = 4;              // slabs requested ahead of th
 }  // namespace
 
 struct ScreenArgs {
-  const uint32_t *A;   // hi halves of the split-fp16 copy of the chunk's points (launch_split_rows' out_hi), row stride lda words
+  const uint32_t *A;   // plane of the hi halves of the chunk's points (see launch_split_rows), lda words a row
   int64_t lda;
   int32_t M;
   const uint32_t *B;   // the same of the centroids
@@ -87,9 +87,8 @@ enum { SCREEN_FIRST_TEST = 0, SCREEN_EXACT = 1, SCREEN_GROUPS = 2, SCREEN_CANDID
 // LDS rows are 64 bytes (four 16-byte pieces: dims 8 c .. 8 c + 7 of the slab, c = 2 h + kh for half-slab h and lane
 // half kh); piece c of row r sits at position c ^ ((r >> 2) & 3), so that the 16-byte fragment reads of 16 consecutive
 // rows fall into 16 different bank groups.  Staging is global -> LDS directly, 16 bytes per lane, four lanes per row:
-// the lane that fills a position fetches the piece that belongs there.  In global memory the hi halves of a row are
-// one contiguous plane (see launch_split_rows): a slab row is 64 contiguous bytes.  The kernel is persistent: every XCD walks a
-// contiguous range of tiles (column tile fastest inside panels of 8 column tiles), its workgroups take every n-th;
+// the lane that fills a position fetches the piece that belongs there.  In global memory (see launch_split_rows) a slab of two
+// rows is a line of 128 bytes.  The kernel is persistent: every XCD walks a contiguous range of tiles (column tile fastest inside panels of 8 column tiles), its workgroups take every n-th;
 // the first slab of a workgroup's next tile is requested before the finished tile is tested.
 //
 // EXACT (Algorithm 1, iteration 1, where nothing prunes): the same multiply over ALL dimensions finds, for every point,
@@ -141,9 +140,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int ld_row = 16 * wave + lrow;                        // + 128 j
   const int ld_c = lpos ^ ((ld_row >> 2) & 3);                // piece that belongs at this lane's position
   const int ld_words = 4 * ld_c;                              // its word offset inside the slab's 16 hi words
-  const int koff = NEIGH ? 0 : -((BK - g.dprime % BK) % BK);
-  const int nslab = (g.dprime - koff) / BK;                   // slabs [koff, d')
-  const int kw0 = NEIGH ? 0 : 8 + koff / 2;                   // word of the hi plane where slab 0 starts
+  const int nslab = (g.dprime + BK - 1) / BK;                 // (the columns' plane is zero from d' on)
 
   // ---- the loading side runs DEPTH slabs ahead of the multiplying side, across tile boundaries (a tile of a
   // well-pruned step is two or three slabs: one tile's worth of loads in flight would leave the matrix cores waiting
@@ -162,9 +159,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       baseB = g.B + (int64_t)col0 * g.ldb;
       const int limA = g.M - 1 - row0, limB = g.N - 1 - col0;   // rows / columns past the end repeat the last one
 #pragma unroll
-      for (int j = 0; j < A_LD; ++j) offA[j] = 4u * (unsigned int)(min(ld_row + ROWS_PASS * j, limA) * (int)g.lda + ld_words);
+      for (int j = 0; j < A_LD; ++j) offA[j] = 4u * (unsigned int)((int)split_row(min(ld_row + ROWS_PASS * j, limA), (int)g.lda) + ld_words);
 #pragma unroll
-      for (int j = 0; j < B_LD; ++j) offB[j] = 4u * (unsigned int)(min(ld_row + ROWS_PASS * j, limB) * (int)g.ldb + ld_words);
+      for (int j = 0; j < B_LD; ++j) offB[j] = 4u * (unsigned int)((int)split_row(min(ld_row + ROWS_PASS * j, limB), (int)g.ldb) + ld_words);
       // the tile's row terms (wavefronts 0-3) and column terms (4-7): one more 4-byte load each, straight into LDS
       {
         const int e = tid & (BM - 1);
@@ -186,7 +183,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // one of a slab's loads: a uniform base and a uniform offset, an offset register per load
   auto load = [&](int j) {
     lds_words_t sb = (lds_words_t)smem + (ljob & (NSTAGE - 1)) * STAGE_WORDS + 16 * wave * ROW_WORDS;
-    const int at = 4 * (kw0 + (BK / 2) * ls);
+    const int at = 128 * ls;
     if (j < A_LD)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(uniform_buffer(baseA), sb + ROWS_PASS * j * ROW_WORDS, 16, (int)offA[j < A_LD ? j : 0], at, 0, 0);
     else
@@ -721,7 +718,7 @@ hipError_t launch_neighbour_screen(const NeighbourLaunch &a, bool groups, hipStr
 
 hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.dprime % 16 != 0 || a.dprime < 16 || a.dprime > a.ds || a.lda != a.ds / 2 + 16 || a.ldb != a.ds / 2 + 16 ||
+  if (a.dprime % 16 != 0 || a.dprime < 16 || a.dprime > a.ds || a.lda != split_ld(a.ds) / 2 || a.ldb != split_ld(a.ds) / 2 ||
       (reinterpret_cast<uintptr_t>(a.A) & 15u) || (reinterpret_cast<uintptr_t>(a.B) & 15u) || a.N > (1 << 24))
     return hipErrorInvalidValue;
   if (a.exact && (!a.rowmin || !a.pairs || !a.pair_count || !a.overflow)) return hipErrorInvalidValue;

@@ -208,16 +208,26 @@ constexpr int kListGroup = 8;    // row tiles whose listed tiles are placed in t
 // at most emit_max are alive, and offers finished distances below tau_i to best[] at t = d.
 // Rows are local to the chunk: global row = row_base + i; tau/prev/best are indexed by global row.
 // Split-fp16 copy of a matrix in the byte order of the progressive kernel's LDS tiles (launch_split_rows): row stride
-// ds + 32 words; dims 16 g .. 16 g + 15 of a row are the 16 words at 16 (g + 1): 8 words of hi halves, 8 of lo halves
-// of the values scaled by split_scale(*absmax); the 16 words before and after the row's data are zero.
-// out_hi (optional): the hi halves once more as a plane of their own (row stride ds / 2 + 16 words: 8 zero words, the
-// row two dimensions a word, 8 zero words), which the low-precision first filter reads.
+// split_ld(ds) words.  Granule g + 1 of a row, dims 16 g .. 16 g + 15, is 16 words: 8 of hi halves, 8 of lo halves of the
+// values scaled by split_scale(*absmax); granule 0 and the one behind the row's data are zero.  Rows lie in pairs: word
+// split_row(r, ld) + 32 g is where granule g of row r starts, the two rows' granules g side by side in 128 bytes.
+// What a tile kernel loads of a row at a time is 64 bytes (four lanes of a global -> LDS load), and the load unit takes a
+// line of 128 bytes every two clocks whether all of it is wanted or half: 17 TB/s of 64-byte pieces from the L2s where two
+// neighbours share a line 32 (gathered pieces across two lines 18).  In pairs of rows, dense tiles of 1M x 1536, k = 1024,
+// took 10.0 instead of 10.75 ms, the one-product multiply of all their pairs 2.9 instead of 4.1 (there the rows used to
+// start in the middle of a 64-byte block as well).
+// The hi halves once more as a plane of their own (what the low-precision filter reads): split_ld(ds) / 2 words a row, unit
+// u (dims 32 u .. 32 u + 31) of row r at word split_row(r, split_ld(ds) / 2) + 32 u; a last unit of 16 dims ends in zeros.
+// Buffers hold an even number of rows; the odd one out is never read.
+__host__ __device__ inline int32_t split_ld(int32_t ds) { return (ds + 31) / 32 * 32 + 32; }
+__host__ __device__ inline int64_t split_row(int64_t r, int64_t ld) { return (r >> 1) * (2 * ld) + 16 * (r & 1); }
+inline size_t split_words(int64_t rows, int32_t ds) { return (size_t)((rows + 1) / 2 * 2) * (size_t)split_ld(ds); }
 hipError_t launch_split_rows(const float *A, int64_t lda, int64_t rows, int32_t ds, const unsigned int *absmax,
-                             uint32_t *out, hipStream_t st, uint32_t *out_hi = nullptr);
+                             uint32_t *out, hipStream_t st);
 
 struct ProgArgs {
   const uint32_t *A;       // split-fp16 copy of the rotated points of the chunk (launch_split_rows)
-  int64_t lda;             // ds + 32 words
+  int64_t lda;             // split_ld(ds)
   int32_t M;
   const uint32_t *B;       // split-fp16 copy of the rotated centroids
   int64_t ldb;
@@ -246,8 +256,9 @@ struct ProgArgs {
   // the list's columns come before the tile.
   const int2 *tile_rt = nullptr;
   const int32_t *col_list = nullptr, *ntiles = nullptr;
-  // Listed columns only: one product and widened tests behind the first test (deep = 1).  Ah / Bh: the planes of hi
-  // halves; widen[m] = (widening per unit of the row's norm behind d', guard) of checkpoint m.  A tile hands over at
+  // Listed columns only: one product and widened tests behind the first test (deep = 1).  Ah: the plane of hi
+  // halves; Bh: those of the centroids, dims d' + 32 u .. of row r at word split_row(r, ldb) + 32 (d' / 32 + u) (rows as far
+  // apart as B's: one offset serves both; a listed row's units lie in whole blocks of 64 bytes for every d'); widen[m] = (widening per unit of the row's norm behind d', guard) of checkpoint m.  A tile hands over at
   // the first test with at most emit_first pairs alive, later with at most emit_deep columns (of half a tile's rows) that
   // hold any; one with more than deep_max pairs alive at the first test takes three products throughout.  A test every
   // deep_stride blocks.
@@ -388,7 +399,9 @@ struct CentroidPrep {
   int32_t pdx_cols = 1 << 30;
   float *ynp = nullptr;        // [nb + 1][k] prefix norms at the checkpoints min(ds, dprime + 64 m)
   uint32_t *Ys = nullptr;      // split-fp16 copy (launch_split_rows), scaled by the bound *y_absmax
-  uint32_t *Yh = nullptr;      // its plane of hi halves
+  uint32_t *Yh = nullptr;      // its plane of hi halves, zero from dimension hi_dims on
+  int32_t hi_dims = 0;
+  uint32_t *Yd = nullptr;      // the hi halves from dprime on (with Ys; see ProgArgs::Bh)
   const unsigned int *y_absmax = nullptr;
   unsigned int *clear = nullptr;
   int64_t clear_words = 0;

@@ -84,7 +84,7 @@ int skm_assign_exact_static(const float *X, int64_t n, int32_t d, const float *c
   GemmOperands g{X, d, (int32_t)n, centroids, d, k, d};
   g.a_absmax = amax;
   g.b_absmax = amax + 1;
-  if (d % 32 == 0 && (size_t)k * ((size_t)d + 32) <= kSplitWords) g.b_split = split;
+  if (d % 32 == 0 && split_words(k, d) <= kSplitWords) g.b_split = split;
   HIPCHK(gemm_argmin(g, ynorm, best, st));
   HIPCHK(launch_finalize_assign(FinalizeArgs{best, nullptr, n, assign_out, nullptr, nullptr, k, nullptr}, st));
   if (dist_out) HIPCHK(launch_tau_init(X, d, n, d, centroids, d, assign_out, dist_out, nullptr, st));

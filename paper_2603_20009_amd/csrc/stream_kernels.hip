@@ -49,13 +49,13 @@ int num_cus() {
 // inclusive scan over the 16 quads of the wavefront (then over u) gives every quad the norm of the row up to the
 // end of its piece.
 // With `xs` the pass also writes the split-fp16 copy of the row that the progressive kernel multiplies (the layout
-// of launch_split_rows: row stride ds + 32 words, zero granules around the data).
+// of launch_split_rows).
 struct PrefixOut {
   float *xnp;        // [ds / 16][n] or NULL
   int64_t n;
   int32_t ds;
-  uint32_t *xs;      // [n][ds + 32] or NULL
-  uint32_t *xh;      // [n][ds / 2 + 16] or NULL (with xs): the hi halves as a plane of their own
+  uint32_t *xs;      // the split copy or NULL
+  uint32_t *xh;      // or NULL (with xs): the hi halves as a plane of their own
   const unsigned int *absmax;   // bound of |X| (bit pattern) that fixes the scale of xs
   float scale;       // split_scale(*absmax), set by the kernel
   // Regrouping (all three or none): output slot p takes point order[p]; its row is copied to xr_out (row stride ds)
@@ -66,31 +66,83 @@ struct PrefixOut {
   unsigned int *unset = nullptr;   // labels taken from packed keys: bit 1 is set if a point has none
   int span = 64;                   // BATCH: points a workgroup takes at a time (64, or 16 when there are few)
   stamp_t *stamp = nullptr;
+  int hi_dims = 1 << 30;           // xh is zero from this dimension on
+  uint32_t *xd = nullptr;          // or NULL (with xs): the hi halves from dimension xd_from on (CentroidPrep::Yd)
+  int xd_from = 0;
 };
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-// this lane's float4 at column c (a quarter of granule c / 16) -> hi and lo halves in the split copy of row i
-__device__ inline void emit_split(const PrefixOut &po, int64_t i, int c, const float4 &v) {
-  const f32x2_t p0 = {v.x * po.scale, v.y * po.scale}, p1 = {v.z * po.scale, v.w * po.scale};
+struct SplitHalves {
+  uint2 hi, lo;
+};
+__device__ inline SplitHalves split_halves(const float4 &v, float scale) {
+  const f32x2_t p0 = {v.x * scale, v.y * scale}, p1 = {v.z * scale, v.w * scale};
   const f16x2_t h0 = __builtin_convertvector(p0, f16x2_t), h1 = __builtin_convertvector(p1, f16x2_t);
   const f16x2_t l0 = __builtin_convertvector(p0 - __builtin_convertvector(h0, f32x2_t), f16x2_t);
   const f16x2_t l1 = __builtin_convertvector(p1 - __builtin_convertvector(h1, f32x2_t), f16x2_t);
-  uint32_t *dst = po.xs + i * (int64_t)(po.ds + 32) + 16 * (c / 16 + 1) + 2 * ((c / 4) & 3);
-  *reinterpret_cast<uint2 *>(dst) = make_uint2(__builtin_bit_cast(unsigned int, h0), __builtin_bit_cast(unsigned int, h1));
-  *reinterpret_cast<uint2 *>(dst + 8) = make_uint2(__builtin_bit_cast(unsigned int, l0), __builtin_bit_cast(unsigned int, l1));
-  if (po.xh)
-    *reinterpret_cast<uint2 *>(po.xh + i * (int64_t)(po.ds / 2 + 16) + 8 + c / 2) =
-        make_uint2(__builtin_bit_cast(unsigned int, h0), __builtin_bit_cast(unsigned int, h1));
+  return {make_uint2(__builtin_bit_cast(unsigned int, h0), __builtin_bit_cast(unsigned int, h1)),
+          make_uint2(__builtin_bit_cast(unsigned int, l0), __builtin_bit_cast(unsigned int, l1))};
 }
-// the zero granules before and after the data of row i (lanes 0..3 and 4..7, 16 bytes each)
+// a quad of lanes holds a granule; its lanes 0, 1 receive the 32 bytes of hi halves, lanes 2, 3 the lo halves, 16 bytes each
+__device__ inline uint4 granule_piece(const SplitHalves &v, int lane) {
+  auto even = [](unsigned int w) { return (unsigned int)__builtin_amdgcn_mov_dpp((int)w, 0x88, 0xF, 0xF, true); };   // quad_perm [0,2,0,2]
+  auto odd = [](unsigned int w) { return (unsigned int)__builtin_amdgcn_mov_dpp((int)w, 0xDD, 0xF, 0xF, true); };    // quad_perm [1,3,1,3]
+  const uint4 h = make_uint4(even(v.hi.x), even(v.hi.y), odd(v.hi.x), odd(v.hi.y));
+  const uint4 l = make_uint4(even(v.lo.x), even(v.lo.y), odd(v.lo.x), odd(v.lo.y));
+  return lane & 2 ? l : h;
+}
+// this lane's float4 at column c (a quarter of granule c / 16; c / 4 = lane modulo 4) -> hi and lo halves in the split copy of
+// row i
+__device__ inline void emit_split(const PrefixOut &po, int64_t i, int c, const float4 &v) {
+  const SplitHalves h = split_halves(v, po.scale);
+  const int ld = split_ld(po.ds), q = (c / 4) & 3;
+  *reinterpret_cast<uint4 *>(po.xs + split_row(i, ld) + 32 * (c / 16 + 1) + 4 * q) = granule_piece(h, q);
+  if (po.xh)
+    *reinterpret_cast<uint2 *>(po.xh + split_row(i, ld / 2) + 32 * (c / 32) + (c % 32) / 2) = c < po.hi_dims ? h.hi : make_uint2(0u, 0u);
+  if (po.xd && c >= po.xd_from) {
+    const int e = c - po.xd_from;
+    *reinterpret_cast<uint2 *>(po.xd + split_row(i, ld) + 32 * (po.xd_from / 32 + e / 32) + (e % 32) / 2) = h.hi;
+  }
+}
+// The same of rows i and i + 1, i even (tables of points), 256 columns from c0 on, through 2 KB of LDS of this wavefront's own:
+// there the two rows' granules lie as they do in memory, 128 bytes each (the 16-byte pieces rotated by the granule's number),
+// and every store takes whole lines.  (Half lines a store, a row a wavefront: the pass of 1M x 1536 that writes the tables
+// 4.7 instead of 3.3 ms.)  All lanes take part; zeros past the row.
+__device__ inline void emit_split_pair(const PrefixOut &po, int64_t i, int lane, int c0, const float4 &v0, const float4 &v1,
+                                       uint32_t *ex) {
+  const int ld = split_ld(po.ds);
+  auto at = [](int g, int piece) { return 32 * g + 4 * (piece ^ (g & 7)); };
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const SplitHalves h = split_halves(r ? v1 : v0, po.scale);
+    uint32_t *w = ex + at(lane >> 2, 4 * r + ((lane >> 1) & 1)) + 2 * (lane & 1);
+    *reinterpret_cast<uint2 *>(w) = h.hi;
+    *reinterpret_cast<uint2 *>(ex + at(lane >> 2, 4 * r + 2 + ((lane >> 1) & 1)) + 2 * (lane & 1)) = h.lo;
+  }
+  __builtin_amdgcn_wave_barrier();
+  uint32_t *dst = po.xs + (i >> 1) * (2 * (int64_t)ld) + 32 * (c0 / 16 + 1) + 4 * lane;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int g = 8 * e + (lane >> 3);
+    if (c0 + 16 * g < po.ds) *reinterpret_cast<uint4 *>(dst + 256 * e) = *reinterpret_cast<const uint4 *>(ex + at(g, lane & 7));
+  }
+  if (po.xh) {   // unit lane / 8 of 32 dimensions, row (lane / 4) & 1, piece lane & 3: a half of one granule's hi halves
+    const int g = 2 * (lane >> 3) + ((lane >> 1) & 1);
+    if (c0 + 16 * g < po.ds)
+      *reinterpret_cast<uint4 *>(po.xh + (i >> 1) * (int64_t)ld + c0 + 4 * lane) =
+          *reinterpret_cast<const uint4 *>(ex + at(g, (lane & 4) + (lane & 1)));
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+// the zero granules before and after the data of row i (lanes 0..3 and 4..7, 16 bytes each), and the zero half of the hi
+// plane's last unit (lanes 8, 9)
 __device__ inline void emit_split_pads(const PrefixOut &po, int64_t i, int lane) {
   if (lane < 8) {
-    uint32_t *dst = po.xs + i * (int64_t)(po.ds + 32) + (lane < 4 ? 4 * lane : po.ds + 16 + 4 * (lane - 4));
+    uint32_t *dst = po.xs + split_row(i, split_ld(po.ds)) + (lane < 4 ? 0 : 32 * (po.ds / 16 + 1)) + 4 * (lane & 3);
     *reinterpret_cast<uint4 *>(dst) = make_uint4(0u, 0u, 0u, 0u);
-  } else if (lane < 12 && po.xh) {   // the 8 zero words at either end of the hi plane's row
-    const int e = lane - 8;
-    uint32_t *dst = po.xh + i * (int64_t)(po.ds / 2 + 16) + (e >> 1) * (8 + po.ds / 2) + 4 * (e & 1);
+  } else if (lane < 10 && po.xh && po.ds % 32 != 0) {
+    uint32_t *dst = po.xh + split_row(i, split_ld(po.ds) / 2) + 32 * (po.ds / 32) + 8 + 4 * (lane - 8);
     *reinterpret_cast<uint4 *>(dst) = make_uint4(0u, 0u, 0u, 0u);
   }
 }
@@ -130,7 +182,7 @@ __device__ inline float4 load_stream4(const float *p) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// BATCH (with po.xnp, NV > 0): a workgroup takes 64 consecutive points at a time and writes their prefix norms through
+// BATCH (with po.xnp and po.xs, NV > 0): a workgroup takes 64 consecutive points at a time and writes their prefix norms through
 // LDS, 256 contiguous bytes per table row, instead of one 4-byte store per point and row.  Where 64 points a workgroup
 // would leave most of the chip without one (a wavefront then walks sixteen rows one after the other while other CUs
 // idle), it takes 16.
@@ -140,10 +192,11 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
                                                        const float *Y, int64_t ldy, const int32_t *assign, float *tau,
                                                        unsigned long long *best, PrefixOut po) {
   __shared__ float s_np[BATCH ? kPrefixStageRows * 64 : 1];
+  __shared__ __align__(16) uint32_t s_pair[BATCH ? 4 * 512 : 4];
   put_stamp(po.stamp);
   if (po.xs) po.scale = split_scale(*po.absmax);
   const int lane = threadIdx.x & 63;
-  auto point = [&](int64_t p, int slot) {   // output slot p <- point i
+  auto point = [&](int64_t p) {   // output slot p <- point i
     const int64_t i = po.order ? (int64_t)po.order[p] : p;
     int a;
     if (assign) {
@@ -186,7 +239,7 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
         for (int u = 0; u < NV; ++u) {
           if (256 * u >= ds) break;
           const float q = fmaf(xv[u].x, xv[u].x, fmaf(xv[u].y, xv[u].y, fmaf(xv[u].z, xv[u].z, xv[u].w * xv[u].w)));
-          base = emit_prefix(po, p, lane, u, q, base, BATCH ? s_np : nullptr, slot);
+          base = emit_prefix(po, p, lane, u, q, base);
         }
       }
       if (po.xs) {
@@ -232,14 +285,87 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
       if (po.label_out) po.label_out[p] = a;
     }
   };
+  // rows p and p + 1 (p even), for the tables; past the end row p stands for row p + 1 and only fills the odd row of its pair
+  auto two_points = [&](int64_t p, int slot) {
+    constexpr int NX = NV > 0 ? NV : 1;
+    const bool both = p + 1 < n;
+    int a[2];
+    float4 xv[2][NX];
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int64_t o = both ? p + r : p, i = po.order ? (int64_t)po.order[o] : o;
+      if (assign) {
+        a[r] = assign[i];
+      } else {   // the labels are still packed keys (an argmin that has just run)
+        const unsigned long long key = best[i];
+        a[r] = (int)(key & 0xffffffffull);
+        if (key == ~0ull) {   // no kernel offered this point a centroid: reported, kept in range
+          a[r] = 0;
+          if (lane == 0 && po.unset) atomicOr(po.unset, 2u);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NX; ++u) {
+        const int c = lane * 4 + 256 * u;
+        xv[r][u] = c < ds ? load_stream4(Xr + i * ldx + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      __builtin_amdgcn_sched_barrier(0);   // (one centroid row at a time in registers)
+      const float *y = Y + (int64_t)a[r] * ldy;
+      float4 yv[NX];
+#pragma unroll
+      for (int u = 0; u < NX; ++u) {
+        const int c = lane * 4 + 256 * u;
+        yv[u] = c < ds ? *reinterpret_cast<const float4 *>(y + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      float base = 0.f;
+#pragma unroll
+      for (int u = 0; u < NX; ++u) {
+        const float4 &x = xv[r][u];
+        const float dx = x.x - yv[u].x, dy = x.y - yv[u].y, dz = x.z - yv[u].z, dw = x.w - yv[u].w;
+        s[r] = fmaf(dx, dx, s[r]);
+        s[r] = fmaf(dy, dy, s[r]);
+        s[r] = fmaf(dz, dz, s[r]);
+        s[r] = fmaf(dw, dw, s[r]);
+      }
+#pragma unroll
+      for (int u = 0; u < NX; ++u) {
+        if (256 * u >= ds) break;
+        const float4 &x = xv[r][u];
+        const float q = fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w)));
+        base = emit_prefix(po, p + r, lane, u, q, base, s_np, slot + r);
+      }
+    }
+    emit_split_pads(po, p, lane);
+    emit_split_pads(po, p + 1, lane);
+#pragma unroll
+    for (int u = 0; u < NX; ++u)
+      if (256 * u < ds) emit_split_pair(po, p, lane, 256 * u, xv[0][u], xv[1][u], s_pair + 512 * (threadIdx.x >> 6));
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (r == 1 && !both) break;
+      if (po.xr_out) {
+#pragma unroll
+        for (int u = 0; u < NX; ++u)
+          if (lane * 4 + 256 * u < ds) *reinterpret_cast<float4 *>(po.xr_out + (p + r) * (int64_t)ds + lane * 4 + 256 * u) = xv[r][u];
+      }
+      const float sum = wave_sum(s[r]);
+      if (lane == 0) {
+        if (tau) tau[p + r] = sum;
+        if (best) best[p + r] = pack_key(sum, a[r]);
+        if (po.label_out) po.label_out[p + r] = a[r];
+      }
+    }
+  };
   if (BATCH) {
     const int wave = threadIdx.x >> 6, rows = ds >> 4;
     const int span = po.span, sh = span == 64 ? 6 : 4;
     for (int64_t b0 = (int64_t)blockIdx.x * span; b0 < n; b0 += (int64_t)gridDim.x * span) {
-      for (int it = 0; it < span / 4; ++it) {
-        const int slot = it * 4 + wave;
-        if (b0 + slot < n) point(b0 + slot, slot);
-      }
+      for (int slot = 2 * wave; slot < span; slot += 8)
+        if (b0 + slot < n) two_points(b0 + slot, slot);
       __syncthreads();
       const int col = threadIdx.x & (span - 1);
       if (b0 + col < n)
@@ -248,7 +374,7 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
     }
   } else {
     const int64_t nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += nwaves) point(i, 0);
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += nwaves) point(i);
   }
 }
 
@@ -320,8 +446,8 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
                            int32_t *label_out, uint32_t *xh, unsigned int *unset, stamp_t *stamp) {
   if (n <= 0) return hipSuccess;
   const int nv = (ds + 255) / 256;
-  const bool batch = xnp != nullptr && nv <= 8 && ds / 16 <= kPrefixStageRows;
-  // five workgroups of the batched form fit a CU (32 KB of LDS each): below one such round of 64 points, 16 at a time
+  const bool batch = xnp != nullptr && xs != nullptr && nv <= 8 && ds / 16 <= kPrefixStageRows;
+  // (below five workgroups a CU, 16 points at a time)
   const int span = n >= (int64_t)num_cus() * 5 * 64 ? 64 : 16;
   int64_t blocks = batch ? (n + span - 1) / span : (n + 3) / 4;
   const int64_t cap = (int64_t)num_cus() * 32;
@@ -558,6 +684,9 @@ __global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, The
   PrefixOut po{nullptr, a.k, a.ds, a.Ys, a.Yh, nullptr, 0.f, nullptr, nullptr, nullptr};
   if (a.Ys) {
     po.scale = split_scale(*a.y_absmax);
+    po.hi_dims = a.hi_dims;
+    po.xd = a.Yd;
+    po.xd_from = a.dprime;
     if (tid < 64) emit_split_pads(po, c, tid);
   }
   const int pdx_end = a.Ypdx ? a.dprime + a.nb * kBlockDims : 0;   // columns up to here have a place in Ypdx
@@ -604,7 +733,7 @@ __global__ void __launch_bounds__(256) prep_centroids_kernel(CentroidPrep a, The
 hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio, int nratio) {
   if (a.k <= 0) return hipSuccess;
   if (a.ds % 16 != 0 || a.ds > 16384 || a.ldy % 4 != 0 || (reinterpret_cast<uintptr_t>(a.Y) & 15u) || a.dn % 16 != 0 ||
-      a.dn > a.ds || a.dprime % 16 != 0 || (a.Ys && !a.y_absmax) || (a.Yh && !a.Ys) || nratio > kMaxBlocks + 1 ||
+      a.dn > a.ds || a.dprime % 16 != 0 || (a.Ys && !a.y_absmax) || (a.Yh && !a.Ys) || (a.Yd && !a.Ys) || (a.Yh && a.hi_dims <= 0) || nratio > kMaxBlocks + 1 ||
       (a.ratio_out != nullptr) != (nratio > 0))
     return hipErrorInvalidValue;
   ThetaRatios r;
