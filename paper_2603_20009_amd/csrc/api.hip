@@ -970,6 +970,25 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
     HIPCHK(launch_screen(sl, c.st));
     PruneArgs pa{c.pairs, fill, (unsigned int)c.sub_cap, c.Xr, c.ldx, c.n, c.Ypdx, c.k, 0, K, nbK, c.Y, c.ratio_dev,
                  c.best, c.scal, 0};
+    // Rows that outgrow the Infinity Cache (256 MB) are read once for all of their candidates instead of once for each.  The
+    // whole stage, list -> rows: 1M x 1536, k = 1024 5.71 -> 4.94 ms, k = 4096 18.65 -> 14.8, 1M x 768, k = 4096 9.10 -> 7.92, 100 000 x
+    // 1024, k = 3000 914 -> 855 us, 200 000 x 400, k = 4000 1067 -> 943; but 120 001 x 208, k = 777 159 -> 164, 20 000 x 1536, k = 600
+    // 112 -> 134, and 1M x 96, k = 800 622 -> 640 (two blocks of 64 dimensions a row).
+    // (the buffers of the filter's lists are free in this form: two slots a point and column tile, four or eight in all)
+    const int32_t slots = std::min<int32_t>(8, (int32_t)progressive_tiles(1, c.k) * (kListCols / 128)) & ~3;
+    if (slots > 0 && K >= 128 && rows * K >= (int64_t)1 << 26) {
+      RowPairsArgs rp{};
+      rp.pairs = c.pairs; rp.count = fill; rp.sub_capacity = (unsigned int)c.sub_cap; rp.overflow = c.flag;
+      rp.left_count = c.counters + ((size_t)c.nchunks * kSubLists + (size_t)ch * 8) * kSubListStride;
+      rp.row_count = reinterpret_cast<unsigned int *>(c.scr_pos); rp.cand = c.scr_cols;
+      rp.slots = slots;
+      rp.rows = (int32_t)rows; rp.row_base = r0;
+      rp.Xr = c.Xr; rp.ldx = c.ldx; rp.Ypdx = c.Ypdx; rp.k = c.k; rp.K = K; rp.nb = nbK;
+      rp.best = c.best; rp.scal = c.scal;
+      HIPCHK(launch_row_pairs(rp, c.st));
+      pa.pairs = c.pairs + c.sub_cap / 2;
+      pa.count = rp.left_count;
+    }
     HIPCHK(launch_prune(pa, c.st));
   }
   return SKM_OK;
@@ -1008,7 +1027,7 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
       if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");
       return SKM_OK;
     }
-    c.exact_filter_off = true;   // the candidate list overflowed (never with the default capacities): the full GEMM instead
+    c.exact_filter_off = true;   // the candidate list overflowed (with seven or more candidates a point, in eight lists): the full GEMM instead
   }
   if (int rc = c.measure_y()) return rc;
   CentroidPrep cp{c.Y, c.ds, c.k, c.ds};

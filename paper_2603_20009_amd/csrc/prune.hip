@@ -13,6 +13,8 @@
 // workload from 1.38 to 1.24 ms.
 #include "skm_internal.h"
 
+#include <algorithm>
+
 namespace skm {
 
 // Sum over 8 consecutive lanes; every lane receives the same bits (symmetric butterfly: swap within
@@ -170,6 +172,163 @@ hipError_t launch_prune(const PruneArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(prune_kernel<true>, dim3(grid), dim3(PRUNE_THREADS), 0, st, a);
   else
     hipLaunchKernelGGL(prune_kernel<false>, dim3(grid), dim3(PRUNE_THREADS), 0, st, a);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- candidates of the one-product search, row by row
+// The pairs of a search in which nothing is dropped on the way (launch_screen's exact form): a point has a few candidates, found
+// by different workgroups at different times.  With a list entry a group of lanes, every entry fetches its point's row again:
+// 2.4 entries a point of 1M x 1536 were 19 GB from beyond the L2s, 2.69 ms at 7.2 TB/s.  Here the entries are dealt out to
+// their points first (up to `slots` each; more stay in a list, behind the middle of their part, for the kernel above), and a
+// group of 8 lanes then takes a point with all of them: the rows stream through once, in a few launches that each take the
+// blocks of 64 dimensions whose centroids' part fits an L2 (7.7 GB from beyond the L2s, 1.93 ms; 4.0 entries a point of k = 4096
+// 6.76 -> 2.80 ms; in one launch 2.17 and 4.00).  The sums are those of the kernel above.
+constexpr int DEAL_THREADS = 256;
+
+__global__ void __launch_bounds__(DEAL_THREADS) deal_pairs_kernel(RowPairsArgs a) {
+  const unsigned int part = blockIdx.x & 7u, half = a.sub_capacity / 2, room = a.sub_capacity - half - (unsigned int)a.rows;
+  Pair *list = a.pairs + (size_t)part * a.sub_capacity;
+  const unsigned int total = a.count[part * kSubListStride];
+  if (total > room) {   // no room for what may be left over: reported like a list that is too short
+    if (threadIdx.x == 0) atomicOr(a.overflow, 1u);
+    return;
+  }
+  for (unsigned int p0 = (blockIdx.x >> 3) * DEAL_THREADS; p0 < total; p0 += (gridDim.x >> 3) * DEAL_THREADS) {
+    const unsigned int p = p0 + threadIdx.x;
+    bool left = false;
+    Pair pr = {0, 0, 0.f, 0.f};
+    if (p < total) {
+      pr = list[p];
+      const unsigned int r = (unsigned int)((int64_t)pr.i - a.row_base);
+      if (r < (unsigned int)a.rows && (unsigned int)pr.j < (unsigned int)a.k) {   // (see the kernel above: never written)
+        const unsigned int rank = atomicAdd(a.row_count + r, 1u);
+        if (rank < (unsigned int)a.slots) a.cand[(size_t)r * a.slots + rank] = pr.j;
+        else left = true;
+      }
+    }
+    const unsigned long long mask = __ballot(left);
+    if (mask) {
+      const int lane = threadIdx.x & 63, first = __builtin_ctzll(mask);
+      unsigned int base = 0;
+      if (lane == first) base = atomicAdd(a.left_count + part * kSubListStride, (unsigned int)__popcll(mask));
+      base = __shfl(base, first, 64);
+      if (left) list[half + base + __popcll(mask & ((1ull << lane) - 1))] = pr;
+    }
+  }
+}
+
+// Blocks [m0, m1) of all points' candidates: the sums so far come from memory and go back there, four to a vector.
+__global__ void __launch_bounds__(PRUNE_THREADS) row_pairs_kernel(RowPairsArgs a, int m0, int m1) {
+  __shared__ unsigned int s_pairs;
+  if (threadIdx.x == 0) s_pairs = 0u;
+  __syncthreads();
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int U = 4;   // candidates at a time
+  const int q = threadIdx.x & (PAIR_LANES - 1);
+  unsigned int my_pairs = 0u;
+  const int ngroups = gridDim.x * (PRUNE_THREADS / PAIR_LANES);
+  // a row's number of candidates and its first four are asked for a row ahead
+  int r = blockIdx.x * (PRUNE_THREADS / PAIR_LANES) + threadIdx.x / PAIR_LANES;
+  unsigned int count = 0u;
+  int4 four = make_int4(0, 0, 0, 0);
+  if (r < a.rows) {
+    count = a.row_count[r];
+    four = *reinterpret_cast<const int4 *>(a.cand + (size_t)r * a.slots);
+  }
+  for (int next; r < a.rows; r = next) {
+    next = r + ngroups;
+    const int c = (int)min(count, (unsigned int)a.slots);
+    int4 cand = four;
+    if (next < a.rows) {
+      count = a.row_count[next];
+      four = *reinterpret_cast<const int4 *>(a.cand + (size_t)next * a.slots);
+    }
+    const float *x = a.Xr + (a.row_base + r) * a.ldx + 4 * q;
+    unsigned long long best = ~0ull;
+    for (int c0 = 0; c0 < c; c0 += U) {
+      const int nu = min(U, c - c0);
+      float4 *sums = reinterpret_cast<float4 *>(a.pairs + (size_t)(c0 / U + 1) * a.sub_capacity - a.rows) + r;
+      if (c0 > 0) cand = *reinterpret_cast<const int4 *>(a.cand + (size_t)r * a.slots + c0);
+      const int j[U] = {cand.x, cand.y, cand.z, cand.w};   // (those past the row's last are not looked at)
+      float acc[U] = {0.f, 0.f, 0.f, 0.f};
+      if (m0 > 0) {
+        const float4 v = *sums;
+        acc[0] = v.x; acc[1] = v.y; acc[2] = v.z; acc[3] = v.w;
+      }
+      f32x4_t x0, x1, n0, n1;
+      // (the rows pass through once: they are not to displace the centroids' blocks)
+      auto fetch = [&](int m, f32x4_t &v0, f32x4_t &v1) {
+        const int col = kBlockDims * m + 4 * q;
+        v0 = v1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (col < a.K) v0 = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(x + kBlockDims * m));
+        if (col + 32 < a.K) v1 = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(x + kBlockDims * m + 32));
+      };
+      fetch(m0, n0, n1);
+      for (int m = m0; m < m1; ++m) {
+        float4 y0[U], y1[U];
+        const float *y = a.Ypdx + (int64_t)m * a.k * kBlockDims + 4 * q;
+        x0 = n0;
+        x1 = n1;
+        if (m + 1 < m1) fetch(m + 1, n0, n1);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (u < nu) {   // (zeros past the K dimensions)
+            y0[u] = *reinterpret_cast<const float4 *>(y + (int64_t)j[u] * kBlockDims);
+            y1[u] = *reinterpret_cast<const float4 *>(y + (int64_t)j[u] * kBlockDims + 32);
+          }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (u < nu) {
+            float dx = x0.x - y0[u].x, dy = x0.y - y0[u].y, dz = x0.z - y0[u].z, dw = x0.w - y0[u].w;
+            float s = dx * dx;
+            s = fmaf(dy, dy, s);
+            s = fmaf(dz, dz, s);
+            s = fmaf(dw, dw, s);
+            dx = x1.x - y1[u].x; dy = x1.y - y1[u].y; dz = x1.z - y1[u].z; dw = x1.w - y1[u].w;
+            s = fmaf(dx, dx, s);
+            s = fmaf(dy, dy, s);
+            s = fmaf(dz, dz, s);
+            s = fmaf(dw, dw, s);
+            acc[u] += row8_sum(s);
+          }
+      }
+      if (m1 < a.nb) {
+        if (q == 0) *sums = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (u < nu && acc[u] < kFarAway) {
+            const unsigned long long key = pack_key(acc[u], j[u]);
+            best = key < best ? key : best;
+          }
+        my_pairs += nu;
+      }
+    }
+    if (q == 0 && best != ~0ull) atomicMin(a.best + a.row_base + r, best);   // (pairs left in the list come on top)
+  }
+  if (q == 0 && my_pairs) atomicAdd(&s_pairs, my_pairs);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_pairs) {
+    unsigned long long *sc = a.scal + (size_t)(blockIdx.x & (kStatReplicas - 1)) * SC_COUNT;
+    atomicAdd(sc + SC_COMPLETED, (unsigned long long)s_pairs);
+    atomicAdd(sc + SC_GATHER_PB, (unsigned long long)s_pairs * a.nb);
+    atomicAdd(sc + SC_GATHER_PAIRS, (unsigned long long)s_pairs);
+  }
+}
+
+hipError_t launch_row_pairs(const RowPairsArgs &a, hipStream_t st) {
+  if (a.rows <= 0) return hipSuccess;
+  if ((a.slots != 4 && a.slots != 8) || a.nb < 1 || a.K % 16 != 0 || a.sub_capacity < 8u * (unsigned int)a.rows) return hipErrorInvalidValue;
+  hipError_t rc = launch_fill_u32(a.row_count, a.rows, 0u, st);
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(deal_pairs_kernel, dim3((unsigned)num_cus() * 4u / 8u * 8u), dim3(DEAL_THREADS), 0, st, a);
+  const int64_t blocks = ((int64_t)a.rows * PAIR_LANES + PRUNE_THREADS - 1) / PRUNE_THREADS;
+  const dim3 grid((unsigned)std::min<int64_t>(blocks, (int64_t)num_cus() * 8));
+  // as many blocks a launch as keep the centroids' part of them within one L2 (4 MB): 1M x 1536, k = 4096 with a launch of 1 MB
+  // 16.1 ms for the whole stage, 2 MB 15.0, 4 MB 14.8, 8 MB 15.0, all blocks 16.0
+  const int step = (int)std::max<int64_t>(1, std::min<int64_t>(a.nb, ((int64_t)4 << 20) / ((int64_t)a.k * kBlockDims * 4)));
+  for (int m0 = 0; m0 < a.nb; m0 += step)
+    hipLaunchKernelGGL(row_pairs_kernel, grid, dim3(PRUNE_THREADS), 0, st, a, m0, std::min(m0 + step, a.nb));
   return hipGetLastError();
 }
 

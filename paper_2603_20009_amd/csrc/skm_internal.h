@@ -351,6 +351,29 @@ struct PruneArgs {
 };
 hipError_t launch_prune(const PruneArgs &a, hipStream_t st);
 
+// The candidates of a search over the first K dimensions in which no pair is dropped, a point with all of its own at a time;
+// what does not fit a point's slots is left to launch_prune on pairs + sub_capacity / 2 and left_count.  A part of the list that is
+// more than half full sets bit 0 of *overflow.
+constexpr float kFarAway = 3.0e38f;   // the threshold of such pairs
+struct RowPairsArgs {
+  Pair *pairs;                 // kSubLists parts of sub_capacity slots each
+  const unsigned int *count;   // [kSubLists * kSubListStride] fill counters
+  unsigned int sub_capacity;
+  unsigned int *overflow;
+  unsigned int *left_count;    // [kSubLists * kSubListStride], zero
+  unsigned int *row_count;     // [rows], cleared here
+  int32_t *cand;               // [rows][slots]
+  int32_t slots, rows;
+  int64_t row_base;            // point of row 0
+  const float *Xr;             // all points
+  int64_t ldx;
+  const float *Ypdx;           // [nb][k][64]: the first K dimensions, zero filled
+  int32_t k, K, nb;
+  unsigned long long *best;    // by point
+  unsigned long long *scal;
+};
+hipError_t launch_row_pairs(const RowPairsArgs &a, hipStream_t st);
+
 // ---------------------------------------------------------------- streaming kernels
 // tau_i = ||x_i - y_{a_i}||^2 over all dims, best_i = pack(tau_i, a_i)
 // (Algorithm 1, "Initial pruning threshold").  Either output may be NULL.

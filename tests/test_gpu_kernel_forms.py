@@ -455,3 +455,25 @@ def test_operands_in_pairs_of_rows(skm, orc, dg, n, d, k, dp):  # noqa: F811
     differ = a0 != a1   # (a pair finishes in a tile of split products or, handed over, in fp32: near-ties may fall either way)
     assert int(differ.sum()) <= 1e-3 * n
     assert ((d0 - d1).abs()[~differ] <= 2e-5 * max(1.0, float(d0.max()))).all()
+
+
+# Candidates of iteration 1 dealt out to their points: from 2^26 elements on, rows of 128 dimensions or more, four slots a point
+# up to 768 clusters and eight above, what does not fit left to the list (points of few components, and of one, have dozens of
+# candidates), one launch of all blocks and several.
+@pytest.mark.parametrize("n,d,k,components", [(66_001, 1024, 600, 1500), (66_000, 1024, 600, 20), (90_001, 752, 300, 4), (141_001, 480, 2100, 3000),
+                                              (141_000, 480, 2100, 60), (524_289, 128, 513, 900), (33_003, 2050, 9000, 9000)])
+def test_candidates_dealt_out_to_their_points(skm, dg, n, d, k, components):  # noqa: F811
+    say("dealt out", n, d, k, components)
+    X = dg.mixture(n, d, components, 3, "embed").cuda()
+    idx = np.random.default_rng(n).choice(n, k, replace=False)
+    R = torch.eye(d, device="cuda")
+    runs = [skm.fit(X, k, 1, 1, skm.FitOptions(R=R, init_idx=idx, final_assign=False, screen=s)) for s in (1, -1)]
+    assert runs[0].trace[0]["gather_pairs"] >= n and runs[1].trace[0]["gather_pairs"] == 0
+    a, b = (r.assign.long() for r in runs)
+    Y = X[torch.as_tensor(idx, device="cuda")].double()
+    # fp32 sums of d squares, and the split product's search: d 2^-24 of the sum, and 2^-20 of the norms' product (norms of 1)
+    for r in range(0, n, 20_000):
+        x = X[r:r + 20_000].double()
+        da, db = (((x - Y[l[r:r + 20_000]]) ** 2).sum(1) for l in (a, b))
+        assert (da <= db * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -20).all() and (db <= da * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -20).all()
+        assert ((runs[0].dist[r:r + 20_000].double() - da).abs() <= 2 * d * 2.0 ** -24 * da + 1e-12).all()
