@@ -530,6 +530,7 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
   __shared__ int s_wave[4];
   __shared__ int s_pos[256];   // positions of the chunk's words
   __shared__ unsigned int s_bits[256];
+  __shared__ unsigned short s_ids[256 * 32];   // the chunk's ids, from its first
   __shared__ int s_base;
   const int rt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -562,28 +563,28 @@ __global__ void __launch_bounds__(256) mask_fill_kernel(const uint32_t *mask, in
     }
     if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    int pos = s_base + incl - mine;
+    int pos = incl - mine;
     for (int ww = 0; ww < wave; ++ww) pos += s_wave[ww];
-    s_pos[tid] = pos;
+    const int base = s_base, here = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    s_pos[tid] = base + pos;
     s_bits[tid] = bits;
-    int at = -1;
-    int32_t *out = nullptr;
     while (bits) {
-      const int b = __builtin_ctz(bits);
+      s_ids[pos++] = (unsigned short)(32 * tid + __builtin_ctz(bits));
       bits &= bits - 1u;
-      if (pos / kListCols != at) {
-        at = pos / kListCols;
-        out = col_list + (int64_t)place(at) * kListCols;
-      }
-      out[pos % kListCols] = w * 32 + b;
-      ++pos;
     }
     __syncthreads();
+    // (through LDS, 256 ids a store: each thread storing its own word's ids, the lists of 2.5M x 384 against 32768 centroids took
+    // 1.25 ms a launch)
+    for (int e = tid; e < here; e += 256) {
+      const int p = base + e;
+      col_list[(int64_t)place(p / kListCols) * kListCols + p % kListCols] = 32 * w0 + s_ids[e];
+    }
     if (inc >= 32 * w0 && inc < 32 * (w0 + 256)) {   // the row's incumbent is in this chunk of words
       const unsigned int b = s_bits[(inc >> 5) - w0], bit = 1u << (inc & 31);
       if (b & bit) at_pos = s_pos[(inc >> 5) - w0] + __popc(b & (bit - 1u));
     }
-    if (tid == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    __syncthreads();
+    if (tid == 0) s_base = base + here;
     __syncthreads();
   }
   if (nt > 0) {

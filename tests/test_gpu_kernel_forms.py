@@ -477,3 +477,20 @@ def test_candidates_dealt_out_to_their_points(skm, dg, n, d, k, components):  # 
         da, db = (((x - Y[l[r:r + 20_000]]) ** 2).sum(1) for l in (a, b))
         assert (da <= db * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -20).all() and (db <= da * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -20).all()
         assert ((runs[0].dist[r:r + 20_000].double() - da).abs() <= 2 * d * 2.0 ** -24 * da + 1e-12).all()
+
+
+# The lists of a row tile's columns are put together 8192 columns at a time: at that number, one more, several times as many, and
+# tiles of which every column, few and hardly any are listed.
+@pytest.mark.parametrize("good", [0, 1])     # the incumbents: the nearest centroids, or any
+@pytest.mark.parametrize("n,d,k,dp", [(300, 64, 8192, 16), (257, 64, 8193, 32), (129, 80, 25_000, 48)])
+def test_lists_of_many_columns(skm, dg, n, d, k, dp, good):  # noqa: F811
+    say("lists", n, d, k, dp, good)
+    X, Y = dg.mixture(n, d, 20, 5, "linear").cuda(), dg.mixture(k, d, 20, 5, "linear", sample_seed=9).cuda()
+    g = torch.Generator("cuda").manual_seed(k)
+    prev = skm.assign_exact(X, Y)[0] if good else torch.randint(0, k, (n,), generator=g, device="cuda", dtype=torch.int32)
+    R = torch.eye(d, device="cuda")
+    (a, da, ra), (b, db, rb) = (skm.assign(X, Y, prev, dp, skm.FitOptions(R=R, screen=s)) for s in (1, -1))
+    assert ra["listed_tiles"] > 0 and ra["survivors"] == rb["survivors"] and ra["completed"] == rb["completed"]
+    # (a pair finishes in a tile of split products or, handed over, in fp32: near-ties may fall either way, by d 2^-24 and 2^-20)
+    dist = [((X.double() - Y.double()[l.long()]) ** 2).sum(1) for l in (a, b)]
+    assert ((dist[0] - dist[1]).abs() <= 2 * d * 2.0 ** -24 * dist[1] + 2.0 ** -19 * float((X ** 2).sum(1).max())).all()
