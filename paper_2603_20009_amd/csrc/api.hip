@@ -2393,6 +2393,72 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   return SKM_OK;
 }
 
+// The exact assignment through the one-product search of iteration 1 (a third of the matrix work of the three-product argmin;
+// the candidates' distances are the direct ones), 2^18 rows at a time.  done = false: nothing to show for it - no memory for the
+// search's buffers, a candidate list that ran over, a row that no centroid was offered to (one that is no number) - and the
+// caller takes the other form, for all rows.
+constexpr int64_t kExactRows = (int64_t)1 << 18;
+// From 2048 centroids on, for rows that the argmin with the rows in registers does not take, and from 2^34 multiply-adds on (the
+// search is a dozen launches more).  Three products -> search: 16 384 x 256, k = 4096 178 -> 173 us, 8000 x 384, k = 8000 228 -> 204,
+// 100 000 x 384, k = 2048 565 -> 493, 700 001 x 300, k = 5000 8.7 -> 4.9 ms, 400 000 x 768, k = 8000 14.8 -> 7.1; but 60 000 x 192, k = 1536
+// 200 -> 214 us, 300 000 x 160, k = 1300 685 -> 702, 200 000 x 96, k = 2000 310 -> 435.  Labels unlike those of fp64: 2 of 100 000 -> 0,
+// 3 of 60 000 (k = 4000) -> 1.
+bool exact_filter_pays(int64_t n, int32_t d, int32_t k) {
+  return k >= 2048 && d > 128 && (double)n * d * k >= 17179869184.0;
+}
+int exact_through_filter(const float *X, int64_t n, int32_t d, const float *centroids, int32_t k, hipStream_t st,
+                         int32_t *assign_out, float *dist_out, bool &done) {
+  done = false;
+  const int64_t W = std::min<int64_t>(n, kExactRows);
+  const int32_t ds = round_up(d, 16);
+  const bool pad = d != ds || !aligned16(X);
+  const size_t plan = plan_common_bytes(W, d, k, 0, 0.f, false);
+  if (!plan) return SKM_OK;
+  CallArena ws(plan + (pad ? (size_t)W * ds * 4 : 0) + ((size_t)1 << 20));
+  Ctx c;
+  c.st = st;
+  c.n = W; c.d = d; c.k = k; c.ds = ds;
+  StageTimer tm(false, st);
+  float *Xo = nullptr;
+  if (c.alloc_bounds() != SKM_OK || c.alloc_common(0, 0.f, false) != SKM_OK || !c.colmask || (pad && c.pool.get(&Xo, (size_t)W * ds) != hipSuccess)) {
+    (void)hipGetLastError();
+    return SKM_OK;
+  }
+  HIPCHK(launch_pad_copy(centroids, d, k, d, c.Y, ds, ds, 0, st));
+  const int64_t tile_rows = c.chunk_rows;
+  for (int64_t r0 = 0; r0 < n; r0 += W) {
+    const int64_t rows = std::min<int64_t>(W, n - r0);
+    c.n = rows;
+    c.nchunks = (int32_t)((rows + tile_rows - 1) / tile_rows);
+    c.Xr = X + r0 * d;
+    c.ldx = d;
+    if (pad) {
+      HIPCHK(launch_pad_copy(c.Xr, d, rows, d, Xo, ds, ds, 0, st));
+      c.Xr = Xo;
+      c.ldx = ds;
+    }
+    if (r0 > 0) HIPCHK(launch_fill_u32(c.xr_bound, 1, 0u, st));
+    if (int rc = c.measure_xr()) return rc;
+    c.xnp_valid = c.xh_valid = false;
+    if (int rc = filtered_nearest(c, ds, tm)) return rc;
+    c.pending = true;
+    if (dist_out)   // (not the search's own distances, which add the blocks of a row one after the other: 2 to 3.7e-7 off, these 1.7e-7)
+      HIPCHK(launch_tau_init(c.Xr, c.ldx, rows, ds, c.Y, ds, nullptr, dist_out + r0, c.best, st, nullptr, nullptr, nullptr, nullptr, nullptr,
+                             assign_out + r0, nullptr, c.flag));
+    else
+      HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, rows, assign_out + r0, nullptr, nullptr, k, c.flag}, st));
+    HIPCHK(hipMemcpyAsync(&c.report->flag, c.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, st));
+    if (int rc = c.wait_step()) return rc;
+    if (c.report->flag != 0) {
+      ws.finished();
+      return SKM_OK;
+    }
+  }
+  ws.finished();
+  done = true;
+  return SKM_OK;
+}
+
 // Sampled fit (Section 4.4): Algorithm 1 runs on a uniform sample of the rows, then every point is assigned
 // to the resulting centroids by the two-phase step without a previous assignment.
 int fit_sampled(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uint64_t seed, const skm_params &p,
@@ -2878,6 +2944,11 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
   if (rc) return rc;
   if (!centroids || !assign_out) return fail(SKM_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;
+  if (exact_filter_pays(n, d, k)) {
+    bool done = false;
+    if ((rc = exact_through_filter(X, n, d, centroids, k, st, assign_out, dist_out, done))) return rc;
+    if (done) return SKM_OK;
+  }
   const int32_t ds = round_up(d, 16);
   // Rows whose length is no multiple of 16, or without alignment, go through a padded copy, 256 MB at a time, unless the
   // multiply can read them as they are: it takes whole float4s and masks the end of the last slab (from 32 dimensions

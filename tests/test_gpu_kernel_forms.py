@@ -494,3 +494,42 @@ def test_lists_of_many_columns(skm, dg, n, d, k, dp, good):  # noqa: F811
     # (a pair finishes in a tile of split products or, handed over, in fp32: near-ties may fall either way, by d 2^-24 and 2^-20)
     dist = [((X.double() - Y.double()[l.long()]) ** 2).sum(1) for l in (a, b)]
     assert ((dist[0] - dist[1]).abs() <= 2 * d * 2.0 ** -24 * dist[1] + 2.0 ** -19 * float((X ** 2).sum(1).max())).all()
+
+
+# The exact assignment through the one-product search: from 2048 centroids, rows of more than 128 dimensions and 2^34 multiply-adds
+# on, 2^18 rows at a time; ragged and unaligned rows through a padded copy.
+@pytest.mark.parametrize("n,d,k,shift", [(16_385, 256, 4100, 0), (262_145, 136, 2048, 0), (20_001, 515, 2100, 0), (9001, 400, 5001, 1),
+                                         (262_144 + 16_000, 144, 2050, 1)])
+def test_exact_assignment_through_the_search(skm, dg, n, d, k, shift):  # noqa: F811
+    say("exact search", n, d, k, shift)
+    X, Y = dg.mixture(n, d, 2 * k, 5, "embed").cuda(), dg.mixture(k, d, 2 * k, 5, "embed", sample_seed=3).cuda()
+    if shift:
+        at = torch.empty(n * d + 1, device="cuda")
+        at[1:] = X.reshape(-1)
+        X = at[1:].view(n, d)
+    a, dist = skm.assign_exact(X, Y)
+    alone = skm.assign_exact(X[:500], Y)[0]                     # (few rows: three products)
+    for r in range(0, n, 16_384):
+        x = X[r:r + 16_384].double()
+        D = (x * x).sum(1, keepdim=True) - 2 * x @ Y.double().T + (Y.double() ** 2).sum(1)
+        own = ((x - Y.double()[a[r:r + 16_384].long()]) ** 2).sum(1)
+        # fp32 sums of d squares: d 2^-24 of the sum (and 2^-45 for the fp64 form of the matrix D, norms of 1)
+        assert (own <= D.min(1).values * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -45).all()
+        assert ((dist[r:r + 16_384].double() - own).abs() <= 2 * d * 2.0 ** -24 * own + 1e-12).all()
+    assert int((alone != a[:500]).sum()) <= 1
+
+
+def test_exact_search_that_has_nothing_to_show(skm, dg):  # noqa: F811
+    """Rows that are no numbers, and centroids that are all the same, take the other form: labels as for few rows."""
+    n, d, k = 40_000, 256, 2100
+    X, Y = dg.mixture(n, d, 500, 5, "embed").cuda(), dg.mixture(k, d, 500, 5, "embed", sample_seed=3).cuda()
+    want, dist = skm.assign_exact(X, Y)
+    X[7777] = float("nan")
+    got, dist_got = skm.assign_exact(X, Y)
+    keep = torch.arange(n, device="cuda") != 7777
+    assert int((got[keep] != want[keep]).sum()) <= 1e-3 * n and int(got[7777]) == int(skm.assign_exact(X[7700:7800], Y)[0][77])
+    same = got == want
+    assert ((dist_got - dist)[same].abs() <= 4 * d * 2.0 ** -24 * dist[same] + 1e-12).all()
+    X[7777] = X[0]
+    Y[:] = Y[0].clone()
+    assert int(skm.assign_exact(X, Y)[0].abs().max()) == 0
