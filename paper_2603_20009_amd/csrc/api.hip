@@ -1085,8 +1085,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   // first test.  The previous step's prune fraction predicts that from below (the centroids only get better): the
   // step after one that cut half of the pairs cuts 85 to 99 % on the mixture workloads, and a wasted filter pass
   // costs a tenth of the poorly pruned step it precedes.
+  // Behind the first test of a listed tile one product and widened tests will do where the gather kernel finishes what is
+  // left (not where every test's count is asked for, nor with a hand-over share beyond an eighth).
+  const bool deep = nb >= 3 && !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
+  // A step after one that cut a third to a half of the pairs cuts 80 to 85 % of them, spread over nearly all columns: there is
+  // nothing for the filter to drop, but the tiles are through with their first test after an eighth of the dimensions and
+  // multiply the rest in one product, so all columns are listed as they are.  Tiles and gather of the third step of a fit, dense ->
+  // listed (behind the filter): 1M x 1536, k = 1024 7.80 -> 6.51 (6.68) ms, k = 4096 36.1 -> 28.2 (28.8), 600 000 x 1280, k = 2000 10.0 ->
+  // 9.4 (9.8), 200 000 x 1536, k = 300 779 -> 746 (788) us.  After a step that cut 32 % one that cut 74 %, a quarter of the tiles done
+  // twice: 100 000 x 896, k = 600 469 -> 569 us.
+  const bool list_all = deep && c.screen_mode == 0 && c.last_prune_frac >= 0.33 && c.last_prune_frac < 0.50;
   const bool screen = c.colmask && nb > 0 &&
-                      (c.screen_mode > 0 || (c.screen_mode == 0 && c.last_prune_frac >= 0.50));
+                      (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
   // theta ratio at checkpoint m: t_m = min(d, d' + 64 m) dimensions seen
   float ratio[kMaxBlocks + 1];
   for (int m = 0; m <= nb; ++m) ratio[m] = (float)theta_ratio(c.d, std::min(c.d, dprime + kBlockDims * m), eps0);
@@ -1203,14 +1213,12 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       sl.tau = c.tau; sl.row_base = r0;
       sl.xn = c.xnp + (int64_t)(dprime / 16 - 1) * c.n;
       sl.yn = c.ynp;
-      // Behind the first test of a listed tile one product and widened tests will do where the gather kernel finishes
-      // what is left (not where every test's count is asked for, nor with a hand-over share beyond an eighth).
-      const bool deep = nb >= 3 && !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
       if (deep) { sl.ynp = c.ynp; sl.nb = nb; sl.widen = c.scr_widen; }
       sl.arow = c.scr_arow; sl.ycol = c.scr_ycol;
       sl.colmask = c.colmask; sl.cnt = c.scr_cnt; sl.first = c.scr_first; sl.ntiles = c.scr_ntiles;
       sl.col_list = c.scr_cols; sl.tile_rt = c.scr_tile_rt; sl.prev = c.prev; sl.list_pos = c.scr_pos;
       sl.scal = c.scal;
+      sl.all = list_all ? 1 : 0;
       sl.stamp = border;
       HIPCHK(launch_screen(sl, c.st));
       g.tile_rt = c.scr_tile_rt; g.col_list = c.scr_cols; g.ntiles = c.scr_ntiles; g.prev = c.scr_pos;

@@ -488,6 +488,14 @@ __global__ void __launch_bounds__(256) mask_count_kernel(const uint32_t *mask, i
   if (lane == 0) cnt[rt] = c;
 }
 
+// every column of every row tile (the columns past the last one stay out)
+__global__ void __launch_bounds__(256) mask_all_kernel(uint32_t *mask, int64_t words, int32_t maskw, int32_t N) {
+  for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < words; w += (int64_t)gridDim.x * 256) {
+    const int left = N - 32 * (int)(w % maskw);
+    mask[w] = left >= 32 ? 0xffffffffu : left > 0 ? (1u << left) - 1u : 0u;
+  }
+}
+
 // first[rt] = first tile of row tile rt (tiles of kListCols listed columns, row tiles in order), *ntiles = their number
 __global__ void __launch_bounds__(1024) mask_scan_kernel(const int32_t *cnt, int32_t nrt, int32_t *first, int32_t *ntiles,
                                                          unsigned long long *scal) {
@@ -736,7 +744,8 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
   float *ynmax = reinterpret_cast<float *>(a.ntiles + 1);   // (the word after the tile count)
   hipLaunchKernelGGL(max_value_kernel, dim3(a.widen ? (unsigned)a.nb + 2 : 1), dim3(1024), 0, st, a.yn, a.ynp, a.N, ynmax,
                      a.widen, a.ds, a.a_absmax, a.b_absmax, a.stamp);
-  hipLaunchKernelGGL(screen_terms_kernel, dim3((unsigned)((std::max<int64_t>(a.M, a.N) + 255) / 256)), dim3(256), 0, st,
+  if (!a.all)
+    hipLaunchKernelGGL(screen_terms_kernel, dim3((unsigned)((std::max<int64_t>(a.M, a.N) + 255) / 256)), dim3(256), 0, st,
                      a.tau, a.xn, a.row_base, a.M, a.yn, a.N, (const float *)ynmax, a.ratio0, a.dprime, a.a_absmax,
                      a.b_absmax, a.arow, a.ycol, a.exact ? 1 : 0);
   g.arow = a.arow; g.ycol = a.ycol; g.colmask = a.colmask; g.maskw = 4 * nct;
@@ -748,7 +757,13 @@ hipError_t launch_screen(const ScreenLaunch &a, hipStream_t st) {
     hipLaunchKernelGGL(screen_kernel<SCREEN_EXACT>, dim3((unsigned)grid), dim3(NT), smem, st, g);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(screen_kernel<SCREEN_FIRST_TEST>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+  if (a.all) {
+    const int64_t words = (int64_t)nrt * 4 * nct;
+    hipLaunchKernelGGL(mask_all_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, (int64_t)setup.wgs * 8)), dim3(256), 0, st, a.colmask,
+                       words, 4 * nct, a.N);
+  } else {
+    hipLaunchKernelGGL(screen_kernel<SCREEN_FIRST_TEST>, dim3((unsigned)grid), dim3(NT), smem, st, g);
+  }
   hipError_t rc = hipGetLastError();
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)((nrt + 3) / 4)), dim3(256), 0, st, a.colmask, nrt, 4 * nct, a.cnt);

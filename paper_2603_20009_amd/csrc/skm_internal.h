@@ -277,6 +277,7 @@ hipError_t launch_progressive(const ProgArgs &g, hipStream_t st);
 // Outputs: cnt[row tiles], first[row tiles] (tiles of 256 listed columns before every row tile), *ntiles,
 // col_list[256 * ntiles], tile_rt[ntiles] (see ProgArgs); capacity needed: one tile per (row tile, column tile) of the full problem.
 struct ScreenLaunch {
+  int32_t all = 0;               // no filter: every column of every row tile is listed
   const uint32_t *A; int64_t lda; int32_t M;
   const uint32_t *B; int64_t ldb; int32_t N;
   const unsigned int *a_absmax, *b_absmax;
