@@ -159,7 +159,9 @@ typedef struct skm_params {
                             dimensions lists for every point the centroids that can be its nearest (those within the
                             rounding bound of the row's smallest approximate distance), and only those get their exact
                             distance.  0 = in pruned steps that follow a step which cut at least half of the pairs at the
-                            first test, and in iteration 1 from 2048 centroids on; 1 = in every step; -1 = never.
+                            first test (one that cut a third to a half: every column listed without the pass), and in
+                            iteration 1 from 512 centroids on (2048 for fewer than 16 384 points); 1 = in every step; -1 =
+                            never.
                             Execution strategy only: a pair the filter drops is dropped by the exact arithmetic too
                             (the distances of those it leaves are rounded as dense_frac says) */
   int32_t tau_group;     /* 0    : centroids after which a point's threshold tau is refreshed inside a step.  0 (= k):
@@ -288,12 +290,15 @@ int skm_assign_ex(const float *X, int64_t n, int32_t d, const float *centroids, 
 
 /* Exact assignment over all d dimensions (Algorithm 1, iteration 1): the GEMM
  * with the ||y||^2 - 2 x.y epilogue and a fused row argmin, then the direct
- * distance to the winner.  No rotation involved. */
+ * distance to the winner.  No rotation involved.  From 2048 centroids, more than
+ * 128 dimensions and n d k >= 2^34 on the search of a fit's iteration 1 takes the
+ * place of the GEMM: the direct distances of a few candidates decide, which can
+ * fall the other way where two centroids are as near as fp32 can tell. */
 int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroids, int32_t k,
                      void *stream, int32_t *assign_out, float *dist_out);
 
 /* skm_assign_exact for callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): the same kernels, the same results, but the call's working memory (packed
+ * loops, harnesses that forbid hipMalloc): the kernels of its GEMM form and the results of that, but the call's working memory (packed
  * minima, centroid norms, operand bounds, the split-fp16 copy of the centroids) is a fixed 16 MiB array in device
  * memory that every GPU the library runs on holds until the process ends.  No hipMalloc, hipFree or allocating
  * library routine is called.  Limits (SKM_EINVAL beyond them): 1 <= n <= 1 048 576, 1 <= k <= 16 384, d a
