@@ -554,3 +554,21 @@ def test_every_column_listed(skm, dg, n, d, k, components):  # noqa: F811
     for a, b in zip(fit.trace, dense.trace):   # (a near-tie that falls the other way moves a point)
         assert abs(a["survivors"] - b["survivors"]) <= 1e-4 * max(b["survivors"], n) and abs(a["completed"] - b["completed"]) <= 2 + 1e-3 * b["completed"]
     assert int((fit.assign != dense.assign).sum()) <= 2e-4 * n
+
+
+# A step of poor incumbents through the listed tiles (most pairs survive, a tile is done again in three products and finished
+# where it stands): a row's least distance is found in LDS, for the last, narrower list tile and the last rows too.
+@pytest.mark.parametrize("n,d,k", [(40_001, 96, 300), (30_007, 160, 257), (35_000, 64, 386), (33_000, 112, 4099)])
+def test_listed_tiles_that_finish_many_pairs(skm, n, d, k):  # noqa: F811
+    say("listed tiles finished", n, d, k)
+    g = torch.Generator().manual_seed(n)
+    X = torch.randn(n, d, generator=g).cuda()
+    Y = X[:k] + 0.1 * torch.randn(k, d, generator=g).cuda()
+    prev = torch.randint(0, k, (n,), generator=g).int().cuda()
+    prev[: n // 2] = 0     # the many rows of one cluster share their row tiles with one incumbent
+    R = skm.make_rotation(d, 4)
+    (a, da, ra), (c, dc, rc) = (skm.assign(X, Y, prev, opts=skm.FitOptions(R=R, screen=s)) for s in (1, -1))
+    assert ra["listed_tiles"] > 0 and rc["listed_tiles"] == 0 and rc["completed"] > n * k // 8
+    assert ra["survivors"] == rc["survivors"] and abs(ra["completed"] - rc["completed"]) <= 2 + 1e-5 * rc["completed"]
+    assert int((a != c).sum()) <= 2e-4 * n     # (near-ties of two roundings)
+    assert bool(((da - dc).abs() <= 2.0 ** -18 * (X.norm(dim=1) + Y.norm(dim=1).max()) ** 2).all())
