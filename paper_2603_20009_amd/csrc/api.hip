@@ -545,7 +545,8 @@ struct Ctx {
   bool regroup_ok = false;       // the caller has enough steps left for it to pay
   int32_t max_cluster = -1;      // size of the largest cluster at the last update (-1: none yet)
   bool group_now = false;        // a single step that groups the points by their incumbents itself (assign_impl)
-  int32_t *grp_cnt = nullptr;    // [k] sizes of those groups
+  int32_t *grp_cnt = nullptr;    // [k + 1] sizes of those groups, and how many of a sample of the thresholds are in a tail
+  int32_t *class_ws = nullptr;   // [threshold_class_words(n)] scratch of their order by threshold
   bool order_fresh = false;      // up.order groups the points by the labels now in `prev`
   bool permuted = false;
   unsigned long long *point_keys = nullptr;   // keys that name points (ETR ground truth): renumbered with the points
@@ -858,7 +859,7 @@ size_t assign_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &
   const size_t ds0 = (size_t)((d + 15) / 16 * 16);
   const size_t plan = plan_common_bytes(n, d, k, p.pair_budget, p.dense_frac, false);
   if (!plan) return 0;
-  const size_t grouping = assign_groups(n, (int32_t)ds0, k, p.screen) ? (size_t)n * ds0 * 4 + (size_t)n * 9 + (size_t)k * 20 + 4096 : 0;
+  const size_t grouping = assign_groups(n, (int32_t)ds0, k, p.screen) ? (size_t)n * ds0 * 4 + (size_t)n * 9 + (size_t)k * 20 + (size_t)threshold_class_words(n) * 4 + 4096 : 0;
   return plan + grouping + (size_t)n * ds0 * 4 + 10 * (size_t)d * ds0 * 4 + (size_t)d * 16384 + ((size_t)32 << 20);
 }
 int64_t sample_size(int64_t n, int32_t k, float frac) {
@@ -1130,16 +1131,20 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
   // far less usefully than those of iteration 2)
   bool regroup = c.regroup_ok && !c.permuted && c.xnp_valid && c.order_fresh && c.Xr2 && have_prev && c.pruned_steps >= 1;
+  bool by_threshold = false;   // the new order follows the thresholds before the labels
   if (c.group_now && !c.permuted && c.Xr2) {
     // A step on its own (no update before it left an order): the points are grouped by the incumbents they come with
     // (or were just given above), so that a row tile holds the points of one or two clusters and the first filter has
-    // columns to drop.  One read-back of the group sizes decides whether the order is reproducible (see below).
+    // columns to drop.  One read-back of the group sizes decides whether the order is reproducible (see below); with them comes
+    // whether the thresholds of a sample have a tail.
     HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.st));
-    std::vector<int32_t> sizes((size_t)c.k);
-    HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * (size_t)c.k, hipMemcpyDeviceToHost, c.st));
+    HIPCHK(launch_threshold_sample(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, (int32_t *)c.dist, c.class_ws, c.grp_cnt + c.k, c.st));
+    std::vector<int32_t> sizes((size_t)c.k + 1);
+    HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * ((size_t)c.k + 1), hipMemcpyDeviceToHost, c.st));
     HIPCHK(hipStreamSynchronize(c.st));
-    c.max_cluster = *std::max_element(sizes.begin(), sizes.end());
+    c.max_cluster = *std::max_element(sizes.begin(), sizes.end() - 1);
     regroup = true;
+    by_threshold = thresholds_have_tail(c.n, sizes.back());
     c.group_now = false;
   }
   if (regroup) {
@@ -1161,6 +1166,16 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       HIPCHK(launch_suborder(c.Xr, c.ldx, c.n, c.k, c.up.off, c.up.order, c.subkey, c.pos_to_id, c.st));
     else
       HIPCHK(hipMemcpyAsync(c.pos_to_id, c.up.order, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
+    if (by_threshold) {
+      // A step on its own takes its thresholds once more, in front of the order that they decide (1.2 of 41 ms at 2.5M x 384):
+      // its incumbents are as old as the caller's, or come from the front dimensions alone.  The steps of a fit do not: with the
+      // points of their steps in this order 1M x 1536 against 4096 centroids lists 10.4 column tiles a row tile instead of 10.5,
+      // 1M x 768 against 1024 2.5 instead of 2.7, tiles and gather within 1 %.
+      HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, nullptr, c.st));
+      HIPCHK(launch_threshold_classes(c.tau, c.n, c.pos_to_id, (int32_t *)c.dist, c.assign, c.class_ws, c.grp_cnt, c.up.off, c.up.cursor,
+                                      c.up.segoff, c.up.order, c.st));
+      std::swap(c.up.order, c.pos_to_id);
+    }
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, c.best, c.st, c.xnp, c.Xs,
                            c.xr_bound, c.pos_to_id, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
     std::swap(c.prev, c.assign);   // the incumbents in the new order; the other buffer receives this step's labels
@@ -2364,7 +2379,8 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     HIPCHK(c.pool.get(&c.up.cursor, (size_t)k));
     HIPCHK(c.pool.get(&c.up.segoff, (size_t)k + 1));
     HIPCHK(c.pool.get(&c.up.order, (size_t)n));
-    HIPCHK(c.pool.get(&c.grp_cnt, (size_t)k));
+    HIPCHK(c.pool.get(&c.grp_cnt, (size_t)k + 1));
+    HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
     c.group_now = true;
     c.last_prune_frac = 1.0;   // the filter runs: with points grouped and thousands of centroids it has columns to drop
   }

@@ -498,6 +498,16 @@ int64_t stable_order_words(int64_t n, int32_t k);   // of `base` below, for n po
 // and segoff[k+1] are scratch).
 hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32_t *cnt, int32_t *off, int32_t *cursor,
                               int32_t *segoff, int32_t *order, hipStream_t st);
+// order_out[] = order[] with the points of low thresholds first (stably, in a few classes; see there).  bin[n], cls[n] and
+// words[threshold_class_words(n)] are scratch, and cnt, off, cursor and segoff of launch_group_order are overwritten.
+int64_t threshold_class_words(int64_t n);
+// *above = how many of every 16th point have a threshold that puts them into a class of its own (tau, bin and words as above)
+hipError_t launch_threshold_sample(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
+                                   const int32_t *labels, float *tau, int32_t *bin, int32_t *words, int32_t *above, hipStream_t st);
+bool thresholds_have_tail(int64_t n, int32_t above);
+hipError_t launch_threshold_classes(const float *tau, int64_t n, const int32_t *order, int32_t *bin, int32_t *cls, int32_t *words,
+                                    int32_t *cnt, int32_t *off, int32_t *cursor, int32_t *segoff, int32_t *order_out,
+                                    hipStream_t st);
 // largest cluster whose members launch_update leaves sorted by index in w.order (larger ones: any order)
 int32_t update_sort_cap();
 // S (optional, [k][ds] fp64) receives the sum of every cluster; y_absmax (optional) the bit pattern of max |Y| of

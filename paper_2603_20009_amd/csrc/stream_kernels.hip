@@ -1852,6 +1852,125 @@ hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32
   return hipGetLastError();
 }
 
+// An order of points partitioned, stably, by the class of their threshold: 0 below THR_TAIL times the median, above that by
+// halves of what is left, 2 for the top quarter, 3 for the top eighth, ..., THR_CLASSES - 1 for the top 1/32 (1 is empty: the
+// median's own half).  Thresholds that are worth a tile of their own are a long tail (incumbents out of date, points far from
+// every centroid: quantiles of 2.5M x 384 against 32 768 centroids 0.22 at 1/2, 0.27 at 0.9, 1.44 at 0.99), and a point of the
+// tail keeps nearly every column of its row tile alive.  Grouped by label alone nearly every tile of 128 points holds one.
+// Column tiles listed per row tile, and the whole call in ms, by label -> with 4 | 6 | 8 classes of any threshold -> with 6 above
+// 1.25 | 1.5 | 2 times the median (these on top of a cheaper finish of poor tiles):
+//   2.5M x 384, k = 32 768            209 -> 28.1 | 16.4 | 16.4 -> 16.4 | 14.4 | 14.4    99.4 -> 42.7 | 40.8 | 40.8 -> 42.4 | 40.0 | 39.9
+//   1M x 768, k = 16 384              108 -> 14.9 | 8.6 | 8.6 -> 8.2 | 8.1 | 8.1         42.3 -> 25.5 | 22.2 | 22.1 -> 22.1 | 21.8 | 21.9
+//   1M x 768, k = 5000                22 -> 5.0 | 3.3 | 3.3 -> 2.9 | 2.9 | 2.9           16.3 -> 13.9 | 13.5 | 13.5 -> 13.2 | 13.3 | 13.2
+//   40 000 x 256, k = 4500            34 -> 4.8 | 3.6 | 3.6 -> 3.2 | 2.8 | 2.7           0.60 -> 0.58 | 0.59 | 0.57 -> 0.56 | 0.55 | 0.57
+//   600 000 x 1536, k = 10 000, no incumbents given  51 -> 7.8 | 5.3 | 5.3 -> 5.0 | 5.0 | 5.0    69.3 -> ... -> 30.9 | 31.0 | 31.0
+// Thresholds that are alike are better left in the order of the labels: 2M x 96 around 16 384 centres, every incumbent right, 10.5
+// column tiles a row tile, 14.7 with classes of any threshold, 11.5 | 10.5 | 10.5 with a limit (8.1 ms by label, 9.5, 9.0 | 8.5 |
+// 8.6).  Twice the median: the squared distances of a normal cloud in 64 dimensions do not reach it.
+// The ranks come from a histogram of the thresholds' upper bits (exponent and 5 bits of the mantissa: a bin is 3 % wide, and
+// a bin that crosses a border goes to the lower class), so no sort is needed and the order depends on the thresholds alone.
+constexpr int THR_BINS = 8192, THR_CLASSES = 6, THR_SAMPLE = 16;
+constexpr float THR_TAIL = 2.f;
+__global__ void threshold_bins_kernel(const float *tau, int64_t n, int32_t *bin) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    bin[i] = (int32_t)((__float_as_uint(tau[i]) & 0x7fffffffu) >> 18);
+}
+// class_of[b] = 0 where the bin starts below THR_TAIL times the median's, else floor(log2(n / number of points in the bins from b
+// on)), at most THR_CLASSES - 1.  *above (optional): the points of the other classes.
+__global__ void __launch_bounds__(1024) threshold_classes_kernel(const int32_t *cnt, int64_t n, int32_t *class_of,
+                                                                 int32_t *above) {
+  constexpr int PER = THR_BINS / 1024;
+  __shared__ int s_sum[16];
+  __shared__ int s_median, s_above;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int v[PER], sum = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) sum += v[u] = cnt[tid * PER + u];
+  int run = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(run, o, 64);
+    if (lane >= o) run += t;
+  }
+  if (lane == 63) s_sum[wave] = run;
+  __syncthreads();
+  int64_t first = run - sum;   // points in the bins below this thread's
+  for (int w = 0; w < wave; ++w) first += s_sum[w];
+  int64_t below = first;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (2 * below <= n && 2 * (below + v[u]) > n) s_median = tid * PER + u;
+    below += v[u];
+  }
+  __syncthreads();
+  if (tid == 0) s_above = 0;
+  __syncthreads();
+  int mine = 0;
+  const float tail = THR_TAIL * __uint_as_float((unsigned int)s_median << 18);
+  below = first;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int b = tid * PER + u;
+    int c = 0;
+    while (c < THR_CLASSES - 1 && ((n - below) << (c + 1)) <= n) ++c;
+    if (__uint_as_float((unsigned int)b << 18) < tail) c = 0;
+    class_of[b] = c;
+    if (c > 0) mine += v[u];
+    below += v[u];
+  }
+  if (mine) atomicAdd(&s_above, mine);
+  __syncthreads();
+  if (above && tid == 0) *above = s_above;
+}
+__global__ void class_of_points_kernel(const int32_t *order, const int32_t *bin, const int32_t *class_of, int64_t n, int32_t *cls) {
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x)
+    cls[p] = class_of[bin[order[p]]];
+}
+__global__ void sample_labels_kernel(const int32_t *labels, int64_t m, int32_t *out) {
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += (int64_t)gridDim.x * blockDim.x)
+    out[j] = labels[j * THR_SAMPLE];
+}
+int64_t threshold_class_words(int64_t n) { return 2 * THR_BINS + stable_order_words(n, THR_CLASSES); }
+static unsigned threshold_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, (int64_t)num_cus() * 16); }
+// words: [THR_BINS] counts | [THR_BINS] classes
+static hipError_t classify_thresholds(const float *tau, int64_t n, int32_t *bin, int32_t *words, int32_t *above, hipStream_t st) {
+  hipLaunchKernelGGL(threshold_bins_kernel, dim3(threshold_grid(n)), dim3(256), 0, st, tau, n, bin);
+  hipError_t rc = launch_fill_u32(reinterpret_cast<unsigned int *>(words), THR_BINS, 0u, st);
+  if (rc != hipSuccess) return rc;
+  // (in LDS for few points too: thresholds that are alike fall into few bins, and 60 000 atomics on those took 0.2 ms)
+  const int per = 8192;
+  hipLaunchKernelGGL(histogram_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(CNT_THREADS), THR_BINS * sizeof(int), st,
+                     (const int32_t *)bin, n, (int32_t)THR_BINS, words, (unsigned int *)nullptr, per, 1);
+  hipLaunchKernelGGL(threshold_classes_kernel, dim3(1), dim3(1024), 0, st, (const int32_t *)words, n, words + THR_BINS, above);
+  return hipGetLastError();
+}
+// A tail of one point in 2000 is in every 16th row tile.  One point of THR_SAMPLE tells whether there is one: the pass over all
+// thresholds and the partition are 3 to 5 % of a step that has none (2M x 96 above 0.4 of 8.1 ms), the sample 0.03 to 0.05 ms.
+hipError_t launch_threshold_sample(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
+                                   const int32_t *labels, float *tau, int32_t *bin, int32_t *words, int32_t *above, hipStream_t st) {
+  if (n <= 0) return hipErrorInvalidValue;
+  const int64_t m = (n + THR_SAMPLE - 1) / THR_SAMPLE;
+  hipLaunchKernelGGL(sample_labels_kernel, dim3(threshold_grid(m)), dim3(256), 0, st, labels, m, bin);
+  hipError_t rc = launch_tau_init(Xr, ldx * THR_SAMPLE, m, ds, Y, ldy, bin, tau, nullptr, st);
+  if (rc != hipSuccess) return rc;
+  return classify_thresholds(tau, m, bin, words, above, st);
+}
+bool thresholds_have_tail(int64_t n, int32_t above) { return (int64_t)above * 2000 > (n + THR_SAMPLE - 1) / THR_SAMPLE; }
+hipError_t launch_threshold_classes(const float *tau, int64_t n, const int32_t *order, int32_t *bin, int32_t *cls, int32_t *words,
+                                    int32_t *cnt, int32_t *off, int32_t *cursor, int32_t *segoff, int32_t *order_out,
+                                    hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const int32_t *class_of = words + THR_BINS;
+  int32_t *base = words + 2 * THR_BINS;
+  hipError_t rc = classify_thresholds(tau, n, bin, words, nullptr, st);
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(class_of_points_kernel, dim3(threshold_grid(n)), dim3(256), 0, st, order, (const int32_t *)bin, class_of, n, cls);
+  launch_stable_counts(cls, n, THR_CLASSES, base, cnt, nullptr, st);
+  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, (const int32_t *)cnt, (int32_t)THR_CLASSES, off, cursor, segoff,
+                     (unsigned int *)nullptr);
+  return launch_stable_scatter(cls, n, THR_CLASSES, off, base, order_out, order, st);
+}
+
 // The same update from the points that changed label only: S (the cluster sums of the previous update) takes the
 // rows of the points that joined minus those of the points that left, and every centroid is S / size again.
 // w.cnt holds the new cluster sizes; `changed` is the number of points with assign != prev (known to the host from

@@ -572,3 +572,36 @@ def test_listed_tiles_that_finish_many_pairs(skm, n, d, k):  # noqa: F811
     assert ra["survivors"] == rc["survivors"] and abs(ra["completed"] - rc["completed"]) <= 2 + 1e-5 * rc["completed"]
     assert int((a != c).sum()) <= 2e-4 * n     # (near-ties of two roundings)
     assert bool(((da - dc).abs() <= 2.0 ** -18 * (X.norm(dim=1) + Y.norm(dim=1).max()) ** 2).all())
+
+
+# A step on its own orders its points by the class of their threshold, then by label: thresholds with a long tail, all of them
+# alike, none above zero, a tail larger than half, and clusters of several row tiles (which have an order of their own inside).
+# Counts, labels and distances are those of the points in the caller's order, and the same from run to run.
+@pytest.mark.parametrize("n,d,k,form", [(33_001, 200, 4100, "tail"), (33_001, 200, 4100, "most"), (40_000, 64, 4096, "alike"),
+                                        (32_768, 80, 4096, "zero"), (530_000, 48, 4097, "tail")])
+def test_points_in_the_order_of_their_thresholds(skm, dg, n, d, k, form):  # noqa: F811
+    say("threshold classes", n, d, k, form)
+    g = torch.Generator().manual_seed(n + d)
+    Y = dg.mixture(k, d, 64, 3, "embed").cuda()
+    lab = torch.randint(0, k, (n,), generator=g).cuda()
+    X = Y[lab].clone()
+    if form == "alike":
+        X[:, 0] += 0.25
+    elif form != "zero":
+        X += 0.02 * torch.randn(n, d, generator=g).cuda()
+    prev = lab.int()
+    if form in ("tail", "most"):
+        far = torch.rand(n, generator=g).cuda() < (0.02 if form == "tail" else 0.7)
+        prev = torch.where(far, torch.randint(0, k, (n,), generator=g).int().cuda(), prev)
+    R = skm.make_rotation(d, 4)
+    runs = [skm.assign(X, Y, prev, opts=skm.FitOptions(R=R, screen=s)) for s in (0, 0, -1)]
+    (a, da, ra), (b, db, rb), (c, dc, rc) = runs
+    assert torch.equal(a, b) and torch.equal(da, db) and ra["survivors"] == rb["survivors"]
+    assert ra["listed_tiles"] > 0 and rc["listed_tiles"] == 0
+    assert abs(ra["survivors"] - rc["survivors"]) <= 1e-5 * max(rc["survivors"], n)
+    # a label that differs is a near-tie: the rounding of a split product, 2^-20 of the norms, either way
+    bound = 2.0 ** -19 * (X.double().norm(dim=1) + Y.double().norm(dim=1).max()) ** 2
+    moved = a != c
+    exact = lambda l: ((X.double() - Y.double()[l.long()]) ** 2).sum(1)  # noqa: E731
+    assert int(moved.sum()) <= 1e-3 * n and bool(((exact(a) - exact(c)).abs() <= bound)[moved].all())
+    assert bool(((da.double() - exact(a)).abs() <= bound).all())
