@@ -854,6 +854,7 @@ struct HostTimes {
 // context's buffers, the rotated points and their regrouped copy, the rotation matrices and their generator, the ETR
 // buffers.  What skm_workspace_bytes reports.
 inline bool assign_groups(int64_t n, int32_t ds, int32_t k, int32_t screen_mode);
+inline bool assign_groups_always(int32_t k);
 // ... of one assignment call (assign_impl)
 size_t assign_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &p) {
   const size_t ds0 = (size_t)((d + 15) / 16 * 16);
@@ -1096,8 +1097,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   // 9.4 (9.8), 200 000 x 1536, k = 300 779 -> 746 (788) us.  After a step that cut 32 % one that cut 74 %, a quarter of the tiles done
   // twice: 100 000 x 896, k = 600 469 -> 569 us.
   const bool list_all = deep && c.screen_mode == 0 && c.last_prune_frac >= 0.33 && c.last_prune_frac < 0.50;
-  const bool screen = c.colmask && nb > 0 &&
-                      (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
+  bool screen = c.colmask && nb > 0 &&
+                (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
   // theta ratio at checkpoint m: t_m = min(d, d' + 64 m) dimensions seen
   float ratio[kMaxBlocks + 1];
   for (int m = 0; m <= nb; ++m) ratio[m] = (float)theta_ratio(c.d, std::min(c.d, dprime + kBlockDims * m), eps0);
@@ -1137,14 +1138,24 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     // (or were just given above), so that a row tile holds the points of one or two clusters and the first filter has
     // columns to drop.  One read-back of the group sizes decides whether the order is reproducible (see below); with them comes
     // whether the thresholds of a sample have a tail.
-    HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.st));
     HIPCHK(launch_threshold_sample(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, (int32_t *)c.dist, c.class_ws, c.grp_cnt + c.k, c.st));
-    std::vector<int32_t> sizes((size_t)c.k + 1);
-    HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * ((size_t)c.k + 1), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
-    c.max_cluster = *std::max_element(sizes.begin(), sizes.end() - 1);
-    regroup = true;
-    by_threshold = thresholds_have_tail(c.n, sizes.back());
+    regroup = assign_groups_always(c.k);
+    if (!regroup) {   // (asked first: the grouping is 3 to 6 % of a step that does not use it)
+      int32_t above = 0;
+      HIPCHK(hipMemcpyAsync(&above, c.grp_cnt + c.k, sizeof(int32_t), hipMemcpyDeviceToHost, c.st));
+      HIPCHK(hipStreamSynchronize(c.st));
+      regroup = thresholds_have_tail(c.n, above);
+      if (!regroup && c.screen_mode == 0) screen = false;
+    }
+    if (regroup) {
+      HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.st));
+      std::vector<int32_t> sizes((size_t)c.k + 1);
+      HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * ((size_t)c.k + 1), hipMemcpyDeviceToHost, c.st));
+      HIPCHK(hipStreamSynchronize(c.st));
+      c.max_cluster = *std::max_element(sizes.begin(), sizes.end() - 1);
+      by_threshold = thresholds_have_tail(c.n, sizes.back());
+      if (c.max_cluster > update_sort_cap() && !assign_groups_always(c.k) && c.screen_mode == 0) screen = false;   // (no new order below)
+    }
     c.group_now = false;
   }
   if (regroup) {
@@ -1666,9 +1677,16 @@ int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const fl
 }
 
 // A single assignment step regroups the points itself (see assign_impl) when there are thousands of centroids, several
-// points per centroid, rows that the regrouping pass covers, and the first filter is not switched off.
+// points per centroid, rows that the regrouping pass covers, and the first filter is not switched off.  From 2048 centroids on
+// only where there is work for some ten milliseconds (2^40 products) and the thresholds have a tail (see step_pruned): then
+// 1M x 768, k = 3000 21.3 -> 12.1 ms, k = 2048 16.2 -> 11.4 (without incumbents 18.8 -> 14.4), 1.4M x 384, k = 2100 15.0 -> 8.0, 2.5M x 128,
+// k = 3500 12.4 -> 8.4 (16.5 -> 15.5), 600 000 x 1200, k = 2048 18.4 -> 13.9; but 1M x 768, k = 1024 10.8 -> 10.5 (11.7 -> 12.0), 1M x 1536,
+// k = 512 23.3 -> 25.5, 200 000 x 256, k = 2048 1.16 -> 1.05 (1.50 -> 2.01), 50 000 x 768, k = 2048 0.95 -> 1.03.  (Up to 2^33
+// values: the regrouped copy must not refuse a call for memory that was served without it.)
+inline bool assign_groups_always(int32_t k) { return k >= 4096; }
 inline bool assign_groups(int64_t n, int32_t ds, int32_t k, int32_t screen_mode) {
-  return screen_mode >= 0 && k >= 4096 && n >= 8 * (int64_t)k && ds <= 2048 && n < ((int64_t)1 << 31);
+  if (screen_mode < 0 || n < 8 * (int64_t)k || ds > 2048 || n >= ((int64_t)1 << 31)) return false;
+  return assign_groups_always(k) || (k >= 2048 && n * ds <= ((int64_t)1 << 33) && (double)n * ds * k >= 0x1p40);
 }
 int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, int32_t k, const int32_t *prev_assign,
                 int32_t dprime_in, const skm_params *pp, int32_t *assign_out, float *dist_out);

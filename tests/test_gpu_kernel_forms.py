@@ -605,3 +605,23 @@ def test_points_in_the_order_of_their_thresholds(skm, dg, n, d, k, form):  # noq
     exact = lambda l: ((X.double() - Y.double()[l.long()]) ** 2).sum(1)  # noqa: E731
     assert int(moved.sum()) <= 1e-3 * n and bool(((exact(a) - exact(c)).abs() <= bound)[moved].all())
     assert bool(((da.double() - exact(a)).abs() <= bound).all())
+
+
+# The same from 2048 centroids on, where there are 2^40 products: with a tail the points are regrouped and the columns listed,
+# without one the step stays as it is (all but the incumbent of a point cut: nothing to list).
+@pytest.mark.parametrize("tail", [True, False])
+def test_order_of_thresholds_with_fewer_centroids(skm, dg, tail):  # noqa: F811
+    n, d, k = 4_194_400, 120, 2049
+    say("fewer centroids", n, d, k, tail)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Y = dg.mixture(k, d, 64, 3, "embed").cuda()
+    prev = torch.randint(0, k, (n,), generator=g, device="cuda").int()
+    X = Y[prev.long()] + 0.02 * torch.randn(n, d, generator=g, device="cuda")
+    if tail:
+        prev = torch.where(torch.rand(n, generator=g, device="cuda") < 0.02, torch.randint(0, k, (n,), generator=g, device="cuda").int(), prev)
+    R = skm.make_rotation(d, 4)
+    (a, da, ra), (c, dc, rc) = (skm.assign(X, Y, prev, opts=skm.FitOptions(R=R, screen=s)) for s in (0, -1))
+    assert (ra["listed_tiles"] > 0) == tail and rc["listed_tiles"] == 0
+    assert abs(ra["survivors"] - rc["survivors"]) <= 1e-5 * max(rc["survivors"], n)
+    bound = 2.0 ** -19 * (X.norm(dim=1).max() + Y.norm(dim=1).max()) ** 2     # as above
+    assert int((a != c).sum()) <= 1e-3 * n and float((da - dc).abs().max()) <= 2 * float(bound)
