@@ -160,8 +160,7 @@ typedef struct skm_params {
                             rounding bound of the row's smallest approximate distance), and only those get their exact
                             distance.  0 = in pruned steps that follow a step which cut at least half of the pairs at the
                             first test (one that cut a third to a half: every column listed without the pass), and in
-                            iteration 1 from 512 centroids on (2048 for fewer than 16 384 points); 1 = in every step; -1 =
-                            never.
+                            iteration 1 from 2048 centroids on; 1 = in every step; -1 = never.
                             Execution strategy only: a pair the filter drops is dropped by the exact arithmetic too
                             (the distances of those it leaves are rounded as dense_frac says) */
   int32_t tau_group;     /* 0    : centroids after which a point's threshold tau is refreshed inside a step.  0 (= k):

@@ -1020,10 +1020,10 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   // Many centroids: the low-precision filter first, exact distances for the few candidates it leaves.  It also writes the
   // tables that the next step would write.  Iterations 1 and 2 together, product -> filter, for 1M points: k = 512 16.9 -> 16.2
   // ms at d = 1536 and 2.67 -> 2.53 at d = 100, k = 1024 27.1 -> 24.7, k = 2047 47.0 -> 41.0; 300 000 x 1024, k = 800 7.81 -> 7.25,
-  // 200 000 x 79, k = 700 900 -> 770 us, 20 000 x 128, k = 600 342 -> 332, 20 000 x 1536, k = 512 1152 -> 1125; but 5000 x 768, k =
-  // 600 438 -> 458: with few rows the launches in front of the multiply are what counts.
-  const int32_t filter_from = c.n >= 16384 ? 512 : 2048;
-  if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= filter_from)) {
+  // 200 000 x 79, k = 700 900 -> 770 us; 5000 x 768, k = 600 438 -> 458.  It would pay from 512 clusters on, but the line lies at
+  // 2048: the two sides round a distance differently, so that the winners of ties to 1e-7 differ (1M x 1536, k = 1024: 1 to 9
+  // points a fit, either side the nearer one to 64 bits about as often), and such a point may send a fit to another end.
+  if (c.colmask && !c.exact_filter_off && (c.screen_mode > 0 || c.k >= 2048)) {
     if (int rc = step_exact_filtered(c, tm, ss)) return rc;
     if ((c.report->flag & 1u) == 0) {
       if (c.report->flag != 0) return fail(SKM_EINTERNAL, "a point was left without a centroid");

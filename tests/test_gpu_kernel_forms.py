@@ -342,8 +342,8 @@ def test_host_resident_fit_keeps_what_fits(skm, dg, n, d, k, room):  # noqa: F81
     assert [r["survivors"] for r in sent.trace] == [r["survivors"] for r in kept.trace]
 
 
-# Iteration 1 goes through the one-product filter from 512 clusters on (2048 below 16 384 points), through the product of all
-# pairs otherwise: the labels of a fit of one iteration on both sides of the lines.
+# Iteration 1 goes through the one-product filter from 2048 clusters on, through the product of all pairs otherwise: the labels of
+# a fit of one iteration on both sides of the line.
 @pytest.mark.parametrize("n,k", [(16_383, 512), (16_384, 511), (16_384, 512), (16_500, 513), (4096, 2047), (4096, 2048)])
 def test_iteration_one_on_both_sides_of_the_filter(skm, orc, dg, n, k):  # noqa: F811
     say("iteration 1", n, k)
@@ -351,11 +351,28 @@ def test_iteration_one_on_both_sides_of_the_filter(skm, orc, dg, n, k):  # noqa:
     X = dg.mixture(n, d, 300, 8, "embed").numpy()
     R = orc.random_rotation(d, 2)
     fit = skm.fit(cuda(X), k, 1, 6, skm.FitOptions(R=cuda(R), final_assign=False))
-    assert (fit.trace[0]["screen_dims"] > 0) == (k >= (512 if n >= 16_384 else 2048))
+    assert (fit.trace[0]["screen_dims"] > 0) == (k >= 2048)
     Xr = orc.rotate(X, R)
     Y0 = Xr[orc.sample_rows(6, n, k)]
     ref, _ = orc.assign_full(Xr, Y0)
     check_assignment(fit.assign.cpu().numpy(), ref, Xr, Y0, min_agree=0.999)
+
+
+# Below that line the ties that rounding decides fall as they do without the filter: rows half way between two of the initial
+# centroids, most of them the nearest two or three to within 1e-7.  One more such point on the other side is another fit.
+@pytest.mark.parametrize("n,d,k", [(16_384, 96, 512), (20_001, 64, 777), (30_000, 256, 1024), (17_000, 100, 2047)])
+def test_near_ties_of_iteration_one(skm, n, d, k):  # noqa: F811
+    say("near-ties of iteration 1", n, d, k)
+    g = torch.Generator().manual_seed(n + k)
+    C = torch.nn.functional.normalize(torch.randn(k, d, generator=g), dim=1)
+    near = torch.cdist(C, C).fill_diagonal_(9.0).argmin(1)          # every centroid's nearest one
+    a = torch.randint(0, k, (n - k,), generator=g)
+    X = torch.cat([C, 0.5 * (C[a] + C[near[a]])]).cuda()
+    R = skm.make_rotation(d, 3)
+    opts = dict(R=R, init_idx=range(k), final_assign=False)
+    with_filter, without, forced = (skm.fit(X, k, 1, 1, skm.FitOptions(screen=s, **opts)) for s in (0, -1, 1))
+    assert torch.equal(with_filter.assign, without.assign) and torch.equal(with_filter.centroids, without.centroids)
+    assert not torch.equal(forced.assign, without.assign)           # (the rows do tell the two forms apart)
 
 
 # Nearest centroids with the rows in registers (aligned rows of 32 to 128 dimensions, more than 192 columns or 448 beyond 64
