@@ -10,8 +10,9 @@
 // Two arithmetic forms share the tile shape and the epilogues:
 //  - gemm_split_kernel: fp32 operands split into two fp16 numbers each, three v_mfma_f32_32x32x16_f16
 //    per product, fp32 accumulation (fp32-class accuracy at a multiple of the fp32 matrix rate).  Used
-//    whenever K >= 32 (64 if the operands are not 16-byte aligned) and the caller supplies magnitude bounds.
-//  - gemm_kernel: plain v_mfma_f32_32x32x2_f32, for shorter K and callers without bounds.
+//    whenever the operands are 16-byte aligned, K >= 32 and the caller supplies magnitude bounds.  (One scale for a matrix: a row
+//    2^-24 of the largest has 16 bits left.)
+//  - gemm_kernel: plain v_mfma_f32_32x32x2_f32, for unaligned operands and K = 16.
 //
 // The score matrix is never written for the distance use of iteration 1: the epilogue reduces it to
 // a row argmin.  Iterations >= 2 use the progressive kernel of progressive.hip, built on the same tile.
@@ -170,6 +171,21 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[TM][TN], const GemmOperands &
   }
 }
 
+// The first `valid` of four values at any 4-byte boundary, zeros behind them: one load unless the row ends among them (46 467 x
+// 495 by 495 x 495 with a load a value: 441 us, now 245).
+__device__ inline float4 load4_any(const float *p, int valid) {
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (valid >= 4) {
+    const f32x4_u u = *reinterpret_cast<const f32x4_u *>(p);
+    v = make_float4(u.x, u.y, u.z, u.w);
+  } else {
+    if (valid > 0) v.x = p[0];
+    if (valid > 1) v.y = p[1];
+    if (valid > 2) v.z = p[2];
+  }
+  return v;
+}
+
 template <int BK, int EPI, bool ALIGNED>
 __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
   put_stamp(g.stamp);
@@ -204,10 +220,7 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
         if (ALIGNED) {
           if (kk < g.K) v = *reinterpret_cast<const float4 *>(src);
         } else {
-          if (kk + 0 < g.K) v.x = src[0];
-          if (kk + 1 < g.K) v.y = src[1];
-          if (kk + 2 < g.K) v.z = src[2];
-          if (kk + 3 < g.K) v.w = src[3];
+          v = load4_any(src, g.K - kk);
         }
       }
       ra[s] = v;
@@ -223,10 +236,7 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
         if (ALIGNED) {
           if (kk < g.K) v = *reinterpret_cast<const float4 *>(src);
         } else {
-          if (kk + 0 < g.K) v.x = src[0];
-          if (kk + 1 < g.K) v.y = src[1];
-          if (kk + 2 < g.K) v.z = src[2];
-          if (kk + 3 < g.K) v.w = src[3];
+          v = load4_any(src, g.K - kk);
         }
       }
       rb[s] = v;
@@ -309,23 +319,10 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
 // compiler keep the loads of two slabs in flight and count them.  While slab s is multiplied from one LDS
 // buffer, slab s + 1 (requested one step earlier) is converted and written to the other buffer between the
 // matrix instructions, and slab s + 2 is requested.
-template <bool ANY>
-__device__ inline float4 load4(const float *p) {
-  if constexpr (ANY) {
-    const f32x4_u v = *reinterpret_cast<const f32x4_u *>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-  } else {
-    return *reinterpret_cast<const float4 *>(p);
-  }
-}
 constexpr int SBK = 32, SLS = SBK + 4;
 constexpr int S_F4 = BM * (SBK / 4) / NTHREADS;   // float4 staged per thread and operand: 4
 
-//
-// ANY (operands that are not 16-byte aligned, or K no multiple of 4): loads of four values at any 4-byte boundary.  The four
-// that would end behind K are the row's last four instead, and those of them that an earlier load of the row has taken
-// count as zero.  (46 467 x 495 by 495 x 495 with fp32 products, a value a load: 460 us, now 109.)
-template <int EPI, bool ANY>
+template <int EPI>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
   put_stamp(g.stamp);
@@ -363,14 +360,12 @@ gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
   auto gload = [&](int k0, float4 *ra, float4 *rb) {
     const int kk = min(k0 + 4 * kq, g.K - 4);
 #pragma unroll
-    for (int s = 0; s < S_F4; ++s) ra[s] = load4<ANY>(pa[s] + kk);
+    for (int s = 0; s < S_F4; ++s) ra[s] = *reinterpret_cast<const float4 *>(pa[s] + kk);
 #pragma unroll
-    for (int s = 0; s < S_F4; ++s) rb[s] = load4<ANY>(pb[s] + kk);
+    for (int s = 0; s < S_F4; ++s) rb[s] = *reinterpret_cast<const float4 *>(pb[s] + kk);
   };
-  // (valid: how many of the four count; the last ones, see ANY)
-  auto split_store = [&](float *dst_row, const float4 &v, float scale, int valid) {
-    const float s3 = ANY && valid < 4 ? 0.f : scale, s2 = ANY && valid < 3 ? 0.f : scale, s1 = ANY && valid < 2 ? 0.f : scale;
-    const f32x2 p0 = {v.x * s3, v.y * s2}, p1 = {v.z * s1, v.w * scale};
+  auto split_store = [&](float *dst_row, const float4 &v, float scale) {
+    const f32x2 p0 = {v.x * scale, v.y * scale}, p1 = {v.z * scale, v.w * scale};
     const f16x2 h0 = __builtin_convertvector(p0, f16x2), h1 = __builtin_convertvector(p1, f16x2);
     const f16x2 l0 = __builtin_convertvector(p0 - __builtin_convertvector(h0, f32x2), f16x2);
     const f16x2 l1 = __builtin_convertvector(p1 - __builtin_convertvector(h1, f32x2), f16x2);
@@ -381,12 +376,11 @@ gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
     *reinterpret_cast<uint2 *>(dst_row + 16 + 2 * kq) = lo;
   };
   auto store_slab = [&](int buf, int k0, const float4 *ra, const float4 *rb) {   // unpipelined (prologue)
-    const int valid = g.K - (k0 + 4 * kq);
-    const bool live = valid > 0;
+    const bool live = k0 + 4 * kq < g.K;
 #pragma unroll
     for (int s = 0; s < S_F4; ++s) {
-      split_store(As + (buf * BM + st_row + 32 * s) * SLS, ra[s], live ? scale_a : 0.f, valid);
-      split_store(Bs + (buf * BN + st_row + 32 * s) * SLS, rb[s], live ? scale_b : 0.f, valid);
+      split_store(As + (buf * BM + st_row + 32 * s) * SLS, ra[s], live ? scale_a : 0.f);
+      split_store(Bs + (buf * BN + st_row + 32 * s) * SLS, rb[s], live ? scale_b : 0.f);
     }
   };
 
@@ -441,8 +435,7 @@ gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
     const float *Bb = Bs + (buf * BN + wn * WTN + r32) * SLS;
     float *Aw = As + ((buf ^ 1) * BM + st_row) * SLS;
     float *Bw = Bs + ((buf ^ 1) * BN + st_row) * SLS;
-    const int valid = g.K - (k_store + 4 * kq);
-    const bool live = valid > 0;
+    const bool live = k_store + 4 * kq < g.K;
     const float fa = live ? scale_a : 0.f, fb = live ? scale_b : 0.f;
     __builtin_amdgcn_sched_barrier(0);
     gload(k_load, la, lb);
@@ -453,35 +446,35 @@ gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
     }
     __builtin_amdgcn_sched_barrier(0);
     mma4(ah, bh);
-    split_store(Aw, sa[0], fa, valid);
-    split_store(Aw + 32 * SLS, sa[1], fa, valid);
+    split_store(Aw, sa[0], fa);
+    split_store(Aw + 32 * SLS, sa[1], fa);
     mix(std::integral_constant<int, 6>());
     __builtin_amdgcn_sched_barrier(0);
     mma4(al, bh);
-    split_store(Aw + 64 * SLS, sa[2], fa, valid);
+    split_store(Aw + 64 * SLS, sa[2], fa);
     mix(std::integral_constant<int, 3>());
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 2; ++t) { al[t] = frag(Ab, 1, 1, t); bh[t] = frag(Bb, 1, 0, t); }
     mma4(ah, bl);
-    split_store(Aw + 96 * SLS, sa[3], fa, valid);
+    split_store(Aw + 96 * SLS, sa[3], fa);
     __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
     mix(std::integral_constant<int, 3>());
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 2; ++t) { ah[t] = frag(Ab, 1, 0, t); bl[t] = frag(Bb, 1, 1, t); }
     mma4(al, bh);
-    split_store(Bw, sb[0], fb, valid);
-    split_store(Bw + 32 * SLS, sb[1], fb, valid);
+    split_store(Bw, sb[0], fb);
+    split_store(Bw + 32 * SLS, sb[1], fb);
     __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
     mix(std::integral_constant<int, 6>());
     __builtin_amdgcn_sched_barrier(0);
     mma4(ah, bl);
-    split_store(Bw + 64 * SLS, sb[2], fb, valid);
+    split_store(Bw + 64 * SLS, sb[2], fb);
     mix(std::integral_constant<int, 3>());
     __builtin_amdgcn_sched_barrier(0);
     mma4(ah, bh);
-    split_store(Bw + 96 * SLS, sb[3], fb, valid);
+    split_store(Bw + 96 * SLS, sb[3], fb);
     mix(std::integral_constant<int, 3>());
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
@@ -820,9 +813,9 @@ static hipError_t launch_one(const GemmOperands &g, const typename EpiArgs<EPI>:
   return hipGetLastError();
 }
 
-template <int EPI, bool ANY>
+template <int EPI>
 static hipError_t launch_split(const GemmOperands &g, const typename EpiArgs<EPI>::type &e, hipStream_t st) {
-  auto kern = gemm_split_kernel<EPI, ANY>;
+  auto kern = gemm_split_kernel<EPI>;
   static const hipError_t attr_rc = hipFuncSetAttribute(
       reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<SBK>());
   if (attr_rc != hipSuccess) return attr_rc;
@@ -954,10 +947,7 @@ static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>:
     shift_rows(eb, r0);
     hipError_t rc;
     if (big) rc = launch_split256<EPI>(gb, eb, st);
-    else if (al && g.K >= SBK && g.a_absmax && g.b_absmax) rc = launch_split<EPI, false>(gb, eb, st);
-    // (from K = 64: its error against fp64 is then well below that of fp32 products, rms of X R 1.25e-7 : 1.5e-7 at 63,
-    // 2.9e-7 : 4.6e-7 at 495; at 33 they are equal)
-    else if (g.K >= 2 * SBK && g.a_absmax && g.b_absmax) rc = launch_split<EPI, true>(gb, eb, st);
+    else if (al && g.K >= SBK && g.a_absmax && g.b_absmax) rc = launch_split<EPI>(gb, eb, st);
     else if (al) rc = bk32 ? launch_one<32, EPI, true>(gb, eb, st) : launch_one<16, EPI, true>(gb, eb, st);
     else rc = bk32 ? launch_one<32, EPI, false>(gb, eb, st) : launch_one<16, EPI, false>(gb, eb, st);
     if (rc != hipSuccess) return rc;

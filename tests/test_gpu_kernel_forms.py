@@ -276,8 +276,8 @@ def test_listed_tiles_behind_one_that_was_done_again(skm, orc, dg, n, d, k, dp):
         assert abs(row["completed"] - ref.enter[-1]) <= max(2, 1e-3 * ref.enter[-1])
 
 
-# Rows of any length and alignment: four values a load from any 4-byte boundary, the last ones of a row again where the length is
-# no multiple of four (from 64 on; shorter rows in fp32 products).  n, d around the tiles of 128 and the slabs of 32.
+# Rows of any length and alignment: fp32 products, four values a load from any 4-byte boundary, the last ones of a row one by one
+# where the length is no multiple of four.  n, d around the tiles of 128 and the slabs of 16.
 @pytest.mark.parametrize("n,d", [(127, 61), (129, 63), (1, 65), (128, 66), (300, 67), (257, 95), (130, 97), (65, 127), (200, 129), (140, 495)])
 def test_products_of_rows_of_any_length(skm, dg, n, d):  # noqa: F811
     say("rows of any length", n, d)
@@ -286,8 +286,9 @@ def test_products_of_rows_of_any_length(skm, dg, n, d):  # noqa: F811
     shifted = torch.empty(n * d + 3, device="cuda")
     shifted[3:] = X.reshape(-1)
     rows = shifted[3:].view(n, d)                      # (not 16-byte aligned)
-    # halves of 22 bits a value and fp32 sums: 2^-21 of every product and 2^-24 of the partial sums at each of d / 16 steps of
-    # 16, all bounded by the norms (Cauchy-Schwarz; rows and columns have norm 1)
+    # the bound of the split form of aligned rows, to which these are held as well: halves of 22 bits a value and fp32 sums, 2^-21 of
+    # every product and 2^-24 of the partial sums at each of d / 16 steps of 16, all bounded by the norms (Cauchy-Schwarz; rows
+    # and columns have norm 1)
     bound = 2.0 ** -21 + (d / 16 + 16) * 2.0 ** -24
     for x in (X, rows):
         for transpose in (False, True):
@@ -298,6 +299,42 @@ def test_products_of_rows_of_any_length(skm, dg, n, d):  # noqa: F811
         out = skm.rotate(X, R)
         bad = torch.isnan(out).any(1)
         assert bool(bad[n // 2]) and int(bad.sum()) == 1
+
+
+# ... and their products know nothing of the other rows: beside one row that is larger by 2^20, 2^40 or 2^60, smaller by 2^20, or
+# not finite, every other row has the bits that it has without it.
+@pytest.mark.parametrize("d,shift", [(495, 0), (495, 1), (129, 0), (97, 3), (256, 1)])
+def test_products_beside_a_row_of_another_size(skm, dg, d, shift):  # noqa: F811
+    n = 300
+    R = skm.make_rotation(d, 3)
+    buf = torch.empty(n * d + 4, device="cuda")
+    X = buf[shift:shift + n * d].view(n, d)
+    X.copy_(dg.mixture(n, d, 5, 2, "embed"))
+    ref = [skm.rotate(X, R, transpose) for transpose in (False, True)]
+    row = X[200].clone()
+    others = torch.arange(n, device="cuda") != 200
+    for factor in (2.0 ** 20, 2.0 ** 40, 2.0 ** 60, 2.0 ** -20, float("inf"), float("nan")):
+        say("rows of another size", d, shift, factor)
+        X[200] = row * factor
+        for transpose in (False, True):
+            out = skm.rotate(X, R, transpose)
+            assert torch.equal(out[others], ref[transpose][others])
+            if 2.0 ** -20 <= factor < float("inf"):
+                assert torch.equal(out[200], ref[transpose][200] * factor)      # (scaling by a power of two is exact)
+            else:
+                assert not torch.isfinite(out[200]).any()
+
+
+def test_ground_truth_beside_a_point_of_another_size(skm, orc, dg):  # noqa: F811
+    n, d = 700, 495                                                 # (few points: the scores of all of them)
+    X = dg.mixture(n, d, 5, 2, "embed").numpy()
+    Q = dg.mixture(9, d, 5, 2, "embed", sample_seed=4).numpy()
+    for factor in (2.0 ** 20, 2.0 ** 40):
+        say("ground truth beside a large point", factor)
+        far = X.copy()
+        far[300] *= np.float32(factor)
+        ref = ((Q[:, None].astype(np.float64) - far[None]) ** 2).sum(2).argsort(1, kind="stable")[:, :10]
+        check_ground_truth(skm.etr_ground_truth(cuda(far), cuda(Q), 10).cpu().numpy(), ref, far, Q)
 
 
 # Few clusters, thousands of rows that change between them: the lists of a cluster's rows are worked off several times in an
