@@ -3000,7 +3000,7 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
   const bool pad_x = !whole || !aligned16(X), pad_y = d != ds || !aligned16(centroids);
   const int32_t dx = pad_x ? ds : d;   // dimensions of a row as the kernels below read it
   const int64_t chunk = pad_x ? std::min<int64_t>(n, std::max<int64_t>(((int64_t)64 << 20) / ds, 1024)) : n;
-  CallArena ws(((pad_x ? (size_t)chunk * ds : 0) + (pad_y ? (size_t)k * ds : 0) + (size_t)k * (ds + 33)) * 4 + (size_t)n * 8 + 8192);
+  CallArena ws(((pad_x ? (size_t)chunk * ds : 0) + (pad_y ? (size_t)k * ds : 0) + (size_t)k + split_words(k, ds)) * 4 + (size_t)n * 8 + 8192);
   Pool pool;
   float *Xo = nullptr, *Yo = nullptr, *ynorm = nullptr;
   unsigned long long *best = nullptr;

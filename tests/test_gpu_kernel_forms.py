@@ -412,6 +412,37 @@ def test_near_ties_of_iteration_one(skm, n, d, k):  # noqa: F811
     assert not torch.equal(forced.assign, without.assign)           # (the rows do tell the two forms apart)
 
 
+def fill_device(leave):
+    """Tensors that take the device's memory but for `leave` bytes (and what torch keeps)."""
+    torch.cuda.empty_cache()
+    held, piece = [], None
+    while (room := torch.cuda.mem_get_info()[0] - leave) > 1 << 22:
+        piece = room if piece is None else min(piece, room)
+        try:
+            held.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+        except torch.OutOfMemoryError:
+            piece //= 2
+    return held
+
+
+# The block that an exact assignment plans holds all of its buffers, the split copy of the centroids in whole units of 32
+# dimensions among them: a call like the one before finds all of its memory in the block that the library has kept.
+@pytest.mark.parametrize("d", [40, 48])
+def test_exact_assignment_in_the_block_of_the_call_before(skm, dg, d):  # noqa: F811
+    say("exact assignment in a kept block", d)
+    n, k = 1000, 200_000
+    Y = dg.mixture(k, d, 50, 3, "linear", "cuda")
+    X = (Y[:n] + 0.001).contiguous()
+    skm.release_memory()
+    a, dist = skm.assign_exact(X, Y)
+    b, dist_b = skm.assign_exact(X, Y)
+    held = fill_device(40 << 20)                        # (less than the split copy of the centroids)
+    b, dist_b = skm.assign_exact(X, Y)
+    del held
+    torch.cuda.empty_cache()
+    assert torch.equal(a, b) and torch.equal(dist, dist_b)
+
+
 # Nearest centroids with the rows in registers (aligned rows of 32 to 128 dimensions, more than 192 columns or 448 beyond 64
 # dimensions, four tiles of 256 x 64 to a CU): every number of 16-dimension steps, rows and columns that end inside a tile,
 # ranges that begin and end inside a row tile; against the oracle and, where the old form stands beside it, bit by bit.
