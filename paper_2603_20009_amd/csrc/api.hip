@@ -2436,9 +2436,9 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
 }
 
 // The exact assignment through the one-product search of iteration 1 (a third of the matrix work of the three-product argmin;
-// the candidates' distances are the direct ones), 2^18 rows at a time.  done = false: nothing to show for it - no memory for the
-// search's buffers, a candidate list that ran over, a row that no centroid was offered to (one that is no number) - and the
-// caller takes the other form, for all rows.
+// the candidates' distances are the direct ones), 2^18 rows at a time.  A batch with a candidate list that ran over or a row that
+// no centroid was offered to (one that is no number) takes the product of all pairs, in the same buffers: nothing is allocated
+// behind the first label that is written.  done = false: no room for the buffers, and the caller takes the other form.
 constexpr int64_t kExactRows = (int64_t)1 << 18;
 // From 2048 centroids on, for rows that the argmin with the rows in registers does not take, and from 2^34 multiply-adds on (the
 // search is a dozen launches more).  Three products -> search: 16 384 x 256, k = 4096 178 -> 173 us, 8000 x 384, k = 8000 228 -> 204,
@@ -2479,21 +2479,30 @@ int exact_through_filter(const float *X, int64_t n, int32_t d, const float *cent
       c.Xr = Xo;
       c.ldx = ds;
     }
-    if (r0 > 0) HIPCHK(launch_fill_u32(c.xr_bound, 1, 0u, st));
     if (int rc = c.measure_xr()) return rc;
     c.xnp_valid = c.xh_valid = false;
     if (int rc = filtered_nearest(c, ds, tm)) return rc;
     c.pending = true;
-    if (dist_out)   // (not the search's own distances, which add the blocks of a row one after the other: 2 to 3.7e-7 off, these 1.7e-7)
-      HIPCHK(launch_tau_init(c.Xr, c.ldx, rows, ds, c.Y, ds, nullptr, dist_out + r0, c.best, st, nullptr, nullptr, nullptr, nullptr, nullptr,
-                             assign_out + r0, nullptr, c.flag));
-    else
-      HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, rows, assign_out + r0, nullptr, nullptr, k, c.flag}, st));
+    // labels (and distances) from c.best
+    auto deliver = [&](unsigned int *unset) -> int {
+      if (dist_out)   // (not the search's own distances, which add the blocks of a row one after the other: 2 to 3.7e-7 off, these 1.7e-7)
+        HIPCHK(launch_tau_init(c.Xr, c.ldx, rows, ds, c.Y, ds, nullptr, dist_out + r0, c.best, st, nullptr, nullptr, nullptr, nullptr, nullptr,
+                               assign_out + r0, nullptr, unset));
+      else
+        HIPCHK(launch_finalize_assign(FinalizeArgs{c.best, nullptr, rows, assign_out + r0, nullptr, nullptr, k, unset}, st));
+      return SKM_OK;
+    };
+    if (int rc = deliver(c.flag)) return rc;
     HIPCHK(hipMemcpyAsync(&c.report->flag, c.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, st));
     if (int rc = c.wait_step()) return rc;
-    if (c.report->flag != 0) {
-      ws.finished();
-      return SKM_OK;
+    if (c.report->flag != 0) {   // (the search has left the centroids' norms and their split copy)
+      HIPCHK(launch_fill_u64(c.best, rows, ~0ull, st));
+      GemmOperands g{c.Xr, c.ldx, (int32_t)rows, c.Y, ds, k, ds};
+      g.a_absmax = c.xr_bound; g.b_absmax = c.amax + Ctx::AM_Y;
+      g.b_presplit = c.Ys; g.ldbs = split_ld(ds);
+      HIPCHK(gemm_argmin(g, c.ynorm, c.best, st));
+      if (int rc = deliver(nullptr)) return rc;
+      HIPCHK(hipStreamSynchronize(st));
     }
   }
   ws.finished();

@@ -1,5 +1,6 @@
 """The forms that a kernel takes by size, type or alignment, at the sizes where one hands over to another: each against the
 CPU oracle (fp64) or against the form next to it."""
+import ctypes
 import os
 import threading
 import zlib
@@ -618,6 +619,41 @@ def test_exact_search_that_has_nothing_to_show(skm, dg):  # noqa: F811
     X[7777] = X[0]
     Y[:] = Y[0].clone()
     assert int(skm.assign_exact(X, Y)[0].abs().max()) == 0
+
+
+# A row that is no number sends its own batch to the product of all pairs, not the others: rows half way between two centroids,
+# whose nearest one is a matter of rounding, have the labels and distances that they have without it.
+@pytest.mark.parametrize("with_dist", [True, False])
+def test_exact_search_with_one_batch_that_fails(skm, with_dist):  # noqa: F811
+    n, d, k = (1 << 18) + 1000, 144, 2048
+    say("exact search, one batch fails", n, d, k, with_dist)
+    g = torch.Generator("cuda").manual_seed(5)
+    Y = torch.nn.functional.normalize(torch.randn(k, d, generator=g, device="cuda"), dim=1)
+    near = torch.cdist(Y, Y).fill_diagonal_(9.0).argmin(1)
+    a = torch.randint(0, k, (n,), generator=g, device="cuda")
+    X = 0.5 * (Y[a] + Y[near[a]])
+
+    def run(x):
+        if with_dist:
+            return skm.assign_exact(x, Y)
+        labels = torch.empty(len(x), dtype=torch.int32, device="cuda")
+        st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert skm.lib().skm_assign_exact(ctypes.c_void_p(x.data_ptr()), len(x), d, ctypes.c_void_p(Y.data_ptr()), k, st,
+                                          ctypes.c_void_p(labels.data_ptr()), None) == 0
+        return labels, None
+
+    want, dist = run(X)
+    few = run(X[:50_000])[0]                              # (too few rows for the search)
+    assert not torch.equal(few, want[:50_000])            # (the rows do tell the two forms apart)
+    X[n - 5] = float("nan")
+    got, dist_got = run(X)
+    first = slice(0, 1 << 18)
+    assert torch.equal(got[first], want[first]) and (not with_dist or torch.equal(dist_got[first], dist[first]))
+    rest = torch.arange(1 << 18, n, device="cuda")
+    rest = rest[rest != n - 5]
+    own = lambda l: ((X[rest].double() - Y.double()[l[rest].long()]) ** 2).sum(1)  # noqa: E731
+    # split products and norms of 1: 2^-20 of a distance either way
+    assert int(got[n - 5]) == 0 and bool(((own(got) - own(want)).abs() <= 2.0 ** -18).all())
 
 
 # A step after one that cut a third to a half of the pairs lists every column without asking the filter, and multiplies in one
