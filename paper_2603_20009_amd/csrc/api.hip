@@ -2436,27 +2436,54 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
 }
 
 // The exact assignment through the one-product search of iteration 1 (a third of the matrix work of the three-product argmin;
-// the candidates' distances are the direct ones), 2^18 rows at a time.  A batch with a candidate list that ran over or a row that
-// no centroid was offered to (one that is no number) takes the product of all pairs, in the same buffers: nothing is allocated
-// behind the first label that is written.  done = false: no room for the buffers, and the caller takes the other form.
-constexpr int64_t kExactRows = (int64_t)1 << 18;
+// the candidates' distances are the direct ones), a batch of rows at a time.  A batch with a candidate list that ran over or a
+// row that no centroid was offered to (one that is no number) takes the product of all pairs, in the same buffers: nothing is
+// allocated behind the first label that is written.  done = false: no room for the buffers, and the caller takes the other form.
+// Up to 2^18 rows to a batch, fewer where the call's block (6.25 d + 2.3 K bytes a row, 10.25 d with a padded copy, 18 d a centroid)
+// would pass half of what the library keeps between calls: a block that it does not keep costs 25 ms a GB once it is freed
+// (262 144 x 3072, k = 2048 in one batch 166 ms, in four 8.9, three products 10.4).  Where the centroids alone are too much for that
+// the search has to save twice as much as the block costs (3 ns for 10^6 multiply-adds: 20 000 x 1024, k = 400 000 220 ms, three
+// products 48).
+constexpr int64_t kExactRows = (int64_t)1 << 18, kExactLeast = (int64_t)1 << 14;
+struct ExactPlan {
+  int64_t rows = 0;   // 0: not this way
+  size_t bytes = 0;
+};
+ExactPlan exact_plan(int64_t n, int32_t d, int32_t k, bool pad) {
+  auto bytes = [&](int64_t rows) -> size_t {
+    const size_t plan = plan_common_bytes(rows, d, k, 0, 0.f, false);
+    return plan ? plan + (pad ? (size_t)rows * round_up(d, 16) * 4 : 0) + ((size_t)1 << 20) : 0;
+  };
+  ExactPlan p;
+  const size_t fixed = bytes(1);
+  if (!fixed) return p;
+  for (p.rows = std::min<int64_t>(n, kExactRows);; p.rows = (p.rows / 2 + 127) / 128 * 128) {
+    p.bytes = bytes(p.rows);
+    if (!p.bytes) return ExactPlan();
+    if (p.rows <= kExactLeast || p.bytes <= BlockCache::kMost / 2 || p.bytes - fixed <= BlockCache::kMost / 4) break;
+  }
+  if (p.bytes > BlockCache::kMost && (double)n * d * k < 2e4 * (double)p.bytes) return ExactPlan();
+  return p;
+}
 // From 2048 centroids on, for rows that the argmin with the rows in registers does not take, and from 2^34 multiply-adds on (the
 // search is a dozen launches more).  Three products -> search: 16 384 x 256, k = 4096 178 -> 173 us, 8000 x 384, k = 8000 228 -> 204,
 // 100 000 x 384, k = 2048 565 -> 493, 700 001 x 300, k = 5000 8.7 -> 4.9 ms, 400 000 x 768, k = 8000 14.8 -> 7.1; but 60 000 x 192, k = 1536
-// 200 -> 214 us, 300 000 x 160, k = 1300 685 -> 702, 200 000 x 96, k = 2000 310 -> 435.  Labels unlike those of fp64: 2 of 100 000 -> 0,
-// 3 of 60 000 (k = 4000) -> 1.
+// 200 -> 214 us, 300 000 x 160, k = 1300 685 -> 702, 200 000 x 96, k = 2000 310 -> 435.  A row's tables are written for every call, and
+// take as long as a few thousand centroids (more beyond 2048 dimensions, where they are written point by point): 20 000 x 8192, k = 2048
+// 2.41 -> 2.27 ms, 20 000 x 10 001 4.35 -> 3.88, 40 000 x 16 384, k = 4096 15.9 -> 15.0; but 40 000 x 12 288, k = 2048 6.41 -> 6.60, 40 000 x
+// 16 384 8.6 -> 11.2.  Labels unlike those of fp64: 2 of 100 000 -> 0, 3 of 60 000 (k = 4000) -> 1.
 bool exact_filter_pays(int64_t n, int32_t d, int32_t k) {
-  return k >= 2048 && d > 128 && (double)n * d * k >= 17179869184.0;
+  return k >= 2048 && d > 128 && d <= 5 * k && (double)n * d * k >= 17179869184.0;
 }
 int exact_through_filter(const float *X, int64_t n, int32_t d, const float *centroids, int32_t k, hipStream_t st,
                          int32_t *assign_out, float *dist_out, bool &done) {
   done = false;
-  const int64_t W = std::min<int64_t>(n, kExactRows);
   const int32_t ds = round_up(d, 16);
   const bool pad = d != ds || !aligned16(X);
-  const size_t plan = plan_common_bytes(W, d, k, 0, 0.f, false);
-  if (!plan) return SKM_OK;
-  CallArena ws(plan + (pad ? (size_t)W * ds * 4 : 0) + ((size_t)1 << 20));
+  const ExactPlan plan = exact_plan(n, d, k, pad);
+  const int64_t W = plan.rows;
+  if (!W) return SKM_OK;
+  CallArena ws(plan.bytes);
   Ctx c;
   c.st = st;
   c.n = W; c.d = d; c.k = k; c.ds = ds;

@@ -621,6 +621,28 @@ def test_exact_search_that_has_nothing_to_show(skm, dg):  # noqa: F811
     assert int(skm.assign_exact(X, Y)[0].abs().max()) == 0
 
 
+# Rows to a batch of the search follow from the bytes of its buffers: long rows go in several batches, whose block is one that the
+# library keeps for the next call.
+@pytest.mark.parametrize("n,d,k", [(262_200, 1401, 2048), (140_000, 2112, 2050)])
+def test_exact_search_in_batches_of_long_rows(skm, dg, n, d, k):  # noqa: F811
+    say("exact search, long rows", n, d, k)
+    X, Y = dg.mixture(n, d, 2 * k, 5, "embed", "cuda"), dg.mixture(k, d, 2 * k, 5, "embed", "cuda", sample_seed=3)
+    skm.release_memory()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    a, dist = skm.assign_exact(X, Y)
+    assert (1 << 30) < before - torch.cuda.mem_get_info()[0] < (1 << 31) + (1 << 25)     # (labels and distances: 2 MB)
+    Yd = Y.double()
+    y2 = (Yd * Yd).sum(1)
+    for r in range(0, n, 16_384):
+        x = X[r:r + 16_384].double()
+        D = (x * x).sum(1, keepdim=True) - 2 * x @ Yd.T + y2
+        own = ((x - Yd[a[r:r + 16_384].long()]) ** 2).sum(1)
+        # fp32 sums of d squares: d 2^-24 of the sum (and 2^-45 for the fp64 form of the matrix D, norms of 1)
+        assert (own <= D.min(1).values * (1 + 2 * d * 2.0 ** -24) + 2.0 ** -45).all()
+        assert ((dist[r:r + 16_384].double() - own).abs() <= 2 * d * 2.0 ** -24 * own + 1e-12).all()
+
+
 # A row that is no number sends its own batch to the product of all pairs, not the others: rows half way between two centroids,
 # whose nearest one is a matter of rounding, have the labels and distances that they have without it.
 @pytest.mark.parametrize("with_dist", [True, False])
