@@ -1682,7 +1682,7 @@ int ground_truth_keys(Pool &pool, const float *X, int64_t n, int32_t d, const fl
 // 1M x 768, k = 3000 21.3 -> 12.1 ms, k = 2048 16.2 -> 11.4 (without incumbents 18.8 -> 14.4), 1.4M x 384, k = 2100 15.0 -> 8.0, 2.5M x 128,
 // k = 3500 12.4 -> 8.4 (16.5 -> 15.5), 600 000 x 1200, k = 2048 18.4 -> 13.9; but 1M x 768, k = 1024 10.8 -> 10.5 (11.7 -> 12.0), 1M x 1536,
 // k = 512 23.3 -> 25.5, 200 000 x 256, k = 2048 1.16 -> 1.05 (1.50 -> 2.01), 50 000 x 768, k = 2048 0.95 -> 1.03.  (Up to 2^33
-// values: the regrouped copy must not refuse a call for memory that was served without it.)
+// values, and where there is memory for the regrouped copy: the call is served without it otherwise.)
 inline bool assign_groups_always(int32_t k) { return k >= 4096; }
 inline bool assign_groups(int64_t n, int32_t ds, int32_t k, int32_t screen_mode) {
   if (screen_mode < 0 || n < 8 * (int64_t)k || ds > 2048 || n >= ((int64_t)1 << 31)) return false;
@@ -2390,17 +2390,28 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   // grouped by their incumbents and the first filter runs in front of the exact kernel (a million tiles of two slabs
   // each otherwise: the fixed costs of a tile, not the arithmetic, are then the whole run time).
   if (assign_groups(n, c.ds, k, p.screen) && c.colmask) {
-    HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
-    HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
-    HIPCHK(c.pool.get(&c.subkey, (size_t)n));
-    HIPCHK(c.pool.get(&c.up.off, (size_t)k + 1));
-    HIPCHK(c.pool.get(&c.up.cursor, (size_t)k));
-    HIPCHK(c.pool.get(&c.up.segoff, (size_t)k + 1));
-    HIPCHK(c.pool.get(&c.up.order, (size_t)n));
-    HIPCHK(c.pool.get(&c.grp_cnt, (size_t)k + 1));
-    HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
-    c.group_now = true;
-    c.last_prune_frac = 1.0;   // the filter runs: with points grouped and thousands of centroids it has columns to drop
+    auto room = [&]() -> int {
+      HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
+      HIPCHK(c.pool.get(&c.subkey, (size_t)n));
+      HIPCHK(c.pool.get(&c.up.off, (size_t)k + 1));
+      HIPCHK(c.pool.get(&c.up.cursor, (size_t)k));
+      HIPCHK(c.pool.get(&c.up.segoff, (size_t)k + 1));
+      HIPCHK(c.pool.get(&c.up.order, (size_t)n));
+      HIPCHK(c.pool.get(&c.grp_cnt, (size_t)k + 1));
+      HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
+      HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
+      return SKM_OK;
+    };
+    rc = room();
+    if (rc == SKM_OK) {
+      c.group_now = true;
+      c.last_prune_frac = 1.0;   // the filter runs: with points grouped and thousands of centroids it has columns to drop
+    } else if (rc != SKM_ENOMEM || assign_groups_always(k)) {
+      return rc;
+    } else {   // no memory for what such a step may do without: the points stay as they are
+      (void)hipGetLastError();
+      c.Xr2 = nullptr;
+    }
   }
   const int32_t dprime = dprime_in > 0 ? snap16((double)dprime_in, d) : dprime_init(d, p.dprime_frac);
   StepStats ss;

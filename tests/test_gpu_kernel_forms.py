@@ -768,3 +768,26 @@ def test_order_of_thresholds_with_fewer_centroids(skm, dg, tail):  # noqa: F811
     assert abs(ra["survivors"] - rc["survivors"]) <= 1e-5 * max(rc["survivors"], n)
     bound = 2.0 ** -19 * (X.norm(dim=1).max() + Y.norm(dim=1).max()) ** 2     # as above
     assert int((a != c).sum()) <= 1e-3 * n and float((da - dc).abs().max()) <= 2 * float(bound)
+
+
+# ... and where there is no memory for the regrouped copy the step is served without it.
+def test_fewer_centroids_without_memory_for_the_order(skm, dg):  # noqa: F811
+    n, d, k = 1_050_000, 512, 2052
+    say("fewer centroids, a full device", n, d, k)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Y = dg.mixture(k, d, 64, 3, "embed", "cuda")
+    prev = torch.randint(0, k, (n,), generator=g, device="cuda").int()
+    X = Y[prev.long()] + 0.02 * torch.randn(n, d, generator=g, device="cuda")
+    prev = torch.where(torch.rand(n, generator=g, device="cuda") < 0.02, torch.randint(0, k, (n,), generator=g, device="cuda").int(), prev)
+    opts = skm.FitOptions(R=skm.make_rotation(d, 4), own_workspace=True)
+    a, da, ra = skm.assign(X, Y, prev, opts=opts)
+    skm.release_memory()
+    # a call's memory but for half of the copy (a fit's is a few ten MB more)
+    held = fill_device(skm.workspace_bytes(n, d, k) - n * d * 2)
+    c, dc, rc = skm.assign(X, Y, prev, opts=opts)
+    del held
+    torch.cuda.empty_cache()
+    assert ra["listed_tiles"] > 0 and rc["listed_tiles"] == 0
+    assert abs(ra["survivors"] - rc["survivors"]) <= 1e-5 * max(rc["survivors"], n)
+    bound = 2.0 ** -19 * (X.norm(dim=1).max() + Y.norm(dim=1).max()) ** 2     # as above
+    assert int((a != c).sum()) <= 1e-3 * n and float((da - dc).abs().max()) <= 2 * float(bound)
