@@ -2033,22 +2033,26 @@ struct KeptRows {
     const size_t row = (size_t)ds * 4, more = (size_t)split_ld(ds) * 4 + (size_t)ds / 4 + (hi ? (size_t)split_ld(ds) * 2 : 0);
     const size_t fixed = (size_t)nbatch * 4 + 5 * 256 + (size_t)split_ld(ds) * 6;   // (an odd row more in the copies)
     if (budget <= fixed) return;
-    // the tables of all rows, or the rows alone, as many whole batches as there is room for
-    const bool with = (size_t)n * (row + more) + fixed <= budget;
-    const int64_t kept = with ? nbatch : std::min<int64_t>(nbatch, (int64_t)((budget - fixed) / ((size_t)W * row)));
-    if (kept < 1) return;
-    const int64_t r = std::min<int64_t>(n, kept * W);
-    const size_t bytes = ((size_t)r * (row + (with ? more : 0)) + fixed + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
-    block = static_cast<char *>(block_cache().take(bytes, &cap));
-    if (!block) {
+    // the tables of all rows, or the rows alone, as many whole batches as there is room for (for what cannot be had in one piece,
+    // idle blocks of the library go back first; then less is asked for)
+    bool with = (size_t)n * (row + more) + fixed <= budget;
+    int64_t kept = with ? nbatch : std::min<int64_t>(nbatch, (int64_t)((budget - fixed) / ((size_t)W * row))), r = 0;
+    while (kept >= 1) {
+      r = std::min<int64_t>(n, kept * W);
+      const size_t bytes = ((size_t)r * (row + (with ? more : 0)) + fixed + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
+      block = static_cast<char *>(block_cache().take(bytes, &cap));
+      if (block) break;
       void *p = nullptr;
-      if (hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
+      if (device_malloc(&p, bytes) == hipSuccess) {
+        block = static_cast<char *>(p);
+        cap = bytes;
+        break;
       }
-      block = static_cast<char *>(p);
-      cap = bytes;
+      (void)hipGetLastError();
+      if (with) with = false;
+      else kept /= 2;
     }
+    if (!block) return;
     size_t at = 0;
     auto carve = [&](size_t want) {
       char *p = block + at;

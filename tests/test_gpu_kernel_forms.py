@@ -380,6 +380,38 @@ def test_host_resident_fit_keeps_what_fits(skm, dg, n, d, k, room):  # noqa: F81
     assert [r["survivors"] for r in sent.trace] == [r["survivors"] for r in kept.trace]
 
 
+# The room that is planned counts the blocks that the library keeps idle: where none of them is large enough and the device is full
+# otherwise, they go back for it.
+def test_host_resident_fit_takes_the_idle_blocks(skm, dg):  # noqa: F811
+    n, d, k = 600_000, 256, 30
+    say("kept rows from idle blocks", n, d, k)
+    X = dg.mixture(n, d, 60, 3, "embed", "cuda")
+    R = skm.make_rotation(d, 2)
+    Xh = X.cpu()
+    sent = skm.fit_host(Xh, k, 3, 5, batch_rows=131_072, opts=skm.FitOptions(R=R))
+    torch.cuda.synchronize()
+    skm.release_memory()
+    blocks, labels = [], torch.arange(n, device="cuda", dtype=torch.int32)
+    for many in (560_000, 580_000, 600_000):             # (updates of so many means: each a little too large for the block before)
+        Y = X[:many].clone()
+        torch.cuda.empty_cache()
+        before = torch.cuda.mem_get_info()[0]
+        skm.update(X, labels % many, Y)
+        torch.cuda.empty_cache()
+        blocks.append(before - torch.cuda.mem_get_info()[0])
+    del X, Y, labels
+    tables = n * 9 * d                                   # rows, split copies, prefix norms: 8.25 bytes a value and 128 a row
+    assert min(blocks) > 1 << 30 and max(blocks) < tables and sum(blocks) < 4 << 30
+    held = fill_device(tables // 2)
+    before = torch.cuda.mem_get_info()[0]
+    kept = skm.fit_host(Xh, k, 3, 5, opts=skm.FitOptions(R=R))
+    after = torch.cuda.mem_get_info()[0]
+    del held
+    torch.cuda.empty_cache()
+    assert after - before > 1 << 28                      # (idle blocks have gone, for less than they held)
+    assert torch.equal(sent.assign, kept.assign) and torch.equal(sent.dist, kept.dist) and torch.equal(sent.centroids, kept.centroids)
+
+
 # Iteration 1 goes through the one-product filter from 2048 clusters on, through the product of all pairs otherwise: the labels of
 # a fit of one iteration on both sides of the line.
 @pytest.mark.parametrize("n,k", [(16_383, 512), (16_384, 511), (16_384, 512), (16_500, 513), (4096, 2047), (4096, 2048)])
