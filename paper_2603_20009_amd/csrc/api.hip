@@ -1090,13 +1090,17 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   // Behind the first test of a listed tile one product and widened tests will do where the gather kernel finishes what is
   // left (not where every test's count is asked for, nor with a hand-over share beyond an eighth).
   const bool deep = nb >= 3 && !c.block_stats && c.emit_max > 0 && c.emit_max <= (unsigned int)progressive_tile_pairs() / 8;
-  // A step after one that cut a third to a half of the pairs cuts 80 to 85 % of them, spread over nearly all columns: there is
+  // A step after one that cut a third to a half of the pairs cuts 70 to 95 % of them, spread over nearly all columns: there is
   // nothing for the filter to drop, but the tiles are through with their first test after an eighth of the dimensions and
   // multiply the rest in one product, so all columns are listed as they are.  Tiles and gather of the third step of a fit, dense ->
   // listed (behind the filter): 1M x 1536, k = 1024 7.80 -> 6.51 (6.68) ms, k = 4096 36.1 -> 28.2 (28.8), 600 000 x 1280, k = 2000 10.0 ->
-  // 9.4 (9.8), 200 000 x 1536, k = 300 779 -> 746 (788) us.  After a step that cut 32 % one that cut 74 %, a quarter of the tiles done
-  // twice: 100 000 x 896, k = 600 469 -> 569 us.
-  const bool list_all = deep && c.screen_mode == 0 && c.last_prune_frac >= 0.33 && c.last_prune_frac < 0.50;
+  // 9.4 (9.8).  Where the lines lie (that step of 196 mixtures of 45 000 to 920 000 rows, 448 to 2040 dimensions, 256 to 4000 clusters):
+  // behind a step that cut less than a third, from 1.39 times as fast to 0.63; with fewer than some 1200 tiles 1.16 to 0.94 (with 350
+  // to 700 down to 0.77); where the last test but the one of the whole row comes before 95 % of it (a quarter of the tiles then
+  // has too many pairs left and is done twice) 1.22 to 0.74; the 112 others 1.60 to 0.89, 110 of them 0.96 and more.
+  const bool list_all = deep && c.screen_mode == 0 && c.last_prune_frac >= 0.33 && c.last_prune_frac < 0.50 &&
+                        (double)(dprime + kBlockDims * (nb - 1)) >= 0.95 * c.d &&
+                        ((c.n + 127) / 128) * (int64_t)((c.k + kListCols - 1) / kListCols) >= 1200;
   bool screen = c.colmask && nb > 0 &&
                 (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
   // theta ratio at checkpoint m: t_m = min(d, d' + 64 m) dimensions seen

@@ -711,21 +711,23 @@ def test_exact_search_with_one_batch_that_fails(skm, with_dist):  # noqa: F811
 
 
 # A step after one that cut a third to a half of the pairs lists every column without asking the filter, and multiplies in one
-# product behind the first test.  Counts and labels are those of the dense tiles.
-@pytest.mark.parametrize("n,d,k,components", [(40_001, 1536, 300, 1200), (30_000, 1500, 515, 2000), (60_000, 1024, 257, 1000)])
-def test_every_column_listed(skm, dg, n, d, k, components):  # noqa: F811
+# product behind the first test: with 1200 tiles or more, and a test behind 95 % of the row.  Counts and labels are those of the
+# dense tiles.
+@pytest.mark.parametrize("n,d,k,components,recipe,lists", [(144_442, 1536, 1198, 3594, "embed", True), (72_645, 1024, 714, 2856, "embed", True),
+                                                           (98_724, 768, 2009, 8036, "embed", True), (45_553, 768, 433, 1515, "embed", False),
+                                                           (57_350, 1216, 1561, 4683, "linear", False)])
+def test_every_column_listed(skm, dg, n, d, k, components, recipe, lists):  # noqa: F811
     say("every column", n, d, k, components)
-    X = dg.mixture(n, d, components, 5, "embed").cuda()
+    X = dg.mixture(n, d, components, 3, recipe, "cuda")
     R = skm.make_rotation(d, 2)
     fit, dense = (skm.fit(X, k, 3, 5, skm.FitOptions(R=R, screen=s)) for s in (0, -1))
     frac = [row["prune_frac"] for row in fit.trace]
     steps = [t for t in range(2, len(frac)) if 0.33 <= frac[t - 1] < 0.5]
     say("every column: pairs cut", frac)
-    if (n, d) == (40_001, 1536):
-        assert steps
+    assert steps
     for t in steps:
         full, rest = divmod(k, 256)
-        assert fit.trace[t]["listed_tiles"] == -(-n // 128) * (2 * full + (rest > 0) + (rest > 128)) and dense.trace[t]["listed_tiles"] == 0
+        assert fit.trace[t]["listed_tiles"] == lists * -(-n // 128) * (2 * full + (rest > 0) + (rest > 128)) and dense.trace[t]["listed_tiles"] == 0
     for a, b in zip(fit.trace, dense.trace):   # (a near-tie that falls the other way moves a point)
         assert abs(a["survivors"] - b["survivors"]) <= 1e-4 * max(b["survivors"], n) and abs(a["completed"] - b["completed"]) <= 2 + 1e-3 * b["completed"]
     assert int((fit.assign != dense.assign).sum()) <= 2e-4 * n
