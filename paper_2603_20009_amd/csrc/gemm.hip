@@ -917,7 +917,7 @@ static hipError_t launch_any(const GemmOperands &g, const typename EpiArgs<EPI>:
   if constexpr (EPI == EPI_ARGMIN) {
     if (wants_rows(g)) {
       switch ((g.K + 15) / 16) {
-        case 2: return big ? launch_rows<2, false>(g, e, st) : launch_rows<2, true>(g, e, st);
+        case 2: return launch_rows<2, true>(g, e, st);   // (K <= 32: never the 256 x 256 form's)
         case 3: return launch_rows<3, true>(g, e, st);   // (an odd number of granules: the same order either way)
         case 4: return big ? launch_rows<4, false>(g, e, st) : launch_rows<4, true>(g, e, st);
         case 5: return launch_rows<5, true>(g, e, st);

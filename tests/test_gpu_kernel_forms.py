@@ -498,6 +498,22 @@ def test_exact_assignment_with_rows_in_registers(skm, orc, dg, n, d, k):  # noqa
     assert torch.equal(a[part], b[:-1]) and torch.equal(dist[part], dist_b[:-1])
 
 
+# ... and in the order of the 256 x 256 tiles where the product would take those (whole slabs of 32 dimensions, 512 tiles).
+@pytest.mark.parametrize("n,d,k", [(140_000, 64, 450), (70_000, 96, 768), (80_001, 128, 500)])
+def test_rows_in_registers_in_the_order_of_wide_tiles(skm, dg, n, d, k):  # noqa: F811
+    say("rows in registers, wide tiles", n, d, k)
+    X, Y = dg.mixture(n, d, 300, 5, "embed", "cuda"), dg.mixture(k, d, 300, 5, "embed", "cuda", sample_seed=3)
+    X[: k] = 0.5 * (Y + Y.roll(1, 0))                                 # (rows for which the order decides)
+    a, dist = skm.assign_exact(X, Y)
+    few = torch.cat([X[:3000], torch.full((1, d), float(X.abs().max()), device="cuda")])     # (the same bound: the same halves)
+    skm.debug_gemm_config(tile256=1)
+    try:
+        b, dist_b = skm.assign_exact(few, Y)
+    finally:
+        skm.debug_gemm_config()
+    assert torch.equal(a[:3000], b[:-1]) and torch.equal(dist[:3000], dist_b[:-1])
+
+
 def test_rows_in_registers_that_are_no_numbers(skm, dg):  # noqa: F811
     say("rows in registers, nan and inf")
     n, d, k = 70_000, 64, 300
