@@ -445,6 +445,20 @@ def test_near_ties_of_iteration_one(skm, n, d, k):  # noqa: F811
     assert not torch.equal(forced.assign, without.assign)           # (the rows do tell the two forms apart)
 
 
+# A row that is no number gets a label like any other, on either side of the lines at which iteration 1 might change its form.
+@pytest.mark.parametrize("n,k", [(16_400, 511), (16_400, 512), (20_000, 2047)])
+def test_iteration_one_with_a_row_that_is_no_number(skm, dg, n, k):  # noqa: F811
+    say("iteration 1, nan", n, k)
+    d = 96
+    X = dg.mixture(n, d, 300, 8, "embed", "cuda")
+    opts = skm.FitOptions(R=skm.make_rotation(d, 3), init_idx=range(k), final_assign=False)
+    want = skm.fit(X, k, 1, 1, opts)
+    X[n - 7] = float("nan")
+    got = skm.fit(X, k, 1, 1, opts)
+    keep = torch.arange(n, device="cuda") != n - 7
+    assert torch.equal(got.assign[keep], want.assign[keep]) and 0 <= int(got.assign[n - 7]) < k
+
+
 def fill_device(leave):
     """Tensors that take the device's memory but for `leave` bytes (and what torch keeps)."""
     torch.cuda.empty_cache()
