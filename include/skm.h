@@ -220,7 +220,8 @@ int skm_fit_ex(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, u
  *                   and rows that fit stay on the device.
  *                   Device memory in use: about 3 * batch_rows * d * 4 bytes for the
  *                   batches plus 8 (12 with dist_out_host) bytes per point; with 0
- *                   and the rows that stay, up to 11 bytes per value more.
+ *                   and the rows that stay, 4 bytes per value more (up to 11 where
+ *                   that is at most 4 GiB).
  *   centroids_out   DEVICE k x d fp32, original space
  *   assign_out_host HOST n int32 or NULL; dist_out_host HOST n fp32 or NULL
  *   params->R, if set, is a DEVICE pointer as elsewhere; params->init_idx a host

@@ -2008,7 +2008,11 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
 // its own beside the workspace.  A pass over kept rows costs its kernels, one over streamed rows the transfer (17 ms per GB,
 // ten times as much): 200 000 x 768 with k = 1024, four passes, 45.6 ms when all of them were sent every time, now 17.0.
 // At most half of what is free is taken, and only where the caller left the batch size, and with it the memory in use, to
-// the library; a block that cannot be had means that everything is streamed.
+// the library; a block that cannot be had means that everything is streamed.  Tables stay with the rows only in a block that
+// is kept between calls: freed memory is cleared by the engine that copies from the host, which then runs at 44 instead of 58
+// GB/s, some 0.25 s behind rows of 6 GB, 0.7 s behind rows and tables of 16.  1M x 1536, k = 1024, ten iterations one call after
+// the other 226 ms with tables, 238 without (195 and 213 after a pause); four fits of two streamed passes behind them 1152 and 949
+// ms (880 otherwise).
 struct KeptRows {
   int64_t batches = 0, rows = 0;
   bool tables = false;              // the split copies and prefix norms stay, too
@@ -2039,7 +2043,7 @@ struct KeptRows {
     if (budget <= fixed) return;
     // the tables of all rows, or the rows alone, as many whole batches as there is room for (for what cannot be had in one piece,
     // idle blocks of the library go back first; then less is asked for)
-    bool with = (size_t)n * (row + more) + fixed <= budget;
+    bool with = (size_t)n * (row + more) + fixed <= std::min(budget, BlockCache::kMost);
     int64_t kept = with ? nbatch : std::min<int64_t>(nbatch, (int64_t)((budget - fixed) / ((size_t)W * row))), r = 0;
     while (kept >= 1) {
       r = std::min<int64_t>(n, kept * W);

@@ -380,6 +380,25 @@ def test_host_resident_fit_keeps_what_fits(skm, dg, n, d, k, room):  # noqa: F81
     assert [r["survivors"] for r in sent.trace] == [r["survivors"] for r in kept.trace]
 
 
+# Tables stay with the rows only in a block that the library keeps between calls; here rows alone are such a block.
+def test_host_resident_fit_keeps_rows_without_tables(skm, dg):  # noqa: F811
+    n, d, k = 1_700_000, 256, 300
+    say("kept rows without tables", n, d, k)
+    Xh = dg.mixture(n, d, 60, 3, "embed", "cuda").cpu()
+    assert n * 10 * d > 1 << 32 > n * 6 * d              # (with tables 10 bytes a value and more)
+    R = skm.make_rotation(d, 2)
+    used, fits = [], []
+    for batch_rows in (131_072, 0):
+        skm.release_memory()
+        torch.cuda.empty_cache()
+        before = torch.cuda.mem_get_info()[0]
+        fits.append(skm.fit_host(Xh, k, 2, 5, batch_rows=batch_rows, opts=skm.FitOptions(R=R)))
+        used.append(before - torch.cuda.mem_get_info()[0])
+    assert abs(used[1] - used[0] - n * d * 4) < 1 << 26     # (a process keeps some more of its first calls)
+    sent, kept = fits
+    assert torch.equal(sent.assign, kept.assign) and torch.equal(sent.dist, kept.dist) and torch.equal(sent.centroids, kept.centroids)
+
+
 # The room that is planned counts the blocks that the library keeps idle: where none of them is large enough and the device is full
 # otherwise, they go back for it.
 def test_host_resident_fit_takes_the_idle_blocks(skm, dg):  # noqa: F811
