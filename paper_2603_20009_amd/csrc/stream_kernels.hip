@@ -1476,11 +1476,33 @@ static void launch_sort_segments(const int32_t *off, int32_t *order, int32_t k, 
   if (most > RANK_CAP) hipLaunchKernelGGL(sort_segments_kernel, dim3(k), dim3(256), 0, st, off, order);
 }
 
+// a lane's four dimensions of a row; ALIGNED: rows are 16-byte aligned and a multiple of 4 long; otherwise one by one
+template <bool ALIGNED>
+__device__ inline void load_row4(const float *row, int32_t ds, int col, float4 &v) {
+  const float *x = row + col;
+  if (ALIGNED) {
+    v = *reinterpret_cast<const float4 *>(x);
+  } else {
+    v.x = x[0];
+    v.y = col + 1 < ds ? x[1] : 0.f;
+    v.z = col + 2 < ds ? x[2] : 0.f;
+    v.w = col + 3 < ds ? x[3] : 0.f;
+  }
+}
+// SIGNED: an entry i >= 0 adds row i, an entry ~i < 0 subtracts row i
+template <bool SIGNED>
+__device__ inline void add_row(const float4 &f, int id, double &a0, double &a1, double &a2, double &a3) {
+  if (SIGNED) {
+    const double sg = id < 0 ? -1.0 : 1.0;
+    a0 += sg * (double)f.x; a1 += sg * (double)f.y; a2 += sg * (double)f.z; a3 += sg * (double)f.w;
+  } else {
+    a0 += (double)f.x; a1 += (double)f.y; a2 += (double)f.z; a3 += (double)f.w;
+  }
+}
+
 // Sum of rows in a fixed order, for a lane's four dimensions: entries first, first + STEP, ... of s_ids[0 .. count),
 // ROWS of them requested while the ROWS before are added (a row is a round trip to memory: 30 us for a segment of 512 rows
 // with four in flight behind the loads of their numbers, 23 with twice eight; the whole update of 1M x 768 680 -> 669).
-// SIGNED: an entry i >= 0 adds row i, an entry ~i < 0 subtracts row i.
-// ALIGNED: rows are 16-byte aligned and a multiple of 4 long; otherwise a lane reads its four values one by one.
 template <bool SIGNED, bool ALIGNED, int STEP>
 __device__ inline void add_rows(const float *Xr, int64_t ldx, int32_t ds, int col, const int *s_ids, int count, int first,
                                 double &a0, double &a1, double &a2, double &a3) {
@@ -1492,29 +1514,13 @@ __device__ inline void add_rows(const float *Xr, int64_t ldx, int32_t ds, int co
     for (int u = 0; u < ROWS; ++u) {
       const int raw = __builtin_amdgcn_readfirstlane(s_ids[min(p + STEP * u, count - 1)]);   // (past the end: the last one again)
       ids[u] = raw;
-      const float *x = Xr + (int64_t)(SIGNED && raw < 0 ? ~raw : raw) * ldx + col;
-      if (ALIGNED) {
-        to[u] = *reinterpret_cast<const float4 *>(x);
-      } else {
-        to[u].x = x[0];
-        to[u].y = col + 1 < ds ? x[1] : 0.f;
-        to[u].z = col + 2 < ds ? x[2] : 0.f;
-        to[u].w = col + 3 < ds ? x[3] : 0.f;
-      }
+      load_row4<ALIGNED>(Xr + (int64_t)(SIGNED && raw < 0 ? ~raw : raw) * ldx, ds, col, to[u]);
     }
   };
   auto add = [&](int p, const float4 (&from)[ROWS], const int (&ids)[ROWS]) {
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
-      if (p + STEP * u < count) {
-        const float4 f = from[u];
-        if (SIGNED) {
-          const double sg = ids[u] < 0 ? -1.0 : 1.0;
-          a0 += sg * (double)f.x; a1 += sg * (double)f.y; a2 += sg * (double)f.z; a3 += sg * (double)f.w;
-        } else {
-          a0 += (double)f.x; a1 += (double)f.y; a2 += (double)f.z; a3 += (double)f.w;
-        }
-      }
+      if (p + STEP * u < count) add_row<SIGNED>(from[u], ids[u], a0, a1, a2, a3);
   };
   constexpr int BATCH = STEP * ROWS;
   if (first >= count) return;
@@ -1527,16 +1533,40 @@ __device__ inline void add_rows(const float *Xr, int64_t ldx, int32_t ds, int co
   }
 }
 
+// The same for a short list in memory (entries first, first + 4, ... of ids[0 .. count)): a wavefront holds the numbers of 64
+// entries and asks for four rows at a time (with eight and their registers fewer segments are under way).
+template <bool SIGNED, bool ALIGNED>
+__device__ inline void add_few_rows(const float *Xr, int64_t ldx, int32_t ds, int col, const int32_t *ids, int count, int first,
+                                    int lane, double &a0, double &a1, double &a2, double &a3) {
+  constexpr int ROWS = 4;
+  for (int b = 0; b < count; b += 64) {
+    const int held = ids[min(b + lane, count - 1)];
+    const int end = min(count - b, 64);
+    for (int p = first; p < end; p += 4 * ROWS) {
+      float4 v[ROWS];
+      int id[ROWS];
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        id[u] = __builtin_amdgcn_readlane(held, min(p + 4 * u, end - 1));   // (past the end: the last one again)
+        load_row4<ALIGNED>(Xr + (int64_t)(SIGNED && id[u] < 0 ? ~id[u] : id[u]) * ldx, ds, col, v[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u)
+        if (p + 4 * u < end) add_row<SIGNED>(v[u], id[u], a0, a1, a2, a3);
+    }
+  }
+}
+
 // One workgroup per (segment of <= kSegPoints points of one cluster, slice of 256 dims): rows are gathered through
 // `order` (each a contiguous row read), fp64 sums per thread; the four wavefronts' sums are added in a fixed order, so the
 // result depends on the segment only.
-// SIGNED, ALIGNED: see add_rows (an entry ~i: a point that left the cluster).
-template <bool SIGNED, bool ALIGNED>
+// SIGNED, ALIGNED: see load_row4 and add_row (an entry ~i: a point that left the cluster).  SHORT: see launch_segment_sums.
+template <bool SIGNED, bool ALIGNED, bool SHORT>
 __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64_t ldx, int32_t ds, int32_t k,
                                                           const int32_t *off, const int32_t *segoff,
                                                           const int32_t *order, double *partial) {
   __shared__ double red[3][64][4];
-  __shared__ int s_ids[kSegPoints];
+  __shared__ int s_ids[SHORT ? 1 : kSegPoints];
   const int seg = blockIdx.x;
   if (seg >= segoff[k]) return;
   // cluster of this segment: last c with segoff[c] <= seg
@@ -1549,13 +1579,17 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
   const int s_in = seg - segoff[c];
   const int p0 = off[c] + s_in * kSegPoints;
   const int p1 = min(off[c + 1], p0 + kSegPoints);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = (blockIdx.y * 64 + lane) * 4;
   const bool live = col < ds;
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-  for (int t = threadIdx.x; t < p1 - p0; t += 256) s_ids[t] = order[p0 + t];
-  __syncthreads();
-  if (live) add_rows<SIGNED, ALIGNED, 4>(Xr, ldx, ds, col, s_ids, p1 - p0, w, a0, a1, a2, a3);
+  if constexpr (SHORT) {   // (lanes past the row's end hold numbers as well, and read its last four values)
+    add_few_rows<SIGNED, ALIGNED>(Xr, ldx, ds, live ? col : ALIGNED ? ds - 4 : ds - 1, order + p0, p1 - p0, w, lane, a0, a1, a2, a3);
+  } else {
+    for (int t = threadIdx.x; t < p1 - p0; t += 256) s_ids[t] = order[p0 + t];
+    __syncthreads();
+    if (live) add_rows<SIGNED, ALIGNED, 4>(Xr, ldx, ds, col, s_ids, p1 - p0, w, a0, a1, a2, a3);
+  }
   if (w > 0) {
     red[w - 1][lane][0] = a0; red[w - 1][lane][1] = a1; red[w - 1][lane][2] = a2; red[w - 1][lane][3] = a3;
   }
@@ -1567,6 +1601,22 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
     if (ALIGNED || col + 2 < ds) dst[2] = (a2 + red[0][lane][2]) + (red[1][lane][2] + red[2][lane][2]);
     if (ALIGNED || col + 3 < ds) dst[3] = (a3 + red[0][lane][3]) + (red[1][lane][3] + red[2][lane][3]);
   }
+}
+
+// (n entries of k lists.)  Segments of a few rows are many workgroups that wait for their numbers and a round trip or two: there the
+// short form, without the stop in LDS and with registers for twice as many of them.  Rows in flight -> short form, us, with 8 | 16 | 32 |
+// 64 | 128 rows on average: 8000 lists, 64 dimensions 23.2 -> 18.1 | 23.6 -> 20.0 | 27.1 -> 24.4 | 34.7 -> 34.1 | 56.7 -> 64.0; 768
+// dimensions 65.2 -> 50.7 | 91.3 -> 91.1 | 167.8 -> 168.9 | 319.8 -> 319.9; 1000 lists of 1536 17.6 -> 14.4 | 20.1 -> 19.7 | 33.4 -> 33.0 |
+// 82.3 -> 81.5 | 153.2 -> 152.1, of 64 with 256 16.3 -> 21.9.
+template <bool SIGNED>
+static void launch_segment_sums(bool aligned, int64_t n, int32_t k, unsigned segs, unsigned slices, const float *Xr, int64_t ldx,
+                                int32_t ds, const int32_t *off, const int32_t *segoff, const int32_t *order, double *partial,
+                                hipStream_t st) {
+  const bool few = n < 64 * (int64_t)k;
+  auto kern = few ? segment_sum_kernel<SIGNED, true, true> : segment_sum_kernel<SIGNED, true, false>;
+  if constexpr (!SIGNED)   // (the rows of a fit are aligned)
+    if (!aligned) kern = few ? segment_sum_kernel<false, false, true> : segment_sum_kernel<false, false, false>;
+  hipLaunchKernelGGL(kern, dim3(segs, slices), dim3(256), 0, st, Xr, ldx, ds, k, off, segoff, order, partial);
 }
 
 // One workgroup per (cluster, slice): partial sums added in segment order, divided by the size.
@@ -1826,12 +1876,7 @@ hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, co
   }
   const unsigned slices = (unsigned)((ds + 255) / 256);   // 64 lanes x 4 dims, or 256 dims, per workgroup
   const bool aligned = (reinterpret_cast<uintptr_t>(Xr) & 15u) == 0 && ldx % 4 == 0 && ds % 4 == 0;
-  if (aligned)
-    hipLaunchKernelGGL((segment_sum_kernel<false, true>), dim3((unsigned)w.max_segments, slices), dim3(256), 0, st, Xr, ldx, ds,
-                       k, w.off, w.segoff, w.order, w.partial);
-  else
-    hipLaunchKernelGGL((segment_sum_kernel<false, false>), dim3((unsigned)w.max_segments, slices), dim3(256), 0, st, Xr, ldx,
-                       ds, k, w.off, w.segoff, w.order, w.partial);
+  launch_segment_sums<false>(aligned, n, k, (unsigned)w.max_segments, slices, Xr, ldx, ds, w.off, w.segoff, w.order, w.partial, st);
   hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, w.partial, ds, w.cnt, w.segoff, Y, ldy, S,
                      accumulate, y_absmax, unsafe ? (const unsigned int *)unsafe->flag : nullptr,
                      unsafe ? unsafe->flag_host : nullptr, unsafe ? unsafe->counts_out : nullptr);
@@ -2000,8 +2045,7 @@ hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, in
                       inc.ent_id, -1, st);
   if (rc != hipSuccess) return rc;
   const int64_t segs = std::min<int64_t>(inc.max_segments, (int64_t)k + m2 / kSegPoints + 1);
-  hipLaunchKernelGGL((segment_sum_kernel<true, true>), dim3((unsigned)segs, slices), dim3(256), 0, st, Xr, ldx, ds, k, inc.off,
-                     inc.segoff, inc.order, inc.partial);
+  launch_segment_sums<true>(true, m2, k, (unsigned)segs, slices, Xr, ldx, ds, inc.off, inc.segoff, inc.order, inc.partial, st);
   hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, inc.partial, ds, w.cnt, inc.segoff, Y, ldy,
                      S, 1, y_absmax, (const unsigned int *)nullptr, (unsigned int *)nullptr, (int32_t *)nullptr);
   return hipGetLastError();

@@ -355,6 +355,43 @@ def test_incremental_update_with_many_changes_in_few_clusters(skm, dg, n, d, k):
     assert (inc.centroids - full.centroids).abs().max().item() < 1e-6 + 8.0 * (moved + 1) * k / n * float(moved > 0)
 
 
+# Sums of short lists of rows (64 on average and fewer: four rows in flight, numbers in registers) and of long ones: the same order of
+# sums, so the same bits.  Lists around the four wavefronts, their rows in flight, 64 numbers and a segment of 512 rows.
+@pytest.mark.parametrize("d,shift", [(16, 0), (100, 1), (258, 0), (771, 0), (1024, 0)])
+def test_update_with_short_lists(skm, dg, d, shift):  # noqa: F811
+    say("short lists", d, shift)
+    sizes = [0, 1, 3, 4, 5, 15, 16, 17, 31, 33, 63, 64, 65, 81, 127, 130, 511, 512, 513, 1040]
+    n, k = sum(sizes), len(sizes)
+    g = torch.Generator().manual_seed(d)
+    buf = torch.empty(n * d + 4, device="cuda")
+    X = buf[shift:shift + n * d].view(n, d)
+    X.copy_(torch.randn(n, d, generator=g))
+    labels = torch.repeat_interleave(torch.arange(k), torch.tensor(sizes))[torch.randperm(n, generator=g)].int().cuda()
+    means = []
+    for lists in (k, n // 64 + 1):                       # (the others are empty: 64 rows a list and fewer)
+        Y = torch.zeros(lists, d, device="cuda")
+        assert skm.update(X, labels, Y)[:k].tolist() == sizes
+        means.append(Y[:k])
+    assert n >= 64 * k and torch.equal(means[0], means[1])
+    want = torch.zeros(k, d, dtype=torch.float64, device="cuda").index_add_(0, labels.long(), X.double())
+    want /= torch.tensor(sizes, device="cuda").clamp_min(1)[:, None]
+    assert float((means[1].double() - want).abs().max()) <= 2.0 ** -24 * float(want.abs().max()) + 1e-12   # (fp64 sums, rounded once)
+
+
+# ... and of the rows that joined and left: few changes a cluster, and many clusters (below, one by one).
+def test_incremental_update_with_few_changes_in_many_clusters(skm, dg):  # noqa: F811
+    n, d, k = 120_000, 40, 6000
+    say("few changes", n, d, k)
+    X = dg.mixture(n, d, 3 * k, 6, "linear", "cuda")
+    R = skm.make_rotation(d, 1)
+    inc, full = (skm.fit(X, k, 6, 4, skm.FitOptions(R=R, eps0=float("inf"), full_update=f)) for f in (False, True))
+    few = [row["changed"] for row in inc.trace[1:] if 8 * row["changed"] <= n]
+    assert inc.timing["inc_updates"] > 0 and max(few) * 2 * k > 1 << 25       # (not the form for a handful of changes)
+    # fp64 sums in another order, rounded to fp32: no near-tie of these rows hangs on that, so every list is the same
+    assert torch.equal(inc.assign, full.assign)
+    assert float((inc.centroids - full.centroids).abs().max()) < 1e-6 and float((inc.dist - full.dist).abs().max()) < 1e-5
+
+
 # Rows of a host-resident fit that stay on the device between its passes: all of them with their tables, or as many whole
 # batches as half of the free memory holds; the results are those of a fit that sends every row in every pass, bit by bit.
 @pytest.mark.parametrize("n,d,k,room", [(140_000, 100, 40, "all"), (300_000, 64, 300, "all"), (280_000, 256, 30, "some")])
