@@ -187,16 +187,8 @@ __global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t
   const int lane = threadIdx.x & 63;
   float most = 0.f;
   auto load = [&](const float *x, int c) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (ALIGNED) {
-      if (c < d) v = *reinterpret_cast<const float4 *>(x + c);
-    } else {
-      if (c + 0 < d) v.x = x[c];
-      if (c + 1 < d) v.y = x[c + 1];
-      if (c + 2 < d) v.z = x[c + 2];
-      if (c + 3 < d) v.w = x[c + 3];
-    }
-    return v;
+    if (!ALIGNED) return load4_any(x + c, d - c);
+    return c < d ? *reinterpret_cast<const float4 *>(x + c) : make_float4(0.f, 0.f, 0.f, 0.f);
   };
   auto emit = [&](uint32_t *dst, int c, const float4 &v, float sc) {
     typedef float f32x2_t __attribute__((ext_vector_type(2)));

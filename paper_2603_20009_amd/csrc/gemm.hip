@@ -171,21 +171,6 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[TM][TN], const GemmOperands &
   }
 }
 
-// The first `valid` of four values at any 4-byte boundary, zeros behind them: one load unless the row ends among them (46 467 x
-// 495 by 495 x 495 with a load a value: 441 us, now 245).
-__device__ inline float4 load4_any(const float *p, int valid) {
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (valid >= 4) {
-    const f32x4_u u = *reinterpret_cast<const f32x4_u *>(p);
-    v = make_float4(u.x, u.y, u.z, u.w);
-  } else {
-    if (valid > 0) v.x = p[0];
-    if (valid > 1) v.y = p[1];
-    if (valid > 2) v.z = p[2];
-  }
-  return v;
-}
-
 template <int BK, int EPI, bool ALIGNED>
 __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
   put_stamp(g.stamp);

@@ -277,6 +277,18 @@ def test_listed_tiles_behind_one_that_was_done_again(skm, orc, dg, n, d, k, dp):
         assert abs(row["completed"] - ref.enter[-1]) <= max(2, 1e-3 * ref.enter[-1])
 
 
+# ... and through points of any length and alignment: four values a load, the last one to three of a row one by one.
+@pytest.mark.parametrize("n,d,shift", [(30_001, 97, 0), (30_000, 98, 0), (20_000, 259, 0), (30_000, 100, 1), (9000, 2050, 0)])
+def test_ground_truth_of_rows_of_any_length(skm, orc, dg, n, d, shift):  # noqa: F811
+    say("ground truth, rows of any length", n, d, shift)
+    X = dg.mixture(n, d, 300, 8, "embed").numpy()
+    Q = dg.mixture(40, d, 300, 8, "embed", sample_seed=9).numpy()
+    buf = torch.full((n * d + 4,), 3e4, device="cuda")   # (what lies beside the rows is not theirs)
+    rows = buf[shift:shift + n * d].view(n, d)
+    rows.copy_(cuda(X))
+    check_ground_truth(skm.etr_ground_truth(rows, cuda(Q), 10).cpu().numpy(), orc.ground_truth(X, Q, 10), X, Q)
+
+
 # Rows of any length and alignment: fp32 products, four values a load from any 4-byte boundary, the last ones of a row one by one
 # where the length is no multiple of four.  n, d around the tiles of 128 and the slabs of 16.
 @pytest.mark.parametrize("n,d", [(127, 61), (129, 63), (1, 65), (128, 66), (300, 67), (257, 95), (130, 97), (65, 127), (200, 129), (140, 495)])
