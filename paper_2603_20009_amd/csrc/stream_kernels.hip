@@ -1604,15 +1604,15 @@ __global__ void __launch_bounds__(256) segment_sum_kernel(const float *Xr, int64
 }
 
 // (n entries of k lists.)  Segments of a few rows are many workgroups that wait for their numbers and a round trip or two: there the
-// short form, without the stop in LDS and with registers for twice as many of them.  Rows in flight -> short form, us, with 8 | 16 | 32 |
-// 64 | 128 rows on average: 8000 lists, 64 dimensions 23.2 -> 18.1 | 23.6 -> 20.0 | 27.1 -> 24.4 | 34.7 -> 34.1 | 56.7 -> 64.0; 768
-// dimensions 65.2 -> 50.7 | 91.3 -> 91.1 | 167.8 -> 168.9 | 319.8 -> 319.9; 1000 lists of 1536 17.6 -> 14.4 | 20.1 -> 19.7 | 33.4 -> 33.0 |
-// 82.3 -> 81.5 | 153.2 -> 152.1, of 64 with 256 16.3 -> 21.9.
+// short form, without the stop in LDS and with registers for twice as many of them.  Sixteen rows in flight -> short form, us of this
+// kernel with 8 | 16 rows on average: 8000 lists of 64 dimensions 23.2 -> 18.1 | 23.6 -> 20.0, of 256 24.6 -> 19.8 | 28.0 -> 26.1, of 768
+// 65.2 -> 50.7 | 91.3 -> 91.1; whole updates with 29 rows a list (201 057 x 64) 87.0 -> 83.3; but with 43 (30 000 x 512) 55.5 -> 58.8, 40
+// (40 000 x 256) 51.9 -> 55.0, and 1000 lists of 256 rows of 64 dimensions 16.3 -> 21.9.
 template <bool SIGNED>
 static void launch_segment_sums(bool aligned, int64_t n, int32_t k, unsigned segs, unsigned slices, const float *Xr, int64_t ldx,
                                 int32_t ds, const int32_t *off, const int32_t *segoff, const int32_t *order, double *partial,
                                 hipStream_t st) {
-  const bool few = n < 64 * (int64_t)k;
+  const bool few = n < 32 * (int64_t)k;
   auto kern = few ? segment_sum_kernel<SIGNED, true, true> : segment_sum_kernel<SIGNED, true, false>;
   if constexpr (!SIGNED)   // (the rows of a fit are aligned)
     if (!aligned) kern = few ? segment_sum_kernel<false, false, true> : segment_sum_kernel<false, false, false>;

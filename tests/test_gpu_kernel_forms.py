@@ -367,7 +367,7 @@ def test_incremental_update_with_many_changes_in_few_clusters(skm, dg, n, d, k):
     assert (inc.centroids - full.centroids).abs().max().item() < 1e-6 + 8.0 * (moved + 1) * k / n * float(moved > 0)
 
 
-# Sums of short lists of rows (64 on average and fewer: four rows in flight, numbers in registers) and of long ones: the same order of
+# Sums of short lists of rows (fewer than 32 on average: four rows in flight, numbers in registers) and of long ones: the same order of
 # sums, so the same bits.  Lists around the four wavefronts, their rows in flight, 64 numbers and a segment of 512 rows.
 @pytest.mark.parametrize("d,shift", [(16, 0), (100, 1), (258, 0), (771, 0), (1024, 0)])
 def test_update_with_short_lists(skm, dg, d, shift):  # noqa: F811
@@ -380,11 +380,11 @@ def test_update_with_short_lists(skm, dg, d, shift):  # noqa: F811
     X.copy_(torch.randn(n, d, generator=g))
     labels = torch.repeat_interleave(torch.arange(k), torch.tensor(sizes))[torch.randperm(n, generator=g)].int().cuda()
     means = []
-    for lists in (k, n // 64 + 1):                       # (the others are empty: 64 rows a list and fewer)
+    for lists in (k, n // 32 + 1):                       # (the others are empty: fewer than 32 rows a list)
         Y = torch.zeros(lists, d, device="cuda")
         assert skm.update(X, labels, Y)[:k].tolist() == sizes
         means.append(Y[:k])
-    assert n >= 64 * k and torch.equal(means[0], means[1])
+    assert n >= 32 * k and torch.equal(means[0], means[1])
     want = torch.zeros(k, d, dtype=torch.float64, device="cuda").index_add_(0, labels.long(), X.double())
     want /= torch.tensor(sizes, device="cuda").clamp_min(1)[:, None]
     assert float((means[1].double() - want).abs().max()) <= 2.0 ** -24 * float(want.abs().max()) + 1e-12   # (fp64 sums, rounded once)
