@@ -787,39 +787,36 @@ __device__ inline void block_absmax(float v, unsigned int *out) {
   }
 }
 
-// Rows without gaps (lda == cols) are read as one array, 16 bytes a load whatever its alignment (global loads need 4 bytes;
-// 46 467 x 495 a value at a time: 70 us, now 16); otherwise an element index is split into row and column.
+// Rows without gaps (lda == cols) are read as one array of at least four values, 16 bytes a load whatever its alignment (global loads
+// need 4 bytes; 46 467 x 495 a value at a time: 70 us, now 16), four loads in flight.  A kernel by itself: behind the code for rows
+// with gaps a small array took 6.4 us instead of 4.5, most of it for the instructions.
+__global__ void __launch_bounds__(256) absmax_flat_kernel(const float *A, int64_t count, unsigned int *out) {
+  const int64_t last = count - 4, stride = (int64_t)gridDim.x * 1024;
+  float m = 0.f;
+  for (int64_t e = (int64_t)blockIdx.x * 1024 + threadIdx.x; 4 * e < count; e += stride) {
+    f32x4_u v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4_u *>(A + min(4 * (e + 256 * u), last));   // (past the end: the last four again)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+  }
+  block_absmax(m, out);
+}
+// Rows with gaps: an element index is split into row and column.
 template <bool VEC4>
 __global__ void __launch_bounds__(256) absmax_kernel(const float *A, int64_t lda, int64_t rows, int32_t cols,
                                                      unsigned int *out) {
   const int64_t per_row = VEC4 ? cols / 4 : cols;
   const int64_t total = rows * per_row;
-  const bool flat = lda == cols;
   float m = 0.f;
-  if (flat && rows * (int64_t)cols >= 4) {   // four loads in flight
-    const int64_t last = rows * (int64_t)cols - 4;
-    const int64_t stride = (int64_t)gridDim.x * 1024;
-    for (int64_t e = (int64_t)blockIdx.x * 1024 + threadIdx.x; 4 * e < last + 4; e += stride) {
-      f32x4_u v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4_u *>(A + min(4 * (e + 256 * u), last));   // (past the end: the last four again)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
-    }
-    block_absmax(m, out);
-    return;
-  }
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    int64_t at = e * (VEC4 ? 4 : 1);
-    if (!flat) {
-      const int64_t r = e / per_row;
-      at = r * lda + (e - r * per_row) * (VEC4 ? 4 : 1);
-    }
+    const int64_t r = e / per_row;
+    const float *at = A + r * lda + (e - r * per_row) * (VEC4 ? 4 : 1);
     if (VEC4) {
-      const float4 v = *reinterpret_cast<const float4 *>(A + at);
+      const float4 v = *reinterpret_cast<const float4 *>(at);
       m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
     } else {
-      m = fmaxf(m, fabsf(A[at]));
+      m = fmaxf(m, fabsf(*at));
     }
   }
   block_absmax(m, out);
@@ -829,11 +826,13 @@ hipError_t launch_absmax(const float *A, int64_t lda, int64_t rows, int32_t cols
                          int max_blocks) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const bool vec = (reinterpret_cast<uintptr_t>(A) & 15u) == 0 && lda % 4 == 0 && cols % 4 == 0;
-  const int64_t work = vec || lda == cols ? (rows * (int64_t)cols + 3) / 4 : rows * (int64_t)cols;
+  const bool flat = lda == cols && rows * (int64_t)cols >= 4;
+  const int64_t work = vec || flat ? (rows * (int64_t)cols + 3) / 4 : rows * (int64_t)cols;
   // At least four elements per thread where there are that many, and two workgroups per CU at most: that keeps enough
   // loads in flight, and the atomics at the one result word, 10 ns each, stay few (4096 workgroups: 40 us for 20 000 x 1536).
   const unsigned blocks = (unsigned)std::min<int64_t>((work + 1023) / 1024, max_blocks > 0 ? max_blocks : 2 * num_cus());
-  if (vec) hipLaunchKernelGGL(absmax_kernel<true>, dim3(blocks), dim3(256), 0, st, A, lda, rows, cols, out);
+  if (flat) hipLaunchKernelGGL(absmax_flat_kernel, dim3(blocks), dim3(256), 0, st, A, rows * (int64_t)cols, out);
+  else if (vec) hipLaunchKernelGGL(absmax_kernel<true>, dim3(blocks), dim3(256), 0, st, A, lda, rows, cols, out);
   else hipLaunchKernelGGL(absmax_kernel<false>, dim3(blocks), dim3(256), 0, st, A, lda, rows, cols, out);
   return hipGetLastError();
 }
