@@ -182,22 +182,25 @@ __device__ inline float4 load_stream4(const float *p) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// BATCH (with po.xnp and po.xs, NV > 0): a workgroup takes 64 consecutive points at a time and writes their prefix norms through
-// LDS, 256 contiguous bytes per table row, instead of one 4-byte store per point and row.  Where 64 points a workgroup
-// would leave most of the chip without one (a wavefront then walks sixteen rows one after the other while other CUs
-// idle), it takes 16.
+// TABLES (po.xnp and po.xs; po.order too if the points change places).  Up to 2048 dimensions (BATCH) a workgroup takes 64 consecutive
+// points at a time and writes their prefix norms through LDS, 256 contiguous bytes per table row, instead of one 4-byte store per
+// point and row.  Where 64 points a workgroup would leave most of the chip without one (a wavefront then walks sixteen rows one
+// after the other while other CUs idle), it takes 16.
+// Without TABLES their code is left out: it costs registers (NV = 6: 68 without it, 137 with it; labels and distances of 11 800 x 1152 in 13.1
+// and 16.9 us).
 constexpr int kPrefixStageRows = 128;   // ds <= 2048 in the batched form
-template <int NV, bool BATCH>
+template <int NV, bool TABLES>
 __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t ldx, int64_t n, int32_t ds,
                                                        const float *Y, int64_t ldy, const int32_t *assign, float *tau,
                                                        unsigned long long *best, PrefixOut po) {
+  constexpr bool BATCH = TABLES && NV > 0;
   __shared__ float s_np[BATCH ? kPrefixStageRows * 64 : 1];
   __shared__ __align__(16) uint32_t s_pair[BATCH ? 4 * 512 : 4];
   put_stamp(po.stamp);
-  if (po.xs) po.scale = split_scale(*po.absmax);
+  if (TABLES) po.scale = split_scale(*po.absmax);
   const int lane = threadIdx.x & 63;
   auto point = [&](int64_t p) {   // output slot p <- point i
-    const int64_t i = po.order ? (int64_t)po.order[p] : p;
+    const int64_t i = TABLES && po.order ? (int64_t)po.order[p] : p;
     int a;
     if (assign) {
       a = assign[i];
@@ -233,26 +236,6 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
         s = fmaf(dz, dz, s);
         s = fmaf(dw, dw, s);
       }
-      if (po.xnp) {
-        float base = 0.f;
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-          if (256 * u >= ds) break;
-          const float q = fmaf(xv[u].x, xv[u].x, fmaf(xv[u].y, xv[u].y, fmaf(xv[u].z, xv[u].z, xv[u].w * xv[u].w)));
-          base = emit_prefix(po, p, lane, u, q, base);
-        }
-      }
-      if (po.xs) {
-        emit_split_pads(po, p, lane);
-#pragma unroll
-        for (int u = 0; u < NV; ++u)
-          if (lane * 4 + 256 * u < ds) emit_split(po, p, lane * 4 + 256 * u, xv[u]);
-      }
-      if (po.xr_out) {
-#pragma unroll
-        for (int u = 0; u < NV; ++u)
-          if (lane * 4 + 256 * u < ds) *reinterpret_cast<float4 *>(po.xr_out + p * (int64_t)ds + lane * 4 + 256 * u) = xv[u];
-      }
     } else {
       float base = 0.f;
       for (int c0 = 0; c0 < ds; c0 += 256) {
@@ -267,15 +250,15 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
         s = fmaf(dy, dy, s);
         s = fmaf(dz, dz, s);
         s = fmaf(dw, dw, s);
-        if (po.xnp) {
+        if (TABLES) {
           const float q = fmaf(xv.x, xv.x, fmaf(xv.y, xv.y, fmaf(xv.z, xv.z, xv.w * xv.w)));
           base = emit_prefix(po, p, lane, c0 >> 8, q, base);
-        }
-        if (po.xs) {
           if (c0 == 0) emit_split_pads(po, p, lane);
-          if (c < ds) emit_split(po, p, c, xv);
+          if (c < ds) {
+            emit_split(po, p, c, xv);
+            if (po.xr_out) *reinterpret_cast<float4 *>(po.xr_out + p * (int64_t)ds + c) = xv;
+          }
         }
-        if (po.xr_out && c < ds) *reinterpret_cast<float4 *>(po.xr_out + p * (int64_t)ds + c) = xv;
       }
     }
     s = wave_sum(s);
@@ -446,13 +429,14 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
                            int32_t *label_out, uint32_t *xh, unsigned int *unset, stamp_t *stamp) {
   if (n <= 0) return hipSuccess;
   const int nv = (ds + 255) / 256;
-  const bool batch = xnp != nullptr && xs != nullptr && nv <= 8 && ds / 16 <= kPrefixStageRows;
+  const bool batch = xnp != nullptr && nv <= 8;   // (then ds / 16 <= kPrefixStageRows)
   // (below five workgroups a CU, 16 points at a time)
   const int span = n >= (int64_t)num_cus() * 5 * 64 ? 64 : 16;
   int64_t blocks = batch ? (n + span - 1) / span : (n + 3) / 4;
   const int64_t cap = (int64_t)num_cus() * 32;
   if (blocks > cap) blocks = cap;
   if (xs && (ds % 16 != 0 || !x_absmax)) return hipErrorInvalidValue;
+  if ((xnp != nullptr) != (xs != nullptr) || (order && !xnp)) return hipErrorInvalidValue;   // (all tables or none)
   if ((order != nullptr) != (xr_out != nullptr) || (order && (!label_out || !assign)) || (!assign && !best)) return hipErrorInvalidValue;
   if (xr_out && (reinterpret_cast<uintptr_t>(xr_out) & 15u)) return hipErrorInvalidValue;
   if (xh && (!xs || (reinterpret_cast<uintptr_t>(xh) & 15u))) return hipErrorInvalidValue;
@@ -463,15 +447,9 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
     return hipGetLastError();
   }
   const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out, unset, span, stamp};
-#define SKM_TAU_LAUNCH(NV)                                                                                      \
-  do {                                                                                                          \
-    if (batch && NV > 0)                                                                                        \
-      hipLaunchKernelGGL((tau_init_kernel<NV, (NV > 0)>), dim3((unsigned)blocks), dim3(256), 0, st, Xr, ldx, n, ds, Y, \
-                         ldy, assign, tau, best, po);                                                           \
-    else                                                                                                        \
-      hipLaunchKernelGGL((tau_init_kernel<NV, false>), dim3((unsigned)blocks), dim3(256), 0, st, Xr, ldx, n, ds, Y,   \
-                         ldy, assign, tau, best, po);                                                           \
-  } while (0)
+#define SKM_TAU_LAUNCH(NV)                                                                                          \
+  hipLaunchKernelGGL((xnp ? tau_init_kernel<NV, true> : tau_init_kernel<NV, false>), dim3((unsigned)blocks), dim3(256), 0, st, Xr, \
+                     ldx, n, ds, Y, ldy, assign, tau, best, po)
   if (nv <= 1) SKM_TAU_LAUNCH(1);
   else if (nv <= 2) SKM_TAU_LAUNCH(2);
   else if (nv <= 3) SKM_TAU_LAUNCH(3);

@@ -36,6 +36,20 @@ def test_exact_assignment_of_rows_that_are_no_multiple_of_16(skm, orc, dg, n, d,
     assert torch.equal(a, b) and torch.equal(dist, dist_b)
 
 
+# Labels and direct distances from the keys of the argmin, without tables: a form for every 256 dimensions up to 2048, one for rows
+# beyond.  A lane adds d / 64 squares, its sum and the lanes' six more steps of rounding to a sum of positive terms.
+@pytest.mark.parametrize("d", [240, 256, 272, 512, 528, 768, 1024, 1040, 1536, 1552, 2048, 2064])
+def test_exact_distances_on_both_sides_of_every_form(skm, d):  # noqa: F811
+    say("exact distances", d)
+    g = torch.Generator().manual_seed(d)
+    X, Y = torch.randn(67, d, generator=g), torch.randn(5, d, generator=g)
+    D = torch.cdist(X.double(), Y.double(), compute_mode="donot_use_mm_for_euclid_dist") ** 2
+    a, dist = skm.assign_exact(X.cuda(), Y.cuda())
+    want, at = D.min(1)
+    assert torch.equal(a.cpu().long(), at)
+    assert float(((dist.cpu().double() - want).abs() / want).max()) <= (d / 64 + 12) * 2.0 ** -23
+
+
 # Behind the first test of a listed tile: one product and widened tests (no counts per block asked for, three blocks or more,
 # pairs handed over), or three products throughout.  Poor incumbents leave tiles that are done again in three products,
 # good ones tiles that hand over at the first test.
