@@ -190,11 +190,11 @@ __global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t
     if (!ALIGNED) return load4_any(x + c, d - c);
     return c < d ? *reinterpret_cast<const float4 *>(x + c) : make_float4(0.f, 0.f, 0.f, 0.f);
   };
-  auto emit = [&](uint32_t *dst, const float4 &v, float sc) {
+  auto emit = [&](uint32_t *dst, int c, const float4 &v, float sc) {
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
     const f32x2_t p0 = {v.x * sc, v.y * sc}, p1 = {v.z * sc, v.w * sc};
-    *reinterpret_cast<uint2 *>(dst) =
+    *reinterpret_cast<uint2 *>(dst + 32 * (c / 32) + (c % 32) / 2) =
         make_uint2(__builtin_bit_cast(unsigned int, __builtin_convertvector(p0, f16x2_t)),
                    __builtin_bit_cast(unsigned int, __builtin_convertvector(p1, f16x2_t)));
   };
@@ -221,13 +221,13 @@ __global__ void __launch_bounds__(256) gt_convert_kernel(const float *X, int64_t
       m = fmaxf(m, __shfl_xor(m, o, 64));
     }
     const float sc = m > 0.f ? split_scale(__builtin_bit_cast(unsigned int, m)) : 1.f;
-    uint32_t *dst = plane + split_row(i, ds / 2) + 32 * (lane >> 3) + 2 * (lane & 7);   // (column 4 lane; 256 columns further on 256 words)
+    uint32_t *dst = plane + split_row(i, ds / 2);
     if (NV > 0) {
 #pragma unroll
       for (int u = 0; u < NV; ++u)
-        if (256 * u + 4 * lane < ds) emit(dst + 256 * u, v[u], sc);
+        if (256 * u + 4 * lane < ds) emit(dst, 256 * u + 4 * lane, v[u], sc);
     } else {
-      for (int c = 4 * lane; c < ds; c += 256) emit(dst + (c - 4 * lane), load(x, c), sc);
+      for (int c = 4 * lane; c < ds; c += 256) emit(dst, c, load(x, c), sc);
     }
     if (lane == 0) {
       scale[i] = sc;
