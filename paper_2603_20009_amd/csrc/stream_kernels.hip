@@ -448,8 +448,9 @@ hipError_t launch_tau_init(const float *Xr, int64_t ldx, int64_t n, int32_t ds, 
   }
   const PrefixOut po{xnp, n, ds, xs, xh, x_absmax, 0.f, order, xr_out, label_out, unset, span, stamp};
   // Long rows that stream from memory do so faster four workgroups a CU (room in LDS that is not used) than seven: 1M x 1536 1218 -> 1189
-  // us (in a fit, points grouped, 1132 -> 1118), 400 000 x 2048 586 -> 582, 100 000 x 1536 98.5 -> 97.7; but 11 800 x 1152 11.4 -> 12.8, and rows of up to 1024 dimensions, 1M x 768 632 ->
-  // 635, 60 000 x 1024 37.4 -> 40.4, 1M x 384 311 -> 409.  (The line: the rows outgrow the Infinity Cache of 256 MB.)
+  // us (in a fit, points grouped, 1132 -> 1118), 400 000 x 2048 586 -> 582, 100 000 x 1536 98.5 -> 97.7; but 11 800 x 1152 11.4 -> 12.8, and
+  // rows of up to 1024 dimensions, 1M x 768 632 -> 635, 60 000 x 1024 37.4 -> 40.4, 1M x 384 311 -> 409.  (The line: the rows outgrow the
+  // Infinity Cache of 256 MB.)
   const unsigned room = !xnp && nv > 4 && nv <= 8 && n * ds >= (int64_t)1 << 26 ? 32 * 1024 : 0;
 #define SKM_TAU_LAUNCH(NV)                                                                                          \
   hipLaunchKernelGGL((xnp ? tau_init_kernel<NV, true> : tau_init_kernel<NV, false>), dim3((unsigned)blocks), dim3(256), room, st, \
