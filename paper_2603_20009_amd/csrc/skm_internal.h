@@ -575,7 +575,7 @@ hipError_t launch_pad_copy(const float *src, int64_t lds, int64_t n, int32_t d, 
 
 // ---------------------------------------------------------------- rotation matrix
 // Haar-distributed orthogonal d x d matrix (fp32) from (d, seed); workspaces in doubles:
-// Qwork d*d + 2, Cwork max(12*64*d, (2*ceil(d/64)+1)*64*64), Wwork ceil(d/64)*64*d.
+// Qwork d*d + 2, Cwork max(6*64*d, (ceil(d/64)+1)*64*64) at least, Wwork ceil(d/64)*64*d.
 hipError_t launch_make_rotation(int32_t d, uint64_t seed, double *Qwork, double *Cwork, double *Wwork, float *R_out,
                                 hipStream_t st);
 

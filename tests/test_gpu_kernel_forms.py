@@ -110,6 +110,30 @@ def test_rotation_at_the_edges_of_its_panels(skm, d):  # noqa: F811
     assert np.abs(R @ R.T - np.eye(d)).max() < 2 * 2.0 ** -24 * np.sqrt(d)
 
 
+# Up to 128 rows one workgroup makes the matrix, beyond that a chain of kernels whose last 128 rows go round twice: the matrix
+# is the orthonormal factor of the normals that (d, seed) stand for, computed here by numpy's QR.  An element is off by half
+# an ulp of fp32 plus what fp64 rounding leaves of either factor, 64 eps times the condition of the matrix of normals.
+@pytest.mark.parametrize("d", [1, 2, 15, 16, 17, 64, 65, 100, 128, 129, 192, 193, 260])
+def test_rotation_is_the_orthonormal_factor_of_its_normals(skm, d):  # noqa: F811
+    say("rotation", d)
+
+    def mix(z):
+        z = z + np.uint64(0x9E3779B97F4A7C15)
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        return z ^ (z >> np.uint64(31))
+
+    with np.errstate(over="ignore"):
+        t = np.arange((d * d + 1) // 2, dtype=np.uint64) * np.uint64(2) + np.uint64((5 + 3 * 0xD1342543DE82EF95) % 2**64)
+        u1, u2 = ((mix(z) >> np.uint64(11)).astype(np.float64) / 2.0**53 for z in (t, t + np.uint64(1)))
+    m = np.sqrt(-2.0 * np.log(u1))
+    G = np.stack([m * np.cos(2 * np.pi * u2), m * np.sin(2 * np.pi * u2)], 1).reshape(-1)[:d * d].reshape(d, d)
+    q, r = np.linalg.qr(G.T)
+    want = (q * np.sign(np.diag(r))).T
+    got = skm.make_rotation(d, 5).cpu().numpy().astype(np.float64)
+    assert (np.abs(got - want) <= 2.0**-24 * np.abs(want) + 64 * 2.0**-52 * np.linalg.cond(G)).all()
+
+
 # The ground truth goes through the points in chunks of whole rounds of tiles (256 points x 256 queries): one tile row and
 # several, a ragged last chunk, and too few points for the one-product form.
 @pytest.mark.parametrize("n,d,nq,K", [(40_000, 1536, 300, 10), (70_001, 1000, 257, 1), (20_000, 96, 64, 10),
