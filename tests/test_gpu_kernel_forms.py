@@ -961,3 +961,23 @@ def test_fewer_centroids_without_memory_for_the_order(skm, dg):  # noqa: F811
     assert abs(ra["survivors"] - rc["survivors"]) <= 1e-5 * max(rc["survivors"], n)
     bound = 2.0 ** -19 * (X.norm(dim=1).max() + Y.norm(dim=1).max()) ** 2     # as above
     assert int((a != c).sum()) <= 1e-3 * n and float((da - dc).abs().max()) <= 2 * float(bound)
+
+
+# Tiles are dealt out to the XCDs in runs of 8 (below 2048 tiles) to 128 (from 16 384 on), eight runs a round, and what does not fill
+# a round in eighths.  With a threshold that drops nothing every pair is finished, so a tile left out, or done in another's place,
+# shows in the labels.  Tiles of listed columns: one a row tile here; the others are narrow: two.
+@pytest.mark.parametrize("screen", [-1, 1])
+@pytest.mark.parametrize("tiles", [1, 31, 63, 64, 65, 127, 129, 1023, 1024, 1025, 2049, 16393])
+def test_tiles_dealt_out_in_runs(skm, tiles, screen):  # noqa: F811
+    say("runs", tiles, screen)
+    n, d, k = 128 * tiles - 3, 32, 256
+    g = torch.Generator().manual_seed(tiles)
+    X, Y = torch.randn(n, d, generator=g), torch.randn(k, d, generator=g)
+    D = (X.double() ** 2).sum(1)[:, None] + (Y.double() ** 2).sum(1)[None] - 2.0 * X.double() @ Y.double().T
+    D, want = D.topk(2, 1, largest=False)
+    prev = torch.randint(0, k, (n,), generator=g, dtype=torch.int32)
+    a, dist, row = skm.assign(X.cuda(), Y.cuda(), prev.cuda(), 16, skm.FitOptions(rotate=False, screen=screen, eps0=100.0))
+    assert (row["listed_tiles"] > 0) == (screen == 1)
+    clear = D[:, 1] - D[:, 0] > 1e-4 * D[:, 0]      # fp32 distances of 22-bit products
+    assert torch.equal(a.cpu()[clear].long(), want[clear, 0])
+    assert float(((dist.cpu().double() - D[:, 0]).abs() / D[:, 0]).max()) < 1e-4
