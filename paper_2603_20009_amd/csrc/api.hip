@@ -534,15 +534,16 @@ struct Ctx {
   float *xnp = nullptr;       // [ds / 16][n] prefix norms of the points at every multiple of 16 dims, written by the
   bool xnp_valid = false;     // first pruned step (the points of a context never change)
   bool xh_valid = false;      // Xh likewise: left out of a pass that a regrouping pass will repeat
-  // Regrouping (a fit with several steps left): once the tables exist and a full update has just grouped the points
-  // by their cluster, the next threshold pass rewrites the points, their split copy, their tables and every per-point
-  // array in that order.  Row tiles then hold points of one or two clusters, whose challengers are the same few
+  // Regrouping (a fit with several steps left): once the tables exist, a threshold pass rewrites the points, their split
+  // copy, their tables and every per-point array in the order of their clusters (step_pruned).  Row tiles then hold points of one or two clusters, whose challengers are the same few
   // centroids: the alive pairs of a step gather in few tiles, the others end at the first test, and the rows and
   // centroid blocks the gather kernel fetches are shared by neighbouring pairs.
   float *Xr2 = nullptr;          // [n][ds] the points in the new order (NULL: no regrouping in this context)
   int32_t *pos_to_id = nullptr;  // [n] point of every position
   unsigned char *subkey = nullptr;   // [n] scratch: the key that orders the points inside a cluster
-  bool regroup_ok = false;       // the caller has enough steps left for it to pay
+  float *Xr_own = nullptr;       // Xr where its rows are the library's own: once regrouped they are room for the next regrouping
+  int32_t regroup_left = 0;      // assignment steps of the fit from this one on (0: its points are not regrouped)
+  int64_t moved = 0;             // changes of a label since the points were last grouped by it
   int32_t max_cluster = -1;      // size of the largest cluster at the last update (-1: none yet)
   bool group_now = false;        // a single step that groups the points by their incumbents itself (assign_impl)
   int32_t *grp_cnt = nullptr;    // [k + 1] sizes of those groups, and how many of a sample of the thresholds are in a tail
@@ -892,7 +893,7 @@ size_t fit_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &p) 
   }
   const size_t plan = plan_common_bytes(n, d, k, p.pair_budget, p.dense_frac, true);
   if (!plan) return 0;
-  size_t need = plan + 2 * (size_t)n * ds0 * 4 + (size_t)n * 5 + 10 * (size_t)d * ds0 * 4 + (size_t)d * 16384 +
+  size_t need = plan + 2 * (size_t)n * ds0 * 4 + (size_t)n * 5 + (size_t)threshold_class_words(n) * 4 + 10 * (size_t)d * ds0 * 4 + (size_t)d * 16384 +
                 (size_t)k * 16 + ((size_t)32 << 20);
   if (p.etr && p.nq > 0 && p.topk > 0) {
     const size_t nq = (size_t)p.nq;
@@ -1059,6 +1060,16 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
   return SKM_OK;
 }
 
+// Whether the points of a fit are regrouped (Ctx) with `left` steps to go, this one included.  The rewrite costs about as much as
+// three threshold passes and saves a part of every later step that grows with the centroids: 614 400 x 1024, k = 4000, four
+// iterations 52.6 -> 45.2 ms, 1M x 768, k = 2048 43.9 -> 37.4; with k = 1024 three steps do not pay for it (31.4 without).
+inline bool regroup_pays(int32_t left, int32_t k) { return left >= 4 || (left >= 2 && (int64_t)left * k >= 4096); }
+// ... and again, once the labels have moved on.  Ten iterations with one regrouping -> with a second one: 1M x 1536, k = 4096, a
+// tenth of the labels changed 183.9 -> 176.4 ms, 614 400 x 1024, k = 4000 89.2 -> 83.9, 1M x 768, k = 2048, a fifth changed 65.6 -> 63.8,
+// where 7 % had changed 43.4 -> 44.3 (left x k x share: 3300, 5000, 3000 and 1100).
+inline bool regroup_pays_again(int32_t left, int32_t k, int64_t moved, int64_t n) {
+  return (double)left * k * (double)moved >= 2048.0 * (double)n;
+}
 // Iterations >= 2 of Algorithm 1: initial threshold, progressive-pruning GEMM, gather kernel for the
 // pairs of sparse tiles, argmin.  On entry c.prev holds the incumbents (c.assign is overwritten);
 // have_prev = false seeds the incumbent with the centroid of smallest partial distance.
@@ -1135,7 +1146,18 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   }
   // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
   // far less usefully than those of iteration 2)
-  bool regroup = c.regroup_ok && !c.permuted && c.xnp_valid && c.order_fresh && c.Xr2 && have_prev && c.pruned_steps >= 1;
+  const bool again = c.permuted;
+  bool regroup = c.regroup_left > 0 && c.xnp_valid && c.Xr2 && have_prev && c.pruned_steps >= 1 &&
+                 (again ? regroup_pays_again(c.regroup_left, c.k, c.moved, c.n) : regroup_pays(c.regroup_left, c.k));
+  // In a fit the points lie by quarters of their distance first, and by label inside a quarter: a point far from its centroid
+  // keeps most columns of its row tile alive, so that the three quarters near theirs are better off without it.  The distances are
+  // those of the step before (to the centroids as they were): there is no pass for them.  Column tiles a row tile lists, by label
+  // -> by quarters, steps 3, 4 and 7: 1M x 1536, k = 4096 32 -> 32, 18.8 -> 14.8, 13.4 -> 11.1, 1M x 768, k = 4096 (steps 3 and 4)
+  // 20.0 -> 12.2, 8.3 -> 6.5; halves and eighths of the distances list 2 to 15 % more.  Whole fits 201.9 -> 183.9 and 62.2 -> 59.3
+  // ms, 300 000 x 512, k = 1500 9.93 -> 9.51, 150 000 x 256, k = 900 3.66 -> 3.57.  The nine small launches (30 to 60 us) are not
+  // earned back below 2^34 products a step: 120 001 x 208, k = 777 (2^34.2) 2.21 -> 2.21, 40 000 x 384, k = 250 1.60 -> 1.59, 60 000 x
+  // 448, k = 256 1.64 -> 1.66, 20 000 x 512, k = 100 1.40 -> 1.42.
+  const bool by_quarters = regroup && (double)c.n * c.ds * c.k >= 0x1p34;
   bool by_threshold = false;   // the new order follows the thresholds before the labels
   if (c.group_now && !c.permuted && c.Xr2) {
     // A step on its own (no update before it left an order): the points are grouped by the incumbents they come with
@@ -1152,7 +1174,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       if (!regroup && c.screen_mode == 0) screen = false;
     }
     if (regroup) {
-      HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.st));
+      HIPCHK(launch_group_order(c.prev, c.n, c.k, c.grp_cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, nullptr, c.st));
       std::vector<int32_t> sizes((size_t)c.k + 1);
       HIPCHK(hipMemcpyAsync(sizes.data(), c.grp_cnt, sizeof(int32_t) * ((size_t)c.k + 1), hipMemcpyDeviceToHost, c.st));
       HIPCHK(hipStreamSynchronize(c.st));
@@ -1170,34 +1192,48 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     // holds for them, which leaves the results of such fits what they were.
     // (the sizes came back with the previous step's scalars: no copy, no wait here)
     regroup = c.max_cluster >= 0 && c.max_cluster <= update_sort_cap();
-    if (!regroup) c.regroup_ok = false;
   }
   if (regroup) {
+    if (c.regroup_left > 0 && !c.order_fresh)   // (the last update did not need the whole order)
+      HIPCHK(launch_group_order(c.prev, c.n, c.k, c.inc.cnt, c.up.off, c.up.cursor, c.up.segoff, c.up.order, c.up.base, c.st));
     // this pass reads every point anyway: it writes them back grouped by cluster (see Ctx)
     // Inside a cluster that spans several row tiles the points follow the signs of their first four dimensions, then
     // their index: which points of a cluster share a tile matters (measured: -3 % on a fit with 1000 points per
     // cluster, nothing to gain where a cluster is smaller than a tile).
+    // The order is made between up.order and `other`; pos_to_id is still in use where the points have been regrouped before (best
+    // is free until the pass below writes this step's keys: it must not be where the order ends up).
+    int32_t *other = again ? reinterpret_cast<int32_t *>(c.best) : c.pos_to_id;
     if (c.n / c.k >= 128)
-      HIPCHK(launch_suborder(c.Xr, c.ldx, c.n, c.k, c.up.off, c.up.order, c.subkey, c.pos_to_id, c.st));
+      HIPCHK(launch_suborder(c.Xr, c.ldx, c.n, c.k, c.up.off, c.up.order, c.subkey, other, c.st));
     else
-      HIPCHK(hipMemcpyAsync(c.pos_to_id, c.up.order, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
+      HIPCHK(hipMemcpyAsync(other, c.up.order, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
+    int32_t *order = c.up.order;
     if (by_threshold) {
       // A step on its own takes its thresholds once more, in front of the order that they decide (1.2 of 41 ms at 2.5M x 384):
-      // its incumbents are as old as the caller's, or come from the front dimensions alone.  The steps of a fit do not: with the
-      // points of their steps in this order 1M x 1536 against 4096 centroids lists 10.4 column tiles a row tile instead of 10.5,
-      // 1M x 768 against 1024 2.5 instead of 2.7, tiles and gather within 1 %.
+      // its incumbents are as old as the caller's, or come from the front dimensions alone.
       HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, nullptr, c.st));
-      HIPCHK(launch_threshold_classes(c.tau, c.n, c.pos_to_id, (int32_t *)c.dist, c.assign, c.class_ws, c.grp_cnt, c.up.off, c.up.cursor,
-                                      c.up.segoff, c.up.order, c.st));
-      std::swap(c.up.order, c.pos_to_id);
+      HIPCHK(launch_threshold_classes(c.tau, c.n, 0, other, (int32_t *)c.dist, c.assign, c.class_ws, order, c.st));
+    } else if (by_quarters) {
+      HIPCHK(launch_threshold_classes(c.dist, c.n, 4, other, (int32_t *)c.tau, c.assign, c.class_ws, order, c.st));
+    } else if (again) {
+      HIPCHK(hipMemcpyAsync(order, other, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
+    } else {
+      order = other;
     }
     HIPCHK(launch_tau_init(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, c.best, c.st, c.xnp, c.Xs,
-                           c.xr_bound, c.pos_to_id, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
+                           c.xr_bound, order, c.Xr2, c.assign, c.Xh, nullptr, tau_stamp));
     std::swap(c.prev, c.assign);   // the incumbents in the new order; the other buffer receives this step's labels
-    if (c.point_keys)   // (up.order is scratch until the next full update rebuilds it)
-      HIPCHK(launch_remap_key_ids(c.point_keys, c.n_point_keys, c.pos_to_id, c.n, c.up.order, c.st));
-    c.Xr = c.Xr2;
+    if (c.point_keys) HIPCHK(launch_remap_key_ids(c.point_keys, c.n_point_keys, order, c.n, c.assign, c.st));
+    if (again) {
+      HIPCHK(launch_compose(c.pos_to_id, order, c.n, c.assign, c.st));
+      HIPCHK(hipMemcpyAsync(c.pos_to_id, c.assign, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.st));
+    } else if (order != c.pos_to_id) {
+      std::swap(c.pos_to_id, c.up.order);   // (up.order is scratch until the next full update rebuilds it)
+    }
+    std::swap(c.Xr_own, c.Xr2);   // the rows as they lay are room for the next time (NULL where they were the caller's: there is none)
+    c.Xr = c.Xr_own;
     c.ldx = c.ds;
+    c.moved = 0;
     c.permuted = true;
     c.xh_valid = c.Xh != nullptr;
   } else if (have_prev && c.tau_kept != Ctx::KEPT_NONE && c.xnp_valid && !(screen && !c.xh_valid)) {
@@ -1796,12 +1832,25 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   rc = c.alloc_common(p.pair_budget, p.dense_frac, true);
   if (rc) return rc;
   // regrouping of the points by cluster (Ctx): not for rows that the batched table writes of the threshold pass do not
-  // cover (it happens in the third step at the earliest and wants four steps, itself included, to pay)
-  const bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && iters + (p.final_assign ? 1 : 0) >= 6;
+  // cover; it happens in the third step at the earliest
+  bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && regroup_pays(iters - 2 + (p.final_assign ? 1 : 0), k);
   if (may_regroup) {
-    HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
-    HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
-    HIPCHK(c.pool.get(&c.subkey, (size_t)n));
+    auto room = [&]() -> int {
+      HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
+      HIPCHK(c.pool.get(&c.subkey, (size_t)n));
+      HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
+      HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
+      return SKM_OK;
+    };
+    rc = room();
+    if (rc == SKM_ENOMEM) {   // no memory for what a fit may do without: its points stay as they are
+      (void)hipGetLastError();
+      c.Xr2 = nullptr;
+      may_regroup = false;
+    } else if (rc) {
+      return rc;
+    }
+    c.Xr_own = Xr_own;
   }
 
   // ---- InitCentroids: k distinct rows of X~.  The row numbers go through the page-locked block, so nothing waits here
@@ -1906,8 +1955,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
       rc = step_exact(c, tm, ss);
     } else {
       std::swap(c.assign, c.prev);
-      // the rewrite costs about as much as three threshold passes and saves a fraction of every later step
-      c.regroup_ok = may_regroup && (iters - t + 1) + (p.final_assign ? 1 : 0) >= 4;
+      c.regroup_left = may_regroup ? (iters - t + 1) + (p.final_assign ? 1 : 0) : 0;
       rc = step_pruned(c, tm, dprime, (double)p.eps0, true, ss);
     }
     if (rc) return rc;
@@ -1928,6 +1976,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     }
     tm.mark_next(ST_UPDATE);   // (no wait: the next step's launches follow while the update runs)
     run = t;
+    c.moved += ss.changed;
     if (tr && rows < tr->capacity) fill_row(tr->row[rows], ss, n, k, nempty, recall);
     ++rows;
     if (t > 1 && p.adjust_dprime && k > 1) {
@@ -1954,7 +2003,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   if (p.final_assign) {
     StepStats ss;
     std::swap(c.assign, c.prev);
-    c.regroup_ok = false;
+    c.regroup_left = 0;
     written = !c.permuted;   // points in the caller's order: the last kernel writes the caller's arrays
     if (written && assign_out) c.assign = assign_out;
     if (written && dist_out) c.dist = dist_out;

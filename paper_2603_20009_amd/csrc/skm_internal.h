@@ -420,6 +420,7 @@ hipError_t launch_suborder(const float *Xr, int64_t ldx, int64_t n, int32_t k, c
                            unsigned char *key_scratch, int32_t *order_out, hipStream_t st);
 // keys hold a point id in their low 32 bits (packed (distance, point) keys; ~0 = none): every id becomes the position
 // p with perm[p] = id.  inv_scratch: n ints.
+hipError_t launch_compose(const int32_t *a, const int32_t *b, int64_t n, int32_t *out, hipStream_t st);   // out[p] = a[b[p]]
 hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32_t *perm, int64_t n, int32_t *inv_scratch,
                                 hipStream_t st);
 
@@ -509,19 +510,18 @@ int64_t update_max_segments(int64_t n, int32_t k);
 bool stable_order_applies(int64_t n, int32_t k);
 int64_t stable_order_words(int64_t n, int32_t k);   // of `base` below, for n points or fewer
 // The grouping half of launch_update alone: cnt[k] sizes, off[k+1] starts, order[n] point ids grouped by label (cursor[k]
-// and segoff[k+1] are scratch).
+// and segoff[k+1] are scratch; base as in UpdateWs, or NULL).
 hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32_t *cnt, int32_t *off, int32_t *cursor,
-                              int32_t *segoff, int32_t *order, hipStream_t st);
-// order_out[] = order[] with the points of low thresholds first (stably, in a few classes; see there).  bin[n], cls[n] and
-// words[threshold_class_words(n)] are scratch, and cnt, off, cursor and segoff of launch_group_order are overwritten.
+                              int32_t *segoff, int32_t *order, int32_t *base, hipStream_t st);
+// order_out[] = order[] with the points of low thresholds first (stably, in a few classes; see there).  quarters = 0: the
+// classes of a tail; else that many (at most six) of equal size.  bin[n], cls[n] and words[threshold_class_words(n)] are scratch.
 int64_t threshold_class_words(int64_t n);
 // *above = how many of every 16th point have a threshold that puts them into a class of its own (tau, bin and words as above)
 hipError_t launch_threshold_sample(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const float *Y, int64_t ldy,
                                    const int32_t *labels, float *tau, int32_t *bin, int32_t *words, int32_t *above, hipStream_t st);
 bool thresholds_have_tail(int64_t n, int32_t above);
-hipError_t launch_threshold_classes(const float *tau, int64_t n, const int32_t *order, int32_t *bin, int32_t *cls, int32_t *words,
-                                    int32_t *cnt, int32_t *off, int32_t *cursor, int32_t *segoff, int32_t *order_out,
-                                    hipStream_t st);
+hipError_t launch_threshold_classes(const float *tau, int64_t n, int quarters, const int32_t *order, int32_t *bin, int32_t *cls,
+                                    int32_t *words, int32_t *order_out, hipStream_t st);
 // largest cluster whose members launch_update leaves sorted by index in w.order (larger ones: any order)
 int32_t update_sort_cap();
 // S (optional, [k][ds] fp64) receives the sum of every cluster; y_absmax (optional) the bit pattern of max |Y| of

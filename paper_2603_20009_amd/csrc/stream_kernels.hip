@@ -623,6 +623,17 @@ hipError_t launch_suborder(const float *Xr, int64_t ldx, int64_t n, int32_t k, c
   return hipGetLastError();
 }
 
+// out[p] = a[b[p]]
+__global__ void compose_kernel(const int32_t *a, const int32_t *b, int64_t n, int32_t *out) {
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) out[p] = a[b[p]];
+}
+hipError_t launch_compose(const int32_t *a, const int32_t *b, int64_t n, int32_t *out, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const int64_t blocks = std::min<int64_t>((n + 255) / 256, (int64_t)num_cus() * 16);
+  hipLaunchKernelGGL(compose_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, b, n, out);
+  return hipGetLastError();
+}
+
 // inv[perm[p]] = p, then the point id in the low half of every key replaced by its position (keys of ~0 stay)
 __global__ void invert_permutation_kernel(const int32_t *perm, int64_t n, int32_t *inv) {
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) inv[perm[p]] = (int32_t)p;
@@ -1865,10 +1876,17 @@ hipError_t launch_update(const float *Xr, int64_t ldx, int64_t n, int32_t ds, co
   return hipGetLastError();
 }
 
-// order[] = the point ids grouped by label (members of a cluster of at most SORT_CAP points in ascending order), off[] the
-// start of every group, cnt[] the group sizes: the first half of launch_update, for callers that only want the grouping.
+// order[] = the point ids grouped by label (members of a cluster of at most SORT_CAP points in ascending order, with `base`
+// those of any cluster), off[] the start of every group, cnt[] the group sizes: the first half of launch_update, for callers
+// that only want the grouping.
 hipError_t launch_group_order(const int32_t *labels, int64_t n, int32_t k, int32_t *cnt, int32_t *off, int32_t *cursor,
-                              int32_t *segoff, int32_t *order, hipStream_t st) {
+                              int32_t *segoff, int32_t *order, int32_t *base, hipStream_t st) {
+  if (base) {
+    if (!stable_order_applies(n, k)) return hipErrorInvalidValue;
+    launch_stable_counts(labels, n, k, base, cnt, nullptr, st);
+    hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, st, cnt, k, off, cursor, segoff, (unsigned int *)nullptr);
+    return launch_stable_scatter(labels, n, k, off, base, order, nullptr, st);
+  }
   hipError_t rc = launch_fill_u32(reinterpret_cast<unsigned int *>(cnt), k, 0u, st);
   if (rc != hipSuccess) return rc;
   rc = launch_histogram(labels, n, k, cnt, nullptr, st);
@@ -1903,9 +1921,10 @@ __global__ void threshold_bins_kernel(const float *tau, int64_t n, int32_t *bin)
     bin[i] = (int32_t)((__float_as_uint(tau[i]) & 0x7fffffffu) >> 18);
 }
 // class_of[b] = 0 where the bin starts below THR_TAIL times the median's, else floor(log2(n / number of points in the bins from b
-// on)), at most THR_CLASSES - 1.  *above (optional): the points of the other classes.
+// on)), at most THR_CLASSES - 1.  *above (optional): the points of the other classes.  With `quarters` the quarter that the
+// bin starts in.
 __global__ void __launch_bounds__(1024) threshold_classes_kernel(const int32_t *cnt, int64_t n, int32_t *class_of,
-                                                                 int32_t *above) {
+                                                                 int32_t *above, int quarters) {
   constexpr int PER = THR_BINS / 1024;
   __shared__ int s_sum[16];
   __shared__ int s_median, s_above;
@@ -1941,6 +1960,7 @@ __global__ void __launch_bounds__(1024) threshold_classes_kernel(const int32_t *
     int c = 0;
     while (c < THR_CLASSES - 1 && ((n - below) << (c + 1)) <= n) ++c;
     if (__uint_as_float((unsigned int)b << 18) < tail) c = 0;
+    if (quarters > 0) c = (int)min(quarters * below / n, (int64_t)quarters - 1);
     class_of[b] = c;
     if (c > 0) mine += v[u];
     below += v[u];
@@ -1957,10 +1977,11 @@ __global__ void sample_labels_kernel(const int32_t *labels, int64_t m, int32_t *
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += (int64_t)gridDim.x * blockDim.x)
     out[j] = labels[j * THR_SAMPLE];
 }
-int64_t threshold_class_words(int64_t n) { return 2 * THR_BINS + stable_order_words(n, THR_CLASSES); }
+int64_t threshold_class_words(int64_t n) { return 2 * THR_BINS + 4 * (THR_CLASSES + 1) + stable_order_words(n, THR_CLASSES); }
 static unsigned threshold_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, (int64_t)num_cus() * 16); }
-// words: [THR_BINS] counts | [THR_BINS] classes
-static hipError_t classify_thresholds(const float *tau, int64_t n, int32_t *bin, int32_t *words, int32_t *above, hipStream_t st) {
+// words: [THR_BINS] counts | [THR_BINS] classes | the classes' sizes and starts | block counts of the partition
+static hipError_t classify_thresholds(const float *tau, int64_t n, int32_t *bin, int32_t *words, int32_t *above, int quarters,
+                                      hipStream_t st) {
   hipLaunchKernelGGL(threshold_bins_kernel, dim3(threshold_grid(n)), dim3(256), 0, st, tau, n, bin);
   hipError_t rc = launch_fill_u32(reinterpret_cast<unsigned int *>(words), THR_BINS, 0u, st);
   if (rc != hipSuccess) return rc;
@@ -1968,7 +1989,8 @@ static hipError_t classify_thresholds(const float *tau, int64_t n, int32_t *bin,
   const int per = 8192;
   hipLaunchKernelGGL(histogram_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(CNT_THREADS), THR_BINS * sizeof(int), st,
                      (const int32_t *)bin, n, (int32_t)THR_BINS, words, (unsigned int *)nullptr, per, 1);
-  hipLaunchKernelGGL(threshold_classes_kernel, dim3(1), dim3(1024), 0, st, (const int32_t *)words, n, words + THR_BINS, above);
+  hipLaunchKernelGGL(threshold_classes_kernel, dim3(1), dim3(1024), 0, st, (const int32_t *)words, n, words + THR_BINS, above,
+                     quarters);
   return hipGetLastError();
 }
 // A tail of one point in 2000 is in every 16th row tile.  One point of THR_SAMPLE tells whether there is one: the pass over all
@@ -1980,16 +2002,16 @@ hipError_t launch_threshold_sample(const float *Xr, int64_t ldx, int64_t n, int3
   hipLaunchKernelGGL(sample_labels_kernel, dim3(threshold_grid(m)), dim3(256), 0, st, labels, m, bin);
   hipError_t rc = launch_tau_init(Xr, ldx * THR_SAMPLE, m, ds, Y, ldy, bin, tau, nullptr, st);
   if (rc != hipSuccess) return rc;
-  return classify_thresholds(tau, m, bin, words, above, st);
+  return classify_thresholds(tau, m, bin, words, above, 0, st);
 }
 bool thresholds_have_tail(int64_t n, int32_t above) { return (int64_t)above * 2000 > (n + THR_SAMPLE - 1) / THR_SAMPLE; }
-hipError_t launch_threshold_classes(const float *tau, int64_t n, const int32_t *order, int32_t *bin, int32_t *cls, int32_t *words,
-                                    int32_t *cnt, int32_t *off, int32_t *cursor, int32_t *segoff, int32_t *order_out,
-                                    hipStream_t st) {
+hipError_t launch_threshold_classes(const float *tau, int64_t n, int quarters, const int32_t *order, int32_t *bin, int32_t *cls,
+                                    int32_t *words, int32_t *order_out, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int32_t *class_of = words + THR_BINS;
-  int32_t *base = words + 2 * THR_BINS;
-  hipError_t rc = classify_thresholds(tau, n, bin, words, nullptr, st);
+  int32_t *cnt = words + 2 * THR_BINS, *off = cnt + THR_CLASSES + 1, *cursor = off + THR_CLASSES + 1, *segoff = cursor + THR_CLASSES + 1;
+  int32_t *base = segoff + THR_CLASSES + 1;
+  hipError_t rc = classify_thresholds(tau, n, bin, words, nullptr, quarters, st);
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(class_of_points_kernel, dim3(threshold_grid(n)), dim3(256), 0, st, order, (const int32_t *)bin, class_of, n, cls);
   launch_stable_counts(cls, n, THR_CLASSES, base, cnt, nullptr, st);

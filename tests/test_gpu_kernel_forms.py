@@ -981,3 +981,41 @@ def test_tiles_dealt_out_in_runs(skm, tiles, screen):  # noqa: F811
     clear = D[:, 1] - D[:, 0] > 1e-4 * D[:, 0]      # fp32 distances of 22-bit products
     assert torch.equal(a.cpu()[clear].long(), want[clear, 0])
     assert float(((dist.cpu().double() - D[:, 0]).abs() / D[:, 0]).max()) < 1e-4
+
+
+# A fit regroups its points by quarters of their distances and by label, and again once the labels have moved on where the rows are
+# its own (rows that are not 16-byte aligned are copied); a caller's rows are regrouped once.  Both fits add the same fp64 sums in
+# another order.  Clusters of a few points and of several row tiles (those have an order of their own inside).
+@pytest.mark.parametrize("n,d,k,iters", [(33_000, 256, 2100, 10), (140_000, 256, 1024, 30), (300_001, 64, 1024, 30)])
+def test_points_of_a_fit_regrouped_again(skm, dg, n, d, k, iters):  # noqa: F811
+    say("regrouped again", n, d, k, iters)
+    X = dg.mixture(n, d, 4 * k, 3, "embed", "cuda")
+    own = torch.empty(n * d + 1, device="cuda")[1:].view(n, d).copy_(X)
+    opts = skm.FitOptions(rotate=False)
+    a, b, c = (skm.fit(x, k, iters, 5, opts) for x in (X, own, own))
+    assert torch.equal(b.assign, c.assign) and torch.equal(b.centroids, c.centroids) and torch.equal(b.dist, c.dist)
+    for ra, rb in zip(a.trace, b.trace):
+        assert abs(ra["survivors"] - rb["survivors"]) <= 1e-4 * max(ra["survivors"], n)
+    assert sum(r["listed_tiles"] for r in b.trace) < sum(r["listed_tiles"] for r in a.trace)
+    assert float((a.centroids - b.centroids).norm() / a.centroids.norm()) < 1e-4
+    assert float((a.assign != b.assign).float().mean()) <= 1e-3
+    # labels and distances belong to the points in the caller's order
+    exact = ((X.double() - b.centroids.double()[b.assign.long()]) ** 2).sum(1)
+    assert float((b.dist.double() - exact).abs().max()) <= 2.0 ** -18 * float(X.norm(dim=1).max() + b.centroids.norm(dim=1).max()) ** 2
+
+
+# ... and where there is no memory for the regrouped copy the fit is served without it.
+def test_fit_without_memory_for_the_order(skm, dg):  # noqa: F811
+    n, d, k = 400_000, 512, 2048
+    say("fit, a full device", n, d, k)
+    X = dg.mixture(n, d, 2 * k, 3, "embed", "cuda")
+    opts = skm.FitOptions(R=skm.make_rotation(d, 4), own_workspace=True)
+    a = skm.fit(X, k, 4, 5, opts)
+    skm.release_memory()
+    held = fill_device(skm.workspace_bytes(n, d, k) - n * d * 2)
+    b = skm.fit(X, k, 4, 5, opts)
+    del held
+    torch.cuda.empty_cache()
+    assert sum(r["listed_tiles"] for r in a.trace) < sum(r["listed_tiles"] for r in b.trace)
+    assert float((a.centroids - b.centroids).norm() / a.centroids.norm()) < 1e-4
+    assert float((a.assign != b.assign).float().mean()) <= 1e-3
