@@ -545,6 +545,7 @@ struct Ctx {
   int32_t regroup_left = 0;      // assignment steps of the fit from this one on (0: its points are not regrouped)
   int64_t moved = 0;             // changes of a label since the points were last grouped by it
   int32_t max_cluster = -1;      // size of the largest cluster at the last update (-1: none yet)
+  bool single_step = false;      // an assignment on its own, with incumbents of the caller's or none
   bool group_now = false;        // a single step that groups the points by their incumbents itself (assign_impl)
   int32_t *grp_cnt = nullptr;    // [k + 1] sizes of those groups, and how many of a sample of the thresholds are in a tail
   int32_t *class_ws = nullptr;   // [threshold_class_words(n)] scratch of their order by threshold
@@ -1295,13 +1296,17 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
         //   emit_deep: 6 110.5 | 45.6 | 246.5, 12 110.4 | 45.5 | 243.6, 48 110.4 | 46.1 | 242.4, 96 111.1 | 48.6 | 251.4
         //   deep_stride: 1 119.5 | 47.3 | 245.0, 2 113.7 | 46.0 | 242.0, 6 107.6 | 45.5 | 242.0 (1M x 768, k = 4096 93.4 -> 95.2)
         //   deep_max: 1/16 143.9 | 55.4 | 264.6, 1/8 123.7 | 49.5 | 253.4, 1/4 as it was, 1/2 105.8 | 44.3 | 239.8, no limit 104.4 | 44.2 |
-        //   239.5: half, so that a tile of poor incumbents is not done twice
+        //   239.5; but half of it where poor incumbents are all there is, whose tiles are done twice (500 000 x 384 on the sphere
+        //   against 6000 centroids, no incumbents 15.6, no limit 18.1 ms, random ones 14.6, 16.7).  The incumbents of a fit, and those
+        //   of a caller whose thresholds have a tail, are right for the most part: the tiles of the tail, most of whose pairs are
+        //   alive until the last tests, end there (the step against 32 768 centroids with its points in the order of
+        //   their thresholds 36.1 -> 29.7, 1M x 384 against 8000, every seventh incumbent random 18.4 -> 16.2; the fit 179.5 -> 178.2)
         g.deep = 1;
         g.Ah = sl.A; g.Bh = c.Yd; g.widen = c.scr_widen;
         g.emit_first = c.emit_max * 5 / 16;
         g.emit_deep = 24;
         g.deep_stride = 3;
-        g.deep_max = (unsigned int)progressive_tile_pairs() / 2;
+        g.deep_max = (unsigned int)progressive_tile_pairs() / (have_prev && (by_threshold || !c.single_step) ? 1 : 2);
       }
     }
     if (!screen) g.stamp = border;
@@ -2446,6 +2451,7 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
     rc = c.measure_xr();
     if (rc) return rc;
   }
+  c.single_step = true;
   c.prev_in = prev_assign;   // checked and copied at the start of the step; a bad label leaves the outputs untouched (close_step)
   // Many centroids: a step on its own pays for what a fit does once in its third step.  The points are rewritten
   // grouped by their incumbents and the first filter runs in front of the exact kernel (a million tiles of two slabs
