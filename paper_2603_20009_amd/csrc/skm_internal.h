@@ -467,7 +467,7 @@ struct StepReport {
   double objective;          // sum over the points of the squared distance found
   unsigned int flag;         // bit 0: list overflow, bit 1: a point without a centroid, bit 2: a label of the caller's outside [0, k)
   int32_t nempty, largest;   // of the cluster sizes
-  int32_t pad;
+  unsigned int seq;          // FinalizeArgs::seq, written when all else is there
   unsigned long long scal[SC_COUNT];   // the step scalars, replicas added up; SC_CHANGED = points with another label than prev
 };
 // Unpack best -> assign, dist (not if *flag is set already); cluster sizes into cnt[k] (zero before).  With `done` (a zero word) the launch also closes
@@ -487,6 +487,7 @@ struct FinalizeArgs {
   const unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]
   int nscal = SC_COUNT;               // scalars to report
   StepReport *report = nullptr;       // device-visible address of the page-locked block
+  unsigned int seq = 0;               // number of the report
   stamp_t *stamp = nullptr, *stamp_end = nullptr;   // start and (of the closing workgroup) end
 };
 hipError_t launch_finalize_assign(const FinalizeArgs &a, hipStream_t st);

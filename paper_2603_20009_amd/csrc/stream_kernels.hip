@@ -890,6 +890,10 @@ template <typename T>
 __device__ inline T load_agent(const T *p) {   // a value that other workgroups of this launch have written
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <typename T>
+__device__ inline void store_system(T *p, T v) {   // a value for the host: written through
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 template <int FIN_THREADS, int PER>
 __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeArgs a, int in_lds) {
@@ -1042,7 +1046,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     for (int j = 0; j < QR; ++j) v += sc[j];
 #pragma unroll
     for (int m = 1; m < QL; m <<= 1) v += __shfl_xor(v, m, 64);
-    if ((tid & (QL - 1)) == 0 && q < a.nscal && q != SC_CHANGED) r->scal[q] = v;
+    if ((tid & (QL - 1)) == 0 && q < a.nscal && q != SC_CHANGED) store_system(&r->scal[q], v);
   }
   int empty = 0, largest = 0;
   if (a.cnt) {
@@ -1076,10 +1080,11 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     for (int u = 0; u < w; ++u) parts[u] += parts[u + w];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) parts[0] += __shfl_down(parts[0], o, 64);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the counters have arrived: the host may take seq for all of the report)
   __syncthreads();
   if (tid == 0) {
-    r->objective = parts[0];
-    r->flag = flag_out;
+    store_system(&r->objective, parts[0]);
+    store_system(&r->flag, flag_out);
     int e = 0, l = 0;
     unsigned int changed = 0;
     for (int u = 0; u < NW; ++u) {
@@ -1087,10 +1092,12 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
       l = max(l, s_hist[NW + u]);
       changed += redc[u];
     }
-    r->nempty = e;
-    r->largest = l;
-    if (a.nscal > SC_CHANGED) r->scal[SC_CHANGED] = (unsigned long long)changed;
+    store_system(&r->nempty, e);
+    store_system(&r->largest, l);
+    if (a.nscal > SC_CHANGED) store_system(&r->scal[SC_CHANGED], (unsigned long long)changed);
     if (a.stamp_end) *a.stamp_end = wall_clock64();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    store_system(&r->seq, a.seq);
   }
 }
 
