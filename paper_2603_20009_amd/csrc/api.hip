@@ -593,7 +593,7 @@ struct Ctx {
   int32_t *scr_cnt = nullptr, *scr_first = nullptr, *scr_ntiles = nullptr, *scr_cols = nullptr, *scr_pos = nullptr;
   int2 *scr_tile_rt = nullptr;
   unsigned int *amax = nullptr;      // [AM_COUNT] magnitude bounds of the GEMM operands
-  enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8 };
+  enum { AM_XR = 0, AM_Y = 1, AM_X = 2, AM_Q = 3, AM_QR = 4, AM_COUNT = 8, AM_ROTATION = 8 };   // (the last: Rot's words, behind the others)
   unsigned int *xr_bound = nullptr;  // that of Xr: amax[AM_XR], or a word that is kept with the rows (fit_host_impl)
 
   // What a step reports: the finalize kernel writes it straight into this page-locked block (see PinnedCache), so the
@@ -680,8 +680,8 @@ struct Ctx {
   bool prev_counts = true;                 // changed points are counted against prev (false in the exact step)
 
   int alloc_bounds(stamp_t *stamp = nullptr) {
-    HIPCHK(pool.get(&amax, (size_t)AM_COUNT));
-    if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT, 0u, st, stamp));
+    HIPCHK(pool.get(&amax, (size_t)AM_COUNT + AM_ROTATION));
+    if (!pool.count_only) HIPCHK(launch_fill_u32(amax, AM_COUNT + AM_ROTATION, 0u, st, stamp));
     xr_bound = amax + AM_XR;
     return SKM_OK;
   }
@@ -690,6 +690,12 @@ struct Ctx {
   void clear_with(CentroidPrep &a) const {
     a.clear = reinterpret_cast<unsigned int *>(zblock);
     a.clear_words = (int64_t)(zbytes / sizeof(unsigned int));
+  }
+  bool best_filled = false;    // best holds ~0 throughout (see launch_opening)
+  int fill_best() {
+    if (!best_filled) HIPCHK(launch_fill_u64(best, n, ~0ull, st));
+    best_filled = false;
+    return SKM_OK;
   }
   bool y_amax_valid = false;   // amax[AM_Y] bounds the current Y (the update writes it; other changes of Y clear this)
   int measure_y() {
@@ -975,7 +981,7 @@ int filtered_nearest(Ctx &c, int32_t K, StageTimer &tm) {
   cp.stamp = start;
   c.clear_with(cp);
   HIPCHK(launch_prep_centroids(cp, c.st, ratio, nbK + 1));
-  HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
+  if (int rc = c.fill_best()) return rc;
   unsigned int *rowmin = reinterpret_cast<unsigned int *>(c.tau);   // (no thresholds while this runs)
   HIPCHK(launch_fill_u32(rowmin, c.n, 0xffffffffu, c.st));
   for (int32_t ch = 0; ch < c.nchunks; ++ch) {
@@ -1157,7 +1163,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   bool from_keys = false;   // the incumbents are the low halves of c.best
   stamp_t *tau_stamp = nullptr;
   if (!have_prev && !found) {
-    HIPCHK(launch_fill_u64(c.best, c.n, ~0ull, c.st));
+    if (int rc = c.fill_best()) return rc;
     GemmOperands g0{c.Xr, c.ldx, (int32_t)c.n, c.Y, c.ds, c.k, dprime};
     g0.a_absmax = c.xr_bound; g0.b_absmax = c.amax + Ctx::AM_Y;
     g0.b_presplit = c.Ys; g0.ldbs = split_ld(c.ds);
@@ -1582,9 +1588,10 @@ struct Rot {
     return SKM_OK;
   }
 };
-// (back = false: nothing will be rotated back, Rp is not made)
+static_assert(Rot::kSlots == Ctx::AM_ROTATION, "Rot's words behind those of a context");
+// (back = false: nothing will be rotated back, Rp is not made; jobs: what else opens the call)
 int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const float *R_dev, uint64_t seed, Rot &rot,
-                   bool back = true) {
+                   bool back = true, OpeningJobs jobs = OpeningJobs()) {
   if (int rc = rot.alloc_bounds(pool, st)) return rc;
   float *Rown = nullptr;
   if (!R_dev) {
@@ -1596,8 +1603,16 @@ int setup_rotation(Pool &pool, hipStream_t st, int32_t d, int32_t ds, const floa
   if (back) HIPCHK(pool.get(&rot.Rp, (size_t)d * ds));
   HIPCHK(pool.get(&rot.Rtp, (size_t)d * ds));
   if (d % 32 == 0) HIPCHK(pool.get(&rot.Rs, split_words(d, d)));
-  HIPCHK(launch_rotation_operands(R_dev, d, rot.Rp, rot.Rtp, ds, rot.amax, st));
+  jobs.R = R_dev; jobs.d = d; jobs.ld = ds;
+  jobs.Rp = rot.Rp; jobs.Rtp = rot.Rtp; jobs.r_bound = rot.amax;
+  HIPCHK(launch_opening(jobs, st));
   return SKM_OK;
+}
+GemmOperands rotation_product(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t ds, const Rot &rot, const unsigned int *in_bound) {
+  GemmOperands g{in, ldin, (int32_t)rows, rot.Rtp, ds, d, d};
+  g.a_absmax = in_bound; g.b_absmax = rot.amax;
+  g.b_split = rot.Rs;
+  return g;
 }
 // out (rows x ds, zero padded) = in (rows x d, stride ldin) * R
 // out_absmax (optional, zero before the call) receives the bit pattern of max |out|
@@ -1611,9 +1626,7 @@ int rotate_into(const float *in, int64_t ldin, int64_t rows, int32_t d, int32_t 
     HIPCHK(launch_absmax(in, ldin, rows, d, slot, st));
     in_bound = slot;
   }
-  GemmOperands g{in, ldin, (int32_t)rows, rot.Rtp, ds, d, d};
-  g.a_absmax = in_bound; g.b_absmax = rot.amax;
-  g.b_split = rot.Rs;
+  GemmOperands g = rotation_product(in, ldin, rows, d, ds, rot, in_bound);
   g.stamp = stamp;
   HIPCHK(gemm_store(g, out, ds, ds, 1.f, 0.f, st, out_absmax));
   return SKM_OK;
@@ -1813,6 +1826,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
 
   // ---- Algorithm 1: R, X~ = X R
   Rot rot;
+  rot.amax = c.amax + Ctx::AM_COUNT;
   float *Xr_own = nullptr;
   if (p.rotate) {
     // The rotation matrix is made by a chain of small kernels that leaves most of the device idle: the pass over X
@@ -1838,7 +1852,12 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
       HIPCHK(launch_absmax(X, d, n, d, x_bound, side.s, 1024));   // four workgroups per CU: the generator's kernels find room
       HIPCHK(hipEventRecord(e_join, side.s));
     }
-    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, seed, rot);
+    OpeningJobs jobs;
+    if (!beside) {
+      if ((rc = rot.next_slot(c.st, &x_bound))) return rc;
+      jobs.bound[0] = {X, n * (int64_t)d, x_bound};
+    }
+    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, seed, rot, true, jobs);
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
     if (beside) HIPCHK(hipStreamWaitEvent(c.st, e_join, 0));
@@ -2457,13 +2476,22 @@ int assign_impl(const float *X, int64_t n, int32_t d, const float *centroids, in
   rc = c.alloc_common(p.pair_budget, p.dense_frac, false);
   if (rc) return rc;
   if (p.rotate) {
-    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, 0, rot, false);
+    OpeningJobs jobs;
+    unsigned int *x_bound = nullptr, *y_bound = nullptr;
+    rot.amax = c.amax + Ctx::AM_COUNT;
+    if ((rc = rot.next_slot(c.st, &x_bound)) || (rc = rot.next_slot(c.st, &y_bound))) return rc;
+    jobs.bound[0] = {X, n * (int64_t)d, x_bound};
+    jobs.bound[1] = {centroids, k * (int64_t)d, y_bound};
+    if (!prev_assign) {   // (the search for the incumbents starts from keys of ~0)
+      jobs.fill = c.best;
+      jobs.nfill = n;
+      c.best_filled = true;
+    }
+    rc = setup_rotation(c.pool, c.st, d, c.ds, p.R, 0, rot, false, jobs);
     if (rc) return rc;
     HIPCHK(c.pool.get(&Xr_own, (size_t)n * c.ds));
-    rc = rotate_into(X, d, n, d, c.ds, rot, Xr_own, c.st, c.xr_bound);
-    if (rc) return rc;
-    rc = rotate_into(centroids, d, k, d, c.ds, rot, c.Y, c.st, c.amax + Ctx::AM_Y);
-    if (rc) return rc;
+    const GemmOperands gx = rotation_product(X, d, n, d, c.ds, rot, x_bound), gy = rotation_product(centroids, d, k, d, c.ds, rot, y_bound);
+    HIPCHK(gemm_store_two(gx, Xr_own, c.xr_bound, gy, c.Y, c.amax + Ctx::AM_Y, c.ds, c.ds, c.st));
     c.y_amax_valid = true;
     c.Xr = Xr_own; c.ldx = c.ds;
   } else {
@@ -3154,15 +3182,20 @@ int skm_assign_exact(const float *X, int64_t n, int32_t d, const float *centroid
   HIPCHK(pool.get(&amax, 2));
   HIPCHK(pool.get(&ysplit, split_words(k, ds)));
   HIPCHK(launch_fill_u32(amax, 2, 0u, st));
-  HIPCHK(launch_absmax(X, d, n, d, amax, st));
-  HIPCHK(launch_absmax(centroids, d, k, d, amax + 1, st));
-  if (pad_y) HIPCHK(launch_pad_copy(centroids, d, k, d, Yo, ds, ds, 0, st));
+  OpeningJobs jobs;
+  jobs.bound[0] = {X, n * (int64_t)d, amax};
+  jobs.bound[1] = {centroids, k * (int64_t)d, amax + 1};
+  if (pad_y) {
+    jobs.src = centroids; jobs.lds = d; jobs.rows = k; jobs.cols = d;
+    jobs.dst = Yo; jobs.ldd = ds; jobs.dpad = ds;
+  }
+  jobs.fill = best; jobs.nfill = n;
+  HIPCHK(launch_opening(jobs, st));
   const float *Yp = pad_y ? Yo : centroids;
   CentroidPrep cp{Yp, ds, k, ds};
   cp.ynorm = ynorm; cp.dn = ds;
   cp.Ys = ysplit; cp.y_absmax = amax + 1;
   HIPCHK(launch_prep_centroids(cp, st));
-  HIPCHK(launch_fill_u64(best, n, ~0ull, st));
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = std::min<int64_t>(chunk, n - r0);
     const float *Xp = X + r0 * d;
@@ -3265,8 +3298,12 @@ int skm_rotate(const float *X, int64_t n, int32_t d, const float *R, int32_t tra
   HIPCHK(pool.get(&B, (size_t)d * ds));
   HIPCHK(pool.get(&amax, 2));
   HIPCHK(launch_fill_u32(amax, 2, 0u, st));
-  HIPCHK(launch_rotation_operands(R, d, transpose ? B : nullptr, transpose ? nullptr : B, ds, amax + 1, st));
-  HIPCHK(launch_absmax(X, d, n, d, amax, st));
+  OpeningJobs jobs;
+  jobs.R = R; jobs.d = d; jobs.ld = ds; jobs.r_bound = amax + 1;
+  (transpose ? jobs.Rp : jobs.Rtp) = B;
+  if (n * (int64_t)d >= 4) jobs.bound[0] = {X, n * (int64_t)d, amax};
+  else HIPCHK(launch_absmax(X, d, n, d, amax, st));
+  HIPCHK(launch_opening(jobs, st));
   GemmOperands g{X, d, (int32_t)n, B, ds, d, d};
   g.a_absmax = amax; g.b_absmax = amax + 1;
   if (d % 32 == 0) HIPCHK(pool.get(&g.b_split, split_words(d, d)));

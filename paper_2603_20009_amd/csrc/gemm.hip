@@ -64,9 +64,7 @@ struct EpiArgs<EPI_ARGMIN> {
 // contiguous range of logical tile ids, and walk the tiles in panels of PC column tiles with the
 // row tile advancing slowest inside a panel, so that the workgroups resident on one XCD share a
 // few row tiles of A and one panel of B.
-__device__ inline void tile_of_block(int nrt, int nct, int PC, int &rt, int &ct) {
-  const int nwg = gridDim.x;
-  const int bid = blockIdx.x;
+__device__ inline void tile_of_block(int nwg, int bid, int nrt, int nct, int PC, int &rt, int &ct) {
   const int xcd = bid & 7, q = bid >> 3;
   const int base = nwg >> 3, rem = nwg & 7;
   const int logical = xcd * base + (xcd < rem ? xcd : rem) + q;
@@ -189,7 +187,7 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
 
   const int nrt = (g.M + BM - 1) / BM, nct = (g.N + BN - 1) / BN;
   int rt, ct;
-  tile_of_block(nrt, nct, g.panel_cols, rt, ct);
+  tile_of_block(gridDim.x, blockIdx.x, nrt, nct, g.panel_cols, rt, ct);
   const int row0 = rt * BM, col0 = ct * BN;
 
   float4 ra[A_F4], rb[B_F4];
@@ -307,10 +305,34 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
 constexpr int SBK = 32, SLS = SBK + 4;
 constexpr int S_F4 = BM * (SBK / 4) / NTHREADS;   // float4 staged per thread and operand: 4
 
-template <int EPI>
+// A second product with the same B behind the first (its workgroups are the last ones): a small one costs a launch and leaves
+// most of the device idle by itself.  Rotating 20 000 rows of 1536 dimensions and 1024 centroids, 326 and 46 us in two launches,
+// takes 340; 64 rows and 100 of 128, 11 and 11, take 11.5.
+struct SecondProduct {
+  const float *A = nullptr;
+  int64_t lda = 0;
+  int32_t M = 0;
+  const unsigned int *a_absmax = nullptr;
+  float *C = nullptr;
+  int64_t ldc = 0;
+  unsigned int *c_absmax = nullptr;
+  int32_t first = 0;   // workgroup
+};
+template <int EPI, bool TWO = false>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
+gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e, typename std::conditional<TWO, SecondProduct, int>::type second) {
   put_stamp(g.stamp);
+  int nwg = gridDim.x, bid = blockIdx.x;
+  if constexpr (TWO) {
+    if (bid >= second.first) {
+      g.A = second.A; g.lda = second.lda; g.M = second.M; g.a_absmax = second.a_absmax;
+      e.C = second.C; e.ldc = second.ldc; e.c_absmax = second.c_absmax;
+      bid -= second.first;
+      nwg -= second.first;
+    } else {
+      nwg = second.first;
+    }
+  }
   extern __shared__ __align__(16) float smem[];
   float *As = smem;                    // [2][BM][SLS]
   float *Bs = smem + 2 * BM * SLS;     // [2][BN][SLS]
@@ -322,7 +344,7 @@ gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e) {
 
   const int nrt = (g.M + BM - 1) / BM, nct = (g.N + BN - 1) / BN;
   int rt, ct;
-  tile_of_block(nrt, nct, g.panel_cols, rt, ct);
+  tile_of_block(nwg, bid, nrt, nct, g.panel_cols, rt, ct);
   const int row0 = rt * BM, col0 = ct * BN;
 
   const unsigned int ma = *g.a_absmax, mb = *g.b_absmax;
@@ -517,7 +539,7 @@ __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, cons
 
   const int nrt = (g.M + T2 - 1) / T2, nct = (g.N + T2 - 1) / T2;
   int rt, ct;
-  tile_of_block(nrt, nct, g.panel_cols, rt, ct);
+  tile_of_block(gridDim.x, blockIdx.x, nrt, nct, g.panel_cols, rt, ct);
   const int row0 = rt * T2, col0 = ct * T2;
 
   const unsigned int ma = *g.a_absmax, mb = *g.b_absmax;
@@ -808,7 +830,7 @@ static hipError_t launch_split(const GemmOperands &g, const typename EpiArgs<EPI
   const int64_t nwg = nrt * nct;
   if (nwg <= 0) return hipSuccess;
   if (nwg > kMaxTilesPerLaunchFwd) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NTHREADS), smem_bytes<SBK>(), st, g, e);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NTHREADS), smem_bytes<SBK>(), st, g, e, 0);
   return hipGetLastError();
 }
 
@@ -944,6 +966,29 @@ hipError_t gemm_store(const GemmOperands &g, float *C, int64_t ldc, int32_t Nsto
                       hipStream_t st, unsigned int *c_absmax) {
   StoreArgs e{C, ldc, Nstore < g.N ? g.N : Nstore, alpha, beta, c_absmax};
   return launch_any<EPI_STORE>(g, e, st);
+}
+
+hipError_t gemm_store_two(const GemmOperands &g, float *C, unsigned int *c_absmax, const GemmOperands &h, float *D, unsigned int *d_absmax,
+                          int64_t ldc, int32_t Nstore, hipStream_t st) {
+  auto narrow = [](const GemmOperands &x) {
+    return x.M > 0 && x.N > 0 && operands_aligned(x) && x.K >= SBK && x.a_absmax && x.b_absmax && !wants_split256(x);
+  };
+  const int64_t nct = (g.N + BN - 1) / BN, first = (g.M + BM - 1) / BM * nct, all = first + (h.M + BM - 1) / BM * nct;
+  if (!narrow(g) || !narrow(h) || h.B != g.B || h.ldb != g.ldb || h.N != g.N || h.K != g.K || h.b_absmax != g.b_absmax ||
+      all > kMaxTilesPerLaunch || g_max_tiles.load(std::memory_order_relaxed) > 0) {
+    hipError_t rc = gemm_store(g, C, ldc, Nstore, 1.f, 0.f, st, c_absmax);
+    return rc == hipSuccess ? gemm_store(h, D, ldc, Nstore, 1.f, 0.f, st, d_absmax) : rc;
+  }
+  auto kern = gemm_split_kernel<EPI_STORE, true>;
+  static const hipError_t attr_rc = hipFuncSetAttribute(
+      reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<SBK>());
+  if (attr_rc != hipSuccess) return attr_rc;
+  GemmOperands gb = g;
+  gb.panel_cols = panel_cols_for(nct);
+  const StoreArgs e{C, ldc, Nstore < g.N ? g.N : Nstore, 1.f, 0.f, c_absmax};
+  const SecondProduct s{h.A, h.lda, h.M, h.a_absmax, D, ldc, d_absmax, (int32_t)first};
+  hipLaunchKernelGGL(kern, dim3((unsigned)all), dim3(NTHREADS), smem_bytes<SBK>(), st, gb, e, s);
+  return hipGetLastError();
 }
 
 hipError_t gemm_argmin(const GemmOperands &g, const float *ynorm, unsigned long long *best, hipStream_t st) {

@@ -194,6 +194,9 @@ hipError_t launch_absmax(const float *A, int64_t lda, int64_t rows, int32_t cols
 // If c_absmax is given, max |C| is folded into *c_absmax (as launch_absmax does).
 hipError_t gemm_store(const GemmOperands &g, float *C, int64_t ldc, int32_t Nstore, float alpha, float beta,
                       hipStream_t st, unsigned int *c_absmax = nullptr);
+// C and D (rows of ldc) = the products g and h, which share B; in one launch where neither is tall
+hipError_t gemm_store_two(const GemmOperands &g, float *C, unsigned int *c_absmax, const GemmOperands &h, float *D, unsigned int *d_absmax,
+                          int64_t ldc, int32_t Nstore, hipStream_t st);
 
 // best[i] = min(best[i], pack_key(ynorm[j] - 2 s(i,j), j)) over all j: the row argmin of the squared
 // distance up to the per-row constant ||x_i||^2 (Algorithm 1, iteration 1).
@@ -568,9 +571,26 @@ hipError_t launch_split(float *Y, int64_t ldy, int32_t d, const int32_t *pairs_d
 hipError_t launch_gather_rows(const float *src, int64_t lds, int32_t d, const int64_t *idx, int32_t k, float *dst,
                               int64_t ldd, int32_t dpad, hipStream_t st, unsigned int *absmax = nullptr,
                               stamp_t *stamp = nullptr);
-// Rp (stride ld, zero padded to it) = R, Rtp likewise = R^T (either may be NULL), max |R| folded into *absmax
-hipError_t launch_rotation_operands(const float *R, int32_t d, float *Rp, float *Rtp, int32_t ld, unsigned int *absmax,
-                                    hipStream_t st);
+// Jobs that open a call, independent of each other, in one launch: the bounds of the operands, the copies of the rotation matrix, a
+// padded copy, keys set to ~0.
+struct OpeningJobs {
+  struct Bound {
+    const float *A = nullptr;      // count >= 4 values without gaps
+    int64_t count = 0;
+    unsigned int *out = nullptr;   // max |A| is folded into it
+  } bound[2];
+  const float *R = nullptr;        // d x d: Rp = R, Rtp = R^T (either may be NULL), rows of ld, zero padded; max |R| folded into r_bound
+  int32_t d = 0, ld = 0;
+  float *Rp = nullptr, *Rtp = nullptr;
+  unsigned int *r_bound = nullptr;
+  const float *src = nullptr;      // dst = src as in launch_pad_copy
+  float *dst = nullptr;
+  int64_t lds = 0, ldd = 0, rows = 0;
+  int32_t cols = 0, dpad = 0;
+  unsigned long long *fill = nullptr;
+  int64_t nfill = 0;
+};
+hipError_t launch_opening(const OpeningJobs &j, hipStream_t st);
 hipError_t launch_pad_copy(const float *src, int64_t lds, int64_t n, int32_t d, float *dst, int64_t ldd, int32_t dpad,
                            int32_t transpose, hipStream_t st);
 

@@ -1019,3 +1019,20 @@ def test_fit_without_memory_for_the_order(skm, dg):  # noqa: F811
     assert sum(r["listed_tiles"] for r in a.trace) < sum(r["listed_tiles"] for r in b.trace)
     assert float((a.centroids - b.centroids).norm() / a.centroids.norm()) < 1e-4
     assert float((a.assign != b.assign).float().mean()) <= 1e-3
+
+
+# A call with a rotation multiplies its rows and its centroids in one launch, behind one that takes both bounds and the copies of
+# the matrix (rows that are not aligned, and the tall form, in launches of their own).  On rows that were rotated before the call
+# labels and distances are the same bits.
+@pytest.mark.parametrize("n,k,d", [(1, 1, 32), (127, 129, 32), (128, 128, 48), (129, 1, 100), (300, 257, 128), (1000, 3, 132),
+                                   (64, 100, 33), (257, 130, 30), (5000, 700, 272), (140_000, 40, 128), (3, 2, 16)])
+def test_rows_and_centroids_rotated_together(skm, dg, n, k, d):  # noqa: F811
+    say("rotated together", n, k, d)
+    X = dg.mixture(n, d, 20, 3, "linear", "cuda")
+    Y = dg.mixture(k, d, 20, 3, "linear", "cuda", sample_seed=4)
+    R = skm.make_rotation(d, 9)
+    prev = torch.randint(0, k, (n,), generator=torch.Generator().manual_seed(1)).int().cuda()
+    for p in (None, prev):
+        a, da, _ = skm.assign(X, Y, p, opts=skm.FitOptions(R=R))
+        b, db, _ = skm.assign(skm.rotate(X, R), skm.rotate(Y, R), p, opts=skm.FitOptions(rotate=False))
+        assert torch.equal(a, b) and torch.equal(da, db)
