@@ -1147,6 +1147,24 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
                         ((c.n + 127) / 128) * (int64_t)((c.k + kListCols - 1) / kListCols) >= 1200;
   bool screen = c.colmask && nb > 0 &&
                 (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
+  // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
+  // far less usefully than those of iteration 2)
+  const bool again = c.permuted;
+  bool regroup = c.regroup_left > 0 && c.xnp_valid && c.Xr2 && have_prev && c.pruned_steps >= 1 &&
+                 (again ? regroup_pays_again(c.regroup_left, c.k, c.moved, c.n) : regroup_pays(c.regroup_left, c.k)) &&
+                 c.max_cluster >= 0 && c.max_cluster <= update_sort_cap();   // (see below)
+  // In a fit the points lie by quarters of their distance first, and by label inside a quarter: a point far from its centroid
+  // keeps most columns of its row tile alive, so that the three quarters near theirs are better off without it.  The distances are
+  // those of the step before (to the centroids as they were): there is no pass for them.  Column tiles a row tile lists, by label
+  // -> by quarters, steps 3, 4 and 7: 1M x 1536, k = 4096 32 -> 32, 18.8 -> 14.8, 13.4 -> 11.1, 1M x 768, k = 4096 (steps 3 and 4)
+  // 20.0 -> 12.2, 8.3 -> 6.5; halves and eighths of the distances list 2 to 15 % more.  Whole fits 201.9 -> 183.9 and 62.2 -> 59.3
+  // ms, 300 000 x 512, k = 1500 9.93 -> 9.51, 150 000 x 256, k = 900 3.66 -> 3.57.  The nine small launches (30 to 60 us) are not
+  // earned back below 2^34 products a step: 120 001 x 208, k = 777 (2^34.2) 2.21 -> 2.21, 40 000 x 384, k = 250 1.60 -> 1.59, 60 000 x
+  // 448, k = 256 1.64 -> 1.66, 20 000 x 512, k = 100 1.40 -> 1.42.
+  const bool by_quarters = regroup && (double)c.n * c.ds * c.k >= 0x1p34;
+  // The thresholds of short rows are taken beside the pass over the centroids, where nothing else comes in between.
+  const bool thresholds_done = have_prev && !c.prev_in && !c.group_now && !regroup && c.tau_kept == Ctx::KEPT_NONE && c.xnp_valid &&
+                               !(screen && !c.xh_valid) && c.ds <= 256;
   // theta ratio at checkpoint m: t_m = min(d, d' + 64 m) dimensions seen
   float ratio[kMaxBlocks + 1];
   for (int m = 0; m <= nb; ++m) ratio[m] = (float)theta_ratio(c.d, std::min(c.d, dprime + kBlockDims * m), eps0);
@@ -1158,7 +1176,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     cp.ratio_out = c.ratio_dev;
     cp.stamp = tm.mark(sought ? ST_GEMM : ST_NONE);   // (the search for the incumbents ends here)
     c.clear_with(cp);
-    HIPCHK(launch_prep_centroids(cp, c.st, ratio, nb + 1));
+    const ShortThresholds t{c.Xr, c.ldx, c.n, c.prev, c.tau, c.best};
+    HIPCHK(launch_prep_centroids(cp, c.st, ratio, nb + 1, thresholds_done ? &t : nullptr));
   }
   bool from_keys = false;   // the incumbents are the low halves of c.best
   stamp_t *tau_stamp = nullptr;
@@ -1177,20 +1196,6 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   } else if (have_prev && c.prev_in) {
     HIPCHK(launch_copy_labels(c.prev_in, c.n, c.k, c.prev, c.flag, c.st));
   }
-  // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
-  // far less usefully than those of iteration 2)
-  const bool again = c.permuted;
-  bool regroup = c.regroup_left > 0 && c.xnp_valid && c.Xr2 && have_prev && c.pruned_steps >= 1 &&
-                 (again ? regroup_pays_again(c.regroup_left, c.k, c.moved, c.n) : regroup_pays(c.regroup_left, c.k));
-  // In a fit the points lie by quarters of their distance first, and by label inside a quarter: a point far from its centroid
-  // keeps most columns of its row tile alive, so that the three quarters near theirs are better off without it.  The distances are
-  // those of the step before (to the centroids as they were): there is no pass for them.  Column tiles a row tile lists, by label
-  // -> by quarters, steps 3, 4 and 7: 1M x 1536, k = 4096 32 -> 32, 18.8 -> 14.8, 13.4 -> 11.1, 1M x 768, k = 4096 (steps 3 and 4)
-  // 20.0 -> 12.2, 8.3 -> 6.5; halves and eighths of the distances list 2 to 15 % more.  Whole fits 201.9 -> 183.9 and 62.2 -> 59.3
-  // ms, 300 000 x 512, k = 1500 9.93 -> 9.51, 150 000 x 256, k = 900 3.66 -> 3.57.  The nine small launches (30 to 60 us) are not
-  // earned back below 2^34 products a step: 120 001 x 208, k = 777 (2^34.2) 2.21 -> 2.21, 40 000 x 384, k = 250 1.60 -> 1.59, 60 000 x
-  // 448, k = 256 1.64 -> 1.66, 20 000 x 512, k = 100 1.40 -> 1.42.
-  const bool by_quarters = regroup && (double)c.n * c.ds * c.k >= 0x1p34;
   bool by_threshold = false;   // the new order follows the thresholds before the labels
   if (c.group_now && !c.permuted && c.Xr2) {
     // A step on its own (no update before it left an order): the points are grouped by the incumbents they come with
@@ -1269,6 +1274,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
     c.moved = 0;
     c.permuted = true;
     c.xh_valid = c.Xh != nullptr;
+  } else if (thresholds_done) {
+    // (already)
   } else if (have_prev && c.tau_kept != Ctx::KEPT_NONE && c.xnp_valid && !(screen && !c.xh_valid)) {
     HIPCHK(launch_tau_kept(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau_kept == Ctx::KEPT_ALL ? nullptr : c.touched, c.tau, c.best,
                            c.st, tau_stamp));

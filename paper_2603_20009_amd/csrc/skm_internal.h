@@ -454,7 +454,16 @@ struct ThetaRatios {
   int n;
   float v[kMaxBlocks + 1];
 };
-hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio = nullptr, int nratio = 0);
+// thresholds (optional, ds <= 256): those of launch_tau_init for labelled rows, against the same centroids
+struct ShortThresholds {
+  const float *Xr;
+  int64_t ldx, n;
+  const int32_t *labels;
+  float *tau;
+  unsigned long long *best;
+};
+hipError_t launch_prep_centroids(const CentroidPrep &a, hipStream_t st, const float *ratio = nullptr, int nratio = 0,
+                                 const ShortThresholds *thresholds = nullptr);
 
 // every non-zero row of A scaled to unit Euclidean length, in place (cols, lda multiples of 4; A 16-byte aligned)
 // (absmax, optional: max |A| of the scaled rows is folded into it)

@@ -1036,3 +1036,18 @@ def test_rows_and_centroids_rotated_together(skm, dg, n, k, d):  # noqa: F811
         a, da, _ = skm.assign(X, Y, p, opts=skm.FitOptions(R=R))
         b, db, _ = skm.assign(skm.rotate(X, R), skm.rotate(Y, R), p, opts=skm.FitOptions(rotate=False))
         assert torch.equal(a, b) and torch.equal(da, db)
+
+
+# Up to 256 dimensions the thresholds of a step are taken in the launch that prepares its centroids (a form for each 128), beyond
+# in one of their own.  With tests that drop nothing the last labels are the nearest centroids, at their direct distances.
+@pytest.mark.parametrize("d", [16, 112, 128, 130, 144, 250, 256, 272])
+def test_thresholds_beside_the_centroids(skm, d):  # noqa: F811
+    say("thresholds beside the centroids", d)
+    n, k = 3001, 37
+    X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).cuda()
+    r = skm.fit(X, k, 4, 3, skm.FitOptions(rotate=False, eps0=100.0))
+    D = torch.cdist(X.double(), r.centroids.double(), compute_mode="donot_use_mm_for_euclid_dist") ** 2
+    near, at = D.topk(2, 1, largest=False)
+    clear = near[:, 1] - near[:, 0] > 1e-4 * near[:, 0]      # fp32 distances of 22-bit products
+    assert torch.equal(r.assign[clear].long(), at[clear, 0])
+    assert bool(((r.dist.double() - near[:, 0]).abs() <= 1e-4 * near[:, 0] + 1e-6).all())      # (a cluster of one point: 0)
