@@ -76,6 +76,34 @@ __device__ inline void tile_of_block(int nwg, int bid, int nrt, int nct, int PC,
   ct = p * PC + (r - rt * pc);
 }
 
+// A second product with the same B behind the first (its workgroups are the last ones): a small one costs a launch and leaves
+// most of the device idle by itself.  Rotating 20 000 rows of 1536 dimensions and 1024 centroids, 326 and 46 us in two launches,
+// takes 340 (in the larger tiles 300); 64 rows and 100 of 128, 11 and 11, take 11.5.
+struct SecondProduct {
+  const float *A = nullptr;
+  int64_t lda = 0;
+  int32_t M = 0;
+  const unsigned int *a_absmax = nullptr;
+  float *C = nullptr;
+  int64_t ldc = 0;
+  unsigned int *c_absmax = nullptr;
+  int32_t first = 0;   // workgroup
+};
+template <bool TWO> using second_t = typename std::conditional<TWO, SecondProduct, int>::type;
+// this workgroup's product, and its place among those of the product
+template <class E>
+__device__ inline void choose_product(GemmOperands &g, E &e, int, int &, int &) {}
+__device__ inline void choose_product(GemmOperands &g, StoreArgs &e, const SecondProduct &second, int &nwg, int &bid) {
+  if (bid < second.first) {
+    nwg = second.first;
+    return;
+  }
+  g.A = second.A; g.lda = second.lda; g.M = second.M; g.a_absmax = second.a_absmax;
+  e.C = second.C; e.ldc = second.ldc; e.c_absmax = second.c_absmax;
+  bid -= second.first;
+  nwg -= second.first;
+}
+
 // Epilogues of a finished TB x TB tile (TB / 64 wavefronts each way).  `unscale` turns an accumulator into the
 // score s(i, j).  Accumulator layout of the 32 x 32 MFMA results: register v of lane (r32, kh) holds
 // row 8*(v/4) + 4*kh + (v%4), column r32 of the 32 x 32 tile.
@@ -305,34 +333,12 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmOperands g, typename
 constexpr int SBK = 32, SLS = SBK + 4;
 constexpr int S_F4 = BM * (SBK / 4) / NTHREADS;   // float4 staged per thread and operand: 4
 
-// A second product with the same B behind the first (its workgroups are the last ones): a small one costs a launch and leaves
-// most of the device idle by itself.  Rotating 20 000 rows of 1536 dimensions and 1024 centroids, 326 and 46 us in two launches,
-// takes 340; 64 rows and 100 of 128, 11 and 11, take 11.5.
-struct SecondProduct {
-  const float *A = nullptr;
-  int64_t lda = 0;
-  int32_t M = 0;
-  const unsigned int *a_absmax = nullptr;
-  float *C = nullptr;
-  int64_t ldc = 0;
-  unsigned int *c_absmax = nullptr;
-  int32_t first = 0;   // workgroup
-};
 template <int EPI, bool TWO = false>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e, typename std::conditional<TWO, SecondProduct, int>::type second) {
+gemm_split_kernel(GemmOperands g, typename EpiArgs<EPI>::type e, second_t<TWO> second) {
   put_stamp(g.stamp);
   int nwg = gridDim.x, bid = blockIdx.x;
-  if constexpr (TWO) {
-    if (bid >= second.first) {
-      g.A = second.A; g.lda = second.lda; g.M = second.M; g.a_absmax = second.a_absmax;
-      e.C = second.C; e.ldc = second.ldc; e.c_absmax = second.c_absmax;
-      bid -= second.first;
-      nwg -= second.first;
-    } else {
-      nwg = second.first;
-    }
-  }
+  choose_product(g, e, second, nwg, bid);
   extern __shared__ __align__(16) float smem[];
   float *As = smem;                    // [2][BM][SLS]
   float *Bs = smem + 2 * BM * SLS;     // [2][BN][SLS]
@@ -526,10 +532,12 @@ constexpr int T2 = 256, NT2 = 1024;
 constexpr int T2_STAGE = 2 * T2 * 32;   // words of one slab of both operands (A rows, then B rows)
 #define SKM_GEMM_VMCNT0() __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8))   // all vector memory operations done
 
-template <int EPI>
+template <int EPI, bool TWO = false>
 __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, const uint32_t *Bsplit, int64_t ldbs,
-                                                            typename EpiArgs<EPI>::type e) {
+                                                            typename EpiArgs<EPI>::type e, second_t<TWO> second) {
   put_stamp(g.stamp);
+  int nwg = gridDim.x, bid = blockIdx.x;
+  choose_product(g, e, second, nwg, bid);
   extern __shared__ __align__(16) float smem[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(smem);   // [2 stages][A 256 rows | B 256 rows][32 words]
   const int tid = threadIdx.x;
@@ -539,7 +547,7 @@ __global__ void __launch_bounds__(NT2) gemm_split256_kernel(GemmOperands g, cons
 
   const int nrt = (g.M + T2 - 1) / T2, nct = (g.N + T2 - 1) / T2;
   int rt, ct;
-  tile_of_block(gridDim.x, blockIdx.x, nrt, nct, g.panel_cols, rt, ct);
+  tile_of_block(nwg, bid, nrt, nct, g.panel_cols, rt, ct);
   const int row0 = rt * T2, col0 = ct * T2;
 
   const unsigned int ma = *g.a_absmax, mb = *g.b_absmax;
@@ -868,7 +876,7 @@ static hipError_t launch_split256(const GemmOperands &g, const typename EpiArgs<
   if (nwg <= 0) return hipSuccess;
   if (nwg > (1 << 22) - 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NT2), smem, st, g,
-                     g.b_presplit ? g.b_presplit : (const uint32_t *)g.b_split, g.b_presplit ? g.ldbs : (int64_t)split_ld(g.K), e);
+                     g.b_presplit ? g.b_presplit : (const uint32_t *)g.b_split, g.b_presplit ? g.ldbs : (int64_t)split_ld(g.K), e, 0);
   return hipGetLastError();
 }
 
@@ -968,27 +976,48 @@ hipError_t gemm_store(const GemmOperands &g, float *C, int64_t ldc, int32_t Nsto
   return launch_any<EPI_STORE>(g, e, st);
 }
 
+// The 256 x 256 form for the two together: where their tiles fill whole rounds of the CUs to four fifths (one workgroup a CU; the
+// smaller tiles, two a CU, leave less idle).  Products of n x d by d x d, 128 -> 256 in us, by the share of the last round that is
+// filled: 20 000 x 1536 (0.93) 366 -> 327, 21 000 (0.97) 373 -> 337, 10 000 (0.94) 204 -> 190, 15 000 x 1024 (0.92) 148 -> 137, 20 000 x 768
+// (0.93) 123 -> 115, 60 000 x 256 (0.92) 78 -> 72, 40 000 x 1024 (0.82) 325 -> 323; 25 000 x 1536 (0.77) 455 -> 453, 15 000 x 1536 (0.69)
+// 286 -> 304, 20 000 x 1024 (0.62) 182 -> 216, 5000 x 1536 (0.47) 127 -> 161.  Whole assignments, before and after: 20 000 x 1536 to 1024
+// centroids 833 -> 793, 55 000 x 256 to 2000 441 -> 426, 60 000 x 224 to 5 367 -> 354, 100 000 x 1536 to 1024 3850 -> 3805.  The products of
+// both are equally exact (against 64 bits: maximum 6.4e-6, root mean square 4.4e-7 at 1536 normal values).
+static bool wants_split256_two(const GemmOperands &g, const GemmOperands &h) {
+  if (!g.b_split || g.K % 32 != 0 || g.K < 64 || !aligned16(g.b_split) || g_tile256.load(std::memory_order_relaxed) >= 0) return false;
+  const int64_t nct = (g.N + T2 - 1) / T2, tiles = ((g.M + T2 - 1) / T2 + (h.M + T2 - 1) / T2) * nct, cus = num_cus();
+  const int64_t slots = (tiles + cus - 1) / cus * cus;
+  return nct * T2 * 4 <= (int64_t)g.N * 5 && tiles * 5 >= slots * 4 && tiles <= (1 << 22) - 1;
+}
+
+template <auto KERN, class... A>
+static hipError_t launch_two(int64_t nwg, int threads, size_t smem, hipStream_t st, const A &...args) {
+  static const hipError_t attr_rc =
+      hipFuncSetAttribute(reinterpret_cast<const void *>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (attr_rc != hipSuccess) return attr_rc;
+  hipLaunchKernelGGL(KERN, dim3((unsigned)nwg), dim3((unsigned)threads), smem, st, args...);
+  return hipGetLastError();
+}
 hipError_t gemm_store_two(const GemmOperands &g, float *C, unsigned int *c_absmax, const GemmOperands &h, float *D, unsigned int *d_absmax,
                           int64_t ldc, int32_t Nstore, hipStream_t st) {
-  auto narrow = [](const GemmOperands &x) {
-    return x.M > 0 && x.N > 0 && operands_aligned(x) && x.K >= SBK && x.a_absmax && x.b_absmax && !wants_split256(x);
-  };
-  const int64_t nct = (g.N + BN - 1) / BN, first = (g.M + BM - 1) / BM * nct, all = first + (h.M + BM - 1) / BM * nct;
-  if (!narrow(g) || !narrow(h) || h.B != g.B || h.ldb != g.ldb || h.N != g.N || h.K != g.K || h.b_absmax != g.b_absmax ||
-      all > kMaxTilesPerLaunch || g_max_tiles.load(std::memory_order_relaxed) > 0) {
+  auto splits = [](const GemmOperands &x) { return x.M > 0 && x.N > 0 && operands_aligned(x) && x.K >= SBK && x.a_absmax && x.b_absmax; };
+  const bool same = splits(g) && splits(h) && h.B == g.B && h.ldb == g.ldb && h.N == g.N && h.K == g.K && h.b_absmax == g.b_absmax &&
+                    g_max_tiles.load(std::memory_order_relaxed) <= 0;
+  const bool wide = same && wants_split256_two(g, h);
+  const int64_t edge = wide ? T2 : BM, nct = (g.N + edge - 1) / edge, first = (g.M + edge - 1) / edge * nct,
+                all = first + (h.M + edge - 1) / edge * nct;
+  if (!same || (!wide && (wants_split256(g) || wants_split256(h) || all > kMaxTilesPerLaunch))) {
     hipError_t rc = gemm_store(g, C, ldc, Nstore, 1.f, 0.f, st, c_absmax);
     return rc == hipSuccess ? gemm_store(h, D, ldc, Nstore, 1.f, 0.f, st, d_absmax) : rc;
   }
-  auto kern = gemm_split_kernel<EPI_STORE, true>;
-  static const hipError_t attr_rc = hipFuncSetAttribute(
-      reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<SBK>());
-  if (attr_rc != hipSuccess) return attr_rc;
   GemmOperands gb = g;
   gb.panel_cols = panel_cols_for(nct);
   const StoreArgs e{C, ldc, Nstore < g.N ? g.N : Nstore, 1.f, 0.f, c_absmax};
   const SecondProduct s{h.A, h.lda, h.M, h.a_absmax, D, ldc, d_absmax, (int32_t)first};
-  hipLaunchKernelGGL(kern, dim3((unsigned)all), dim3(NTHREADS), smem_bytes<SBK>(), st, gb, e, s);
-  return hipGetLastError();
+  if (!wide) return launch_two<gemm_split_kernel<EPI_STORE, true>>(all, NTHREADS, smem_bytes<SBK>(), st, gb, e, s);
+  if (hipError_t rc = launch_split_rows(g.B, g.ldb, g.N, g.K, g.b_absmax, g.b_split, st); rc != hipSuccess) return rc;
+  return launch_two<gemm_split256_kernel<EPI_STORE, true>>(all, NT2, (size_t)2 * T2_STAGE * sizeof(uint32_t), st, gb,
+                                                                   (const uint32_t *)g.b_split, (int64_t)split_ld(g.K), e, s);
 }
 
 hipError_t gemm_argmin(const GemmOperands &g, const float *ynorm, unsigned long long *best, hipStream_t st) {

@@ -1038,6 +1038,30 @@ def test_rows_and_centroids_rotated_together(skm, dg, n, k, d):  # noqa: F811
         assert torch.equal(a, b) and torch.equal(da, db)
 
 
+# The same launch with 256 x 256 tiles, where those of both fill the rounds of the device (a first, a part and a second round; ragged
+# rows and columns).  A rotated coordinate is off by 2^-21 of its row in the 22-bit products and the rotation's own entries by
+# fp32, so that a vector is by less than e = 2^-18 of both norms (256 to 1536 terms added in fp32) and its squared distance by
+# 2 e dist + e^2; a distance from |x|^2 + |y|^2 - 2 x.y adds 2^-20 of the squares (22-bit operands, three fp32
+# roundings) and 2^-24 for each of the d / 8 partial sums behind one another.  Tests that drop nothing leave the nearest centroid,
+# by distances of that error.
+@pytest.mark.parametrize("n,k,d", [(52_100, 300, 256), (60_000, 5, 224), (26_300, 1, 448), (9000, 257, 1536), (120_000, 300, 256)])
+def test_rows_and_centroids_rotated_together_in_large_tiles(skm, dg, n, k, d):  # noqa: F811
+    say("rotated together, large tiles", n, k, d)
+    X = dg.mixture(n, d, 20, 3, "linear", "cuda")
+    Y = dg.mixture(k, d, 20, 3, "linear", "cuda", sample_seed=4)
+    prev = torch.randint(0, k, (n,), generator=torch.Generator().manual_seed(1)).int().cuda()
+    for p in (None, prev):
+        a, da, _ = skm.assign(X, Y, p, opts=skm.FitOptions(R=skm.make_rotation(d, 9), eps0=100.0))
+        for i in range(0, n, 8192):
+            x, y = X[i:i + 8192].double(), Y.double()
+            D = torch.cdist(x, y, compute_mode="donot_use_mm_for_euclid_dist")
+            e = 2.0 ** -18 * (x.norm(dim=1) + y.norm(dim=1).max())
+            at = D.gather(1, a[i:i + 8192, None].long())[:, 0]
+            off = 2 * at * e + e ** 2 + (2.0 ** -20 + d * 2.0 ** -27) * ((x ** 2).sum(1) + (y ** 2).sum(1).max())
+            assert bool(((da[i:i + 8192].double() - at ** 2).abs() <= off).all())
+            assert bool((at ** 2 <= D.min(1).values ** 2 + 2 * off).all())
+
+
 # Up to 256 dimensions the thresholds of a step are taken in the launch that prepares its centroids (a form for each 128), beyond
 # in one of their own.  With tests that drop nothing the last labels are the nearest centroids, at their direct distances.
 @pytest.mark.parametrize("d", [16, 112, 128, 130, 144, 250, 256, 272])
