@@ -194,7 +194,7 @@ hipError_t launch_absmax(const float *A, int64_t lda, int64_t rows, int32_t cols
 // If c_absmax is given, max |C| is folded into *c_absmax (as launch_absmax does).
 hipError_t gemm_store(const GemmOperands &g, float *C, int64_t ldc, int32_t Nstore, float alpha, float beta,
                       hipStream_t st, unsigned int *c_absmax = nullptr);
-// C and D (rows of ldc) = the products g and h, which share B; in one launch where neither is tall
+// C and D (rows of ldc) = the products g and h, which share B; in one launch where neither is tall or large tiles fill the device
 hipError_t gemm_store_two(const GemmOperands &g, float *C, unsigned int *c_absmax, const GemmOperands &h, float *D, unsigned int *d_absmax,
                           int64_t ldc, int32_t Nstore, hipStream_t st);
 
