@@ -2005,7 +2005,8 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     return SKM_OK;
   };
 
-  c.watch = ws.on;   // (not in the many small fits that share the host's cores)
+  // (not in the many small fits that share the host's cores, nor where the stream is waited for after every step anyway, for the recall)
+  c.watch = ws.on && !p.etr;
   for (int32_t t = 1; t <= iters; ++t) {
     StepStats ss;
     tm.begin_step();
