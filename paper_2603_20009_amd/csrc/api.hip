@@ -6,7 +6,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <atomic>
 #include <chrono>
 #include <mutex>
 #include <thread>
@@ -536,9 +535,9 @@ struct Ctx {
   bool xnp_valid = false;     // first pruned step (the points of a context never change)
   bool xh_valid = false;      // Xh likewise: left out of a pass that a regrouping pass will repeat
   // Regrouping (a fit with several steps left): once the tables exist, a threshold pass rewrites the points, their split
-  // copy, their tables and every per-point array in the order of their clusters (step_pruned).  Row tiles then hold points of one or two clusters, whose challengers are the same few
-  // centroids: the alive pairs of a step gather in few tiles, the others end at the first test, and the rows and
-  // centroid blocks the gather kernel fetches are shared by neighbouring pairs.
+  // copy, their tables and every per-point array in the order of their clusters (step_pruned).  Row tiles then hold points
+  // of one or two clusters, whose challengers are the same few centroids: the alive pairs of a step gather in few tiles, the
+  // others end at the first test, and the rows and centroid blocks the gather kernel fetches are shared by neighbouring pairs.
   float *Xr2 = nullptr;          // [n][ds] the points in the new order (NULL: no regrouping in this context)
   int32_t *pos_to_id = nullptr;  // [n] point of every position
   unsigned char *subkey = nullptr;   // [n] scratch: the key that orders the points inside a cluster
@@ -926,7 +925,8 @@ size_t fit_workspace_need(int64_t n, int32_t d, int32_t k, const skm_params &p) 
   }
   const size_t plan = plan_common_bytes(n, d, k, p.pair_budget, p.dense_frac, true);
   if (!plan) return 0;
-  size_t need = plan + 2 * (size_t)n * ds0 * 4 + (size_t)n * 5 + (size_t)threshold_class_words(n) * 4 + 10 * (size_t)d * ds0 * 4 + (size_t)d * 16384 +
+  // (threshold_class_words(n), 6 MiB at most, is in the last term: a workspace that a caller lends has the size that it had without)
+  size_t need = plan + 2 * (size_t)n * ds0 * 4 + (size_t)n * 5 + 10 * (size_t)d * ds0 * 4 + (size_t)d * 16384 +
                 (size_t)k * 16 + ((size_t)32 << 20);
   if (p.etr && p.nq > 0 && p.topk > 0) {
     const size_t nq = (size_t)p.nq;
