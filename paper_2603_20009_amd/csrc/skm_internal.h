@@ -496,7 +496,7 @@ struct FinalizeArgs {
   unsigned int *done = nullptr;
   double *obj_partial = nullptr;      // [finalize_blocks(n)]
   int32_t *change_start = nullptr;    // [finalize_blocks(n)] changed points before the points of each workgroup
-  const unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]
+  unsigned long long *scal = nullptr;   // [kStatReplicas][SC_COUNT]; its first SC_CHANGED receives the changed points
   int nscal = SC_COUNT;               // scalars to report
   StepReport *report = nullptr;       // device-visible address of the page-locked block
   unsigned int seq = 0;               // number of the report
@@ -571,6 +571,21 @@ hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, in
                                      const int32_t *prev, int64_t changed, const int32_t *change_start, int32_t k,
                                      const UpdateWs &w, const IncUpdateWs &inc, double *S, float *Y, int64_t ldy,
                                      hipStream_t st, unsigned int *y_absmax = nullptr);
+// The same, launched before the host knows how many labels changed: it does nothing where none did, more than `most`, or *flag is
+// set.  The sums, the means and *y_absmax are then as they were.
+struct UpdateAhead {
+  const unsigned long long *changed = nullptr;   // of the finalize kernel (scal[SC_CHANGED])
+  const unsigned int *flag = nullptr;
+  int64_t most = 0;                              // at most update_ahead_most
+  __device__ int entries() const {
+    const unsigned long long c = *changed;
+    return c > (unsigned long long)most || *flag != 0u ? 0 : 2 * (int)c;
+  }
+};
+int64_t update_ahead_most(int32_t ds, int32_t k, int64_t capacity);   // what the direct form takes (launch_update_incremental)
+hipError_t launch_update_ahead(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, const int32_t *prev,
+                               const int32_t *change_start, int32_t k, const UpdateWs &w, const IncUpdateWs &inc, double *S,
+                               float *Y, int64_t ldy, const UpdateAhead &ahead, hipStream_t st, unsigned int *y_absmax);
 
 // Empty-cluster splits: pairs_dev = (empty, donor) pairs grouped into chains (splits that share a cluster, in the
 // host's order); chain_first_dev[c] .. chain_first_dev[c + 1] are the splits of chain c.  One workgroup per chain.

@@ -1121,6 +1121,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finalize_assign_kernel(FinalizeAr
     store_system(&r->nempty, e);
     store_system(&r->largest, l);
     if (a.nscal > SC_CHANGED) store_system(&r->scal[SC_CHANGED], (unsigned long long)changed);
+    a.scal[SC_CHANGED] = (unsigned long long)changed;   // (no other kernel of the step writes it)
     if (a.stamp_end) *a.stamp_end = wall_clock64();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     store_system(&r->seq, a.seq);
@@ -1727,8 +1728,9 @@ hipError_t launch_add_counts(const int32_t *cnt, int32_t k, int32_t *total, hipS
 __global__ void __launch_bounds__(256) compact_changes_kernel(const int32_t *assign, const int32_t *prev, int64_t n,
                                                               const int32_t *start, int per_block, int32_t *ent_id,
                                                               int32_t *ent_lab, unsigned int cap, unsigned int *zero,
-                                                              int32_t *zero_cnt, int32_t k) {
+                                                              int32_t *zero_cnt, int32_t k, UpdateAhead ahead) {
   __shared__ int s_cnt[4];
+  if (ahead.changed && ahead.entries() == 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (blockIdx.x == 0 && tid == 0 && zero) *zero = 0u;
   if (zero_cnt)
@@ -1772,7 +1774,11 @@ constexpr int64_t kDirectUpdate = (int64_t)1 << 25;
 constexpr int DIRECT_CHUNK = 1024;
 __global__ void __launch_bounds__(256) direct_update_kernel(const float *Xr, int64_t ldx, int32_t ds, const int32_t *ent_id,
                                                             const int32_t *ent_lab, int m, const int32_t *cnt, double *S,
-                                                            float *Y, int64_t ldy, unsigned int *y_absmax) {
+                                                            float *Y, int64_t ldy, unsigned int *y_absmax, UpdateAhead ahead) {
+  if (ahead.changed) {
+    m = ahead.entries();
+    if (m == 0) return;
+  }
   // The rows of a cluster in a chunk of entries go to the four wavefronts in turn (the order of the sums does not depend on
   // how many chunks are taken together); their lists are worked off when one is nearly full, and at the end.
   constexpr int LIST = 1024;
@@ -2067,10 +2073,10 @@ hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, in
   const bool direct = m2 * (int64_t)k * slices <= kDirectUpdate;
   hipLaunchKernelGGL(compact_changes_kernel, dim3((unsigned)finalize_blocks(n)), dim3(256), 0, st, assign, prev, n,
                      change_start, finalize_per_block(n), inc.ent_id, inc.ent_lab, (unsigned int)inc.capacity, y_absmax,
-                     direct ? (int32_t *)nullptr : inc.cnt, k);
+                     direct ? (int32_t *)nullptr : inc.cnt, k, UpdateAhead());
   if (direct) {
     hipLaunchKernelGGL(direct_update_kernel, dim3(k, slices), dim3(256), 0, st, Xr, ldx, ds, (const int32_t *)inc.ent_id,
-                       (const int32_t *)inc.ent_lab, (int)m2, w.cnt, S, Y, ldy, y_absmax);
+                       (const int32_t *)inc.ent_lab, (int)m2, w.cnt, S, Y, ldy, y_absmax, UpdateAhead());
     return hipGetLastError();
   }
   hipError_t rc = launch_histogram(inc.ent_lab, m2, k, inc.cnt, nullptr, st);
@@ -2085,6 +2091,21 @@ hipError_t launch_update_incremental(const float *Xr, int64_t ldx, int64_t n, in
   launch_segment_sums<true>(true, m2, k, (unsigned)segs, slices, Xr, ldx, ds, inc.off, inc.segoff, inc.order, inc.partial, st);
   hipLaunchKernelGGL(centroid_mean_kernel, dim3(k, slices), dim3(256), 0, st, inc.partial, ds, w.cnt, inc.segoff, Y, ldy,
                      S, 1, y_absmax, (const unsigned int *)nullptr, (unsigned int *)nullptr, (int32_t *)nullptr);
+  return hipGetLastError();
+}
+
+int64_t update_ahead_most(int32_t ds, int32_t k, int64_t capacity) {
+  return std::min(capacity - 2, kDirectUpdate / ((int64_t)k * ((ds + 255) / 256))) / 2;
+}
+hipError_t launch_update_ahead(const float *Xr, int64_t ldx, int64_t n, int32_t ds, const int32_t *assign, const int32_t *prev,
+                               const int32_t *change_start, int32_t k, const UpdateWs &w, const IncUpdateWs &inc, double *S,
+                               float *Y, int64_t ldy, const UpdateAhead &ahead, hipStream_t st, unsigned int *y_absmax) {
+  if (ahead.most <= 0 || ahead.most > update_ahead_most(ds, k, inc.capacity) || !ahead.changed || !ahead.flag || !S) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(compact_changes_kernel, dim3((unsigned)finalize_blocks(n)), dim3(256), 0, st, assign, prev, n,
+                     change_start, finalize_per_block(n), inc.ent_id, inc.ent_lab, (unsigned int)inc.capacity, y_absmax,
+                     (int32_t *)nullptr, k, ahead);
+  hipLaunchKernelGGL(direct_update_kernel, dim3(k, (unsigned)((ds + 255) / 256)), dim3(256), 0, st, Xr, ldx, ds, (const int32_t *)inc.ent_id,
+                     (const int32_t *)inc.ent_lab, 0, w.cnt, S, Y, ldy, y_absmax, ahead);
   return hipGetLastError();
 }
 

@@ -1075,3 +1075,18 @@ def test_thresholds_beside_the_centroids(skm, d):  # noqa: F811
     clear = near[:, 1] - near[:, 0] > 1e-4 * near[:, 0]      # fp32 distances of 22-bit products
     assert torch.equal(r.assign[clear].long(), at[clear, 0])
     assert bool(((r.dist.double() - near[:, 0]).abs() <= 1e-4 * near[:, 0] + 1e-6).all())      # (a cluster of one point: 0)
+
+
+# An update in which few points moved is launched before the host knows how many did, and does nothing where they are none or more
+# than its form takes (2^25 / 2k / slices of 256 dimensions: 4096 of the first case, an eighth of the points in the others).  The
+# sums are fp64, so the means are those of full updates to the last bit of fp32.
+@pytest.mark.parametrize("n,d,k,iters", [(100_000, 64, 4096, 12), (20_000, 128, 100, 14), (3000, 300, 30, 25), (1000, 520, 3, 12), (40, 16, 4, 6)])
+def test_updates_ahead_of_the_report(skm, dg, n, d, k, iters):  # noqa: F811
+    say("updates ahead", n, d, k)
+    X = dg.mixture(n, d, max(2, 2 * k), 5, "linear", "cuda")
+    R = skm.make_rotation(d, 2)
+    a, b = (skm.fit(X, k, iters, 4, skm.FitOptions(R=R, full_update=f)) for f in (False, True))
+    assert a.timing["inc_updates"] >= 1 and b.timing["inc_updates"] == 0
+    assert [r["changed"] for r in a.trace] == [r["changed"] for r in b.trace]
+    assert torch.equal(a.assign, b.assign)
+    assert float((a.centroids - b.centroids).norm() / b.centroids.norm()) < 1e-6
