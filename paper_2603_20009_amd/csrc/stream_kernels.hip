@@ -186,6 +186,10 @@ __device__ inline float4 load_stream4(const float *p) {
 // points at a time and writes their prefix norms through LDS, 256 contiguous bytes per table row, instead of one 4-byte store per
 // point and row.  Where 64 points a workgroup would leave most of the chip without one (a wavefront then walks sixteen rows one
 // after the other while other CUs idle), it takes 16.
+// A pair of rows is a chain of loads (place, label, centroid) and of sums over the lanes, and registers allow sixteen wavefronts a CU.
+// Rows of up to 256 dimensions leave room for the next pair's labels and rows, requested ahead of this one's: 120 001 x 208 56.6 -> 45.5
+// us, changing places as well 108.7 -> 94.6 (3.7 TB/s); 20 000 x 128 15.9 -> 14.2. (More wavefronts instead, with registers in
+// memory: five to six a SIMD 80 and 151 us, 2.5M x 384 2.92 -> 3.31 ms, 1M x 768 2.23 -> 2.31.)
 // Without TABLES their code is left out: it costs registers (NV = 6: 68 without it, 137 with it; labels and distances of 11 800 x 1152 in 13.1
 // and 16.9 us).
 constexpr int kPrefixStageRows = 128;   // ds <= 2048 in the batched form
@@ -193,7 +197,7 @@ template <int NV, bool TABLES>
 __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t ldx, int64_t n, int32_t ds,
                                                        const float *Y, int64_t ldy, const int32_t *assign, float *tau,
                                                        unsigned long long *best, PrefixOut po) {
-  constexpr bool BATCH = TABLES && NV > 0;
+  constexpr bool BATCH = TABLES && NV > 0, AHEAD = NV == 1;
   __shared__ float s_np[BATCH ? kPrefixStageRows * 64 : 1];
   __shared__ __align__(16) uint32_t s_pair[BATCH ? 4 * 512 : 4];
   put_stamp(po.stamp);
@@ -269,12 +273,9 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
     }
   };
   // rows p and p + 1 (p even), for the tables; past the end row p stands for row p + 1 and only fills the odd row of its pair
-  auto two_points = [&](int64_t p, int slot) {
-    constexpr int NX = NV > 0 ? NV : 1;
+  constexpr int NX = NV > 0 ? NV : 1;
+  auto take_two = [&](int64_t p, int (&a)[2], float4 (&xv)[2][NX]) {   // their labels and rows
     const bool both = p + 1 < n;
-    int a[2];
-    float4 xv[2][NX];
-    float s[2] = {0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       const int64_t o = both ? p + r : p, i = po.order ? (int64_t)po.order[o] : o;
@@ -294,6 +295,10 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
         xv[r][u] = c < ds ? load_stream4(Xr + i * ldx + c) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
+  };
+  auto two_points = [&](int64_t p, int slot, const int (&a)[2], const float4 (&xv)[2][NX]) {
+    const bool both = p + 1 < n;
+    float s[2] = {0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       __builtin_amdgcn_sched_barrier(0);   // (one centroid row at a time in registers)
@@ -347,8 +352,22 @@ __global__ void __launch_bounds__(256) tau_init_kernel(const float *Xr, int64_t 
     const int wave = threadIdx.x >> 6, rows = ds >> 4;
     const int span = po.span, sh = span == 64 ? 6 : 4;
     for (int64_t b0 = (int64_t)blockIdx.x * span; b0 < n; b0 += (int64_t)gridDim.x * span) {
-      for (int slot = 2 * wave; slot < span; slot += 8)
-        if (b0 + slot < n) two_points(b0 + slot, slot);
+      int a[2], a_next[2] = {0, 0};
+      float4 xv[2][NX], xv_next[2][NX];
+      if (AHEAD && b0 + 2 * wave < n) take_two(b0 + 2 * wave, a_next, xv_next);
+      for (int slot = 2 * wave; slot < span && b0 + slot < n; slot += 8) {
+        if (AHEAD) {
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            a[r] = a_next[r];
+            xv[r][0] = xv_next[r][0];
+          }
+          if (slot + 8 < span && b0 + slot + 8 < n) take_two(b0 + slot + 8, a_next, xv_next);
+        } else {
+          take_two(b0 + slot, a, xv);
+        }
+        two_points(b0 + slot, slot, a, xv);
+      }
       __syncthreads();
       const int col = threadIdx.x & (span - 1);
       if (b0 + col < n)
