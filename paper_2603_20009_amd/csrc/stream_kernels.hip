@@ -826,20 +826,21 @@ __device__ inline void block_absmax(float v, unsigned int *out) {
 // Rows without gaps (lda == cols) are read as one array of at least four values, 16 bytes a load whatever its alignment (global loads
 // need 4 bytes; 46 467 x 495 a value at a time: 70 us, now 16), four loads in flight.  A kernel by itself: behind the code for rows
 // with gaps a small array took 6.4 us instead of 4.5, most of it for the instructions.
+template <int LOADS>   // in flight
 __device__ inline void absmax_flat(const float *A, int64_t count, unsigned int *out, int block, int nblocks) {
-  const int64_t last = count - 4, stride = (int64_t)nblocks * 1024;
+  const int64_t last = count - 4, stride = (int64_t)nblocks * 256 * LOADS;
   float m = 0.f;
-  for (int64_t e = (int64_t)block * 1024 + threadIdx.x; 4 * e < count; e += stride) {
-    f32x4_u v[4];
+  for (int64_t e = (int64_t)block * 256 * LOADS + threadIdx.x; 4 * e < count; e += stride) {
+    f32x4_u v[LOADS];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4_u *>(A + min(4 * (e + 256 * u), last));   // (past the end: the last four again)
+    for (int u = 0; u < LOADS; ++u) v[u] = *reinterpret_cast<const f32x4_u *>(A + min(4 * (e + 256 * u), last));   // (past the end: the last four again)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+    for (int u = 0; u < LOADS; ++u) m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
   }
   block_absmax(m, out);
 }
 __global__ void __launch_bounds__(256) absmax_flat_kernel(const float *A, int64_t count, unsigned int *out) {
-  absmax_flat(A, count, out, blockIdx.x, gridDim.x);
+  absmax_flat<4>(A, count, out, blockIdx.x, gridDim.x);
 }
 // Rows with gaps: an element index is split into row and column.
 template <bool VEC4>
@@ -2235,20 +2236,24 @@ __device__ inline void rotation_operands(const float *R, int32_t d, float *Rp, f
     }
   block_absmax(m, absmax);
 }
-// One workgroup does a part of one job.  The long one comes first: its two workgroups a CU are then placed evenly and the short
+// One workgroup does a part of one job.  The long one comes first: its workgroups are then placed evenly and the short
 // ones run beside them (last, on whichever CUs the short ones had left, 460 366 x 817 and 1653 centroids took 499 us instead of 252).  A launch behind another costs
 // 3 to 5 us whatever it does: whole calls, with the pair of products of gemm.hip, 64 rows of 128 dimensions 210 -> 188 us, 20 000
 // of 1536 888 -> 832, exact assignment of 100 003 of 100 127 -> 118.
+// A bound takes one workgroup a CU and eight loads in flight: what it costs beside its bytes is its workgroups, which meet at one
+// word.  The launch of 20 000 x 1536 and 1024 centroids 43.9 -> 39.2 us with two and four, 100 003 x 100 11.5 -> 9.2, 2.5M x 384 623 ->
+// 618 (two and eight 42.5, 12.3 and 638; four and four 49, 21 and 639; one and sixteen 36.5, 11.9 and 618).
+constexpr int kBoundLoads = 8;
 struct OpeningGrid {
   int ops_x = 0, ops = 0, bound[2] = {0, 0}, pad = 0, fill = 0;   // workgroups of every job
 };
 __global__ void __launch_bounds__(256) opening_kernel(OpeningJobs j, OpeningGrid g) {
   int b = blockIdx.x;
-  if (b < g.bound[0]) return absmax_flat(j.bound[0].A, j.bound[0].count, j.bound[0].out, b, g.bound[0]);
+  if (b < g.bound[0]) return absmax_flat<kBoundLoads>(j.bound[0].A, j.bound[0].count, j.bound[0].out, b, g.bound[0]);
   b -= g.bound[0];
   if (b < g.ops) return rotation_operands(j.R, j.d, j.Rp, j.Rtp, j.ld, j.r_bound, b % g.ops_x, b / g.ops_x);
   b -= g.ops;
-  if (b < g.bound[1]) return absmax_flat(j.bound[1].A, j.bound[1].count, j.bound[1].out, b, g.bound[1]);
+  if (b < g.bound[1]) return absmax_flat<kBoundLoads>(j.bound[1].A, j.bound[1].count, j.bound[1].out, b, g.bound[1]);
   b -= g.bound[1];
   if (b < g.pad) return pad_copy(j.src, j.lds, j.rows, j.cols, j.dst, j.ldd, j.dpad, 0, b, g.pad);
   b -= g.pad;
@@ -2263,7 +2268,7 @@ hipError_t launch_opening(const OpeningJobs &j, hipStream_t st) {
   for (int u = 0; u < 2; ++u) {
     if (!j.bound[u].out) continue;
     if (j.bound[u].count < 4) return hipErrorInvalidValue;
-    g.bound[u] = (int)std::min<int64_t>((j.bound[u].count + 4095) / 4096, 2 * num_cus());   // (as in launch_absmax)
+    g.bound[u] = (int)std::min<int64_t>((j.bound[u].count + 1024 * kBoundLoads - 1) / (1024 * kBoundLoads), num_cus());
   }
   if (j.dst) g.pad = (int)std::min<int64_t>((j.rows * j.dpad + 255) / 256, (int64_t)num_cus() * 16);
   if (j.fill) g.fill = (int)std::min<int64_t>((j.nfill + 255) / 256, (int64_t)num_cus() * 4);
