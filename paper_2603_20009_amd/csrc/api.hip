@@ -201,6 +201,16 @@ struct Pool {
     *out = static_cast<T *>(p);
     return hipSuccess;
   }
+  // gives back what has been taken since `m` (nothing launched may use it)
+  struct Mark {
+    size_t nptrs, off;
+  };
+  Mark taken() const { return {ptrs.size(), arena ? arena->off : 0}; }
+  void give_back(const Mark &m) {
+    for (size_t i = m.nptrs; i < ptrs.size(); ++i) (void)hipFree(ptrs[i]);
+    ptrs.resize(m.nptrs);
+    if (arena) arena->off = m.off;
+  }
 };
 
 // Page-locked host memory for the few numbers that every step reports to the host: copies into it are asynchronous,
@@ -1905,27 +1915,6 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   }
   rc = c.alloc_common(p.pair_budget, p.dense_frac, true);
   if (rc) return rc;
-  // regrouping of the points by cluster (Ctx): not for rows that the batched table writes of the threshold pass do not
-  // cover; it happens in the third step at the earliest
-  bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && regroup_pays(iters - 2 + (p.final_assign ? 1 : 0), k);
-  if (may_regroup) {
-    auto room = [&]() -> int {
-      HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
-      HIPCHK(c.pool.get(&c.subkey, (size_t)n));
-      HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
-      HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
-      return SKM_OK;
-    };
-    rc = room();
-    if (rc == SKM_ENOMEM) {   // no memory for what a fit may do without: its points stay as they are
-      (void)hipGetLastError();
-      c.Xr2 = nullptr;
-      may_regroup = false;
-    } else if (rc) {
-      return rc;
-    }
-    c.Xr_own = Xr_own;
-  }
 
   // ---- InitCentroids: k distinct rows of X~.  The row numbers go through the page-locked block, so nothing waits here
   // (the numbers are drawn while the rotation runs); a few are read from there by the gather itself.
@@ -1997,6 +1986,33 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
     HIPCHK(c.pool.get(&etr_scal, 2));
     c.point_keys = gt_keys;   // the ground truth names points: it follows them if they are regrouped
     c.n_point_keys = (int64_t)p.nq * p.topk;
+  }
+
+  // Regrouping of the points by cluster (Ctx): not for rows that the batched table writes of the threshold pass do not
+  // cover; it happens in the third step at the earliest.  Its room is the last that the call takes, and given back where it cannot be
+  // had in full: a fit may do without, and its points stay as they are.
+  bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && regroup_pays(iters - 2 + (p.final_assign ? 1 : 0), k);
+  if (may_regroup) {
+    const Pool::Mark before = c.pool.taken();
+    auto room = [&]() -> int {
+      HIPCHK(c.pool.get(&c.pos_to_id, (size_t)n));
+      HIPCHK(c.pool.get(&c.subkey, (size_t)n));
+      HIPCHK(c.pool.get(&c.class_ws, (size_t)threshold_class_words(n)));
+      HIPCHK(c.pool.get(&c.Xr2, (size_t)n * c.ds));
+      return SKM_OK;
+    };
+    rc = room();
+    if (rc == SKM_ENOMEM) {
+      (void)hipGetLastError();
+      c.pool.give_back(before);
+      c.pos_to_id = c.class_ws = nullptr;
+      c.subkey = nullptr;
+      c.Xr2 = nullptr;
+      may_regroup = false;
+    } else if (rc) {
+      return rc;
+    }
+    c.Xr_own = Xr_own;
   }
 
   int32_t dprime = dprime_init(d, p.dprime_frac);

@@ -1021,6 +1021,33 @@ def test_fit_without_memory_for_the_order(skm, dg):  # noqa: F811
     assert float((a.assign != b.assign).float().mean()) <= 1e-3
 
 
+# ... also a short one with recall, whose queries, ground truth and scores are taken after its points: where there is memory for those
+# or for the regrouped copy, not for both, the fit gets what it cannot do without.
+def test_short_fit_with_recall_without_memory_for_the_order(skm, dg):  # noqa: F811
+    n, d, k, nq, topk = 400_000, 512, 2048, 16_000, 10
+    say("short fit with recall, a full device", n, d, k)
+    X = dg.mixture(n, d, 2 * k, 3, "embed", "cuda")
+    Q = dg.mixture(nq, d, 2 * k, 3, "embed", "cuda", sample_seed=9)
+    opts = skm.FitOptions(R=skm.make_rotation(d, 4), own_workspace=True, etr=True, queries=Q, topk=topk, etr_patience=10)
+    a = skm.fit(X, k, 4, 5, opts)
+    skm.release_memory()
+    copy = n * d * 4
+    # what is taken before the recall's buffers: the plan of a fit without recall but for a copy and for what that plan holds for the
+    # making of a rotation and in reserve
+    base = skm.workspace_bytes(n, d, k) - copy - 7 * d * d * 4 - d * 16384 - (32 << 20)
+    # the recall's own: a chunk of points and the queries in 16 bits, a group's minima, 1024 candidates, keys, rotated queries, scores
+    recall = nq * (65_536 // 64 * 4 + 1024 * 8 + topk * 8 + d * 6 + k * 4) + 131_072 * d * 2
+    assert base + recall < base + copy + recall // 2
+    held = fill_device(base + copy + recall // 2)
+    b = skm.fit(X, k, 4, 5, opts)
+    del held
+    torch.cuda.empty_cache()
+    assert sum(r["listed_tiles"] for r in a.trace) < sum(r["listed_tiles"] for r in b.trace)
+    assert max(abs(p["recall"] - q["recall"]) for p, q in zip(a.trace[:4], b.trace[:4])) <= 1e-3
+    assert float((a.centroids - b.centroids).norm() / a.centroids.norm()) < 1e-4
+    assert float((a.assign != b.assign).float().mean()) <= 1e-3
+
+
 # A call with a rotation multiplies its rows and its centroids in one launch, behind one that takes both bounds and the copies of
 # the matrix (rows that are not aligned, and the tall form, in launches of their own).  On rows that were rotated before the call
 # labels and distances are the same bits.
