@@ -115,10 +115,7 @@ def test_rotation_at_the_edges_of_its_panels(skm, d):  # noqa: F811
 # Up to 128 rows one workgroup makes the matrix, beyond that a chain of kernels whose last 128 rows go round twice: the matrix
 # is the orthonormal factor of the normals that (d, seed) stand for, computed here by numpy's QR.  An element is off by half
 # an ulp of fp32 plus what fp64 rounding leaves of either factor, 64 eps times the condition of the matrix of normals.
-@pytest.mark.parametrize("d", [1, 2, 15, 16, 17, 64, 65, 100, 128, 129, 192, 193, 260])
-def test_rotation_is_the_orthonormal_factor_of_its_normals(skm, d):  # noqa: F811
-    say("rotation", d)
-
+def normals_of(d, seed):
     def mix(z):
         z = z + np.uint64(0x9E3779B97F4A7C15)
         z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
@@ -126,14 +123,45 @@ def test_rotation_is_the_orthonormal_factor_of_its_normals(skm, d):  # noqa: F81
         return z ^ (z >> np.uint64(31))
 
     with np.errstate(over="ignore"):
-        t = np.arange((d * d + 1) // 2, dtype=np.uint64) * np.uint64(2) + np.uint64((5 + 3 * 0xD1342543DE82EF95) % 2**64)
+        t = np.arange((d * d + 1) // 2, dtype=np.uint64) * np.uint64(2) + np.uint64((seed + 3 * 0xD1342543DE82EF95) % 2**64)
         u1, u2 = ((mix(z) >> np.uint64(11)).astype(np.float64) / 2.0**53 for z in (t, t + np.uint64(1)))
     m = np.sqrt(-2.0 * np.log(u1))
-    G = np.stack([m * np.cos(2 * np.pi * u2), m * np.sin(2 * np.pi * u2)], 1).reshape(-1)[:d * d].reshape(d, d)
+    return np.stack([m * np.cos(2 * np.pi * u2), m * np.sin(2 * np.pi * u2)], 1).reshape(-1)[:d * d].reshape(d, d)
+
+
+def check_rotation_of_normals(skm, d, seed):  # noqa: F811
+    G = normals_of(d, seed)
     q, r = np.linalg.qr(G.T)
     want = (q * np.sign(np.diag(r))).T
-    got = skm.make_rotation(d, 5).cpu().numpy().astype(np.float64)
+    got = skm.make_rotation(d, seed).cpu().numpy().astype(np.float64)
     assert (np.abs(got - want) <= 2.0**-24 * np.abs(want) + 64 * 2.0**-52 * np.linalg.cond(G)).all()
+    assert np.abs(got @ got.T - np.eye(d)).max() < 2 * 2.0 ** -24 * np.sqrt(d)      # as below
+
+
+@pytest.mark.parametrize("d", [1, 2, 15, 16, 17, 64, 65, 100, 128, 129, 192, 193, 260])
+def test_rotation_is_the_orthonormal_factor_of_its_normals(skm, d):  # noqa: F811
+    say("rotation", d)
+    check_rotation_of_normals(skm, d, 5)
+
+
+# The second factor of a panel is taken without eliminations where its Gram matrix is within 2^-33 of the unit matrix, as it is for the
+# seeds of the other tests.  For these it is off by 16 times that and more, in fp64 steps of the same kind, so that what rounding
+# does in another order does not bring it back: both generators take the eliminations in their last panel of 64, 36 or 8 rows.
+@pytest.mark.parametrize("d,seed", [(64, 346), (64, 366), (100, 340), (100, 8), (128, 392), (128, 54), (192, 41), (192, 16), (200, 32)])
+def test_rotation_whose_second_factor_takes_the_eliminations(skm, d, seed):  # noqa: F811
+    say("rotation", d, seed)
+    W, off = normals_of(d, seed), 0.0
+    for p0 in range(0, d, 64):
+        P, Q = W[p0:p0 + 64], W[:p0]
+        for again in range(2 if d - p0 <= 128 else 1):
+            P = P - (P @ Q.T) @ Q
+            gram = P @ P.T
+            if again:
+                off = np.abs(gram - np.eye(len(P))).max()
+            P = np.linalg.solve(np.linalg.cholesky(gram), P)
+        W[p0:p0 + 64] = P
+    assert off > 16 * 2.0**-33
+    check_rotation_of_normals(skm, d, seed)
 
 
 # The ground truth goes through the points in chunks of whole rounds of tiles (256 points x 256 queries): one tile row and
