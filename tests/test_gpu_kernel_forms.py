@@ -1135,18 +1135,38 @@ def test_thresholds_beside_the_centroids(skm, d):  # noqa: F811
 
 
 # An update in which few points moved is launched before the host knows how many did, and does nothing where they are none or more
-# than its form takes (2^25 / 2k / slices of 256 dimensions: 4096 of the first case, an eighth of the points in the others).  The
-# sums are fp64, so the means are those of full updates to the last bit of fp32.
-@pytest.mark.parametrize("n,d,k,iters", [(100_000, 64, 4096, 12), (20_000, 128, 100, 14), (3000, 300, 30, 25), (1000, 520, 3, 12), (40, 16, 4, 6)])
-def test_updates_ahead_of_the_report(skm, dg, n, d, k, iters):  # noqa: F811
-    say("updates ahead", n, d, k)
-    X = dg.mixture(n, d, max(2, 2 * k), 5, "linear", "cuda")
+# than its form takes (2^25 / 2k / slices of 256 dimensions, or an eighth of the points).  It is launched where the step before says
+# that it may be that form (some changed, and at most four times as many), so the labels that changed say which steps it was
+# launched in and what it did there: it took effect, they were too many, or none.  The sums are fp64, so the means are
+# those of full updates to the last bit of fp32; unit rows (the angular metric) add that of their length.  With most points
+# on a few places clusters run empty in every step, and their splits follow an update that has run ahead.
+@pytest.mark.parametrize("n,d,k,iters,places,angular,reached", [
+    (100_000, 64, 4096, 12, 0, False, {"took", "many"}), (20_000, 128, 100, 14, 0, False, {"took", "none"}),
+    (3000, 300, 30, 25, 0, False, {"took", "none"}), (1000, 520, 3, 12, 0, False, {"none"}), (40, 16, 4, 6, 0, False, {"none"}),
+    (100_000, 64, 4096, 12, 0, True, {"took", "many"}), (1000, 520, 3, 12, 0, True, {"took", "none"}),
+    (6000, 64, 60, 14, 40, False, {"split", "many"}), (6000, 64, 80, 14, 20, True, {"split", "many", "none"})])
+def test_updates_ahead_of_the_report(skm, dg, n, d, k, iters, places, angular, reached):  # noqa: F811
+    say("updates ahead", n, d, k, places, angular)
+    X = dg.mixture(n, d, max(2, 2 * k), 5, "linear", "cpu" if places else "cuda")
+    if places:
+        g = torch.Generator().manual_seed(8)
+        far, m = torch.randn(places, d, generator=g) * 3, n * 9 // 10
+        X[:m] = far[torch.randint(0, places, (m,), generator=g)]
+        X = X[torch.randperm(n, generator=g)].cuda()
     R = skm.make_rotation(d, 2)
-    a, b = (skm.fit(X, k, iters, 4, skm.FitOptions(R=R, full_update=f)) for f in (False, True))
+    a, b = (skm.fit(X, k, iters, 4, skm.FitOptions(R=R, full_update=f, angular=angular)) for f in (False, True))
     assert a.timing["inc_updates"] >= 1 and b.timing["inc_updates"] == 0
     assert [r["changed"] for r in a.trace] == [r["changed"] for r in b.trace]
+    assert [r["nempty"] for r in a.trace] == [r["nempty"] for r in b.trace]
     assert torch.equal(a.assign, b.assign)
     assert float((a.centroids - b.centroids).norm() / b.centroids.norm()) < 1e-6
+    most = min(2 * (n // 8), 2**25 // (k * (((d + 15) // 16 * 16 + 255) // 256))) // 2
+    seen = set()
+    for before, step in zip(a.trace[1:iters], a.trace[2:iters]):   # from iteration 3 on
+        if 0 < before["changed"] <= 4 * most:
+            c = step["changed"]
+            seen.add("none" if c == 0 else "many" if c > most else "split" if step["nempty"] else "took")
+    assert seen >= reached
 
 
 # A program that asks the runtime for blocking waits, before its first GPU call, keeps the core for itself in a fit as well: of 30 steps
