@@ -1003,8 +1003,10 @@ def test_tiles_dealt_out_in_runs(skm, tiles, screen):  # noqa: F811
     n, d, k = 128 * tiles - 3, 32, 256
     g = torch.Generator().manual_seed(tiles)
     X, Y = torch.randn(n, d, generator=g), torch.randn(k, d, generator=g)
-    D = (X.double() ** 2).sum(1)[:, None] + (Y.double() ** 2).sum(1)[None] - 2.0 * X.double() @ Y.double().T
-    D, want = D.topk(2, 1, largest=False)
+    near = []
+    for x in X.double().split(1 << 16):      # (all of the largest case at once are 4.3 GB a matrix)
+        near.append(((x ** 2).sum(1)[:, None] + (Y.double() ** 2).sum(1)[None] - 2.0 * x @ Y.double().T).topk(2, 1, largest=False))
+    D, want = (torch.cat(p) for p in zip(*near))
     prev = torch.randint(0, k, (n,), generator=g, dtype=torch.int32)
     a, dist, row = skm.assign(X.cuda(), Y.cuda(), prev.cuda(), 16, skm.FitOptions(rotate=False, screen=screen, eps0=100.0))
     assert (row["listed_tiles"] > 0) == (screen == 1)
