@@ -496,7 +496,7 @@ int32_t nprobe_of(int32_t k, double frac) {
 int make_rotation_dev(Pool &pool, int32_t d, uint64_t seed, hipStream_t st, float *R_out) {
   double *Qw = nullptr, *Cw = nullptr, *Ww = nullptr;
   HIPCHK(pool.get(&Qw, (size_t)d * d + 2));
-  HIPCHK(pool.get(&Cw, std::max<size_t>((size_t)12 * 64 * d, (size_t)(2 * ((d + 63) / 64) + 1) * 64 * 64)));
+  HIPCHK(pool.get(&Cw, rotation_cwork(d)));
   HIPCHK(pool.get(&Ww, (size_t)((d + 63) / 64) * 64 * d));
   HIPCHK(launch_make_rotation(d, rng_stream(seed, STREAM_ROTATION).s, Qw, Cw, Ww, R_out, st));
   return SKM_OK;

@@ -340,8 +340,8 @@ __global__ void __launch_bounds__(256) gram_sum_kernel(const double *part, int n
 // NEAR: the panel has been factorised once, G is next to the unit matrix, and its factor's inverse is taken without the
 // eliminations (they remain for a G that is not).
 // The two 32 x 32 factorisations run in the registers of the first wavefront; the products use all four.
-constexpr int kAreaDoubles = 64 * SR + 96;               // G, then L21; later the tile of W (row stride SR, then SK)
-static_assert(PB * (PB + 1) + HB * (HB + 1) <= kAreaDoubles && PB * SK <= kAreaDoubles, "what shares the area");
+constexpr int kAreaDoubles = PB * SR + 96;               // G and L21; later the tile of W (row stride SR)
+static_assert(PB * (PB + 1) + HB * (HB + 1) <= kAreaDoubles, "what shares the area");
 constexpr size_t kFactorLds = sizeof(double) * (size_t)(kAreaDoubles + PB * SK);
 template <bool NEAR>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) factor_apply_kernel(double *Q, int d, int p0, int nr, const double *part, int nchunks,
@@ -385,66 +385,66 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
     }
   }
   if (full) {
-  __syncthreads();
-  // block products: wavefront w holds a 16 x 16 quarter, rows rq .. + 15 and columns cq .. + 15, of the 32 x 32 result
-  const int rq = 16 * (w >> 1), cq = 16 * (w & 1);
+    __syncthreads();
+    // block products: wavefront w holds a 16 x 16 quarter, rows rq .. + 15 and columns cq .. + 15, of the 32 x 32 result
+    const int rq = 16 * (w >> 1), cq = 16 * (w & 1);
 #pragma unroll 1
-  for (int o = 0; o < PB; o += HB) {
-    if (tid < 64) {   // the diagonal block at o: its factor's inverse takes its place
-      const int t = lane & 31;
-      double v[HB];
+    for (int o = 0; o < PB; o += HB) {
+      if (tid < 64) {   // the diagonal block at o: its factor's inverse takes its place
+        const int t = lane & 31;
+        double v[HB];
 #pragma unroll
-      for (int j = 0; j < HB; ++j) v[j] = s_g[o + t][o + j];
-      if (lane >= HB)
+        for (int j = 0; j < HB; ++j) v[j] = s_g[o + t][o + j];
+        if (lane >= HB)
 #pragma unroll
-        for (int j = 0; j < HB; ++j) v[j] = j == t ? 1.0 : 0.0;
-      chol_inv32(v);
-      if (lane >= HB)
+          for (int j = 0; j < HB; ++j) v[j] = j == t ? 1.0 : 0.0;
+        chol_inv32(v);
+        if (lane >= HB)
 #pragma unroll
-        for (int i = 0; i < HB; ++i) s_g[o + i][o + t] = v[i];
+          for (int i = 0; i < HB; ++i) s_g[o + i][o + t] = v[i];
+      }
+      if (o > 0) {   // (beside X22) L21 X11 into the unused upper right block
+        f64x4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < HB; k += 4) acc = mma_f64(s_l21[rq + l16][k + lk], s_g[k + lk][cq + l16], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_g[rq + lk + 4 * v][HB + cq + l16] = acc[v];
+      }
+      __syncthreads();
+      if (o > 0) break;
+      {   // L21 = G21 X11^T
+        f64x4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < HB; k += 4) acc = mma_f64(s_g[HB + rq + l16][k + lk], s_g[cq + l16][k + lk], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_l21[rq + lk + 4 * v][cq + l16] = acc[v];
+      }
+      __syncthreads();
+      {   // G22 - L21 L21^T, in place
+        f64x4 acc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = s_g[HB + rq + lk + 4 * v][HB + cq + l16];
+#pragma unroll
+        for (int k = 0; k < HB; k += 4) acc = mma_f64(-s_l21[rq + l16][k + lk], s_l21[cq + l16][k + lk], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_g[HB + rq + lk + 4 * v][HB + cq + l16] = acc[v];
+      }
+      __syncthreads();
     }
-    if (o > 0) {   // (beside X22) L21 X11 into the unused upper right block
+    {   // L^-1 = [X11 0; -X22 (L21 X11), X22]
       f64x4 acc = {0, 0, 0, 0};
 #pragma unroll
-      for (int k = 0; k < HB; k += 4) acc = mma_f64(s_l21[rq + l16][k + lk], s_g[k + lk][cq + l16], acc);
+      for (int k = 0; k < HB; k += 4) acc = mma_f64(-s_g[HB + rq + l16][HB + k + lk], s_g[k + lk][HB + cq + l16], acc);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) s_g[rq + lk + 4 * v][HB + cq + l16] = acc[v];
+      for (int v = 0; v < 4; ++v) {
+        const int row = rq + lk + 4 * v, col = cq + l16;
+        s_l[(HB + row) * SK + col] = acc[v];
+        s_l[row * SK + col] = s_g[row][col];
+        s_l[row * SK + HB + col] = 0.0;
+        s_l[(HB + row) * SK + HB + col] = s_g[HB + row][HB + col];
+      }
     }
     __syncthreads();
-    if (o > 0) break;
-    {   // L21 = G21 X11^T
-      f64x4 acc = {0, 0, 0, 0};
-#pragma unroll
-      for (int k = 0; k < HB; k += 4) acc = mma_f64(s_g[HB + rq + l16][k + lk], s_g[cq + l16][k + lk], acc);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) s_l21[rq + lk + 4 * v][cq + l16] = acc[v];
-    }
-    __syncthreads();
-    {   // G22 - L21 L21^T, in place
-      f64x4 acc;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[v] = s_g[HB + rq + lk + 4 * v][HB + cq + l16];
-#pragma unroll
-      for (int k = 0; k < HB; k += 4) acc = mma_f64(-s_l21[rq + l16][k + lk], s_l21[cq + l16][k + lk], acc);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) s_g[HB + rq + lk + 4 * v][HB + cq + l16] = acc[v];
-    }
-    __syncthreads();
-  }
-  {   // L^-1 = [X11 0; -X22 (L21 X11), X22]
-    f64x4 acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < HB; k += 4) acc = mma_f64(-s_g[HB + rq + l16][HB + k + lk], s_g[k + lk][HB + cq + l16], acc);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = rq + lk + 4 * v, col = cq + l16;
-      s_l[(HB + row) * SK + col] = acc[v];
-      s_l[row * SK + col] = s_g[row][col];
-      s_l[row * SK + HB + col] = 0.0;
-      s_l[(HB + row) * SK + HB + col] = s_g[HB + row][HB + col];
-    }
-  }
-  __syncthreads();
   }
   const bool cok = c0 + wcol < d;
 #pragma unroll
@@ -675,7 +675,8 @@ __global__ void __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per
 static_assert(3 * HB >= PB && kSmallThreads == 512, "half of the coefficients in the room of the three blocks; eight wavefronts");
 }  // namespace
 
-// Qwork: d*d + 2 doubles; Cwork: max(6 * 64 * d, (ceil(d/64) + 1) * 64 * 64) at least; Wwork: ceil(d/64) * 64 * d.
+// Qwork: d*d + 2 doubles; Cwork: rotation_cwork(d); Wwork: ceil(d/64) * 64 * d.
+static_assert(KS == 6 && PB == 64 && GC == 64, "rotation_cwork");
 hipError_t launch_make_rotation(int32_t d, uint64_t seed, double *Qwork, double *Cwork, double *Wwork, float *R_out,
                                 hipStream_t st) {
   struct Setup {   // (once per process: the kernel's LDS size)

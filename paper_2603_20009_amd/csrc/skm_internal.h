@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace skm {
 
 // four floats at any 4-byte boundary: one 16-byte load from global memory (the vector memory path takes unaligned addresses)
@@ -421,9 +423,9 @@ hipError_t launch_scatter_by_index(const void *src, const int32_t *idx, int64_t 
 // the signs of the first four dimensions of its points.  key_scratch: n bytes.
 hipError_t launch_suborder(const float *Xr, int64_t ldx, int64_t n, int32_t k, const int32_t *off, const int32_t *order_in,
                            unsigned char *key_scratch, int32_t *order_out, hipStream_t st);
+hipError_t launch_compose(const int32_t *a, const int32_t *b, int64_t n, int32_t *out, hipStream_t st);   // out[p] = a[b[p]]
 // keys hold a point id in their low 32 bits (packed (distance, point) keys; ~0 = none): every id becomes the position
 // p with perm[p] = id.  inv_scratch: n ints.
-hipError_t launch_compose(const int32_t *a, const int32_t *b, int64_t n, int32_t *out, hipStream_t st);   // out[p] = a[b[p]]
 hipError_t launch_remap_key_ids(unsigned long long *keys, int64_t m, const int32_t *perm, int64_t n, int32_t *inv_scratch,
                                 hipStream_t st);
 
@@ -620,7 +622,11 @@ hipError_t launch_pad_copy(const float *src, int64_t lds, int64_t n, int32_t d, 
 
 // ---------------------------------------------------------------- rotation matrix
 // Haar-distributed orthogonal d x d matrix (fp32) from (d, seed); workspaces in doubles:
-// Qwork d*d + 2, Cwork max(6*64*d, (ceil(d/64)+1)*64*64) at least, Wwork ceil(d/64)*64*d.
+// Qwork d*d + 2, Cwork rotation_cwork(d), Wwork ceil(d/64)*64*d.
+// (coefficients in six parts; the parts of a panel's Gram matrix and their sum take their place)
+inline size_t rotation_cwork(int32_t d) {
+  return std::max((size_t)6 * 64 * d, ((size_t)(d + 63) / 64 + 1) * 64 * 64);
+}
 hipError_t launch_make_rotation(int32_t d, uint64_t seed, double *Qwork, double *Cwork, double *Wwork, float *R_out,
                                 hipStream_t st);
 
