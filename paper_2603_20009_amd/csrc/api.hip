@@ -1160,12 +1160,19 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
                         ((c.n + 127) / 128) * (int64_t)((c.k + kListCols - 1) / kListCols) >= 1200;
   bool screen = c.colmask && nb > 0 &&
                 (c.screen_mode > 0 || (c.screen_mode == 0 && (c.last_prune_frac >= 0.50 || list_all)));
+  // A grouping that scatters and then orders the members of a cluster does so only up to a size (larger clusters keep
+  // the order in which the scatter placed them, which depends on scheduling): with such a cluster the new order, and with
+  // it the rounding of the results, would differ from run to run, so the points keep the input order.  The updates of a
+  // fit of n >= 8 k points into at most 8192 clusters order every cluster by counting, whatever its size; the same limit
+  // holds for them, which leaves the results of such fits what they were.
+  // (in a fit the sizes came back with the previous step's scalars: no copy, no wait here)
+  auto order_is_reproducible = [&]() { return c.max_cluster >= 0 && c.max_cluster <= update_sort_cap(); };
   // (not before one pruned step has run: the labels of iteration 1, assigned against the initial rows, group the points
   // far less usefully than those of iteration 2)
   const bool again = c.permuted;
   bool regroup = c.regroup_left > 0 && c.xnp_valid && c.Xr2 && have_prev && c.pruned_steps >= 1 &&
                  (again ? regroup_pays_again(c.regroup_left, c.k, c.moved, c.n) : regroup_pays(c.regroup_left, c.k)) &&
-                 c.max_cluster >= 0 && c.max_cluster <= update_sort_cap();   // (see below)
+                 order_is_reproducible();
   // In a fit the points lie by quarters of their distance first, and by label inside a quarter: a point far from its centroid
   // keeps most columns of its row tile alive, so that the three quarters near theirs are better off without it.  The distances are
   // those of the step before (to the centroids as they were): there is no pass for them.  Column tiles a row tile lists, by label
@@ -1213,7 +1220,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   if (c.group_now && !c.permuted && c.Xr2) {
     // A step on its own (no update before it left an order): the points are grouped by the incumbents they come with
     // (or were just given above), so that a row tile holds the points of one or two clusters and the first filter has
-    // columns to drop.  One read-back of the group sizes decides whether the order is reproducible (see below); with them comes
+    // columns to drop.  One read-back of the group sizes decides whether the order is reproducible; with them comes
     // whether the thresholds of a sample have a tail.
     HIPCHK(launch_threshold_sample(c.Xr, c.ldx, c.n, c.ds, c.Y, c.ds, c.prev, c.tau, (int32_t *)c.dist, c.class_ws, c.grp_cnt + c.k, c.st));
     regroup = assign_groups_always(c.k);
@@ -1231,18 +1238,10 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
       HIPCHK(hipStreamSynchronize(c.st));
       c.max_cluster = *std::max_element(sizes.begin(), sizes.end() - 1);
       by_threshold = thresholds_have_tail(c.n, sizes.back());
-      if (c.max_cluster > update_sort_cap() && !assign_groups_always(c.k) && c.screen_mode == 0) screen = false;   // (no new order below)
+      regroup = order_is_reproducible();
+      if (!regroup && !assign_groups_always(c.k) && c.screen_mode == 0) screen = false;
     }
     c.group_now = false;
-  }
-  if (regroup) {
-    // A grouping that scatters and then orders the members of a cluster does so only up to a size (larger clusters keep
-    // the order in which the scatter placed them, which depends on scheduling): with such a cluster the new order, and with
-    // it the rounding of the results, would differ from run to run, so the points keep the input order.  The updates of a
-    // fit of n >= 8 k points into at most 8192 clusters order every cluster by counting, whatever its size; the same limit
-    // holds for them, which leaves the results of such fits what they were.
-    // (the sizes came back with the previous step's scalars: no copy, no wait here)
-    regroup = c.max_cluster >= 0 && c.max_cluster <= update_sort_cap();
   }
   if (regroup) {
     if (c.regroup_left > 0 && !c.order_fresh)   // (the last update did not need the whole order)

@@ -223,9 +223,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // points follow their thresholds the last ones hold most of the pairs that live on.  One contiguous eighth for each XCD, one
   // of them worked (and its part of the hand-over list was gathered) long after the others were done: assignment of 2.5M x 384
   // to 32 768 centroids 39.4 -> 34.9 ms, the gather kernel in it 4.30 -> 1.22.  Runs of 32, 64, 128 and 256 tiles are alike
-  // (35.1, 35.5, 34.9, 35.2); fewer than 1024 tiles go in shorter ones.  What does not fill a round is split evenly as it is.
+  // (35.1, 35.5, 34.9, 35.2).  So that there are 16 rounds (from 1024 tiles on), fewer than 16 384 tiles go in shorter ones, 64 tiles from 8192 on,
+  // 32 from 4096, 16 from 2048 and 8 below (the last two not measured against others).  What does not fill a round is split evenly.
   const int xcd = blockIdx.x & 7;
-  const int run = min(max(31 - __builtin_clz(max(ntiles, 1)) - 7, 3), 7);   // log2 of the tiles in a run: at least 16 rounds or runs of 8
+  const int run = min(max(31 - __builtin_clz(max(ntiles, 1)) - 7, 3), 7);   // log2 of the tiles in a run
   const int rounds = ntiles >> (run + 3), rest = ntiles - (rounds << (run + 3));
   const int in_rounds = rounds << run;   // tiles of this XCD in whole rounds
   const int tbase = rest >> 3, trem = rest & 7;
