@@ -53,7 +53,10 @@ def test_host_rules_agree_with_the_oracle(skm, orc):
         for dp in range(16, d + 1, 16):
             for f in (0.5, 0.949, 0.96, 0.971, 0.999):
                 assert skm.dprime_adjust(d, dp, f) == orc.dprime_adjust(d, dp, f)
-    for seed, n, k in ((42, 20_000, 100), (1, 1000, 1000), (7, 10**6, 1024), (2**63 + 5, 333, 17)):
+    # (drawn from a table of the rows moved so far where k < n / 8: on both sides of that, at its smallest sizes, nearly half full,
+    # and with many rows that are met again)
+    for seed, n, k in ((42, 20_000, 100), (1, 1000, 1000), (7, 10**6, 1024), (2**63 + 5, 333, 17), (3, 9, 1), (3, 17, 2), (4, 65, 8),
+                       (5, 1000, 124), (5, 1000, 125), (6, 32_769, 4096), (8, 100_000, 3000), (9, 10**6, 65_536), (10, 10**6, 124_999)):
         assert skm.sample_rows(seed, n, k) == orc.sample_rows(seed, n, k).tolist()
     # hierarchical fit: number of meso-clusters and the shares of k
     for k in (1, 2, 3, 10, 99, 1024, 16384, 32768, 2**24):
