@@ -605,6 +605,7 @@ struct Ctx {
   // low-precision first filter (screen.hip): mode as params->screen; buffers for one chunk of rows
   int32_t screen_mode = 0;
   double last_prune_frac = -1.0;     // of the previous pruned step of this context (-1: none yet)
+  double last_listed = 1.0;          // share of the 128 x 128 tiles that it worked on (1 where it listed none)
   uint32_t *colmask = nullptr;
   float *scr_arow = nullptr, *scr_ycol = nullptr;
   uint32_t *Xh = nullptr, *Yh = nullptr;   // the hi halves of Xs, Ys as planes of their own
@@ -1120,14 +1121,27 @@ int step_exact(Ctx &c, StageTimer &tm, StepStats &ss) {
 }
 
 // Whether the points of a fit are regrouped (Ctx) with `left` steps to go, this one included.  The rewrite costs about as much as
-// three threshold passes and saves a part of every later step that grows with the centroids: 614 400 x 1024, k = 4000, four
-// iterations 52.6 -> 45.2 ms, 1M x 768, k = 2048 43.9 -> 37.4; with k = 1024 three steps do not pay for it (31.4 without).
-inline bool regroup_pays(int32_t left, int32_t k) { return left >= 4 || (left >= 2 && (int64_t)left * k >= 4096); }
-// ... and again, once the labels have moved on.  Ten iterations with one regrouping -> with a second one: 1M x 1536, k = 4096, a
-// tenth of the labels changed 183.9 -> 176.4 ms, 614 400 x 1024, k = 4000 89.2 -> 83.9, 1M x 768, k = 2048, a fifth changed 65.6 -> 63.8,
-// where 7 % had changed 43.4 -> 44.3 (left x k x share: 3300, 5000, 3000 and 1100).
-inline bool regroup_pays_again(int32_t left, int32_t k, int64_t moved, int64_t n) {
-  return (double)left * k * (double)moved >= 2048.0 * (double)n;
+// three threshold passes and saves a part of every later step.  With fewer than four steps there have to be many centroids, a quarter
+// of a row tile's worth of points to each, and work; and unless there are very many centroids the step before has to have cut a
+// fifth to 85 % of the pairs (`cut`): with less the next one multiplies every column whatever the order, with more its tiles are
+// few.  Fits of four iterations (left = 3) without -> with it: 1M x 768, k = 2048, cut 0.54 38.3 -> 32.8 ms, 200 000 x 384 5.5 -> 4.7, 1M x
+// 1536, k = 4096, cut 0.995 77.0 -> 70.1, 1M x 128, k = 3000, cut 0.97 11.3 -> 10.4; beyond the lines 1M x 768, k = 2048, cut 0.95 29.6 -> 30.9 and
+// k = 512 21.8 -> 23.0, 1M x 128, k = 1366, cut 0.04 10.7 -> 10.9, 50 000 x 768, k = 3000 (17 points to a centroid) 3.16 -> 3.35, 100 000 x 64,
+// k = 2048 1.52 -> 1.60.
+inline bool regroup_pays(int32_t left, int64_t n, int32_t ds, int32_t k) {
+  return left >= 4 || (left >= 2 && (int64_t)left * k >= 4096 && n >= 32 * (int64_t)k && (double)n * ds * k >= 1e11);
+}
+inline bool regroup_pays_behind(int32_t left, int32_t k, double cut) {
+  return left >= 4 || (int64_t)left * k >= 8192 || (cut >= 0.20 && cut < 0.85);
+}
+// ... and again, once a twentieth of the labels has changed since, where the last step left enough to save: `listed` is the share of
+// the tiles that it worked on (1: all).  Without a second regrouping -> with, of 432 fits of 6, 10 and 20 iterations (1M x 128 to 1536,
+// 400 000 x 1024, 200 000 x 384, 50 000 x 768, 100 000 x 64; 256 to 4096 clusters, mixtures of 1024 to 16 384): 1M x 1536, k = 4096, cut
+// 0.83 184 -> 176 ms; 20 iterations of 400 000 x 1024, k = 4096, cut 0.78 12 % faster, 1M x 768, k = 3000, cut 0.52 8, 200 000 x 384, k = 2048, cut
+// 0.25 11, cut 0.89 with 61 % listed 4.  Beyond the lines 20 iterations of 1M x 768, k = 3000, cut 0.999 are 5 % slower, of 1M x 128, k = 4096,
+// cut 0.998 4, of 1M x 1536, k = 4096, a quarter of the tiles listed, nine steps to go, 3, of 1M x 128, k = 512, cut 0.03, three times regrouped, 7.
+inline bool regroup_pays_again(int32_t left, int64_t n, int32_t k, int64_t moved, double cut, double listed) {
+  return 20 * moved >= n && cut >= 0.20 && cut < 0.98 && (double)left * k * (double)moved * listed >= 1500.0 * (double)n;
 }
 // Iterations >= 2 of Algorithm 1: initial threshold, progressive-pruning GEMM, gather kernel for the
 // pairs of sparse tiles, argmin.  On entry c.prev holds the incumbents (c.assign is overwritten);
@@ -1184,7 +1198,8 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   // far less usefully than those of iteration 2)
   const bool again = c.permuted;
   bool regroup = c.regroup_left > 0 && c.xnp_valid && c.Xr2 && have_prev && c.pruned_steps >= 1 &&
-                 (again ? regroup_pays_again(c.regroup_left, c.k, c.moved, c.n) : regroup_pays(c.regroup_left, c.k)) &&
+                 (again ? regroup_pays_again(c.regroup_left, c.n, c.k, c.moved, c.last_prune_frac, c.last_listed)
+                        : regroup_pays(c.regroup_left, c.n, c.ds, c.k) && regroup_pays_behind(c.regroup_left, c.k, c.last_prune_frac)) &&
                  order_is_reproducible();
   // In a fit the points lie by quarters of their distance first, and by label inside a quarter: a point far from its centroid
   // keeps most columns of its row tile alive, so that the three quarters near theirs are better off without it.  The distances are
@@ -1415,6 +1430,7 @@ int step_pruned(Ctx &c, StageTimer &tm, int32_t dprime, double eps0, bool have_p
   ss.screen_dims = (int64_t)scal_h[SC_SCREEN_DIMS];
   ss.listed_tiles = (int64_t)scal_h[SC_LISTED_TILES];
   c.last_prune_frac = c.k > 1 ? 1.0 - (double)ss.survivors / ((double)c.n * (double)(c.k - 1)) : -1.0;
+  c.last_listed = ss.listed_tiles > 0 ? (double)ss.listed_tiles / ((double)((c.n + 127) / 128) * (double)((c.k + 127) / 128)) : 1.0;
   ++c.pruned_steps;
   if (c.block_stats)
     for (int m = 0; m < std::min<int>(nb, SKM_MAX_BLOCKS); ++m) ss.enter[m] = (int64_t)scal_h[SC_ENTER + (size_t)m];
@@ -2016,7 +2032,7 @@ int fit_impl(const float *X, int64_t n, int32_t d, int32_t k, int32_t iters, uin
   // Regrouping of the points by cluster (Ctx): not for rows that the batched table writes of the threshold pass do not
   // cover; it happens in the third step at the earliest.  Its room is the last that the call takes, and given back where it cannot be
   // had in full: a fit may do without, and its points stay as they are.
-  bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && regroup_pays(iters - 2 + (p.final_assign ? 1 : 0), k);
+  bool may_regroup = c.ds <= 2048 && n < ((int64_t)1 << 31) && regroup_pays(iters - 2 + (p.final_assign ? 1 : 0), n, c.ds, k);
   if (may_regroup) {
     const Pool::Mark before = c.pool.taken();
     auto room = [&]() -> int {
