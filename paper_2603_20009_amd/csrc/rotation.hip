@@ -303,8 +303,8 @@ __device__ __forceinline__ void chol_inv32(double (&v)[HB]) {
 // The Gram matrix of a panel that has been factorised once is next to the unit matrix, and the inverse of its factor needs no
 // eliminations: I + E = L L^T with L = I + low(E) + O(|E|^2), low(E) = the part of E below the diagonal and half of its
 // diagonal, so L^-1 W = W - low(E) W + O(|E|^2).  With no element of E beyond kNearUnit the norm of E is at most 64 of these,
-// and its square below the rounding of the unit matrix; an element that is larger, in one panel of ten of the last 64 rows,
-// makes the panel take the eliminations.  Returns the element of -low(E) for element (r, c) of the Gram matrix; far: whether
+// and its square below the rounding of the unit matrix; an element that is larger, in three to six of a
+// hundred last panels of 64 rows (fp64 model of the step, 150 to 400 seeds each of d = 64, 128, 192), makes the panel take the eliminations.  Returns the element of -low(E) for element (r, c) of the Gram matrix; far: whether
 // that is so.
 constexpr double kNearUnit = 1.0 / (1ull << 33);
 __device__ inline double minus_low(double g, int r, int c, bool &far) {
@@ -477,7 +477,7 @@ static_assert(PB == 64 && HB * 2 == PB, "factor_apply_kernel: two blocks of 32")
 // The whole chain for up to 128 rows in one workgroup, the matrix in its LDS: two panels of 64 rows, each cleared of the
 // finished rows and factorised twice, as above.  The chain of kernels waits for a launch and for its loads in each of its
 // twelve kernels; here a step waits for a barrier, and what bounds it are the fp64 products on one CU (3.4 us for 64 x 64 x 128)
-// and the two eliminations of a panel (4.2 us each).  The generator at d = 64 41 -> 30 us, at d = 128 113 -> 76.
+// and the two eliminations of a panel (4.2 us each).  The generator at d = 64 41 -> 30 us, at d = 128 113 -> 77.
 constexpr int kSmallDim = 2 * PB, kSmallThreads = 512;
 constexpr int SW = 130, SB = 34;   // LDS row strides (doubles) of the matrix and of the blocks of the factor
 constexpr size_t kSmallLds = sizeof(double) * (size_t)(kSmallDim * SW + 3 * HB * SB);
@@ -706,9 +706,10 @@ hipError_t launch_make_rotation(int32_t d, uint64_t seed, double *Qwork, double 
     // has more than twice as many dimensions as rows its condition is at most 6, so one projection and one Cholesky-QR leave
     // errors near fp64 rounding.  Behind that it gets up to 10^5, and both steps are done twice, the second projection behind
     // the first factor: what the factor's inverse has blown up of the first one's rounding goes with it.  The largest |Q Q^T - I|
-    // before rounding, median and maximum of 60 matrices, and the time: d = 200 2e-15, 2e-15 and 208 us, 384 2e-15, 3e-15 and 301,
-    // 1536 4e-15, 5e-15 and 1433 (with 128 rows a workgroup of the update); with both projections before both factorisations, in the last 256 rows, d = 200 1e-15, 9e-14 and
-    // 299 us, 384 5e-15, 8e-14 and 422, 1536 5e-15, 2e-13 and 1593; in this order for the last 256 rows the same errors, 248, 366 and 1527.
+    // before rounding, median and maximum of 60 matrices, and the time of the generator, all three forms with 128 rows a workgroup
+    // of the update: this one d = 200 2e-15, 2e-15 and 208 us, 384 2e-15, 3e-15 and 301, 1536 4e-15, 5e-15 and 1433; with both projections
+    // before both factorisations, in the last 256 rows, d = 200 1e-15, 9e-14 and 299 us, 384 5e-15, 8e-14 and 422, 1536 5e-15, 2e-13 and
+    // 1593; in this order for the last 256 rows the same errors, 248, 366 and 1527.
     const int passes = d - p0 <= 2 * PB ? 2 : 1;
     const int njs = p0 > 0 ? (p0 + JR - 1) / JR : 0;
     const int nchunks = (d + GC - 1) / GC;
